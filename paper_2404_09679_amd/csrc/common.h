@@ -108,10 +108,9 @@ struct PoolArgs {
   const int32_t* offsets;
   const float* dense;
   void* x;
-  bf16_t* xt;             // optional transposed copy [ldx + 8, ldt] (bf16 activations only)
   int32_t* lookup_sample; // optional [nnz]: global sample index of every lookup (sort payload)
   int32_t F, D, num_dense, ldx, B, s0, ns;
-  int64_t R, ldt;
+  int64_t R;
   int32_t table_bf16, x_bf16;
   int32_t mean_pool;      // divide every bag's sum by its number of lookups
 };
@@ -128,19 +127,15 @@ enum Epilogue { EPI_BIAS_RELU = 0, EPI_RELU_MASK = 1, EPI_PLAIN = 2 };
 // C[m, n] = sum_k A(m, k) * B(n, k).
 // fp32 path: a_kc: A(m,k) = A[m*lda + k], else A[k*lda + m]; b_kc likewise for B; with
 // `grouped`, group g (blockIdx.z) contracts over rows [tab.start[k0+g], +tab.len[k0+g]) of A
-// and B (both not *_kc).
-// bf16 path: both operands have the contraction index contiguous (A[m*lda + k], B[n*ldb + k]);
-// with `grouped`, group g contracts over k in [tab.start[k0+g], +tab.len[k0+g]).
-// Grouped launches write C + (k0+g)*group_stride.  CT, when set, receives the bf16 result
-// transposed: CT[n*ldct + ct_col0 + m].
+// and B (both not *_kc) and writes C + (k0+g)*group_stride.
+// bf16 path: A(m,k) = A[m*lda + k]; B(n,k) = B[n*ldb + k] (b_kc) or B[k*ldb + n]; not grouped.
 struct GemmArgs {
   const void* A;
   const void* B;
   void* C;
-  bf16_t* CT;
   const float* bias;   // EPI_BIAS_RELU: [N]
   const void* mask;    // EPI_RELU_MASK: activations [M, ldmask], C = acc where mask > 0 else 0
-  int64_t lda, ldb, ldc, ldct, ct_col0, ldmask;
+  int64_t lda, ldb, ldc, ldmask;
   int32_t M, N, K;
   int32_t a_kc, b_kc, epi;
   int32_t bf16_in;     // operands (and mask) are bf16, else fp32
@@ -150,31 +145,38 @@ struct GemmArgs {
 };
 hipError_t launch_gemm(const GemmArgs& a, const ShardTab& tab, hipStream_t s);
 
-// Weight gradients of all hidden layers with the server's aggregation and dense update applied
-// on the spot: for layer l the tile of [dW_l ; db_l] = sum_k w_k * ([act_l ; 1]^T dH_{l+1}) over
-// the samples of shard k, accumulated shard after shard in registers, then Adagrad on the matching
-// tile of the flat parameters (W_l with b_l right behind it) and the bf16 copy of W_l.  Neither
-// the per-shard nor the aggregated gradient goes to memory.
-struct KSegments {        // sample ranges with one aggregation weight each (shards; neighbours of
-  int32_t n;              // equal weight merged), in sample order
-  int32_t ks[ANTDT_MAX_SHARDS], ke[ANTDT_MAX_SHARDS];
+// Sample ranges (shards; neighbours of equal weight merged) in sample order, with their aggregation
+// weights, and the partial sums that the loss kernel left for them.
+struct KSegments {
+  int32_t n;
+  int32_t ks[ANTDT_MAX_SHARDS], ke[ANTDT_MAX_SHARDS];   // samples [ks, ke)
+  int32_t ts[ANTDT_MAX_SHARDS], te[ANTDT_MAX_SHARDS];   // tiles of the loss kernel [ts, te)
   float w[ANTDT_MAX_SHARDS];
 };
-struct WgradUpdateArgs {
-  int32_t n_layers;
-  const bf16_t* A[ANTDT_MAX_LAYERS];   // transposed activations [M (with the ones row), ld]
-  const bf16_t* B[ANTDT_MAX_LAYERS];   // transposed pre-activation gradients [N, ld]
-  int32_t M[ANTDT_MAX_LAYERS], N[ANTDT_MAX_LAYERS];
-  int64_t w_off[ANTDT_MAX_LAYERS];     // W_l inside the flat parameters, [M - 1, N] then the bias [N]
+// Weight gradients of all layers of a bf16 model in one launch (see wgrad_kernel): per range written to
+// the shards' flat gradients, or aggregated and applied (Adagrad) on the spot, in which case neither
+// the per-shard nor the aggregated gradient goes to memory.
+struct WgradArgs {
+  int32_t n_layers;                    // hidden layers
+  const bf16_t* A[ANTDT_MAX_LAYERS];   // activations [samples, lda], M columns
+  const bf16_t* B[ANTDT_MAX_LAYERS];   // pre-activation gradients [samples, ldb], N columns
+  int32_t M[ANTDT_MAX_LAYERS], N[ANTDT_MAX_LAYERS], lda[ANTDT_MAX_LAYERS], ldb[ANTDT_MAX_LAYERS];
+  int64_t w_off[ANTDT_MAX_LAYERS];     // W_l inside the flat parameters, [M, N] then the bias [N]
   bf16_t* wb[ANTDT_MAX_LAYERS];        // bf16 copy of W_l, [rows padded, N]
   int32_t tile_base[ANTDT_MAX_LAYERS + 1];
   int32_t tiles_n[ANTDT_MAX_LAYERS];
-  int64_t ld;
+  // last layer (one output): the loss kernel's sums over its tiles of samples
+  const float* part;                   // [tiles, ldpart] sum of dz * h per column; column `width`: sum of dz
+  int64_t ldpart, last_off;            // offset of the last layer in the flat parameters (bias behind the weights)
+  int32_t width;
   float* p;
   float* state;
   float lr, eps;
+  float* grads;                        // per-shard flat gradients [K, stride] (when storing), ranges = shards k0 ..
+  int64_t stride;
+  int32_t k0;
 };
-hipError_t launch_wgrad_update(const WgradUpdateArgs& a, const KSegments& seg, hipStream_t s);
+hipError_t launch_wgrad(const WgradArgs& a, const KSegments& seg, bool store, hipStream_t s);
 
 struct CastArgs {  // fp32 [rows, cols] -> bf16 [rows_pad, cols], extra rows zero
   const float* src;
@@ -182,23 +184,6 @@ struct CastArgs {  // fp32 [rows, cols] -> bf16 [rows_pad, cols], extra rows zer
   int64_t n_src, n_dst;
 };
 hipError_t launch_cast_bf16(const CastArgs& a, hipStream_t s);
-
-struct TransposeArgs {  // dst[c*ld_dst + r] = src[r*ld_src + c] for up to 8 bf16 matrices
-  int32_t n;
-  const bf16_t* src[ANTDT_MAX_LAYERS];
-  bf16_t* dst[ANTDT_MAX_LAYERS];
-  int32_t rows[ANTDT_MAX_LAYERS], cols[ANTDT_MAX_LAYERS];
-  int64_t ld_src[ANTDT_MAX_LAYERS], ld_dst[ANTDT_MAX_LAYERS];
-  int32_t tile_base[ANTDT_MAX_LAYERS + 1];
-};
-hipError_t launch_transpose_bf16(const TransposeArgs& a, hipStream_t s);
-
-struct OnesRowArgs {    // row `row` of a bf16 matrix [.., ld] = 1, the `zero_rows` rows after it = 0
-  bf16_t* base;
-  int64_t ld;
-  int32_t row, zero_rows;
-};
-hipError_t launch_ones_row(const OnesRowArgs& a, hipStream_t s);
 
 // ----------------------------------------------------------------- head.hip
 struct HeadArgs {
@@ -210,12 +195,32 @@ struct HeadArgs {
   float* loss_s;        // [B] per-sample loss
   float* dz;            // [B] d(mean shard loss)/dz
   void* dh;             // [B, lddh] gradient w.r.t. h (masked by h > 0 when `relu`), or fp32 dX
-  bf16_t* dht;          // optional transposed bf16 copy [dh_cols, ldt]
-  int64_t ldh, lddh, ldt;
+  int64_t ldh, lddh;
   int32_t width, dh_cols, relu, bf16_h, bf16_dh;
   int32_t k_begin, k_end;
+  // bf16 models: the sums over the samples are formed along the way, per tile of samples of one shard
+  float* part;          // [tiles, ldpart] sum of dz * h per column; column `width`: sum of dz, `width` + 1: of the losses
+  int64_t ldpart;
+  int32_t* done;        // blocks that have finished (0 between launches)
+  float* loss_k;        // workspace [K]
+  float* loss_out;      // caller's buffer or NULL; element (k - k_begin)
 };
 hipError_t launch_head(const HeadArgs& a, const ShardTab& tab, hipStream_t s);
+
+// Tiles of the loss kernel: HEAD_TILE consecutive samples of one shard.  tile_base[k] = first tile of shard k.
+constexpr int HEAD_TILE = 16;
+struct HeadTiles {
+  int32_t base[ANTDT_MAX_SHARDS + 1];
+};
+inline HeadTiles head_tiles(const ShardTab& tab) {
+  HeadTiles t;
+  t.base[0] = 0;
+  for (int k = 0; k < ANTDT_MAX_SHARDS; ++k)
+    t.base[k + 1] = t.base[k] + (k < tab.K ? (tab.len[k] + HEAD_TILE - 1) / HEAD_TILE : 0);
+  return t;
+}
+hipError_t launch_head_tiles(const HeadArgs& a, const ShardTab& tab, hipStream_t s);
+hipError_t launch_zero_words(int32_t* p, int n, hipStream_t s);
 
 struct HeadReduceArgs {
   const void* h;
@@ -224,10 +229,8 @@ struct HeadReduceArgs {
   float* grads;         // [K, P] per-shard flat dense gradients
   float* loss_k;        // workspace [K]
   float* loss_out;      // caller's buffer or NULL; element (k - k_begin)
-  const bf16_t* ht;     // optional transposed activation [width, ldt]: selects the coalesced kernel
-  int64_t ldh, ldt, P, w_off, b_off;
+  int64_t ldh, P, w_off, b_off;
   int32_t width, bf16_h, k_begin, k_end;
-  int32_t part;         // transposed-activation kernel only: 0 everything, 1 the weight sums, 2 bias sum and loss
 };
 hipError_t launch_head_reduce(const HeadReduceArgs& a, const ShardTab& tab, hipStream_t s);
 
@@ -310,10 +313,9 @@ struct DenseAggArgs {
 hipError_t launch_dense_agg(const DenseAggArgs& a, const ShardTab& tab, hipStream_t s);
 
 // Dense Adagrad on the flat MLP parameters with the gradient aggregated on the fly
-// (g = sum_k w_k grads[k]).  Hidden-layer weight matrices are walked in 64x64 tiles so that
-// both bf16 operand copies (W as [in,out] and W^T as [out,in_pad]) are refreshed with
-// coalesced stores in the same pass; everything else (biases, the last layer) goes through
-// plain ranges.
+// (g = sum_k w_k grads[k]).  Hidden-layer weight matrices of bf16 models are walked in 64x64 tiles
+// and their bf16 operand copies refreshed in the same pass; everything else (biases, the last
+// layer, fp32 models) goes through plain ranges.
 struct DenseAdagradArgs {
   float* p;
   float* state;
@@ -322,9 +324,8 @@ struct DenseAdagradArgs {
   float lr, eps;
   int32_t n_mat;
   int64_t w_off[ANTDT_MAX_LAYERS];
-  int32_t rows[ANTDT_MAX_LAYERS], cols[ANTDT_MAX_LAYERS], rows_pad[ANTDT_MAX_LAYERS];
+  int32_t rows[ANTDT_MAX_LAYERS], cols[ANTDT_MAX_LAYERS];
   bf16_t* wb[ANTDT_MAX_LAYERS];
-  bf16_t* wbt[ANTDT_MAX_LAYERS];
   int32_t tile_base[ANTDT_MAX_LAYERS + 1];
   int32_t n_rng;
   int64_t rng_off[ANTDT_MAX_LAYERS + 1], rng_len[ANTDT_MAX_LAYERS + 1];

@@ -114,13 +114,12 @@ struct antdt_ctx {
   char* dh[ANTDT_MAX_LAYERS] = {};
   float *z = nullptr, *loss_s = nullptr, *dz = nullptr, *loss_k = nullptr, *dx = nullptr;
   float *shard_grads = nullptr, *g_dense = nullptr, *sample_w = nullptr, *G = nullptr;
-  bf16_t* wb[ANTDT_MAX_LAYERS] = {};     // bf16 W_l as [in (padded), out]: operand of the data gradient
+  bf16_t* wb[ANTDT_MAX_LAYERS] = {};     // bf16 W_l as [in (padded), out]: operand of the forward product and the data gradient
   bf16_t* wb0_alt = nullptr;             // second buffer for W_0: the fused dense update writes the new copy there
                                          // while the input-gradient product may still read the old one
-  bf16_t* wbt[ANTDT_MAX_LAYERS] = {};    // bf16 W_l^T as [out, in (padded)]: operand of the forward product
-  bf16_t* act_t[ANTDT_MAX_LAYERS] = {};  // transposed activations [width + 8, ldt], row `width` = ones
-  bf16_t* dh_t[ANTDT_MAX_LAYERS] = {};   // transposed pre-activation gradients [width, ldt]
-  int64_t ldt = 0;
+  float* head_part = nullptr;            // loss kernel's sums per tile of samples [tiles, ldpart]
+  int64_t ldpart = 0;
+  int32_t* head_done = nullptr;          // its count of finished blocks (0 between launches)
   int32_t* lookup_sample = nullptr;
   int32_t *key[2] = {}, *pay[2] = {}, *tile_heads = nullptr, *ubase = nullptr, *uniq = nullptr;
   int32_t *segoff = nullptr, *ufield = nullptr, *segabs = nullptr, *counters = nullptr, *long_seg = nullptr, *items = nullptr, *qcnt = nullptr, *xcd_tab = nullptr;
@@ -150,14 +149,12 @@ struct antdt_ctx {
   bool included[ANTDT_MAX_SHARDS] = {};
   double shard_scale[ANTDT_MAX_SHARDS];  // per-worker factor on the aggregation weight (1 unless set)
   bool weights_dirty = false;            // the factors changed after the weights were last formed
-  bool head_weights_deferred = false;    // the last layer's weight sums of this worker step are still to be launched
   // Weight gradients formed inside the dense update (bf16 products with a weight-gradient stream):
   // the worker step only leaves their operands behind and an event (ev_dh[0]) that says they are
   // complete; per-shard gradients are computed when a view asks for them.
   bool eager_wgrad = false;              // option: the worker step computes the per-shard weight gradients itself
   bool wgrad_deferred = false;           // this worker step left the weight gradients to apply_update / the views
   bool shard_grads_done = false;         // the per-shard dense gradients of this worker step are (being) written
-  HeadReduceArgs head_reduce_args;
   int sorted_buf = 0;
   // side stream on which the coalescing structure of a batch is built while the MLP runs
   hipStream_t side = nullptr;
@@ -232,14 +229,10 @@ static size_t carve(antdt_ctx* c, char* base) {
       const int64_t rows = l == 0 ? c->ldx : c->width[l];
       c->wb[l] = (bf16_t*)take((size_t)rows * c->width[l + 1] * 2);
       if (l == 0) c->wb0_alt = (bf16_t*)take((size_t)rows * c->width[l + 1] * 2);
-      c->wbt[l] = (bf16_t*)take((size_t)rows * c->width[l + 1] * 2);
     }
-    for (int l = 0; l < c->L; ++l) {
-      const int64_t rows = (l == 0 ? c->ldx : c->width[l]) + 8;
-      c->act_t[l] = (bf16_t*)take((size_t)rows * c->ldt * 2);
-      if (l > 0) c->dh_t[l] = (bf16_t*)take((size_t)c->width[l] * c->ldt * 2);
-    }
+    c->head_part = (float*)take((size_t)(Bm / HEAD_TILE + K) * c->ldpart * 4);
   }
+  c->head_done = (int32_t*)take(4);
   c->lookup_sample = (int32_t*)take((size_t)N * 4);
   for (int i = 0; i < 2; ++i) {
     c->key[i] = (int32_t*)take((size_t)N * 4);
@@ -349,7 +342,7 @@ int antdt_create(const antdt_model* model, antdt_ctx** out) {
   c->ldx = (c->in0 + 7) / 8 * 8;
   c->act_bf16 = m.gemm_dtype == ANTDT_BF16;
   c->act_size = c->act_bf16 ? 2 : 4;
-  c->ldt = (m.max_batch + 63) / 64 * 64;
+  c->ldpart = (m.layer_sizes[c->L - 1] + 2 + 3) / 4 * 4;
   int64_t off = 0;
   for (int l = 0; l <= c->L; ++l) c->width[l] = m.layer_sizes[l];
   for (int l = 0; l < c->L; ++l) {
@@ -404,24 +397,9 @@ int antdt_workspace_bytes(const antdt_ctx* ctx, size_t* bytes) {
   return ANTDT_OK;
 }
 
-// wbt[l] = transpose of wb[l] for every hidden layer, one launch.
-static int transpose_weights(antdt_ctx* c, hipStream_t s) {
-  if (!c->act_bf16 || c->L < 2) return ANTDT_OK;
-  TransposeArgs t;
-  memset(&t, 0, sizeof(t));
-  for (int l = 0; l + 1 < c->L; ++l) {
-    const int rows = l == 0 ? c->ldx : c->width[l], cols = c->width[l + 1];
-    t.src[l] = c->wb[l]; t.dst[l] = c->wbt[l];
-    t.rows[l] = rows; t.cols[l] = cols; t.ld_src[l] = cols; t.ld_dst[l] = rows;
-    t.tile_base[l + 1] = t.tile_base[l] + ((rows + 63) / 64) * ((cols + 63) / 64);
-  }
-  t.n = c->L - 1;
-  ProfScope ps(prof_of(c), KID_TRANSPOSE, s);
-  HIP_TRY(c, launch_transpose_bf16(t, s));
-  return ANTDT_OK;
-}
-
-static int refresh_bf16_weights(antdt_ctx* c, hipStream_t s) {
+// What a fresh workspace has to hold before the first iteration.
+static int init_workspace(antdt_ctx* c, hipStream_t s) {
+  HIP_TRY(c, launch_zero_words(c->head_done, 1, s));
   if (!c->act_bf16) return ANTDT_OK;
   for (int l = 0; l + 1 < c->L; ++l) {
     CastArgs a;
@@ -435,17 +413,7 @@ static int refresh_bf16_weights(antdt_ctx* c, hipStream_t s) {
       HIP_TRY(c, launch_cast_bf16(a, s));
     }
   }
-  // constant rows of the transposed activations: a row of ones below the last feature row
-  // (it turns the bias gradient into one more row of the weight-gradient product), zeros after
-  for (int l = 0; l < c->L; ++l) {
-    OnesRowArgs o;
-    o.base = c->act_t[l];
-    o.ld = c->ldt;
-    o.row = c->width[l];
-    o.zero_rows = (l == 0 ? c->ldx : c->width[l]) + 8 - c->width[l] - 1;
-    HIP_TRY(c, launch_ones_row(o, s));
-  }
-  return transpose_weights(c, s);
+  return ANTDT_OK;
 }
 
 int antdt_bind(antdt_ctx* c, void* tables, float* table_state, float* mlp_params, float* mlp_state,
@@ -474,7 +442,7 @@ int antdt_bind(antdt_ctx* c, void* tables, float* table_state, float* mlp_params
     for (int l = 0; l <= c->L; ++l) HIP_TRY(c, hipEventCreateWithFlags(&c->ev_dh[l], SYNC_EVENT_FLAGS));
   }
   c->stage = ST_BOUND;
-  return refresh_bf16_weights(c, (hipStream_t)stream);
+  return init_workspace(c, (hipStream_t)stream);
 }
 
 int antdt_bind_static(antdt_ctx* c, void* tables, float* table_state, float* mlp_params, float* mlp_state,
@@ -530,7 +498,7 @@ int antdt_bind_static(antdt_ctx* c, void* tables, float* table_state, float* mlp
   carve(c, (char*)base);
   c->stage = ST_BOUND;
   c->have_shards = false;
-  return refresh_bf16_weights(c, (hipStream_t)stream);
+  return init_workspace(c, (hipStream_t)stream);
 }
 
 // Tile decomposition of per-field lookup ranges.
@@ -719,31 +687,53 @@ static int build_coalescing(antdt_ctx* c, const int32_t* ids, const int32_t* pay
   return ANTDT_OK;
 }
 
-// Per-shard weight gradient of hidden layer l for shards [k0, k1), one grouped product on `ws`.
-static int shard_weight_gradient(antdt_ctx* c, int l, int k0, int k1, hipStream_t ws) {
+// Per-shard weight gradient of hidden layer l of an fp32 model for shards [k0, k1), one grouped product on `ws`.
+static int shard_weight_gradient_f32(antdt_ctx* c, int l, int k0, int k1, hipStream_t ws) {
   Profiler* pr = prof_of(c);
   GemmArgs g;
   memset(&g, 0, sizeof(g));
-  if (c->act_bf16) {
-    // [dW_l ; db_l][k] = [act_l ; 1]^T dh_{l+1} over the shard's samples: both operands are the
-    // transposed copies (sample index contiguous); the ones row yields the bias gradient,
-    // which sits right behind W_l in the flat layout.
-    g.A = c->act_t[l]; g.lda = c->ldt;
-    g.B = c->dh_t[l + 1]; g.ldb = c->ldt;
-    g.M = c->width[l] + 1;
-    g.bf16_in = 1;
-  } else {  // dW_l[k] = act_l^T dh_{l+1} over the shard's samples
-    g.A = l == 0 ? c->x : c->h[l]; g.lda = l == 0 ? c->ldx : c->width[l]; g.a_kc = 0;
-    g.B = c->dh[l + 1]; g.ldb = c->width[l + 1]; g.b_kc = 0;
-    g.M = c->width[l];
-    g.bf16_in = 0;
-  }
+  // dW_l[k] = act_l^T dh_{l+1} over the shard's samples
+  g.A = l == 0 ? c->x : c->h[l]; g.lda = l == 0 ? c->ldx : c->width[l]; g.a_kc = 0;
+  g.B = c->dh[l + 1]; g.ldb = c->width[l + 1]; g.b_kc = 0;
+  g.M = c->width[l];
   g.C = c->shard_grads + c->w_off[l]; g.ldc = c->width[l + 1];
   g.N = c->width[l + 1]; g.K = 0;
-  g.epi = EPI_PLAIN; g.bf16_out = 0;
+  g.epi = EPI_PLAIN;
   g.grouped = 1; g.k0 = k0; g.groups = k1 - k0; g.group_stride = c->Pstride;
   ProfScope ps(pr, KID_GEMM_WGRAD, ws);
   HIP_TRY(c, launch_gemm(g, c->tab, ws));
+  return ANTDT_OK;
+}
+
+static void fill_wgrad_args(antdt_ctx* c, WgradArgs& u) {
+  memset(&u, 0, sizeof(u));
+  u.n_layers = c->L - 1;
+  for (int l = 0; l + 1 < c->L; ++l) {
+    u.A[l] = (const bf16_t*)(l == 0 ? c->x : c->h[l]); u.lda[l] = l == 0 ? c->ldx : c->width[l];
+    u.B[l] = (const bf16_t*)c->dh[l + 1]; u.ldb[l] = c->width[l + 1];
+    u.M[l] = c->width[l]; u.N[l] = c->width[l + 1];
+    u.w_off[l] = c->w_off[l]; u.wb[l] = l == 0 ? c->wb0_alt : c->wb[l];
+  }
+  u.part = c->head_part; u.ldpart = c->ldpart; u.width = c->width[c->L - 1]; u.last_off = c->w_off[c->L - 1];
+  u.p = c->params; u.state = c->pstate; u.lr = c->m.lr; u.eps = c->m.eps;
+  u.grads = c->shard_grads; u.stride = c->Pstride;
+}
+
+// Per-shard gradients of all dense layers of a bf16 model for shards [k0, k1), one launch on `ws`.
+static int shard_weight_gradients(antdt_ctx* c, int k0, int k1, hipStream_t ws) {
+  WgradArgs u;
+  fill_wgrad_args(c, u);
+  u.k0 = k0;
+  const HeadTiles ht = head_tiles(c->tab);
+  KSegments seg;
+  memset(&seg, 0, sizeof(seg));
+  seg.n = k1 - k0;
+  for (int q = 0; q < seg.n; ++q) {
+    seg.ks[q] = c->tab.start[k0 + q]; seg.ke[q] = seg.ks[q] + c->tab.len[k0 + q];
+    seg.ts[q] = ht.base[k0 + q]; seg.te[q] = ht.base[k0 + q + 1];
+  }
+  ProfScope ps(prof_of(c), KID_GEMM_WGRAD, ws);
+  HIP_TRY(c, launch_wgrad(u, seg, true, ws));
   return ANTDT_OK;
 }
 
@@ -755,15 +745,7 @@ static int compute_shard_grads(antdt_ctx* c) {
   hipStream_t ws = c->wside;
   HIP_TRY(c, hipStreamWaitEvent(ws, c->ev_dh[0], 0));
   {
-    HeadReduceArgs r = c->head_reduce_args;
-    r.part = 1;
-    r.k_begin = 0; r.k_end = c->tab.K;
-    r.loss_out = nullptr;
-    ProfScope ps(prof_of(c), KID_HEAD_REDUCE, ws);
-    HIP_TRY(c, launch_head_reduce(r, c->tab, ws));
-  }
-  for (int l = c->L - 2; l >= 0; --l) {
-    const int rc = shard_weight_gradient(c, l, 0, c->tab.K, ws);
+    const int rc = shard_weight_gradients(c, 0, c->tab.K, ws);
     if (rc) return rc;
   }
   HIP_TRY(c, hipEventRecord(c->ev_wgrad, ws));
@@ -800,7 +782,7 @@ static int worker_range(antdt_ctx* c, int k0, int k1, float* loss_out, hipStream
     a.s0 = (int32_t)s0; a.ns = (int32_t)ns; a.R = m.rows_per_field;
     a.table_bf16 = m.table_dtype == ANTDT_BF16; a.x_bf16 = c->act_bf16;
     a.mean_pool = m.pooling == ANTDT_POOL_MEAN;
-    a.xt = c->act_bf16 ? c->act_t[0] : nullptr; a.ldt = c->ldt; a.lookup_sample = c->lookup_sample;
+    a.lookup_sample = c->lookup_sample;
     ProfScope ps(pr, KID_POOL, s);
     HIP_TRY(c, launch_pool(a, c->fp, s));
   }
@@ -834,10 +816,9 @@ static int worker_range(antdt_ctx* c, int k0, int k1, float* loss_out, hipStream
     g.C = c->h[l + 1] + s0 * c->width[l + 1] * es; g.ldc = c->width[l + 1];
     g.bias = c->params + c->b_off[l];
     g.M = (int32_t)ns; g.N = c->width[l + 1];
-    if (c->act_bf16) {  // B = W_l^T [out, in padded]; the result also goes to the transposed copy
+    if (c->act_bf16) {  // (the padding rows of W_0's copy are zero)
       g.K = (int32_t)ld(l);
-      g.B = c->wbt[l]; g.ldb = ld(l); g.b_kc = 1;
-      g.CT = c->act_t[l + 1]; g.ldct = c->ldt; g.ct_col0 = s0;
+      g.B = c->wb[l]; g.ldb = c->width[l + 1]; g.b_kc = 0;
     } else {
       g.K = c->width[l];
       g.B = c->params + c->w_off[l]; g.ldb = c->width[l + 1]; g.b_kc = 0;
@@ -859,45 +840,21 @@ static int worker_range(antdt_ctx* c, int k0, int k1, float* loss_out, hipStream
       a.dh = c->dx; a.lddh = c->FD; a.dh_cols = c->FD; a.relu = 0; a.bf16_dh = 0;
     }
     a.k_begin = k0; a.k_end = k1;
-    const bool head_writes_dht = c->act_bf16 && L > 1 && c->width[L - 1] <= 4096;
-    if (head_writes_dht) {
-      a.dht = c->dh_t[L - 1];
-      a.ldt = c->ldt;
-    }
+    a.part = c->head_part; a.ldpart = c->ldpart; a.done = c->head_done;
+    a.loss_k = c->loss_k; a.loss_out = loss_out;
     {
       ProfScope ps(pr, KID_HEAD, s);
-      HIP_TRY(c, launch_head(a, tab, s));
+      if (c->act_bf16) HIP_TRY(c, launch_head_tiles(a, tab, s));
+      else HIP_TRY(c, launch_head(a, tab, s));
     }
-    HeadReduceArgs r;
-    memset(&r, 0, sizeof(r));
-    r.h = act(L - 1); r.ldh = ld(L - 1); r.width = c->width[L - 1]; r.bf16_h = c->act_bf16;
-    r.dz = c->dz; r.loss_s = c->loss_s; r.grads = c->shard_grads; r.loss_k = c->loss_k; r.loss_out = loss_out;
-    r.P = c->Pstride; r.w_off = c->w_off[L - 1]; r.b_off = c->b_off[L - 1]; r.k_begin = k0; r.k_end = k1;
-    if (c->act_bf16 && L > 1) {
-      r.ht = c->act_t[L - 1];
-      r.ldt = c->ldt;
-    }
-    // With a weight-gradient stream, only the bias sum and the shard losses stay on the launch
-    // stream (one wavefront per shard); the weight sums of the last layer, which nothing needs
-    // before the dense update, are computed on that stream ahead of the other weight gradients.
-    c->head_weights_deferred = r.ht != nullptr && L > 1 && wgrad_stream(c) != nullptr;  // (launched with the weight gradients)
-    r.part = c->head_weights_deferred ? 2 : 0;
-    {
+    if (!c->act_bf16) {
+      HeadReduceArgs r;
+      memset(&r, 0, sizeof(r));
+      r.h = act(L - 1); r.ldh = ld(L - 1); r.width = c->width[L - 1]; r.bf16_h = 0;
+      r.dz = c->dz; r.loss_s = c->loss_s; r.grads = c->shard_grads; r.loss_k = c->loss_k; r.loss_out = loss_out;
+      r.P = c->Pstride; r.w_off = c->w_off[L - 1]; r.b_off = c->b_off[L - 1]; r.k_begin = k0; r.k_end = k1;
       ProfScope ps(pr, KID_HEAD_REDUCE, s);
       HIP_TRY(c, launch_head_reduce(r, tab, s));
-    }
-    c->head_reduce_args = r;
-    if (c->act_bf16 && L > 1 && !head_writes_dht) {  // the weight-gradient product wants dh^T
-      TransposeArgs t;
-      memset(&t, 0, sizeof(t));
-      t.n = 1;
-      t.src[0] = (const bf16_t*)c->dh[L - 1] + s0 * c->width[L - 1];
-      t.dst[0] = c->dh_t[L - 1] + s0;
-      t.rows[0] = (int32_t)ns; t.cols[0] = c->width[L - 1];
-      t.ld_src[0] = c->width[L - 1]; t.ld_dst[0] = c->ldt;
-      t.tile_base[1] = (int32_t)((ns + 63) / 64) * ((c->width[L - 1] + 63) / 64);
-      ProfScope ps(pr, KID_TRANSPOSE, s);
-      HIP_TRY(c, launch_transpose_bf16(t, s));
     }
   }
   // Backward.  The data-gradient chain dH_{l+1} -> dH_l stays on the launch stream; the weight
@@ -908,14 +865,16 @@ static int worker_range(antdt_ctx* c, int k0, int k1, float* loss_out, hipStream
   // at all: apply_update forms them inside the dense update (aggregated over the shards in
   // registers, never written per shard), and this step only records when their operands are
   // complete.  The per-shard gradients of the contract are computed when a view asks for them.
-  const bool deferred = c->act_bf16 && L > 1 && c->wside && !c->static_bound && !c->eager_wgrad;
+  const bool deferred = c->act_bf16 && c->wside && !c->static_bound && !c->eager_wgrad;
   c->wgrad_deferred = deferred;
   c->shard_grads_done = false;
-  if (deferred && L == 2) HIP_TRY(c, hipEventRecord(c->ev_dh[0], s));  // dH_1 comes from the loss kernel
+  // The event behind the last operand of the weight gradients (with up to one hidden layer the loss kernel
+  // writes it, else the data gradient of layer 1).
+  const bool mark = c->act_bf16 && (deferred || ws != s);
+  if (mark && L <= 2) HIP_TRY(c, hipEventRecord(c->ev_dh[0], s));
   ProfScope bwd_scope(c->act_bf16 && L > 1 ? pr : nullptr, KID_GEMM_BWD, s);
   bwd_scope.launches(L - 1);
   Profiler* pr_each = c->act_bf16 ? nullptr : pr;  // the fp32 path has other kernels in between
-  auto weight_gradient = [&](int l) -> int { return shard_weight_gradient(c, l, k0, k1, ws); };
   // An event record costs the launch stream about as much as a small kernel, so the weight
   // gradients are released in pairs: after the data gradient of layer l both dW_l (needs
   // dH_{l+1}) and dW_{l-1} (needs dH_l) can start.
@@ -940,9 +899,6 @@ static int worker_range(antdt_ctx* c, int k0, int k1, float* loss_out, hipStream
         g.C = c->dh[l] + s0 * c->width[l] * es; g.ldc = c->width[l]; g.N = c->width[l];
         g.mask = c->h[l] + s0 * c->width[l] * es; g.ldmask = c->width[l];
         g.epi = EPI_RELU_MASK; g.bf16_out = c->act_bf16;
-        if (c->act_bf16) {
-          g.CT = c->dh_t[l]; g.ldct = c->ldt; g.ct_col0 = s0;
-        }
       } else {
         g.C = c->dx + s0 * c->FD; g.ldc = c->FD; g.N = c->FD;
         g.epi = EPI_PLAIN; g.bf16_out = 0;
@@ -950,32 +906,29 @@ static int worker_range(antdt_ctx* c, int k0, int k1, float* loss_out, hipStream
       ProfScope ps(pr_each, KID_GEMM_DGRAD, s);
       HIP_TRY(c, launch_gemm(g, tab, s));
     }
-    if (deferred) {
-      if (l == 1) HIP_TRY(c, hipEventRecord(c->ev_dh[0], s));  // dH_1, the last operand of the weight gradients
+    if (c->act_bf16) {
+      if (l == 1 && mark) HIP_TRY(c, hipEventRecord(c->ev_dh[0], s));
       continue;
     }
     const bool release = l == 0 || ((L - 2 - l) & 1) == 0;
     if (release) {
       if (ws != s) {
-        if (l == 0) bwd_scope.close();
         HIP_TRY(c, hipEventRecord(c->ev_dh[l], s));
         HIP_TRY(c, hipStreamWaitEvent(ws, c->ev_dh[l], 0));
-        if (c->head_weights_deferred) {  // (first release: everything the loss kernel wrote is behind this event)
-          HeadReduceArgs r = c->head_reduce_args;
-          r.part = 1;
-          ProfScope ps(pr, KID_HEAD_REDUCE, ws);
-          HIP_TRY(c, launch_head_reduce(r, tab, ws));
-          c->head_weights_deferred = false;
-        }
       }
       for (const int last = l > 0 ? l - 1 : 0; next_w >= last; --next_w) {
-        const int rc = weight_gradient(next_w);
+        const int rc = shard_weight_gradient_f32(c, next_w, k0, k1, ws);
         if (rc) return rc;
       }
     }
   }
   bwd_scope.close();
-  if (L > 1 && ws != s && !deferred) {
+  if (c->act_bf16 && !deferred) {
+    if (ws != s) HIP_TRY(c, hipStreamWaitEvent(ws, c->ev_dh[0], 0));
+    const int rc = shard_weight_gradients(c, k0, k1, ws);
+    if (rc) return rc;
+  }
+  if ((L > 1 || c->act_bf16) && ws != s && !deferred) {
     HIP_TRY(c, hipEventRecord(c->ev_wgrad, ws));
     c->wgrad_pending = true;
   }
@@ -1098,8 +1051,8 @@ int antdt_apply_update(antdt_ctx* c, void* stream) {
   // weight-gradient stream (behind those products, which it needs anyway) beside the sparse
   // update; `s` joins it before this call's work on `s` is complete.
   hipStream_t ds = wgrad_stream(c) ? wgrad_stream(c) : s;
-  if (ds != s && c->L == 1) {
-    // (with hidden layers every worker step ends by making this stream wait for the launch stream)
+  if (ds != s && !c->wgrad_deferred) {
+    // (the dense update overwrites weights that the worker step's last products on `s` read)
     HIP_TRY(c, hipEventRecord(c->ev_dh[c->L], s));  // everything enqueued on `s` so far (loss, last layer's gradient)
     HIP_TRY(c, hipStreamWaitEvent(ds, c->ev_dh[c->L], 0));
   }
@@ -1119,34 +1072,9 @@ int antdt_apply_update(antdt_ctx* c, void* stream) {
       const int rcj = join_wgrad(c, s);
       if (rcj) return rcj;
     }
-    const int Lh = c->L - 1;  // hidden layers
-    if (!c->shard_grads_done) {  // last layer: per-shard weight sums (its bias sum is already there)
-      HeadReduceArgs r = c->head_reduce_args;
-      r.part = 1;
-      r.k_begin = 0; r.k_end = c->tab.K;
-      r.loss_out = nullptr;
-      ProfScope ps(pr, KID_HEAD_REDUCE, ds);
-      HIP_TRY(c, launch_head_reduce(r, c->tab, ds));
-    }
-    {
-      DenseAdagradArgs a;  // plain range: the last layer's weights and bias
-      memset(&a, 0, sizeof(a));
-      a.p = c->params; a.state = c->pstate; a.grads = c->shard_grads; a.stride = c->Pstride; a.lr = m.lr; a.eps = m.eps;
-      a.n_mat = 0; a.n_rng = 1;
-      a.rng_off[0] = c->w_off[Lh]; a.rng_len[0] = c->P - c->w_off[Lh];
-      a.rng_block[0] = 0; a.rng_block[1] = (int)((a.rng_len[0] + 255) / 256);
-      ProfScope ps(pr, KID_DENSE_ADAGRAD, ds);
-      HIP_TRY(c, launch_dense_adagrad(a, c->tab, ds));
-    }
-    WgradUpdateArgs u;
-    memset(&u, 0, sizeof(u));
-    u.n_layers = Lh;
-    for (int l = 0; l < Lh; ++l) {
-      u.A[l] = c->act_t[l]; u.B[l] = c->dh_t[l + 1];
-      u.M[l] = c->width[l] + 1; u.N[l] = c->width[l + 1];
-      u.w_off[l] = c->w_off[l]; u.wb[l] = l == 0 ? c->wb0_alt : c->wb[l];
-    }
-    u.ld = c->ldt; u.p = c->params; u.state = c->pstate; u.lr = m.lr; u.eps = m.eps;
+    WgradArgs u;
+    fill_wgrad_args(c, u);
+    const HeadTiles ht = head_tiles(c->tab);
     KSegments seg;
     memset(&seg, 0, sizeof(seg));
     for (int k = 0; k < c->tab.K; ++k) {
@@ -1155,24 +1083,22 @@ int antdt_apply_update(antdt_ctx* c, void* stream) {
       const int ks = c->tab.start[k], ke = ks + c->tab.len[k];
       if (seg.n > 0 && seg.w[seg.n - 1] == w && seg.ke[seg.n - 1] == ks) {
         seg.ke[seg.n - 1] = ke;  // neighbours of equal weight: one range
+        seg.te[seg.n - 1] = ht.base[k + 1];
       } else {
         seg.ks[seg.n] = ks; seg.ke[seg.n] = ke; seg.w[seg.n] = w;
+        seg.ts[seg.n] = ht.base[k]; seg.te[seg.n] = ht.base[k + 1];
         ++seg.n;
       }
     }
     {
       ProfScope ps(pr, KID_WGRAD_ADAGRAD, ds);
-      HIP_TRY(c, launch_wgrad_update(u, seg, ds));
+      HIP_TRY(c, launch_wgrad(u, seg, false, ds));
     }
     // The input-gradient product of this step, enqueued behind the event this stream waited for,
     // may still be reading the old bf16 copy of W_0: the kernel wrote the new one to the other
     // buffer, which is the current one from here on (the products of deeper layers ran before
     // the event).
     std::swap(c->wb[0], c->wb0_alt);
-    {
-      const int rc = transpose_weights(c, ds);  // the forward operand copies W_l^T from the new W_l
-      if (rc) return rc;
-    }
     if (ds != s) {
       HIP_TRY(c, hipEventRecord(c->ev_wgrad, ds));
       HIP_TRY(c, hipStreamWaitEvent(s, c->ev_wgrad, 0));
@@ -1191,8 +1117,7 @@ int antdt_apply_update(antdt_ctx* c, void* stream) {
     if (c->act_bf16) {
       for (int l = 0; l + 1 < c->L; ++l) {
         a.w_off[l] = c->w_off[l]; a.rows[l] = c->width[l]; a.cols[l] = c->width[l + 1];
-        a.rows_pad[l] = l == 0 ? c->ldx : c->width[l];
-        a.wb[l] = c->wb[l]; a.wbt[l] = c->wbt[l];
+        a.wb[l] = c->wb[l];
         a.tile_base[l + 1] = a.tile_base[l] + ((c->width[l] + 63) / 64) * ((c->width[l + 1] + 63) / 64);
         add_range(c->b_off[l], c->width[l + 1]);
       }

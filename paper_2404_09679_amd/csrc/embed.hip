@@ -41,8 +41,8 @@ template <> __device__ __forceinline__ void store_row<bf16_t, 8>(bf16_t* dst, co
                                               (uint32_t)f2bf(v[6]) | ((uint32_t)f2bf(v[7]) << 16));
 }
 
-// Dense-feature columns of 64 samples: copied behind the pooled embeddings (and into the
-// transposed copy), the padding columns of the row are zeroed.
+// Dense-feature columns of 64 samples: copied behind the pooled embeddings, the padding columns of
+// the row are zeroed.
 template <typename OT>
 __device__ __forceinline__ void dense_columns(const PoolArgs& a, int sl0) {
   const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
@@ -53,7 +53,6 @@ __device__ __forceinline__ void dense_columns(const PoolArgs& a, int sl0) {
   for (int c = ty; c < a.ldx - FD; c += 4) {
     const float v = c < a.num_dense ? a.dense[s * a.num_dense + c] : 0.0f;
     xrow[c] = from_f32<OT>(v);
-    if (a.xt && c < a.num_dense) a.xt[(int64_t)(FD + c) * a.ldt + s] = f2bf(v);
   }
 }
 
@@ -61,16 +60,13 @@ __device__ __forceinline__ void dense_columns(const PoolArgs& a, int sl0) {
 // LPR = D*sizeof(T)/16 lanes owns one bag, so a wavefront works on 64/LPR bags at once.
 // The group fetches LPR ids with one coalesced load, hands them round with lane
 // shuffles and issues the LPR row loads (16 bytes per lane, one whole row per group)
-// back to back before adding them, which keeps 64 rows in flight per wavefront.  The
-// pooled rows are written to X and, through an LDS tile, to the transposed copy that the
-// weight-gradient GEMM reads.  Every lookup's sample index is recorded for the sort.
+// back to back before adding them, which keeps 64 rows in flight per wavefront.  Every
+// lookup's sample index is recorded for the sort.
 template <typename TT, typename OT, int LPR>
 __global__ __launch_bounds__(256) void pool_tile_kernel(PoolArgs a, FieldPtr fp) {
   constexpr int EV = Vec16<TT>::N;
   constexpr int G = 256 / LPR;       // bags per round
   constexpr int ROUNDS = 64 / G;
-  constexpr int TP = 130;            // tile pitch (odd number of dwords: conflict-free column reads)
-  __shared__ bf16_t tile[64 * TP];
   const int f = blockIdx.y, sl0 = blockIdx.x * 64;
   if (f == a.F) {
     dense_columns<OT>(a, sl0);
@@ -80,7 +76,6 @@ __global__ __launch_bounds__(256) void pool_tile_kernel(PoolArgs a, FieldPtr fp)
   const int gl = (threadIdx.x & 63) - c;  // first lane of this group inside the wavefront
   const int32_t* ids = a.ids + fp.p[f];
   const TT* tab = reinterpret_cast<const TT*>(a.tables) + (int64_t)f * a.R * a.D + c * EV;
-  const bool use_tile = a.xt != nullptr && a.D <= 128;
 #pragma unroll
   for (int r = 0; r < ROUNDS; ++r) {
     const int ls = r * G + g;
@@ -120,26 +115,7 @@ __global__ __launch_bounds__(256) void pool_tile_kernel(PoolArgs a, FieldPtr fp)
 #pragma unroll
       for (int e = 0; e < EV; ++e) acc[e] /= len;
     }
-    if (valid) {
-      store_row<OT, EV>(reinterpret_cast<OT*>(a.x) + s * a.ldx + f * a.D + c * EV, acc);
-      if (a.xt) {
-        if (use_tile) {
-#pragma unroll
-          for (int e = 0; e < EV; ++e) tile[ls * TP + c * EV + e] = f2bf(acc[e]);
-        } else {
-#pragma unroll
-          for (int e = 0; e < EV; ++e) a.xt[(int64_t)(f * a.D + c * EV + e) * a.ldt + s] = f2bf(acc[e]);
-        }
-      }
-    }
-  }
-  if (use_tile) {
-    __syncthreads();
-    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-    if (sl0 + tx < a.ns) {
-      bf16_t* dst = a.xt + (int64_t)f * a.D * a.ldt + a.s0 + sl0 + tx;
-      for (int d = ty; d < a.D; d += 4) dst[(int64_t)d * a.ldt] = tile[tx * TP + d];
-    }
+    if (valid) store_row<OT, EV>(reinterpret_cast<OT*>(a.x) + s * a.ldx + f * a.D + c * EV, acc);
   }
 }
 
@@ -184,13 +160,7 @@ __global__ __launch_bounds__(256) void pool_kernel(PoolArgs a, FieldPtr fp) {
 #pragma unroll
     for (int e = 0; e < EV; ++e) acc[e] /= len;
   }
-  if (sub == 0) {
-    store_row<OT, EV>(xrow + f * a.D + c * EV, acc);
-    if (a.xt) {
-#pragma unroll
-      for (int e = 0; e < EV; ++e) a.xt[(int64_t)(f * a.D + c * EV + e) * a.ldt + s] = f2bf(acc[e]);
-    }
-  }
+  if (sub == 0) store_row<OT, EV>(xrow + f * a.D + c * EV, acc);
 }
 
 template <typename OT>

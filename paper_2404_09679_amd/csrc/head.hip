@@ -47,81 +47,143 @@ __global__ __launch_bounds__(256) void head_kernel(HeadArgs a, ShardTab tab) {
   }
 }
 
-// bf16 variant working on a tile of `spb` samples staged in LDS, so that the gradient can be
-// written both row-major (dh) and transposed (dht, sample index contiguous) with coalesced
-// stores; same arithmetic as head_kernel.
-constexpr int HEAD_LDS_ELEMS = 16448;  // largest tile: 32 x (512 + 2) bf16
-// Shared memory is sized at the launch to the tile actually used (spb x (width + 2) bf16, the
-// last-layer weights, spb floats), so that small widths leave room for many blocks per
-// compute unit: the kernel is a chain of dependent global round trips and needs them in flight.
-__host__ __device__ inline size_t head_tile_lds_bytes(int spb, int width) {
-  return (((size_t)spb * (width + 2) * 2 + 15) & ~(size_t)15) + (size_t)width * 4 + 32 * 4;
-}
-__global__ __launch_bounds__(256) void head_tile_kernel(HeadArgs a, ShardTab tab, int spb) {
-  extern __shared__ __attribute__((aligned(16))) char head_lds[];
-  const int width = a.width, pitch = width + 2, vpr = width >> 3;
-  bf16_t* tile = reinterpret_cast<bf16_t*>(head_lds);
-  float* wl = reinterpret_cast<float*>(head_lds + (((size_t)spb * pitch * 2 + 15) & ~(size_t)15));  // last-layer weights
-  float* dzs = wl + width;
-  for (int j = threadIdx.x; j < width; j += 256) wl[j] = a.w[j];
-  const int64_t first = tab.start[a.k_begin];
-  const int64_t last = (int64_t)tab.start[a.k_end - 1] + tab.len[a.k_end - 1];
-  const int64_t s0 = first + (int64_t)blockIdx.x * spb;
-  const int rows = (int)min((int64_t)spb, last - s0);
-  const bf16_t* h = reinterpret_cast<const bf16_t*>(a.h);
-  for (int idx = threadIdx.x; idx < rows * vpr; idx += 256) {
-    const int r = idx / vpr, c8 = idx - r * vpr;
-    const uint4 v = *reinterpret_cast<const uint4*>(h + (s0 + r) * a.ldh + c8 * 8);
-    uint32_t* d = reinterpret_cast<uint32_t*>(tile + r * pitch + c8 * 8);
-    d[0] = v.x; d[1] = v.y; d[2] = v.z; d[3] = v.w;
-  }
-  __syncthreads();
+// bf16 variant: a block works on HEAD_TILE consecutive samples of one shard, four per wavefront, 8 columns
+// (16 bytes) per lane.  Besides the loss, dz and dh (same arithmetic as head_kernel) it leaves the sums
+// over its samples that the last layer's weight gradient, bias gradient and the shard's loss are made of,
+// so that nothing has to read the activation again; the last block to finish adds up the losses of the
+// shards (in tile order: the result does not depend on which block that is).
+template <typename TD>
+__global__ __launch_bounds__(256) void head_tile_kernel(HeadArgs a, ShardTab tab, HeadTiles ht) {
+  constexpr int SPW = HEAD_TILE / 4;   // samples per wavefront
+  __shared__ float col[4][512 + 8];
+  __shared__ float sums[4][2];
+  __shared__ int last;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int r = wave; r < rows; r += 4) {  // logits of the tile, from LDS only
-    float part = 0.0f;
-    for (int j = lane; j < width; j += 64) part = fmaf(bf2f(tile[r * pitch + j]), wl[j], part);
-    part = wave_sum(part);
-    if (lane == 0) dzs[r] = part;
-  }
-  __syncthreads();
-  if ((int)threadIdx.x < rows) {  // one thread per sample: loss and dz, their loads side by side
-    const int r = threadIdx.x;
-    const int64_t s = s0 + r;
-    const float z = dzs[r] + a.b[0];
-    int k = a.k_begin;
-    while (k + 1 < a.k_end && s >= (int64_t)tab.start[k] + tab.len[k]) ++k;
-    const float y = a.labels[s];
-    const float e = expf(-fabsf(z));
-    const float sig = z >= 0.0f ? 1.0f / (1.0f + e) : e / (1.0f + e);
-    const float dz = (sig - y) * (1.0f / (float)tab.len[k]);
-    a.z[s] = z;
-    a.loss_s[s] = fmaxf(z, 0.0f) - z * y + log1pf(e);
-    a.dz[s] = dz;
-    dzs[r] = dz;
-  }
-  __syncthreads();
-  bf16_t* dh = reinterpret_cast<bf16_t*>(a.dh);
-  for (int idx = threadIdx.x; idx < rows * vpr; idx += 256) {
-    const int r = idx / vpr, c8 = idx - r * vpr;
-    const float dz = dzs[r];
-    uint32_t o[4];
+  const int tile = ht.base[a.k_begin] + blockIdx.x;
+  int k = a.k_begin;
+  while (k + 1 < a.k_end && tile >= ht.base[k + 1]) ++k;
+  const int t0 = (tile - ht.base[k]) * HEAD_TILE;   // first sample inside the shard
+  const int64_t s0 = (int64_t)tab.start[k] + t0 + wave * SPW;
+  const int rows = min(max(tab.len[k] - t0 - wave * SPW, 0), SPW);   // samples of this wavefront
+  const bf16_t* h = reinterpret_cast<const bf16_t*>(a.h);
+  const int64_t last_row = max(rows - 1, 0);
+  const float label = rows > 0 ? a.labels[s0 + min(lane, (int)last_row)] : 0.0f;   // lanes 0 .. SPW-1: one sample each
+
+  float part[SPW] = {};
+  for (int j = lane * 8; j < a.width; j += 512) {
+    uint4 v[SPW];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int j = c8 * 8 + 2 * q;
-      const float g0 = bf2f(tile[r * pitch + j]) > 0.0f ? dz * wl[j] : 0.0f;
-      const float g1 = bf2f(tile[r * pitch + j + 1]) > 0.0f ? dz * wl[j + 1] : 0.0f;
-      o[q] = (uint32_t)f2bf(g0) | ((uint32_t)f2bf(g1) << 16);
+    for (int r = 0; r < SPW; ++r)
+      v[r] = rows > 0 ? *reinterpret_cast<const uint4*>(h + (s0 + min((int64_t)r, last_row)) * a.ldh + j) : make_uint4(0, 0, 0, 0);
+    float w[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) w[e] = j + e < a.width ? a.w[j + e] : 0.0f;
+#pragma unroll
+    for (int r = 0; r < SPW; ++r) {
+      const uint32_t x[4] = {v[r].x, v[r].y, v[r].z, v[r].w};
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        part[r] = fmaf(__uint_as_float(x[q] << 16), w[2 * q], part[r]);
+        part[r] = fmaf(__uint_as_float(x[q] & 0xFFFF0000u), w[2 * q + 1], part[r]);
+      }
     }
-    *reinterpret_cast<uint4*>(dh + (s0 + r) * a.lddh + c8 * 8) = make_uint4(o[0], o[1], o[2], o[3]);
   }
-  const int ls = threadIdx.x % spb, jj = threadIdx.x / spb, jstep = 256 / spb;
-  if (ls < rows) {
-    const float dz = dzs[ls];
-    for (int j = jj; j < width; j += jstep) {
-      const float g = bf2f(tile[ls * pitch + j]) > 0.0f ? dz * wl[j] : 0.0f;
-      a.dht[(int64_t)j * a.ldt + s0 + ls] = f2bf(g);
+  float mine = 0.0f;   // lane r < SPW: logit of sample r
+#pragma unroll
+  for (int r = 0; r < SPW; ++r) {
+    const float z = wave_sum(part[r]);
+    if (lane == r) mine = z;
+  }
+  const float z = mine + a.b[0];
+  const float e = expf(-fabsf(z));
+  const float sig = z >= 0.0f ? 1.0f / (1.0f + e) : e / (1.0f + e);
+  const bool on = lane < rows;
+  const float dz_lane = on ? (sig - label) * (1.0f / (float)tab.len[k]) : 0.0f;
+  const float loss_lane = on ? fmaxf(z, 0.0f) - z * label + log1pf(e) : 0.0f;
+  float dz[SPW], sdz = 0.0f, sl = 0.0f;
+#pragma unroll
+  for (int r = 0; r < SPW; ++r) {
+    dz[r] = __shfl(dz_lane, r, 64);
+    sdz += dz[r];
+    sl += __shfl(loss_lane, r, 64);
+  }
+  if (lane == 0) {
+    sums[wave][0] = sdz;
+    sums[wave][1] = sl;
+  }
+  float* part_out = a.part + (int64_t)tile * a.ldpart;
+  const int cols = max(a.width, a.dh_cols);
+  for (int j0 = 0; j0 < cols; j0 += 512) {
+    const int j = j0 + lane * 8;
+    float g[8] = {};
+    if (j < a.width) {
+      float w[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) w[q] = j + q < a.width ? a.w[j + q] : 0.0f;
+#pragma unroll
+      for (int r = 0; r < SPW; ++r)
+        if (r < rows) {
+          const uint4 v = *reinterpret_cast<const uint4*>(h + (s0 + r) * a.ldh + j);
+          const uint32_t x[4] = {v.x, v.y, v.z, v.w};
+          float d[8];
+#pragma unroll
+          for (int q = 0; q < 8; ++q) {
+            const float hv = (q & 1) ? __uint_as_float(x[q >> 1] & 0xFFFF0000u) : __uint_as_float(x[q >> 1] << 16);
+            g[q] = fmaf(hv, dz[r], g[q]);
+            d[q] = (!a.relu || hv > 0.0f) ? dz[r] * w[q] : 0.0f;
+          }
+          TD* dst = reinterpret_cast<TD*>(a.dh) + (s0 + r) * a.lddh + j;
+          if (sizeof(TD) == 2) {   // (the gradient of a hidden activation: its width is a multiple of 8)
+            *reinterpret_cast<uint4*>(dst) = make_uint4((uint32_t)f2bf(d[0]) | ((uint32_t)f2bf(d[1]) << 16),
+                                                        (uint32_t)f2bf(d[2]) | ((uint32_t)f2bf(d[3]) << 16),
+                                                        (uint32_t)f2bf(d[4]) | ((uint32_t)f2bf(d[5]) << 16),
+                                                        (uint32_t)f2bf(d[6]) | ((uint32_t)f2bf(d[7]) << 16));
+          } else {
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+              if (j + q < a.dh_cols) dst[q] = from_f32<TD>(d[q]);
+          }
+        }
+    }
+    *reinterpret_cast<float4*>(&col[wave][lane * 8]) = make_float4(g[0], g[1], g[2], g[3]);
+    *reinterpret_cast<float4*>(&col[wave][lane * 8 + 4]) = make_float4(g[4], g[5], g[6], g[7]);
+    __syncthreads();
+    for (int q = threadIdx.x; q < 512 && j0 + q < a.width; q += 256)
+      part_out[j0 + q] = (col[0][q] + col[1][q]) + (col[2][q] + col[3][q]);
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) {
+    // agent-scope stores: the block that adds them up may run on another XCD
+    __hip_atomic_store(part_out + a.width, (sums[0][0] + sums[1][0]) + (sums[2][0] + sums[3][0]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(part_out + a.width + 1, (sums[0][1] + sums[1][1]) + (sums[2][1] + sums[3][1]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    last = __hip_atomic_fetch_add(a.done, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
+  }
+  __syncthreads();
+  if (!last) return;
+  if (threadIdx.x == 0) __hip_atomic_store(a.done, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  for (int q = a.k_begin + wave; q < a.k_end; q += 4) {
+    float l = 0.0f;
+    for (int t = ht.base[q] + lane; t < ht.base[q + 1]; t += 64)
+      l += __hip_atomic_load(a.part + (int64_t)t * a.ldpart + a.width + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    l = wave_sum(l);
+    if (lane == 0) {
+      const float lk = tab.len[q] > 0 ? l / (float)tab.len[q] : 0.0f;
+      a.loss_k[q] = lk;
+      if (a.loss_out) a.loss_out[q - a.k_begin] = lk;
     }
   }
+}
+
+// Losses of shards without samples, when no shard of the range has any.
+__global__ __launch_bounds__(64) void head_no_samples_kernel(HeadArgs a) {
+  for (int k = a.k_begin + (int)threadIdx.x; k < a.k_end; k += 64) {
+    a.loss_k[k] = 0.0f;
+    if (a.loss_out) a.loss_out[k - a.k_begin] = 0.0f;
+  }
+}
+
+__global__ __launch_bounds__(64) void zero_words_kernel(int32_t* p, int n) {
+  for (int i = threadIdx.x; i < n; i += 64) p[i] = 0;
 }
 
 // Block (64 columns x 4 sample lanes) of shard k = k_begin + blockIdx.y:
@@ -166,40 +228,6 @@ __global__ __launch_bounds__(256) void head_reduce_kernel(HeadReduceArgs a, Shar
   }
 }
 
-// The same reductions from the transposed activation hT[j][s]: one wavefront per (j, shard)
-// reads a contiguous run of samples; wavefront `width` of a shard does db and the loss.
-__global__ __launch_bounds__(256) void head_reduce_t_kernel(HeadReduceArgs a, ShardTab tab) {
-  const int k = a.k_begin + blockIdx.y;
-  const int64_t s0 = tab.start[k];
-  const int n = tab.len[k];
-  const int lane = threadIdx.x & 63;
-  const int j = a.part == 2 ? a.width + (int)(threadIdx.x >> 6) : blockIdx.x * 4 + (int)(threadIdx.x >> 6);
-  float* g = a.grads + (int64_t)k * a.P;
-  if (j < a.width) {
-    const bf16_t* h = a.ht + (int64_t)j * a.ldt + s0;
-    float acc = 0.0f;
-#pragma unroll 4
-    for (int s = lane; s < n; s += 64) acc = fmaf(bf2f(h[s]), a.dz[s0 + s], acc);
-    acc = wave_sum(acc);
-    if (lane == 0) g[a.w_off + j] = acc;
-  } else if (j == a.width && a.part != 1) {
-    float sdz = 0.0f, sl = 0.0f;
-#pragma unroll 4
-    for (int s = lane; s < n; s += 64) {
-      sdz += a.dz[s0 + s];
-      sl += a.loss_s[s0 + s];
-    }
-    sdz = wave_sum(sdz);
-    sl = wave_sum(sl);
-    if (lane == 0) {
-      g[a.b_off] = sdz;
-      const float lk = n > 0 ? sl / (float)n : 0.0f;
-      a.loss_k[k] = lk;
-      if (a.loss_out) a.loss_out[k - a.k_begin] = lk;
-    }
-  }
-}
-
 // db[k][o] = sum over the samples of shard k of dh[s, o].
 template <typename TD>
 __global__ __launch_bounds__(256) void bias_grad_kernel(BiasGradArgs a, ShardTab tab) {
@@ -233,31 +261,27 @@ hipError_t launch_head(const HeadArgs& a, const ShardTab& tab, hipStream_t s) {
   const int64_t last = (int64_t)tab.start[a.k_end - 1] + tab.len[a.k_end - 1];
   if (last <= first) return hipSuccess;
   dim3 grid((unsigned)((last - first + 3) / 4)), block(256);
-  if (a.dht) {  // bf16 hidden activation with a transposed gradient copy: tile kernel
-    int spb = 16;
-    while (spb > 4 && spb * (a.width + 2) > HEAD_LDS_ELEMS) spb >>= 1;
-    hipLaunchKernelGGL(head_tile_kernel, dim3((unsigned)((last - first + spb - 1) / spb)), block,
-                       head_tile_lds_bytes(spb, a.width), s, a, tab, spb);
-    return hipGetLastError();
-  }
-  if (a.bf16_h) {
-    if (a.bf16_dh) hipLaunchKernelGGL((head_kernel<bf16_t, bf16_t>), grid, block, 0, s, a, tab);
-    else hipLaunchKernelGGL((head_kernel<bf16_t, float>), grid, block, 0, s, a, tab);
-  } else {
-    hipLaunchKernelGGL((head_kernel<float, float>), grid, block, 0, s, a, tab);
-  }
+  hipLaunchKernelGGL((head_kernel<float, float>), grid, block, 0, s, a, tab);
+  return hipGetLastError();
+}
+
+hipError_t launch_head_tiles(const HeadArgs& a, const ShardTab& tab, hipStream_t s) {
+  const HeadTiles ht = head_tiles(tab);
+  const int tiles = ht.base[a.k_end] - ht.base[a.k_begin];
+  if (tiles == 0) hipLaunchKernelGGL(head_no_samples_kernel, dim3(1), dim3(64), 0, s, a);
+  else if (a.bf16_dh) hipLaunchKernelGGL(head_tile_kernel<bf16_t>, dim3(tiles), dim3(256), 0, s, a, tab, ht);
+  else hipLaunchKernelGGL(head_tile_kernel<float>, dim3(tiles), dim3(256), 0, s, a, tab, ht);
+  return hipGetLastError();
+}
+
+hipError_t launch_zero_words(int32_t* p, int n, hipStream_t s) {
+  hipLaunchKernelGGL(zero_words_kernel, dim3(1), dim3(64), 0, s, p, n);
   return hipGetLastError();
 }
 
 hipError_t launch_head_reduce(const HeadReduceArgs& a, const ShardTab& tab, hipStream_t s) {
-  if (a.ht) {
-    const unsigned bx = a.part == 2 ? 1u : (unsigned)((a.width + (a.part == 1 ? 0 : 1) + 3) / 4);
-    hipLaunchKernelGGL(head_reduce_t_kernel, dim3(bx, a.k_end - a.k_begin), dim3(256), 0, s, a, tab);
-    return hipGetLastError();
-  }
   dim3 grid((a.width + 63) / 64, a.k_end - a.k_begin), block(256);
-  if (a.bf16_h) hipLaunchKernelGGL(head_reduce_kernel<bf16_t>, grid, block, 0, s, a, tab);
-  else hipLaunchKernelGGL(head_reduce_kernel<float>, grid, block, 0, s, a, tab);
+  hipLaunchKernelGGL(head_reduce_kernel<float>, grid, block, 0, s, a, tab);
   return hipGetLastError();
 }
 

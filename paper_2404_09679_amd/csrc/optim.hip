@@ -44,7 +44,6 @@ __device__ __forceinline__ float adagrad_elem(const DenseAdagradArgs& a, const S
 }
 
 __global__ __launch_bounds__(256) void dense_adagrad_kernel(DenseAdagradArgs a, ShardTab tab) {
-  __shared__ bf16_t tile[64][66];
   const int nt = a.tile_base[a.n_mat];
   if ((int)blockIdx.x < nt) {
     int mi = 0;
@@ -78,22 +77,15 @@ __global__ __launch_bounds__(256) void dense_adagrad_kernel(DenseAdagradArgs a, 
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
       const int r = ty + 4 * q;
-      bf16_t h = 0;
       if (r0 + r < rows && col_ok) {
         const int64_t e = (int64_t)(r0 + r) * cols + c0 + tx;
         const float s1 = fmaf(g[q], g[q], s0[q]);
         const float p1 = p0[q] - a.lr * g[q] / (sqrtf(s1) + a.eps);
         a.state[a.w_off[mi] + e] = s1;
         a.p[a.w_off[mi] + e] = p1;
-        h = f2bf(p1);
-        a.wb[mi][e] = h;
+        a.wb[mi][e] = f2bf(p1);
       }
-      tile[r][tx] = h;
     }
-    __syncthreads();
-    for (int cidx = ty; cidx < 64; cidx += 4)
-      if (c0 + cidx < cols && r0 + tx < rows)
-        a.wbt[mi][(int64_t)(c0 + cidx) * a.rows_pad[mi] + r0 + tx] = tile[tx][cidx];
     return;
   }
   const int rb = blockIdx.x - nt;
