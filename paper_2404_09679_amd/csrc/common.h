@@ -201,7 +201,7 @@ struct HeadArgs {
   // bf16 models: the sums over the samples are formed along the way, per tile of samples of one shard
   float* part;          // [tiles, ldpart] sum of dz * h per column; column `width`: sum of dz, `width` + 1: of the losses
   int64_t ldpart;
-  int32_t* done;        // blocks that have finished (0 between launches)
+  int32_t* done;        // [K] blocks of each shard that have finished (0 between launches)
   float* loss_k;        // workspace [K]
   float* loss_out;      // caller's buffer or NULL; element (k - k_begin)
 };

@@ -119,7 +119,7 @@ struct antdt_ctx {
                                          // while the input-gradient product may still read the old one
   float* head_part = nullptr;            // loss kernel's sums per tile of samples [tiles, ldpart]
   int64_t ldpart = 0;
-  int32_t* head_done = nullptr;          // its count of finished blocks (0 between launches)
+  int32_t* head_done = nullptr;          // per shard: its finished blocks (0 between launches)
   int32_t* lookup_sample = nullptr;
   int32_t *key[2] = {}, *pay[2] = {}, *tile_heads = nullptr, *ubase = nullptr, *uniq = nullptr;
   int32_t *segoff = nullptr, *ufield = nullptr, *segabs = nullptr, *counters = nullptr, *long_seg = nullptr, *items = nullptr, *qcnt = nullptr, *xcd_tab = nullptr;
@@ -232,7 +232,7 @@ static size_t carve(antdt_ctx* c, char* base) {
     }
     c->head_part = (float*)take((size_t)(Bm / HEAD_TILE + K) * c->ldpart * 4);
   }
-  c->head_done = (int32_t*)take(4);
+  c->head_done = (int32_t*)take((size_t)K * 4);
   c->lookup_sample = (int32_t*)take((size_t)N * 4);
   for (int i = 0; i < 2; ++i) {
     c->key[i] = (int32_t*)take((size_t)N * 4);
@@ -399,7 +399,7 @@ int antdt_workspace_bytes(const antdt_ctx* ctx, size_t* bytes) {
 
 // What a fresh workspace has to hold before the first iteration.
 static int init_workspace(antdt_ctx* c, hipStream_t s) {
-  HIP_TRY(c, launch_zero_words(c->head_done, 1, s));
+  HIP_TRY(c, launch_zero_words(c->head_done, c->m.max_shards, s));
   if (!c->act_bf16) return ANTDT_OK;
   for (int l = 0; l + 1 < c->L; ++l) {
     CastArgs a;

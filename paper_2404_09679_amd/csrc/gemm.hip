@@ -57,27 +57,18 @@ __global__ __launch_bounds__(64 * WR * WC * WK) void gemm_bf16_kernel(GemmArgs p
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int fr = lane & 31, fg = lane >> 5;
 
+  // One bias column per lane, requested ahead of the product and added at its end: a sum that started from the
+  // bias would round differently, and where activations are bf16 such a difference grows from layer to layer.
+  constexpr int WN = 32 * TN;
+  static_assert(WN <= 64, "one bias column per lane");
+  float bias = 0.0f;
+  if (p.epi == EPI_BIAS_RELU) bias = p.bias[min(n0 + (wave % (WR * WC) % WC) * WN + lane % WN, p.N - 1)];
   f32x16 acc[TM][TN];
-  if (p.epi == EPI_BIAS_RELU) {   // the sums start from the bias: its loads overlap with those of the first stage
-    const int nb = n0 + (wave % (WR * WC) % WC) * (32 * TN);
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const float4 b = *reinterpret_cast<const float4*>(p.bias + min(nb + j * 32 + 8 * v + 4 * fg, p.N - 4));
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-          acc[i][j][4 * v] = b.x; acc[i][j][4 * v + 1] = b.y; acc[i][j][4 * v + 2] = b.z; acc[i][j][4 * v + 3] = b.w;
-        }
-      }
-  } else {
-    zero_acc(acc);
-  }
+  zero_acc(acc);
   P::run(reinterpret_cast<const bf16_t*>(p.A), reinterpret_cast<const bf16_t*>(p.B), p.lda, p.ldb, p.M, p.N, m0, n0, 0,
          p.K, lds, acc);
   if (wave >= WR * WC) return;
   const int wr = wave / WC, wc = wave % WC;
-  constexpr int WN = 32 * TN;
   const int mw = m0 + wr * (32 * TM), nw = n0 + wc * WN;
   if (p.bf16_out) {
     constexpr int SP = WN + 8;
@@ -86,6 +77,22 @@ __global__ __launch_bounds__(64 * WR * WC * WK) void gemm_bf16_kernel(GemmArgs p
     constexpr int CPR = WN / 8, RPI = 64 / CPR;   // 16-byte pieces per row, rows per wavefront instruction
     const int rr = lane / CPR, cc = (lane % CPR) * 8;
     bf16_t* C = reinterpret_cast<bf16_t*>(p.C);
+    if (p.epi == EPI_BIAS_RELU) {
+      float* sb = reinterpret_cast<float*>(st);
+      if (lane < WN) sb[lane] = bias;
+      wave_lds_fence();
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const float4 b = *reinterpret_cast<const float4*>(sb + j * 32 + 8 * v + 4 * fg);
+#pragma unroll
+          for (int i = 0; i < TM; ++i) {
+            acc[i][j][4 * v] += b.x; acc[i][j][4 * v + 1] += b.y; acc[i][j][4 * v + 2] += b.z; acc[i][j][4 * v + 3] += b.w;
+          }
+        }
+      wave_lds_fence();
+    }
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
 #pragma unroll

@@ -47,46 +47,63 @@ __global__ __launch_bounds__(256) void head_kernel(HeadArgs a, ShardTab tab) {
   }
 }
 
-// bf16 variant: a block works on HEAD_TILE consecutive samples of one shard, four per wavefront, 8 columns
-// (16 bytes) per lane.  Besides the loss, dz and dh (same arithmetic as head_kernel) it leaves the sums
-// over its samples that the last layer's weight gradient, bias gradient and the shard's loss are made of,
-// so that nothing has to read the activation again; the last block to finish adds up the losses of the
-// shards (in tile order: the result does not depend on which block that is).
-template <typename TD>
+// A block works on HEAD_TILE consecutive samples of one shard, four per wavefront; a lane holds the columns
+// lane, lane + 64, ... of all four, 512 columns at a time (its loads are then in flight together, and widths
+// up to 512 are read once).  Besides the loss, dz and dh it leaves the sums over its samples that the last
+// layer's weight gradient, bias gradient and the shard's loss are made of, so that nothing has to read the
+// activation again; the last block of a shard to finish adds up the shard's loss (in tile order: the
+// result does not depend on which block that is).
+// Bound by the chain of round trips (activation -> logit -> gradient), not by bytes.
+template <typename TH, typename TD>
 __global__ __launch_bounds__(256) void head_tile_kernel(HeadArgs a, ShardTab tab, HeadTiles ht) {
   constexpr int SPW = HEAD_TILE / 4;   // samples per wavefront
-  __shared__ float col[4][512 + 8];
+  constexpr int CPL = 8, CHUNK = 64 * CPL;
+  __shared__ float col[4][CHUNK];
   __shared__ float sums[4][2];
   __shared__ int last;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int tile = ht.base[a.k_begin] + blockIdx.x;
   int k = a.k_begin;
   while (k + 1 < a.k_end && tile >= ht.base[k + 1]) ++k;
-  const int t0 = (tile - ht.base[k]) * HEAD_TILE;   // first sample inside the shard
-  const int64_t s0 = (int64_t)tab.start[k] + t0 + wave * SPW;
-  const int rows = min(max(tab.len[k] - t0 - wave * SPW, 0), SPW);   // samples of this wavefront
-  const bf16_t* h = reinterpret_cast<const bf16_t*>(a.h);
-  const int64_t last_row = max(rows - 1, 0);
-  const float label = rows > 0 ? a.labels[s0 + min(lane, (int)last_row)] : 0.0f;   // lanes 0 .. SPW-1: one sample each
+  const int t0 = (tile - ht.base[k]) * HEAD_TILE;            // first sample inside the shard
+  const int count = min(tab.len[k] - t0, HEAD_TILE);         // samples of the tile (at least one)
+  const int rows = min(max(count - wave * SPW, 0), SPW);     // samples of this wavefront
+  const int64_t s0 = (int64_t)tab.start[k] + t0;
+  int64_t row[SPW];                                          // (clamped into the tile)
+#pragma unroll
+  for (int r = 0; r < SPW; ++r) row[r] = s0 + min(wave * SPW + r, count - 1);
+  const TH* h = reinterpret_cast<const TH*>(a.h);
+  const float label = a.labels[s0 + min(wave * SPW + min(lane, SPW - 1), count - 1)];   // lanes 0 .. SPW-1: one sample each
+  const float bias = a.b[0];
 
-  float part[SPW] = {};
-  for (int j = lane * 8; j < a.width; j += 512) {
-    uint4 v[SPW];
+  float hv[SPW][CPL], w[CPL];
+  auto load = [&](int j0) {
 #pragma unroll
-    for (int r = 0; r < SPW; ++r)
-      v[r] = rows > 0 ? *reinterpret_cast<const uint4*>(h + (s0 + min((int64_t)r, last_row)) * a.ldh + j) : make_uint4(0, 0, 0, 0);
-    float w[8];
+    for (int i = 0; i < CPL; ++i) {
+      if (j0 + i * 64 >= a.width) {   // (the same for all lanes)
+        w[i] = 0.0f;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) w[e] = j + e < a.width ? a.w[j + e] : 0.0f;
+        for (int r = 0; r < SPW; ++r) hv[r][i] = 0.0f;
+      } else {
+        const int j = j0 + i * 64 + lane, jc = min(j, a.width - 1);
+        w[i] = a.w[jc];
 #pragma unroll
-    for (int r = 0; r < SPW; ++r) {
-      const uint32_t x[4] = {v[r].x, v[r].y, v[r].z, v[r].w};
+        for (int r = 0; r < SPW; ++r) hv[r][i] = to_f32(h[row[r] * a.ldh + jc]);
+        if (j >= a.width) {
+          w[i] = 0.0f;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        part[r] = fmaf(__uint_as_float(x[q] << 16), w[2 * q], part[r]);
-        part[r] = fmaf(__uint_as_float(x[q] & 0xFFFF0000u), w[2 * q + 1], part[r]);
+          for (int r = 0; r < SPW; ++r) hv[r][i] = 0.0f;
+        }
       }
     }
+  };
+  float part[SPW] = {};
+  for (int j0 = 0; j0 < a.width; j0 += CHUNK) {
+    load(j0);
+#pragma unroll
+    for (int i = 0; i < CPL; ++i)
+#pragma unroll
+      for (int r = 0; r < SPW; ++r) part[r] = fmaf(hv[r][i], w[i], part[r]);
   }
   float mine = 0.0f;   // lane r < SPW: logit of sample r
 #pragma unroll
@@ -94,7 +111,7 @@ __global__ __launch_bounds__(256) void head_tile_kernel(HeadArgs a, ShardTab tab
     const float z = wave_sum(part[r]);
     if (lane == r) mine = z;
   }
-  const float z = mine + a.b[0];
+  const float z = mine + bias;
   const float e = expf(-fabsf(z));
   const float sig = z >= 0.0f ? 1.0f / (1.0f + e) : e / (1.0f + e);
   const bool on = lane < rows;
@@ -112,65 +129,51 @@ __global__ __launch_bounds__(256) void head_tile_kernel(HeadArgs a, ShardTab tab
     sums[wave][1] = sl;
   }
   float* part_out = a.part + (int64_t)tile * a.ldpart;
-  const int cols = max(a.width, a.dh_cols);
-  for (int j0 = 0; j0 < cols; j0 += 512) {
-    const int j = j0 + lane * 8;
-    float g[8] = {};
-    if (j < a.width) {
-      float w[8];
+  for (int j0 = 0; j0 < a.width; j0 += CHUNK) {   // (dh_cols <= width)
+    if (a.width > CHUNK) load(j0);
 #pragma unroll
-      for (int q = 0; q < 8; ++q) w[q] = j + q < a.width ? a.w[j + q] : 0.0f;
+    for (int i = 0; i < CPL; ++i) {
+      const int j = j0 + i * 64 + lane;
+      float g = 0.0f;
 #pragma unroll
       for (int r = 0; r < SPW; ++r)
         if (r < rows) {
-          const uint4 v = *reinterpret_cast<const uint4*>(h + (s0 + r) * a.ldh + j);
-          const uint32_t x[4] = {v.x, v.y, v.z, v.w};
-          float d[8];
-#pragma unroll
-          for (int q = 0; q < 8; ++q) {
-            const float hv = (q & 1) ? __uint_as_float(x[q >> 1] & 0xFFFF0000u) : __uint_as_float(x[q >> 1] << 16);
-            g[q] = fmaf(hv, dz[r], g[q]);
-            d[q] = (!a.relu || hv > 0.0f) ? dz[r] * w[q] : 0.0f;
-          }
-          TD* dst = reinterpret_cast<TD*>(a.dh) + (s0 + r) * a.lddh + j;
-          if (sizeof(TD) == 2) {   // (the gradient of a hidden activation: its width is a multiple of 8)
-            *reinterpret_cast<uint4*>(dst) = make_uint4((uint32_t)f2bf(d[0]) | ((uint32_t)f2bf(d[1]) << 16),
-                                                        (uint32_t)f2bf(d[2]) | ((uint32_t)f2bf(d[3]) << 16),
-                                                        (uint32_t)f2bf(d[4]) | ((uint32_t)f2bf(d[5]) << 16),
-                                                        (uint32_t)f2bf(d[6]) | ((uint32_t)f2bf(d[7]) << 16));
-          } else {
-#pragma unroll
-            for (int q = 0; q < 8; ++q)
-              if (j + q < a.dh_cols) dst[q] = from_f32<TD>(d[q]);
-          }
+          g = fmaf(hv[r][i], dz[r], g);
+          const float d = (!a.relu || hv[r][i] > 0.0f) ? dz[r] * w[i] : 0.0f;
+          if (j < a.dh_cols) reinterpret_cast<TD*>(a.dh)[row[r] * a.lddh + j] = from_f32<TD>(d);
         }
+      if (j0 + i * 64 < a.width) col[wave][i * 64 + lane] = g;
     }
-    *reinterpret_cast<float4*>(&col[wave][lane * 8]) = make_float4(g[0], g[1], g[2], g[3]);
-    *reinterpret_cast<float4*>(&col[wave][lane * 8 + 4]) = make_float4(g[4], g[5], g[6], g[7]);
     __syncthreads();
-    for (int q = threadIdx.x; q < 512 && j0 + q < a.width; q += 256)
+    for (int q = threadIdx.x; q < CHUNK && j0 + q < a.width; q += 256)
       part_out[j0 + q] = (col[0][q] + col[1][q]) + (col[2][q] + col[3][q]);
     __syncthreads();
   }
   if (threadIdx.x == 0) {
-    // agent-scope stores: the block that adds them up may run on another XCD
+    // The block that adds the losses up may run on another XCD: stores that go past this XCD's L2, waited for
+    // before this block is counted.  (A release fence instead would write back all that L2 holds of the
+    // products before this kernel.)
     __hip_atomic_store(part_out + a.width, (sums[0][0] + sums[1][0]) + (sums[2][0] + sums[3][0]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(part_out + a.width + 1, (sums[0][1] + sums[1][1]) + (sums[2][1] + sums[3][1]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    last = __hip_atomic_fetch_add(a.done, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    const int tiles = ht.base[k + 1] - ht.base[k];
+    last = __hip_atomic_fetch_add(a.done + k, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == tiles - 1;
+  }
+  if (blockIdx.x == 0 && a.k_begin + (int)threadIdx.x < a.k_end && tab.len[a.k_begin + threadIdx.x] == 0) {   // shards without samples
+    a.loss_k[a.k_begin + threadIdx.x] = 0.0f;
+    if (a.loss_out) a.loss_out[threadIdx.x] = 0.0f;
   }
   __syncthreads();
-  if (!last) return;
-  if (threadIdx.x == 0) __hip_atomic_store(a.done, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  for (int q = a.k_begin + wave; q < a.k_end; q += 4) {
-    float l = 0.0f;
-    for (int t = ht.base[q] + lane; t < ht.base[q + 1]; t += 64)
-      l += __hip_atomic_load(a.part + (int64_t)t * a.ldpart + a.width + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    l = wave_sum(l);
-    if (lane == 0) {
-      const float lk = tab.len[q] > 0 ? l / (float)tab.len[q] : 0.0f;
-      a.loss_k[q] = lk;
-      if (a.loss_out) a.loss_out[q - a.k_begin] = lk;
-    }
+  if (!last || wave != 0) return;
+  float l = 0.0f;
+  for (int t = ht.base[k] + lane; t < ht.base[k + 1]; t += 64)
+    l += __hip_atomic_load(a.part + (int64_t)t * a.ldpart + a.width + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  l = wave_sum(l);
+  if (lane == 0) {
+    __hip_atomic_store(a.done + k, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const float lk = l / (float)tab.len[k];
+    a.loss_k[k] = lk;
+    if (a.loss_out) a.loss_out[k - a.k_begin] = lk;
   }
 }
 
@@ -269,8 +272,9 @@ hipError_t launch_head_tiles(const HeadArgs& a, const ShardTab& tab, hipStream_t
   const HeadTiles ht = head_tiles(tab);
   const int tiles = ht.base[a.k_end] - ht.base[a.k_begin];
   if (tiles == 0) hipLaunchKernelGGL(head_no_samples_kernel, dim3(1), dim3(64), 0, s, a);
-  else if (a.bf16_dh) hipLaunchKernelGGL(head_tile_kernel<bf16_t>, dim3(tiles), dim3(256), 0, s, a, tab, ht);
-  else hipLaunchKernelGGL(head_tile_kernel<float>, dim3(tiles), dim3(256), 0, s, a, tab, ht);
+  else if (a.bf16_dh) hipLaunchKernelGGL((head_tile_kernel<bf16_t, bf16_t>), dim3(tiles), dim3(256), 0, s, a, tab, ht);
+  else if (a.bf16_h) hipLaunchKernelGGL((head_tile_kernel<bf16_t, float>), dim3(tiles), dim3(256), 0, s, a, tab, ht);
+  else hipLaunchKernelGGL((head_tile_kernel<float, float>), dim3(tiles), dim3(256), 0, s, a, tab, ht);
   return hipGetLastError();
 }
 
