@@ -81,7 +81,7 @@ typedef struct antdt_model {
   int32_t num_dense;        /* dense features per sample (may be 0) */
   int32_t num_layers;       /* 1..ANTDT_MAX_LAYERS */
   int32_t layer_sizes[ANTDT_MAX_LAYERS + 1];
-  int32_t gemm_dtype;       /* ANTDT_F32: fp32 FMA GEMMs.  ANTDT_BF16: hidden-layer GEMM operands
+  int32_t gemm_dtype;       /* ANTDT_F32: fp32 products and sums.  ANTDT_BF16: hidden-layer GEMM operands
                                are bf16, accumulation fp32 (matrix cores); hidden widths must then
                                be multiples of 8 */
   float lr;                 /* Adagrad learning rate (tables and MLP) */

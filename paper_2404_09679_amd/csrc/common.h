@@ -124,11 +124,7 @@ hipError_t launch_fill_tables(void* tables, int bf16, int F, int64_t R, int D, f
 // ----------------------------------------------------------------- gemm.hip
 enum Epilogue { EPI_BIAS_RELU = 0, EPI_RELU_MASK = 1, EPI_PLAIN = 2 };
 
-// C[m, n] = sum_k A(m, k) * B(n, k).
-// fp32 path: a_kc: A(m,k) = A[m*lda + k], else A[k*lda + m]; b_kc likewise for B; with
-// `grouped`, group g (blockIdx.z) contracts over rows [tab.start[k0+g], +tab.len[k0+g]) of A
-// and B (both not *_kc) and writes C + (k0+g)*group_stride.
-// bf16 path: A(m,k) = A[m*lda + k]; B(n,k) = B[n*ldb + k] (b_kc) or B[k*ldb + n]; not grouped.
+// C[m, n] = sum_k A(m, k) * B(n, k): A(m,k) = A[m*lda + k]; B(n,k) = B[n*ldb + k] (b_kc) or B[k*ldb + n].
 struct GemmArgs {
   const void* A;
   const void* B;
@@ -137,13 +133,11 @@ struct GemmArgs {
   const void* mask;    // EPI_RELU_MASK: activations [M, ldmask], C = acc where mask > 0 else 0
   int64_t lda, ldb, ldc, ldmask;
   int32_t M, N, K;
-  int32_t a_kc, b_kc, epi;
+  int32_t b_kc, epi;
   int32_t bf16_in;     // operands (and mask) are bf16, else fp32
   int32_t bf16_out;    // C is bf16, else fp32
-  int32_t grouped, k0, groups;
-  int64_t group_stride;
 };
-hipError_t launch_gemm(const GemmArgs& a, const ShardTab& tab, hipStream_t s);
+hipError_t launch_gemm(const GemmArgs& a, hipStream_t s);
 
 // Sample ranges (shards; neighbours of equal weight merged) in sample order, with their aggregation
 // weights, and the partial sums that the loss kernel left for them.
@@ -153,16 +147,17 @@ struct KSegments {
   int32_t ts[ANTDT_MAX_SHARDS], te[ANTDT_MAX_SHARDS];   // tiles of the loss kernel [ts, te)
   float w[ANTDT_MAX_SHARDS];
 };
-// Weight gradients of all layers of a bf16 model in one launch (see wgrad_kernel): per range written to
+// Weight gradients of all layers in one launch (see wgrad_kernel, wgrad_f32_kernel): per range written to
 // the shards' flat gradients, or aggregated and applied (Adagrad) on the spot, in which case neither
 // the per-shard nor the aggregated gradient goes to memory.
 struct WgradArgs {
   int32_t n_layers;                    // hidden layers
-  const bf16_t* A[ANTDT_MAX_LAYERS];   // activations [samples, lda], M columns
-  const bf16_t* B[ANTDT_MAX_LAYERS];   // pre-activation gradients [samples, ldb], N columns
+  int32_t bf16;                        // type of A and B
+  const void* A[ANTDT_MAX_LAYERS];     // activations [samples, lda], M columns
+  const void* B[ANTDT_MAX_LAYERS];     // pre-activation gradients [samples, ldb], N columns
   int32_t M[ANTDT_MAX_LAYERS], N[ANTDT_MAX_LAYERS], lda[ANTDT_MAX_LAYERS], ldb[ANTDT_MAX_LAYERS];
   int64_t w_off[ANTDT_MAX_LAYERS];     // W_l inside the flat parameters, [M, N] then the bias [N]
-  bf16_t* wb[ANTDT_MAX_LAYERS];        // bf16 copy of W_l, [rows padded, N]
+  bf16_t* wb[ANTDT_MAX_LAYERS];        // bf16 models: copy of W_l, [rows padded, N]
   int32_t tile_base[ANTDT_MAX_LAYERS + 1];
   int32_t tiles_n[ANTDT_MAX_LAYERS];
   // last layer (one output): the loss kernel's sums over its tiles of samples
@@ -191,22 +186,17 @@ struct HeadArgs {
   const float* w;       // [width] last-layer weight
   const float* b;       // [1]
   const float* labels;  // [B]
-  float* z;             // [B]
-  float* loss_s;        // [B] per-sample loss
-  float* dz;            // [B] d(mean shard loss)/dz
   void* dh;             // [B, lddh] gradient w.r.t. h (masked by h > 0 when `relu`), or fp32 dX
   int64_t ldh, lddh;
   int32_t width, dh_cols, relu, bf16_h, bf16_dh;
   int32_t k_begin, k_end;
-  // bf16 models: the sums over the samples are formed along the way, per tile of samples of one shard
+  // the sums over the samples are formed along the way, per tile of samples of one shard
   float* part;          // [tiles, ldpart] sum of dz * h per column; column `width`: sum of dz, `width` + 1: of the losses
   int64_t ldpart;
   int32_t* done;        // [K] blocks of each shard that have finished (0 between launches)
   float* loss_k;        // workspace [K]
   float* loss_out;      // caller's buffer or NULL; element (k - k_begin)
 };
-hipError_t launch_head(const HeadArgs& a, const ShardTab& tab, hipStream_t s);
-
 // Tiles of the loss kernel: HEAD_TILE consecutive samples of one shard.  tile_base[k] = first tile of shard k.
 constexpr int HEAD_TILE = 16;
 struct HeadTiles {
@@ -221,26 +211,6 @@ inline HeadTiles head_tiles(const ShardTab& tab) {
 }
 hipError_t launch_head_tiles(const HeadArgs& a, const ShardTab& tab, hipStream_t s);
 hipError_t launch_zero_words(int32_t* p, int n, hipStream_t s);
-
-struct HeadReduceArgs {
-  const void* h;
-  const float* dz;
-  const float* loss_s;
-  float* grads;         // [K, P] per-shard flat dense gradients
-  float* loss_k;        // workspace [K]
-  float* loss_out;      // caller's buffer or NULL; element (k - k_begin)
-  int64_t ldh, P, w_off, b_off;
-  int32_t width, bf16_h, k_begin, k_end;
-};
-hipError_t launch_head_reduce(const HeadReduceArgs& a, const ShardTab& tab, hipStream_t s);
-
-struct BiasGradArgs {   // db[k][o] = sum over the shard's samples of dh[s, o]
-  const void* dh;
-  float* grads;
-  int64_t lddh, P, b_off;
-  int32_t width, bf16_dh, k_begin, k_end;
-};
-hipError_t launch_bias_grad(const BiasGradArgs& a, const ShardTab& tab, hipStream_t s);
 
 // ------------------------------------------------------------- coalesce.hip
 // Keys per sort tile (one block of 512 threads, ANTDT_SORT_TILE / 512 keys per thread).

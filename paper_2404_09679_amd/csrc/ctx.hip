@@ -112,7 +112,7 @@ struct antdt_ctx {
   char* x = nullptr;
   char* h[ANTDT_MAX_LAYERS] = {};
   char* dh[ANTDT_MAX_LAYERS] = {};
-  float *z = nullptr, *loss_s = nullptr, *dz = nullptr, *loss_k = nullptr, *dx = nullptr;
+  float *loss_k = nullptr, *dx = nullptr;
   float *shard_grads = nullptr, *g_dense = nullptr, *sample_w = nullptr, *G = nullptr;
   bf16_t* wb[ANTDT_MAX_LAYERS] = {};     // bf16 W_l as [in (padded), out]: operand of the forward product and the data gradient
   bf16_t* wb0_alt = nullptr;             // second buffer for W_0: the fused dense update writes the new copy there
@@ -216,9 +216,6 @@ static size_t carve(antdt_ctx* c, char* base) {
     c->h[l] = take((size_t)Bm * c->width[l] * c->act_size);
     c->dh[l] = take((size_t)Bm * c->width[l] * c->act_size);
   }
-  c->z = (float*)take(Bm * 4);
-  c->loss_s = (float*)take(Bm * 4);
-  c->dz = (float*)take(Bm * 4);
   c->sample_w = (float*)take(Bm * 4);
   c->loss_k = (float*)take(K * 4);
   c->dx = (float*)take((size_t)Bm * c->FD * 4);
@@ -230,8 +227,8 @@ static size_t carve(antdt_ctx* c, char* base) {
       c->wb[l] = (bf16_t*)take((size_t)rows * c->width[l + 1] * 2);
       if (l == 0) c->wb0_alt = (bf16_t*)take((size_t)rows * c->width[l + 1] * 2);
     }
-    c->head_part = (float*)take((size_t)(Bm / HEAD_TILE + K) * c->ldpart * 4);
   }
+  c->head_part = (float*)take((size_t)(Bm / HEAD_TILE + K) * c->ldpart * 4);
   c->head_done = (int32_t*)take((size_t)K * 4);
   c->lookup_sample = (int32_t*)take((size_t)N * 4);
   for (int i = 0; i < 2; ++i) {
@@ -687,30 +684,13 @@ static int build_coalescing(antdt_ctx* c, const int32_t* ids, const int32_t* pay
   return ANTDT_OK;
 }
 
-// Per-shard weight gradient of hidden layer l of an fp32 model for shards [k0, k1), one grouped product on `ws`.
-static int shard_weight_gradient_f32(antdt_ctx* c, int l, int k0, int k1, hipStream_t ws) {
-  Profiler* pr = prof_of(c);
-  GemmArgs g;
-  memset(&g, 0, sizeof(g));
-  // dW_l[k] = act_l^T dh_{l+1} over the shard's samples
-  g.A = l == 0 ? c->x : c->h[l]; g.lda = l == 0 ? c->ldx : c->width[l]; g.a_kc = 0;
-  g.B = c->dh[l + 1]; g.ldb = c->width[l + 1]; g.b_kc = 0;
-  g.M = c->width[l];
-  g.C = c->shard_grads + c->w_off[l]; g.ldc = c->width[l + 1];
-  g.N = c->width[l + 1]; g.K = 0;
-  g.epi = EPI_PLAIN;
-  g.grouped = 1; g.k0 = k0; g.groups = k1 - k0; g.group_stride = c->Pstride;
-  ProfScope ps(pr, KID_GEMM_WGRAD, ws);
-  HIP_TRY(c, launch_gemm(g, c->tab, ws));
-  return ANTDT_OK;
-}
-
 static void fill_wgrad_args(antdt_ctx* c, WgradArgs& u) {
   memset(&u, 0, sizeof(u));
   u.n_layers = c->L - 1;
+  u.bf16 = c->act_bf16;
   for (int l = 0; l + 1 < c->L; ++l) {
-    u.A[l] = (const bf16_t*)(l == 0 ? c->x : c->h[l]); u.lda[l] = l == 0 ? c->ldx : c->width[l];
-    u.B[l] = (const bf16_t*)c->dh[l + 1]; u.ldb[l] = c->width[l + 1];
+    u.A[l] = l == 0 ? c->x : c->h[l]; u.lda[l] = l == 0 ? c->ldx : c->width[l];
+    u.B[l] = c->dh[l + 1]; u.ldb[l] = c->width[l + 1];
     u.M[l] = c->width[l]; u.N[l] = c->width[l + 1];
     u.w_off[l] = c->w_off[l]; u.wb[l] = l == 0 ? c->wb0_alt : c->wb[l];
   }
@@ -719,7 +699,7 @@ static void fill_wgrad_args(antdt_ctx* c, WgradArgs& u) {
   u.grads = c->shard_grads; u.stride = c->Pstride;
 }
 
-// Per-shard gradients of all dense layers of a bf16 model for shards [k0, k1), one launch on `ws`.
+// Per-shard gradients of all dense layers for shards [k0, k1), one launch on `ws`.
 static int shard_weight_gradients(antdt_ctx* c, int k0, int k1, hipStream_t ws) {
   WgradArgs u;
   fill_wgrad_args(c, u);
@@ -812,7 +792,7 @@ static int worker_range(antdt_ctx* c, int k0, int k1, float* loss_out, hipStream
   for (int l = 0; l + 1 < L; ++l) {  // hidden layers
     GemmArgs g;
     memset(&g, 0, sizeof(g));
-    g.A = act(l) + s0 * ld(l) * es; g.lda = ld(l); g.a_kc = 1;
+    g.A = act(l) + s0 * ld(l) * es; g.lda = ld(l);
     g.C = c->h[l + 1] + s0 * c->width[l + 1] * es; g.ldc = c->width[l + 1];
     g.bias = c->params + c->b_off[l];
     g.M = (int32_t)ns; g.N = c->width[l + 1];
@@ -824,7 +804,7 @@ static int worker_range(antdt_ctx* c, int k0, int k1, float* loss_out, hipStream
       g.B = c->params + c->w_off[l]; g.ldb = c->width[l + 1]; g.b_kc = 0;
     }
     g.epi = EPI_BIAS_RELU; g.bf16_in = c->act_bf16; g.bf16_out = c->act_bf16;
-    HIP_TRY(c, launch_gemm(g, tab, s));
+    HIP_TRY(c, launch_gemm(g, s));
   }
   fwd_scope.close();
   {
@@ -832,7 +812,7 @@ static int worker_range(antdt_ctx* c, int k0, int k1, float* loss_out, hipStream
     memset(&a, 0, sizeof(a));
     a.h = act(L - 1); a.ldh = ld(L - 1); a.width = c->width[L - 1];
     a.w = c->params + c->w_off[L - 1]; a.b = c->params + c->b_off[L - 1];
-    a.labels = c->labels; a.z = c->z; a.loss_s = c->loss_s; a.dz = c->dz;
+    a.labels = c->labels;
     a.bf16_h = c->act_bf16;
     if (L > 1) {
       a.dh = c->dh[L - 1]; a.lddh = c->width[L - 1]; a.dh_cols = c->width[L - 1]; a.relu = 1; a.bf16_dh = c->act_bf16;
@@ -842,95 +822,52 @@ static int worker_range(antdt_ctx* c, int k0, int k1, float* loss_out, hipStream
     a.k_begin = k0; a.k_end = k1;
     a.part = c->head_part; a.ldpart = c->ldpart; a.done = c->head_done;
     a.loss_k = c->loss_k; a.loss_out = loss_out;
-    {
-      ProfScope ps(pr, KID_HEAD, s);
-      if (c->act_bf16) HIP_TRY(c, launch_head_tiles(a, tab, s));
-      else HIP_TRY(c, launch_head(a, tab, s));
-    }
-    if (!c->act_bf16) {
-      HeadReduceArgs r;
-      memset(&r, 0, sizeof(r));
-      r.h = act(L - 1); r.ldh = ld(L - 1); r.width = c->width[L - 1]; r.bf16_h = 0;
-      r.dz = c->dz; r.loss_s = c->loss_s; r.grads = c->shard_grads; r.loss_k = c->loss_k; r.loss_out = loss_out;
-      r.P = c->Pstride; r.w_off = c->w_off[L - 1]; r.b_off = c->b_off[L - 1]; r.k_begin = k0; r.k_end = k1;
-      ProfScope ps(pr, KID_HEAD_REDUCE, s);
-      HIP_TRY(c, launch_head_reduce(r, tab, s));
-    }
+    ProfScope ps(pr, KID_HEAD, s);
+    HIP_TRY(c, launch_head_tiles(a, tab, s));
   }
-  // Backward.  The data-gradient chain dH_{l+1} -> dH_l stays on the launch stream; the weight
-  // gradient of layer l needs dH_{l+1} but nothing needs it before the dense update, so it goes
-  // to its own stream and runs beside the rest of the chain and the sparse reduction.
-  hipStream_t ws = wgrad_stream(c) ? wgrad_stream(c) : s;
-  // With bf16 products and a weight-gradient stream the weight gradients are not computed here
-  // at all: apply_update forms them inside the dense update (aggregated over the shards in
-  // registers, never written per shard), and this step only records when their operands are
-  // complete.  The per-shard gradients of the contract are computed when a view asks for them.
+  // Backward.  The data-gradient chain dH_{l+1} -> dH_l stays on the launch stream; nothing needs the weight
+  // gradients before the dense update.  With bf16 products they are not computed here at all, unless the
+  // caller asked for them or the library may have no streams of its own: apply_update forms them inside the
+  // dense update (aggregated over the shards in registers, never written per shard), and this step only
+  // records when their operands are complete; the per-shard gradients of the contract are computed when a
+  // view asks for them.  fp32 models are small: their per-shard gradients are one short launch here.
+  hipStream_t ws = c->act_bf16 && wgrad_stream(c) ? wgrad_stream(c) : s;
   const bool deferred = c->act_bf16 && c->wside && !c->static_bound && !c->eager_wgrad;
   c->wgrad_deferred = deferred;
   c->shard_grads_done = false;
   // The event behind the last operand of the weight gradients (with up to one hidden layer the loss kernel
   // writes it, else the data gradient of layer 1).
-  const bool mark = c->act_bf16 && (deferred || ws != s);
+  const bool mark = deferred || ws != s;
   if (mark && L <= 2) HIP_TRY(c, hipEventRecord(c->ev_dh[0], s));
-  ProfScope bwd_scope(c->act_bf16 && L > 1 ? pr : nullptr, KID_GEMM_BWD, s);
+  ProfScope bwd_scope(L > 1 ? pr : nullptr, KID_GEMM_BWD, s);
   bwd_scope.launches(L - 1);
-  Profiler* pr_each = c->act_bf16 ? nullptr : pr;  // the fp32 path has other kernels in between
-  // An event record costs the launch stream about as much as a small kernel, so the weight
-  // gradients are released in pairs: after the data gradient of layer l both dW_l (needs
-  // dH_{l+1}) and dW_{l-1} (needs dH_l) can start.
-  int next_w = L - 2;  // highest layer whose weight gradient is not launched yet
-  for (int l = L - 2; l >= 0; --l) {
-    if (!c->act_bf16) {
-      BiasGradArgs b;
-      memset(&b, 0, sizeof(b));
-      b.dh = c->dh[l + 1]; b.lddh = c->width[l + 1]; b.width = c->width[l + 1]; b.bf16_dh = 0;
-      b.grads = c->shard_grads; b.P = c->Pstride; b.b_off = c->b_off[l]; b.k_begin = k0; b.k_end = k1;
-      ProfScope ps(pr, KID_BIAS_GRAD, s);
-      HIP_TRY(c, launch_bias_grad(b, tab, s));
+  for (int l = L - 2; l >= 0; --l) {   // gradient w.r.t. act_l: through W_l, then the ReLU of layer l-1 (none for the input)
+    GemmArgs g;
+    memset(&g, 0, sizeof(g));
+    g.A = c->dh[l + 1] + s0 * c->width[l + 1] * es; g.lda = c->width[l + 1];
+    g.B = weight(l); g.ldb = c->width[l + 1]; g.b_kc = 1;
+    g.M = (int32_t)ns; g.K = c->width[l + 1];
+    g.bf16_in = c->act_bf16;
+    if (l > 0) {
+      g.C = c->dh[l] + s0 * c->width[l] * es; g.ldc = c->width[l]; g.N = c->width[l];
+      g.mask = c->h[l] + s0 * c->width[l] * es; g.ldmask = c->width[l];
+      g.epi = EPI_RELU_MASK; g.bf16_out = c->act_bf16;
+    } else {
+      g.C = c->dx + s0 * c->FD; g.ldc = c->FD; g.N = c->FD;
+      g.epi = EPI_PLAIN; g.bf16_out = 0;
     }
-    {  // gradient w.r.t. act_l: through W_l, then the ReLU of layer l-1 (none for the input)
-      GemmArgs g;
-      memset(&g, 0, sizeof(g));
-      g.A = c->dh[l + 1] + s0 * c->width[l + 1] * es; g.lda = c->width[l + 1]; g.a_kc = 1;
-      g.B = weight(l); g.ldb = c->width[l + 1]; g.b_kc = 1;
-      g.M = (int32_t)ns; g.K = c->width[l + 1];
-      g.bf16_in = c->act_bf16;
-      if (l > 0) {
-        g.C = c->dh[l] + s0 * c->width[l] * es; g.ldc = c->width[l]; g.N = c->width[l];
-        g.mask = c->h[l] + s0 * c->width[l] * es; g.ldmask = c->width[l];
-        g.epi = EPI_RELU_MASK; g.bf16_out = c->act_bf16;
-      } else {
-        g.C = c->dx + s0 * c->FD; g.ldc = c->FD; g.N = c->FD;
-        g.epi = EPI_PLAIN; g.bf16_out = 0;
-      }
-      ProfScope ps(pr_each, KID_GEMM_DGRAD, s);
-      HIP_TRY(c, launch_gemm(g, tab, s));
-    }
-    if (c->act_bf16) {
-      if (l == 1 && mark) HIP_TRY(c, hipEventRecord(c->ev_dh[0], s));
-      continue;
-    }
-    const bool release = l == 0 || ((L - 2 - l) & 1) == 0;
-    if (release) {
-      if (ws != s) {
-        HIP_TRY(c, hipEventRecord(c->ev_dh[l], s));
-        HIP_TRY(c, hipStreamWaitEvent(ws, c->ev_dh[l], 0));
-      }
-      for (const int last = l > 0 ? l - 1 : 0; next_w >= last; --next_w) {
-        const int rc = shard_weight_gradient_f32(c, next_w, k0, k1, ws);
-        if (rc) return rc;
-      }
-    }
+    HIP_TRY(c, launch_gemm(g, s));
+    if (l == 1 && mark) HIP_TRY(c, hipEventRecord(c->ev_dh[0], s));
   }
   bwd_scope.close();
-  if (c->act_bf16 && !deferred) {
+  if (!deferred) {
     if (ws != s) HIP_TRY(c, hipStreamWaitEvent(ws, c->ev_dh[0], 0));
     const int rc = shard_weight_gradients(c, k0, k1, ws);
     if (rc) return rc;
-  }
-  if ((L > 1 || c->act_bf16) && ws != s && !deferred) {
-    HIP_TRY(c, hipEventRecord(c->ev_wgrad, ws));
-    c->wgrad_pending = true;
+    if (ws != s) {
+      HIP_TRY(c, hipEventRecord(c->ev_wgrad, ws));
+      c->wgrad_pending = true;
+    }
   }
   for (int k = k0; k < k1; ++k) c->stepped[k] = true;
   if (c->stage == ST_AGGREGATED) c->stage = ST_BATCH;

@@ -1,18 +1,13 @@
 // MLP matrix products of the worker step (forward, data gradient, weight gradient).
 //   bf16 operands / fp32 accumulate: LDS-tiled kernels on the gfx950 matrix cores (mfma.h);
-//   fp32: a plain LDS-tiled FMA kernel (small models, exactness checks).
+//   fp32 operands: matrix cores as well (v_mfma_f32_16x16x4_f32: fp32 products and sums), operands straight
+//   from memory to registers.
 #include <algorithm>
 
 #include "mfma.h"
 
 namespace antdt {
 namespace {
-
-__device__ __forceinline__ float epilogue_value(const GemmArgs& p, int64_t m, int n, float acc) {
-  if (p.epi == EPI_BIAS_RELU) return fmaxf(acc + p.bias[n], 0.0f);
-  if (p.epi == EPI_RELU_MASK) return reinterpret_cast<const float*>(p.mask)[m * p.ldmask + n] > 0.0f ? acc : 0.0f;
-  return acc;
-}
 
 __device__ __forceinline__ uint32_t pack2(float a, float b) { return (uint32_t)f2bf(a) | ((uint32_t)f2bf(b) << 16); }
 
@@ -233,7 +228,7 @@ __global__ __launch_bounds__(64 * WR * WC) void wgrad_kernel(WgradArgs u, KSegme
   zero_acc(totb);
   if (MODE != WGRAD_MANY) {
     const int q = MODE == WGRAD_STORE ? blockIdx.y : 0;
-    P::template run<true>(u.A[li], u.B[li], u.lda[li], u.ldb[li], M, N, m0, n0, seg.ks[q], seg.ke[q], lds, tot, totb[0], ones);
+    P::template run<true>(reinterpret_cast<const bf16_t*>(u.A[li]), reinterpret_cast<const bf16_t*>(u.B[li]), u.lda[li], u.ldb[li], M, N, m0, n0, seg.ks[q], seg.ke[q], lds, tot, totb[0], ones);
     if (MODE == WGRAD_ONE) {
       const float w = seg.w[0];
 #pragma unroll
@@ -250,7 +245,7 @@ __global__ __launch_bounds__(64 * WR * WC) void wgrad_kernel(WgradArgs u, KSegme
       f32x16 acc[TM][TN], accb[1][TN];
       zero_acc(acc);
       zero_acc(accb);
-      P::template run<true>(u.A[li], u.B[li], u.lda[li], u.ldb[li], M, N, m0, n0, seg.ks[q], seg.ke[q], lds, acc, accb[0], ones);
+      P::template run<true>(reinterpret_cast<const bf16_t*>(u.A[li]), reinterpret_cast<const bf16_t*>(u.B[li]), u.lda[li], u.ldb[li], M, N, m0, n0, seg.ks[q], seg.ke[q], lds, acc, accb[0], ones);
       const float w = seg.w[q];
 #pragma unroll
       for (int j = 0; j < TN; ++j)
@@ -321,60 +316,163 @@ __global__ __launch_bounds__(64 * WR * WC) void wgrad_kernel(WgradArgs u, KSegme
   }
 }
 
-// fp32 tiled FMA kernel with arbitrary operand orientation: 64x64 block tile, 4x4 per thread.
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs p, ShardTab tab) {
-  constexpr int T = 64, KT = 16;
-  __shared__ float As[KT][T + 4];
-  __shared__ float Bs[KT][T + 4];
-  const float* A = reinterpret_cast<const float*>(p.A);
-  const float* B = reinterpret_cast<const float*>(p.B);
-  char* C = reinterpret_cast<char*>(p.C);
-  int K = p.K;
-  if (p.grouped) {
-    const int k = p.k0 + blockIdx.z;
-    const int64_t r0 = tab.start[k];
-    K = tab.len[k];
-    A += r0 * p.lda;
-    B += r0 * p.ldb;
-    C += (int64_t)k * p.group_stride * 4;
+// ---------------------------------------------------------------- fp32 products
+// One wavefront computes TM x TN tiles of 16 x 16 with v_mfma_f32_16x16x4_f32 (fp32 throughout, twice the rate
+// of the vector FMAs).  A step is 16 contraction slots, four MFMAs: lane (l & 15) of quarter l >> 4 supplies the
+// slots 4 (l >> 4) .. + 3 of its row, one 16-byte load where the contraction index is contiguous, four loads
+// of 16 neighbouring rows each where it is not.  No LDS: the models that use fp32 products are small, their
+// products are bound by load latency and by how few tiles there are, so loads run D steps ahead and tiles
+// stay small; what neighbouring wavefronts share comes from the L1.
+// (Through LDS in 64 x 64 tiles, one step in flight: 1500 x 256 x 397 91 us, here 13; 1500 x 384 x 256 110 us, here 16.)
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+template <int T, bool KC, bool VEC>   // KC: contraction index contiguous; VEC: rows 16-byte aligned
+struct F32Operand {
+  const float* row[T];
+  int64_t ld;
+  __device__ __forceinline__ F32Operand(const float* x, int64_t ld_, int r0, int rows, int lane) : ld(ld_) {
+#pragma unroll
+    for (int t = 0; t < T; ++t) {   // rows past the end repeat the last one (their products are not stored)
+      const int r = min(r0 + 16 * t + (lane & 15), rows - 1);
+      row[t] = KC ? x + (int64_t)r * ld : x + r;
+    }
   }
-  const int64_t sAm = p.a_kc ? p.lda : 1, sAk = p.a_kc ? 1 : p.lda;
-  const int64_t sBn = p.b_kc ? p.ldb : 1, sBk = p.b_kc ? 1 : p.ldb;
-  const int m0 = blockIdx.y * T, n0 = blockIdx.x * T;
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += KT) {
+  // Slots past the end are read at the last slot (or the last whole vector) instead and cleared by `clip`.
+  __device__ __forceinline__ void load(int step, int K, int lane, float (&f)[T][4]) const {
+    const int k = step * 16 + 4 * (lane >> 4);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int e = tid + i * 256;
-      // contiguous index runs fastest across threads for either orientation
-      const int kk = p.a_kc ? (e & 15) : (e >> 6), mm = p.a_kc ? (e >> 4) : (e & 63);
-      As[kk][mm] = (m0 + mm < p.M && k0 + kk < K) ? A[(int64_t)(m0 + mm) * sAm + (int64_t)(k0 + kk) * sAk] : 0.0f;
-      const int kb = p.b_kc ? (e & 15) : (e >> 6), nn = p.b_kc ? (e >> 4) : (e & 63);
-      Bs[kb][nn] = (n0 + nn < p.N && k0 + kb < K) ? B[(int64_t)(n0 + nn) * sBn + (int64_t)(k0 + kb) * sBk] : 0.0f;
+    for (int t = 0; t < T; ++t) {
+      if (KC && VEC) {
+        const float4 v = *reinterpret_cast<const float4*>(row[t] + min(k, (K - 1) & ~3));
+        f[t][0] = v.x; f[t][1] = v.y; f[t][2] = v.z; f[t][3] = v.w;
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) f[t][i] = row[t][KC ? (int64_t)min(k + i, K - 1) : (int64_t)min(k + i, K - 1) * ld];
+      }
     }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < KT; ++kk) {
-      float a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tx * 4 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
   }
+  static __device__ __forceinline__ void clip(int step, int K, int lane, float (&f)[T][4]) {
+    const int k = step * 16 + 4 * (lane >> 4);
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+    for (int t = 0; t < T; ++t)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int m = m0 + ty * 4 + i, n = n0 + tx * 4 + j;
-      if (m < p.M && n < p.N) reinterpret_cast<float*>(C)[(int64_t)m * p.ldc + n] = epilogue_value(p, m, n, acc[i][j]);
+      for (int i = 0; i < 4; ++i) f[t][i] = k + i < K ? f[t][i] : 0.0f;
+  }
+};
+
+// acc += A B^T over the steps first, first + stride, ... of the K contraction slots; with `ones`, sum_b also
+// receives the sums of B's rows (products with ones).  Result layout: lane l of acc[i][j] holds row l & 15
+// and the columns 4 (l >> 4) .. + 3 of tile (i, j).
+template <int TM, int TN, int D, bool ONES, typename OA, typename OB>
+__device__ __forceinline__ void f32_product(const OA& oa, const OB& ob, int K, int first, int stride, int lane,
+                                            f32x4 (&acc)[TM][TN], f32x4 (&sum_b)[TN], bool ones) {
+  if (K <= 0) return;
+  const int nk = (K + 15) / 16;
+  float a[D][TM][4], b[D][TN][4];
+#pragma unroll
+  for (int q = 0; q < D; ++q) {
+    oa.load(first + q * stride, K, lane, a[q]);
+    ob.load(first + q * stride, K, lane, b[q]);
+  }
+  for (int s = first; s < nk; s += D * stride) {
+#pragma unroll
+    for (int q = 0; q < D; ++q) {
+      const int step = s + q * stride;
+      if (step * 16 + 16 > K) {   // (uniform) partly or wholly past the end
+        OA::clip(step, K, lane, a[q]);
+        OB::clip(step, K, lane, b[q]);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[q][j][e], a[q][i][e], acc[i][j], 0, 0, 0);
+        if (ONES && ones) {
+#pragma unroll
+          for (int j = 0; j < TN; ++j)
+            sum_b[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[q][j][e], 1.0f, sum_b[j], 0, 0, 0);
+        }
+      }
+      oa.load(step + D * stride, K, lane, a[q]);
+      ob.load(step + D * stride, K, lane, b[q]);
     }
+  }
+}
+
+// C[m, n] = sum_k A[m * lda + k] B(n, k) with the epilogue of GemmArgs; four wavefronts per block, each a tile of
+// its own (neighbours along n first: they share the rows of A).
+template <int TM, int TN, int D, bool BKC, bool VA, bool VB>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs p, int tiles_n, int tiles) {
+  const int lane = threadIdx.x & 63;
+  const int id = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (id >= tiles) return;
+  const int m0 = id / tiles_n * (16 * TM), n0 = id % tiles_n * (16 * TN);
+  const F32Operand<TM, true, VA> oa(reinterpret_cast<const float*>(p.A), p.lda, m0, p.M, lane);
+  const F32Operand<TN, BKC, VB> ob(reinterpret_cast<const float*>(p.B), p.ldb, n0, p.N, lane);
+  f32x4 acc[TM][TN] = {}, none[TN];
+  f32_product<TM, TN, D, false>(oa, ob, p.K, 0, 1, lane, acc, none, false);
+  float* C = reinterpret_cast<float*>(p.C);
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      const int m = m0 + 16 * i + (lane & 15);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int n = n0 + 16 * j + 4 * (lane >> 4) + e;
+        if (m >= p.M || n >= p.N) continue;
+        float v = acc[i][j][e];
+        if (p.epi == EPI_BIAS_RELU) v = fmaxf(v + p.bias[n], 0.0f);
+        else if (p.epi == EPI_RELU_MASK) v = reinterpret_cast<const float*>(p.mask)[(int64_t)m * p.ldmask + n] > 0.0f ? v : 0.0f;
+        C[(int64_t)m * p.ldc + n] = v;
+      }
+    }
+}
+
+// Per-shard weight gradients of an fp32 model: tile blockIdx.x, shard blockIdx.y (wgrad_kernel's WGRAD_STORE).  The
+// four wavefronts of a block share one tile and take every fourth step of the contraction (over samples:
+// there are few tiles and the contraction is long); their sums are added in LDS.  397-256-128 model, 1500 samples
+// of five shards: 16 us, against 177 us for the four products and bias sums of one layer each before.
+template <int TM, int TN, int D>
+__global__ __launch_bounds__(256) void wgrad_f32_kernel(WgradArgs u, KSegments seg) {
+  constexpr int BM = 16 * TM, BN = 16 * TN, PITCH = BN + 4;
+  __shared__ __attribute__((aligned(16))) float red[4][(BM + 1) * PITCH];   // row BM: the bias gradient
+  if ((int)blockIdx.x >= u.tile_base[u.n_layers]) {
+    last_layer<WGRAD_STORE>(u, seg, blockIdx.x - u.tile_base[u.n_layers], reinterpret_cast<float(*)[64]>(&red[0][0]));
+    return;
+  }
+  int li = 0;
+  while (li + 1 < u.n_layers && (int)blockIdx.x >= u.tile_base[li + 1]) ++li;
+  const int pid = blockIdx.x - u.tile_base[li], q = blockIdx.y;
+  const int M = u.M[li], N = u.N[li];
+  const int m0 = (pid / u.tiles_n[li]) * BM, n0 = (pid % u.tiles_n[li]) * BN;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool ones = m0 == 0;
+  f32x4 acc[TM][TN] = {}, accb[TN] = {};
+  const float* A = reinterpret_cast<const float*>(u.A[li]) + (int64_t)seg.ks[q] * u.lda[li];
+  const float* B = reinterpret_cast<const float*>(u.B[li]) + (int64_t)seg.ks[q] * u.ldb[li];
+  const F32Operand<TM, false, false> oa(A, u.lda[li], m0, M, lane);
+  const F32Operand<TN, false, false> ob(B, u.ldb[li], n0, N, lane);
+  f32_product<TM, TN, D, true>(oa, ob, seg.ke[q] - seg.ks[q], wave, 4, lane, acc, accb, ones);
+  float* mine = red[wave];
+#pragma unroll
+  for (int j = 0; j < TN; ++j) {
+    const int c = 16 * j + 4 * (lane >> 4);
+#pragma unroll
+    for (int i = 0; i < TM; ++i) *reinterpret_cast<f32x4*>(mine + (16 * i + (lane & 15)) * PITCH + c) = acc[i][j];
+    if ((lane & 15) == 0) *reinterpret_cast<f32x4*>(mine + BM * PITCH + c) = accb[j];   // (all its rows are the same)
+  }
+  __syncthreads();
+  float* out = u.grads + (int64_t)(u.k0 + q) * u.stride + u.w_off[li];
+  for (int e = threadIdx.x; e < (BM + (ones ? 1 : 0)) * BN; e += 256) {
+    const int r = e / BN, c = e % BN, n = n0 + c;
+    const int m = r == BM ? M : m0 + r;   // the bias lies behind the weights
+    if (n >= N || (r < BM && m >= M)) continue;
+    const int o = r * PITCH + c;
+    out[(int64_t)m * N + n] = (red[0][o] + red[1][o]) + (red[2][o] + red[3][o]);
+  }
 }
 
 __global__ __launch_bounds__(256) void cast_bf16_kernel(CastArgs a) {
@@ -415,6 +513,49 @@ hipError_t launch_bf16_sized(const GemmArgs& a, hipStream_t s) {
   return launch_bf16<1, 1, 1, 1, 1, 128, 3, BS>(a, s);
 }
 
+template <int TM, int TN, int D>
+hipError_t launch_f32_tile(const GemmArgs& a, hipStream_t s) {
+  const int tiles_n = (a.N + 16 * TN - 1) / (16 * TN), tiles = (a.M + 16 * TM - 1) / (16 * TM) * tiles_n;
+  const dim3 grid((tiles + 3) / 4), block(256);
+  const bool va = (a.lda & 3) == 0 && (reinterpret_cast<uintptr_t>(a.A) & 15) == 0;
+  const bool vb = a.b_kc && (a.ldb & 3) == 0 && (reinterpret_cast<uintptr_t>(a.B) & 15) == 0;
+  if (a.b_kc) {
+    if (va && vb) hipLaunchKernelGGL((gemm_f32_kernel<TM, TN, D, true, true, true>), grid, block, 0, s, a, tiles_n, tiles);
+    else if (va) hipLaunchKernelGGL((gemm_f32_kernel<TM, TN, D, true, true, false>), grid, block, 0, s, a, tiles_n, tiles);
+    else hipLaunchKernelGGL((gemm_f32_kernel<TM, TN, D, true, false, false>), grid, block, 0, s, a, tiles_n, tiles);
+  } else {
+    if (va) hipLaunchKernelGGL((gemm_f32_kernel<TM, TN, D, false, true, false>), grid, block, 0, s, a, tiles_n, tiles);
+    else hipLaunchKernelGGL((gemm_f32_kernel<TM, TN, D, false, false, false>), grid, block, 0, s, a, tiles_n, tiles);
+  }
+  return hipGetLastError();
+}
+
+// 32 x 32 per wavefront (half the operand bytes of 16 x 16) where that leaves every SIMD of the 256 compute units
+// two wavefronts, else 16 x 16.  Every tile shape adds up the products in the same order.
+hipError_t launch_f32(const GemmArgs& a, hipStream_t s) {
+  if ((int64_t)((a.M + 31) / 32) * ((a.N + 31) / 32) >= 2048) return launch_f32_tile<2, 2, 2>(a, s);
+  return launch_f32_tile<1, 1, 4>(a, s);
+}
+
+template <int TM, int TN, int D>
+hipError_t launch_wgrad_f32_tile(const WgradArgs& a, const KSegments& seg, hipStream_t s) {
+  WgradArgs u = a;
+  u.tile_base[0] = 0;
+  for (int l = 0; l < u.n_layers; ++l) {
+    u.tiles_n[l] = (u.N[l] + 16 * TN - 1) / (16 * TN);
+    u.tile_base[l + 1] = u.tile_base[l] + (u.M[l] + 16 * TM - 1) / (16 * TM) * u.tiles_n[l];
+  }
+  hipLaunchKernelGGL((wgrad_f32_kernel<TM, TN, D>), dim3(u.tile_base[u.n_layers] + (u.width + 64) / 64, seg.n), dim3(256), 0, s, u, seg);
+  return hipGetLastError();
+}
+
+hipError_t launch_wgrad_f32(const WgradArgs& a, const KSegments& seg, hipStream_t s) {
+  int64_t blocks = 0;
+  for (int l = 0; l < a.n_layers; ++l) blocks += (int64_t)((a.M[l] + 31) / 32) * ((a.N[l] + 31) / 32);
+  if (blocks * seg.n >= 512) return launch_wgrad_f32_tile<2, 2, 2>(a, seg, s);
+  return launch_wgrad_f32_tile<1, 1, 4>(a, seg, s);
+}
+
 template <int TM, int TN, int WR, int WC, int BK, int STAGES, WgradMode MODE>
 hipError_t launch_wgrad_tile(const WgradArgs& a, const KSegments& seg, int groups, hipStream_t s) {
   typedef BlockProduct<TM, TN, WR, WC, 1, BK, STAGES, true, true> P;
@@ -448,22 +589,17 @@ hipError_t launch_wgrad_sized(const WgradArgs& a, const KSegments& seg, int grou
 
 }  // namespace
 
-hipError_t launch_gemm(const GemmArgs& a, const ShardTab& tab, hipStream_t s) {
+hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
   if (a.M <= 0 || a.N <= 0) return hipSuccess;
-  if (!a.bf16_in) {
-    const int groups = a.grouped ? a.groups : 1;
-    if (groups <= 0) return hipSuccess;
-    dim3 grid((a.N + 63) / 64, (a.M + 63) / 64, groups);
-    hipLaunchKernelGGL(gemm_f32_kernel, grid, dim3(256), 0, s, a, tab);
-    return hipGetLastError();
-  }
+  if (!a.bf16_in) return launch_f32(a, s);
   return a.b_kc ? launch_bf16_sized<false>(a, s) : launch_bf16_sized<true>(a, s);
 }
 
 hipError_t launch_wgrad(const WgradArgs& a, const KSegments& seg, bool store, hipStream_t s) {
   if (store && seg.n <= 0) return hipSuccess;
   for (int l = 0; l < a.n_layers; ++l)
-    if (a.M[l] <= 0 || a.N[l] <= 0 || (a.N[l] & 7)) return hipErrorInvalidValue;
+    if (a.M[l] <= 0 || a.N[l] <= 0 || (a.bf16 && (a.N[l] & 7))) return hipErrorInvalidValue;
+  if (!a.bf16) return store ? launch_wgrad_f32(a, seg, s) : hipErrorInvalidValue;
   if (store) return launch_wgrad_sized<WGRAD_STORE>(a, seg, seg.n, s);
   return seg.n == 1 ? launch_wgrad_sized<WGRAD_ONE>(a, seg, 1, s) : launch_wgrad_sized<WGRAD_MANY>(a, seg, 1, s);
 }

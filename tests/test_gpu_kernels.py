@@ -30,3 +30,13 @@ PRODUCT_SHAPES = [((1,), (8,)), ((20, 13), (40, 8)), ((513, 0, 199), (264, 72)),
 def test_bf16_product_tiles(sizes, hidden):
     cfg = _config(f"tiles-{sum(sizes)}", 400 + sum(sizes), layer_sizes=hidden, shard_sizes=sizes)
     check_iteration(cfg, sizes, tol=TOLBF, bf16_gemm_oracle=True, batched=True, nonzero_state=True)
+
+
+# the same for fp32 products: tiles of 16 and 32, widths that no vector load fits, fewer contraction slots than a step
+F32_SHAPES = [((1,), (7,)), ((15, 17), (33, 5)), ((513, 0, 199), (64, 19)), ((2600, 1501), (520, 36))]
+
+
+@pytest.mark.parametrize("sizes,hidden", F32_SHAPES, ids=[str(sum(s)) for s, _ in F32_SHAPES])
+def test_f32_product_tiles(sizes, hidden):
+    cfg = _config(f"f32-tiles-{sum(sizes)}", 500 + sum(sizes), layer_sizes=hidden, shard_sizes=sizes, gemm_dtype="f32")
+    check_iteration(cfg, sizes, tol=TOL32, batched=True, nonzero_state=True)
