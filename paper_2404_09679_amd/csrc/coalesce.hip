@@ -18,28 +18,39 @@ constexpr int SORT_TILE = ANTDT_SORT_TILE;            // keys per block
 constexpr int SORT_ITEMS = SORT_TILE / SORT_THREADS;
 constexpr int MAX_BINS = 1024;
 
+// Blocks of a launch of one block per tile (see tile_of_block).
+unsigned tile_grid(int total_tiles) { return 8u * ((total_tiles + 7) / 8); }
+
 __device__ __forceinline__ uint64_t lanemask_lt() {
   const unsigned lane = threadIdx.x & 63;
   return lane == 0 ? 0ull : (~0ull >> (64 - lane));
 }
 
-// Block -> (field, tile) for the kernels that walk the lookups of the fields tile by tile.  The
-// hardware hands block i to XCD i mod 8, and every XCD has an L2 of its own: the blocks whose index
-// is x modulo 8 take the tiles of the fields x, x + 8, x + 16, ..., so that every pass over a
-// field's lookups runs on one XCD.  The scattered 4-byte stores of a sort pass are then assembled
-// into full lines in that L2 (spread over eight L2s, each wrote its partial lines back: 3.7 times
-// the payload), and the next pass over the field finds them there.
-__device__ __forceinline__ bool field_tile_of_block(const TileBase& tb, int F, int& f, int& t) {
-  constexpr int G = ANTDT_MAX_FIELDS / 8;
-  const int x = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  const int32_t* cum = tb.xcum[x];  // (one row of the table: a single scalar load)
-  if (slot >= cum[G]) return false;
-  int j = 0;
-#pragma unroll
-  for (int i = 1; i < G; ++i) j += slot >= cum[i] ? 1 : 0;
-  f = x + 8 * j;
-  t = slot - cum[j];
-  return f < F;
+// Tile T of all fields' tiles -> (field, tile of the field): how many fields end at or before it, counted by the
+// lanes of the wavefront (one load of the table instead of a chain of them).
+__device__ __forceinline__ void field_of_tile(const TileBase& tb, int T, int& f, int& t) {
+  const int lane = threadIdx.x & 63;
+  static_assert(ANTDT_MAX_FIELDS == 128, "two table entries per lane");
+  const int t0 = tb.t[1 + lane], t1 = tb.t[65 + lane];
+  f = __builtin_amdgcn_readfirstlane(__popcll(__ballot(t0 <= T)) + __popcll(__ballot(t1 <= T)));
+  t = T - tb.t[f];
+}
+
+// Block -> (field, tile, part of the tile) for the kernels that walk the lookups of the fields tile by tile,
+// `parts` blocks per tile.  The hardware hands block i to XCD i mod 8, and every XCD has an L2 of its own: the
+// blocks whose index is x modulo 8 take the x-th eighth of all tiles, so that every pass over a field's lookups
+// runs on one XCD (two where a field crosses an eighth).  The scattered 4-byte stores of a sort pass are then
+// assembled into full lines in that L2 (spread over eight L2s, each wrote its partial lines back: 3.7 times
+// the payload), and the next pass over the field finds them there; so does the reduction with the field's
+// slice of the pooled gradients.
+__device__ __forceinline__ bool tile_of_block(const TileBase& tb, int F, int parts, int& f, int& t, int& part) {
+  const int total = tb.t[F], share = (total + 7) >> 3;
+  const int slot = (int)(blockIdx.x >> 3) / parts;
+  const int T = (int)(blockIdx.x & 7) * share + slot;
+  if (slot >= share || T >= total) return false;
+  part = (int)(blockIdx.x >> 3) % parts;
+  field_of_tile(tb, T, f, t);
+  return true;
 }
 
 // ----------------------------------------------------------------- sort
@@ -50,8 +61,8 @@ __device__ __forceinline__ bool field_tile_of_block(const TileBase& tb, int F, i
 __global__ __launch_bounds__(SORT_THREADS) void sort_hist_kernel(const int32_t* keys, uint32_t* hist,
                                                                  FieldPtr fp, TileBase tb, int F, int shift, int rb) {
   __shared__ uint32_t h[MAX_BINS];
-  int f, t;
-  if (!field_tile_of_block(tb, F, f, t)) return;
+  int f, t, part;
+  if (!tile_of_block(tb, F, 1, f, t, part)) return;
   const int nb = 1 << rb;
   const int64_t base = fp.p[f];
   const int nnz = (int)(fp.p[f + 1] - base);
@@ -73,11 +84,23 @@ __global__ __launch_bounds__(SORT_THREADS) void sort_hist_kernel(const int32_t* 
   for (int d = threadIdx.x; d < nb; d += SORT_THREADS) out[d] = h[d];
 }
 
+__device__ __forceinline__ void write_sample_weights(float* sample_w, const ShardTab& tab, int s) {
+  int k = 0;
+  while (k + 1 < tab.K && s >= tab.start[k + 1]) ++k;   // (an empty shard starts where the next one does)
+  if (s < tab.start[k] + tab.len[k]) sample_w[s] = tab.w[k];
+}
+
 // One block per field, one thread per digit: the counts of a digit are replaced by their
-// exclusive prefix over the tiles, and the digit totals by their exclusive prefix over digits.
-__global__ __launch_bounds__(MAX_BINS) void sort_scan_kernel(uint32_t* hist, uint32_t* digit_base, TileBase tb, int rb) {
+// exclusive prefix over the tiles, and the digit totals by their exclusive prefix over digits.  Further blocks
+// (first pass) write the aggregation weight of every sample.
+__global__ __launch_bounds__(MAX_BINS) void sort_scan_kernel(uint32_t* hist, uint32_t* digit_base, TileBase tb, int F, int rb,
+                                                             float* sample_w, ShardTab tab) {
   __shared__ uint32_t wsum[MAX_BINS / 64];
   const int f = blockIdx.x;
+  if (f >= F) {
+    write_sample_weights(sample_w, tab, (f - F) * MAX_BINS + (int)threadIdx.x);
+    return;
+  }
   const int tiles = tb.t[f + 1] - tb.t[f];
   const int nb = 1 << rb;
   const int d = threadIdx.x;
@@ -122,8 +145,8 @@ __global__ __launch_bounds__(SORT_THREADS) void sort_scatter_kernel(
     const uint32_t* digit_base, FieldPtr fp, TileBase tb, int F, int shift, int rb) {
   __shared__ uint32_t cnt[SORT_WAVES][MAX_BINS];
   __shared__ uint32_t gbase[MAX_BINS];
-  int f, t;
-  if (!field_tile_of_block(tb, F, f, t)) return;
+  int f, t, part;
+  if (!tile_of_block(tb, F, 1, f, t, part)) return;
   const int nb = 1 << rb;
   const int64_t base = fp.p[f];
   const int nnz = (int)(fp.p[f + 1] - base);
@@ -310,8 +333,8 @@ __device__ __forceinline__ bool is_head(const int32_t* key, int pos) {
 // Number of run heads in each tile of the sorted keys.
 __global__ __launch_bounds__(SORT_THREADS) void seg_heads_kernel(SegArgs a, FieldPtr fp, TileBase tb) {
   __shared__ int wsum[SORT_WAVES];
-  int f, t;
-  if (!field_tile_of_block(tb, a.F, f, t)) return;
+  int f, t, part;
+  if (!tile_of_block(tb, a.F, 1, f, t, part)) return;
   const int32_t* key = a.key + fp.p[f];
   const int nnz = (int)(fp.p[f + 1] - fp.p[f]);
   int c = 0;
@@ -331,9 +354,9 @@ __global__ __launch_bounds__(SORT_THREADS) void seg_heads_kernel(SegArgs a, Fiel
   }
 }
 
-// One block: exclusive prefix over all tiles (-> first unique of every tile and field),
-// the terminal segment offset of every field and the per-sample aggregation weight.
-__global__ __launch_bounds__(1024) void seg_scan_kernel(SegArgs a, FieldPtr fp, TileBase tb, ShardTab tab) {
+// One block: exclusive prefix over all tiles (-> first unique of every tile and field) and the terminal
+// segment offset of every field.
+__global__ __launch_bounds__(1024) void seg_scan_kernel(SegArgs a, FieldPtr fp, TileBase tb) {
   __shared__ int wsum[16];
   const int n = a.total_tiles;
   const int chunk = (n + 1023) / 1024;
@@ -369,17 +392,13 @@ __global__ __launch_bounds__(1024) void seg_scan_kernel(SegArgs a, FieldPtr fp, 
   for (int f = threadIdx.x; f <= a.F; f += 1024) a.ubase[f] = a.tile_heads[tb.t[f]];
   for (int f = threadIdx.x; f < a.F; f += 1024)
     a.segoff[a.tile_heads[tb.t[f + 1]] + f] = (int32_t)(fp.p[f + 1] - fp.p[f]);
-  for (int k = 0; k < tab.K; ++k) {
-    const float wk = tab.w[k];
-    for (int s = threadIdx.x; s < tab.len[k]; s += 1024) a.sample_w[tab.start[k] + s] = wk;
-  }
 }
 
 // Unique ids and segment offsets.  Thread j of a tile owns 8 consecutive sorted positions.
 __global__ __launch_bounds__(SORT_THREADS) void seg_emit_kernel(SegArgs a, FieldPtr fp, TileBase tb) {
   __shared__ int wsum[SORT_WAVES];
-  int f, t;
-  if (!field_tile_of_block(tb, a.F, f, t)) return;
+  int f, t, part;
+  if (!tile_of_block(tb, a.F, 1, f, t, part)) return;
   const int32_t* key = a.key + fp.p[f];
   const int nnz = (int)(fp.p[f + 1] - fp.p[f]);
   const int p0 = t * SORT_TILE + threadIdx.x * SORT_ITEMS;
@@ -403,165 +422,10 @@ __global__ __launch_bounds__(SORT_THREADS) void seg_emit_kernel(SegArgs a, Field
   for (int i = 0; i < SORT_ITEMS; ++i)
     if (flags & (1u << i)) {
       a.uniq[rank] = key[p0 + i];
-      a.ufield[rank] = f;
       a.segabs[rank] = (int32_t)fp.p[f] + p0 + i;
       a.segoff[rank + f] = p0 + i;
       ++rank;
     }
-}
-
-// Runs longer than the threshold are cut into chunks of `chunk` lookups; the list of such runs
-// and the list of their chunks are built here, beside the run table, so that the reduction
-// kernel finds them ready.  Both lists are in run order (count per block of runs, prefix sum
-// over the blocks, write): consecutive entries belong to the same field, which is what lets the
-// reduction give each of its eight shares a contiguous piece of every list.
-constexpr int QUEUE_RUNS = 8;  // runs per thread
-static_assert(256 * QUEUE_RUNS == ANTDT_QUEUE_BLOCK_RUNS, "queue block size");
-constexpr int SHARES = 8;      // one per XCD: blocks are handed to the XCDs round robin
-
-// Long runs and chunks among the block's runs; lengths of the thread's runs in len[].
-__device__ __forceinline__ void queue_count(const SegArgs& a, int U, int64_t u0, int (&len)[QUEUE_RUNS], int& nl, int& nc) {
-  nl = 0;
-  nc = 0;
-#pragma unroll
-  for (int i = 0; i < QUEUE_RUNS; ++i) {
-    const int64_t u = u0 + i;
-    len[i] = u < U ? a.segabs[u + 1] - a.segabs[u] : 0;
-    if (len[i] > a.long_threshold) {
-      ++nl;
-      nc += (len[i] + a.chunk - 1) / a.chunk;
-    }
-  }
-}
-
-__global__ __launch_bounds__(256) void seg_queue_count_kernel(SegArgs a) {
-  __shared__ int wl[4], wc[4];
-  const int U = a.ubase[a.F];
-  const int64_t u0 = ((int64_t)blockIdx.x * 256 + threadIdx.x) * QUEUE_RUNS;
-  int len[QUEUE_RUNS], nl, nc;
-  queue_count(a, U, u0, len, nl, nc);
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    nl += __shfl_xor(nl, o, 64);
-    nc += __shfl_xor(nc, o, 64);
-  }
-  if ((threadIdx.x & 63) == 0) {
-    wl[threadIdx.x >> 6] = nl;
-    wc[threadIdx.x >> 6] = nc;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    a.qcnt[2 * blockIdx.x] = (wl[0] + wl[1]) + (wl[2] + wl[3]);
-    a.qcnt[2 * blockIdx.x + 1] = (wc[0] + wc[1]) + (wc[2] + wc[3]);
-  }
-}
-
-// One block: exclusive prefix sums of the per-block counts (qcnt[2 * nblocks ..] = the totals),
-// the list lengths, and the table of shares: share x of the reduction owns the runs of the
-// queue blocks [ceil(nq x / 8), ceil(nq (x+1) / 8)), nq = blocks that hold runs, hence a
-// contiguous piece of the run table and of both lists.
-__global__ __launch_bounds__(1024) void seg_queue_scan_kernel(SegArgs a, int nblocks) {
-  __shared__ int wsl[16], wsc[16];
-  const int per = (nblocks + 1023) / 1024;
-  const int lo = min(nblocks, (int)threadIdx.x * per), hi = min(nblocks, lo + per);
-  int sl = 0, sc = 0;
-  for (int i = lo; i < hi; ++i) {
-    sl += a.qcnt[2 * i];
-    sc += a.qcnt[2 * i + 1];
-  }
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  int il = sl, ic = sc;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int vl = __shfl_up(il, o, 64), vc = __shfl_up(ic, o, 64);
-    if (lane >= o) {
-      il += vl;
-      ic += vc;
-    }
-  }
-  if (lane == 63) {
-    wsl[w] = il;
-    wsc[w] = ic;
-  }
-  __syncthreads();
-  int bl = il - sl, bc = ic - sc, tl = 0, tc = 0;
-  for (int i = 0; i < 16; ++i) {
-    if (i < w) {
-      bl += wsl[i];
-      bc += wsc[i];
-    }
-    tl += wsl[i];
-    tc += wsc[i];
-  }
-  for (int i = lo; i < hi; ++i) {
-    const int cl = a.qcnt[2 * i], cc = a.qcnt[2 * i + 1];
-    a.qcnt[2 * i] = bl;
-    a.qcnt[2 * i + 1] = bc;
-    bl += cl;
-    bc += cc;
-  }
-  if (threadIdx.x == 0) {
-    a.qcnt[2 * nblocks] = tl;
-    a.qcnt[2 * nblocks + 1] = tc;
-    a.counters[0] = tl;
-    a.counters[1] = tc;
-  }
-  __threadfence_block();
-  __syncthreads();
-  if (threadIdx.x <= SHARES) {
-    const int U = a.ubase[a.F];
-    const int nq = (U + ANTDT_QUEUE_BLOCK_RUNS - 1) / ANTDT_QUEUE_BLOCK_RUNS;  // <= nblocks
-    const int x = threadIdx.x;
-    const int qb = min(nblocks, (int)(((int64_t)nq * x + SHARES - 1) / SHARES));
-    a.xcd_tab[x] = (int)min((int64_t)U, (int64_t)qb * ANTDT_QUEUE_BLOCK_RUNS);
-    a.xcd_tab[9 + x] = a.qcnt[2 * qb + 1];   // first chunk item
-    a.xcd_tab[18 + x] = a.qcnt[2 * qb];      // first long run
-  }
-}
-
-__global__ __launch_bounds__(256) void seg_queue_write_kernel(SegArgs a) {
-  __shared__ int wl[4], wc[4];
-  const int U = a.ubase[a.F];
-  if ((int64_t)blockIdx.x * ANTDT_QUEUE_BLOCK_RUNS >= U) return;
-  const int64_t u0 = ((int64_t)blockIdx.x * 256 + threadIdx.x) * QUEUE_RUNS;
-  int len[QUEUE_RUNS], nl, nc;
-  queue_count(a, U, u0, len, nl, nc);
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  int il = nl, ic = nc;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int vl = __shfl_up(il, o, 64), vc = __shfl_up(ic, o, 64);
-    if (lane >= o) {
-      il += vl;
-      ic += vc;
-    }
-  }
-  if (lane == 63) {
-    wl[w] = il;
-    wc[w] = ic;
-  }
-  __syncthreads();
-  int slot = a.qcnt[2 * blockIdx.x] + il - nl, item = a.qcnt[2 * blockIdx.x + 1] + ic - nc;
-  for (int i = 0; i < w; ++i) {
-    slot += wl[i];
-    item += wc[i];
-  }
-#pragma unroll
-  for (int i = 0; i < QUEUE_RUNS; ++i) {
-    if (len[i] <= a.long_threshold) continue;
-    const int nch = (len[i] + a.chunk - 1) / a.chunk;
-    if (slot < a.long_cap && item + nch <= a.item_cap) {  // (the capacities are upper bounds: always true)
-      a.long_seg[slot * 3 + 0] = (int)(u0 + i);
-      a.long_seg[slot * 3 + 1] = item;
-      a.long_seg[slot * 3 + 2] = nch;
-      for (int q = 0; q < nch; ++q) {
-        a.items[(item + q) * 2 + 0] = (int)(u0 + i);
-        a.items[(item + q) * 2 + 1] = q;
-      }
-    }
-    ++slot;
-    item += nch;
-  }
 }
 
 // ------------------------------------------------- weighted run sums (+ update)
@@ -578,61 +442,45 @@ __device__ __forceinline__ float lookup_weight(const SegArgs& a, const int32_t* 
   return w / (float)max(off[s + 1] - off[s], 1);
 }
 
-// g += w(lookup) * dX[sample, field slice] over sorted entries [b, e) of field f taken with
-// stride `step`, NF entries in flight (added in order).  The sample indices of the next NF entries
-// are requested before the pooled-gradient rows of the current ones are waited for: the chain of
-// dependent accesses is one round trip per NF entries instead of two.
-template <bool MEAN, int NF = 4>
-__device__ __forceinline__ void accumulate_run(const SegArgs& a, int f, int c, int b, int e, int step, Row4& g) {
+// g += w(lookup) * dX[sample, field slice] over the `n` lookups whose samples are pay[0 .. n), added in order.
+template <bool MEAN>
+__device__ __forceinline__ void accumulate_run(const SegArgs& a, int f, int c, const int32_t* pay, int n, Row4& g) {
   const float* dxcol = a.dx + f * a.D + c * 4;
   const int32_t* off = MEAN ? a.offsets + (int64_t)f * (a.B + 1) : nullptr;
-  int i = b;
-  int sn[NF];
-#pragma unroll
-  for (int q = 0; q < NF; ++q) sn[q] = i + q * step < e ? a.pay[i + q * step] : 0;
-  for (; i + (NF - 1) * step < e; i += NF * step) {
-    int s[NF];
-#pragma unroll
-    for (int q = 0; q < NF; ++q) s[q] = min(max(sn[q], 0), a.B - 1);
-#pragma unroll
-    for (int q = 0; q < NF; ++q) sn[q] = i + (NF + q) * step < e ? a.pay[i + (NF + q) * step] : 0;
+  auto add = [&](float w, const float4& x) {
+    g.v[0] = fmaf(w, x.x, g.v[0]);
+    g.v[1] = fmaf(w, x.y, g.v[1]);
+    g.v[2] = fmaf(w, x.z, g.v[2]);
+    g.v[3] = fmaf(w, x.w, g.v[3]);
+  };
+  auto whole = [&](int i) {   // four lookups in flight
+    constexpr int NF = 4;
     float w[NF];
     float4 x[NF];
 #pragma unroll
     for (int q = 0; q < NF; ++q) {
-      w[q] = lookup_weight<MEAN>(a, off, s[q]);
-      x[q] = *reinterpret_cast<const float4*>(dxcol + (int64_t)s[q] * a.lddx);
+      const int s = min(max(pay[i + q], 0), a.B - 1);
+      w[q] = lookup_weight<MEAN>(a, off, s);
+      x[q] = *reinterpret_cast<const float4*>(dxcol + (int64_t)s * a.lddx);
     }
 #pragma unroll
-    for (int q = 0; q < NF; ++q) {
-      g.v[0] = fmaf(w[q], x[q].x, g.v[0]);
-      g.v[1] = fmaf(w[q], x[q].y, g.v[1]);
-      g.v[2] = fmaf(w[q], x[q].z, g.v[2]);
-      g.v[3] = fmaf(w[q], x[q].w, g.v[3]);
-    }
-  }
-  // fewer than NF entries are left; their sample indices are in sn[]
-  {
-    float w[NF];
-    float4 x[NF];
+    for (int q = 0; q < NF; ++q) add(w[q], x[q]);
+  };
+  int i = 0;
+  for (; i + 4 <= n; i += 4) whole(i);
+  if (i < n) {   // up to three more
+    float w[3];
+    float4 x[3];
 #pragma unroll
-    for (int q = 0; q < NF; ++q) {
-      const int s = min(max(sn[q], 0), a.B - 1);
-      w[q] = 0.0f;
-      x[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (i + q * step < e) {
+    for (int q = 0; q < 3; ++q)
+      if (i + q < n) {
+        const int s = min(max(pay[i + q], 0), a.B - 1);
         w[q] = lookup_weight<MEAN>(a, off, s);
         x[q] = *reinterpret_cast<const float4*>(dxcol + (int64_t)s * a.lddx);
       }
-    }
 #pragma unroll
-    for (int q = 0; q < NF; ++q)
-      if (i + q * step < e) {
-        g.v[0] = fmaf(w[q], x[q].x, g.v[0]);
-        g.v[1] = fmaf(w[q], x[q].y, g.v[1]);
-        g.v[2] = fmaf(w[q], x[q].z, g.v[2]);
-        g.v[3] = fmaf(w[q], x[q].w, g.v[3]);
-      }
+    for (int q = 0; q < 3; ++q)
+      if (i + q < n) add(w[q], x[q]);
   }
 }
 
@@ -686,177 +534,272 @@ __device__ __forceinline__ void load_row(const SegArgs& a, int64_t row, int c, f
   else s0 = *reinterpret_cast<const float4*>(a.state + row * a.D + c * 4);
 }
 
-// Chunk sums of the long runs.  One block per chunk: the lane groups stride over the chunk, then
-// their partial sums are added in group order (fixed order: repeatable bit for bit).
-template <bool MEAN>
-__device__ __forceinline__ void chunk_sums(const SegArgs& a, int first, int last, int step) {
-  __shared__ float4 red[256];
-  const int lps = a.D >> 2;
-  const int ngroups = 256 / lps;
-  const int g = threadIdx.x / lps, c = threadIdx.x - g * lps;
-  const int count = min(last, a.item_cap);
-  for (int idx = first; idx < count; idx += step) {
-    const int u = a.items[idx * 2], q = a.items[idx * 2 + 1];
-    const int b = a.segabs[u] + q * a.chunk, e = min(a.segabs[u + 1], b + a.chunk);
-    const int f = a.ufield[u];
-    Row4 gsum = {{0.f, 0.f, 0.f, 0.f}};
-    accumulate_run<MEAN>(a, f, c, b + g, e, ngroups, gsum);
-    red[threadIdx.x] = make_float4(gsum.v[0], gsum.v[1], gsum.v[2], gsum.v[3]);
-    __syncthreads();
-    for (int half = ngroups >> 1; half > 0; half >>= 1) {
-      if (g < half) {
-        const float4 o = red[(g + half) * lps + c];
-        float4 m = red[g * lps + c];
-        m.x += o.x; m.y += o.y; m.z += o.z; m.w += o.w;
-        red[g * lps + c] = m;
-      }
-      __syncthreads();
-    }
-    if (g == 0) *reinterpret_cast<float4*>(a.partial + (int64_t)idx * a.D + c * 4) = red[c];
-    __syncthreads();
+// Run u of field f that starts at absolute position `pos` of the sorted lookups (run table present).
+__device__ __forceinline__ int64_t run_index(const SegArgs& a, int f, int pos) {
+  int lo = a.ubase[f], hi = a.ubase[f + 1] - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi) >> 1;
+    if (a.segabs[mid] < pos) lo = mid + 1;
+    else hi = mid;
   }
+  return lo;
 }
 
-// The first `chunk_blocks` blocks take the chunks of the long runs (their sums are added up by
-// the kernel after this one); the others work one group of D/4 lanes per run: short runs are
-// summed in sorted (= sample) order and, when `UPDATE`, the Adagrad step of the row is applied
-// at once (the coalesced gradient never goes to memory); otherwise the sum is written to G.
-// The work is divided into eight shares of consecutive runs (consecutive runs belong to the same
-// field), and the blocks whose index is x modulo 8, which the hardware places on XCD x, work
-// on share x: the pooled-gradient slice of a field (all samples x D columns) is then fetched into
-// one XCD's L2 instead of all eight.  With fewer than eight blocks there is one share.
-template <typename TT, bool ROWWISE, bool UPDATE, bool MEAN>
-__global__ __launch_bounds__(256) void seg_reduce_kernel(SegArgs a, int chunk_blocks) {
-  const int x = blockIdx.x & (SHARES - 1);
-  if ((int)blockIdx.x < chunk_blocks) {  // (chunk_blocks is a multiple of 8)
-    chunk_sums<MEAN>(a, a.xcd_tab[9 + x] + (int)(blockIdx.x >> 3), a.xcd_tab[9 + x + 1], chunk_blocks >> 3);
+// Sums of the runs of equal ids and, when `UPDATE`, the Adagrad step of each row at once (the coalesced
+// gradient never goes to memory); otherwise the sums are written to G.
+//
+// A block takes a window of W sorted lookups, straight from the sort: keys and sample indices of the window
+// (and of LONG_RUN lookups on either side) go to LDS, the block finds the runs' heads there, and groups of
+// D/4 lanes take one item of work each: a whole run of up to LONG_RUN lookups that starts in the window (it may
+// end behind it), summed in sorted (= sample) order, or, of longer runs, a piece of at most 32 lookups
+// that ends at a multiple of 32 in the window.  The pieces' sums meet in LDS in order; what of a run leaves the window
+// goes to memory (two slots per window: the run that comes in, the run that goes out) and is added up by
+// seg_finish_kernel.  No run table is needed (counting, scanning and writing one, with lists of the long
+// runs, were six launches and 10-250 us between sort and reduction), only keys, sample indices and the rows
+// themselves are read, and the chain of dependent accesses is down to LDS -> row and pooled gradients.
+// Bound by the rows and accumulators (HBM) where runs are short, by the pooled-gradient rows (L2 and the
+// memory-side cache) where they are long.
+constexpr int LONG_RUN = 32;
+
+template <typename TT, bool ROWWISE, bool UPDATE, bool MEAN, int W>
+__global__ __launch_bounds__(256) void seg_window_kernel(SegArgs a, FieldPtr fp, TileBase tb) {
+  constexpr int PARTS = SORT_TILE / W, ROUNDS = W / 256;
+  __shared__ int32_t key_[W + 2 * LONG_RUN + 1];    // positions -LONG_RUN .. W + LONG_RUN relative to the window
+  __shared__ int32_t pay[W + LONG_RUN];
+  __shared__ uint16_t start[W + LONG_RUN + 2];      // first position of every item, then of the run behind the last
+  __shared__ int16_t lead[W / 32 + 1];              // pieces' runs: [0] the one that comes in, [1 + j] starts in (32 j, 32 j + 31)
+  __shared__ int counts[ROUNDS + 1][4];
+  __shared__ int goes_out;
+  extern __shared__ __attribute__((aligned(16))) float4 piece_sum[];   // [W / 16][D / 4]: 2 j: starts at 32 j inside its run, 2 j + 1: at the run's head
+  int f, t, part;
+  if (!tile_of_block(tb, a.F, PARTS, f, t, part)) return;
+  const int win = (tb.t[f] + t) * PARTS + part;
+  const int64_t base = fp.p[f];
+  const int nnz = (int)(fp.p[f + 1] - base);
+  const int P = t * SORT_TILE + part * W;
+  const int tid = threadIdx.x;
+  if (P >= nnz) {
+    if (tid == 0) a.goes_out[win] = 0;
     return;
   }
-  const int64_t bid = (int64_t)blockIdx.x - chunk_blocks, nblk = (int64_t)gridDim.x - chunk_blocks;
-  const int lps = a.D >> 2;
-  const int groups_per_block = 256 / lps;
-  const int g = threadIdx.x / lps, c = threadIdx.x - g * lps;
-  int64_t lo, hi, slot, nslots;
-  if (nblk >= SHARES) {
-    lo = a.xcd_tab[x];
-    hi = a.xcd_tab[x + 1];
-    slot = bid >> 3;
-    nslots = (nblk - x + SHARES - 1) >> 3;
-  } else {
-    lo = 0;
-    hi = a.ubase[a.F];
-    slot = bid;
-    nslots = nblk;
-  }
-  // The kernel is bound by the chain of dependent accesses of a run (its description -> its row,
-  // accumulators and sample indices -> the pooled-gradient rows of its samples), every wavefront
-  // slot of the device being taken: the bounds, field and row id of a run are requested together,
-  // and those of the group's next run while the current one is summed.
-  const int64_t ustep = nslots * groups_per_block;
-  int64_t u = lo + slot * groups_per_block + g;
-  int nb = 0, ne = 0, nf = 0, nid = 0;
-  if (u < hi) {
-    nb = a.segabs[u]; ne = a.segabs[u + 1]; nf = a.ufield[u]; nid = a.uniq[u];
-  }
-  for (; u < hi; u += ustep) {
-    const int b = nb, e = ne, f = nf, id = nid;
-    if (u + ustep < hi) {
-      nb = a.segabs[u + ustep]; ne = a.segabs[u + ustep + 1]; nf = a.ufield[u + ustep]; nid = a.uniq[u + ustep];
-    }
-    if (e - b > a.long_threshold) continue;
-    const int64_t row = (int64_t)f * a.R + min(max(id, 0), (int)(a.R - 1));
-    float p0[4] = {0.f, 0.f, 0.f, 0.f};
-    float4 s0 = make_float4(0.f, 0.f, 0.f, 0.f);
-    float srow0 = 0.f;
-    if (UPDATE) load_row<TT, ROWWISE>(a, row, c, p0, s0, srow0);
-    Row4 gsum = {{0.f, 0.f, 0.f, 0.f}};
-    accumulate_run<MEAN>(a, f, c, b, e, 1, gsum);
-    if (UPDATE) adagrad_row<TT, ROWWISE>(a, row, c, lps, gsum, p0, s0, srow0);
-    else *reinterpret_cast<float4*>(a.G + u * a.D + c * 4) = make_float4(gsum.v[0], gsum.v[1], gsum.v[2], gsum.v[3]);
-  }
-}
-
-// One lane group per long run: add its chunk sums in chunk order, then update or store.
-template <typename TT, bool ROWWISE, bool UPDATE>
-__global__ __launch_bounds__(256) void seg_finish_kernel(SegArgs a) {
-  const int lps = a.D >> 2;
-  const int groups_per_block = 256 / lps;
-  const int g = threadIdx.x / lps, c = threadIdx.x - g * lps;
-  const int count = min(a.counters[0], a.long_cap);
-  for (int idx = blockIdx.x * groups_per_block + g; idx < count; idx += gridDim.x * groups_per_block) {
-    const int u = a.long_seg[idx * 3], base = a.long_seg[idx * 3 + 1], nch = a.long_seg[idx * 3 + 2];
-    const int f = a.ufield[u];
-    const int64_t row = (int64_t)f * a.R + min(max(a.uniq[u], 0), (int)(a.R - 1));
-    float p0[4] = {0.f, 0.f, 0.f, 0.f};
-    float4 s0 = make_float4(0.f, 0.f, 0.f, 0.f);
-    float srow0 = 0.f;
-    if (UPDATE) load_row<TT, ROWWISE>(a, row, c, p0, s0, srow0);
-    Row4 gsum = {{0.f, 0.f, 0.f, 0.f}};
-    const float* part = a.partial + (int64_t)base * a.D + c * 4;
-    int q = 0;
-    for (; q + 3 < nch; q += 4) {  // four loads in flight, added in chunk order
-      float4 v[4];
+  for (int i = tid; i < W + 2 * LONG_RUN + 1; i += 256) key_[i] = a.key[base + min(max(P + i - LONG_RUN, 0), nnz - 1)];
+  for (int i = tid; i < W + LONG_RUN; i += 256) pay[i] = a.pay[base + min(P + i, nnz - 1)];
+  if (tid <= W / 32) lead[tid] = -1;
+  if (tid == 0) goes_out = 0;
+  __syncthreads();
+  const int32_t* key = key_ + LONG_RUN;   // key[q]: position P + q
+  auto is_head = [&](int q) { return P + q == 0 || key[q - 1] != key[q]; };
+  auto same = [&](int q, int32_t k) { return P + q < nnz && key[q] == k; };   // (0 <= P + q)
+  // items: heads, and multiples of 32 inside long runs; position nnz counts as a head
+  bool flag[ROUNDS + 1];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) v[j] = *reinterpret_cast<const float4*>(part + (int64_t)(q + j) * a.D);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        gsum.v[0] += v[j].x; gsum.v[1] += v[j].y; gsum.v[2] += v[j].z; gsum.v[3] += v[j].w;
+  for (int r = 0; r <= ROUNDS; ++r) {
+    const int q = r * 256 + tid;
+    bool st = false;
+    if (q <= W + LONG_RUN && P + q <= nnz) {
+      if (P + q == nnz) st = true;
+      else if (is_head(q)) st = true;
+      else if (q < W && (q & 31) == 0) {
+        int lo = max(q - LONG_RUN, -P), hi = q;   // first position of the run, at most LONG_RUN back
+        while (lo < hi) {
+          const int mid = (lo + hi) >> 1;
+          if (key[mid] < key[q]) lo = mid + 1;
+          else hi = mid;
+        }
+        st = same(lo + LONG_RUN, key[q]);
       }
     }
-    for (; q < nch; ++q) {
-      const float4 v = *reinterpret_cast<const float4*>(part + (int64_t)q * a.D);
-      gsum.v[0] += v.x; gsum.v[1] += v.y; gsum.v[2] += v.z; gsum.v[3] += v.w;
+    flag[r] = st;
+    const uint64_t m = __ballot(st);
+    if ((tid & 63) == 0) counts[r][tid >> 6] = __popcll(m);
+  }
+  __syncthreads();
+  int items = 0, total;   // items of the window; with what follows it
+  {
+    const uint64_t lt = lanemask_lt();
+    int before = 0;
+#pragma unroll
+    for (int r = 0; r <= ROUNDS; ++r) {
+      const uint64_t m = __ballot(flag[r]);
+      int mine = before;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        if (w < (tid >> 6)) mine += counts[r][w];
+        before += counts[r][w];
+      }
+      if (flag[r]) start[mine + __popcll(m & lt)] = (uint16_t)(r * 256 + tid);
+      if (r == ROUNDS - 1) items = before;
     }
-    if (UPDATE) adagrad_row<TT, ROWWISE>(a, row, c, lps, gsum, p0, s0, srow0);
-    else *reinterpret_cast<float4*>(a.G + (int64_t)u * a.D + c * 4) = make_float4(gsum.v[0], gsum.v[1], gsum.v[2], gsum.v[3]);
+    total = before;
+  }
+  // (the last window of a field: position nnz may lie inside it)
+  if (P + W > nnz) items = min(items, total - 1);
+  __syncthreads();
+  const int lps = a.D >> 2;
+  const int ngroups = 256 / lps;
+  const int g = tid / lps, c = tid - g * lps;
+  const int64_t row0 = (int64_t)f * a.R;
+  auto finish = [&](int64_t row, const Row4& sum, const float (&p0)[4], const float4& s0, float srow0, int q) {
+    if (UPDATE) adagrad_row<TT, ROWWISE>(a, row, c, lps, sum, p0, s0, srow0);
+    else *reinterpret_cast<float4*>(a.G + run_index(a, f, (int)base + P + q) * a.D + c * 4) =
+        make_float4(sum.v[0], sum.v[1], sum.v[2], sum.v[3]);
+  };
+  for (int i = g; i < items; i += ngroups) {
+    const int q0 = start[i];
+    int e = i + 1 < total ? start[i + 1] : W;
+    const bool head = is_head(q0);
+    const bool piece = !head || same(q0 + LONG_RUN, key[q0]);
+    if (piece) e = min(e, W);
+    const int64_t row = row0 + min(max(key[q0], 0), (int)(a.R - 1));
+    float p0[4] = {0.f, 0.f, 0.f, 0.f};
+    float4 s0 = make_float4(0.f, 0.f, 0.f, 0.f);
+    float srow0 = 0.f;
+    if (UPDATE && !piece) load_row<TT, ROWWISE>(a, row, c, p0, s0, srow0);
+    Row4 sum = {{0.f, 0.f, 0.f, 0.f}};
+    accumulate_run<MEAN>(a, f, c, pay + q0, min(e - q0, LONG_RUN), sum);
+    if (piece) {
+      piece_sum[(2 * (q0 >> 5) + (head ? 1 : 0)) * lps + c] = make_float4(sum.v[0], sum.v[1], sum.v[2], sum.v[3]);
+      if (c == 0 && (head || q0 == 0)) lead[head ? 1 + (q0 >> 5) : 0] = (int16_t)q0;
+    } else {
+      finish(row, sum, p0, s0, srow0, q0);
+    }
+  }
+  __syncthreads();
+  for (int l = g; l < W / 32 + 1; l += ngroups) {
+    const int q0 = lead[l];
+    if (q0 < 0) continue;
+    const int32_t k = key[q0];
+    const bool out = same(W, k);
+    const int64_t row = row0 + min(max(k, 0), (int)(a.R - 1));
+    float p0[4] = {0.f, 0.f, 0.f, 0.f};
+    float4 s0 = make_float4(0.f, 0.f, 0.f, 0.f);
+    float srow0 = 0.f;
+    if (UPDATE && l > 0 && !out) load_row<TT, ROWWISE>(a, row, c, p0, s0, srow0);
+    const float4 x0 = piece_sum[(2 * (q0 >> 5) + (l > 0 ? 1 : 0)) * lps + c];
+    Row4 sum = {{x0.x, x0.y, x0.z, x0.w}};
+    for (int j = (q0 >> 5) + 1; j < W / 32 && same(j * 32, k); ++j) {
+      const float4 x = piece_sum[2 * j * lps + c];
+      sum.v[0] += x.x; sum.v[1] += x.y; sum.v[2] += x.z; sum.v[3] += x.w;
+    }
+    if (l > 0 && !out) {
+      finish(row, sum, p0, s0, srow0, q0);
+    } else {
+      *reinterpret_cast<float4*>(a.partial + ((int64_t)win * 2 + (l > 0 ? 1 : 0)) * a.D + c * 4) =
+          make_float4(sum.v[0], sum.v[1], sum.v[2], sum.v[3]);
+      if (l > 0) goes_out = 1;
+    }
+  }
+  __syncthreads();
+  if (tid == 0) a.goes_out[win] = goes_out;
+}
+
+// Runs that leave the window they start in, one wavefront each: the sum of the first window's part, then those
+// of the windows the run comes into, lane groups taking turns (fixed order: repeatable bit for bit).
+template <typename TT, bool ROWWISE, bool UPDATE>
+__global__ __launch_bounds__(256) void seg_finish_kernel(SegArgs a, FieldPtr fp, TileBase tb, int W) {
+  const int parts = SORT_TILE / W;
+  const int win = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (win >= a.total_tiles * parts || !a.goes_out[win]) return;
+  int f, t;
+  field_of_tile(tb, win / parts, f, t);
+  const int64_t base = fp.p[f];
+  const int nnz = (int)(fp.p[f + 1] - base);
+  const int lane = threadIdx.x & 63;
+  const int next = t * SORT_TILE + (win % parts + 1) * W;   // where the following window starts
+  const int32_t k = a.key[base + next - 1];
+  int n = 0;   // following windows that start inside the run
+  for (;;) {
+    const int64_t pos = next + (int64_t)(n + lane) * W;
+    const bool in = pos < nnz && a.key[base + min(pos, (int64_t)nnz - 1)] == k;
+    const uint64_t out = ~__ballot(in);
+    if (out) {
+      n += __ffsll((unsigned long long)out) - 1;
+      break;
+    }
+    n += 64;
+  }
+  const int lps = a.D >> 2, ngroups = 64 / lps;
+  const int g = lane / lps, c = lane - g * lps;
+  const int64_t row = (int64_t)f * a.R + min(max(k, 0), (int)(a.R - 1));
+  float p0[4] = {0.f, 0.f, 0.f, 0.f};
+  float4 s0 = make_float4(0.f, 0.f, 0.f, 0.f);
+  float srow0 = 0.f;
+  if (UPDATE) load_row<TT, ROWWISE>(a, row, c, p0, s0, srow0);
+  auto slot = [&](int i, int which) { return *reinterpret_cast<const float4*>(a.partial + ((int64_t)(win + i) * 2 + which) * a.D + c * 4); };
+  Row4 sum = {{0.f, 0.f, 0.f, 0.f}};
+  auto add = [&](const float4& v) { sum.v[0] += v.x; sum.v[1] += v.y; sum.v[2] += v.z; sum.v[3] += v.w; };
+  if (g == 0) add(slot(0, 1));
+  int i = 1 + g;
+  for (; i + 3 * ngroups <= n; i += 4 * ngroups) {   // four loads in flight
+    float4 v[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = slot(i + j * ngroups, 0);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) add(v[j]);
+  }
+  for (; i <= n; i += ngroups) add(slot(i, 0));
+  for (int o = lps; o < 64; o <<= 1) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) sum.v[e] += __shfl_xor(sum.v[e], o, 64);
+  }
+  if (g != 0) return;
+  if (UPDATE) {
+    adagrad_row<TT, ROWWISE>(a, row, c, lps, sum, p0, s0, srow0);
+  } else {   // the run's head: the first position of the key in the window
+    int lo = next - W, hi = next - 1;
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (a.key[base + mid] < k) lo = mid + 1;
+      else hi = mid;
+    }
+    *reinterpret_cast<float4*>(a.G + run_index(a, f, (int)base + lo) * a.D + c * 4) = make_float4(sum.v[0], sum.v[1], sum.v[2], sum.v[3]);
   }
 }
 
-template <typename TT, bool ROWWISE, bool UPDATE, bool MEAN>
-void launch_reduce_pooling(const SegArgs& a, unsigned blocks, unsigned finish_blocks, Profiler* prof, hipStream_t s) {
+template <typename TT, bool ROWWISE, bool UPDATE, bool MEAN, int W>
+void launch_reduce_window(const SegArgs& a, const FieldPtr& fp, const TileBase& tb, Profiler* prof, hipStream_t s) {
+  const unsigned parts = SORT_TILE / W;
   {
     ProfScope ps(prof, UPDATE ? KID_SPARSE_ADAGRAD : KID_SEG_REDUCE, s);
-    constexpr int CHUNK_BLOCKS = 2048;
-    hipLaunchKernelGGL((seg_reduce_kernel<TT, ROWWISE, UPDATE, MEAN>), dim3(blocks + CHUNK_BLOCKS), dim3(256), 0, s, a,
-                       CHUNK_BLOCKS);
+    hipLaunchKernelGGL((seg_window_kernel<TT, ROWWISE, UPDATE, MEAN, W>), dim3(tile_grid(a.total_tiles) * parts), dim3(256),
+                       W / 16 * a.D * 4, s, a, fp, tb);
   }
   {
     ProfScope ps(prof, KID_SEG_REDUCE_LONG, s);
-    hipLaunchKernelGGL((seg_finish_kernel<TT, ROWWISE, UPDATE>), dim3(finish_blocks), dim3(256), 0, s, a);
+    hipLaunchKernelGGL((seg_finish_kernel<TT, ROWWISE, UPDATE>), dim3((a.total_tiles * parts + 3) / 4), dim3(256), 0, s, a, fp, tb, W);
   }
 }
 
+template <typename TT, bool ROWWISE, bool UPDATE, bool MEAN>
+void launch_reduce_pooling(const SegArgs& a, const FieldPtr& fp, const TileBase& tb, Profiler* prof, hipStream_t s) {
+  if (a.window == 512) launch_reduce_window<TT, ROWWISE, UPDATE, MEAN, 512>(a, fp, tb, prof, s);
+  else launch_reduce_window<TT, ROWWISE, UPDATE, MEAN, 256>(a, fp, tb, prof, s);
+}
+
 template <typename TT, bool ROWWISE, bool UPDATE>
-void launch_reduce_variant(const SegArgs& a, unsigned blocks, unsigned finish_blocks, Profiler* prof, hipStream_t s) {
-  if (a.mean_pool) launch_reduce_pooling<TT, ROWWISE, UPDATE, true>(a, blocks, finish_blocks, prof, s);
-  else launch_reduce_pooling<TT, ROWWISE, UPDATE, false>(a, blocks, finish_blocks, prof, s);
+void launch_reduce_variant(const SegArgs& a, const FieldPtr& fp, const TileBase& tb, Profiler* prof, hipStream_t s) {
+  if (a.mean_pool) launch_reduce_pooling<TT, ROWWISE, UPDATE, true>(a, fp, tb, prof, s);
+  else launch_reduce_pooling<TT, ROWWISE, UPDATE, false>(a, fp, tb, prof, s);
 }
 
 }  // namespace
 
-// Blocks of a launch whose block b works on tile (b / 8) of the fields b mod 8, b mod 8 + 8, ...:
-// eight times the largest number of tiles any of the eight groups of fields has.
-static unsigned tile_grid(const TileBase& tb, int F) {
-  int most = 1;
-  for (int x = 0; x < 8; ++x) most = std::max(most, (int)tb.xcum[x][ANTDT_MAX_FIELDS / 8]);
-  (void)F;
-  return (unsigned)(8 * most);
-}
-
 hipError_t launch_sort_pass(const SortPlan& pl, const SortBuffers& sb, int pass, const FieldPtr& fp,
-                            const TileBase& tb, Profiler* prof, hipStream_t s) {
+                            const TileBase& tb, const ShardTab& tab, Profiler* prof, hipStream_t s) {
   if (pl.total_tiles == 0) return hipSuccess;
   const int shift = pass * pl.radix_bits;
   const int32_t* kin = pass == 0 ? sb.ids : sb.key[(pass - 1) & 1];
   const int32_t* pin = pass == 0 ? sb.pay0 : sb.pay[(pass - 1) & 1];
-  dim3 grid(tile_grid(tb, pl.F));
+  dim3 grid(tile_grid(pl.total_tiles));
   {
     ProfScope ps(prof, KID_SORT_HIST, s);
     hipLaunchKernelGGL(sort_hist_kernel, grid, dim3(SORT_THREADS), 0, s, kin, sb.hist, fp, tb, pl.F, shift, pl.radix_bits);
   }
   {
     ProfScope ps(prof, KID_SORT_SCAN, s);
-    hipLaunchKernelGGL(sort_scan_kernel, dim3(pl.F), dim3(MAX_BINS), 0, s, sb.hist, sb.digit_base, tb, pl.radix_bits);
+    const int wblocks = pass == 0 ? (pl.B + MAX_BINS - 1) / MAX_BINS : 0;
+    hipLaunchKernelGGL(sort_scan_kernel, dim3(pl.F + wblocks), dim3(MAX_BINS), 0, s, sb.hist, sb.digit_base, tb, pl.F, pl.radix_bits,
+                       sb.sample_w, tab);
   }
   {
     ProfScope ps(prof, KID_SORT_SCATTER, s);
@@ -866,28 +809,19 @@ hipError_t launch_sort_pass(const SortPlan& pl, const SortBuffers& sb, int pass,
   return hipGetLastError();
 }
 
-hipError_t launch_segments(const SegArgs& a, const FieldPtr& fp, const TileBase& tb, const ShardTab& tab,
-                           Profiler* prof, hipStream_t s) {
-  dim3 grid(tile_grid(tb, a.F));
+hipError_t launch_segments(const SegArgs& a, const FieldPtr& fp, const TileBase& tb, Profiler* prof, hipStream_t s) {
+  dim3 grid(tile_grid(a.total_tiles));
   if (a.total_tiles > 0) {
     ProfScope ps(prof, KID_SEG_HEADS, s);
     hipLaunchKernelGGL(seg_heads_kernel, grid, dim3(SORT_THREADS), 0, s, a, fp, tb);
   }
   {
     ProfScope ps(prof, KID_SEG_SCAN, s);
-    hipLaunchKernelGGL(seg_scan_kernel, dim3(1), dim3(1024), 0, s, a, fp, tb, tab);
+    hipLaunchKernelGGL(seg_scan_kernel, dim3(1), dim3(1024), 0, s, a, fp, tb);
   }
   if (a.total_tiles > 0) {
     ProfScope ps(prof, KID_SEG_EMIT, s);
     hipLaunchKernelGGL(seg_emit_kernel, grid, dim3(SORT_THREADS), 0, s, a, fp, tb);
-  }
-  {  // lists of the long runs and their chunks, and the table of shares (also when there is no lookup)
-    const int64_t nnz = fp.p[a.F];
-    const unsigned qb = (unsigned)((nnz + ANTDT_QUEUE_BLOCK_RUNS - 1) / ANTDT_QUEUE_BLOCK_RUNS);  // runs <= lookups
-    ProfScope ps(prof, KID_SEG_EMIT, s);
-    if (qb) hipLaunchKernelGGL(seg_queue_count_kernel, dim3(qb), dim3(256), 0, s, a);
-    hipLaunchKernelGGL(seg_queue_scan_kernel, dim3(1), dim3(1024), 0, s, a, (int)qb);
-    if (qb) hipLaunchKernelGGL(seg_queue_write_kernel, dim3(qb), dim3(256), 0, s, a);
   }
   return hipGetLastError();
 }
@@ -901,29 +835,18 @@ hipError_t launch_mask_pack(const int32_t* ids, const int32_t* lookup_sample, co
   return hipGetLastError();
 }
 
-hipError_t launch_seg_reduce(const SegArgs& a, int64_t nnz_total, Profiler* prof, hipStream_t s) {
-  if (nnz_total == 0) return hipSuccess;
-  const int groups_per_block = 256 / (a.D >> 2);
-  int64_t nb = (nnz_total + groups_per_block - 1) / groups_per_block;
-  if (nb > 256 * 32) nb = 256 * 32;
-  if (nb >= SHARES) nb = (nb + SHARES - 1) / SHARES * SHARES;   // the same number of blocks for every share
-  const unsigned blocks = (unsigned)nb;
-  // one lane group per long run; there are at most nnz / threshold of them (blocks past the
-  // actual number leave at once)
-  int64_t fb = (nnz_total / (a.long_threshold > 0 ? a.long_threshold : 1) + groups_per_block) / groups_per_block;
-  if (fb < 64) fb = 64;
-  if (fb > 8192) fb = 8192;
-  const unsigned finish_blocks = (unsigned)fb;
+hipError_t launch_seg_reduce(const SegArgs& a, const FieldPtr& fp, const TileBase& tb, Profiler* prof, hipStream_t s) {
+  if (a.total_tiles == 0) return hipSuccess;
   if (a.update) {
     if (a.table_bf16) {
-      if (a.rowwise) launch_reduce_variant<bf16_t, true, true>(a, blocks, finish_blocks, prof, s);
-      else launch_reduce_variant<bf16_t, false, true>(a, blocks, finish_blocks, prof, s);
+      if (a.rowwise) launch_reduce_variant<bf16_t, true, true>(a, fp, tb, prof, s);
+      else launch_reduce_variant<bf16_t, false, true>(a, fp, tb, prof, s);
     } else {
-      if (a.rowwise) launch_reduce_variant<float, true, true>(a, blocks, finish_blocks, prof, s);
-      else launch_reduce_variant<float, false, true>(a, blocks, finish_blocks, prof, s);
+      if (a.rowwise) launch_reduce_variant<float, true, true>(a, fp, tb, prof, s);
+      else launch_reduce_variant<float, false, true>(a, fp, tb, prof, s);
     }
   } else {
-    launch_reduce_variant<float, false, false>(a, blocks, finish_blocks, prof, s);
+    launch_reduce_variant<float, false, false>(a, fp, tb, prof, s);
   }
   return hipGetLastError();
 }

@@ -43,11 +43,7 @@ struct ShardTab {
 };
 struct TileBase {
   int32_t t[ANTDT_MAX_FIELDS + 1];  // prefix sum of sort tiles per field
-  // xcum[x][j] = tiles of the fields x, x + 8, ..., x + 8 (j - 1): the blocks with index x modulo 8 take the
-  // tiles of these fields in this order (16 fields per group at most; entries past the last field repeat the total)
-  int32_t xcum[8][ANTDT_MAX_FIELDS / 8 + 1];
 };
-static_assert(ANTDT_MAX_FIELDS % 8 == 0, "fields are dealt to eight groups");
 
 // Kernel classes for the optional event timing.
 enum KernelId {
@@ -215,13 +211,9 @@ hipError_t launch_zero_words(int32_t* p, int n, hipStream_t s);
 // ------------------------------------------------------------- coalesce.hip
 // Keys per sort tile (one block of 512 threads, ANTDT_SORT_TILE / 512 keys per thread).
 constexpr int ANTDT_SORT_TILE = 2048;
-// Runs per block of the kernels that list the long runs (256 threads, 8 runs each).
-constexpr int ANTDT_QUEUE_BLOCK_RUNS = 2048;
-
 struct SortPlan {
   int32_t F, B;
   int32_t passes, radix_bits;      // digit width per pass
-  int32_t max_tiles;               // max tiles of one field (grid.x)
   int32_t total_tiles;
 };
 struct SortBuffers {
@@ -232,34 +224,30 @@ struct SortBuffers {
   int32_t* pay[2];
   uint32_t* hist;                  // [total_tiles << radix_bits]
   uint32_t* digit_base;            // [F << radix_bits]
+  float* sample_w;                 // [B] aggregation weight of every sample, written beside the first pass
 };
 hipError_t launch_sort_pass(const SortPlan& pl, const SortBuffers& sb, int pass, const FieldPtr& fp,
-                            const TileBase& tb, Profiler* prof, hipStream_t s);
+                            const TileBase& tb, const ShardTab& tab, Profiler* prof, hipStream_t s);
 
 struct SegArgs {
   const int32_t* key;              // sorted row ids, field-major at fp.p[f]
   const int32_t* pay;              // sample index of each sorted lookup
+  // run table (for the views only)
   int32_t* tile_heads;             // [total_tiles + 1] heads per tile -> exclusive prefix
   int32_t* ubase;                  // [F + 1] first unique of each field; ubase[F] = U
   int32_t* uniq;                   // [U] row id of each run
-  int32_t* ufield;                 // [U] field of each run
   int32_t* segabs;                 // [U + 1] start of each run in the sorted arrays (all fields)
   int32_t* segoff;                 // [U + F], per-field offsets; field f's slice starts at ubase[f] + f
-  float* sample_w;                 // [B]
-  int32_t* counters;               // [2]: number of long runs, number of chunk work items
-  int32_t* qcnt;                   // [2 * queue blocks]: long runs and chunks found by each block of the list
-                                   // builder, then their exclusive prefix sums
-  int32_t* xcd_tab;                // [3][9]: first run, first chunk item and first long run of each of the 8
-                                   // shares into which the reduction divides its work (entry 8 = the totals)
-  int32_t* long_seg;               // [long_cap][3]: run, first item, number of chunks
-  int32_t* items;                  // [item_cap][2]: run, chunk index
-  float* partial;                  // [item_cap, D] chunk sums of long runs
   float* G;                        // [U, D] coalesced gradient (written when not updating)
+  const float* sample_w;           // [B]
+  int32_t window;                  // sorted lookups per block of the reduction: 256 or 512
+  int32_t* goes_out;               // [windows] the last run of the window starts there, is long and goes on in the next one
+  float* partial;                  // [windows, 2, D] sums over the window: of the run that comes in, of the run that goes out
   const float* dx;                 // [B, lddx]
   int64_t lddx;
   const int32_t* offsets;          // [F][B + 1] bag boundaries of the batch (read when mean_pool)
   int32_t mean_pool;               // bags are averaged: a lookup's gradient is dX / bag length
-  int32_t F, D, B, max_tiles, total_tiles, long_threshold, chunk, long_cap, item_cap;
+  int32_t F, D, B, total_tiles;
   // parameter update fused into the reduction (update != 0)
   int32_t update, table_bf16, rowwise;
   void* tables;
@@ -267,12 +255,11 @@ struct SegArgs {
   int64_t R;
   float lr, eps;
 };
-hipError_t launch_segments(const SegArgs& a, const FieldPtr& fp, const TileBase& tb,
-                           const ShardTab& tab, Profiler* prof, hipStream_t s);
+hipError_t launch_segments(const SegArgs& a, const FieldPtr& fp, const TileBase& tb, Profiler* prof, hipStream_t s);
 hipError_t launch_mask_pack(const int32_t* ids, const int32_t* lookup_sample, const int32_t* offsets, int64_t B, int F,
                             const FieldPtr& fp, const ShardTab& tab, int64_t* cbase, int32_t* ids_out,
                             int32_t* pay_out, hipStream_t s);
-hipError_t launch_seg_reduce(const SegArgs& a, int64_t nnz_total, Profiler* prof, hipStream_t s);
+hipError_t launch_seg_reduce(const SegArgs& a, const FieldPtr& fp, const TileBase& tb, Profiler* prof, hipStream_t s);
 
 // ---------------------------------------------------------------- optim.hip
 struct DenseAggArgs {

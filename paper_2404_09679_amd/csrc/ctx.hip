@@ -96,11 +96,6 @@ struct antdt_ctx {
   int width[ANTDT_MAX_LAYERS + 1];  // width[l] = layer_sizes[l]
   int sort_passes = 1, radix_bits = 1;
   int64_t max_tiles_total = 0;
-  // Runs of more than long_threshold lookups are summed by whole blocks, `chunk` lookups at a time (measured on
-  // configurations 2-4: 32 / 1024 against 64 / 256 shortens the sparse update by 3-5 %; below 32 and above 1024 flat)
-  int long_threshold = 32;
-  int64_t long_cap = 0, item_cap = 0;
-  int chunk = 1024;
   bool g_valid = false;
   size_t ws_bytes = 0;
   // caller's buffers
@@ -122,7 +117,7 @@ struct antdt_ctx {
   int32_t* head_done = nullptr;          // per shard: its finished blocks (0 between launches)
   int32_t* lookup_sample = nullptr;
   int32_t *key[2] = {}, *pay[2] = {}, *tile_heads = nullptr, *ubase = nullptr, *uniq = nullptr;
-  int32_t *segoff = nullptr, *ufield = nullptr, *segabs = nullptr, *counters = nullptr, *long_seg = nullptr, *items = nullptr, *qcnt = nullptr, *xcd_tab = nullptr;
+  int32_t *segoff = nullptr, *pack_pay = nullptr, *segabs = nullptr, *goes_out = nullptr;
   float* partial = nullptr;
   uint32_t *hist = nullptr, *digit_base = nullptr;
   // batch
@@ -133,12 +128,12 @@ struct antdt_ctx {
   int64_t B = 0;
   FieldPtr fp;
   TileBase tb;
-  int max_tiles = 0, total_tiles = 0;
+  int total_tiles = 0;
   // the lookups that the current aggregation coalesces: all of the batch (the four above), or
   // the packed lookups of the included shards when some are left out
   FieldPtr afp;
   TileBase atb;
-  int amax_tiles = 0, atotal_tiles = 0;
+  int atotal_tiles = 0;
   int64_t* cbase = nullptr;
   int32_t* vflags = nullptr;  // result of antdt_validate_batch
   // shards
@@ -241,16 +236,13 @@ static size_t carve(antdt_ctx* c, char* base) {
   c->ubase = (int32_t*)take((size_t)(m.num_fields + 1) * 4);
   c->uniq = (int32_t*)take((size_t)N * 4);
   c->segoff = (int32_t*)take((size_t)(N + m.num_fields + 1) * 4);
-  c->ufield = (int32_t*)take((size_t)N * 4);
+  c->pack_pay = (int32_t*)take((size_t)N * 4);
   c->segabs = (int32_t*)take((size_t)(N + 1) * 4);
-  c->counters = (int32_t*)take(8);
-  c->qcnt = (int32_t*)take((size_t)(N / ANTDT_QUEUE_BLOCK_RUNS + 2) * 8);
-  c->xcd_tab = (int32_t*)take(3 * 9 * 4);
   c->cbase = (int64_t*)take((size_t)(ANTDT_MAX_FIELDS + 1) * 8);
   c->vflags = (int32_t*)take(8);
-  c->long_seg = (int32_t*)take((size_t)c->long_cap * 12);
-  c->items = (int32_t*)take((size_t)c->item_cap * 8);
-  c->partial = (float*)take((size_t)c->item_cap * m.dim * 4);
+  const size_t windows = (size_t)c->max_tiles_total * (ANTDT_SORT_TILE / 256);
+  c->goes_out = (int32_t*)take(windows * 4);
+  c->partial = (float*)take(windows * 2 * m.dim * 4);
   c->G = (float*)take((size_t)N * m.dim * 4);
   return off;
 }
@@ -355,8 +347,6 @@ int antdt_create(const antdt_model* model, antdt_ctx** out) {
   c->sort_passes = (bits + 9) / 10;
   c->radix_bits = (bits + c->sort_passes - 1) / c->sort_passes;
   c->max_tiles_total = m.max_nnz / ANTDT_SORT_TILE + m.num_fields + 1;
-  c->long_cap = m.max_nnz / c->long_threshold + 1;
-  c->item_cap = m.max_nnz / c->chunk + c->long_cap + 1;
   c->ws_bytes = carve(c, nullptr);
   memset(&c->tab, 0, sizeof(c->tab));
   *out = c;
@@ -499,27 +489,17 @@ int antdt_bind_static(antdt_ctx* c, void* tables, float* table_state, float* mlp
 }
 
 // Tile decomposition of per-field lookup ranges.
-static void plan_tiles(int F, const FieldPtr& fp, TileBase& tb, int& max_tiles, int& total_tiles) {
+static void plan_tiles(int F, const FieldPtr& fp, TileBase& tb, int& total_tiles) {
   memset(&tb, 0, sizeof(tb));
-  max_tiles = 0;
-  for (int f = 0; f < F; ++f) {
-    const int tiles = (int)((fp.p[f + 1] - fp.p[f] + ANTDT_SORT_TILE - 1) / ANTDT_SORT_TILE);
-    tb.t[f + 1] = tb.t[f] + tiles;
-    if (tiles > max_tiles) max_tiles = tiles;
-  }
+  for (int f = 0; f < F; ++f)
+    tb.t[f + 1] = tb.t[f] + (int)((fp.p[f + 1] - fp.p[f] + ANTDT_SORT_TILE - 1) / ANTDT_SORT_TILE);
   for (int f = F + 1; f <= ANTDT_MAX_FIELDS; ++f) tb.t[f] = tb.t[F];
   total_tiles = tb.t[F];
-  for (int x = 0; x < 8; ++x)
-    for (int j = 0; j < ANTDT_MAX_FIELDS / 8; ++j) {
-      const int f = x + 8 * j;
-      tb.xcum[x][j + 1] = tb.xcum[x][j] + (f < F ? tb.t[f + 1] - tb.t[f] : 0);
-    }
 }
 
 static void coalesce_whole_batch(antdt_ctx* c) {
   c->afp = c->fp;
   c->atb = c->tb;
-  c->amax_tiles = c->max_tiles;
   c->atotal_tiles = c->total_tiles;
 }
 
@@ -539,7 +519,7 @@ int antdt_set_batch(antdt_ctx* c, const int32_t* ids, const int64_t* field_ptr, 
   memset(&c->fp, 0, sizeof(c->fp));
   for (int f = 0; f < F; ++f) c->fp.p[f + 1] = field_ptr[f + 1];
   for (int f = F + 1; f <= ANTDT_MAX_FIELDS; ++f) c->fp.p[f] = c->fp.p[F];
-  plan_tiles(F, c->fp, c->tb, c->max_tiles, c->total_tiles);
+  plan_tiles(F, c->fp, c->tb, c->total_tiles);
   coalesce_whole_batch(c);
   c->ids = ids;
   c->offsets = offsets;
@@ -639,14 +619,12 @@ static void fill_seg_args(antdt_ctx* c, SegArgs& a) {
   const antdt_model& m = c->m;
   memset(&a, 0, sizeof(a));
   a.key = c->key[c->sorted_buf]; a.pay = c->pay[c->sorted_buf];
-  a.tile_heads = c->tile_heads; a.ubase = c->ubase; a.uniq = c->uniq; a.ufield = c->ufield;
-  a.segabs = c->segabs; a.segoff = c->segoff; a.sample_w = c->sample_w; a.counters = c->counters; a.qcnt = c->qcnt; a.xcd_tab = c->xcd_tab;
-  a.long_seg = c->long_seg; a.items = c->items; a.partial = c->partial;
+  a.tile_heads = c->tile_heads; a.ubase = c->ubase; a.uniq = c->uniq; a.segabs = c->segabs; a.segoff = c->segoff;
+  a.sample_w = c->sample_w; a.goes_out = c->goes_out; a.partial = c->partial;
   a.G = c->G; a.dx = c->dx; a.lddx = c->FD;
   a.offsets = c->offsets; a.mean_pool = m.pooling == ANTDT_POOL_MEAN;
-  a.F = m.num_fields; a.D = m.dim; a.B = (int32_t)c->B; a.max_tiles = c->amax_tiles;
-  a.total_tiles = c->atotal_tiles; a.long_threshold = c->long_threshold; a.chunk = c->chunk;
-  a.long_cap = (int32_t)c->long_cap; a.item_cap = (int32_t)c->item_cap;
+  a.F = m.num_fields; a.D = m.dim; a.B = (int32_t)c->B; a.total_tiles = c->atotal_tiles;
+  a.window = c->afp.p[m.num_fields] >= (4 << 20) && m.dim <= 128 ? 512 : 256;
   a.tables = c->tables; a.state = c->table_state; a.R = m.rows_per_field; a.lr = m.lr; a.eps = m.eps;
   a.table_bf16 = m.table_dtype == ANTDT_BF16; a.rowwise = m.adagrad_state == ANTDT_STATE_ROWWISE;
 }
@@ -662,25 +640,23 @@ static void set_weights(antdt_ctx* c) {
   c->weights_dirty = false;
 }
 
-// Sort the lookups by row id, find the runs, and fill the per-sample weights: everything of
-// the server side that depends only on the batch's ids and on the shard weights.
+// Sort the lookups by row id and fill the per-sample weights: everything of the server side that depends only
+// on the batch's ids and on the shard weights.
 static int build_coalescing(antdt_ctx* c, const int32_t* ids, const int32_t* pay0, hipStream_t s) {
   Profiler* pr = prof_of(c);
   const antdt_model& m = c->m;
   SortPlan pl;
   pl.F = m.num_fields; pl.B = (int32_t)c->B; pl.passes = c->sort_passes; pl.radix_bits = c->radix_bits;
-  pl.max_tiles = c->amax_tiles; pl.total_tiles = c->atotal_tiles;
+  pl.total_tiles = c->atotal_tiles;
   SortBuffers sb;
   sb.ids = ids; sb.offsets = c->offsets;
   sb.key[0] = c->key[0]; sb.key[1] = c->key[1]; sb.pay[0] = c->pay[0]; sb.pay[1] = c->pay[1];
   sb.hist = c->hist;
   sb.digit_base = c->digit_base;
+  sb.sample_w = c->sample_w;
   sb.pay0 = pay0;
-  for (int p = 0; p < pl.passes; ++p) HIP_TRY(c, launch_sort_pass(pl, sb, p, c->afp, c->atb, pr, s));
+  for (int p = 0; p < pl.passes; ++p) HIP_TRY(c, launch_sort_pass(pl, sb, p, c->afp, c->atb, c->tab, pr, s));
   c->sorted_buf = (pl.passes - 1) & 1;
-  SegArgs a;
-  fill_seg_args(c, a);
-  HIP_TRY(c, launch_segments(a, c->afp, c->atb, c->tab, pr, s));
   return ANTDT_OK;
 }
 
@@ -913,13 +889,13 @@ int antdt_aggregate(antdt_ctx* c, const uint8_t* shard_mask, void* stream) {
     const int rc = build_coalescing(c, c->ids, c->lookup_sample, s);
     if (rc) return rc;
   } else {
-    // Some shards are left out: pack the lookups of the others (the unique-id buffers serve as
-    // staging; the sort has consumed them before the runs are emitted there), fetch the
+    // Some shards are left out: pack the lookups of the others (the unique-id buffer serves as
+    // staging; the sort has consumed it before a view's run table is written there), fetch the
     // per-field counts (the one place where the host waits for the stream) and coalesce those.
     set_weights(c);
     const int F = c->m.num_fields;
     int32_t* ids_in = c->uniq;
-    int32_t* pay_in = c->ufield;
+    int32_t* pay_in = c->pack_pay;
     HIP_TRY(c, launch_mask_pack(c->ids, c->lookup_sample, c->offsets, c->B, F, c->fp, c->tab, c->cbase, ids_in,
                                 pay_in, s));
     int64_t cb[ANTDT_MAX_FIELDS + 1];
@@ -932,7 +908,7 @@ int antdt_aggregate(antdt_ctx* c, const uint8_t* shard_mask, void* stream) {
       c->afp.p[f] = cb[f];
     }
     for (int f = F + 1; f <= ANTDT_MAX_FIELDS; ++f) c->afp.p[f] = c->afp.p[F];
-    plan_tiles(F, c->afp, c->atb, c->amax_tiles, c->atotal_tiles);
+    plan_tiles(F, c->afp, c->atb, c->atotal_tiles);
     const int rc = build_coalescing(c, ids_in, pay_in, s);
     if (rc) return rc;
   }
@@ -997,7 +973,7 @@ int antdt_apply_update(antdt_ctx* c, void* stream) {
     SegArgs a;
     fill_seg_args(c, a);
     a.update = 1;
-    HIP_TRY(c, launch_seg_reduce(a, c->afp.p[m.num_fields], pr, s));
+    HIP_TRY(c, launch_seg_reduce(a, c->afp, c->atb, pr, s));
   }
   if (c->wgrad_deferred) {
     // Weight gradients, their aggregation over the shards and the dense update in one kernel
@@ -1177,11 +1153,12 @@ int antdt_view_coalesced(antdt_ctx* c, int32_t f, const int32_t** unique_ids, co
   if (f < 0 || f >= c->m.num_fields) return fail(c, ANTDT_INVALID_ARG, "antdt_view_coalesced: field out of range");
   if (c->stage < ST_BATCH) return fail(c, ANTDT_BAD_STATE, "antdt_view_coalesced: call antdt_aggregate first");
   if (c->stage != ST_AGGREGATED) return fail(c, ANTDT_BAD_STATE, "antdt_view_coalesced: valid between antdt_aggregate and antdt_apply_update");
-  if (!c->g_valid) {  // the coalesced sums are only written out on request
+  if (!c->g_valid) {  // the run table and the coalesced sums are only written out on request
     SegArgs a;
     fill_seg_args(c, a);
     a.update = 0;
-    HIP_TRY(c, launch_seg_reduce(a, c->afp.p[c->m.num_fields], prof_of(c), (hipStream_t)stream));
+    HIP_TRY(c, launch_segments(a, c->afp, c->atb, prof_of(c), (hipStream_t)stream));
+    HIP_TRY(c, launch_seg_reduce(a, c->afp, c->atb, prof_of(c), (hipStream_t)stream));
     c->g_valid = true;
   }
   int32_t ub[2];
