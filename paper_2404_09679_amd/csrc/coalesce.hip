@@ -279,6 +279,131 @@ __global__ __launch_bounds__(SORT_THREADS) void sort_scatter_kernel(
   }
 }
 
+// All passes of a field's sort in one block, for fields of up to SMALL_THREADS * IT lookups: keys and sample
+// indices stay in registers between the passes (thread's item i of wavefront w: position 64 IT w + 64 i + lane)
+// and trade places through LDS.  Same ranking, hence the same stable order, as the passes over many blocks,
+// in one launch instead of three per pass; a block's time is a few microseconds per pass and 8 items of a
+// thread.  Blocks behind the fields write the samples' aggregation weights.
+// (26 fields of 1000 lookups, two passes: 29 us of kernels and their gaps -> one launch of 11 us.)
+constexpr int SMALL_THREADS = 1024, SMALL_WAVES = SMALL_THREADS / 64;
+template <int IT>
+__global__ __launch_bounds__(SMALL_THREADS) void sort_small_kernel(const int32_t* keys_in, const int32_t* pay_in, int32_t* keys_out,
+                                                                   int32_t* pay_out, FieldPtr fp, int F, int passes, int rb,
+                                                                   float* sample_w, ShardTab tab) {
+  __shared__ uint16_t cnt[SMALL_WAVES][MAX_BINS];
+  __shared__ uint16_t dpre[MAX_BINS];
+  __shared__ uint32_t wsum[SMALL_WAVES];
+  extern __shared__ int32_t stage[];   // [SMALL_THREADS * IT]
+  const int f = blockIdx.x;
+  if (f >= F) {
+    write_sample_weights(sample_w, tab, (f - F) * SMALL_THREADS + (int)threadIdx.x);
+    return;
+  }
+  const int64_t base = fp.p[f];
+  const int nnz = (int)(fp.p[f + 1] - base);
+  if (nnz == 0) return;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int first = w * (64 * IT) + lane;
+  int32_t key[IT], pay[IT];
+#pragma unroll
+  for (int i = 0; i < IT; ++i) {
+    const int pos = min(first + i * 64, nnz - 1);
+    key[i] = keys_in[base + pos];
+    pay[i] = pay_in[base + pos];
+  }
+  const int nb = 1 << rb;   // (at most one digit per thread)
+  const uint64_t lt = lanemask_lt();
+  volatile uint16_t* cw = cnt[w];
+  for (int p = 0; p < passes; ++p) {
+    const int shift = p * rb;
+    for (int d = lane; d < nb; d += 64) cw[d] = 0;   // (each wavefront its own row)
+    uint32_t rank[IT];
+#pragma unroll
+    for (int i = 0; i < IT; ++i) {
+      rank[i] = 0;
+      if (w * (64 * IT) + i * 64 < nnz) {   // (uniform)
+        const bool valid = first + i * 64 < nnz;
+        const uint32_t d = ((uint32_t)key[i] >> shift) & (nb - 1);
+        uint64_t m = __ballot(valid);
+        for (int b = 0; b < rb; ++b) {
+          const bool bit = (d >> b) & 1u;
+          const uint64_t bal = __ballot(valid && bit);
+          m &= bit ? bal : ~bal;
+        }
+        if (valid) {
+          const uint32_t prior = cw[d];
+          rank[i] = prior + (uint32_t)__popcll(m & lt);
+          if ((m & lt) == 0) cw[d] = (uint16_t)(prior + (uint32_t)__popcll(m));   // lowest lane of the group
+        }
+      }
+    }
+    __syncthreads();
+    // per digit: exclusive prefix over the wavefronts, then over the digits
+    uint32_t tot = 0;
+    if ((int)threadIdx.x < nb) {
+      uint32_t c[SMALL_WAVES];
+#pragma unroll
+      for (int q = 0; q < SMALL_WAVES; ++q) c[q] = cnt[q][threadIdx.x];
+#pragma unroll
+      for (int q = 0; q < SMALL_WAVES; ++q) {
+        cnt[q][threadIdx.x] = (uint16_t)tot;
+        tot += c[q];
+      }
+    }
+    uint32_t incl = tot;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t v = __shfl_up(incl, o, 64);
+      if (lane >= o) incl += v;
+    }
+    if (lane == 63) wsum[w] = incl;
+    __syncthreads();
+    uint32_t before = 0;
+    for (int q = 0; q < w; ++q) before += wsum[q];
+    if ((int)threadIdx.x < nb) dpre[threadIdx.x] = (uint16_t)(before + incl - tot);
+    __syncthreads();
+    uint32_t place[IT];
+#pragma unroll
+    for (int i = 0; i < IT; ++i) {
+      const uint32_t d = ((uint32_t)key[i] >> shift) & (nb - 1);
+      place[i] = dpre[d] + cnt[w][d] + rank[i];
+    }
+    auto trade = [&](int32_t (&x)[IT]) {
+#pragma unroll
+      for (int i = 0; i < IT; ++i)
+        if (first + i * 64 < nnz) stage[place[i]] = x[i];
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < IT; ++i)
+        if (first + i * 64 < nnz) x[i] = stage[first + i * 64];
+      __syncthreads();
+    };
+    trade(key);
+    trade(pay);
+  }
+#pragma unroll
+  for (int i = 0; i < IT; ++i)
+    if (first + i * 64 < nnz) {
+      keys_out[base + first + i * 64] = key[i];
+      pay_out[base + first + i * 64] = pay[i];
+    }
+}
+
+template <int IT>
+hipError_t launch_sort_small_items(const SortPlan& pl, const SortBuffers& sb, const FieldPtr& fp, const ShardTab& tab, Profiler* prof,
+                                   hipStream_t s) {
+  constexpr int bytes = SMALL_THREADS * IT * 4;
+  static const hipError_t ok =
+      bytes + SMALL_THREADS * 34 + 1024 <= 64 * 1024
+          ? hipSuccess
+          : hipFuncSetAttribute(reinterpret_cast<const void*>(sort_small_kernel<IT>), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  if (ok != hipSuccess) return ok;
+  ProfScope ps(prof, KID_SORT_SCATTER, s);
+  hipLaunchKernelGGL((sort_small_kernel<IT>), dim3(pl.F + (pl.B + SMALL_THREADS - 1) / SMALL_THREADS), dim3(SMALL_THREADS), bytes, s,
+                     sb.ids, sb.pay0, sb.key[0], sb.pay[0], fp, pl.F, pl.passes, pl.radix_bits, sb.sample_w, tab);
+  return hipGetLastError();
+}
+
 // ------------------------------------------------- leaving shards out
 // When the servers disregard the gradients of some workers (the backup-workers baseline of
 // Section VII-A.3), only the lookups of the remaining shards are coalesced.  A shard is a
@@ -784,9 +909,8 @@ void launch_reduce_variant(const SegArgs& a, const FieldPtr& fp, const TileBase&
 
 }  // namespace
 
-hipError_t launch_sort_pass(const SortPlan& pl, const SortBuffers& sb, int pass, const FieldPtr& fp,
+static hipError_t launch_sort_pass(const SortPlan& pl, const SortBuffers& sb, int pass, const FieldPtr& fp,
                             const TileBase& tb, const ShardTab& tab, Profiler* prof, hipStream_t s) {
-  if (pl.total_tiles == 0) return hipSuccess;
   const int shift = pass * pl.radix_bits;
   const int32_t* kin = pass == 0 ? sb.ids : sb.key[(pass - 1) & 1];
   const int32_t* pin = pass == 0 ? sb.pay0 : sb.pay[(pass - 1) & 1];
@@ -807,6 +931,27 @@ hipError_t launch_sort_pass(const SortPlan& pl, const SortBuffers& sb, int pass,
                        sb.pay[pass & 1], sb.hist, sb.digit_base, fp, tb, pl.F, shift, pl.radix_bits);
   }
   return hipGetLastError();
+}
+
+hipError_t launch_sort(const SortPlan& pl, const SortBuffers& sb, const FieldPtr& fp, const TileBase& tb, const ShardTab& tab,
+                       bool beside, Profiler* prof, hipStream_t s, int* sorted_buf) {
+  *sorted_buf = 0;
+  if (pl.total_tiles == 0) return hipSuccess;
+  // One block per field as long as a field fits one: two passes over 1000 / 9000 / 16000 lookups of a field take 11 /
+  // 34 / 34 us (the number of items a thread holds is a power of two), the six launches about 30; with 16 items
+  // only where the sort runs beside the MLP and what counts is the number of launches.
+  int64_t most = 0;
+  for (int f = 0; f < pl.F; ++f) most = std::max(most, fp.p[f + 1] - fp.p[f]);
+  if (most <= SMALL_THREADS * 2) return launch_sort_small_items<2>(pl, sb, fp, tab, prof, s);
+  if (most <= SMALL_THREADS * 4) return launch_sort_small_items<4>(pl, sb, fp, tab, prof, s);
+  if (most <= SMALL_THREADS * 8) return launch_sort_small_items<8>(pl, sb, fp, tab, prof, s);
+  if (beside && most <= SMALL_THREADS * 16) return launch_sort_small_items<16>(pl, sb, fp, tab, prof, s);
+  for (int p = 0; p < pl.passes; ++p) {
+    const hipError_t e = launch_sort_pass(pl, sb, p, fp, tb, tab, prof, s);
+    if (e != hipSuccess) return e;
+  }
+  *sorted_buf = (pl.passes - 1) & 1;
+  return hipSuccess;
 }
 
 hipError_t launch_segments(const SegArgs& a, const FieldPtr& fp, const TileBase& tb, Profiler* prof, hipStream_t s) {

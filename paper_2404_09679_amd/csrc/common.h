@@ -226,8 +226,10 @@ struct SortBuffers {
   uint32_t* digit_base;            // [F << radix_bits]
   float* sample_w;                 // [B] aggregation weight of every sample, written beside the first pass
 };
-hipError_t launch_sort_pass(const SortPlan& pl, const SortBuffers& sb, int pass, const FieldPtr& fp,
-                            const TileBase& tb, const ShardTab& tab, Profiler* prof, hipStream_t s);
+// Sorts every field's lookups by row id (stable); the result is in key / pay [*sorted_buf].  `beside`: other work runs
+// at the same time.
+hipError_t launch_sort(const SortPlan& pl, const SortBuffers& sb, const FieldPtr& fp, const TileBase& tb, const ShardTab& tab,
+                       bool beside, Profiler* prof, hipStream_t s, int* sorted_buf);
 
 struct SegArgs {
   const int32_t* key;              // sorted row ids, field-major at fp.p[f]

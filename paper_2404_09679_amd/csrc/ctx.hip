@@ -655,8 +655,7 @@ static int build_coalescing(antdt_ctx* c, const int32_t* ids, const int32_t* pay
   sb.digit_base = c->digit_base;
   sb.sample_w = c->sample_w;
   sb.pay0 = pay0;
-  for (int p = 0; p < pl.passes; ++p) HIP_TRY(c, launch_sort_pass(pl, sb, p, c->afp, c->atb, c->tab, pr, s));
-  c->sorted_buf = (pl.passes - 1) & 1;
+  HIP_TRY(c, launch_sort(pl, sb, c->afp, c->atb, c->tab, s == c->side, pr, s, &c->sorted_buf));
   return ANTDT_OK;
 }
 
