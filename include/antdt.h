@@ -191,9 +191,9 @@ int antdt_assign_shard(antdt_ctx* ctx, int64_t B, int32_t K, const int64_t* size
  * the shard, flat layout) and d loss_k / d pooled-embedding for each of its samples — the
  * pair (ids, that gradient) is the shard's sparse gradient.  loss_out: DEVICE fp32 [1], may
  * be NULL.  Requires set_batch and assign_shard with matching B.
- * Everything is enqueued on `stream` except the weight gradients of the hidden layers, which the
- * library computes on a stream of its own, beside the rest of the backward pass or inside
- * antdt_apply_update (see antdt_set_eager_weight_gradients): the dense parameters are complete, in
+ * Everything is enqueued on `stream` except the weight gradients of bf16 models, which by default
+ * are formed inside antdt_apply_update, which may use a stream of the library's own
+ * (see antdt_set_eager_weight_gradients): the dense parameters are complete, in
  * the order of `stream`, after antdt_apply_update; antdt_view_shard_grads computes the per-shard
  * gradients if need be and waits for them on the host.
  */
@@ -246,9 +246,9 @@ int antdt_set_eager_weight_gradients(antdt_ctx* ctx, int32_t on);
  * on == 0: every kernel of the following iterations is enqueued on the caller's stream, one
  * after the other, although the context owns streams (the order a context bound by
  * antdt_bind_static always uses: per-kernel durations without overlap, captures of a whole
- * iteration on one stream).  on != 0 (the state after antdt_bind): the sort and run detection run
- * on a stream of the library beside the MLP, the weight-gradient work on another beside the
- * input-gradient product and the sparse update.  Results are the same.  To be called between
+ * iteration on one stream).  on != 0 (the state after antdt_bind): where the batch is large enough
+ * for it to pay, the sort runs on a stream of the library beside the MLP, and the weight-gradient
+ * work on another beside the sparse update.  Results are the same.  To be called between
  * iterations (ANTDT_BAD_STATE while work of an iteration is outstanding).  Host only.
  */
 int antdt_set_library_streams(antdt_ctx* ctx, int32_t on);
@@ -420,7 +420,7 @@ int antdt_fill_tables(void* tables, int32_t dtype, int32_t num_fields, int64_t r
 int antdt_view_pooled(antdt_ctx* ctx, int32_t k, const void** x, int64_t* rows, int64_t* ld,
                       int32_t* dtype);
 /* Shard k's dense gradient (fp32, flat layout) and d loss_k / d pooled (fp32 [B_k, ld_dx]).
- * Waits (on the host) for the library's own stream that writes the weight gradients; the
+ * Waits (on the host) for the library's own stream if the weight gradients are written there; the
  * caller still synchronises the stream it passed to antdt_worker_step before reading. */
 int antdt_view_shard_grads(antdt_ctx* ctx, int32_t k, const float** dense, const float** dx,
                            int64_t* ld_dx);

@@ -169,9 +169,20 @@ struct antdt_ctx {
   int static_device = -1;
 };
 
-// The library's own streams, or none when the context works on the caller's stream only.
-static inline hipStream_t side_stream(const antdt_ctx* c) { return (c->static_bound || c->no_streams) ? nullptr : c->side; }
-static inline hipStream_t wgrad_stream(const antdt_ctx* c) { return (c->static_bound || c->no_streams) ? nullptr : c->wside; }
+// The library's own streams, or none when the context works on the caller's stream only.  Going to another stream
+// and back costs the host about 25 us (the waits on events), so it has to hide that much GPU work.
+//   Sort: all but the smallest batches (5 000 / 26 000 / 140 000 lookups, sort on the side or not: 71 / 62, 92 / 95 and
+//   106 / 115 us per step).
+//   Dense update beside the sparse one: where there are many lookups or many weights (26 fields, 1024-512-256:
+//   26 000 / 70 000 / 140 000 / 560 000 lookups, beside or after: 98 / 92, 107 / 101, 106 / 108, 137 / 145 us per
+//   step; 3840-1024-512 at 50 000: 102 / 122).  fp32 models never (171 / 176 us at 430 000 lookups).
+static inline hipStream_t side_stream(const antdt_ctx* c) {
+  return (c->static_bound || c->no_streams || c->fp.p[c->m.num_fields] < 16384) ? nullptr : c->side;
+}
+static inline hipStream_t wgrad_stream(const antdt_ctx* c) {
+  const bool enough = c->act_bf16 && (c->fp.p[c->m.num_fields] >= 100000 || c->P >= 2000000);
+  return (c->static_bound || c->no_streams || !enough) ? nullptr : c->wside;
+}
 
 static int fail(antdt_ctx* c, int code, const std::string& msg) {
   if (c) c->err = msg;
@@ -800,20 +811,19 @@ static int worker_range(antdt_ctx* c, int k0, int k1, float* loss_out, hipStream
     ProfScope ps(pr, KID_HEAD, s);
     HIP_TRY(c, launch_head_tiles(a, tab, s));
   }
-  // Backward.  The data-gradient chain dH_{l+1} -> dH_l stays on the launch stream; nothing needs the weight
-  // gradients before the dense update.  With bf16 products they are not computed here at all, unless the
-  // caller asked for them or the library may have no streams of its own: apply_update forms them inside the
-  // dense update (aggregated over the shards in registers, never written per shard), and this step only
-  // records when their operands are complete; the per-shard gradients of the contract are computed when a
-  // view asks for them.  fp32 models are small: their per-shard gradients are one short launch here.
-  hipStream_t ws = c->act_bf16 && wgrad_stream(c) ? wgrad_stream(c) : s;
+  // Backward.  The data-gradient chain dH_{l+1} -> dH_l first; nothing needs the weight gradients before the dense
+  // update.  With bf16 products they are not computed here at all, unless the caller asked for them or the
+  // library may have no streams of its own: apply_update forms them inside the dense update (aggregated over
+  // the shards in registers, never written per shard), and this step only records when their operands are
+  // complete; the per-shard gradients of the contract are computed when a view asks for them.  Otherwise
+  // (fp32 models: they are small) one launch behind the chain: beside the input gradient on another stream it would
+  // hide less than the hop costs (one worker's step on 64 / 1531 samples: 87 / 109 us that way, 54 / 78 here).
   const bool deferred = c->act_bf16 && c->wside && !c->static_bound && !c->eager_wgrad;
   c->wgrad_deferred = deferred;
   c->shard_grads_done = false;
   // The event behind the last operand of the weight gradients (with up to one hidden layer the loss kernel
   // writes it, else the data gradient of layer 1).
-  const bool mark = deferred || ws != s;
-  if (mark && L <= 2) HIP_TRY(c, hipEventRecord(c->ev_dh[0], s));
+  if (deferred && L <= 2) HIP_TRY(c, hipEventRecord(c->ev_dh[0], s));
   ProfScope bwd_scope(L > 1 ? pr : nullptr, KID_GEMM_BWD, s);
   bwd_scope.launches(L - 1);
   for (int l = L - 2; l >= 0; --l) {   // gradient w.r.t. act_l: through W_l, then the ReLU of layer l-1 (none for the input)
@@ -832,17 +842,12 @@ static int worker_range(antdt_ctx* c, int k0, int k1, float* loss_out, hipStream
       g.epi = EPI_PLAIN; g.bf16_out = 0;
     }
     HIP_TRY(c, launch_gemm(g, s));
-    if (l == 1 && mark) HIP_TRY(c, hipEventRecord(c->ev_dh[0], s));
+    if (l == 1 && deferred) HIP_TRY(c, hipEventRecord(c->ev_dh[0], s));
   }
   bwd_scope.close();
   if (!deferred) {
-    if (ws != s) HIP_TRY(c, hipStreamWaitEvent(ws, c->ev_dh[0], 0));
-    const int rc = shard_weight_gradients(c, k0, k1, ws);
+    const int rc = shard_weight_gradients(c, k0, k1, s);
     if (rc) return rc;
-    if (ws != s) {
-      HIP_TRY(c, hipEventRecord(c->ev_wgrad, ws));
-      c->wgrad_pending = true;
-    }
   }
   for (int k = k0; k < k1; ++k) c->stepped[k] = true;
   if (c->stage == ST_AGGREGATED) c->stage = ST_BATCH;
