@@ -31,14 +31,10 @@ template <> __device__ __forceinline__ void store_row<float, 8>(float* dst, cons
   reinterpret_cast<float4*>(dst)[1] = make_float4(v[4], v[5], v[6], v[7]);
 }
 template <> __device__ __forceinline__ void store_row<bf16_t, 4>(bf16_t* dst, const float* v) {
-  *reinterpret_cast<uint2*>(dst) = make_uint2((uint32_t)f2bf(v[0]) | ((uint32_t)f2bf(v[1]) << 16),
-                                              (uint32_t)f2bf(v[2]) | ((uint32_t)f2bf(v[3]) << 16));
+  *reinterpret_cast<uint2*>(dst) = make_uint2(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]));
 }
 template <> __device__ __forceinline__ void store_row<bf16_t, 8>(bf16_t* dst, const float* v) {
-  *reinterpret_cast<uint4*>(dst) = make_uint4((uint32_t)f2bf(v[0]) | ((uint32_t)f2bf(v[1]) << 16),
-                                              (uint32_t)f2bf(v[2]) | ((uint32_t)f2bf(v[3]) << 16),
-                                              (uint32_t)f2bf(v[4]) | ((uint32_t)f2bf(v[5]) << 16),
-                                              (uint32_t)f2bf(v[6]) | ((uint32_t)f2bf(v[7]) << 16));
+  *reinterpret_cast<uint4*>(dst) = make_uint4(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]), f2bf2(v[4], v[5]), f2bf2(v[6], v[7]));
 }
 
 // Dense-feature columns of 64 samples: copied behind the pooled embeddings, the padding columns of
@@ -58,64 +54,78 @@ __device__ __forceinline__ void dense_columns(const PoolArgs& a, int sl0) {
 
 // Gather and sum-pool.  A block owns 64 consecutive samples of one field; a group of
 // LPR = D*sizeof(T)/16 lanes owns one bag, so a wavefront works on 64/LPR bags at once.
-// The group fetches LPR ids with one coalesced load, hands them round with lane
-// shuffles and issues the LPR row loads (16 bytes per lane, one whole row per group)
-// back to back before adding them, which keeps 64 rows in flight per wavefront.  Every
-// lookup's sample index is recorded for the sort.
-template <typename TT, typename OT, int LPR>
+// The group fetches LPR ids with one coalesced load, hands the rows' places round with lane
+// exchanges and issues the LPR row loads (16 bytes per lane, one whole row per group)
+// back to back before adding them, which keeps 64 rows in flight per wavefront; the next ids are
+// requested before the rows are waited for.  Every lookup's sample index is recorded for the sort.
+// Bound by vector instructions where bags are long (of 57 per row and wavefront 16 unpack and add a bf16 row;
+// bounds and addresses are therefore worked out once per lookup, by the lane that loads its id), else by
+// round trips.  Like the sort's tiles, the blocks of a field go to one XCD: its rows are fetched into one L2.
+// WIDE: a table of 2^32 or more 16-byte pieces.
+template <typename TT, typename OT, int LPR, bool WIDE>
 __global__ __launch_bounds__(256) void pool_tile_kernel(PoolArgs a, FieldPtr fp) {
   constexpr int EV = Vec16<TT>::N;
   constexpr int G = 256 / LPR;       // bags per round
   constexpr int ROUNDS = 64 / G;
-  const int f = blockIdx.y, sl0 = blockIdx.x * 64;
+  const int tiles = (a.ns + 63) >> 6, total = tiles * (a.F + 1), share = (total + 7) >> 3;
+  const int idx = (int)(blockIdx.x & 7) * share + (int)(blockIdx.x >> 3);
+  if ((int)(blockIdx.x >> 3) >= share || idx >= total) return;
+  const int f = idx / tiles, sl0 = (idx - f * tiles) * 64;
   if (f == a.F) {
     dense_columns<OT>(a, sl0);
     return;
   }
   const int g = threadIdx.x / LPR, c = threadIdx.x % LPR;
-  const int gl = (threadIdx.x & 63) - c;  // first lane of this group inside the wavefront
+  const int gl4 = ((threadIdx.x & 63) - c) * 4;  // first lane of this group inside the wavefront
   const int32_t* ids = a.ids + fp.p[f];
-  const TT* tab = reinterpret_cast<const TT*>(a.tables) + (int64_t)f * a.R * a.D + c * EV;
+  int32_t* smp = a.lookup_sample ? a.lookup_sample + fp.p[f] : nullptr;
+  const uint4* tab = reinterpret_cast<const uint4*>(reinterpret_cast<const TT*>(a.tables) + (int64_t)f * a.R * a.D) + c;
+  const int last = (int)(a.R - 1);
+  auto fetch = [&](int j, int end) { return j < end ? ids[j] : 0; };
+  int begin[ROUNDS], end[ROUNDS];
 #pragma unroll
   for (int r = 0; r < ROUNDS; ++r) {
     const int ls = r * G + g;
-    const bool valid = sl0 + ls < a.ns;
-    const int64_t s = a.s0 + sl0 + ls;
-    int begin = 0, end = 0;
-    if (valid) {
-      const int32_t* off = a.offsets + (int64_t)f * (a.B + 1) + s;
-      begin = off[0];
-      end = off[1];
+    begin[r] = end[r] = 0;
+    if (sl0 + ls < a.ns) {
+      const int32_t* off = a.offsets + (int64_t)f * (a.B + 1) + a.s0 + sl0 + ls;
+      begin[r] = off[0];
+      end[r] = off[1];
     }
+  }
+#pragma unroll
+  for (int r = 0; r < ROUNDS; ++r) {
+    const int ls = r * G + g;
+    const int64_t s = a.s0 + sl0 + ls;
+    const int b0 = begin[r], e0 = end[r];
     float acc[EV];
 #pragma unroll
     for (int e = 0; e < EV; ++e) acc[e] = 0.0f;
-    for (int jb = begin; jb < end; jb += LPR) {
-      const int my_j = jb + c;
-      int my_id = 0;
-      if (my_j < end) {
-        my_id = ids[my_j];
-        if (a.lookup_sample) a.lookup_sample[fp.p[f] + my_j] = (int32_t)s;
-      }
+    int next = fetch(b0 + c, e0);
+    for (int jb = b0; jb < e0; jb += LPR) {
+      const int id = min(max(next, 0), last);   // keeps a bad id in bounds
+      const uint32_t mine = WIDE ? (uint32_t)id : (uint32_t)id * LPR;
+      if (smp && jb + c < e0) smp[jb + c] = (int32_t)s;
+      next = fetch(jb + LPR + c, e0);
       Vec16<TT> v[LPR];
 #pragma unroll
       for (int q = 0; q < LPR; ++q) {
-        const int64_t row = min(max((int64_t)__shfl(my_id, gl + q, 64), (int64_t)0), a.R - 1);
-        if (jb + q < end) v[q].v = *reinterpret_cast<const decltype(v[q].v)*>(tab + row * a.D);
+        const uint32_t o = (uint32_t)__builtin_amdgcn_ds_bpermute(gl4 + q * 4, (int)mine);
+        if (jb + q < e0) v[q].v = *reinterpret_cast<const decltype(v[q].v)*>(tab + (WIDE ? (uint64_t)o * LPR : (uint64_t)o));
       }
 #pragma unroll
       for (int q = 0; q < LPR; ++q)
-        if (jb + q < end) {
+        if (jb + q < e0) {
 #pragma unroll
           for (int e = 0; e < EV; ++e) acc[e] += v[q].get(e);
         }
     }
-    if (a.mean_pool && end - begin > 1) {
-      const float len = (float)(end - begin);
+    if (a.mean_pool && e0 - b0 > 1) {
+      const float len = (float)(e0 - b0);
 #pragma unroll
       for (int e = 0; e < EV; ++e) acc[e] /= len;
     }
-    if (valid) store_row<OT, EV>(reinterpret_cast<OT*>(a.x) + s * a.ldx + f * a.D + c * EV, acc);
+    if (sl0 + ls < a.ns) store_row<OT, EV>(reinterpret_cast<OT*>(a.x) + s * a.ldx + f * a.D + c * EV, acc);
   }
 }
 
@@ -168,17 +178,23 @@ __global__ __launch_bounds__(256) void pool_dense_kernel(PoolArgs a) {
   dense_columns<OT>(a, blockIdx.x * 64);
 }
 
+template <typename TT, typename OT, int LPR>
+static void launch_pool_tiles(const PoolArgs& a, const FieldPtr& fp, hipStream_t s) {
+  const dim3 grid(8 * (((a.ns + 63) / 64 * (a.F + 1) + 7) / 8)), block(256);
+  if ((uint64_t)a.R * LPR >> 32) hipLaunchKernelGGL((pool_tile_kernel<TT, OT, LPR, true>), grid, block, 0, s, a, fp);
+  else hipLaunchKernelGGL((pool_tile_kernel<TT, OT, LPR, false>), grid, block, 0, s, a, fp);
+}
+
 template <typename TT, typename OT>
 static void launch_pool_typed(const PoolArgs& a, const FieldPtr& fp, hipStream_t s) {
   const int lpr = a.D / Vec16<TT>::N;
-  dim3 grid((a.ns + 63) / 64, a.F + 1), block(256);
-  if (lpr == 4) hipLaunchKernelGGL((pool_tile_kernel<TT, OT, 4>), grid, block, 0, s, a, fp);
-  else if (lpr == 8) hipLaunchKernelGGL((pool_tile_kernel<TT, OT, 8>), grid, block, 0, s, a, fp);
-  else if (lpr == 16) hipLaunchKernelGGL((pool_tile_kernel<TT, OT, 16>), grid, block, 0, s, a, fp);
+  if (lpr == 4) launch_pool_tiles<TT, OT, 4>(a, fp, s);
+  else if (lpr == 8) launch_pool_tiles<TT, OT, 8>(a, fp, s);
+  else if (lpr == 16) launch_pool_tiles<TT, OT, 16>(a, fp, s);
   else {
     const int64_t items = (int64_t)a.ns * a.F;
-    hipLaunchKernelGGL((pool_kernel<TT, OT>), dim3((unsigned)((items + 3) / 4)), block, 0, s, a, fp);
-    hipLaunchKernelGGL((pool_dense_kernel<OT>), dim3((a.ns + 63) / 64), block, 0, s, a);
+    hipLaunchKernelGGL((pool_kernel<TT, OT>), dim3((unsigned)((items + 3) / 4)), dim3(256), 0, s, a, fp);
+    hipLaunchKernelGGL((pool_dense_kernel<OT>), dim3((a.ns + 63) / 64), dim3(256), 0, s, a);
   }
 }
 

@@ -9,8 +9,6 @@
 namespace antdt {
 namespace {
 
-__device__ __forceinline__ uint32_t pack2(float a, float b) { return (uint32_t)f2bf(a) | ((uint32_t)f2bf(b) << 16); }
-
 // Two packed bf16 values, each kept where the matching mask value is positive.
 __device__ __forceinline__ uint32_t relu_mask2(uint32_t v, uint32_t mk) {
   const uint32_t lo = ((mk & 0x8000u) == 0 && (mk & 0x7FFFu) != 0) ? 0x0000FFFFu : 0u;
@@ -102,7 +100,7 @@ __global__ __launch_bounds__(64 * WR * WC * WK) void gemm_bf16_kernel(GemmArgs p
 #pragma unroll
             for (int e = 0; e < 4; ++e) x[e] = fmaxf(x[e], 0.0f);
           }
-          *reinterpret_cast<uint2*>(st + fr * SP + c) = make_uint2(pack2(x[0], x[1]), pack2(x[2], x[3]));
+          *reinterpret_cast<uint2*>(st + fr * SP + c) = make_uint2(f2bf2(x[0], x[1]), f2bf2(x[2], x[3]));
         }
       wave_lds_fence();
 #pragma unroll
@@ -285,7 +283,7 @@ __global__ __launch_bounds__(64 * WR * WC) void wgrad_kernel(WgradArgs u, KSegme
     p1.w = adagrad1(p0.w, s1.w, g.w, u.lr, u.eps);
     *reinterpret_cast<float4*>(S + idx) = s1;
     *reinterpret_cast<float4*>(Pm + idx) = p1;
-    if (weight) *reinterpret_cast<uint2*>(Wb + idx) = make_uint2(pack2(p1.x, p1.y), pack2(p1.z, p1.w));
+    if (weight) *reinterpret_cast<uint2*>(Wb + idx) = make_uint2(f2bf2(p1.x, p1.y), f2bf2(p1.z, p1.w));
   };
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
