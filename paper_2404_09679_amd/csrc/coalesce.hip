@@ -137,6 +137,21 @@ __global__ __launch_bounds__(MAX_BINS) void sort_scan_kernel(uint32_t* hist, uin
   if (d < nb) digit_base[((int64_t)f << rb) + d] = wbase + incl - run;
 }
 
+// Lanes (among the valid ones) that hold the same digit.  Per bit: the lane's bit spread over a word, one compare
+// for the ballot, and one three-operand logic operation per half of the mask (these instructions are what
+// bounds the sort's scatter).
+__device__ __forceinline__ uint64_t same_digit(uint32_t d, int rb, bool valid) {
+  const uint64_t all = __ballot(valid);
+  uint32_t lo = (uint32_t)all, hi = (uint32_t)(all >> 32);
+  for (int b = 0; b < rb; ++b) {
+    const uint32_t mine = (uint32_t)__builtin_amdgcn_sbfe((int)d, b, 1);   // 0 or ~0
+    const uint64_t bal = __ballot(mine != 0);
+    lo &= ~(mine ^ (uint32_t)bal);
+    hi &= ~(mine ^ (uint32_t)(bal >> 32));
+  }
+  return (uint64_t)lo | ((uint64_t)hi << 32);
+}
+
 // Stable scatter of one tile.  Wave w owns the contiguous slice w of the tile and walks it in
 // rounds of 64 keys; lanes holding equal digits find each other with one
 // ballot per digit bit, the per-wave running count of the digit lives in LDS.
@@ -181,12 +196,7 @@ __global__ __launch_bounds__(SORT_THREADS) void sort_scatter_kernel(
     const int pos = t * SORT_TILE + w * (64 * SORT_ITEMS) + i * 64 + lane;
     const bool valid = pos < nnz;
     const uint32_t d = ((uint32_t)key[i] >> shift) & (nb - 1);
-    uint64_t m = __ballot(valid);
-    for (int b = 0; b < rb; ++b) {
-      const bool bit = (d >> b) & 1u;
-      const uint64_t bal = __ballot(valid && bit);
-      m &= bit ? bal : ~bal;
-    }
+    const uint64_t m = same_digit(d, rb, valid);
     rank[i] = 0;
     if (valid) {
       const uint32_t prior = cw[d];
@@ -324,12 +334,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void sort_small_kernel(const int32_t
       if (w * (64 * IT) + i * 64 < nnz) {   // (uniform)
         const bool valid = first + i * 64 < nnz;
         const uint32_t d = ((uint32_t)key[i] >> shift) & (nb - 1);
-        uint64_t m = __ballot(valid);
-        for (int b = 0; b < rb; ++b) {
-          const bool bit = (d >> b) & 1u;
-          const uint64_t bal = __ballot(valid && bit);
-          m &= bit ? bal : ~bal;
-        }
+        const uint64_t m = same_digit(d, rb, valid);
         if (valid) {
           const uint32_t prior = cw[d];
           rank[i] = prior + (uint32_t)__popcll(m & lt);
@@ -554,7 +559,7 @@ __global__ __launch_bounds__(SORT_THREADS) void seg_emit_kernel(SegArgs a, Field
 }
 
 // ------------------------------------------------- weighted run sums (+ update)
-struct Row4 {
+struct RowSum {   // a lane's four columns (4c .. 4c + 3, c: the lane inside its group of D/4)
   float v[4];
 };
 
@@ -567,97 +572,98 @@ __device__ __forceinline__ float lookup_weight(const SegArgs& a, const int32_t* 
   return w / (float)max(off[s + 1] - off[s], 1);
 }
 
-// g += w(lookup) * dX[sample, field slice] over the `n` lookups whose samples are pay[0 .. n), added in order.
-template <bool MEAN>
-__device__ __forceinline__ void accumulate_run(const SegArgs& a, int f, int c, const int32_t* pay, int n, Row4& g) {
-  const float* dxcol = a.dx + f * a.D + c * 4;
-  const int32_t* off = MEAN ? a.offsets + (int64_t)f * (a.B + 1) : nullptr;
-  auto add = [&](float w, const float4& x) {
-    g.v[0] = fmaf(w, x.x, g.v[0]);
-    g.v[1] = fmaf(w, x.y, g.v[1]);
-    g.v[2] = fmaf(w, x.z, g.v[2]);
-    g.v[3] = fmaf(w, x.w, g.v[3]);
-  };
-  auto whole = [&](int i) {   // four lookups in flight
-    constexpr int NF = 4;
-    float w[NF];
-    float4 x[NF];
+// What the sums need of a sorted lookup, worked out once per lookup when it is staged (and not by each of the D/4
+// lanes that then use it): its sample's byte offset in dX, and its weight.
+struct __attribute__((aligned(16))) Lookup {
+  uint64_t offset;
+  float w;
+  int32_t unused;
+};
+
+// g += w(lookup) * dX[sample, field slice] over `n` staged lookups, added in order, four in flight; dx: this lane's
+// columns of sample 0.
+__device__ __forceinline__ void accumulate_run(const char* dx, const Lookup* look, int n, RowSum& g) {
+  for (int i = 0; i < n; i += 4) {
+    float w[4];
+    float4 x[4];
 #pragma unroll
-    for (int q = 0; q < NF; ++q) {
-      const int s = min(max(pay[i + q], 0), a.B - 1);
-      w[q] = lookup_weight<MEAN>(a, off, s);
-      x[q] = *reinterpret_cast<const float4*>(dxcol + (int64_t)s * a.lddx);
-    }
-#pragma unroll
-    for (int q = 0; q < NF; ++q) add(w[q], x[q]);
-  };
-  int i = 0;
-  for (; i + 4 <= n; i += 4) whole(i);
-  if (i < n) {   // up to three more
-    float w[3];
-    float4 x[3];
-#pragma unroll
-    for (int q = 0; q < 3; ++q)
+    for (int q = 0; q < 4; ++q)
       if (i + q < n) {
-        const int s = min(max(pay[i + q], 0), a.B - 1);
-        w[q] = lookup_weight<MEAN>(a, off, s);
-        x[q] = *reinterpret_cast<const float4*>(dxcol + (int64_t)s * a.lddx);
+        const Lookup l = look[i + q];
+        w[q] = l.w;
+        x[q] = *reinterpret_cast<const float4*>(dx + l.offset);
       }
 #pragma unroll
-    for (int q = 0; q < 3; ++q)
-      if (i + q < n) add(w[q], x[q]);
+    for (int q = 0; q < 4; ++q)
+      if (i + q < n) {
+        g.v[0] = fmaf(w[q], x[q].x, g.v[0]);
+        g.v[1] = fmaf(w[q], x[q].y, g.v[1]);
+        g.v[2] = fmaf(w[q], x[q].z, g.v[2]);
+        g.v[3] = fmaf(w[q], x[q].w, g.v[3]);
+      }
   }
 }
 
-// Row-sparse Adagrad of one table row by its lane group (lane c owns columns 4c .. 4c+3):
+__device__ __forceinline__ void add_floats(RowSum& g, const float* x) {
+  const float4 v = *reinterpret_cast<const float4*>(x);
+  g.v[0] += v.x; g.v[1] += v.y; g.v[2] += v.z; g.v[3] += v.w;
+}
+__device__ __forceinline__ void store_floats(float* x, const RowSum& g) {
+  *reinterpret_cast<float4*>(x) = make_float4(g.v[0], g.v[1], g.v[2], g.v[3]);
+}
+
+// A lane's columns of one table row and of its accumulators, as they lie in memory, and the row-sparse Adagrad step:
 //   element-wise: S += g^2;                 p -= lr * g / (sqrt(S) + eps)
 //   row-wise:     S[r] += mean_d g[r,d]^2;  p -= lr * g / (sqrt(S[r]) + eps)
 // bf16 tables are written back round-to-nearest-even.
-template <typename TT, bool ROWWISE>
-__device__ __forceinline__ void adagrad_row(const SegArgs& a, int64_t row, int c, int lps, const Row4& g,
-                                            const float (&p0)[4], const float4& s0, float srow0) {
-  float den[4], p[4];
-  if (ROWWISE) {
-    float sq = (g.v[0] * g.v[0] + g.v[1] * g.v[1]) + (g.v[2] * g.v[2] + g.v[3] * g.v[3]);
-    for (int o = 1; o < lps; o <<= 1) sq += __shfl_xor(sq, o, 64);
-    const float s1 = srow0 + sq / (float)a.D;
-    if (c == 0) a.state[row] = s1;
-    den[0] = den[1] = den[2] = den[3] = sqrtf(s1) + a.eps;
-  } else {
-    float4 sv = s0;
-    sv.x = fmaf(g.v[0], g.v[0], sv.x);
-    sv.y = fmaf(g.v[1], g.v[1], sv.y);
-    sv.z = fmaf(g.v[2], g.v[2], sv.z);
-    sv.w = fmaf(g.v[3], g.v[3], sv.w);
-    *reinterpret_cast<float4*>(a.state + row * a.D + c * 4) = sv;
-    den[0] = sqrtf(sv.x) + a.eps; den[1] = sqrtf(sv.y) + a.eps;
-    den[2] = sqrtf(sv.z) + a.eps; den[3] = sqrtf(sv.w) + a.eps;
+template <typename TT, bool ROWWISE> struct TableRow {
+  uint4 p;          // (bf16: x and y only)
+  float4 s;
+  float srow;
+  __device__ __forceinline__ void load(const SegArgs& a, int64_t row, int c) {
+    const TT* src = reinterpret_cast<const TT*>(a.tables) + row * a.D + c * 4;
+    if (sizeof(TT) == 4) {
+      p = *reinterpret_cast<const uint4*>(src);
+    } else {
+      const uint2 v = *reinterpret_cast<const uint2*>(src);
+      p.x = v.x;
+      p.y = v.y;
+    }
+    if (ROWWISE) srow = a.state[row];
+    else s = *reinterpret_cast<const float4*>(a.state + row * a.D + c * 4);
   }
+  __device__ __forceinline__ void update(const SegArgs& a, int64_t row, int c, int lps, const RowSum& g) const {
+    float den[4];
+    if (ROWWISE) {
+      float sq = (g.v[0] * g.v[0] + g.v[1] * g.v[1]) + (g.v[2] * g.v[2] + g.v[3] * g.v[3]);
+      for (int o = 1; o < lps; o <<= 1) sq += __shfl_xor(sq, o, 64);
+      const float s1 = srow + sq / (float)a.D;
+      if (c == 0) a.state[row] = s1;
+      den[0] = den[1] = den[2] = den[3] = sqrtf(s1) + a.eps;
+    } else {
+      float4 sv = s;
+      sv.x = fmaf(g.v[0], g.v[0], sv.x);
+      sv.y = fmaf(g.v[1], g.v[1], sv.y);
+      sv.z = fmaf(g.v[2], g.v[2], sv.z);
+      sv.w = fmaf(g.v[3], g.v[3], sv.w);
+      *reinterpret_cast<float4*>(a.state + row * a.D + c * 4) = sv;
+      den[0] = sqrtf(sv.x) + a.eps; den[1] = sqrtf(sv.y) + a.eps;
+      den[2] = sqrtf(sv.z) + a.eps; den[3] = sqrtf(sv.w) + a.eps;
+    }
+    float p0[4], p1[4];
+    if (sizeof(TT) == 4) {
+      p0[0] = __uint_as_float(p.x); p0[1] = __uint_as_float(p.y); p0[2] = __uint_as_float(p.z); p0[3] = __uint_as_float(p.w);
+    } else {
+      p0[0] = __uint_as_float(p.x << 16); p0[1] = __uint_as_float(p.x & 0xFFFF0000u);
+      p0[2] = __uint_as_float(p.y << 16); p0[3] = __uint_as_float(p.y & 0xFFFF0000u);
+    }
 #pragma unroll
-  for (int e = 0; e < 4; ++e) p[e] = p0[e] - a.lr * g.v[e] / den[e];
-  TT* prow = reinterpret_cast<TT*>(a.tables) + row * a.D + c * 4;
-  if (sizeof(TT) == 4) {
-    *reinterpret_cast<float4*>(prow) = make_float4(p[0], p[1], p[2], p[3]);
-  } else {
-    *reinterpret_cast<uint2*>(prow) = make_uint2((uint32_t)f2bf(p[0]) | ((uint32_t)f2bf(p[1]) << 16),
-                                                 (uint32_t)f2bf(p[2]) | ((uint32_t)f2bf(p[3]) << 16));
+    for (int e = 0; e < 4; ++e) p1[e] = p0[e] - a.lr * g.v[e] / den[e];
+    TT* dst = reinterpret_cast<TT*>(a.tables) + row * a.D + c * 4;
+    if (sizeof(TT) == 4) *reinterpret_cast<float4*>(dst) = make_float4(p1[0], p1[1], p1[2], p1[3]);
+    else *reinterpret_cast<uint2*>(dst) = make_uint2(f2bf2(p1[0], p1[1]), f2bf2(p1[2], p1[3]));
   }
-}
-
-template <typename TT, bool ROWWISE>
-__device__ __forceinline__ void load_row(const SegArgs& a, int64_t row, int c, float (&p0)[4], float4& s0, float& srow0) {
-  const TT* prow = reinterpret_cast<const TT*>(a.tables) + row * a.D + c * 4;
-  if (sizeof(TT) == 4) {
-    const float4 v = *reinterpret_cast<const float4*>(prow);
-    p0[0] = v.x; p0[1] = v.y; p0[2] = v.z; p0[3] = v.w;
-  } else {
-    const uint2 v = *reinterpret_cast<const uint2*>(prow);
-    p0[0] = __uint_as_float(v.x << 16); p0[1] = __uint_as_float(v.x & 0xFFFF0000u);
-    p0[2] = __uint_as_float(v.y << 16); p0[3] = __uint_as_float(v.y & 0xFFFF0000u);
-  }
-  if (ROWWISE) srow0 = a.state[row];
-  else s0 = *reinterpret_cast<const float4*>(a.state + row * a.D + c * 4);
-}
+};
 
 // Run u of field f that starts at absolute position `pos` of the sorted lookups (run table present).
 __device__ __forceinline__ int64_t run_index(const SegArgs& a, int f, int pos) {
@@ -676,26 +682,27 @@ __device__ __forceinline__ int64_t run_index(const SegArgs& a, int f, int pos) {
 // A block takes a window of W sorted lookups, straight from the sort: keys and sample indices of the window
 // (and of LONG_RUN lookups on either side) go to LDS, the block finds the runs' heads there, and groups of
 // D/4 lanes take one item of work each: a whole run of up to LONG_RUN lookups that starts in the window (it may
-// end behind it), summed in sorted (= sample) order, or, of longer runs, a piece of at most 32 lookups
-// that ends at a multiple of 32 in the window.  The pieces' sums meet in LDS in order; what of a run leaves the window
+// end behind it), summed in sorted (= sample) order, or, of longer runs, a piece of at most LONG_RUN lookups
+// that ends at a multiple of LONG_RUN in the window.  The pieces' sums meet in LDS in order; what of a run leaves the window
 // goes to memory (two slots per window: the run that comes in, the run that goes out) and is added up by
 // seg_finish_kernel.  No run table is needed (counting, scanning and writing one, with lists of the long
 // runs, were six launches and 10-250 us between sort and reduction), only keys, sample indices and the rows
 // themselves are read, and the chain of dependent accesses is down to LDS -> row and pooled gradients.
 // Bound by the rows and accumulators (HBM) where runs are short, by the pooled-gradient rows (L2 and the
 // memory-side cache) where they are long.
-constexpr int LONG_RUN = 32;
+constexpr int LONG_RUN = 16;
 
 template <typename TT, bool ROWWISE, bool UPDATE, bool MEAN, int W>
 __global__ __launch_bounds__(256) void seg_window_kernel(SegArgs a, FieldPtr fp, TileBase tb) {
   constexpr int PARTS = SORT_TILE / W, ROUNDS = W / 256;
-  __shared__ int32_t key_[W + 2 * LONG_RUN + 1];    // positions -LONG_RUN .. W + LONG_RUN relative to the window
-  __shared__ int32_t pay[W + LONG_RUN];
-  __shared__ uint16_t start[W + LONG_RUN + 2];      // first position of every item, then of the run behind the last
-  __shared__ int16_t lead[W / 32 + 1];              // pieces' runs: [0] the one that comes in, [1 + j] starts in (32 j, 32 j + 31)
-  __shared__ int counts[ROUNDS + 1][4];
+  static_assert(W <= 512 && LONG_RUN == 16, "list entries and the search for long runs");
+  __shared__ int32_t key_[W + 2 * LONG_RUN];        // positions -LONG_RUN .. W + LONG_RUN - 1 relative to the window
+  __shared__ Lookup look[W + LONG_RUN];
+  __shared__ uint16_t order[W];                     // work items: runs of up to four lookups from the front (position, length), others from the end
+  __shared__ int16_t lead[W / LONG_RUN + 1];        // pieces' runs: [0] the one that comes in, [1 + j] starts in the j-th LONG_RUN positions
+  __shared__ int counts[ROUNDS][4];
   __shared__ int goes_out;
-  extern __shared__ __attribute__((aligned(16))) float4 piece_sum[];   // [W / 16][D / 4]: 2 j: starts at 32 j inside its run, 2 j + 1: at the run's head
+  extern __shared__ __attribute__((aligned(16))) float piece_sum[];   // [2 W / LONG_RUN][D]: 2 j: starts at LONG_RUN j inside its run, 2 j + 1: at the run's head
   int f, t, part;
   if (!tile_of_block(tb, a.F, PARTS, f, t, part)) return;
   const int win = (tb.t[f] + t) * PARTS + part;
@@ -707,110 +714,124 @@ __global__ __launch_bounds__(256) void seg_window_kernel(SegArgs a, FieldPtr fp,
     if (tid == 0) a.goes_out[win] = 0;
     return;
   }
-  for (int i = tid; i < W + 2 * LONG_RUN + 1; i += 256) key_[i] = a.key[base + min(max(P + i - LONG_RUN, 0), nnz - 1)];
-  for (int i = tid; i < W + LONG_RUN; i += 256) pay[i] = a.pay[base + min(P + i, nnz - 1)];
-  if (tid <= W / 32) lead[tid] = -1;
+  for (int i = tid; i < W + 2 * LONG_RUN; i += 256) key_[i] = a.key[base + min(max(P + i - LONG_RUN, 0), nnz - 1)];
+  const int32_t* off = MEAN ? a.offsets + (int64_t)f * (a.B + 1) : nullptr;
+  for (int i = tid; i < W + LONG_RUN; i += 256) {
+    const int smp = min(max(a.pay[base + min(P + i, nnz - 1)], 0), a.B - 1);
+    Lookup l;
+    l.offset = (uint64_t)smp * (uint64_t)(a.lddx * 4);
+    l.w = lookup_weight<MEAN>(a, off, smp);
+    l.unused = 0;
+    look[i] = l;
+  }
+  if (tid <= W / LONG_RUN) lead[tid] = -1;
   if (tid == 0) goes_out = 0;
   __syncthreads();
   const int32_t* key = key_ + LONG_RUN;   // key[q]: position P + q
-  auto is_head = [&](int q) { return P + q == 0 || key[q - 1] != key[q]; };
   auto same = [&](int q, int32_t k) { return P + q < nnz && key[q] == k; };   // (0 <= P + q)
-  // items: heads, and multiples of 32 inside long runs; position nnz counts as a head
-  bool flag[ROUNDS + 1];
+  // Items: heads, and multiples of LONG_RUN inside long runs.  A run is long if two of its keys are LONG_RUN apart;
+  // for a position q inside a run: if one of the pairs (q - LONG_RUN, q) ... (q, q + LONG_RUN) is equal.
+  uint32_t entry[ROUNDS];
+  bool few[ROUNDS], other[ROUNDS];
 #pragma unroll
-  for (int r = 0; r <= ROUNDS; ++r) {
+  for (int r = 0; r < ROUNDS; ++r) {
     const int q = r * 256 + tid;
-    bool st = false;
-    if (q <= W + LONG_RUN && P + q <= nnz) {
-      if (P + q == nnz) st = true;
-      else if (is_head(q)) st = true;
-      else if (q < W && (q & 31) == 0) {
-        int lo = max(q - LONG_RUN, -P), hi = q;   // first position of the run, at most LONG_RUN back
-        while (lo < hi) {
-          const int mid = (lo + hi) >> 1;
-          if (key[mid] < key[q]) lo = mid + 1;
-          else hi = mid;
-        }
-        st = same(lo + LONG_RUN, key[q]);
-      }
-    }
-    flag[r] = st;
-    const uint64_t m = __ballot(st);
-    if ((tid & 63) == 0) counts[r][tid >> 6] = __popcll(m);
+    const bool valid = P + q < nnz;
+    const int32_t k = key[q];
+    const bool head = valid && (P + q == 0 || key[q - 1] != k);
+    const bool ahead = same(q + LONG_RUN, k);
+    const uint64_t behind = __ballot(valid && P + q >= LONG_RUN && key[q - LONG_RUN] == k);
+    const bool long_inside = ahead || ((behind >> (tid & 48)) & 0xFFFFu) != 0;
+    few[r] = head && !same(q + 4, k);
+    other[r] = head ? !few[r] : valid && (q & (LONG_RUN - 1)) == 0 && long_inside;
+    entry[r] = few[r] ? q | (((int)same(q + 1, k) + (int)same(q + 2, k) + (int)same(q + 3, k)) << 9)
+                      : q | (head ? 512 : 0) | (!head || ahead ? 1024 : 0);
+    const uint64_t mf = __ballot(few[r]), mo = __ballot(other[r]);
+    if ((tid & 63) == 0) counts[r][tid >> 6] = __popcll(mf) | (__popcll(mo) << 16);
   }
   __syncthreads();
-  int items = 0, total;   // items of the window; with what follows it
+  int sum_counts = 0;
   {
     const uint64_t lt = lanemask_lt();
-    int before = 0;
 #pragma unroll
-    for (int r = 0; r <= ROUNDS; ++r) {
-      const uint64_t m = __ballot(flag[r]);
-      int mine = before;
+    for (int r = 0; r < ROUNDS; ++r) {
+      const uint64_t mf = __ballot(few[r]), mo = __ballot(other[r]);
+      int before = sum_counts;
 #pragma unroll
       for (int w = 0; w < 4; ++w) {
-        if (w < (tid >> 6)) mine += counts[r][w];
-        before += counts[r][w];
+        if (w < (tid >> 6)) before += counts[r][w];
+        sum_counts += counts[r][w];
       }
-      if (flag[r]) start[mine + __popcll(m & lt)] = (uint16_t)(r * 256 + tid);
-      if (r == ROUNDS - 1) items = before;
+      if (few[r]) order[(before & 0xFFFF) + __popcll(mf & lt)] = (uint16_t)entry[r];
+      if (other[r]) order[W - 1 - (before >> 16) - __popcll(mo & lt)] = (uint16_t)entry[r];
     }
-    total = before;
   }
-  // (the last window of a field: position nnz may lie inside it)
-  if (P + W > nnz) items = min(items, total - 1);
   __syncthreads();
+  const int n_few = sum_counts & 0xFFFF, n_other = sum_counts >> 16;
   const int lps = a.D >> 2;
   const int ngroups = 256 / lps;
   const int g = tid / lps, c = tid - g * lps;
-  const int64_t row0 = (int64_t)f * a.R;
-  auto finish = [&](int64_t row, const Row4& sum, const float (&p0)[4], const float4& s0, float srow0, int q) {
-    if (UPDATE) adagrad_row<TT, ROWWISE>(a, row, c, lps, sum, p0, s0, srow0);
-    else *reinterpret_cast<float4*>(a.G + run_index(a, f, (int)base + P + q) * a.D + c * 4) =
-        make_float4(sum.v[0], sum.v[1], sum.v[2], sum.v[3]);
+  const char* dx = reinterpret_cast<const char*>(a.dx + f * a.D + c * 4);
+  auto row_of = [&](int q) { return (int64_t)f * a.R + min(max(key[q], 0), (int)(a.R - 1)); };
+  auto finish = [&](int64_t row, const RowSum& sum, const TableRow<TT, ROWWISE>& tr, int q) {
+    if (UPDATE) tr.update(a, row, c, lps, sum);
+    else store_floats(a.G + run_index(a, f, (int)base + P + q) * a.D + c * 4, sum);
   };
-  for (int i = g; i < items; i += ngroups) {
-    const int q0 = start[i];
-    int e = i + 1 < total ? start[i + 1] : W;
-    const bool head = is_head(q0);
-    const bool piece = !head || same(q0 + LONG_RUN, key[q0]);
-    if (piece) e = min(e, W);
-    const int64_t row = row0 + min(max(key[q0], 0), (int)(a.R - 1));
-    float p0[4] = {0.f, 0.f, 0.f, 0.f};
-    float4 s0 = make_float4(0.f, 0.f, 0.f, 0.f);
-    float srow0 = 0.f;
-    if (UPDATE && !piece) load_row<TT, ROWWISE>(a, row, c, p0, s0, srow0);
-    Row4 sum = {{0.f, 0.f, 0.f, 0.f}};
-    accumulate_run<MEAN>(a, f, c, pay + q0, min(e - q0, LONG_RUN), sum);
+  // The long items first, so that the lane groups of a wavefront have items of about the same length; the next
+  // item's row and accumulators are requested before the current one's lookups are waited for.
+  auto entry_of = [&](int i) { return i < n_other ? (int)order[W - 1 - i] : (int)order[i - n_other]; };
+  TableRow<TT, ROWWISE> next;
+  int next_en = g < n_other + n_few ? entry_of(g) : 0;
+  auto request = [&](int i) {
+    if (UPDATE && !(i < n_other && (next_en & 1024))) next.load(a, row_of(next_en & 511), c);
+  };
+  if (g < n_other + n_few) request(g);
+  for (int i = g; i < n_other + n_few; i += ngroups) {
+    const int en = next_en, q0 = en & 511;
+    const TableRow<TT, ROWWISE> tr = next;
+    if (i + ngroups < n_other + n_few) {
+      next_en = entry_of(i + ngroups);
+      request(i + ngroups);
+    }
+    int n = (en >> 9) + 1;
+    bool head = true, piece = false;
+    if (i < n_other) {
+      head = en & 512;
+      piece = en & 1024;
+      n = LONG_RUN - (q0 & (LONG_RUN - 1));   // of a long run that starts here: up to the next multiple
+      if (!head || !piece) {                  // the run's keys from here on, LONG_RUN at most (sorted: bisection)
+        const int32_t k = key[q0];
+        n = 1;
+#pragma unroll
+        for (int st = 8; st > 0; st >>= 1)
+          if (same(q0 + n + st - 1, k)) n += st;
+      }
+    }
+    RowSum sum = {};
+    accumulate_run(dx, look + q0, n, sum);
     if (piece) {
-      piece_sum[(2 * (q0 >> 5) + (head ? 1 : 0)) * lps + c] = make_float4(sum.v[0], sum.v[1], sum.v[2], sum.v[3]);
-      if (c == 0 && (head || q0 == 0)) lead[head ? 1 + (q0 >> 5) : 0] = (int16_t)q0;
+      store_floats(piece_sum + (2 * (q0 / LONG_RUN) + (head ? 1 : 0)) * a.D + c * 4, sum);
+      if (c == 0 && (head || q0 == 0)) lead[head ? 1 + q0 / LONG_RUN : 0] = (int16_t)q0;
     } else {
-      finish(row, sum, p0, s0, srow0, q0);
+      finish(row_of(q0), sum, tr, q0);
     }
   }
   __syncthreads();
-  for (int l = g; l < W / 32 + 1; l += ngroups) {
+  for (int l = g; l < W / LONG_RUN + 1; l += ngroups) {
     const int q0 = lead[l];
     if (q0 < 0) continue;
     const int32_t k = key[q0];
     const bool out = same(W, k);
-    const int64_t row = row0 + min(max(k, 0), (int)(a.R - 1));
-    float p0[4] = {0.f, 0.f, 0.f, 0.f};
-    float4 s0 = make_float4(0.f, 0.f, 0.f, 0.f);
-    float srow0 = 0.f;
-    if (UPDATE && l > 0 && !out) load_row<TT, ROWWISE>(a, row, c, p0, s0, srow0);
-    const float4 x0 = piece_sum[(2 * (q0 >> 5) + (l > 0 ? 1 : 0)) * lps + c];
-    Row4 sum = {{x0.x, x0.y, x0.z, x0.w}};
-    for (int j = (q0 >> 5) + 1; j < W / 32 && same(j * 32, k); ++j) {
-      const float4 x = piece_sum[2 * j * lps + c];
-      sum.v[0] += x.x; sum.v[1] += x.y; sum.v[2] += x.z; sum.v[3] += x.w;
-    }
+    const int64_t row = row_of(q0);
+    TableRow<TT, ROWWISE> tr;
+    if (UPDATE && l > 0 && !out) tr.load(a, row, c);
+    RowSum sum = {};
+    add_floats(sum, piece_sum + (2 * (q0 / LONG_RUN) + (l > 0 ? 1 : 0)) * a.D + c * 4);
+    for (int j = q0 / LONG_RUN + 1; j < W / LONG_RUN && same(j * LONG_RUN, k); ++j) add_floats(sum, piece_sum + 2 * j * a.D + c * 4);
     if (l > 0 && !out) {
-      finish(row, sum, p0, s0, srow0, q0);
+      finish(row, sum, tr, q0);
     } else {
-      *reinterpret_cast<float4*>(a.partial + ((int64_t)win * 2 + (l > 0 ? 1 : 0)) * a.D + c * 4) =
-          make_float4(sum.v[0], sum.v[1], sum.v[2], sum.v[3]);
+      store_floats(a.partial + ((int64_t)win * 2 + (l > 0 ? 1 : 0)) * a.D + c * 4, sum);
       if (l > 0) goes_out = 1;
     }
   }
@@ -846,30 +867,20 @@ __global__ __launch_bounds__(256) void seg_finish_kernel(SegArgs a, FieldPtr fp,
   const int lps = a.D >> 2, ngroups = 64 / lps;
   const int g = lane / lps, c = lane - g * lps;
   const int64_t row = (int64_t)f * a.R + min(max(k, 0), (int)(a.R - 1));
-  float p0[4] = {0.f, 0.f, 0.f, 0.f};
-  float4 s0 = make_float4(0.f, 0.f, 0.f, 0.f);
-  float srow0 = 0.f;
-  if (UPDATE) load_row<TT, ROWWISE>(a, row, c, p0, s0, srow0);
-  auto slot = [&](int i, int which) { return *reinterpret_cast<const float4*>(a.partial + ((int64_t)(win + i) * 2 + which) * a.D + c * 4); };
-  Row4 sum = {{0.f, 0.f, 0.f, 0.f}};
-  auto add = [&](const float4& v) { sum.v[0] += v.x; sum.v[1] += v.y; sum.v[2] += v.z; sum.v[3] += v.w; };
-  if (g == 0) add(slot(0, 1));
-  int i = 1 + g;
-  for (; i + 3 * ngroups <= n; i += 4 * ngroups) {   // four loads in flight
-    float4 v[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = slot(i + j * ngroups, 0);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) add(v[j]);
-  }
-  for (; i <= n; i += ngroups) add(slot(i, 0));
+  TableRow<TT, ROWWISE> tr;
+  if (UPDATE) tr.load(a, row, c);
+  RowSum sum = {};
+  const float* part = a.partial + (int64_t)win * 2 * a.D + c * 4;
+  if (g == 0) add_floats(sum, part + a.D);
+#pragma unroll 4
+  for (int i = 1 + g; i <= n; i += ngroups) add_floats(sum, part + (int64_t)i * 2 * a.D);
   for (int o = lps; o < 64; o <<= 1) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) sum.v[e] += __shfl_xor(sum.v[e], o, 64);
   }
   if (g != 0) return;
   if (UPDATE) {
-    adagrad_row<TT, ROWWISE>(a, row, c, lps, sum, p0, s0, srow0);
+    tr.update(a, row, c, lps, sum);
   } else {   // the run's head: the first position of the key in the window
     int lo = next - W, hi = next - 1;
     while (lo < hi) {
@@ -877,7 +888,7 @@ __global__ __launch_bounds__(256) void seg_finish_kernel(SegArgs a, FieldPtr fp,
       if (a.key[base + mid] < k) lo = mid + 1;
       else hi = mid;
     }
-    *reinterpret_cast<float4*>(a.G + run_index(a, f, (int)base + lo) * a.D + c * 4) = make_float4(sum.v[0], sum.v[1], sum.v[2], sum.v[3]);
+    store_floats(a.G + run_index(a, f, (int)base + lo) * a.D + c * 4, sum);
   }
 }
 
@@ -887,7 +898,7 @@ void launch_reduce_window(const SegArgs& a, const FieldPtr& fp, const TileBase& 
   {
     ProfScope ps(prof, UPDATE ? KID_SPARSE_ADAGRAD : KID_SEG_REDUCE, s);
     hipLaunchKernelGGL((seg_window_kernel<TT, ROWWISE, UPDATE, MEAN, W>), dim3(tile_grid(a.total_tiles) * parts), dim3(256),
-                       W / 16 * a.D * 4, s, a, fp, tb);
+                       2 * W / LONG_RUN * a.D * 4, s, a, fp, tb);
   }
   {
     ProfScope ps(prof, KID_SEG_REDUCE_LONG, s);

@@ -635,7 +635,10 @@ static void fill_seg_args(antdt_ctx* c, SegArgs& a) {
   a.G = c->G; a.dx = c->dx; a.lddx = c->FD;
   a.offsets = c->offsets; a.mean_pool = m.pooling == ANTDT_POOL_MEAN;
   a.F = m.num_fields; a.D = m.dim; a.B = (int32_t)c->B; a.total_tiles = c->atotal_tiles;
-  a.window = c->afp.p[m.num_fields] >= (4 << 20) && m.dim <= 128 ? 512 : 256;
+  // 512 lookups per block need half the blocks but, with LDS growing with D, leave fewer of them on a compute unit:
+  // 4.3 M lookups with D = 32: 160 us against 172, with D = 64: 3.8 M 173 against 143, 42 M 1486 against 1239; 1.1 M
+  // with D = 32: 50 against 45.
+  a.window = c->afp.p[m.num_fields] >= (4 << 20) && m.dim <= 32 ? 512 : 256;
   a.tables = c->tables; a.state = c->table_state; a.R = m.rows_per_field; a.lr = m.lr; a.eps = m.eps;
   a.table_bf16 = m.table_dtype == ANTDT_BF16; a.rowwise = m.adagrad_state == ANTDT_STATE_ROWWISE;
 }

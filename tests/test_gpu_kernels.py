@@ -1,6 +1,8 @@
 """GPU parity of kernel variants at the sizes where their tiling can go wrong: one sample more or
 fewer than a tile, remainders in every dimension, the smallest and largest problem a variant is
 chosen for.  Same oracle and tolerances as test_gpu_parity.py."""
+import dataclasses
+
 import numpy as np
 import pytest
 
@@ -40,3 +42,36 @@ F32_SHAPES = [((1,), (7,)), ((15, 17), (33, 5)), ((513, 0, 199), (64, 19)), ((26
 def test_f32_product_tiles(sizes, hidden):
     cfg = _config(f"f32-tiles-{sum(sizes)}", 500 + sum(sizes), layer_sizes=hidden, shard_sizes=sizes, gemm_dtype="f32")
     check_iteration(cfg, sizes, tol=TOL32, batched=True, nonzero_state=True)
+
+
+# the reduction works on windows of 256 (or 512) sorted lookups: runs of 1 .. 5 lookups, of 15 .. 17 around the length
+# from which they are cut into pieces, runs that end at, start at and cross window boundaries or span several
+# windows, and a field that ends in the middle of one; the block-per-field sort at 2048 lookups more or fewer
+RUN_LENGTHS = [1, 1, 2, 3, 4, 5, 15, 16, 17, 31, 33, 100, 28, 1, 255, 256, 257, 1, 1, 700, 2, 16, 16, 500, 17, 1, 1, 1200, 3]
+
+
+@pytest.mark.parametrize("dim,table,state,more", [(4, "f32", "elementwise", 0), (32, "f32", "elementwise", 3), (256, "f32", "rowwise", 1),
+                                                  (8, "bf16", "rowwise", 255), (64, "bf16", "elementwise", 256)])
+def test_runs_and_windows(dim, table, state, more, monkeypatch):
+    lengths = RUN_LENGTHS + [1] * more
+    bag = 5
+    total = sum(lengths)
+    B = -(-total // bag)
+    cfg = _config(f"windows-{dim}", 600 + dim, num_fields=2, rows_per_field=1200, dim=dim, table_dtype=table, adagrad_state=state,
+                  layer_sizes=(8,), gemm_dtype="f32", shard_sizes=(B // 3, B - B // 3), max_bag=bag)
+    real = wl.make_batch
+
+    def planted(c, index=0):
+        b = real(c, index)
+        rng = np.random.default_rng(7 + dim)
+        ids, offsets, ptr = [], np.zeros((2, B + 1), np.int32), [0]
+        for f in range(2):
+            rows = rng.permutation(c.rows_per_field)[:len(lengths)]
+            field = np.repeat(rows, lengths)
+            ids.append(rng.permutation(field).astype(np.int32))
+            offsets[f] = np.minimum(np.arange(B + 1) * bag, total)
+            ptr.append(ptr[-1] + total)
+        return dataclasses.replace(b, ids=np.concatenate(ids), offsets=offsets, field_ptr=np.array(ptr, np.int64))
+
+    monkeypatch.setattr(wl, "make_batch", planted)
+    check_iteration(cfg, cfg.shard_sizes, tol=TOL32, batched=True, nonzero_state=True)
