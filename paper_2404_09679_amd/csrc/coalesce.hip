@@ -290,8 +290,8 @@ __global__ __launch_bounds__(SORT_THREADS) void sort_scatter_kernel(
 }
 
 // All passes of a field's sort in one block, for fields of up to SMALL_THREADS * IT lookups: keys and sample
-// indices stay in registers between the passes (thread's item i of wavefront w: position 64 IT w + 64 i + lane)
-// and trade places through LDS.  Same ranking, hence the same stable order, as the passes over many blocks,
+// indices stay in registers between the passes (item i of wavefront w: position 64 (w per + i) + lane, all wavefronts
+// holding the same number `per` of items a lane) and trade places through LDS.  Same ranking, hence the same stable order, as the passes over many blocks,
 // in one launch instead of three per pass; a block's time is a few microseconds per pass and 8 items of a
 // thread.  Blocks behind the fields write the samples' aggregation weights.
 // (26 fields of 1000 lookups, two passes: 29 us of kernels and their gaps -> one launch of 11 us.)
@@ -313,13 +313,17 @@ __global__ __launch_bounds__(SMALL_THREADS) void sort_small_kernel(const int32_t
   const int nnz = (int)(fp.p[f + 1] - base);
   if (nnz == 0) return;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int first = w * (64 * IT) + lane;
+  const int per = (nnz + SMALL_THREADS - 1) / SMALL_THREADS;   // <= IT
+  const int first = w * (64 * per) + lane;
+  auto mine = [&](int i) { return i < per && first + i * 64 < nnz; };
   int32_t key[IT], pay[IT];
 #pragma unroll
   for (int i = 0; i < IT; ++i) {
     const int pos = min(first + i * 64, nnz - 1);
-    key[i] = keys_in[base + pos];
-    pay[i] = pay_in[base + pos];
+    if (i < per) {
+      key[i] = keys_in[base + pos];
+      pay[i] = pay_in[base + pos];
+    }
   }
   const int nb = 1 << rb;   // (at most one digit per thread)
   const uint64_t lt = lanemask_lt();
@@ -331,7 +335,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void sort_small_kernel(const int32_t
 #pragma unroll
     for (int i = 0; i < IT; ++i) {
       rank[i] = 0;
-      if (w * (64 * IT) + i * 64 < nnz) {   // (uniform)
+      if (i < per && w * (64 * per) + i * 64 < nnz) {   // (uniform)
         const bool valid = first + i * 64 < nnz;
         const uint32_t d = ((uint32_t)key[i] >> shift) & (nb - 1);
         const uint64_t m = same_digit(d, rb, valid);
@@ -370,17 +374,18 @@ __global__ __launch_bounds__(SMALL_THREADS) void sort_small_kernel(const int32_t
     uint32_t place[IT];
 #pragma unroll
     for (int i = 0; i < IT; ++i) {
+      if (i >= per) break;
       const uint32_t d = ((uint32_t)key[i] >> shift) & (nb - 1);
       place[i] = dpre[d] + cnt[w][d] + rank[i];
     }
     auto trade = [&](int32_t (&x)[IT]) {
 #pragma unroll
       for (int i = 0; i < IT; ++i)
-        if (first + i * 64 < nnz) stage[place[i]] = x[i];
+        if (mine(i)) stage[place[i]] = x[i];
       __syncthreads();
 #pragma unroll
       for (int i = 0; i < IT; ++i)
-        if (first + i * 64 < nnz) x[i] = stage[first + i * 64];
+        if (mine(i)) x[i] = stage[first + i * 64];
       __syncthreads();
     };
     trade(key);
@@ -388,7 +393,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void sort_small_kernel(const int32_t
   }
 #pragma unroll
   for (int i = 0; i < IT; ++i)
-    if (first + i * 64 < nnz) {
+    if (mine(i)) {
       keys_out[base + first + i * 64] = key[i];
       pay_out[base + first + i * 64] = pay[i];
     }
@@ -945,18 +950,17 @@ static hipError_t launch_sort_pass(const SortPlan& pl, const SortBuffers& sb, in
 }
 
 hipError_t launch_sort(const SortPlan& pl, const SortBuffers& sb, const FieldPtr& fp, const TileBase& tb, const ShardTab& tab,
-                       bool beside, Profiler* prof, hipStream_t s, int* sorted_buf) {
+                       Profiler* prof, hipStream_t s, int* sorted_buf) {
   *sorted_buf = 0;
   if (pl.total_tiles == 0) return hipSuccess;
-  // One block per field as long as a field fits one: two passes over 1000 / 9000 / 16000 lookups of a field take 11 /
-  // 34 / 34 us (the number of items a thread holds is a power of two), the six launches about 30; with 16 items
-  // only where the sort runs beside the MLP and what counts is the number of launches.
+  // One block per field as long as a field fits one: two passes over 1000 / 9000 lookups of a field take 10 / 26 us, the
+  // six launches 29 / 30 and the host four times as long.
   int64_t most = 0;
   for (int f = 0; f < pl.F; ++f) most = std::max(most, fp.p[f + 1] - fp.p[f]);
   if (most <= SMALL_THREADS * 2) return launch_sort_small_items<2>(pl, sb, fp, tab, prof, s);
   if (most <= SMALL_THREADS * 4) return launch_sort_small_items<4>(pl, sb, fp, tab, prof, s);
   if (most <= SMALL_THREADS * 8) return launch_sort_small_items<8>(pl, sb, fp, tab, prof, s);
-  if (beside && most <= SMALL_THREADS * 16) return launch_sort_small_items<16>(pl, sb, fp, tab, prof, s);
+  if (most <= SMALL_THREADS * 16) return launch_sort_small_items<16>(pl, sb, fp, tab, prof, s);
   for (int p = 0; p < pl.passes; ++p) {
     const hipError_t e = launch_sort_pass(pl, sb, p, fp, tb, tab, prof, s);
     if (e != hipSuccess) return e;

@@ -136,6 +136,10 @@ struct GemmArgs {
   int32_t b_kc, epi;
   int32_t bf16_in;     // operands (and mask) are bf16, else fp32
   int32_t bf16_out;    // C is bf16, else fp32
+  // Further blocks of the launch add up the losses that the loss kernel left per tile of samples, one shard each (nobody
+  // waits for them, and counting the loss kernel's blocks to have its last one do it kept the chain waiting 3 us).
+  int32_t loss_blocks;
+  const struct LossJob* loss;
 };
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s);
 
@@ -193,8 +197,7 @@ struct HeadArgs {
   // the sums over the samples are formed along the way, per tile of samples of one shard
   float* part;          // [tiles, ldpart] sum of dz * h per column; column `width`: sum of dz, `width` + 1: of the losses
   int64_t ldpart;
-  int32_t* done;        // [K] blocks of each shard that have finished (0 between launches)
-  float* loss_k;        // workspace [K]
+  struct LossJob* job;  // written by the first block, for the launch that adds up the losses
   float* loss_out;      // caller's buffer or NULL; element (k - k_begin)
 };
 // Tiles of the loss kernel: HEAD_TILE consecutive samples of one shard.  tile_base[k] = first tile of shard k.
@@ -210,7 +213,26 @@ inline HeadTiles head_tiles(const ShardTab& tab) {
   return t;
 }
 hipError_t launch_head_tiles(const HeadArgs& a, const ShardTab& tab, hipStream_t s);
-hipError_t launch_zero_words(int32_t* p, int n, hipStream_t s);
+hipError_t launch_losses(const LossJob* job, int shards, hipStream_t s);   // stand-alone, for models without a hidden layer
+
+// The mean loss of a shard: its tiles' sums in a fixed order (lanes take every 64th tile).
+struct LossJob {
+  const float* part;    // + width + 1: the tile's sum of losses
+  float* loss_out;      // element i: shard first + i
+  int64_t ldpart;
+  int32_t width, first;
+  int32_t base[ANTDT_MAX_SHARDS + 1];   // first tile of every shard
+  int32_t len[ANTDT_MAX_SHARDS];
+};
+__device__ __forceinline__ void add_up_losses(const LossJob* job, int i) {   // (the first wavefront of a block)
+  if (threadIdx.x >= 64) return;
+  const int k = job->first + i, t1 = job->base[k + 1];
+  float l = 0.0f;
+  for (int t = job->base[k] + (int)threadIdx.x; t < t1; t += 64) l += job->part[(int64_t)t * job->ldpart + job->width + 1];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) l += __shfl_xor(l, o, 64);
+  if (threadIdx.x == 0 && job->loss_out) job->loss_out[i] = job->len[k] > 0 ? l / (float)job->len[k] : 0.0f;
+}
 
 // ------------------------------------------------------------- coalesce.hip
 // Keys per sort tile (one block of 512 threads, ANTDT_SORT_TILE / 512 keys per thread).
@@ -230,10 +252,9 @@ struct SortBuffers {
   uint32_t* digit_base;            // [F << radix_bits]
   float* sample_w;                 // [B] aggregation weight of every sample, written beside the first pass
 };
-// Sorts every field's lookups by row id (stable); the result is in key / pay [*sorted_buf].  `beside`: other work runs
-// at the same time.
+// Sorts every field's lookups by row id (stable); the result is in key / pay [*sorted_buf].
 hipError_t launch_sort(const SortPlan& pl, const SortBuffers& sb, const FieldPtr& fp, const TileBase& tb, const ShardTab& tab,
-                       bool beside, Profiler* prof, hipStream_t s, int* sorted_buf);
+                       Profiler* prof, hipStream_t s, int* sorted_buf);
 
 struct SegArgs {
   const int32_t* key;              // sorted row ids, field-major at fp.p[f]

@@ -107,14 +107,14 @@ struct antdt_ctx {
   char* x = nullptr;
   char* h[ANTDT_MAX_LAYERS] = {};
   char* dh[ANTDT_MAX_LAYERS] = {};
-  float *loss_k = nullptr, *dx = nullptr;
+  float* dx = nullptr;
   float *shard_grads = nullptr, *g_dense = nullptr, *sample_w = nullptr, *G = nullptr;
   bf16_t* wb[ANTDT_MAX_LAYERS] = {};     // bf16 W_l as [in (padded), out]: operand of the forward product and the data gradient
   bf16_t* wb0_alt = nullptr;             // second buffer for W_0: the fused dense update writes the new copy there
                                          // while the input-gradient product may still read the old one
   float* head_part = nullptr;            // loss kernel's sums per tile of samples [tiles, ldpart]
   int64_t ldpart = 0;
-  int32_t* head_done = nullptr;          // per shard: its finished blocks (0 between launches)
+  LossJob* loss_job = nullptr;           // what it leaves to the launch that adds up the losses
   int32_t* lookup_sample = nullptr;
   int32_t *key[2] = {}, *pay[2] = {}, *tile_heads = nullptr, *ubase = nullptr, *uniq = nullptr;
   int32_t *segoff = nullptr, *pack_pay = nullptr, *segabs = nullptr, *goes_out = nullptr;
@@ -148,6 +148,7 @@ struct antdt_ctx {
   // the worker step only leaves their operands behind and an event (ev_dh[0]) that says they are
   // complete; per-shard gradients are computed when a view asks for them.
   bool eager_wgrad = false;              // option: the worker step computes the per-shard weight gradients itself
+  bool batched = false;                  // the last worker step covered all shards
   bool wgrad_deferred = false;           // this worker step left the weight gradients to apply_update / the views
   bool shard_grads_done = false;         // the per-shard dense gradients of this worker step are (being) written
   int sorted_buf = 0;
@@ -175,12 +176,14 @@ struct antdt_ctx {
 //   106 / 115 us per step).
 //   Dense update beside the sparse one: where there are many lookups or many weights (26 fields, 1024-512-256:
 //   26 000 / 70 000 / 140 000 / 560 000 lookups, beside or after: 98 / 92, 107 / 101, 106 / 108, 137 / 145 us per
-//   step; 3840-1024-512 at 50 000: 102 / 122).  fp32 models never (171 / 176 us at 430 000 lookups).
+//   step; 3840-1024-512 at 50 000: 102 / 122).  After one worker step per shard the launch stream is busy for longer:
+//   six workers with 164 000 / 819 000 lookups 369 / 326 and 396 / 405 us.  fp32 models never (176 / 171 us at
+//   430 000 lookups).
 static inline hipStream_t side_stream(const antdt_ctx* c) {
   return (c->static_bound || c->no_streams || c->fp.p[c->m.num_fields] < 16384) ? nullptr : c->side;
 }
 static inline hipStream_t wgrad_stream(const antdt_ctx* c) {
-  const bool enough = c->act_bf16 && (c->fp.p[c->m.num_fields] >= 100000 || c->P >= 2000000);
+  const bool enough = c->act_bf16 && (c->fp.p[c->m.num_fields] >= (c->batched ? 100000 : 600000) || c->P >= 2000000);
   return (c->static_bound || c->no_streams || !enough) ? nullptr : c->wside;
 }
 
@@ -223,7 +226,6 @@ static size_t carve(antdt_ctx* c, char* base) {
     c->dh[l] = take((size_t)Bm * c->width[l] * c->act_size);
   }
   c->sample_w = (float*)take(Bm * 4);
-  c->loss_k = (float*)take(K * 4);
   c->dx = (float*)take((size_t)Bm * c->FD * 4);
   c->shard_grads = (float*)take((size_t)K * c->Pstride * 4);
   c->g_dense = (float*)take((size_t)c->P * 4);
@@ -235,7 +237,7 @@ static size_t carve(antdt_ctx* c, char* base) {
     }
   }
   c->head_part = (float*)take((size_t)(Bm / HEAD_TILE + K) * c->ldpart * 4);
-  c->head_done = (int32_t*)take((size_t)K * 4);
+  c->loss_job = (LossJob*)take(sizeof(LossJob));
   c->lookup_sample = (int32_t*)take((size_t)N * 4);
   for (int i = 0; i < 2; ++i) {
     c->key[i] = (int32_t*)take((size_t)N * 4);
@@ -397,7 +399,6 @@ int antdt_workspace_bytes(const antdt_ctx* ctx, size_t* bytes) {
 
 // What a fresh workspace has to hold before the first iteration.
 static int init_workspace(antdt_ctx* c, hipStream_t s) {
-  HIP_TRY(c, launch_zero_words(c->head_done, c->m.max_shards, s));
   if (!c->act_bf16) return ANTDT_OK;
   for (int l = 0; l + 1 < c->L; ++l) {
     CastArgs a;
@@ -669,7 +670,7 @@ static int build_coalescing(antdt_ctx* c, const int32_t* ids, const int32_t* pay
   sb.digit_base = c->digit_base;
   sb.sample_w = c->sample_w;
   sb.pay0 = pay0;
-  HIP_TRY(c, launch_sort(pl, sb, c->afp, c->atb, c->tab, s == c->side, pr, s, &c->sorted_buf));
+  HIP_TRY(c, launch_sort(pl, sb, c->afp, c->atb, c->tab, pr, s, &c->sorted_buf));
   return ANTDT_OK;
 }
 
@@ -756,7 +757,8 @@ static int worker_range(antdt_ctx* c, int k0, int k1, float* loss_out, hipStream
     HIP_TRY(c, launch_pool(a, c->fp, s));
   }
   c->presorted = false;
-  if (k0 == 0 && k1 == tab.K && side_stream(c)) {
+  c->batched = k0 == 0 && k1 == tab.K;
+  if (c->batched && side_stream(c)) {
     // All shards in one pass: the ids and the sample index of every lookup are known now, so
     // the sort and the run detection of the coming aggregate can run beside the MLP.
     for (int k = 0; k < tab.K; ++k) c->included[k] = true;
@@ -809,10 +811,10 @@ static int worker_range(antdt_ctx* c, int k0, int k1, float* loss_out, hipStream
       a.dh = c->dx; a.lddh = c->FD; a.dh_cols = c->FD; a.relu = 0; a.bf16_dh = 0;
     }
     a.k_begin = k0; a.k_end = k1;
-    a.part = c->head_part; a.ldpart = c->ldpart; a.done = c->head_done;
-    a.loss_k = c->loss_k; a.loss_out = loss_out;
+    a.part = c->head_part; a.ldpart = c->ldpart; a.job = c->loss_job; a.loss_out = loss_out;
     ProfScope ps(pr, KID_HEAD, s);
     HIP_TRY(c, launch_head_tiles(a, tab, s));
+    if (L == 1 && loss_out && ns > 0) HIP_TRY(c, launch_losses(c->loss_job, k1 - k0, s));   // (else beside the input gradient)
   }
   // Backward.  The data-gradient chain dH_{l+1} -> dH_l first; nothing needs the weight gradients before the dense
   // update.  With bf16 products they are not computed here at all, unless the caller asked for them or the
@@ -843,6 +845,10 @@ static int worker_range(antdt_ctx* c, int k0, int k1, float* loss_out, hipStream
     } else {
       g.C = c->dx + s0 * c->FD; g.ldc = c->FD; g.N = c->FD;
       g.epi = EPI_PLAIN; g.bf16_out = 0;
+      if (loss_out) {
+        g.loss = c->loss_job;
+        g.loss_blocks = k1 - k0;
+      }
     }
     HIP_TRY(c, launch_gemm(g, s));
     if (l == 1 && deferred) HIP_TRY(c, hipEventRecord(c->ev_dh[0], s));

@@ -37,12 +37,12 @@ template <> __device__ __forceinline__ void store_row<bf16_t, 8>(bf16_t* dst, co
   *reinterpret_cast<uint4*>(dst) = make_uint4(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]), f2bf2(v[4], v[5]), f2bf2(v[6], v[7]));
 }
 
-// Dense-feature columns of 64 samples: copied behind the pooled embeddings, the padding columns of
+// Dense-feature columns of up to 64 samples (below `end`): copied behind the pooled embeddings, the padding columns of
 // the row are zeroed.
 template <typename OT>
-__device__ __forceinline__ void dense_columns(const PoolArgs& a, int sl0) {
+__device__ __forceinline__ void dense_columns(const PoolArgs& a, int sl0, int end) {
   const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-  if (sl0 + tx >= a.ns) return;
+  if (sl0 + tx >= end) return;
   const int64_t s = a.s0 + sl0 + tx;
   const int FD = a.F * a.D;
   OT* xrow = reinterpret_cast<OT*>(a.x) + s * a.ldx + FD;
@@ -52,7 +52,7 @@ __device__ __forceinline__ void dense_columns(const PoolArgs& a, int sl0) {
   }
 }
 
-// Gather and sum-pool.  A block owns 64 consecutive samples of one field; a group of
+// Gather and sum-pool.  A block owns SPB consecutive samples of one field; a group of
 // LPR = D*sizeof(T)/16 lanes owns one bag, so a wavefront works on 64/LPR bags at once.
 // The group fetches LPR ids with one coalesced load, hands the rows' places round with lane
 // exchanges and issues the LPR row loads (16 bytes per lane, one whole row per group)
@@ -62,17 +62,17 @@ __device__ __forceinline__ void dense_columns(const PoolArgs& a, int sl0) {
 // bounds and addresses are therefore worked out once per lookup, by the lane that loads its id), else by
 // round trips.  Like the sort's tiles, the blocks of a field go to one XCD: its rows are fetched into one L2.
 // WIDE: a table of 2^32 or more 16-byte pieces.
-template <typename TT, typename OT, int LPR, bool WIDE>
+template <typename TT, typename OT, int LPR, int SPB, bool WIDE>
 __global__ __launch_bounds__(256) void pool_tile_kernel(PoolArgs a, FieldPtr fp) {
   constexpr int EV = Vec16<TT>::N;
   constexpr int G = 256 / LPR;       // bags per round
-  constexpr int ROUNDS = 64 / G;
-  const int tiles = (a.ns + 63) >> 6, total = tiles * (a.F + 1), share = (total + 7) >> 3;
+  constexpr int ROUNDS = (SPB + G - 1) / G;
+  const int tiles = (a.ns + SPB - 1) / SPB, total = tiles * (a.F + 1), share = (total + 7) >> 3;
   const int idx = (int)(blockIdx.x & 7) * share + (int)(blockIdx.x >> 3);
   if ((int)(blockIdx.x >> 3) >= share || idx >= total) return;
-  const int f = idx / tiles, sl0 = (idx - f * tiles) * 64;
+  const int f = idx / tiles, sl0 = (idx - f * tiles) * SPB, sl1 = min(sl0 + SPB, a.ns);
   if (f == a.F) {
-    dense_columns<OT>(a, sl0);
+    dense_columns<OT>(a, sl0, sl1);
     return;
   }
   const int g = threadIdx.x / LPR, c = threadIdx.x % LPR;
@@ -87,7 +87,7 @@ __global__ __launch_bounds__(256) void pool_tile_kernel(PoolArgs a, FieldPtr fp)
   for (int r = 0; r < ROUNDS; ++r) {
     const int ls = r * G + g;
     begin[r] = end[r] = 0;
-    if (sl0 + ls < a.ns) {
+    if (sl0 + ls < sl1) {
       const int32_t* off = a.offsets + (int64_t)f * (a.B + 1) + a.s0 + sl0 + ls;
       begin[r] = off[0];
       end[r] = off[1];
@@ -125,7 +125,7 @@ __global__ __launch_bounds__(256) void pool_tile_kernel(PoolArgs a, FieldPtr fp)
 #pragma unroll
       for (int e = 0; e < EV; ++e) acc[e] /= len;
     }
-    if (sl0 + ls < a.ns) store_row<OT, EV>(reinterpret_cast<OT*>(a.x) + s * a.ldx + f * a.D + c * EV, acc);
+    if (sl0 + ls < sl1) store_row<OT, EV>(reinterpret_cast<OT*>(a.x) + s * a.ldx + f * a.D + c * EV, acc);
   }
 }
 
@@ -175,22 +175,31 @@ __global__ __launch_bounds__(256) void pool_kernel(PoolArgs a, FieldPtr fp) {
 
 template <typename OT>
 __global__ __launch_bounds__(256) void pool_dense_kernel(PoolArgs a) {
-  dense_columns<OT>(a, blockIdx.x * 64);
+  dense_columns<OT>(a, blockIdx.x * 64, a.ns);
 }
 
-template <typename TT, typename OT, int LPR>
+template <typename TT, typename OT, int LPR, int SPB>
 static void launch_pool_tiles(const PoolArgs& a, const FieldPtr& fp, hipStream_t s) {
-  const dim3 grid(8 * (((a.ns + 63) / 64 * (a.F + 1) + 7) / 8)), block(256);
-  if ((uint64_t)a.R * LPR >> 32) hipLaunchKernelGGL((pool_tile_kernel<TT, OT, LPR, true>), grid, block, 0, s, a, fp);
-  else hipLaunchKernelGGL((pool_tile_kernel<TT, OT, LPR, false>), grid, block, 0, s, a, fp);
+  const dim3 grid(8 * (((a.ns + SPB - 1) / SPB * (a.F + 1) + 7) / 8)), block(256);
+  if ((uint64_t)a.R * LPR >> 32) hipLaunchKernelGGL((pool_tile_kernel<TT, OT, LPR, SPB, true>), grid, block, 0, s, a, fp);
+  else hipLaunchKernelGGL((pool_tile_kernel<TT, OT, LPR, SPB, false>), grid, block, 0, s, a, fp);
+}
+
+// 64 samples per block, or as many as the block takes at once (at most 32) where that leaves most of the places on the
+// compute units empty and the round trips of one bag after the other are the kernel's time: 26 fields x 64 samples
+// 9.4 us -> 6.0, x 1531 samples (624 blocks of 64) 12.5 -> 11.4, x 4096 samples 17.2 -> 18.2.
+template <typename TT, typename OT, int LPR>
+static void launch_pool_row(const PoolArgs& a, const FieldPtr& fp, hipStream_t s) {
+  if ((int64_t)((a.ns + 63) / 64) * a.F < 1024) launch_pool_tiles<TT, OT, LPR, (LPR > 8 ? 256 / LPR : 32)>(a, fp, s);
+  else launch_pool_tiles<TT, OT, LPR, 64>(a, fp, s);
 }
 
 template <typename TT, typename OT>
 static void launch_pool_typed(const PoolArgs& a, const FieldPtr& fp, hipStream_t s) {
   const int lpr = a.D / Vec16<TT>::N;
-  if (lpr == 4) launch_pool_tiles<TT, OT, 4>(a, fp, s);
-  else if (lpr == 8) launch_pool_tiles<TT, OT, 8>(a, fp, s);
-  else if (lpr == 16) launch_pool_tiles<TT, OT, 16>(a, fp, s);
+  if (lpr == 4) launch_pool_row<TT, OT, 4>(a, fp, s);
+  else if (lpr == 8) launch_pool_row<TT, OT, 8>(a, fp, s);
+  else if (lpr == 16) launch_pool_row<TT, OT, 16>(a, fp, s);
   else {
     const int64_t items = (int64_t)a.ns * a.F;
     hipLaunchKernelGGL((pool_kernel<TT, OT>), dim3((unsigned)((items + 3) / 4)), dim3(256), 0, s, a, fp);

@@ -43,7 +43,11 @@ __global__ __launch_bounds__(64 * WR * WC * WK) void gemm_bf16_kernel(GemmArgs p
   typedef BlockProduct<TM, TN, WR, WC, WK, BK, STAGES, false, B_STRIDED> P;
   extern __shared__ __attribute__((aligned(16))) char lds[];
   int pid = blockIdx.x;
-  const int nblk = gridDim.x;
+  const int nblk = gridDim.x - p.loss_blocks;
+  if (pid >= nblk) {
+    add_up_losses(p.loss, pid - nblk);
+    return;
+  }
   if ((nblk & 7) == 0) pid = (pid & 7) * (nblk >> 3) + (pid >> 3);
   const int m0 = (pid / tiles_n) * P::BM, n0 = (pid % tiles_n) * P::BN;
   const int lane = threadIdx.x & 63;
@@ -403,6 +407,11 @@ __device__ __forceinline__ void f32_product(const OA& oa, const OB& ob, int K, i
 // its own (neighbours along n first: they share the rows of A).
 template <int TM, int TN, int D, bool BKC, bool VA, bool VB>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs p, int tiles_n, int tiles) {
+  const int nblk = gridDim.x - p.loss_blocks;
+  if ((int)blockIdx.x >= nblk) {
+    add_up_losses(p.loss, blockIdx.x - nblk);
+    return;
+  }
   const int lane = threadIdx.x & 63;
   const int id = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (id >= tiles) return;
@@ -492,7 +501,7 @@ hipError_t launch_bf16(const GemmArgs& a, hipStream_t s) {
   static const hipError_t ok = allow_lds(gemm_bf16_kernel<TM, TN, WR, WC, WK, BK, STAGES, BS>, P::LDS_BYTES);
   if (ok != hipSuccess) return ok;
   const int tiles_m = (a.M + P::BM - 1) / P::BM, tiles_n = (a.N + P::BN - 1) / P::BN;
-  hipLaunchKernelGGL((gemm_bf16_kernel<TM, TN, WR, WC, WK, BK, STAGES, BS>), dim3(tiles_m * tiles_n), dim3(P::THREADS),
+  hipLaunchKernelGGL((gemm_bf16_kernel<TM, TN, WR, WC, WK, BK, STAGES, BS>), dim3(tiles_m * tiles_n + a.loss_blocks), dim3(P::THREADS),
                      P::LDS_BYTES, s, a, tiles_n);
   return hipGetLastError();
 }
@@ -514,7 +523,7 @@ hipError_t launch_bf16_sized(const GemmArgs& a, hipStream_t s) {
 template <int TM, int TN, int D>
 hipError_t launch_f32_tile(const GemmArgs& a, hipStream_t s) {
   const int tiles_n = (a.N + 16 * TN - 1) / (16 * TN), tiles = (a.M + 16 * TM - 1) / (16 * TM) * tiles_n;
-  const dim3 grid((tiles + 3) / 4), block(256);
+  const dim3 grid((tiles + 3) / 4 + a.loss_blocks), block(256);
   const bool va = (a.lda & 3) == 0 && (reinterpret_cast<uintptr_t>(a.A) & 15) == 0;
   const bool vb = a.b_kc && (a.ldb & 3) == 0 && (reinterpret_cast<uintptr_t>(a.B) & 15) == 0;
   if (a.b_kc) {

@@ -17,8 +17,7 @@ __device__ __forceinline__ float wave_sum(float v) {
 // lane, lane + 64, ... of all four, 512 columns at a time (its loads are then in flight together, and widths
 // up to 512 are read once).  Besides the loss, dz and dh it leaves the sums over its samples that the last
 // layer's weight gradient, bias gradient and the shard's loss are made of, so that nothing has to read the
-// activation again; the last block of a shard to finish adds up the shard's loss (in tile order: the
-// result does not depend on which block that is).
+// activation again.
 // Bound by the chain of round trips (activation -> logit -> gradient), not by bytes.
 template <typename TH, typename TD>
 __global__ __launch_bounds__(256) void head_tile_kernel(HeadArgs a, ShardTab tab, HeadTiles ht) {
@@ -26,7 +25,6 @@ __global__ __launch_bounds__(256) void head_tile_kernel(HeadArgs a, ShardTab tab
   constexpr int CPL = 8, CHUNK = 64 * CPL;
   __shared__ float col[4][CHUNK];
   __shared__ float sums[4][2];
-  __shared__ int last;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int tile = ht.base[a.k_begin] + blockIdx.x;
   int k = a.k_begin;
@@ -116,44 +114,29 @@ __global__ __launch_bounds__(256) void head_tile_kernel(HeadArgs a, ShardTab tab
     __syncthreads();
   }
   if (threadIdx.x == 0) {
-    // The block that adds the losses up may run on another XCD: stores that go past this XCD's L2, waited for
-    // before this block is counted.  (A release fence instead would write back all that L2 holds of the
-    // products before this kernel.)
-    __hip_atomic_store(part_out + a.width, (sums[0][0] + sums[1][0]) + (sums[2][0] + sums[3][0]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(part_out + a.width + 1, (sums[0][1] + sums[1][1]) + (sums[2][1] + sums[3][1]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    const int tiles = ht.base[k + 1] - ht.base[k];
-    last = __hip_atomic_fetch_add(a.done + k, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == tiles - 1;
+    part_out[a.width] = (sums[0][0] + sums[1][0]) + (sums[2][0] + sums[3][0]);
+    part_out[a.width + 1] = (sums[0][1] + sums[1][1]) + (sums[2][1] + sums[3][1]);
   }
-  if (blockIdx.x == 0 && a.k_begin + (int)threadIdx.x < a.k_end && tab.len[a.k_begin + threadIdx.x] == 0) {   // shards without samples
-    a.loss_k[a.k_begin + threadIdx.x] = 0.0f;
-    if (a.loss_out) a.loss_out[threadIdx.x] = 0.0f;
-  }
-  __syncthreads();
-  if (!last || wave != 0) return;
-  float l = 0.0f;
-  for (int t = ht.base[k] + lane; t < ht.base[k + 1]; t += 64)
-    l += __hip_atomic_load(a.part + (int64_t)t * a.ldpart + a.width + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  l = wave_sum(l);
-  if (lane == 0) {
-    __hip_atomic_store(a.done + k, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const float lk = l / (float)tab.len[k];
-    a.loss_k[k] = lk;
-    if (a.loss_out) a.loss_out[k - a.k_begin] = lk;
+  if (blockIdx.x == 0) {
+    if (threadIdx.x <= ANTDT_MAX_SHARDS) a.job->base[threadIdx.x] = ht.base[threadIdx.x];
+    if (threadIdx.x < ANTDT_MAX_SHARDS) a.job->len[threadIdx.x] = tab.len[threadIdx.x];
+    if (threadIdx.x == 0) {
+      a.job->part = a.part;
+      a.job->ldpart = a.ldpart;
+      a.job->width = a.width;
+      a.job->loss_out = a.loss_out;
+      a.job->first = a.k_begin;
+    }
   }
 }
 
 // Losses of shards without samples, when no shard of the range has any.
 __global__ __launch_bounds__(64) void head_no_samples_kernel(HeadArgs a) {
-  for (int k = a.k_begin + (int)threadIdx.x; k < a.k_end; k += 64) {
-    a.loss_k[k] = 0.0f;
+  for (int k = a.k_begin + (int)threadIdx.x; k < a.k_end; k += 64)
     if (a.loss_out) a.loss_out[k - a.k_begin] = 0.0f;
-  }
 }
 
-__global__ __launch_bounds__(64) void zero_words_kernel(int32_t* p, int n) {
-  for (int i = threadIdx.x; i < n; i += 64) p[i] = 0;
-}
+__global__ __launch_bounds__(64) void losses_kernel(const LossJob* job) { add_up_losses(job, blockIdx.x); }
 
 }  // namespace
 
@@ -167,8 +150,8 @@ hipError_t launch_head_tiles(const HeadArgs& a, const ShardTab& tab, hipStream_t
   return hipGetLastError();
 }
 
-hipError_t launch_zero_words(int32_t* p, int n, hipStream_t s) {
-  hipLaunchKernelGGL(zero_words_kernel, dim3(1), dim3(64), 0, s, p, n);
+hipError_t launch_losses(const LossJob* job, int shards, hipStream_t s) {
+  hipLaunchKernelGGL(losses_kernel, dim3(shards), dim3(64), 0, s, job);
   return hipGetLastError();
 }
 
