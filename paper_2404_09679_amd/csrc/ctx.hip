@@ -4,6 +4,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
 #include <mutex>
 #include <string>
 #include <utility>
@@ -724,6 +725,77 @@ static int compute_shard_grads(antdt_ctx* c) {
   return ANTDT_OK;
 }
 
+// Dense update from gradients in memory: g = sum over the rows of `tab` with their weights, then Adagrad and the bf16
+// copies of the weights (W_0's to `wb0`).
+static int dense_update(antdt_ctx* c, const ShardTab& tab, bf16_t* wb0, hipStream_t s) {
+  DenseAdagradArgs a;
+  memset(&a, 0, sizeof(a));
+  a.p = c->params; a.state = c->pstate; a.grads = c->shard_grads; a.stride = c->Pstride; a.lr = c->m.lr; a.eps = c->m.eps;
+  int nr = 0, rblocks = 0;
+  auto add_range = [&](int64_t off, int64_t len) {
+    a.rng_off[nr] = off; a.rng_len[nr] = len; a.rng_block[nr] = rblocks;
+    rblocks += (int)((len + 255) / 256);
+    ++nr;
+  };
+  if (c->act_bf16) {
+    for (int l = 0; l + 1 < c->L; ++l) {
+      a.w_off[l] = c->w_off[l]; a.rows[l] = c->width[l]; a.cols[l] = c->width[l + 1];
+      a.wb[l] = l == 0 ? wb0 : c->wb[l];
+      a.tile_base[l + 1] = a.tile_base[l] + ((c->width[l] + 63) / 64) * ((c->width[l + 1] + 63) / 64);
+      add_range(c->b_off[l], c->width[l + 1]);
+    }
+    a.n_mat = c->L - 1;
+    add_range(c->w_off[c->L - 1], c->P - c->w_off[c->L - 1]);
+  } else {
+    add_range(0, c->P);
+  }
+  a.n_rng = nr;
+  a.rng_block[nr] = rblocks;
+  ProfScope ps(prof_of(c), KID_DENSE_ADAGRAD, s);
+  HIP_TRY(c, launch_dense_adagrad(a, tab, s));
+  return ANTDT_OK;
+}
+
+// Cuts the sample ranges into pieces (one row of the gradient buffer each, the longest first) if the weight gradients
+// are better formed piece by piece, on large tiles, and added up by the update than by blocks that each walk all
+// samples.  With few tiles and many samples the latter have to be small tiles to be enough for the compute
+// units, and read each operand twice as often (845-1024-512-256, 15625 samples of eight unequal shards: 168 us against
+// 85 + 19 for the update; the whole step at 9000 / 15625 samples 389 / 577 -> 376 / 542 us).  Every piece costs a write
+// and a read of all gradients, which takes about a thousand samples to pay (6500 samples in 7 pieces 284 / 294 us,
+// 2573-1024-512 with 6500 in 12 pieces 471 / 507, 11000 in 12 779 / 777).
+static int cut_ranges(const antdt_ctx* c, const KSegments& seg, KSegments& pieces) {
+  int64_t samples = 0, tiles = 0;
+  for (int q = 0; q < seg.n; ++q) samples += seg.ke[q] - seg.ks[q];
+  for (int l = 0; l + 1 < c->L; ++l) tiles += (int64_t)((c->width[l] + 127) / 128) * ((c->width[l + 1] + 127) / 128);
+  if (tiles >= 400) return 0;
+  auto count = [&](int64_t len) {
+    int64_t n = 0;
+    for (int q = 0; q < seg.n; ++q) n += (seg.ke[q] - seg.ks[q] + len - 1) / len;
+    return n;
+  };
+  int64_t len = 1536;
+  while (count(len) > c->m.max_shards) len += len / 4;   // (ends: there are no more ranges than shards)
+  if (tiles * count(len) < 400 || samples < 1024 * count(len)) return 0;
+  memset(&pieces, 0, sizeof(pieces));
+  std::vector<std::pair<int, int>> order;   // (-length, place in the list of all pieces)
+  KSegments all;
+  memset(&all, 0, sizeof(all));
+  for (int q = 0; q < seg.n; ++q)
+    for (int k = seg.ks[q]; k < seg.ke[q]; k += (int)len) {
+      const int i = all.n++;
+      all.ks[i] = k; all.ke[i] = std::min(seg.ke[q], k + (int)len); all.w[i] = seg.w[q];
+      all.ts[i] = seg.ts[q]; all.te[i] = k == seg.ks[q] ? seg.te[q] : seg.ts[q];   // (the last layer's sums: with the first piece)
+      order.push_back({-(all.ke[i] - all.ks[i]), i});
+    }
+  std::sort(order.begin(), order.end());
+  for (const auto& o : order) {
+    const int i = pieces.n++;
+    pieces.ks[i] = all.ks[o.second]; pieces.ke[i] = all.ke[o.second]; pieces.w[i] = all.w[o.second];
+    pieces.ts[i] = all.ts[o.second]; pieces.te[i] = all.te[o.second];
+  }
+  return pieces.n;
+}
+
 // Forward and backward of shards [k0, k1) as one batched sequence of launches.
 static int worker_range(antdt_ctx* c, int k0, int k1, float* loss_out, hipStream_t s) {
   if (c->stage < ST_BATCH) return fail(c, ANTDT_BAD_STATE, "antdt_worker_step: call antdt_set_batch first");
@@ -972,7 +1044,6 @@ int antdt_apply_update(antdt_ctx* c, void* stream) {
   if (c->stage != ST_AGGREGATED) return fail(c, ANTDT_BAD_STATE, "antdt_apply_update: call antdt_aggregate first");
   hipStream_t s = (hipStream_t)stream;
   Profiler* pr = prof_of(c);
-  const antdt_model& m = c->m;
   // The dense update touches nothing the sparse update touches, so it runs on the
   // weight-gradient stream (behind those products, which it needs anyway) beside the sparse
   // update; `s` joins it before this call's work on `s` is complete.
@@ -990,8 +1061,9 @@ int antdt_apply_update(antdt_ctx* c, void* stream) {
   }
   if (c->wgrad_deferred) {
     // Weight gradients, their aggregation over the shards and the dense update in one kernel
-    // (the per-shard and the aggregated gradient stay in registers), behind the event that
-    // says the worker step's activations and pre-activation gradients are complete.
+    // (the per-shard and the aggregated gradient stay in registers; see cut_ranges for the other
+    // way), behind the event that says the worker step's activations and pre-activation gradients are
+    // complete.
     if (ds != s) {
       HIP_TRY(c, hipStreamWaitEvent(ds, c->ev_dh[0], 0));
     } else {  // (per-shard gradients that a view asked for may still be in flight on the library's stream)
@@ -1016,7 +1088,19 @@ int antdt_apply_update(antdt_ctx* c, void* stream) {
         ++seg.n;
       }
     }
-    {
+    KSegments pieces;
+    if (!c->shard_grads_done && cut_ranges(c, seg, pieces) > 0) {   // (a view's gradients stay where they are)
+      {
+        ProfScope ps(pr, KID_GEMM_WGRAD, ds);
+        HIP_TRY(c, launch_wgrad(u, pieces, true, ds));
+      }
+      ShardTab tab;
+      memset(&tab, 0, sizeof(tab));
+      tab.K = pieces.n;
+      for (int i = 0; i < pieces.n; ++i) tab.w[i] = pieces.w[i];
+      const int rc = dense_update(c, tab, c->wb0_alt, ds);
+      if (rc) return rc;
+    } else {
       ProfScope ps(pr, KID_WGRAD_ADAGRAD, ds);
       HIP_TRY(c, launch_wgrad(u, seg, false, ds));
     }
@@ -1031,33 +1115,8 @@ int antdt_apply_update(antdt_ctx* c, void* stream) {
     }
     c->wgrad_pending = false;  // `s` now waits for everything on that stream
   } else {
-    DenseAdagradArgs a;
-    memset(&a, 0, sizeof(a));
-    a.p = c->params; a.state = c->pstate; a.grads = c->shard_grads; a.stride = c->Pstride; a.lr = m.lr; a.eps = m.eps;
-    int nr = 0, rblocks = 0;
-    auto add_range = [&](int64_t off, int64_t len) {
-      a.rng_off[nr] = off; a.rng_len[nr] = len; a.rng_block[nr] = rblocks;
-      rblocks += (int)((len + 255) / 256);
-      ++nr;
-    };
-    if (c->act_bf16) {
-      for (int l = 0; l + 1 < c->L; ++l) {
-        a.w_off[l] = c->w_off[l]; a.rows[l] = c->width[l]; a.cols[l] = c->width[l + 1];
-        a.wb[l] = c->wb[l];
-        a.tile_base[l + 1] = a.tile_base[l] + ((c->width[l] + 63) / 64) * ((c->width[l + 1] + 63) / 64);
-        add_range(c->b_off[l], c->width[l + 1]);
-      }
-      a.n_mat = c->L - 1;
-      add_range(c->w_off[c->L - 1], c->P - c->w_off[c->L - 1]);
-    } else {
-      add_range(0, c->P);
-    }
-    a.n_rng = nr;
-    a.rng_block[nr] = rblocks;
-    {
-      ProfScope ps(pr, KID_DENSE_ADAGRAD, ds);
-      HIP_TRY(c, launch_dense_adagrad(a, c->tab, ds));
-    }
+    const int rc = dense_update(c, c->tab, c->wb[0], ds);
+    if (rc) return rc;
     if (ds != s) {
       HIP_TRY(c, hipEventRecord(c->ev_wgrad, ds));
       HIP_TRY(c, hipStreamWaitEvent(s, c->ev_wgrad, 0));

@@ -75,3 +75,35 @@ def test_runs_and_windows(dim, table, state, more, monkeypatch):
 
     monkeypatch.setattr(wl, "make_batch", planted)
     check_iteration(cfg, cfg.shard_sizes, tol=TOL32, batched=True, nonzero_state=True)
+
+
+# enough samples per shard that the weight gradients are formed piece by piece: unequal weights (a piece per shard, the
+# longest first) and equal ones (one range cut into pieces), against the update that walks all samples (a per-shard
+# view in between keeps it to that)
+@pytest.mark.parametrize("sizes", [(1500, 2700, 1100, 3700), (2300,) * 4])
+def test_weight_gradient_pieces(sizes):
+    import torch
+    from gpu_helpers import GpuRun
+    from test_gpu_parity import assert_close, make_inputs
+    cfg = _config(f"pieces-{sizes[0]}", 700 + sizes[0], num_fields=3, layer_sizes=(1288, 1032), shard_sizes=sizes)
+    tables, state, flat, fstate, batch = make_inputs(cfg, nonzero_state=True)
+    got = []
+    for view in (False, True):
+        run = GpuRun(cfg, tables, flat, state, fstate)
+        run.set_batch(batch)
+        run.ctx.assign_shard(batch.batch, len(sizes), sizes=sizes)
+        run.ctx.worker_step_all(torch.zeros(len(sizes), device="cuda:0"))
+        if view:
+            run.ctx.view_shard_grads(0)
+        run.ctx.aggregate()
+        run.ctx.apply_update()
+        run.ctx.worker_step_all(torch.zeros(len(sizes), device="cuda:0"))   # (from the updated bf16 copies)
+        torch.cuda.synchronize()
+        got.append((run.params.cpu().numpy().copy(), run.pstate.cpu().numpy().copy(), run.ctx.view_pooled(0).float().cpu().numpy().copy(),
+                    run.ctx.view_shard_grads(1)[1].cpu().numpy().copy()))
+    # sums over up to 9200 products of fp32, in another order: 1e-6 of their size
+    for a, b, what in zip(got[0], got[1], ("MLP parameters", "MLP accumulators", "pooled input", "input gradient")):
+        if what == "input gradient":   # (bf16 weights one rounding apart here and there)
+            assert np.linalg.norm(a - b) <= 2.0 ** -8 * np.linalg.norm(b), what
+        else:
+            assert_close(a, b, 1e-6, what, 1e-5)
