@@ -362,14 +362,18 @@ struct F32Operand {
   }
 };
 
-// acc += A B^T over the steps first, first + stride, ... of the K contraction slots; with `ones`, sum_b also
-// receives the sums of B's rows (products with ones).  Result layout: lane l of acc[i][j] holds row l & 15
+// acc = A B^T over the steps first, first + stride, ... of the K contraction slots; with `ones`, sum_b also
+// receives the sums of B's rows (products with ones).  The four MFMAs of a step go to CH sums of their own, added up at
+// the end: with four none waits for the one before, and chains a quarter as long round less (errors against 64
+// bits of a 397-256-128 model's coalesced gradients 1.05e-7 with one, 7.7e-8 with four; 9.8e-8 in vector FMAs); the
+// weight gradients, in four chains by wavefront already, keep one and the registers.  Result layout: lane l of acc[i][j] holds row l & 15
 // and the columns 4 (l >> 4) .. + 3 of tile (i, j).
-template <int TM, int TN, int D, bool ONES, typename OA, typename OB>
+template <int TM, int TN, int D, int CH, bool ONES, typename OA, typename OB>
 __device__ __forceinline__ void f32_product(const OA& oa, const OB& ob, int K, int first, int stride, int lane,
                                             f32x4 (&acc)[TM][TN], f32x4 (&sum_b)[TN], bool ones) {
   if (K <= 0) return;
   const int nk = (K + 15) / 16;
+  f32x4 part[CH][TM][TN] = {}, part_b[CH][TN] = {};
   float a[D][TM][4], b[D][TN][4];
 #pragma unroll
   for (int q = 0; q < D; ++q) {
@@ -390,16 +394,22 @@ __device__ __forceinline__ void f32_product(const OA& oa, const OB& ob, int K, i
         for (int i = 0; i < TM; ++i)
 #pragma unroll
           for (int j = 0; j < TN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[q][j][e], a[q][i][e], acc[i][j], 0, 0, 0);
+            part[e % CH][i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[q][j][e], a[q][i][e], part[e % CH][i][j], 0, 0, 0);
         if (ONES && ones) {
 #pragma unroll
           for (int j = 0; j < TN; ++j)
-            sum_b[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[q][j][e], 1.0f, sum_b[j], 0, 0, 0);
+            part_b[e % CH][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[q][j][e], 1.0f, part_b[e % CH][j], 0, 0, 0);
         }
       }
       oa.load(step + D * stride, K, lane, a[q]);
       ob.load(step + D * stride, K, lane, b[q]);
     }
+  }
+#pragma unroll
+  for (int j = 0; j < TN; ++j) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i) acc[i][j] = CH == 4 ? (part[0][i][j] + part[1 % CH][i][j]) + (part[2 % CH][i][j] + part[3 % CH][i][j]) : part[0][i][j];
+    if (ONES) sum_b[j] = CH == 4 ? (part_b[0][j] + part_b[1 % CH][j]) + (part_b[2 % CH][j] + part_b[3 % CH][j]) : part_b[0][j];
   }
 }
 
@@ -419,7 +429,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs p, int tiles_n, 
   const F32Operand<TM, true, VA> oa(reinterpret_cast<const float*>(p.A), p.lda, m0, p.M, lane);
   const F32Operand<TN, BKC, VB> ob(reinterpret_cast<const float*>(p.B), p.ldb, n0, p.N, lane);
   f32x4 acc[TM][TN] = {}, none[TN];
-  f32_product<TM, TN, D, false>(oa, ob, p.K, 0, 1, lane, acc, none, false);
+  f32_product<TM, TN, D, 4, false>(oa, ob, p.K, 0, 1, lane, acc, none, false);
   float* C = reinterpret_cast<float*>(p.C);
 #pragma unroll
   for (int i = 0; i < TM; ++i)
@@ -462,7 +472,7 @@ __global__ __launch_bounds__(256) void wgrad_f32_kernel(WgradArgs u, KSegments s
   const float* B = reinterpret_cast<const float*>(u.B[li]) + (int64_t)seg.ks[q] * u.ldb[li];
   const F32Operand<TM, false, false> oa(A, u.lda[li], m0, M, lane);
   const F32Operand<TN, false, false> ob(B, u.ldb[li], n0, N, lane);
-  f32_product<TM, TN, D, true>(oa, ob, seg.ke[q] - seg.ks[q], wave, 4, lane, acc, accb, ones);
+  f32_product<TM, TN, D, 1, true>(oa, ob, seg.ke[q] - seg.ks[q], wave, 4, lane, acc, accb, ones);
   float* mine = red[wave];
 #pragma unroll
   for (int j = 0; j < TN; ++j) {
