@@ -414,6 +414,19 @@ hipError_t launch_sort_small_items(const SortPlan& pl, const SortBuffers& sb, co
   return hipGetLastError();
 }
 
+// Sample index of every lookup, from the offsets alone: what the gather records along the way, for a sort that does not
+// wait for the gather.  Eight lanes per bag.  Bound by its stores.
+__global__ __launch_bounds__(256) void expand_samples_kernel(const int32_t* offsets, int32_t* lookup_sample, FieldPtr fp, int B) {
+  const int f = blockIdx.y, c = threadIdx.x & 7;
+  const int s = blockIdx.x * 32 + (threadIdx.x >> 3);
+  if (s >= B) return;
+  const int32_t* off = offsets + (int64_t)f * (B + 1) + s;
+  const int nnz = (int)(fp.p[f + 1] - fp.p[f]);
+  const int e = min(off[1], nnz);
+  int32_t* out = lookup_sample + fp.p[f];
+  for (int j = max(off[0], 0) + c; j < e; j += 8) out[j] = s;
+}
+
 // ------------------------------------------------- leaving shards out
 // When the servers disregard the gradients of some workers (the backup-workers baseline of
 // Section VII-A.3), only the lookups of the remaining shards are coalesced.  A shard is a
@@ -967,6 +980,12 @@ hipError_t launch_sort(const SortPlan& pl, const SortBuffers& sb, const FieldPtr
   }
   *sorted_buf = (pl.passes - 1) & 1;
   return hipSuccess;
+}
+
+hipError_t launch_expand_samples(const int32_t* offsets, int32_t* lookup_sample, const FieldPtr& fp, int F, int B, hipStream_t s) {
+  if (B <= 0) return hipSuccess;
+  hipLaunchKernelGGL(expand_samples_kernel, dim3((B + 31) / 32, F), dim3(256), 0, s, offsets, lookup_sample, fp, B);
+  return hipGetLastError();
 }
 
 hipError_t launch_segments(const SegArgs& a, const FieldPtr& fp, const TileBase& tb, Profiler* prof, hipStream_t s) {

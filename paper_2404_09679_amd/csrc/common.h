@@ -282,6 +282,7 @@ struct SegArgs {
   int64_t R;
   float lr, eps;
 };
+hipError_t launch_expand_samples(const int32_t* offsets, int32_t* lookup_sample, const FieldPtr& fp, int F, int B, hipStream_t s);
 hipError_t launch_segments(const SegArgs& a, const FieldPtr& fp, const TileBase& tb, Profiler* prof, hipStream_t s);
 hipError_t launch_mask_pack(const int32_t* ids, const int32_t* lookup_sample, const int32_t* offsets, int64_t B, int F,
                             const FieldPtr& fp, const ShardTab& tab, int64_t* cbase, int32_t* ids_out,
