@@ -101,17 +101,15 @@ def _bytes_and_flops(cfg, stats, model):
         "seg_heads": ("hbm", 4 * nnz),
         "seg_emit": ("hbm", 4 * nnz + 8 * U),
         # one fused kernel: segmented sum of the per-lookup gradient rows + row-sparse Adagrad
-        # (sample indices, run table, every pooled-gradient row once, touched rows and state
-        # read and written); the long-run chunk kernels work on the same bytes
-        "sparse_adagrad": ("hbm", 4 * nnz + 12 * U + B * F * D * 4 + U * (2 * D * e + 2 * state_row)),
-        # the long runs' finish kernel: chunk sums read, rows and state of the hot rows (counted
-        # with the fused kernel above, whose launch computes the chunk sums)
+        # (sorted keys and sample indices, every pooled-gradient row once, touched rows and state
+        # read and written)
+        "sparse_adagrad": ("hbm", 8 * nnz + B * F * D * 4 + U * (2 * D * e + 2 * state_row)),
+        # runs over several windows: their partial sums, rows and state (counted with the kernel above)
         "seg_reduce_long": ("hbm", 0),
-        # K shard gradients read once, fp32 weights and state read and written, both bf16 copies
-        "dense_adagrad": ("hbm", P * ((K + 4) * 4 + (4 if cfg.gemm_dtype == "bf16" else 0))),
-        # last hidden activation read; its gradient written row-major and transposed; labels,
-        # logits, per-sample loss and dz
-        "head": ("hbm", B * (s[L - 1] * es * (3 if cfg.gemm_dtype == "bf16" else 2) + 16)),
+        # K shard gradients read once, fp32 weights and state read and written, the bf16 copy
+        "dense_adagrad": ("hbm", P * ((K + 4) * 4 + (2 if cfg.gemm_dtype == "bf16" else 0))),
+        # last hidden activation read, its gradient written; labels
+        "head": ("hbm", B * (s[L - 1] * es * 2 + 4)),
         "head_reduce": ("hbm", B * (s[L - 1] * es + 8)),
         "bias_grad": ("hbm", sum(B * s[l + 1] * 4 for l in range(L - 1))),
         "sort_scan": ("hbm", 0),

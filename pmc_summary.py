@@ -48,13 +48,13 @@ def class_totals(rows):
             after_head, cls = True, "head"
         elif "head_reduce" in k:
             cls = "head_reduce"
-        elif "wgrad_update" in k:
+        elif "wgrad_" in k:
             cls = "wgrad_adagrad"
         elif "transpose" in k:
             cls = "transpose"
-        elif "gemm_" in k:  # the grouped instantiations (last template argument true) are the weight gradients
-            cls = "gemm_fwd" if not after_head else ("gemm_wgrad" if "true>" in k else "gemm_bwd")
-        elif "seg_reduce" in k:
+        elif "gemm_" in k:
+            cls = "gemm_bwd" if after_head else "gemm_fwd"
+        elif "seg_reduce" in k or "seg_window" in k:
             cls = "sparse_adagrad"
         elif "seg_chunk" in k or "seg_finish" in k:
             cls = "seg_reduce_long"
