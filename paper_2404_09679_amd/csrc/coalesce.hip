@@ -403,10 +403,8 @@ template <int IT>
 hipError_t launch_sort_small_items(const SortPlan& pl, const SortBuffers& sb, const FieldPtr& fp, const ShardTab& tab, Profiler* prof,
                                    hipStream_t s) {
   constexpr int bytes = SMALL_THREADS * IT * 4;
-  static const hipError_t ok =
-      bytes + SMALL_THREADS * 34 + 1024 <= 64 * 1024
-          ? hipSuccess
-          : hipFuncSetAttribute(reinterpret_cast<const void*>(sort_small_kernel<IT>), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  static std::atomic<uint64_t> allowed{0};
+  const hipError_t ok = allow_lds(sort_small_kernel<IT>, bytes, 36 * 1024, allowed);
   if (ok != hipSuccess) return ok;
   ProfScope ps(prof, KID_SORT_SCATTER, s);
   hipLaunchKernelGGL((sort_small_kernel<IT>), dim3(pl.F + (pl.B + SMALL_THREADS - 1) / SMALL_THREADS), dim3(SMALL_THREADS), bytes, s,

@@ -6,6 +6,7 @@
 
 #include "antdt.h"
 
+#include <atomic>
 #include <string>
 
 namespace antdt {
@@ -48,6 +49,21 @@ struct ShardTab {
 struct TileBase {
   int32_t t[ANTDT_MAX_FIELDS + 1];  // prefix sum of sort tiles per field
 };
+
+// Kernels whose blocks need more than 64 KB of LDS have to be allowed it, once per device; `done`: the devices (a bit
+// each) on which that has been done for this kernel.
+template <typename F>
+inline hipError_t allow_lds(F kernel, int dynamic_bytes, int static_bytes, std::atomic<uint64_t>& done) {
+  if (dynamic_bytes + static_bytes <= 64 * 1024) return hipSuccess;
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const uint64_t bit = 1ull << (dev & 63);
+  if (done.load(std::memory_order_relaxed) & bit) return hipSuccess;
+  e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, dynamic_bytes);
+  if (e == hipSuccess) done.fetch_or(bit, std::memory_order_relaxed);
+  return e;
+}
 
 // Kernel classes for the optional event timing.
 enum KernelId {

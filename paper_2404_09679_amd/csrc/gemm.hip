@@ -498,17 +498,11 @@ __global__ __launch_bounds__(256) void cast_bf16_kernel(CastArgs a) {
     a.dst[i] = i < a.n_src ? f2bf(a.src[i]) : (bf16_t)0;
 }
 
-// Kernels with more than 64 KB of LDS have to be told so once.
-template <typename F>
-hipError_t allow_lds(F f, int bytes) {
-  if (bytes <= 64 * 1024) return hipSuccess;
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(f), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-}
-
 template <int TM, int TN, int WR, int WC, int WK, int BK, int STAGES, bool BS>
 hipError_t launch_bf16(const GemmArgs& a, hipStream_t s) {
   typedef BlockProduct<TM, TN, WR, WC, WK, BK, STAGES, false, BS> P;
-  static const hipError_t ok = allow_lds(gemm_bf16_kernel<TM, TN, WR, WC, WK, BK, STAGES, BS>, P::LDS_BYTES);
+  static std::atomic<uint64_t> allowed{0};
+  const hipError_t ok = allow_lds(gemm_bf16_kernel<TM, TN, WR, WC, WK, BK, STAGES, BS>, P::LDS_BYTES, 0, allowed);
   if (ok != hipSuccess) return ok;
   const int tiles_m = (a.M + P::BM - 1) / P::BM, tiles_n = (a.N + P::BN - 1) / P::BN;
   hipLaunchKernelGGL((gemm_bf16_kernel<TM, TN, WR, WC, WK, BK, STAGES, BS>), dim3(tiles_m * tiles_n + a.loss_blocks), dim3(P::THREADS),
@@ -576,7 +570,8 @@ hipError_t launch_wgrad_f32(const WgradArgs& a, const KSegments& seg, hipStream_
 template <int TM, int TN, int WR, int WC, int BK, int STAGES, WgradMode MODE>
 hipError_t launch_wgrad_tile(const WgradArgs& a, const KSegments& seg, int groups, hipStream_t s) {
   typedef BlockProduct<TM, TN, WR, WC, 1, BK, STAGES, true, true> P;
-  static const hipError_t ok = allow_lds(wgrad_kernel<TM, TN, WR, WC, BK, STAGES, MODE>, P::LDS_BYTES);
+  static std::atomic<uint64_t> allowed{0};
+  const hipError_t ok = allow_lds(wgrad_kernel<TM, TN, WR, WC, BK, STAGES, MODE>, P::LDS_BYTES, 0, allowed);
   if (ok != hipSuccess) return ok;
   WgradArgs u = a;
   u.tile_base[0] = 0;
