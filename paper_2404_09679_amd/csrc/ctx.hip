@@ -157,9 +157,9 @@ struct antdt_ctx {
   hipStream_t side = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
   // second side stream: the weight-gradient products, which nothing needs before the dense
-  // update, run there beside the data-gradient chain and the sparse reduction
+  // update, run there beside the sparse reduction
   hipStream_t wside = nullptr;
-  hipEvent_t ev_dh[ANTDT_MAX_LAYERS + 1] = {};  // ev_dh[l]: dH_l (and its transposed copy) is ready
+  hipEvent_t ev_dh[ANTDT_MAX_LAYERS + 1] = {};  // [0]: the operands of the weight gradients are complete; [L]: all before the dense update
   hipEvent_t ev_wgrad = nullptr;                // all weight gradients of the last worker step are written
   bool wgrad_pending = false;
   bool presorted = false;     // the coalescing structure of the current batch and split is built (or being built)
@@ -1109,6 +1109,8 @@ int antdt_apply_update(antdt_ctx* c, void* stream) {
       for (int i = 0; i < pieces.n; ++i) tab.w[i] = pieces.w[i];
       const int rc = dense_update(c, tab, c->wb0_alt, ds);
       if (rc) return rc;
+      // a view may form the per-shard gradients in the same buffer, on the library's stream, behind this event
+      if (ds == s) HIP_TRY(c, hipEventRecord(c->ev_dh[0], s));
     } else {
       ProfScope ps(pr, KID_WGRAD_ADAGRAD, ds);
       HIP_TRY(c, launch_wgrad(u, seg, false, ds));
