@@ -250,6 +250,13 @@ int antdt_set_eager_weight_gradients(antdt_ctx* ctx, int32_t on);
  * for it to pay, the sort runs on a stream of the library beside the MLP, and the weight-gradient
  * work on another beside the sparse update.  Results are the same.  To be called between
  * iterations (ANTDT_BAD_STATE while work of an iteration is outstanding).  Host only.
+ *
+ * Captures: an iteration (antdt_worker_step* ... antdt_apply_update) may be captured into a graph and
+ * replayed, alone or with iterations outside the graph in between; the batch is the one the captured calls
+ * were given, at the same addresses.  A replay does not advance the context: synchronise it before
+ * antdt_view_pooled / antdt_view_shard_grads, which then show its results; the other views belong to calls.
+ * antdt_view_shard_grads of a bf16 model forms the per-shard gradients on a stream of the library
+ * also when on == 0 (it has no stream argument and waits for them).
  */
 int antdt_set_library_streams(antdt_ctx* ctx, int32_t on);
 

@@ -111,8 +111,8 @@ struct antdt_ctx {
   float* dx = nullptr;
   float *shard_grads = nullptr, *g_dense = nullptr, *sample_w = nullptr, *G = nullptr;
   bf16_t* wb[ANTDT_MAX_LAYERS] = {};     // bf16 W_l as [in (padded), out]: operand of the forward product and the data gradient
-  bf16_t* wb0_alt = nullptr;             // second buffer for W_0: the fused dense update writes the new copy there
-                                         // while the input-gradient product may still read the old one
+  bf16_t* wb0_alt = nullptr;             // second buffer for W_0: a dense update beside the launch stream writes the new
+                                         // copy there while the input-gradient product may still read the old one
   float* head_part = nullptr;            // loss kernel's sums per tile of samples [tiles, ldpart]
   int64_t ldpart = 0;
   LossJob* loss_job = nullptr;           // what it leaves to the launch that adds up the losses
@@ -152,6 +152,8 @@ struct antdt_ctx {
   bool batched = false;                  // the last worker step covered all shards
   bool wgrad_deferred = false;           // this worker step left the weight gradients to apply_update / the views
   bool shard_grads_done = false;         // the per-shard dense gradients of this worker step are (being) written
+  bool captured = false;                 // a stream capture has recorded calls of this binding (see note_capture)
+  bool operands_captured = false;        // ev_dh[0] was last recorded into a capture
   int sorted_buf = 0;
   // side stream on which the coalescing structure of a batch is built while the MLP runs
   hipStream_t side = nullptr;
@@ -186,6 +188,16 @@ static inline hipStream_t side_stream(const antdt_ctx* c) {
 static inline hipStream_t wgrad_stream(const antdt_ctx* c) {
   const bool enough = c->act_bf16 && (c->fp.p[c->m.num_fields] >= (c->batched ? 100000 : 600000) || c->P >= 2000000);
   return (c->static_bound || c->no_streams || !enough) ? nullptr : c->wside;
+}
+
+// A captured call is replayed behind the library's back, with the addresses it was captured with: from the first one on
+// (until the context is bound again) W_0's copy keeps its place, and per-shard gradients that a view computed are not
+// taken for those of the last replay.
+static bool note_capture(antdt_ctx* c, hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  const bool capturing = hipStreamIsCapturing(s, &st) == hipSuccess && st != hipStreamCaptureStatusNone;
+  c->captured = c->captured || capturing;
+  return capturing;
 }
 
 static int fail(antdt_ctx* c, int code, const std::string& msg) {
@@ -431,6 +443,7 @@ int antdt_bind(antdt_ctx* c, void* tables, float* table_state, float* mlp_params
   c->params = mlp_params;
   c->pstate = mlp_state;
   carve(c, (char*)workspace);
+  c->captured = false;
   if (!c->side) {
     HIP_TRY(c, hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking));
     HIP_TRY(c, hipEventCreateWithFlags(&c->ev_fork, SYNC_EVENT_FLAGS));
@@ -496,6 +509,7 @@ int antdt_bind_static(antdt_ctx* c, void* tables, float* table_state, float* mlp
   c->params = mlp_params;
   c->pstate = mlp_state;
   carve(c, (char*)base);
+  c->captured = false;
   c->stage = ST_BOUND;
   c->have_shards = false;
   return init_workspace(c, (hipStream_t)stream);
@@ -683,7 +697,7 @@ static void fill_wgrad_args(antdt_ctx* c, WgradArgs& u) {
     u.A[l] = l == 0 ? c->x : c->h[l]; u.lda[l] = l == 0 ? c->ldx : c->width[l];
     u.B[l] = c->dh[l + 1]; u.ldb[l] = c->width[l + 1];
     u.M[l] = c->width[l]; u.N[l] = c->width[l + 1];
-    u.w_off[l] = c->w_off[l]; u.wb[l] = l == 0 ? c->wb0_alt : c->wb[l];
+    u.w_off[l] = c->w_off[l]; u.wb[l] = c->wb[l];
   }
   u.part = c->head_part; u.ldpart = c->ldpart; u.width = c->width[c->L - 1]; u.last_off = c->w_off[c->L - 1];
   u.p = c->params; u.state = c->pstate; u.lr = c->m.lr; u.eps = c->m.eps;
@@ -711,10 +725,10 @@ static int shard_weight_gradients(antdt_ctx* c, int k0, int k1, hipStream_t ws) 
 // The per-shard dense gradients of a worker step that left them to the dense update: computed
 // now, on the weight-gradient stream, for a view (or the stand-alone aggregation) that wants
 // them in memory.  Shards that were not stepped get whatever their rows hold (never read back).
-static int compute_shard_grads(antdt_ctx* c) {
-  if (!c->wgrad_deferred || c->shard_grads_done) return ANTDT_OK;
+static int compute_shard_grads(antdt_ctx* c, bool capturing) {
+  if (!c->wgrad_deferred || (c->shard_grads_done && !c->captured)) return ANTDT_OK;
   hipStream_t ws = c->wside;
-  HIP_TRY(c, hipStreamWaitEvent(ws, c->ev_dh[0], 0));
+  if (!c->operands_captured || capturing) HIP_TRY(c, hipStreamWaitEvent(ws, c->ev_dh[0], 0));   // (else the replay is complete)
   {
     const int rc = shard_weight_gradients(c, 0, c->tab.K, ws);
     if (rc) return rc;
@@ -909,6 +923,7 @@ static int worker_range(antdt_ctx* c, int k0, int k1, float* loss_out, hipStream
   c->shard_grads_done = false;
   // The event behind the last operand of the weight gradients (with up to one hidden layer the loss kernel
   // writes it, else the data gradient of layer 1).
+  c->operands_captured = note_capture(c, s);
   if (deferred && L <= 2) HIP_TRY(c, hipEventRecord(c->ev_dh[0], s));
   ProfScope bwd_scope(L > 1 ? pr : nullptr, KID_GEMM_BWD, s);
   bwd_scope.launches(L - 1);
@@ -1057,8 +1072,14 @@ int antdt_apply_update(antdt_ctx* c, void* stream) {
   // weight-gradient stream (behind those products, which it needs anyway) beside the sparse
   // update; `s` joins it before this call's work on `s` is complete.
   hipStream_t ds = wgrad_stream(c) ? wgrad_stream(c) : s;
-  if (ds != s && !c->wgrad_deferred) {
-    // (the dense update overwrites weights that the worker step's last products on `s` read)
+  const bool capturing = note_capture(c, s);
+  // Beside the launch stream the input-gradient product of this step, enqueued behind the event that `ds` waits for, may
+  // still be reading the bf16 copy of W_0: the new one goes to the other buffer, which is the current one from then
+  // on (the products of deeper layers ran before the event).  On one stream, and for a captured iteration, whose
+  // replays would never see the buffers change places, it is overwritten behind everything on `s`.
+  const bool other_w0 = c->wgrad_deferred && ds != s && !c->captured;
+  if (ds != s && !other_w0) {
+    // (the dense update overwrites weights or copies that the worker step's last products on `s` read)
     HIP_TRY(c, hipEventRecord(c->ev_dh[c->L], s));  // everything enqueued on `s` so far (loss, last layer's gradient)
     HIP_TRY(c, hipStreamWaitEvent(ds, c->ev_dh[c->L], 0));
   }
@@ -1073,14 +1094,16 @@ int antdt_apply_update(antdt_ctx* c, void* stream) {
     // (the per-shard and the aggregated gradient stay in registers; see cut_ranges for the other
     // way), behind the event that says the worker step's activations and pre-activation gradients are
     // complete.
-    if (ds != s) {
+    if (other_w0) {
       HIP_TRY(c, hipStreamWaitEvent(ds, c->ev_dh[0], 0));
-    } else {  // (per-shard gradients that a view asked for may still be in flight on the library's stream)
+    } else if (ds == s) {  // (per-shard gradients that a view asked for may still be in flight on the library's stream)
       const int rcj = join_wgrad(c, s);
       if (rcj) return rcj;
     }
     WgradArgs u;
     fill_wgrad_args(c, u);
+    bf16_t* wb0 = other_w0 ? c->wb0_alt : c->wb[0];
+    u.wb[0] = wb0;
     const HeadTiles ht = head_tiles(c->tab);
     KSegments seg;
     memset(&seg, 0, sizeof(seg));
@@ -1107,19 +1130,18 @@ int antdt_apply_update(antdt_ctx* c, void* stream) {
       memset(&tab, 0, sizeof(tab));
       tab.K = pieces.n;
       for (int i = 0; i < pieces.n; ++i) tab.w[i] = pieces.w[i];
-      const int rc = dense_update(c, tab, c->wb0_alt, ds);
+      const int rc = dense_update(c, tab, wb0, ds);
       if (rc) return rc;
       // a view may form the per-shard gradients in the same buffer, on the library's stream, behind this event
-      if (ds == s) HIP_TRY(c, hipEventRecord(c->ev_dh[0], s));
+      if (ds == s) {
+        HIP_TRY(c, hipEventRecord(c->ev_dh[0], s));
+        c->operands_captured = capturing;
+      }
     } else {
       ProfScope ps(pr, KID_WGRAD_ADAGRAD, ds);
       HIP_TRY(c, launch_wgrad(u, seg, false, ds));
     }
-    // The input-gradient product of this step, enqueued behind the event this stream waited for,
-    // may still be reading the old bf16 copy of W_0: the kernel wrote the new one to the other
-    // buffer, which is the current one from here on (the products of deeper layers ran before
-    // the event).
-    std::swap(c->wb[0], c->wb0_alt);
+    if (other_w0) std::swap(c->wb[0], c->wb0_alt);
     if (ds != s) {
       HIP_TRY(c, hipEventRecord(c->ev_wgrad, ds));
       HIP_TRY(c, hipStreamWaitEvent(s, c->ev_wgrad, 0));
@@ -1195,7 +1217,7 @@ int antdt_view_shard_grads(antdt_ctx* c, int32_t k, const float** dense, const f
   if (!c->have_shards || k < 0 || k >= c->tab.K) return fail(c, ANTDT_INVALID_ARG, "antdt_view_shard_grads: shard index out of range");
   if (c->stage < ST_BATCH) return fail(c, ANTDT_BAD_STATE, "antdt_view_shard_grads: nothing computed yet");
   {
-    const int rcg = compute_shard_grads(c);
+    const int rcg = compute_shard_grads(c, false);
     if (rcg) return rcg;
   }
   if (c->wgrad_pending) {  // the weight gradients are written on their own stream: wait for it here
@@ -1212,7 +1234,7 @@ int antdt_view_dense_grad(antdt_ctx* c, const float** g, void* stream) {
   if (!c || !g) return fail(c, ANTDT_INVALID_ARG, "antdt_view_dense_grad: null argument");
   if (c->stage != ST_AGGREGATED) return fail(c, ANTDT_BAD_STATE, "antdt_view_dense_grad: valid between antdt_aggregate and antdt_apply_update");
   {
-    const int rcg = compute_shard_grads(c);
+    const int rcg = compute_shard_grads(c, note_capture(c, (hipStream_t)stream));
     if (rcg) return rcg;
     const int rcj = join_wgrad(c, (hipStream_t)stream);
     if (rcj) return rcj;

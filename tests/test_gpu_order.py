@@ -1,0 +1,71 @@
+"""The order of the calls and the streams they go to: captured iterations, worker steps on streams of their
+own, views between and after the calls, options changed on the way.  The same work in the plainest order
+(one stream, no view, nothing captured) is the reference; sums are formed in the same order, so results are equal bit
+for bit unless stated."""
+import numpy as np
+import pytest
+import torch
+
+import workload as wl
+
+pytestmark = pytest.mark.gpu
+
+# bf16 products; 55 000 lookups and 0.09 M parameters (dense update on the launch stream) or 2.3 M (on a stream of its own)
+SMALL_BF = wl.RankingConfig("order-small", 5, 20_000, 32, "f32", "elementwise", 13, (173, 256, 128, 64, 1), "bf16",
+                            20, 1.1, (300, 37, 0, 663), wl.SEED0 + 801)
+WIDE_BF = wl.scaled(SMALL_BF, name="order-wide", layer_sizes=(173, 2048, 1024, 1))
+
+
+def start(cfg, **kw):
+    from gpu_helpers import GpuRun
+    from test_gpu_parity import make_inputs
+    tables, state, flat, fstate, batch = make_inputs(cfg, nonzero_state=True)
+    run = GpuRun(cfg, tables, flat, state, fstate, max_batch=batch.batch, max_shards=len(cfg.shard_sizes),
+                 max_nnz=int(batch.field_ptr[-1]), **kw)
+    run.set_batch(batch)
+    run.ctx.assign_shard(batch.batch, len(cfg.shard_sizes), sizes=cfg.shard_sizes)
+    run.loss = torch.zeros(len(cfg.shard_sizes), device="cuda:0")
+    torch.cuda.synchronize()
+    return run
+
+
+def step(run):
+    run.ctx.worker_step_all(run.loss)
+    run.ctx.aggregate()
+    run.ctx.apply_update()
+
+
+def weights(run):
+    torch.cuda.synchronize()
+    return [t.float().cpu().numpy().copy() for t in (run.loss, run.params, run.pstate, run.tables, run.state)]
+
+
+def assert_same(a, b, what):
+    for x, y, name in zip(a, b, ("losses", "MLP parameters", "MLP accumulators", "tables", "accumulators")):
+        assert np.array_equal(x, y), f"{what}: {name}"
+
+
+@pytest.mark.parametrize("cfg,streams", [(SMALL_BF, False), (WIDE_BF, False), (WIDE_BF, True)],
+                         ids=["small-one-stream", "wide-one-stream", "wide"])
+def test_replays_of_a_captured_iteration(cfg, streams):
+    """Every replay reads the weights that the one before wrote, the bf16 copy of the first layer's among them, also with
+    iterations outside the graph in between."""
+    ref, run = start(cfg, streams=streams), start(cfg, streams=streams)
+    step(ref)
+    step(run)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        step(run)
+    for i in range(4):
+        step(ref)
+        graph.replay()
+        assert_same(weights(run), weights(ref), f"replay {i}")
+        for k in (1, 3):
+            for a, b in zip(run.ctx.view_shard_grads(k), ref.ctx.view_shard_grads(k)):
+                torch.cuda.synchronize()
+                assert torch.equal(a, b), f"gradients of shard {k}, replay {i}"
+        if i == 1:
+            step(ref)
+            step(run)
+            assert_same(weights(run), weights(ref), "iteration between the replays")
