@@ -155,7 +155,7 @@ struct GemmArgs {
   // Further blocks of the launch add up the losses that the loss kernel left per tile of samples, one shard each (nobody
   // waits for them, and counting the loss kernel's blocks to have its last one do it kept the chain waiting 3 us).
   int32_t loss_blocks;
-  const struct LossJob* loss;
+  const struct LossJob* loss;   // [loss_blocks]
 };
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s);
 
@@ -213,7 +213,7 @@ struct HeadArgs {
   // the sums over the samples are formed along the way, per tile of samples of one shard
   float* part;          // [tiles, ldpart] sum of dz * h per column; column `width`: sum of dz, `width` + 1: of the losses
   int64_t ldpart;
-  struct LossJob* job;  // written by the first block, for the launch that adds up the losses
+  struct LossJob* job;  // [K] those of the range's shards are written by the first block, for the launch that adds up the losses
   float* loss_out;      // caller's buffer or NULL; element (k - k_begin)
 };
 // Tiles of the loss kernel: HEAD_TILE consecutive samples of one shard.  tile_base[k] = first tile of shard k.
@@ -231,23 +231,21 @@ inline HeadTiles head_tiles(const ShardTab& tab) {
 hipError_t launch_head_tiles(const HeadArgs& a, const ShardTab& tab, hipStream_t s);
 hipError_t launch_losses(const LossJob* job, int shards, hipStream_t s);   // stand-alone, for models without a hidden layer
 
-// The mean loss of a shard: its tiles' sums in a fixed order (lanes take every 64th tile).
+// The mean loss of a shard: its tiles' sums in a fixed order (lanes take every 64th tile).  One job per shard: worker
+// steps of different shards may run on different streams at the same time.
 struct LossJob {
-  const float* part;    // + width + 1: the tile's sum of losses
-  float* loss_out;      // element i: shard first + i
+  const float* sums;    // the first tile's sum of losses, ldpart further on the next one's
+  float* loss_out;
   int64_t ldpart;
-  int32_t width, first;
-  int32_t base[ANTDT_MAX_SHARDS + 1];   // first tile of every shard
-  int32_t len[ANTDT_MAX_SHARDS];
+  int32_t tiles, len;   // samples: len
 };
-__device__ __forceinline__ void add_up_losses(const LossJob* job, int i) {   // (the first wavefront of a block)
+__device__ __forceinline__ void add_up_losses(const LossJob* job) {   // (the first wavefront of a block)
   if (threadIdx.x >= 64) return;
-  const int k = job->first + i, t1 = job->base[k + 1];
   float l = 0.0f;
-  for (int t = job->base[k] + (int)threadIdx.x; t < t1; t += 64) l += job->part[(int64_t)t * job->ldpart + job->width + 1];
+  for (int t = (int)threadIdx.x; t < job->tiles; t += 64) l += job->sums[(int64_t)t * job->ldpart];
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) l += __shfl_xor(l, o, 64);
-  if (threadIdx.x == 0 && job->loss_out) job->loss_out[i] = job->len[k] > 0 ? l / (float)job->len[k] : 0.0f;
+  if (threadIdx.x == 0 && job->loss_out) *job->loss_out = job->len > 0 ? l / (float)job->len : 0.0f;
 }
 
 // ------------------------------------------------------------- coalesce.hip

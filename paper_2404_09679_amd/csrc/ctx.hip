@@ -115,7 +115,7 @@ struct antdt_ctx {
                                          // copy there while the input-gradient product may still read the old one
   float* head_part = nullptr;            // loss kernel's sums per tile of samples [tiles, ldpart]
   int64_t ldpart = 0;
-  LossJob* loss_job = nullptr;           // what it leaves to the launch that adds up the losses
+  LossJob* loss_job = nullptr;           // [K] what it leaves to the launch that adds up the losses
   int32_t* lookup_sample = nullptr;
   int32_t *key[2] = {}, *pay[2] = {}, *tile_heads = nullptr, *ubase = nullptr, *uniq = nullptr;
   int32_t *segoff = nullptr, *pack_pay = nullptr, *segabs = nullptr, *goes_out = nullptr;
@@ -250,7 +250,7 @@ static size_t carve(antdt_ctx* c, char* base) {
     }
   }
   c->head_part = (float*)take((size_t)(Bm / HEAD_TILE + K) * c->ldpart * 4);
-  c->loss_job = (LossJob*)take(sizeof(LossJob));
+  c->loss_job = (LossJob*)take((size_t)K * sizeof(LossJob));
   c->lookup_sample = (int32_t*)take((size_t)N * 4);
   for (int i = 0; i < 2; ++i) {
     c->key[i] = (int32_t*)take((size_t)N * 4);
@@ -909,7 +909,7 @@ static int worker_range(antdt_ctx* c, int k0, int k1, float* loss_out, hipStream
     a.part = c->head_part; a.ldpart = c->ldpart; a.job = c->loss_job; a.loss_out = loss_out;
     ProfScope ps(pr, KID_HEAD, s);
     HIP_TRY(c, launch_head_tiles(a, tab, s));
-    if (L == 1 && loss_out && ns > 0) HIP_TRY(c, launch_losses(c->loss_job, k1 - k0, s));   // (else beside the input gradient)
+    if (L == 1 && loss_out && ns > 0) HIP_TRY(c, launch_losses(c->loss_job + k0, k1 - k0, s));   // (else beside the input gradient)
   }
   // Backward.  The data-gradient chain dH_{l+1} -> dH_l first; nothing needs the weight gradients before the dense
   // update.  With bf16 products they are not computed here at all, unless the caller asked for them or the
@@ -942,7 +942,7 @@ static int worker_range(antdt_ctx* c, int k0, int k1, float* loss_out, hipStream
       g.C = c->dx + s0 * c->FD; g.ldc = c->FD; g.N = c->FD;
       g.epi = EPI_PLAIN; g.bf16_out = 0;
       if (loss_out) {
-        g.loss = c->loss_job;
+        g.loss = c->loss_job + k0;
         g.loss_blocks = k1 - k0;
       }
     }

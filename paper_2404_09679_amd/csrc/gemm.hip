@@ -45,7 +45,7 @@ __global__ __launch_bounds__(64 * WR * WC * WK) void gemm_bf16_kernel(GemmArgs p
   int pid = blockIdx.x;
   const int nblk = gridDim.x - p.loss_blocks;
   if (pid >= nblk) {
-    add_up_losses(p.loss, pid - nblk);
+    add_up_losses(p.loss + (pid - nblk));
     return;
   }
   if ((nblk & 7) == 0) pid = (pid & 7) * (nblk >> 3) + (pid >> 3);
@@ -419,7 +419,7 @@ template <int TM, int TN, int D, bool BKC, bool VA, bool VB>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs p, int tiles_n, int tiles) {
   const int nblk = gridDim.x - p.loss_blocks;
   if ((int)blockIdx.x >= nblk) {
-    add_up_losses(p.loss, blockIdx.x - nblk);
+    add_up_losses(p.loss + (blockIdx.x - nblk));
     return;
   }
   const int lane = threadIdx.x & 63;

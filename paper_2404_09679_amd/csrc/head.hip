@@ -117,16 +117,15 @@ __global__ __launch_bounds__(256) void head_tile_kernel(HeadArgs a, ShardTab tab
     part_out[a.width] = (sums[0][0] + sums[1][0]) + (sums[2][0] + sums[3][0]);
     part_out[a.width + 1] = (sums[0][1] + sums[1][1]) + (sums[2][1] + sums[3][1]);
   }
-  if (blockIdx.x == 0) {
-    if (threadIdx.x <= ANTDT_MAX_SHARDS) a.job->base[threadIdx.x] = ht.base[threadIdx.x];
-    if (threadIdx.x < ANTDT_MAX_SHARDS) a.job->len[threadIdx.x] = tab.len[threadIdx.x];
-    if (threadIdx.x == 0) {
-      a.job->part = a.part;
-      a.job->ldpart = a.ldpart;
-      a.job->width = a.width;
-      a.job->loss_out = a.loss_out;
-      a.job->first = a.k_begin;
-    }
+  if (blockIdx.x == 0 && (int)threadIdx.x < a.k_end - a.k_begin) {
+    const int q = a.k_begin + threadIdx.x;
+    LossJob j;
+    j.sums = a.part + (int64_t)ht.base[q] * a.ldpart + a.width + 1;
+    j.loss_out = a.loss_out ? a.loss_out + threadIdx.x : nullptr;
+    j.ldpart = a.ldpart;
+    j.tiles = ht.base[q + 1] - ht.base[q];
+    j.len = tab.len[q];
+    a.job[q] = j;
   }
 }
 
@@ -136,7 +135,7 @@ __global__ __launch_bounds__(64) void head_no_samples_kernel(HeadArgs a) {
     if (a.loss_out) a.loss_out[k - a.k_begin] = 0.0f;
 }
 
-__global__ __launch_bounds__(64) void losses_kernel(const LossJob* job) { add_up_losses(job, blockIdx.x); }
+__global__ __launch_bounds__(64) void losses_kernel(const LossJob* job) { add_up_losses(job + blockIdx.x); }
 
 }  // namespace
 

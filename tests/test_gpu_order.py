@@ -69,3 +69,34 @@ def test_replays_of_a_captured_iteration(cfg, streams):
             step(ref)
             step(run)
             assert_same(weights(run), weights(ref), "iteration between the replays")
+
+
+def on_streams_of_their_own(run, delayed=()):
+    """One worker_step per shard, each on its own stream behind everything enqueued so far (`delayed`: these
+    start late); the current stream continues behind all of them."""
+    main = torch.cuda.current_stream()
+    ready = torch.cuda.Event()
+    ready.record(main)
+    for k in range(len(run.cfg.shard_sizes)):
+        s = torch.cuda.Stream()
+        s.wait_event(ready)
+        with torch.cuda.stream(s):
+            if k in delayed:
+                torch.cuda._sleep(4_000_000)   # about two milliseconds
+            run.ctx.worker_step(k, run.loss[k:k + 1])
+        main.wait_stream(s)
+
+
+@pytest.mark.parametrize("cfg", [wl.scaled(SMALL_BF, name="order-f32", gemm_dtype="f32"), SMALL_BF,
+                                 wl.scaled(SMALL_BF, name="order-one-layer", layer_sizes=(173, 1))], ids=lambda c: c.name)
+def test_losses_of_worker_steps_on_different_streams(cfg):
+    """What a step leaves for the launch that adds up its losses is not overwritten by another worker's step."""
+    ref, run = start(cfg), start(cfg)
+    for k in range(len(cfg.shard_sizes)):
+        ref.ctx.worker_step(k, ref.loss[k:k + 1])
+    torch.cuda.synchronize()
+    for _ in range(8):
+        run.loss.fill_(-1.0)
+        on_streams_of_their_own(run)
+        torch.cuda.synchronize()
+        assert torch.equal(run.loss, ref.loss)
