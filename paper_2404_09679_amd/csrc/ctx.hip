@@ -154,6 +154,7 @@ struct antdt_ctx {
   bool shard_grads_done = false;         // the per-shard dense gradients of this worker step are (being) written
   bool captured = false;                 // a stream capture has recorded calls of this binding (see note_capture)
   bool operands_captured = false;        // ev_dh[0] was last recorded into a capture
+  hipStream_t operands_stream = nullptr; // the stream it was last recorded on (only compared)
   int sorted_buf = 0;
   // side stream on which the coalescing structure of a batch is built while the MLP runs
   hipStream_t side = nullptr;
@@ -923,7 +924,17 @@ static int worker_range(antdt_ctx* c, int k0, int k1, float* loss_out, hipStream
   c->shard_grads_done = false;
   // The event behind the last operand of the weight gradients (with up to one hidden layer the loss kernel
   // writes it, else the data gradient of layer 1).
-  c->operands_captured = note_capture(c, s);
+  const bool capturing = note_capture(c, s);
+  if (deferred) {
+    // Steps of other shards since the last update on another stream: the library's stream waits for their operands before
+    // the event stands for this step's (in a capture on one stream the caller's own order is all there is).
+    bool others = false;
+    for (int k = 0; k < tab.K; ++k) others = others || c->stepped[k];
+    if (others && c->operands_stream != s && c->operands_captured == capturing && !(capturing && !wgrad_stream(c)))
+      HIP_TRY(c, hipStreamWaitEvent(c->wside, c->ev_dh[0], 0));
+    c->operands_stream = s;
+  }
+  c->operands_captured = capturing;
   if (deferred && L <= 2) HIP_TRY(c, hipEventRecord(c->ev_dh[0], s));
   ProfScope bwd_scope(L > 1 ? pr : nullptr, KID_GEMM_BWD, s);
   bwd_scope.launches(L - 1);

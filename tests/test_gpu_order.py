@@ -100,3 +100,22 @@ def test_losses_of_worker_steps_on_different_streams(cfg):
         on_streams_of_their_own(run)
         torch.cuda.synchronize()
         assert torch.equal(run.loss, ref.loss)
+
+
+@pytest.mark.parametrize("view", [False, True], ids=["update", "view"])
+@pytest.mark.parametrize("cfg", [SMALL_BF, WIDE_BF], ids=lambda c: c.name)
+def test_update_waits_for_worker_steps_on_different_streams(cfg, view):
+    """The weight gradients are formed behind all workers' steps, not only behind the one enqueued last."""
+    ref, run = start(cfg), start(cfg)
+    for _ in range(2):
+        for k in range(len(cfg.shard_sizes)):
+            ref.ctx.worker_step(k, ref.loss[k:k + 1])
+        on_streams_of_their_own(run, delayed=(0, 1))
+        if view:
+            a, b = run.ctx.view_shard_grads(0)[0], ref.ctx.view_shard_grads(0)[0]
+            torch.cuda.synchronize()
+            assert torch.equal(a, b)
+        for r in (ref, run):
+            r.ctx.aggregate()
+            r.ctx.apply_update()
+        assert_same(weights(run), weights(ref), "update")
