@@ -428,7 +428,8 @@ int antdt_view_pooled(antdt_ctx* ctx, int32_t k, const void** x, int64_t* rows, 
                       int32_t* dtype);
 /* Shard k's dense gradient (fp32, flat layout) and d loss_k / d pooled (fp32 [B_k, ld_dx]).
  * Waits (on the host) for the library's own stream if the weight gradients are written there; the
- * caller still synchronises the stream it passed to antdt_worker_step before reading. */
+ * caller still synchronises the stream it passed to antdt_worker_step before reading.  Valid until the
+ * next worker step of shard k, a new split or a new binding; antdt_apply_update leaves them as they are. */
 int antdt_view_shard_grads(antdt_ctx* ctx, int32_t k, const float** dense, const float** dx,
                            int64_t* ld_dx);
 /* Aggregated dense gradient (fp32, flat layout), written out on this request (apply_update

@@ -152,6 +152,7 @@ struct antdt_ctx {
   bool batched = false;                  // the last worker step covered all shards
   bool wgrad_deferred = false;           // this worker step left the weight gradients to apply_update / the views
   bool shard_grads_done = false;         // the per-shard dense gradients of this worker step are (being) written
+  bool grads_viewed[ANTDT_MAX_SHARDS] = {};  // a view handed out the shard's gradients of its last worker step
   bool captured = false;                 // a stream capture has recorded calls of this binding (see note_capture)
   bool operands_captured = false;        // ev_dh[0] was last recorded into a capture
   hipStream_t operands_stream = nullptr; // the stream it was last recorded on (only compared)
@@ -445,6 +446,7 @@ int antdt_bind(antdt_ctx* c, void* tables, float* table_state, float* mlp_params
   c->pstate = mlp_state;
   carve(c, (char*)workspace);
   c->captured = false;
+  memset(c->grads_viewed, 0, sizeof(c->grads_viewed));
   if (!c->side) {
     HIP_TRY(c, hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking));
     HIP_TRY(c, hipEventCreateWithFlags(&c->ev_fork, SYNC_EVENT_FLAGS));
@@ -511,6 +513,7 @@ int antdt_bind_static(antdt_ctx* c, void* tables, float* table_state, float* mlp
   c->pstate = mlp_state;
   carve(c, (char*)base);
   c->captured = false;
+  memset(c->grads_viewed, 0, sizeof(c->grads_viewed));
   c->stage = ST_BOUND;
   c->have_shards = false;
   return init_workspace(c, (hipStream_t)stream);
@@ -639,6 +642,7 @@ int antdt_assign_shard(antdt_ctx* c, int64_t B, int32_t K, const int64_t* sizes,
   c->presorted = false;
   c->shard_B = B;
   memset(c->stepped, 0, sizeof(c->stepped));
+  memset(c->grads_viewed, 0, sizeof(c->grads_viewed));
   if (c->stage == ST_AGGREGATED) c->stage = ST_BATCH;
   return ANTDT_OK;
 }
@@ -965,7 +969,10 @@ static int worker_range(antdt_ctx* c, int k0, int k1, float* loss_out, hipStream
     const int rc = shard_weight_gradients(c, k0, k1, s);
     if (rc) return rc;
   }
-  for (int k = k0; k < k1; ++k) c->stepped[k] = true;
+  for (int k = k0; k < k1; ++k) {
+    c->stepped[k] = true;
+    c->grads_viewed[k] = false;
+  }
   if (c->stage == ST_AGGREGATED) c->stage = ST_BATCH;
   return ANTDT_OK;
 }
@@ -1132,7 +1139,9 @@ int antdt_apply_update(antdt_ctx* c, void* stream) {
       }
     }
     KSegments pieces;
-    if (!c->shard_grads_done && cut_ranges(c, seg, pieces) > 0) {   // (a view's gradients stay where they are)
+    bool free_rows = !c->shard_grads_done;   // (gradients that a view handed out stay where they are)
+    for (int k = 0; k < c->tab.K; ++k) free_rows = free_rows && !c->grads_viewed[k];
+    if (free_rows && cut_ranges(c, seg, pieces) > 0) {
       {
         ProfScope ps(pr, KID_GEMM_WGRAD, ds);
         HIP_TRY(c, launch_wgrad(u, pieces, true, ds));
@@ -1235,6 +1244,7 @@ int antdt_view_shard_grads(antdt_ctx* c, int32_t k, const float** dense, const f
     HIP_TRY(c, hipStreamSynchronize(c->wside));
     c->wgrad_pending = false;
   }
+  c->grads_viewed[k] = true;
   *dense = c->shard_grads + (int64_t)k * c->Pstride;
   *dx = c->dx + (int64_t)c->tab.start[k] * c->FD;
   *ld_dx = c->FD;

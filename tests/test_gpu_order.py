@@ -119,3 +119,24 @@ def test_update_waits_for_worker_steps_on_different_streams(cfg, view):
             r.ctx.aggregate()
             r.ctx.apply_update()
         assert_same(weights(run), weights(ref), "update")
+
+
+# enough samples per shard that the update forms the weight gradients in pieces, in the per-shard gradient buffer
+PIECES = wl.RankingConfig("order-pieces", 3, 2000, 16, "f32", "elementwise", 5, (53, 1288, 1032, 1), "bf16", 3, 1.1,
+                          (1500, 2700, 1100, 3700), wl.SEED0 + 810)
+
+
+def test_viewed_gradients_stay_through_the_update():
+    """A shard's gradients viewed before the other workers' steps are the same after the update, which has to
+    form all weight gradients itself then."""
+    run = start(PIECES)
+    run.ctx.worker_step(0, run.loss[:1])
+    dense, dx = run.ctx.view_shard_grads(0)
+    torch.cuda.synchronize()
+    before = dense.clone(), dx.clone()
+    for k in range(1, 4):
+        run.ctx.worker_step(k, run.loss[k:k + 1])
+    run.ctx.aggregate()
+    run.ctx.apply_update()
+    torch.cuda.synchronize()
+    assert torch.equal(dense, before[0]) and torch.equal(dx, before[1])
