@@ -238,7 +238,8 @@ int antdt_apply_update(antdt_ctx* ctx, void* stream);
  * on request.  With on != 0 every antdt_worker_step computes its shards' weight gradients itself,
  * as K separate workers would before pushing them (Section II), and antdt_apply_update
  * aggregates what they wrote; the results agree to rounding.  Takes effect at the next
- * antdt_worker_step.  Host only.
+ * antdt_worker_step; while the step of another shard of the same iteration has left its weight gradients to
+ * antdt_apply_update, the following ones do so too.  Host only.
  */
 int antdt_set_eager_weight_gradients(antdt_ctx* ctx, int32_t on);
 

@@ -923,7 +923,10 @@ static int worker_range(antdt_ctx* c, int k0, int k1, float* loss_out, hipStream
   // complete; the per-shard gradients of the contract are computed when a view asks for them.  Otherwise
   // (fp32 models: they are small) one launch behind the chain: beside the input gradient on another stream it would
   // hide less than the hop costs (one worker's step on 64 / 1531 samples: 87 / 109 us that way, 54 / 78 here).
-  const bool deferred = c->act_bf16 && c->wside && !c->static_bound && !c->eager_wgrad;
+  bool defer = !c->eager_wgrad;
+  for (int k = 0; k < tab.K; ++k)   // (also when another shard's step of this iteration did: apply_update goes one way for all)
+    defer = defer || ((k < k0 || k >= k1) && c->stepped[k] && c->wgrad_deferred);
+  const bool deferred = defer && c->act_bf16 && c->wside && !c->static_bound;
   c->wgrad_deferred = deferred;
   c->shard_grads_done = false;
   // The event behind the last operand of the weight gradients (with up to one hidden layer the loss kernel

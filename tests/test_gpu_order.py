@@ -140,3 +140,21 @@ def test_viewed_gradients_stay_through_the_update():
     run.ctx.apply_update()
     torch.cuda.synchronize()
     assert torch.equal(dense, before[0]) and torch.equal(dx, before[1])
+
+
+@pytest.mark.parametrize("first,then", [(False, True), (True, False)], ids=["deferred-then-eager", "eager-then-deferred"])
+def test_weight_gradient_option_changed_between_worker_steps(first, then):
+    """Whichever steps left their weight gradients to the update, all of them are in it, and in the views."""
+    ref, run = start(SMALL_BF), start(SMALL_BF)
+    for k in range(4):
+        ref.ctx.worker_step(k, ref.loss[k:k + 1])
+        run.ctx.set_eager_weight_gradients(first if k < 2 else then)
+        run.ctx.worker_step(k, run.loss[k:k + 1])
+    for r in (ref, run):
+        r.ctx.aggregate()
+        r.ctx.apply_update()
+    assert_same(weights(run), weights(ref), "update")
+    for k in (0, 1, 3):
+        a, b = run.ctx.view_shard_grads(k)[0], ref.ctx.view_shard_grads(k)[0]
+        torch.cuda.synchronize()
+        assert torch.equal(a, b), f"shard {k}"
