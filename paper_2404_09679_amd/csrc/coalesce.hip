@@ -681,6 +681,9 @@ template <typename TT, bool ROWWISE> struct TableRow {
   }
 };
 
+// Slot of a field's first window (see window_slots).
+__device__ __forceinline__ int64_t window_slot(int64_t field_start) { return field_start >> 7; }
+
 // Run u of field f that starts at absolute position `pos` of the sorted lookups (run table present).
 __device__ __forceinline__ int64_t run_index(const SegArgs& a, int f, int pos) {
   int lo = a.ubase[f], hi = a.ubase[f + 1] - 1;
@@ -721,15 +724,12 @@ __global__ __launch_bounds__(256) void seg_window_kernel(SegArgs a, FieldPtr fp,
   extern __shared__ __attribute__((aligned(16))) float piece_sum[];   // [2 W / LONG_RUN][D]: 2 j: starts at LONG_RUN j inside its run, 2 j + 1: at the run's head
   int f, t, part;
   if (!tile_of_block(tb, a.F, PARTS, f, t, part)) return;
-  const int win = (tb.t[f] + t) * PARTS + part;
   const int64_t base = fp.p[f];
   const int nnz = (int)(fp.p[f + 1] - base);
   const int P = t * SORT_TILE + part * W;
   const int tid = threadIdx.x;
-  if (P >= nnz) {
-    if (tid == 0) a.goes_out[win] = 0;
-    return;
-  }
+  if (P >= nnz) return;
+  const int64_t slot = window_slot(base) + t * PARTS + part;
   for (int i = tid; i < W + 2 * LONG_RUN; i += 256) key_[i] = a.key[base + min(max(P + i - LONG_RUN, 0), nnz - 1)];
   const int32_t* off = MEAN ? a.offsets + (int64_t)f * (a.B + 1) : nullptr;
   for (int i = tid; i < W + LONG_RUN; i += 256) {
@@ -847,12 +847,12 @@ __global__ __launch_bounds__(256) void seg_window_kernel(SegArgs a, FieldPtr fp,
     if (l > 0 && !out) {
       finish(row, sum, tr, q0);
     } else {
-      store_floats(a.partial + ((int64_t)win * 2 + (l > 0 ? 1 : 0)) * a.D + c * 4, sum);
+      store_floats(a.partial + (slot * 2 + (l > 0 ? 1 : 0)) * a.D + c * 4, sum);   // (a run over two windows: the field has slots)
       if (l > 0) goes_out = 1;
     }
   }
   __syncthreads();
-  if (tid == 0) a.goes_out[win] = goes_out;
+  if (tid == 0 && nnz > W) a.goes_out[slot] = goes_out;
 }
 
 // Runs that leave the window they start in, one wavefront each: the sum of the first window's part, then those
@@ -861,13 +861,16 @@ template <typename TT, bool ROWWISE, bool UPDATE>
 __global__ __launch_bounds__(256) void seg_finish_kernel(SegArgs a, FieldPtr fp, TileBase tb, int W) {
   const int parts = SORT_TILE / W;
   const int win = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (win >= a.total_tiles * parts || !a.goes_out[win]) return;
+  if (win >= a.total_tiles * parts) return;
   int f, t;
   field_of_tile(tb, win / parts, f, t);
   const int64_t base = fp.p[f];
   const int nnz = (int)(fp.p[f + 1] - base);
-  const int lane = threadIdx.x & 63;
   const int next = t * SORT_TILE + (win % parts + 1) * W;   // where the following window starts
+  if (next >= nnz) return;
+  const int64_t slot = window_slot(base) + t * parts + win % parts;
+  if (!a.goes_out[slot]) return;
+  const int lane = threadIdx.x & 63;
   const int32_t k = a.key[base + next - 1];
   int n = 0;   // following windows that start inside the run
   for (;;) {
@@ -886,7 +889,7 @@ __global__ __launch_bounds__(256) void seg_finish_kernel(SegArgs a, FieldPtr fp,
   TableRow<TT, ROWWISE> tr;
   if (UPDATE) tr.load(a, row, c);
   RowSum sum = {};
-  const float* part = a.partial + (int64_t)win * 2 * a.D + c * 4;
+  const float* part = a.partial + slot * 2 * a.D + c * 4;
   if (g == 0) add_floats(sum, part + a.D);
 #pragma unroll 4
   for (int i = 1 + g; i <= n; i += ngroups) add_floats(sum, part + (int64_t)i * 2 * a.D);

@@ -182,6 +182,7 @@ struct WgradArgs {
   int32_t tiles_n[ANTDT_MAX_LAYERS];
   // last layer (one output): the loss kernel's sums over its tiles of samples
   const float* part;                   // [tiles, ldpart] sum of dz * h per column; column `width`: sum of dz
+  const float* dz;                     // fp32 models without a hidden layer: [samples] instead of those sums, or NULL
   int64_t ldpart, last_off;            // offset of the last layer in the flat parameters (bias behind the weights)
   int32_t width;
   float* p;
@@ -213,6 +214,8 @@ struct HeadArgs {
   // the sums over the samples are formed along the way, per tile of samples of one shard
   float* part;          // [tiles, ldpart] sum of dz * h per column; column `width`: sum of dz, `width` + 1: of the losses
   int64_t ldpart;
+  float* dz;            // [B] d(mean shard loss)/d logit of every sample, and [B] its loss, instead of those sums (or NULL)
+  float* loss_s;
   struct LossJob* job;  // [K] those of the range's shards are written by the first block, for the launch that adds up the losses
   float* loss_out;      // caller's buffer or NULL; element (k - k_begin)
 };
@@ -270,6 +273,11 @@ struct SortBuffers {
 hipError_t launch_sort(const SortPlan& pl, const SortBuffers& sb, const FieldPtr& fp, const TileBase& tb, const ShardTab& tab,
                        Profiler* prof, hipStream_t s, int* sorted_buf);
 
+// Slots of the windows: window i of a field that starts at lookup p has slot p / 128 + i.  A field of n > 256 lookups has
+// ceil(n / 256) <= floor(n / 128) windows at most, so no two fields' windows meet and none lies past the last
+// lookup's; a field in one window needs no slot (and has none).
+inline int64_t window_slots(int64_t lookups) { return lookups >> 7; }
+
 struct SegArgs {
   const int32_t* key;              // sorted row ids, field-major at fp.p[f]
   const int32_t* pay;              // sample index of each sorted lookup
@@ -282,8 +290,8 @@ struct SegArgs {
   float* G;                        // [U, D] coalesced gradient (written when not updating)
   const float* sample_w;           // [B]
   int32_t window;                  // sorted lookups per block of the reduction: 256 or 512
-  int32_t* goes_out;               // [windows] the last run of the window starts there, is long and goes on in the next one
-  float* partial;                  // [windows, 2, D] sums over the window: of the run that comes in, of the run that goes out
+  int32_t* goes_out;               // [slots] the last run of the window starts there, is long and goes on in the next one
+  float* partial;                  // [slots, 2, D] sums over the window: of the run that comes in, of the run that goes out
   const float* dx;                 // [B, lddx]
   int64_t lddx;
   const int32_t* offsets;          // [F][B + 1] bag boundaries of the batch (read when mean_pool)

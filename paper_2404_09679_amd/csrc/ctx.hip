@@ -115,6 +115,7 @@ struct antdt_ctx {
                                          // copy there while the input-gradient product may still read the old one
   float* head_part = nullptr;            // loss kernel's sums per tile of samples [tiles, ldpart]
   int64_t ldpart = 0;
+  bool sums_per_sample = false;          // head_part: d loss / d logit [max_batch], losses [max_batch] (see carve)
   LossJob* loss_job = nullptr;           // [K] what it leaves to the launch that adds up the losses
   int32_t* lookup_sample = nullptr;
   int32_t *key[2] = {}, *pay[2] = {}, *tile_heads = nullptr, *ubase = nullptr, *uniq = nullptr;
@@ -238,12 +239,14 @@ static size_t carve(antdt_ctx* c, char* base) {
   c->x = take((size_t)Bm * c->ldx * c->act_size);
   for (int l = 1; l < c->L; ++l) {
     c->h[l] = take((size_t)Bm * c->width[l] * c->act_size);
-    c->dh[l] = take((size_t)Bm * c->width[l] * c->act_size);
+    // (the loss kernel is the last to read the last activation, and leaves the gradient in its place: fp32 models need no
+    // more than before these sums existed; bf16 models keep both, a place of its own costs them nothing)
+    if (l == c->L - 1 && !c->act_bf16) c->dh[l] = c->h[l];
+    else c->dh[l] = take((size_t)Bm * c->width[l] * c->act_size);
   }
   c->sample_w = (float*)take(Bm * 4);
   c->dx = (float*)take((size_t)Bm * c->FD * 4);
   c->shard_grads = (float*)take((size_t)K * c->Pstride * 4);
-  c->g_dense = (float*)take((size_t)c->P * 4);
   if (c->act_bf16) {
     for (int l = 0; l + 1 < c->L; ++l) {
       const int64_t rows = l == 0 ? c->ldx : c->width[l];
@@ -251,8 +254,6 @@ static size_t carve(antdt_ctx* c, char* base) {
       if (l == 0) c->wb0_alt = (bf16_t*)take((size_t)rows * c->width[l + 1] * 2);
     }
   }
-  c->head_part = (float*)take((size_t)(Bm / HEAD_TILE + K) * c->ldpart * 4);
-  c->loss_job = (LossJob*)take((size_t)K * sizeof(LossJob));
   c->lookup_sample = (int32_t*)take((size_t)N * 4);
   for (int i = 0; i < 2; ++i) {
     c->key[i] = (int32_t*)take((size_t)N * 4);
@@ -260,19 +261,33 @@ static size_t carve(antdt_ctx* c, char* base) {
   }
   c->hist = (uint32_t*)take((size_t)(c->max_tiles_total << c->radix_bits) * 4);
   c->digit_base = (uint32_t*)take((size_t)(m.num_fields << c->radix_bits) * 4);
+  c->cbase = (int64_t*)take((size_t)(ANTDT_MAX_FIELDS + 1) * 8);
+  c->vflags = (int32_t*)take(8);
+  // The loss kernel's sums and jobs.  Of an fp32 model without a hidden layer they share memory with what only an
+  // aggregation and what follows it use: the worker step itself reads them last (in bf16 models apply_update does).
+  // Where that is too small for sums over tiles (few lookups, many dense features), they are kept per sample instead, and
+  // the last layer's gradient is added up from the samples.
+  const size_t tiles = (size_t)std::min(Bm, Bm / HEAD_TILE + K);   // (every tile has a sample)
+  const size_t shared = off;
+  const bool share = !c->act_bf16 && c->L == 1;
+  c->loss_job = (LossJob*)take((size_t)K * sizeof(LossJob));
+  const size_t sums = off;
+  c->head_part = (float*)take(tiles * c->ldpart * 4);
+  size_t behind = off;
+  if (share) off = shared;
+  c->g_dense = (float*)take((size_t)c->P * 4);
   c->tile_heads = (int32_t*)take((size_t)(c->max_tiles_total + 1) * 4);
   c->ubase = (int32_t*)take((size_t)(m.num_fields + 1) * 4);
   c->uniq = (int32_t*)take((size_t)N * 4);
   c->segoff = (int32_t*)take((size_t)(N + m.num_fields + 1) * 4);
   c->pack_pay = (int32_t*)take((size_t)N * 4);
   c->segabs = (int32_t*)take((size_t)(N + 1) * 4);
-  c->cbase = (int64_t*)take((size_t)(ANTDT_MAX_FIELDS + 1) * 8);
-  c->vflags = (int32_t*)take(8);
-  const size_t windows = (size_t)c->max_tiles_total * (ANTDT_SORT_TILE / 256);
-  c->goes_out = (int32_t*)take(windows * 4);
-  c->partial = (float*)take(windows * 2 * m.dim * 4);
+  c->goes_out = (int32_t*)take((size_t)window_slots(N) * 4);
+  c->partial = (float*)take((size_t)window_slots(N) * 2 * m.dim * 4);
   c->G = (float*)take((size_t)N * m.dim * 4);
-  return off;
+  c->sums_per_sample = share && behind > off;
+  if (c->sums_per_sample) behind = align_up(sums + (size_t)Bm * 8, 256);
+  return std::max(off, behind);
 }
 
 // ----------------------------------------------------------------------------------------
@@ -359,7 +374,7 @@ int antdt_create(const antdt_model* model, antdt_ctx** out) {
   c->ldx = (c->in0 + 7) / 8 * 8;
   c->act_bf16 = m.gemm_dtype == ANTDT_BF16;
   c->act_size = c->act_bf16 ? 2 : 4;
-  c->ldpart = (m.layer_sizes[c->L - 1] + 2 + 3) / 4 * 4;
+  c->ldpart = (int64_t)m.layer_sizes[c->L - 1] + 2;
   int64_t off = 0;
   for (int l = 0; l <= c->L; ++l) c->width[l] = m.layer_sizes[l];
   for (int l = 0; l < c->L; ++l) {
@@ -704,7 +719,11 @@ static void fill_wgrad_args(antdt_ctx* c, WgradArgs& u) {
     u.M[l] = c->width[l]; u.N[l] = c->width[l + 1];
     u.w_off[l] = c->w_off[l]; u.wb[l] = c->wb[l];
   }
-  u.part = c->head_part; u.ldpart = c->ldpart; u.width = c->width[c->L - 1]; u.last_off = c->w_off[c->L - 1];
+  u.part = c->head_part; u.ldpart = c->ldpart;
+  if (c->sums_per_sample) {
+    u.dz = c->head_part; u.A[0] = c->x; u.lda[0] = c->ldx;
+  }
+  u.width = c->width[c->L - 1]; u.last_off = c->w_off[c->L - 1];
   u.p = c->params; u.state = c->pstate; u.lr = c->m.lr; u.eps = c->m.eps;
   u.grads = c->shard_grads; u.stride = c->Pstride;
 }
@@ -911,7 +930,11 @@ static int worker_range(antdt_ctx* c, int k0, int k1, float* loss_out, hipStream
       a.dh = c->dx; a.lddh = c->FD; a.dh_cols = c->FD; a.relu = 0; a.bf16_dh = 0;
     }
     a.k_begin = k0; a.k_end = k1;
-    a.part = c->head_part; a.ldpart = c->ldpart; a.job = c->loss_job; a.loss_out = loss_out;
+    a.part = c->head_part; a.ldpart = c->ldpart;
+    if (c->sums_per_sample) {
+      a.dz = c->head_part; a.loss_s = c->head_part + m.max_batch;
+    }
+    a.job = c->loss_job; a.loss_out = loss_out;
     ProfScope ps(pr, KID_HEAD, s);
     HIP_TRY(c, launch_head_tiles(a, tab, s));
     if (L == 1 && loss_out && ns > 0) HIP_TRY(c, launch_losses(c->loss_job + k0, k1 - k0, s));   // (else beside the input gradient)

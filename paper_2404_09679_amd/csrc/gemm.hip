@@ -206,6 +206,22 @@ __device__ __forceinline__ void last_layer(const WgradArgs& u, const KSegments& 
   }
 }
 
+// The same of an fp32 model without a hidden layer whose loss kernel left dz per sample: from the samples.
+__device__ __forceinline__ void last_layer_from_samples(const WgradArgs& u, const float* x, int64_t ldx, int ks, int ke, int block,
+                                                        float (*red)[64]) {
+  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
+  const int j = block * 64 + tx;
+  float sum = 0.0f;
+  if (j <= u.width) {
+#pragma unroll 8
+    for (int s = ks + ty; s < ke; s += 4) sum = fmaf(j < u.width ? x[s * ldx + j] : 1.0f, u.dz[s], sum);
+  }
+  red[ty][tx] = sum;
+  __syncthreads();
+  if (j <= u.width && ty == 0)
+    u.grads[(int64_t)(u.k0 + blockIdx.y) * u.stride + u.last_off + j] = (red[0][tx] + red[1][tx]) + (red[2][tx] + red[3][tx]);
+}
+
 template <int TM, int TN, int WR, int WC, int BK, int STAGES, WgradMode MODE>
 __global__ __launch_bounds__(64 * WR * WC) void wgrad_kernel(WgradArgs u, KSegments seg) {
   typedef BlockProduct<TM, TN, WR, WC, 1, BK, STAGES, true, true> P;
@@ -457,7 +473,10 @@ __global__ __launch_bounds__(256) void wgrad_f32_kernel(WgradArgs u, KSegments s
   constexpr int BM = 16 * TM, BN = 16 * TN, PITCH = BN + 4;
   __shared__ __attribute__((aligned(16))) float red[4][(BM + 1) * PITCH];   // row BM: the bias gradient
   if ((int)blockIdx.x >= u.tile_base[u.n_layers]) {
-    last_layer<WGRAD_STORE>(u, seg, blockIdx.x - u.tile_base[u.n_layers], reinterpret_cast<float(*)[64]>(&red[0][0]));
+    const int block = blockIdx.x - u.tile_base[u.n_layers], q = blockIdx.y;
+    float(*r)[64] = reinterpret_cast<float(*)[64]>(&red[0][0]);
+    if (u.dz) last_layer_from_samples(u, reinterpret_cast<const float*>(u.A[0]), u.lda[0], seg.ks[q], seg.ke[q], block, r);
+    else last_layer<WGRAD_STORE>(u, seg, block, r);
     return;
   }
   int li = 0;

@@ -33,10 +33,14 @@ __global__ __launch_bounds__(256) void head_tile_kernel(HeadArgs a, ShardTab tab
   const int count = min(tab.len[k] - t0, HEAD_TILE);         // samples of the tile (at least one)
   const int rows = min(max(count - wave * SPW, 0), SPW);     // samples of this wavefront
   const int64_t s0 = (int64_t)tab.start[k] + t0;
-  int64_t row[SPW];                                          // (clamped into the tile)
+  // (fp32: dh may lie in h's place, so a wavefront reads its own samples only, or the weights if it has none)
+  int64_t row[SPW];
+  const TH* h[SPW];
 #pragma unroll
-  for (int r = 0; r < SPW; ++r) row[r] = s0 + min(wave * SPW + r, count - 1);
-  const TH* h = reinterpret_cast<const TH*>(a.h);
+  for (int r = 0; r < SPW; ++r) {
+    row[r] = s0 + min(wave * SPW + min(r, max(rows - 1, 0)), count - 1);
+    h[r] = sizeof(TH) == 4 && rows == 0 ? reinterpret_cast<const TH*>(a.w) : reinterpret_cast<const TH*>(a.h) + row[r] * a.ldh;
+  }
   const float label = a.labels[s0 + min(wave * SPW + min(lane, SPW - 1), count - 1)];   // lanes 0 .. SPW-1: one sample each
   const float bias = a.b[0];
 
@@ -52,7 +56,7 @@ __global__ __launch_bounds__(256) void head_tile_kernel(HeadArgs a, ShardTab tab
         const int j = j0 + i * 64 + lane, jc = min(j, a.width - 1);
         w[i] = a.w[jc];
 #pragma unroll
-        for (int r = 0; r < SPW; ++r) hv[r][i] = to_f32(h[row[r] * a.ldh + jc]);
+        for (int r = 0; r < SPW; ++r) hv[r][i] = to_f32(h[r][jc]);
         if (j >= a.width) {
           w[i] = 0.0f;
 #pragma unroll
@@ -92,6 +96,10 @@ __global__ __launch_bounds__(256) void head_tile_kernel(HeadArgs a, ShardTab tab
     sums[wave][0] = sdz;
     sums[wave][1] = sl;
   }
+  if (a.dz && on) {   // (lane r < rows: the wavefront's sample r)
+    a.dz[s0 + wave * SPW + lane] = dz_lane;
+    a.loss_s[s0 + wave * SPW + lane] = loss_lane;
+  }
   float* part_out = a.part + (int64_t)tile * a.ldpart;
   for (int j0 = 0; j0 < a.width; j0 += CHUNK) {   // (dh_cols <= width)
     if (a.width > CHUNK) load(j0);
@@ -108,22 +116,23 @@ __global__ __launch_bounds__(256) void head_tile_kernel(HeadArgs a, ShardTab tab
         }
       if (j0 + i * 64 < a.width) col[wave][i * 64 + lane] = g;
     }
+    if (a.dz) continue;
     __syncthreads();
     for (int q = threadIdx.x; q < CHUNK && j0 + q < a.width; q += 256)
       part_out[j0 + q] = (col[0][q] + col[1][q]) + (col[2][q] + col[3][q]);
     __syncthreads();
   }
-  if (threadIdx.x == 0) {
+  if (threadIdx.x == 0 && !a.dz) {
     part_out[a.width] = (sums[0][0] + sums[1][0]) + (sums[2][0] + sums[3][0]);
     part_out[a.width + 1] = (sums[0][1] + sums[1][1]) + (sums[2][1] + sums[3][1]);
   }
   if (blockIdx.x == 0 && (int)threadIdx.x < a.k_end - a.k_begin) {
     const int q = a.k_begin + threadIdx.x;
     LossJob j;
-    j.sums = a.part + (int64_t)ht.base[q] * a.ldpart + a.width + 1;
+    j.sums = a.dz ? a.loss_s + tab.start[q] : a.part + (int64_t)ht.base[q] * a.ldpart + a.width + 1;
     j.loss_out = a.loss_out ? a.loss_out + threadIdx.x : nullptr;
-    j.ldpart = a.ldpart;
-    j.tiles = ht.base[q + 1] - ht.base[q];
+    j.ldpart = a.dz ? 1 : a.ldpart;
+    j.tiles = a.dz ? tab.len[q] : ht.base[q + 1] - ht.base[q];
     j.len = tab.len[q];
     a.job[q] = j;
   }

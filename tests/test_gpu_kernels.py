@@ -107,3 +107,46 @@ def test_weight_gradient_pieces(sizes):
             assert np.linalg.norm(a - b) <= 2.0 ** -8 * np.linalg.norm(b), what
         else:
             assert_close(a, b, 1e-6, what, 1e-5)
+
+
+# Windows of fields that follow one another at any place: one window (no slot for partial sums), exactly one, one lookup
+# more, several; hot rows, so that runs cross the windows wherever there are several.
+@pytest.mark.parametrize("rows", [2, 40])
+def test_window_slots_of_neighbouring_fields(rows, monkeypatch):
+    sizes = [0, 1, 257, 128, 300, 255, 256, 513, 127, 512, 511, 129, 258, 2049, 3, 1025]
+    B, F = 100, len(sizes)
+    cfg = _config(f"slots-{rows}", 650 + rows, num_fields=F, rows_per_field=rows, dim=8, layer_sizes=(8,), gemm_dtype="f32",
+                  shard_sizes=(30, 0, 50, 20), max_bag=21, min_bag=0)
+    real = wl.make_batch
+
+    def planted(c, index=0):
+        b = real(c, index)
+        rng = np.random.default_rng(11 + rows)
+        offsets = np.zeros((F, B + 1), np.int32)
+        for f, n in enumerate(sizes):
+            offsets[f, 1:] = np.sort(rng.integers(0, n + 1, B))
+            offsets[f, -1] = n
+        ids = rng.integers(0, rows, sum(sizes)).astype(np.int32)
+        return dataclasses.replace(b, ids=ids, offsets=offsets, field_ptr=np.cumsum([0] + sizes).astype(np.int64))
+
+    monkeypatch.setattr(wl, "make_batch", planted)
+    check_iteration(cfg, cfg.shard_sizes, tol=TOL32, batched=True, nonzero_state=True)
+    check_iteration(cfg, cfg.shard_sizes, tol=TOL32, mask=(1, 1, 0, 1), nonzero_state=True)
+
+
+# No hidden layer: sums over tiles of samples, or per sample where those would need memory of their own (few lookups, many
+# dense features); shards of less, exactly and more than a tile
+@pytest.mark.parametrize("fields,num_dense,max_bag", [(3, 2, 5), (1, 700, 1)])
+def test_f32_model_without_hidden_layer(fields, num_dense, max_bag):
+    cfg = _config(f"no-hidden-{fields}", 660 + fields, num_fields=fields, rows_per_field=500, dim=4, num_dense=num_dense, layer_sizes=(),
+                  gemm_dtype="f32", shard_sizes=(16, 1, 0, 33, 200), max_bag=max_bag, min_bag=0)
+    check_iteration(cfg, cfg.shard_sizes, tol=TOL32, batched=True, nonzero_state=True)
+    check_iteration(cfg, cfg.shard_sizes, tol=TOL32, mask=(1, 1, 1, 0, 1), nonzero_state=True)
+
+
+# fp32 models: the gradient of the last hidden layer takes the activation's place; widths around the 512 columns that a
+# wavefront keeps at once
+@pytest.mark.parametrize("width", [1, 63, 512, 513, 1300])
+def test_f32_last_hidden_layer(width):
+    cfg = _config(f"last-hidden-{width}", 670, layer_sizes=(24, width), gemm_dtype="f32", shard_sizes=(16, 3, 0, 37))
+    check_iteration(cfg, cfg.shard_sizes, tol=TOL32, batched=True, nonzero_state=True)
