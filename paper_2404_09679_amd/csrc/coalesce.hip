@@ -684,7 +684,7 @@ template <typename TT, bool ROWWISE> struct TableRow {
 // Slot of a field's first window (see window_slots).
 __device__ __forceinline__ int64_t window_slot(int64_t field_start) { return field_start >> 7; }
 
-// Run u of field f that starts at absolute position `pos` of the sorted lookups (run table present).
+// First run of field f that starts at absolute position `pos` of the sorted lookups or behind it (run table present).
 __device__ __forceinline__ int64_t run_index(const SegArgs& a, int f, int pos) {
   int lo = a.ubase[f], hi = a.ubase[f + 1] - 1;
   while (lo < hi) {
@@ -721,6 +721,8 @@ __global__ __launch_bounds__(256) void seg_window_kernel(SegArgs a, FieldPtr fp,
   __shared__ int16_t lead[W / LONG_RUN + 1];        // pieces' runs: [0] the one that comes in, [1 + j] starts in the j-th LONG_RUN positions
   __shared__ int counts[ROUNDS][4];
   __shared__ int goes_out;
+  __shared__ uint64_t heads[UPDATE ? 1 : W / 64];   // (sums written out: the place of a run is the window's first one's + heads before)
+  __shared__ int64_t first_run;
   extern __shared__ __attribute__((aligned(16))) float piece_sum[];   // [2 W / LONG_RUN][D]: 2 j: starts at LONG_RUN j inside its run, 2 j + 1: at the run's head
   int f, t, part;
   if (!tile_of_block(tb, a.F, PARTS, f, t, part)) return;
@@ -741,7 +743,10 @@ __global__ __launch_bounds__(256) void seg_window_kernel(SegArgs a, FieldPtr fp,
     look[i] = l;
   }
   if (tid <= W / LONG_RUN) lead[tid] = -1;
-  if (tid == 0) goes_out = 0;
+  if (tid == 0) {
+    goes_out = 0;
+    if (!UPDATE) first_run = run_index(a, f, (int)base + P);
+  }
   __syncthreads();
   const int32_t* key = key_ + LONG_RUN;   // key[q]: position P + q
   auto same = [&](int q, int32_t k) { return P + q < nnz && key[q] == k; };   // (0 <= P + q)
@@ -764,6 +769,10 @@ __global__ __launch_bounds__(256) void seg_window_kernel(SegArgs a, FieldPtr fp,
                       : q | (head ? 512 : 0) | (!head || ahead ? 1024 : 0);
     const uint64_t mf = __ballot(few[r]), mo = __ballot(other[r]);
     if ((tid & 63) == 0) counts[r][tid >> 6] = __popcll(mf) | (__popcll(mo) << 16);
+    if (!UPDATE) {
+      const uint64_t mh = __ballot(head);
+      if ((tid & 63) == 0) heads[q >> 6] = mh;
+    }
   }
   __syncthreads();
   int sum_counts = 0;
@@ -790,8 +799,13 @@ __global__ __launch_bounds__(256) void seg_window_kernel(SegArgs a, FieldPtr fp,
   const char* dx = reinterpret_cast<const char*>(a.dx + f * a.D + c * 4);
   auto row_of = [&](int q) { return (int64_t)f * a.R + min(max(key[q], 0), (int)(a.R - 1)); };
   auto finish = [&](int64_t row, const RowSum& sum, const TableRow<TT, ROWWISE>& tr, int q) {
-    if (UPDATE) tr.update(a, row, c, lps, sum);
-    else store_floats(a.G + run_index(a, f, (int)base + P + q) * a.D + c * 4, sum);
+    if (UPDATE) {
+      tr.update(a, row, c, lps, sum);
+    } else {
+      int64_t u = first_run + __popcll(heads[q >> 6] & ((1ull << (q & 63)) - 1));
+      for (int i = 0; i < (q >> 6); ++i) u += __popcll(heads[i]);
+      store_floats(a.G + u * a.D + c * 4, sum);
+    }
   };
   // The long items first, so that the lane groups of a wavefront have items of about the same length; the next
   // item's row and accumulators are requested before the current one's lookups are waited for.
