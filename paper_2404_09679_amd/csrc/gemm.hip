@@ -343,8 +343,15 @@ __global__ __launch_bounds__(64 * WR * WC) void wgrad_kernel(WgradArgs u, KSegme
 // stay small; what neighbouring wavefronts share comes from the L1.
 // (Through LDS in 64 x 64 tiles, one step in flight: 1500 x 256 x 397 91 us, here 13; 1500 x 384 x 256 110 us, here 16.)
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));   // a 16-byte load takes any 4-byte-aligned address
 
-template <int T, bool KC, bool VEC>   // KC: contraction index contiguous; VEC: rows 16-byte aligned
+// How an operand whose contraction index is contiguous is loaded: slot by slot (fewer than 4 slots), 16 bytes at a time
+// from aligned rows (the last vector may reach into the row's padding), or from rows at any place.  845-1001-333
+// model, 4096 / 16384 samples, a step: slot by slot 942 / 3103 us, from any place 590 / 1954; 845-1024-512-256 with
+// 512 samples: aligned 201 us, as if at any place 207.
+enum F32Load { F32_SLOTS, F32_ALIGNED, F32_ANY };
+
+template <int T, bool KC, F32Load L>   // KC: contraction index contiguous
 struct F32Operand {
   const float* row[T];
   int64_t ld;
@@ -355,13 +362,17 @@ struct F32Operand {
       row[t] = KC ? x + (int64_t)r * ld : x + r;
     }
   }
-  // Slots past the end are read at the last slot (or the last whole vector) instead and cleared by `clip`.
+  // Slots past the end are read at the last slot (or the last whole vector, or the last four) instead; `clip` moves the ones
+  // that are inside to their places and clears the others.
   __device__ __forceinline__ void load(int step, int K, int lane, float (&f)[T][4]) const {
     const int k = step * 16 + 4 * (lane >> 4);
 #pragma unroll
     for (int t = 0; t < T; ++t) {
-      if (KC && VEC) {
+      if (KC && L == F32_ALIGNED) {
         const float4 v = *reinterpret_cast<const float4*>(row[t] + min(k, (K - 1) & ~3));
+        f[t][0] = v.x; f[t][1] = v.y; f[t][2] = v.z; f[t][3] = v.w;
+      } else if (KC && L == F32_ANY) {
+        const f32x4_any v = *reinterpret_cast<const f32x4_any*>(row[t] + min(k, K - 4));
         f[t][0] = v.x; f[t][1] = v.y; f[t][2] = v.z; f[t][3] = v.w;
       } else {
 #pragma unroll
@@ -372,9 +383,18 @@ struct F32Operand {
   static __device__ __forceinline__ void clip(int step, int K, int lane, float (&f)[T][4]) {
     const int k = step * 16 + 4 * (lane >> 4);
 #pragma unroll
-    for (int t = 0; t < T; ++t)
+    for (int t = 0; t < T; ++t) {
+      if (KC && L == F32_ANY) {
+        const int over = k - (K - 4);   // 1 .. 3: slots the vector was read ahead of its place
+        const bool by1 = over > 0 && (over & 1), by2 = over > 0 && (over & 2);
+        const float g0 = by1 ? f[t][1] : f[t][0], g1 = by1 ? f[t][2] : f[t][1], g2 = by1 ? f[t][3] : f[t][2];
+        f[t][0] = by2 ? g2 : g0;
+        f[t][1] = by2 ? f[t][3] : g1;
+        f[t][2] = g2;
+      }
 #pragma unroll
       for (int i = 0; i < 4; ++i) f[t][i] = k + i < K ? f[t][i] : 0.0f;
+    }
   }
 };
 
@@ -431,7 +451,7 @@ __device__ __forceinline__ void f32_product(const OA& oa, const OB& ob, int K, i
 
 // C[m, n] = sum_k A[m * lda + k] B(n, k) with the epilogue of GemmArgs; four wavefronts per block, each a tile of
 // its own (neighbours along n first: they share the rows of A).
-template <int TM, int TN, int D, bool BKC, bool VA, bool VB>
+template <int TM, int TN, int D, bool BKC, F32Load L>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs p, int tiles_n, int tiles) {
   const int nblk = gridDim.x - p.loss_blocks;
   if ((int)blockIdx.x >= nblk) {
@@ -442,8 +462,8 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs p, int tiles_n, 
   const int id = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (id >= tiles) return;
   const int m0 = id / tiles_n * (16 * TM), n0 = id % tiles_n * (16 * TN);
-  const F32Operand<TM, true, VA> oa(reinterpret_cast<const float*>(p.A), p.lda, m0, p.M, lane);
-  const F32Operand<TN, BKC, VB> ob(reinterpret_cast<const float*>(p.B), p.ldb, n0, p.N, lane);
+  const F32Operand<TM, true, L> oa(reinterpret_cast<const float*>(p.A), p.lda, m0, p.M, lane);
+  const F32Operand<TN, BKC, L> ob(reinterpret_cast<const float*>(p.B), p.ldb, n0, p.N, lane);
   f32x4 acc[TM][TN] = {}, none[TN];
   f32_product<TM, TN, D, 4, false>(oa, ob, p.K, 0, 1, lane, acc, none, false);
   float* C = reinterpret_cast<float*>(p.C);
@@ -489,8 +509,8 @@ __global__ __launch_bounds__(256) void wgrad_f32_kernel(WgradArgs u, KSegments s
   f32x4 acc[TM][TN] = {}, accb[TN] = {};
   const float* A = reinterpret_cast<const float*>(u.A[li]) + (int64_t)seg.ks[q] * u.lda[li];
   const float* B = reinterpret_cast<const float*>(u.B[li]) + (int64_t)seg.ks[q] * u.ldb[li];
-  const F32Operand<TM, false, false> oa(A, u.lda[li], m0, M, lane);
-  const F32Operand<TN, false, false> ob(B, u.ldb[li], n0, N, lane);
+  const F32Operand<TM, false, F32_SLOTS> oa(A, u.lda[li], m0, M, lane);
+  const F32Operand<TN, false, F32_SLOTS> ob(B, u.ldb[li], n0, N, lane);
   f32_product<TM, TN, D, 1, true>(oa, ob, seg.ke[q] - seg.ks[q], wave, 4, lane, acc, accb, ones);
   float* mine = red[wave];
 #pragma unroll
@@ -547,16 +567,12 @@ template <int TM, int TN, int D>
 hipError_t launch_f32_tile(const GemmArgs& a, hipStream_t s) {
   const int tiles_n = (a.N + 16 * TN - 1) / (16 * TN), tiles = (a.M + 16 * TM - 1) / (16 * TM) * tiles_n;
   const dim3 grid((tiles + 3) / 4 + a.loss_blocks), block(256);
-  const bool va = (a.lda & 3) == 0 && (reinterpret_cast<uintptr_t>(a.A) & 15) == 0;
-  const bool vb = a.b_kc && (a.ldb & 3) == 0 && (reinterpret_cast<uintptr_t>(a.B) & 15) == 0;
-  if (a.b_kc) {
-    if (va && vb) hipLaunchKernelGGL((gemm_f32_kernel<TM, TN, D, true, true, true>), grid, block, 0, s, a, tiles_n, tiles);
-    else if (va) hipLaunchKernelGGL((gemm_f32_kernel<TM, TN, D, true, true, false>), grid, block, 0, s, a, tiles_n, tiles);
-    else hipLaunchKernelGGL((gemm_f32_kernel<TM, TN, D, true, false, false>), grid, block, 0, s, a, tiles_n, tiles);
-  } else {
-    if (va) hipLaunchKernelGGL((gemm_f32_kernel<TM, TN, D, false, true, false>), grid, block, 0, s, a, tiles_n, tiles);
-    else hipLaunchKernelGGL((gemm_f32_kernel<TM, TN, D, false, false, false>), grid, block, 0, s, a, tiles_n, tiles);
-  }
+  auto aligned = [](const void* x, int64_t ld) { return (ld & 3) == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0; };
+  const F32Load load = aligned(a.A, a.lda) && (!a.b_kc || aligned(a.B, a.ldb)) ? F32_ALIGNED : a.K >= 4 ? F32_ANY : F32_SLOTS;
+  auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, s, a, tiles_n, tiles); };
+  if (load == F32_ALIGNED) a.b_kc ? launch(gemm_f32_kernel<TM, TN, D, true, F32_ALIGNED>) : launch(gemm_f32_kernel<TM, TN, D, false, F32_ALIGNED>);
+  else if (load == F32_ANY) a.b_kc ? launch(gemm_f32_kernel<TM, TN, D, true, F32_ANY>) : launch(gemm_f32_kernel<TM, TN, D, false, F32_ANY>);
+  else a.b_kc ? launch(gemm_f32_kernel<TM, TN, D, true, F32_SLOTS>) : launch(gemm_f32_kernel<TM, TN, D, false, F32_SLOTS>);
   return hipGetLastError();
 }
 
