@@ -151,6 +151,7 @@ struct antdt_ctx {
   // complete; per-shard gradients are computed when a view asks for them.
   bool eager_wgrad = false;              // option: the worker step computes the per-shard weight gradients itself
   bool batched = false;                  // the last worker step covered all shards
+  bool left_out = false;                 // the aggregation of its gradients left shards out
   bool wgrad_deferred = false;           // this worker step left the weight gradients to apply_update / the views
   bool shard_grads_done = false;         // the per-shard dense gradients of this worker step are (being) written
   bool grads_viewed[ANTDT_MAX_SHARDS] = {};  // a view handed out the shard's gradients of its last worker step
@@ -182,14 +183,18 @@ struct antdt_ctx {
 //   106 / 115 us per step).
 //   Dense update beside the sparse one: where there are many lookups or many weights (26 fields, 1024-512-256:
 //   26 000 / 70 000 / 140 000 / 560 000 lookups, beside or after: 98 / 92, 107 / 101, 106 / 108, 137 / 145 us per
-//   step; 3840-1024-512 at 50 000: 102 / 122).  After one worker step per shard the launch stream is busy for longer:
-//   six workers with 164 000 / 819 000 lookups 369 / 326 and 396 / 405 us.  fp32 models never (176 / 171 us at
-//   430 000 lookups).
+//   step; 3840-1024-512 at 50 000: 102 / 122).  After one worker step per shard not: six workers, 1024-512-256, with
+//   300 000 / 500 000 / 700 000 / 1.6 M / 4.1 M lookups 367 / 322, 398 / 345, 424 / 376, 539 / 500, 838 / 816 us; eight, 3840-1024-512
+//   with 0.9 / 3.8 / 12 M 550 / 505, 846 / 845, 1504 / 1497 us.  Unless shards were left out: the host has then waited for the
+//   stream and is no longer ahead of it (one of six workers left out, 700 000 / 1.6 M / 4.1 M lookups 374 / 380, 473 / 482,
+//   804 / 829 us, fewer lookups alike; one of eight with 0.9 / 3.8 M 486 / 508, 778 / 822).  fp32 models never (176 / 171 us
+//   at 430 000 lookups).
 static inline hipStream_t side_stream(const antdt_ctx* c) {
   return (c->static_bound || c->no_streams || c->fp.p[c->m.num_fields] < 16384) ? nullptr : c->side;
 }
 static inline hipStream_t wgrad_stream(const antdt_ctx* c) {
-  const bool enough = c->act_bf16 && (c->fp.p[c->m.num_fields] >= (c->batched ? 100000 : 600000) || c->P >= 2000000);
+  const bool enough = c->act_bf16 && (c->batched || c->left_out) &&
+                      (c->fp.p[c->m.num_fields] >= (c->batched ? 100000 : 600000) || c->P >= 2000000);
   return (c->static_bound || c->no_streams || !enough) ? nullptr : c->wside;
 }
 
@@ -671,9 +676,11 @@ static void fill_seg_args(antdt_ctx* c, SegArgs& a) {
   a.G = c->G; a.dx = c->dx; a.lddx = c->FD;
   a.offsets = c->offsets; a.mean_pool = m.pooling == ANTDT_POOL_MEAN;
   a.F = m.num_fields; a.D = m.dim; a.B = (int32_t)c->B; a.total_tiles = c->atotal_tiles;
-  // 512 lookups per block need half the blocks but, with LDS growing with D, leave fewer of them on a compute unit:
-  // 4.3 M lookups with D = 32: 160 us against 172, with D = 64: 3.8 M 173 against 143, 42 M 1486 against 1239; 1.1 M
-  // with D = 32: 50 against 45.
+  // 512 lookups per block need half the blocks but, with LDS growing with D, leave fewer of them on a compute unit.  The
+  // launch, 512 against 256: 4.3 M lookups with D = 32 160 us against 172, with D = 64 3.8 M 173 against 143, 42 M 1486 against
+  // 1239; 1.1 M with D = 32 50 against 45.  A step of 26 fields, 1024-512-256: D = 32 with 1.5 / 2.8 / 4.2 / 7 M lookups
+  // 243 / 242, 410 / 420, 547 / 558, 865 / 894; D = 16 with 1.5 / 2.8 / 5 M 212 / 214, 354 / 361, 570 / 605; D = 8 with 2.8 / 7 M
+  // 309 / 309, 647 / 659.
   a.window = c->afp.p[m.num_fields] >= (4 << 20) && m.dim <= 32 ? 512 : 256;
   a.tables = c->tables; a.state = c->table_state; a.R = m.rows_per_field; a.lr = m.lr; a.eps = m.eps;
   a.table_bf16 = m.table_dtype == ANTDT_BF16; a.rowwise = m.adagrad_state == ANTDT_STATE_ROWWISE;
@@ -862,6 +869,7 @@ static int worker_range(antdt_ctx* c, int k0, int k1, float* loss_out, hipStream
   const size_t es = c->act_size;
   c->presorted = false;
   c->batched = k0 == 0 && k1 == tab.K;
+  c->left_out = false;
   const bool beside = c->batched && side_stream(c);
   const bool early = beside && c->fp.p[m.num_fields] >= EARLY_MIN;
   if (early) HIP_TRY(c, hipEventRecord(c->ev_fork, s));
@@ -1065,6 +1073,7 @@ int antdt_aggregate(antdt_ctx* c, const uint8_t* shard_mask, void* stream) {
     const int rc = build_coalescing(c, ids_in, pay_in, s);
     if (rc) return rc;
   }
+  c->left_out = !all;
   c->presorted = false;
   c->g_valid = false;
   c->gdense_valid = false;  // the dense sum is formed inside the optimizer kernel (or on request)
