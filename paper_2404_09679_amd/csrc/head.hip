@@ -96,7 +96,8 @@ __global__ __launch_bounds__(256) void head_tile_kernel(HeadArgs a, ShardTab tab
     sums[wave][0] = sdz;
     sums[wave][1] = sl;
   }
-  if (a.dz && on) {   // (lane r < rows: the wavefront's sample r)
+  const bool per_sample = sizeof(TH) == 4 && a.dz;
+  if (per_sample && on) {   // (lane r < rows: the wavefront's sample r)
     a.dz[s0 + wave * SPW + lane] = dz_lane;
     a.loss_s[s0 + wave * SPW + lane] = loss_lane;
   }
@@ -116,23 +117,23 @@ __global__ __launch_bounds__(256) void head_tile_kernel(HeadArgs a, ShardTab tab
         }
       if (j0 + i * 64 < a.width) col[wave][i * 64 + lane] = g;
     }
-    if (a.dz) continue;
+    if (per_sample) continue;
     __syncthreads();
     for (int q = threadIdx.x; q < CHUNK && j0 + q < a.width; q += 256)
       part_out[j0 + q] = (col[0][q] + col[1][q]) + (col[2][q] + col[3][q]);
     __syncthreads();
   }
-  if (threadIdx.x == 0 && !a.dz) {
+  if (threadIdx.x == 0 && !per_sample) {
     part_out[a.width] = (sums[0][0] + sums[1][0]) + (sums[2][0] + sums[3][0]);
     part_out[a.width + 1] = (sums[0][1] + sums[1][1]) + (sums[2][1] + sums[3][1]);
   }
   if (blockIdx.x == 0 && (int)threadIdx.x < a.k_end - a.k_begin) {
     const int q = a.k_begin + threadIdx.x;
     LossJob j;
-    j.sums = a.dz ? a.loss_s + tab.start[q] : a.part + (int64_t)ht.base[q] * a.ldpart + a.width + 1;
+    j.sums = per_sample ? a.loss_s + tab.start[q] : a.part + (int64_t)ht.base[q] * a.ldpart + a.width + 1;
     j.loss_out = a.loss_out ? a.loss_out + threadIdx.x : nullptr;
-    j.ldpart = a.dz ? 1 : a.ldpart;
-    j.tiles = a.dz ? tab.len[q] : ht.base[q + 1] - ht.base[q];
+    j.ldpart = per_sample ? 1 : a.ldpart;
+    j.tiles = per_sample ? tab.len[q] : ht.base[q + 1] - ht.base[q];
     j.len = tab.len[q];
     a.job[q] = j;
   }
