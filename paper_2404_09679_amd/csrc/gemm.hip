@@ -38,9 +38,9 @@ __device__ __forceinline__ void zero_acc(f32x16 (&acc)[TM][TN]) {
 // The results leave through LDS, 32 rows of a wavefront's tile at a time: a lane of the MFMA result holds
 // groups of four neighbouring columns of one row, which would be 8-byte stores (16 with fp32 results) all
 // over 32 rows; staged, they are 16-byte stores of whole row segments.
-template <int TM, int TN, int WR, int WC, int WK, int BK, int STAGES, bool B_STRIDED>
+template <int TM, int TN, int WR, int WC, int WK, int BK, int STAGES, bool B_STRIDED, bool FAR>
 __global__ __launch_bounds__(64 * WR * WC * WK) void gemm_bf16_kernel(GemmArgs p, int tiles_n) {
-  typedef BlockProduct<TM, TN, WR, WC, WK, BK, STAGES, false, B_STRIDED> P;
+  typedef BlockProduct<TM, TN, WR, WC, WK, BK, STAGES, false, B_STRIDED, FAR> P;
   extern __shared__ __attribute__((aligned(16))) char lds[];
   int pid = blockIdx.x;
   const int nblk = gridDim.x - p.loss_blocks;
@@ -222,9 +222,9 @@ __device__ __forceinline__ void last_layer_from_samples(const WgradArgs& u, cons
     u.grads[(int64_t)(u.k0 + blockIdx.y) * u.stride + u.last_off + j] = (red[0][tx] + red[1][tx]) + (red[2][tx] + red[3][tx]);
 }
 
-template <int TM, int TN, int WR, int WC, int BK, int STAGES, WgradMode MODE>
+template <int TM, int TN, int WR, int WC, int BK, int STAGES, WgradMode MODE, bool FAR>
 __global__ __launch_bounds__(64 * WR * WC) void wgrad_kernel(WgradArgs u, KSegments seg) {
-  typedef BlockProduct<TM, TN, WR, WC, 1, BK, STAGES, true, true> P;
+  typedef BlockProduct<TM, TN, WR, WC, 1, BK, STAGES, true, true, FAR> P;
   extern __shared__ __attribute__((aligned(16))) char lds[];
   if ((int)blockIdx.x >= u.tile_base[u.n_layers]) {
     last_layer<MODE>(u, seg, blockIdx.x - u.tile_base[u.n_layers], reinterpret_cast<float(*)[64]>(lds));
@@ -537,20 +537,23 @@ __global__ __launch_bounds__(256) void cast_bf16_kernel(CastArgs a) {
     a.dst[i] = i < a.n_src ? f2bf(a.src[i]) : (bf16_t)0;
 }
 
-template <int TM, int TN, int WR, int WC, int WK, int BK, int STAGES, bool BS>
+template <int TM, int TN, int WR, int WC, int WK, int BK, int STAGES, bool BS, bool FAR = false>
 hipError_t launch_bf16(const GemmArgs& a, hipStream_t s) {
-  typedef BlockProduct<TM, TN, WR, WC, WK, BK, STAGES, false, BS> P;
+  typedef BlockProduct<TM, TN, WR, WC, WK, BK, STAGES, false, BS, FAR> P;
   static std::atomic<uint64_t> allowed{0};
-  const hipError_t ok = allow_lds(gemm_bf16_kernel<TM, TN, WR, WC, WK, BK, STAGES, BS>, P::LDS_BYTES, 0, allowed);
+  const hipError_t ok = allow_lds(gemm_bf16_kernel<TM, TN, WR, WC, WK, BK, STAGES, BS, FAR>, P::LDS_BYTES, 0, allowed);
   if (ok != hipSuccess) return ok;
   const int tiles_m = (a.M + P::BM - 1) / P::BM, tiles_n = (a.N + P::BN - 1) / P::BN;
-  hipLaunchKernelGGL((gemm_bf16_kernel<TM, TN, WR, WC, WK, BK, STAGES, BS>), dim3(tiles_m * tiles_n + a.loss_blocks), dim3(P::THREADS),
+  hipLaunchKernelGGL((gemm_bf16_kernel<TM, TN, WR, WC, WK, BK, STAGES, BS, FAR>), dim3(tiles_m * tiles_n + a.loss_blocks), dim3(P::THREADS),
                      P::LDS_BYTES, s, a, tiles_n);
   return hipGetLastError();
 }
 
 template <bool BS>
 hipError_t launch_bf16_sized(const GemmArgs& a, hipStream_t s) {
+  // A tile holds up to 256 rows of an operand (128 contraction slots of a strided one); its pieces are addressed by 32-bit
+  // offsets where those reach.
+  if (std::max(a.lda, a.ldb) * (256 * 2) >> 32) return launch_bf16<1, 1, 1, 1, 1, 128, 3, BS, true>(a, s);
   auto blocks = [&](int bm, int bn) { return (int64_t)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
   // Measured (us; M x N x K; tiles of 256, 128, 64 and 32 rows and columns, eight wavefronts on the first two,
   // four, one):  16384 x 1024 x 6400: 189 / 224 / 483 / -;   2501 x 3840 x 1024: 30 / 32 / 47 / 89;
@@ -602,11 +605,11 @@ hipError_t launch_wgrad_f32(const WgradArgs& a, const KSegments& seg, hipStream_
   return launch_wgrad_f32_tile<1, 1, 4>(a, seg, s);
 }
 
-template <int TM, int TN, int WR, int WC, int BK, int STAGES, WgradMode MODE>
+template <int TM, int TN, int WR, int WC, int BK, int STAGES, WgradMode MODE, bool FAR = false>
 hipError_t launch_wgrad_tile(const WgradArgs& a, const KSegments& seg, int groups, hipStream_t s) {
-  typedef BlockProduct<TM, TN, WR, WC, 1, BK, STAGES, true, true> P;
+  typedef BlockProduct<TM, TN, WR, WC, 1, BK, STAGES, true, true, FAR> P;
   static std::atomic<uint64_t> allowed{0};
-  const hipError_t ok = allow_lds(wgrad_kernel<TM, TN, WR, WC, BK, STAGES, MODE>, P::LDS_BYTES, 0, allowed);
+  const hipError_t ok = allow_lds(wgrad_kernel<TM, TN, WR, WC, BK, STAGES, MODE, FAR>, P::LDS_BYTES, 0, allowed);
   if (ok != hipSuccess) return ok;
   WgradArgs u = a;
   u.tile_base[0] = 0;
@@ -614,7 +617,7 @@ hipError_t launch_wgrad_tile(const WgradArgs& a, const KSegments& seg, int group
     u.tiles_n[l] = (u.N[l] + P::BN - 1) / P::BN;
     u.tile_base[l + 1] = u.tile_base[l] + ((u.M[l] + P::BM - 1) / P::BM) * u.tiles_n[l];
   }
-  hipLaunchKernelGGL((wgrad_kernel<TM, TN, WR, WC, BK, STAGES, MODE>), dim3(u.tile_base[u.n_layers] + (u.width + 64) / 64, groups),
+  hipLaunchKernelGGL((wgrad_kernel<TM, TN, WR, WC, BK, STAGES, MODE, FAR>), dim3(u.tile_base[u.n_layers] + (u.width + 64) / 64, groups),
                      dim3(P::THREADS), P::LDS_BYTES, s, u, seg);
   return hipGetLastError();
 }
@@ -626,6 +629,8 @@ hipError_t launch_wgrad_sized(const WgradArgs& a, const KSegments& seg, int grou
     for (int l = 0; l < a.n_layers; ++l) n += ((a.M[l] + bm - 1) / bm) * ((a.N[l] + bn - 1) / bn);
     return n * groups;
   };
+  for (int l = 0; l < a.n_layers; ++l)   // 64 samples of a tile beyond 32-bit offsets
+    if ((int64_t)std::max(a.lda[l], a.ldb[l]) * (64 * 2) >> 32) return launch_wgrad_tile<1, 1, 2, 2, 64, 3, MODE, true>(a, seg, groups, s);
   // Every block walks all samples, so a large tile means few operand bytes per output but also few blocks.
   // Measured alone (us; tiles of 128 x 128 with eight wavefronts / 64 x 64): 6400-1024-512 model, 16384 samples,
   // one range (432 large tiles) 320 / 509; 3840-1024-512, 2501 samples, 16 ranges (272) 128 / 83;

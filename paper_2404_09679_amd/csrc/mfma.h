@@ -16,6 +16,8 @@
 // bank once.
 #pragma once
 
+#include <type_traits>
+
 #include "common.h"
 
 namespace antdt {
@@ -30,6 +32,9 @@ static __device__ __attribute__((aligned(16))) uint32_t mfma_zero16[4];
 // One 16-byte piece per lane from memory to LDS slot `lds + 16 * lane` (`lds` is wavefront-uniform).
 __device__ __forceinline__ void load_lds16(const void* src, uint32_t lds) {
   asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"{m0}"(lds), "v"(src) : "memory");
+}
+__device__ __forceinline__ void load_lds16(const void* base, uint64_t off, uint32_t lds) {
+  load_lds16(reinterpret_cast<const char*>(base) + off, lds);
 }
 // The same from base + off (base wavefront-uniform).
 __device__ __forceinline__ void load_lds16(const void* base, uint32_t off, uint32_t lds) {
@@ -93,8 +98,10 @@ struct OperandTile {
 // only fetch: a small tile needs few MFMAs but its loads are best spread over many wavefronts.  (They do not
 // take a part of the contraction: every tile shape adds up the products in the same order, so that a
 // sample's results do not depend on how many samples are computed with it.)
-template <int TM, int TN, int WR, int WC, int WK, int BK, int STAGES, bool A_STRIDED, bool B_STRIDED>
+// FAR: pieces of a tile may lie 4 GiB or more from its origin (operands wider than 2^31 / rows of the tile).
+template <int TM, int TN, int WR, int WC, int WK, int BK, int STAGES, bool A_STRIDED, bool B_STRIDED, bool FAR = false>
 struct BlockProduct {
+  typedef typename std::conditional<FAR, uint64_t, uint32_t>::type Offset;
   static constexpr int THREADS = 64 * WR * WC * WK;
   static constexpr int BM = 32 * TM * WR, BN = 32 * TN * WC;
   typedef OperandTile<BM, BK, A_STRIDED> TA;
@@ -126,7 +133,7 @@ struct BlockProduct {
     const uint32_t lds0 = lds_address(lds) + wave * 1024;
     // Byte offsets of this thread's pieces from the tile's origin, the same for every stage; the origin
     // moves along the contraction (scalar arithmetic only).
-    uint32_t oa[VA], ob[VB];
+    Offset oa[VA], ob[VB];
     int ka[VA], kb[VB];   // contraction slot (relative to the stage) of each piece
 #pragma unroll
     for (int i = 0; i < VA; ++i) piece<TA, A_STRIDED>(tid + i * THREADS, lda, rows_a, m0, oa[i], ka[i]);
@@ -217,14 +224,14 @@ struct BlockProduct {
   // Piece `slot` of an operand's tile whose first row is r0: its offset from the tile's origin and its
   // contraction slot.
   template <typename T, bool STRIDED>
-  static __device__ __forceinline__ void piece(int slot, int64_t ld, int rows, int r0, uint32_t& off, int& k) {
+  static __device__ __forceinline__ void piece(int slot, int64_t ld, int rows, int r0, Offset& off, int& k) {
     const int r = slot / T::PITCH, c = (slot % T::PITCH) ^ T::swizzle(r);
     if (!STRIDED) {
       k = c * 8;
-      off = (uint32_t)(min(r, rows - 1 - r0) * ld + k) * 2;
+      off = (Offset)(min(r, rows - 1 - r0) * ld + k) * 2;
     } else {   // (the row length is a multiple of 8, so the last whole piece of a row is in bounds)
       k = r;
-      off = (uint32_t)(r * ld + min(c * 8, ((rows - 1) & ~7) - r0)) * 2;
+      off = (Offset)(r * ld + min(c * 8, ((rows - 1) & ~7) - r0)) * 2;
     }
   }
 };

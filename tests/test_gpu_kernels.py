@@ -150,3 +150,52 @@ def test_f32_model_without_hidden_layer(fields, num_dense, max_bag):
 def test_f32_last_hidden_layer(width):
     cfg = _config(f"last-hidden-{width}", 670, layer_sizes=(24, width), gemm_dtype="f32", shard_sizes=(16, 3, 0, 37))
     check_iteration(cfg, cfg.shard_sizes, tol=TOL32, batched=True, nonzero_state=True)
+
+
+def test_bf16_products_of_rows_beyond_32_bit_offsets():
+    """34.1 million dense features: 64 samples of the weight gradient's tile span more than 4 GiB.  Against the same
+    products in torch, formed from the library's own pooled input (the hidden layer is small)."""
+    import torch
+    import paper_2404_09679_amd as A
+    nd, B, N = 34_100_003, 70, 8
+    cfg = _config("far", 690, num_fields=1, rows_per_field=50, dim=8, num_dense=nd, layer_sizes=(N,), shard_sizes=(B,))
+    width = cfg.layer_sizes[0]
+    dev = "cuda:0"
+    g = torch.Generator(device=dev).manual_seed(5)
+    params = torch.randn(width * N + N + N + 1, generator=g, device=dev) * 2e-4
+    W1 = params[width * N + N:width * N + 2 * N]
+    W1.copy_(torch.tensor([1.0, -1.0] * 4, device=dev))
+    pstate = torch.ones_like(params)
+    tables = torch.randn((50, 8), generator=g, device=dev)
+    dense = torch.randn((B, nd), generator=g, device=dev)
+    labels = (torch.rand(B, generator=g, device=dev) < 0.5).float()
+    ids = torch.randint(0, 50, (B,), generator=g, device=dev, dtype=torch.int32)
+    ctx = A.Context(A.model_from_config(cfg, max_nnz=B))
+    ctx.bind(tables, torch.ones_like(tables), params, pstate)
+    ctx.set_batch(ids, [0, B], torch.arange(B + 1, dtype=torch.int32, device=dev).reshape(1, -1), dense, labels)
+    ctx.assign_shard(B, 1)
+    loss = torch.zeros(1, device=dev)
+    ctx.worker_step_all(loss)
+    got, dx = ctx.view_shard_grads(0)
+    torch.cuda.synchronize()
+    x = ctx.view_pooled(0)
+    z = params[width * N:width * N + N].double().expand(B, N).clone()
+    step = 1 << 20
+    for c in range(0, width, step):
+        e = min(width, c + step)
+        z += (x[:, c:e].float() @ params[c * N:e * N].reshape(-1, N).bfloat16().float()).double()
+    h = z.clamp(min=0).float().bfloat16().double()
+    logit = h @ W1.double() + params[-1].double()
+    want_loss = torch.nn.functional.binary_cross_entropy_with_logits(logit, labels.double())
+    assert abs(loss.item() - want_loss.item()) <= 2e-2 * want_loss.item()
+    dh = ((torch.sigmoid(logit) - labels.double()) / B)[:, None] * W1.double() * (h > 0)
+    dh = dh.float().bfloat16().float()
+    num = den = 0.0
+    for c in range(0, width, step):
+        e = min(width, c + step)
+        want = x[:, c:e].float().T @ dh
+        num += float(((got[c * N:e * N].reshape(-1, N) - want) ** 2).sum())
+        den += float((want ** 2).sum())
+    assert num <= (TOLBF * TOLBF) * den
+    want = dh @ params[:8 * N].reshape(8, N).bfloat16().float().T
+    assert float((dx - want).norm()) <= TOLBF * float(want.norm())
