@@ -10,7 +10,7 @@ import workload as wl
 
 pytestmark = pytest.mark.gpu
 
-# bf16 products; 55 000 lookups and 0.09 M parameters (dense update on the launch stream) or 2.3 M (on a stream of its own)
+# bf16 products; 52 000 lookups and 0.09 M parameters (dense update on the launch stream) or 2.3 M (on a stream of its own)
 SMALL_BF = wl.RankingConfig("order-small", 5, 20_000, 32, "f32", "elementwise", 13, (173, 256, 128, 64, 1), "bf16",
                             20, 1.1, (300, 37, 0, 663), wl.SEED0 + 801)
 WIDE_BF = wl.scaled(SMALL_BF, name="order-wide", layer_sizes=(173, 2048, 1024, 1))
@@ -158,3 +158,25 @@ def test_weight_gradient_option_changed_between_worker_steps(first, then):
         a, b = run.ctx.view_shard_grads(k)[0], ref.ctx.view_shard_grads(k)[0]
         torch.cuda.synchronize()
         assert torch.equal(a, b), f"shard {k}"
+
+
+@pytest.mark.parametrize("cfg", [WIDE_BF, wl.scaled(WIDE_BF, name="order-equal", shard_sizes=(250,) * 4),
+                                 wl.scaled(PIECES, name="order-pieces-wide", layer_sizes=(53, 1288, 1544, 1))], ids=lambda c: c.name)
+@pytest.mark.parametrize("batched", [True, False], ids=["batched", "by-worker"])
+def test_dense_update_beside_the_launch_stream(cfg, batched):
+    """Models whose dense update runs beside the input gradient and the sparse update (batched steps; after steps by worker
+    once shards are left out), fused with the weight gradients of several ranges or one, or from pieces; no view in
+    between that would wait for anything.  Three iterations, the last two on the weights of the ones before."""
+    runs = [start(cfg, streams=s) for s in (True, False)]
+    K = len(cfg.shard_sizes)
+    for _ in range(3):
+        for run in runs:
+            if batched:
+                run.ctx.worker_step_all(run.loss)
+                run.ctx.aggregate()
+            else:
+                for k in range(1, K):
+                    run.ctx.worker_step(k, run.loss[k:k + 1])
+                run.ctx.aggregate([0] + [1] * (K - 1))
+            run.ctx.apply_update()
+    assert_same(weights(runs[0]), weights(runs[1]), "three iterations")

@@ -193,7 +193,7 @@ def test_masked_aggregation_leaves_shards_out():
     check_iteration(cfg, cfg.shard_sizes, mask=(1, 1, 0, 1), nonzero_state=True)
     # after a batched step (structure of the whole batch already built on the side stream)
     check_iteration(cfg, cfg.shard_sizes, mask=(0, 1, 1, 1), batched=True)
-    # multi-tile fields and long runs; everything but one shard left out
+    # long runs over several windows; everything but one shard left out
     K = len(MID.shard_sizes)
     check_iteration(MID, MID.shard_sizes, mask=tuple(int(k % 3 != 1) for k in range(K)), batched=True)
     check_iteration(MID, MID.shard_sizes, mask=tuple(int(k == K - 1) for k in range(K)))
@@ -620,9 +620,10 @@ def test_other_batches_of_the_mid_size_models(batch_index):
 
 @pytest.mark.parametrize("batch", [512, 513, 1024, 1535])
 def test_lookup_counts_at_the_sort_tile_boundaries(batch):
-    """Every bag has four lookups: a field has exactly 2048 or 4096 lookups (whole sort tiles), or a
-    few more or fewer (a last tile with a handful of keys, or short of a handful); 9 fields, so the
-    groups of fields dealt to the eight XCDs differ in size."""
+    """Every bag has four lookups: a field has exactly 2048 or 4096 lookups, or a few more or fewer
+    (whole numbers of lookups per thread of the sort in one block, and of windows of the reduction);
+    9 fields, so the groups of fields dealt to the eight XCDs differ in size.  Fields at the tiles of
+    the sort over many blocks: test_gpu_kernels.py."""
     cfg = wl.RankingConfig(f"tile-boundary-{batch}", 9, 3000, 8, "f32", "elementwise", 2, (74, 16, 1), "f32",
                            4, 1.1, (batch - 200, 200), wl.SEED0 + 300 + batch, min_bag=4)
     b = wl.make_batch(cfg)
