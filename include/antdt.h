@@ -234,12 +234,14 @@ int antdt_apply_update(antdt_ctx* ctx, void* stream);
  * matrix products and a context bound by antdt_bind, antdt_worker_step leaves them out:
  * antdt_apply_update forms them inside the dense update (per shard in registers, weighted and
  * added up in shard order, then Adagrad; neither the per-shard nor the aggregated gradient is
- * written), and antdt_view_shard_grads / antdt_view_dense_grad compute the per-shard gradients
- * on request.  With on != 0 every antdt_worker_step computes its shards' weight gradients itself,
- * as K separate workers would before pushing them (Section II), and antdt_apply_update
- * aggregates what they wrote; the results agree to rounding.  Takes effect at the next
- * antdt_worker_step; while the step of another shard of the same iteration has left its weight gradients to
- * antdt_apply_update, the following ones do so too.  Host only.
+ * written; large batches: in pieces of the batch, added up by the dense update, unless a view of this
+ * iteration's per-shard gradients holds the memory of the pieces, which changes the rounding only),
+ * and antdt_view_shard_grads / antdt_view_dense_grad compute the per-shard gradients on request.  With
+ * on != 0 every antdt_worker_step computes its shards' weight gradients itself, as K separate
+ * workers would before pushing them (Section II), and antdt_apply_update aggregates what they
+ * wrote; the results agree to rounding.  Takes effect at the next antdt_worker_step; while the
+ * step of another shard of the same iteration has left its weight gradients to antdt_apply_update,
+ * the following ones do so too.  Host only.
  */
 int antdt_set_eager_weight_gradients(antdt_ctx* ctx, int32_t on);
 

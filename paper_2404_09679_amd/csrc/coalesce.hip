@@ -291,8 +291,8 @@ __global__ __launch_bounds__(SORT_THREADS) void sort_scatter_kernel(
 
 // All passes of a field's sort in one block, for fields of up to SMALL_THREADS * IT lookups: keys and sample
 // indices stay in registers between the passes (item i of wavefront w: position 64 (w per + i) + lane, all wavefronts
-// holding the same number `per` of items a lane) and trade places through LDS.  Same ranking, hence the same stable order, as the passes over many blocks,
-// in one launch instead of three per pass; a block's time is a few microseconds per pass and 8 items of a
+// holding the same number `per` of items a lane) and trade places through LDS.  Same ranking, hence the same stable
+// order, as the passes over many blocks, in one launch instead of three per pass; a block's time is a few microseconds per pass and 8 items of a
 // thread.  Blocks behind the fields write the samples' aggregation weights.
 // (26 fields of 1000 lookups, two passes: 29 us of kernels and their gaps -> one launch of 11 us.)
 constexpr int SMALL_THREADS = 1024, SMALL_WAVES = SMALL_THREADS / 64;
@@ -413,7 +413,8 @@ hipError_t launch_sort_small_items(const SortPlan& pl, const SortBuffers& sb, co
 }
 
 // Sample index of every lookup, from the offsets alone: what the gather records along the way, for a sort that does not
-// wait for the gather.  Eight lanes per bag.  Bound by its stores.
+// wait for the gather.  Eight lanes per bag.  It runs beside the gather, which the two then share the memory with: 17 MB of
+// sample indices in 61 us, 167 MB in 404 us (the gather 490), far from what its stores alone would take.
 __global__ __launch_bounds__(256) void expand_samples_kernel(const int32_t* offsets, int32_t* lookup_sample, FieldPtr fp, int B) {
   const int f = blockIdx.y, c = threadIdx.x & 7;
   const int s = blockIdx.x * 32 + (threadIdx.x >> 3);

@@ -65,15 +65,16 @@ inline hipError_t allow_lds(F kernel, int dynamic_bytes, int static_bytes, std::
   return e;
 }
 
-// Kernel classes for the optional event timing.
+// Kernel classes for the optional event timing.  (Ids are part of the C interface: classes whose kernels are gone
+// keep their places and count no launches.)
 enum KernelId {
   KID_POOL = 0,
   KID_GEMM_FWD,
-  KID_GEMM_DGRAD,
+  KID_GEMM_DGRAD,      // gone: counted under KID_GEMM_BWD
   KID_GEMM_WGRAD,
   KID_HEAD,
-  KID_HEAD_REDUCE,
-  KID_BIAS_GRAD,
+  KID_HEAD_REDUCE,     // gone: blocks of the input-gradient and the weight-gradient launch
+  KID_BIAS_GRAD,       // gone: part of the weight gradients
   KID_SORT_HIST,
   KID_SORT_SCAN,
   KID_SORT_SCATTER,
@@ -86,7 +87,7 @@ enum KernelId {
   KID_SPARSE_ADAGRAD,
   KID_DENSE_ADAGRAD,
   KID_ADAM,
-  KID_TRANSPOSE,
+  KID_TRANSPOSE,       // gone
   KID_GEMM_BWD,
   KID_WGRAD_ADAGRAD,
   KID_COUNT
@@ -261,7 +262,6 @@ struct SortPlan {
 };
 struct SortBuffers {
   const int32_t* ids;
-  const int32_t* offsets;          // [F][B+1]
   const int32_t* pay0;             // sample index of every lookup (payload of the first pass)
   int32_t* key[2];
   int32_t* pay[2];

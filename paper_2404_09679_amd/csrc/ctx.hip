@@ -706,7 +706,7 @@ static int build_coalescing(antdt_ctx* c, const int32_t* ids, const int32_t* pay
   pl.F = m.num_fields; pl.B = (int32_t)c->B; pl.passes = c->sort_passes; pl.radix_bits = c->radix_bits;
   pl.total_tiles = c->atotal_tiles;
   SortBuffers sb;
-  sb.ids = ids; sb.offsets = c->offsets;
+  sb.ids = ids;
   sb.key[0] = c->key[0]; sb.key[1] = c->key[1]; sb.pay[0] = c->pay[0]; sb.pay[1] = c->pay[1];
   sb.hist = c->hist;
   sb.digit_base = c->digit_base;

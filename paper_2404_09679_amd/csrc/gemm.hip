@@ -38,9 +38,9 @@ __device__ __forceinline__ void zero_acc(f32x16 (&acc)[TM][TN]) {
 // The results leave through LDS, 32 rows of a wavefront's tile at a time: a lane of the MFMA result holds
 // groups of four neighbouring columns of one row, which would be 8-byte stores (16 with fp32 results) all
 // over 32 rows; staged, they are 16-byte stores of whole row segments.
-template <int TM, int TN, int WR, int WC, int WK, int BK, int STAGES, bool B_STRIDED, bool FAR>
-__global__ __launch_bounds__(64 * WR * WC * WK) void gemm_bf16_kernel(GemmArgs p, int tiles_n) {
-  typedef BlockProduct<TM, TN, WR, WC, WK, BK, STAGES, false, B_STRIDED, FAR> P;
+template <int TM, int TN, int WR, int WC, int BK, int STAGES, bool B_STRIDED, bool FAR>
+__global__ __launch_bounds__(64 * WR * WC) void gemm_bf16_kernel(GemmArgs p, int tiles_n) {
+  typedef BlockProduct<TM, TN, WR, WC, BK, STAGES, false, B_STRIDED, FAR> P;
   extern __shared__ __attribute__((aligned(16))) char lds[];
   int pid = blockIdx.x;
   const int nblk = gridDim.x - p.loss_blocks;
@@ -59,12 +59,12 @@ __global__ __launch_bounds__(64 * WR * WC * WK) void gemm_bf16_kernel(GemmArgs p
   constexpr int WN = 32 * TN;
   static_assert(WN <= 64, "one bias column per lane");
   float bias = 0.0f;
-  if (p.epi == EPI_BIAS_RELU) bias = p.bias[min(n0 + (wave % (WR * WC) % WC) * WN + lane % WN, p.N - 1)];
+  if (p.epi == EPI_BIAS_RELU) bias = p.bias[min(n0 + wave % WC * WN + lane % WN, p.N - 1)];
   f32x16 acc[TM][TN];
   zero_acc(acc);
   P::run(reinterpret_cast<const bf16_t*>(p.A), reinterpret_cast<const bf16_t*>(p.B), p.lda, p.ldb, p.M, p.N, m0, n0, 0,
          p.K, lds, acc);
-  if (wave >= WR * WC) return;
+  __builtin_assume(wave < WR * WC);   // (which the compiler cannot see)
   const int wr = wave / WC, wc = wave % WC;
   const int mw = m0 + wr * (32 * TM), nw = n0 + wc * WN;
   if (p.bf16_out) {
@@ -224,7 +224,7 @@ __device__ __forceinline__ void last_layer_from_samples(const WgradArgs& u, cons
 
 template <int TM, int TN, int WR, int WC, int BK, int STAGES, WgradMode MODE, bool FAR>
 __global__ __launch_bounds__(64 * WR * WC) void wgrad_kernel(WgradArgs u, KSegments seg) {
-  typedef BlockProduct<TM, TN, WR, WC, 1, BK, STAGES, true, true, FAR> P;
+  typedef BlockProduct<TM, TN, WR, WC, BK, STAGES, true, true, FAR> P;
   extern __shared__ __attribute__((aligned(16))) char lds[];
   if ((int)blockIdx.x >= u.tile_base[u.n_layers]) {
     last_layer<MODE>(u, seg, blockIdx.x - u.tile_base[u.n_layers], reinterpret_cast<float(*)[64]>(lds));
@@ -537,14 +537,14 @@ __global__ __launch_bounds__(256) void cast_bf16_kernel(CastArgs a) {
     a.dst[i] = i < a.n_src ? f2bf(a.src[i]) : (bf16_t)0;
 }
 
-template <int TM, int TN, int WR, int WC, int WK, int BK, int STAGES, bool BS, bool FAR = false>
+template <int TM, int TN, int WR, int WC, int BK, int STAGES, bool BS, bool FAR = false>
 hipError_t launch_bf16(const GemmArgs& a, hipStream_t s) {
-  typedef BlockProduct<TM, TN, WR, WC, WK, BK, STAGES, false, BS, FAR> P;
+  typedef BlockProduct<TM, TN, WR, WC, BK, STAGES, false, BS, FAR> P;
   static std::atomic<uint64_t> allowed{0};
-  const hipError_t ok = allow_lds(gemm_bf16_kernel<TM, TN, WR, WC, WK, BK, STAGES, BS, FAR>, P::LDS_BYTES, 0, allowed);
+  const hipError_t ok = allow_lds(gemm_bf16_kernel<TM, TN, WR, WC, BK, STAGES, BS, FAR>, P::LDS_BYTES, 0, allowed);
   if (ok != hipSuccess) return ok;
   const int tiles_m = (a.M + P::BM - 1) / P::BM, tiles_n = (a.N + P::BN - 1) / P::BN;
-  hipLaunchKernelGGL((gemm_bf16_kernel<TM, TN, WR, WC, WK, BK, STAGES, BS, FAR>), dim3(tiles_m * tiles_n + a.loss_blocks), dim3(P::THREADS),
+  hipLaunchKernelGGL((gemm_bf16_kernel<TM, TN, WR, WC, BK, STAGES, BS, FAR>), dim3(tiles_m * tiles_n + a.loss_blocks), dim3(P::THREADS),
                      P::LDS_BYTES, s, a, tiles_n);
   return hipGetLastError();
 }
@@ -553,17 +553,17 @@ template <bool BS>
 hipError_t launch_bf16_sized(const GemmArgs& a, hipStream_t s) {
   // A tile holds up to 256 rows of an operand (128 contraction slots of a strided one); its pieces are addressed by 32-bit
   // offsets where those reach.
-  if (std::max(a.lda, a.ldb) * (256 * 2) >> 32) return launch_bf16<1, 1, 1, 1, 1, 128, 3, BS, true>(a, s);
+  if (std::max(a.lda, a.ldb) * (256 * 2) >> 32) return launch_bf16<1, 1, 1, 1, 128, 3, BS, true>(a, s);
   auto blocks = [&](int bm, int bn) { return (int64_t)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
   // Measured (us; M x N x K; tiles of 256, 128, 64 and 32 rows and columns, eight wavefronts on the first two,
   // four, one):  16384 x 1024 x 6400: 189 / 224 / 483 / -;   2501 x 3840 x 1024: 30 / 32 / 47 / 89;
   // 15625 x 512 x 1024: 38 / 24 / 31 / 61;  4096 x 1024 x 848: 32 / 16 / 18 / 35;  4096 x 512 x 1024: 31 / 15 / 10 / 20;
   // 1531 x 1024 x 848: - / 16 / 10 / 16;  96 x 1024 x 848: - / 15 / 7.7 / 6.4.   The largest tile that gives most of
   // the 256 compute units a block wins (it reads the fewest operand bytes), and below that more blocks do.
-  if (blocks(256, 256) >= 150) return launch_bf16<4, 2, 2, 4, 1, 64, 2, BS>(a, s);
-  if (blocks(128, 128) >= 200) return launch_bf16<2, 1, 2, 4, 1, 64, 2, BS>(a, s);
-  if (blocks(64, 64) >= 100) return launch_bf16<1, 1, 2, 2, 1, 64, 3, BS>(a, s);
-  return launch_bf16<1, 1, 1, 1, 1, 128, 3, BS>(a, s);
+  if (blocks(256, 256) >= 150) return launch_bf16<4, 2, 2, 4, 64, 2, BS>(a, s);
+  if (blocks(128, 128) >= 200) return launch_bf16<2, 1, 2, 4, 64, 2, BS>(a, s);
+  if (blocks(64, 64) >= 100) return launch_bf16<1, 1, 2, 2, 64, 3, BS>(a, s);
+  return launch_bf16<1, 1, 1, 1, 128, 3, BS>(a, s);
 }
 
 template <int TM, int TN, int D>
@@ -607,7 +607,7 @@ hipError_t launch_wgrad_f32(const WgradArgs& a, const KSegments& seg, hipStream_
 
 template <int TM, int TN, int WR, int WC, int BK, int STAGES, WgradMode MODE, bool FAR = false>
 hipError_t launch_wgrad_tile(const WgradArgs& a, const KSegments& seg, int groups, hipStream_t s) {
-  typedef BlockProduct<TM, TN, WR, WC, 1, BK, STAGES, true, true, FAR> P;
+  typedef BlockProduct<TM, TN, WR, WC, BK, STAGES, true, true, FAR> P;
   static std::atomic<uint64_t> allowed{0};
   const hipError_t ok = allow_lds(wgrad_kernel<TM, TN, WR, WC, BK, STAGES, MODE, FAR>, P::LDS_BYTES, 0, allowed);
   if (ok != hipSuccess) return ok;

@@ -94,15 +94,13 @@ struct OperandTile {
   }
 };
 
-// The tiles of one block: WR x WC wavefronts of TM x TN MFMA tiles each.  WK - 1 times as many wavefronts more
-// only fetch: a small tile needs few MFMAs but its loads are best spread over many wavefronts.  (They do not
-// take a part of the contraction: every tile shape adds up the products in the same order, so that a
-// sample's results do not depend on how many samples are computed with it.)
+// The tiles of one block: WR x WC wavefronts of TM x TN MFMA tiles each.  Every shape adds up the products in the
+// same order, so that a sample's results do not depend on how many samples are computed with it.
 // FAR: pieces of a tile may lie 4 GiB or more from its origin (operands wider than 2^31 / rows of the tile).
-template <int TM, int TN, int WR, int WC, int WK, int BK, int STAGES, bool A_STRIDED, bool B_STRIDED, bool FAR = false>
+template <int TM, int TN, int WR, int WC, int BK, int STAGES, bool A_STRIDED, bool B_STRIDED, bool FAR = false>
 struct BlockProduct {
   typedef typename std::conditional<FAR, uint64_t, uint32_t>::type Offset;
-  static constexpr int THREADS = 64 * WR * WC * WK;
+  static constexpr int THREADS = 64 * WR * WC;
   static constexpr int BM = 32 * TM * WR, BN = 32 * TN * WC;
   typedef OperandTile<BM, BK, A_STRIDED> TA;
   typedef OperandTile<BN, BK, B_STRIDED> TB;
@@ -127,9 +125,8 @@ struct BlockProduct {
                                              int rows_b, int m0, int n0, int ks, int ke, char* lds,
                                              f32x16 (&acc)[TM][TN], f32x16 (&sum_b)[TN], bool ones) {
     const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const bool multiplies = WK == 1 || wave < WR * WC;
-    const int wr = wave % (WR * WC) / WC, wc = wave % WC;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wr = wave % (WR * WC) / WC, wc = wave % WC;   // (the modulo says that a single wavefront is number 0)
     const uint32_t lds0 = lds_address(lds) + wave * 1024;
     // Byte offsets of this thread's pieces from the tile's origin, the same for every stage; the origin
     // moves along the contraction (scalar arithmetic only).
@@ -175,10 +172,6 @@ struct BlockProduct {
       if (t + STAGES - 2 < nk) wait_loads<(STAGES - 2) * PER_STAGE>();
       else wait_loads<0>();
       block_barrier();          // ... and so have everyone's; stage t-1 has been read by everyone
-      if (!multiplies) {
-        if (left > 0) issue();
-        continue;
-      }
       // The fragments of the next contraction step are requested before the current one is multiplied, and
       // the next stage behind the first multiplications: with one or two wavefronts per SIMD nothing else
       // would hide those instructions.

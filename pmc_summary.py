@@ -46,12 +46,8 @@ def class_totals(rows):
             continue
         elif "head_tile" in k or "head_kernel" in k:
             after_head, cls = True, "head"
-        elif "head_reduce" in k:
-            cls = "head_reduce"
         elif "wgrad_" in k:
             cls = "wgrad_adagrad"
-        elif "transpose" in k:
-            cls = "transpose"
         elif "gemm_" in k:
             cls = "gemm_bwd" if after_head else "gemm_fwd"
         elif "seg_reduce" in k or "seg_window" in k:
