@@ -58,9 +58,9 @@ __device__ __forceinline__ void dense_columns(const PoolArgs& a, int sl0, int en
 // exchanges and issues the LPR row loads (16 bytes per lane, one whole row per group)
 // back to back before adding them, which keeps 64 rows in flight per wavefront; the next ids are
 // requested before the rows are waited for.  Every lookup's sample index is recorded for the sort.
-// Bound by vector instructions where bags are long (of 57 per row and wavefront 16 unpack and add a bf16 row;
-// bounds and addresses are therefore worked out once per lookup, by the lane that loads its id), else by
-// round trips.  Like the sort's tiles, the blocks of a field go to one XCD: its rows are fetched into one L2.
+// Bound by vector instructions where bags are long (41.8 M lookups of 128-byte bf16 rows: they issue in 73 % of the
+// cycles; 40 per eight rows of a wavefront, 16 of them to unpack and add, 57 before bounds and addresses were worked out
+// once per lookup, by the lane that loads its id), else by round trips.  Like the sort's tiles, the blocks of a field go to one XCD: its rows are fetched into one L2.
 // WIDE: a table of 2^32 or more 16-byte pieces.
 template <typename TT, typename OT, int LPR, int SPB, bool WIDE>
 __global__ __launch_bounds__(256) void pool_tile_kernel(PoolArgs a, FieldPtr fp) {

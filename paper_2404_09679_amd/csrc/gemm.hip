@@ -341,7 +341,9 @@ __global__ __launch_bounds__(64 * WR * WC) void wgrad_kernel(WgradArgs u, KSegme
 // of 16 neighbouring rows each where it is not.  No LDS: the models that use fp32 products are small, their
 // products are bound by load latency and by how few tiles there are, so loads run D steps ahead and tiles
 // stay small; what neighbouring wavefronts share comes from the L1.
-// (Through LDS in 64 x 64 tiles, one step in flight: 1500 x 256 x 397 91 us, here 13; 1500 x 384 x 256 110 us, here 16.)
+// (Through LDS in 64 x 64 tiles, one step in flight: 1500 x 256 x 397 91 us, here 13; 1500 x 384 x 256 110 us, here 16;
+// whole steps of an 845-1024-512-256 model with 512 / 4096 / 16384 samples 952 / 1145 / 3230 us, here 200 / 695 / 2400; of
+// 653-2048-2048 with 4096 2550, here 2025.)
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));   // a 16-byte load takes any 4-byte-aligned address
 
