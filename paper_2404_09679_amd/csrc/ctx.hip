@@ -822,7 +822,7 @@ static int cut_ranges(const antdt_ctx* c, const KSegments& seg, KSegments& piece
   while (count(len) > c->m.max_shards) len += len / 4;   // (ends: there are no more ranges than shards)
   if (tiles * count(len) < 400 || samples < 1024 * count(len)) return 0;
   memset(&pieces, 0, sizeof(pieces));
-  std::vector<std::pair<int, int>> order;   // (-length, place in the list of all pieces)
+  std::pair<int, int> order[ANTDT_MAX_SHARDS];   // (-length, place in the list of all pieces)
   KSegments all;
   memset(&all, 0, sizeof(all));
   for (int q = 0; q < seg.n; ++q)
@@ -830,13 +830,13 @@ static int cut_ranges(const antdt_ctx* c, const KSegments& seg, KSegments& piece
       const int i = all.n++;
       all.ks[i] = k; all.ke[i] = std::min(seg.ke[q], k + (int)len); all.w[i] = seg.w[q];
       all.ts[i] = seg.ts[q]; all.te[i] = k == seg.ks[q] ? seg.te[q] : seg.ts[q];   // (the last layer's sums: with the first piece)
-      order.push_back({-(all.ke[i] - all.ks[i]), i});
+      order[i] = {-(all.ke[i] - all.ks[i]), i};
     }
-  std::sort(order.begin(), order.end());
-  for (const auto& o : order) {
-    const int i = pieces.n++;
-    pieces.ks[i] = all.ks[o.second]; pieces.ke[i] = all.ke[o.second]; pieces.w[i] = all.w[o.second];
-    pieces.ts[i] = all.ts[o.second]; pieces.te[i] = all.te[o.second];
+  std::sort(order, order + all.n);
+  for (pieces.n = 0; pieces.n < all.n; ++pieces.n) {
+    const int i = pieces.n, j = order[i].second;
+    pieces.ks[i] = all.ks[j]; pieces.ke[i] = all.ke[j]; pieces.w[i] = all.w[j];
+    pieces.ts[i] = all.ts[j]; pieces.te[i] = all.te[j];
   }
   return pieces.n;
 }
