@@ -43,7 +43,7 @@ MEASURED_TRAFFIC = {
              "embed.hip": "87a1b7f61b5910b7a97e45e3c92ffc2864dd8c55",
              "coalesce.hip": "efd3807105898269ff08e64a2635a027ac729c34",
              "optim.hip": "10a9d8df954dfd1c5c03af1b0ba1d46512dc8303",
-             "ctx.hip": "afbf9ae52de7445a1204af1b82cd5677a351f774"},
+             "ctx.hip": "00febdac1c47c54e59edd3b813aa527b6fdfaf30"},
 }
 
 
