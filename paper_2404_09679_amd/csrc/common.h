@@ -183,7 +183,7 @@ struct WgradArgs {
   int32_t tiles_n[ANTDT_MAX_LAYERS];
   // last layer (one output): the loss kernel's sums over its tiles of samples
   const float* part;                   // [tiles, ldpart] sum of dz * h per column; column `width`: sum of dz
-  const float* dz;                     // fp32 models without a hidden layer: [samples] instead of those sums, or NULL
+  const float* dz;                     // models without a hidden layer: [samples] instead of those sums (A[0]: the input), or NULL
   int64_t ldpart, last_off;            // offset of the last layer in the flat parameters (bias behind the weights)
   int32_t width;
   float* p;

@@ -266,18 +266,23 @@ static size_t carve(antdt_ctx* c, char* base) {
   }
   c->hist = (uint32_t*)take((size_t)(c->max_tiles_total << c->radix_bits) * 4);
   c->digit_base = (uint32_t*)take((size_t)(m.num_fields << c->radix_bits) * 4);
-  c->cbase = (int64_t*)take((size_t)(ANTDT_MAX_FIELDS + 1) * 8);
-  c->vflags = (int32_t*)take(8);
+  const bool share = !c->act_bf16 && c->L == 1;   // (see below)
+  const size_t jobs = (size_t)K * sizeof(LossJob), counts = (size_t)(ANTDT_MAX_FIELDS + 1) * 8;
+  char* small = take(counts + 8 + (share ? 0 : jobs));
+  c->cbase = (int64_t*)small;
+  c->vflags = (int32_t*)(small ? small + counts : nullptr);
+  c->loss_job = (LossJob*)(small ? small + counts + 8 : nullptr);
   // The loss kernel's sums and jobs.  Of an fp32 model without a hidden layer they share memory with what only an
   // aggregation and what follows it use: the worker step itself reads them last (in bf16 models apply_update does).
-  // Where that is too small for sums over tiles (few lookups, many dense features), they are kept per sample instead, and
-  // the last layer's gradient is added up from the samples.
+  // Where that is too small for sums over tiles (few lookups, many dense features), or where those of a bf16 model
+  // without a hidden layer would take more than its inputs (most shards hold one sample), they are kept per sample instead,
+  // and the last layer's gradient is added up from the samples.
   const size_t tiles = (size_t)std::min(Bm, Bm / HEAD_TILE + K);   // (every tile has a sample)
   const size_t shared = off;
-  const bool share = !c->act_bf16 && c->L == 1;
-  c->loss_job = (LossJob*)take((size_t)K * sizeof(LossJob));
+  if (share) c->loss_job = (LossJob*)take(jobs);
   const size_t sums = off;
-  c->head_part = (float*)take(tiles * c->ldpart * 4);
+  c->sums_per_sample = c->act_bf16 && c->L == 1 && tiles * c->ldpart * 4 > (size_t)Bm * c->ldx * 2;
+  c->head_part = (float*)take(c->sums_per_sample ? (size_t)Bm * 8 : tiles * c->ldpart * 4);
   size_t behind = off;
   if (share) off = shared;
   c->g_dense = (float*)take((size_t)c->P * 4);
@@ -290,8 +295,10 @@ static size_t carve(antdt_ctx* c, char* base) {
   c->goes_out = (int32_t*)take((size_t)window_slots(N) * 4);
   c->partial = (float*)take((size_t)window_slots(N) * 2 * m.dim * 4);
   c->G = (float*)take((size_t)N * m.dim * 4);
-  c->sums_per_sample = share && behind > off;
-  if (c->sums_per_sample) behind = align_up(sums + (size_t)Bm * 8, 256);
+  if (share && behind > off) {
+    c->sums_per_sample = true;
+    behind = align_up(sums + (size_t)Bm * 8, 256);
+  }
   return std::max(off, behind);
 }
 

@@ -167,8 +167,9 @@ __device__ __forceinline__ float adagrad1(float p, float& s, float g, float lr, 
 }
 
 // The last layer (one output): the loss kernel has summed dz * h (and dz, the bias gradient) over its tiles of
-// samples; 64 columns per block, four lanes of tiles per column.
-template <WgradMode MODE>
+// samples, or, of a model without a hidden layer, may have left dz per sample (the sums are then formed from the samples,
+// T: type of the input); 64 columns per block, four lanes of tiles or samples per column.
+template <WgradMode MODE, typename T>
 __device__ __forceinline__ void last_layer(const WgradArgs& u, const KSegments& seg, int block, float (*red)[64]) {
   const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
   const int j = block * 64 + tx;
@@ -177,7 +178,11 @@ __device__ __forceinline__ void last_layer(const WgradArgs& u, const KSegments& 
   float g = 0.0f;
   for (int q = q0; q < q1; ++q) {
     float sum = 0.0f;
-    if (on && ty < 4) {
+    if (on && ty < 4 && u.dz) {
+      const T* x = reinterpret_cast<const T*>(u.A[0]) + min(j, u.width - 1);
+#pragma unroll 8
+      for (int s = seg.ks[q] + ty; s < seg.ke[q]; s += 4) sum = fmaf(j < u.width ? to_f32(x[(int64_t)s * u.lda[0]]) : 1.0f, u.dz[s], sum);
+    } else if (on && ty < 4) {
       const float* x = u.part + j;
       int t = seg.ts[q] + ty;
       for (; t + 28 < seg.te[q]; t += 32) {   // eight loads in flight
@@ -206,28 +211,12 @@ __device__ __forceinline__ void last_layer(const WgradArgs& u, const KSegments& 
   }
 }
 
-// The same of an fp32 model without a hidden layer whose loss kernel left dz per sample: from the samples.
-__device__ __forceinline__ void last_layer_from_samples(const WgradArgs& u, const float* x, int64_t ldx, int ks, int ke, int block,
-                                                        float (*red)[64]) {
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-  const int j = block * 64 + tx;
-  float sum = 0.0f;
-  if (j <= u.width) {
-#pragma unroll 8
-    for (int s = ks + ty; s < ke; s += 4) sum = fmaf(j < u.width ? x[s * ldx + j] : 1.0f, u.dz[s], sum);
-  }
-  red[ty][tx] = sum;
-  __syncthreads();
-  if (j <= u.width && ty == 0)
-    u.grads[(int64_t)(u.k0 + blockIdx.y) * u.stride + u.last_off + j] = (red[0][tx] + red[1][tx]) + (red[2][tx] + red[3][tx]);
-}
-
 template <int TM, int TN, int WR, int WC, int BK, int STAGES, WgradMode MODE, bool FAR>
 __global__ __launch_bounds__(64 * WR * WC) void wgrad_kernel(WgradArgs u, KSegments seg) {
   typedef BlockProduct<TM, TN, WR, WC, BK, STAGES, true, true, FAR> P;
   extern __shared__ __attribute__((aligned(16))) char lds[];
   if ((int)blockIdx.x >= u.tile_base[u.n_layers]) {
-    last_layer<MODE>(u, seg, blockIdx.x - u.tile_base[u.n_layers], reinterpret_cast<float(*)[64]>(lds));
+    last_layer<MODE, bf16_t>(u, seg, blockIdx.x - u.tile_base[u.n_layers], reinterpret_cast<float(*)[64]>(lds));
     return;
   }
   int li = 0;
@@ -495,10 +484,7 @@ __global__ __launch_bounds__(256) void wgrad_f32_kernel(WgradArgs u, KSegments s
   constexpr int BM = 16 * TM, BN = 16 * TN, PITCH = BN + 4;
   __shared__ __attribute__((aligned(16))) float red[4][(BM + 1) * PITCH];   // row BM: the bias gradient
   if ((int)blockIdx.x >= u.tile_base[u.n_layers]) {
-    const int block = blockIdx.x - u.tile_base[u.n_layers], q = blockIdx.y;
-    float(*r)[64] = reinterpret_cast<float(*)[64]>(&red[0][0]);
-    if (u.dz) last_layer_from_samples(u, reinterpret_cast<const float*>(u.A[0]), u.lda[0], seg.ks[q], seg.ke[q], block, r);
-    else last_layer<WGRAD_STORE>(u, seg, block, r);
+    last_layer<WGRAD_STORE, float>(u, seg, blockIdx.x - u.tile_base[u.n_layers], reinterpret_cast<float(*)[64]>(&red[0][0]));
     return;
   }
   int li = 0;

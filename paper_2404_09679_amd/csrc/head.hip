@@ -96,7 +96,7 @@ __global__ __launch_bounds__(256) void head_tile_kernel(HeadArgs a, ShardTab tab
     sums[wave][0] = sdz;
     sums[wave][1] = sl;
   }
-  const bool per_sample = sizeof(TH) == 4 && a.dz;
+  const bool per_sample = sizeof(TD) == 4 && a.dz;   // (bf16 gradients: there is a hidden layer)
   if (per_sample && on) {   // (lane r < rows: the wavefront's sample r)
     a.dz[s0 + wave * SPW + lane] = dz_lane;
     a.loss_s[s0 + wave * SPW + lane] = loss_lane;

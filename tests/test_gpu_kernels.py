@@ -251,21 +251,23 @@ def test_window_slots_of_neighbouring_fields(rows, monkeypatch):
     check_iteration(cfg, cfg.shard_sizes, tol=TOL32, mask=(1, 1, 0, 1), nonzero_state=True)
 
 
-# bf16 products without a hidden layer: the last layer's gradient is formed inside the update as well, or by the step
+# bf16 products without a hidden layer: the last layer's gradient is formed inside the update as well, or by the step;
+# from sums over tiles of samples, or from the samples where most shards hold one
+@pytest.mark.parametrize("sizes", [(16, 1, 0, 33, 200), (1,) * 30 + (0, 3) + (1,) * 20 + (2,)], ids=["tiles", "samples"])
 @pytest.mark.parametrize("kw", [{}, {"eager": True}, {"streams": False}, {"static": True}], ids=["update", "step", "one-stream", "static"])
-def test_bf16_model_without_hidden_layer(kw):
+def test_bf16_model_without_hidden_layer(kw, sizes):
     import torch
     from gpu_helpers import GpuRun
     from helpers import flat_layers, oracle_iteration, rel_err
     from test_gpu_parity import make_inputs
-    cfg = _config("no-hidden-bf16", 668, layer_sizes=(), shard_sizes=(16, 1, 0, 33, 200))
+    cfg = _config("no-hidden-bf16", 668, layer_sizes=(), shard_sizes=sizes)
     check_iteration(cfg, cfg.shard_sizes, tol=TOLBF, bf16_gemm_oracle=True, batched=True, nonzero_state=True)
     tables, state, flat, fstate, batch = make_inputs(cfg, nonzero_state=True)
     _, _, _, upd = oracle_iteration(cfg, tables, state, flat, fstate, batch, cfg.shard_sizes, bf16_gemm=True)
     run = GpuRun(cfg, tables, flat, state, fstate, **kw)
     run.set_batch(batch)
-    run.ctx.assign_shard(batch.batch, 5, sizes=cfg.shard_sizes)
-    run.ctx.worker_step_all(torch.zeros(5, device="cuda:0"))
+    run.ctx.assign_shard(batch.batch, len(sizes), sizes=sizes)
+    run.ctx.worker_step_all(torch.zeros(len(sizes), device="cuda:0"))
     run.ctx.aggregate()
     run.ctx.apply_update()
     torch.cuda.synchronize()

@@ -86,14 +86,15 @@ def test_static_binding_checks_its_arguments_before_any_gpu_work():
     assert "#define ANTDT_STATIC_SCRATCH_BYTES (32u << 20)" in header
 
 
-@pytest.mark.parametrize("fields,dim,num_dense,hidden,shards,batch,lookups,most", [
-    (128, 64, 0, (64,), 4, 152, 38_912, 33_375_744),      # few lookups per field
-    (100, 128, 0, (64,), 4, 100, 10_000, 33_177_600),
-    (4, 8, 0, (1608,), 25, 2100, 2100, 33_464_064),       # a wide last hidden layer, less than a lookup per bag
-    (1, 4, 0, (1024,), 4, 4000, 4000, 33_381_632),
-    (1, 4, 1024, (), 4, 7900, 7900, 33_334_784),          # no hidden layer, many dense features
-    (60, 128, 0, (), 64, 500, 0, 33_227_008)])            # no lookups
-def test_workspace_of_fp32_models_at_the_static_buffer(fields, dim, num_dense, hidden, shards, batch, lookups, most):
+@pytest.mark.parametrize("gemm,fields,dim,num_dense,hidden,shards,batch,lookups,most", [
+    (0, 128, 64, 0, (64,), 4, 152, 38_912, 33_375_744),      # few lookups per field
+    (0, 100, 128, 0, (64,), 4, 100, 10_000, 33_177_600),
+    (0, 4, 8, 0, (1608,), 25, 2100, 2100, 33_464_064),       # a wide last hidden layer, less than a lookup per bag
+    (0, 1, 4, 0, (1024,), 4, 4000, 4000, 33_381_632),
+    (0, 1, 4, 1024, (), 4, 7900, 7900, 33_334_784),          # no hidden layer, many dense features
+    (0, 60, 128, 0, (), 64, 500, 0, 33_227_008),            # no lookups
+    (1, 46, 256, 0, (), 54, 50, 23_000, 33_219_584)])          # bf16 products, most shards of one sample
+def test_workspace_of_models_at_the_static_buffer(gemm, fields, dim, num_dense, hidden, shards, batch, lookups, most):
     """Models that antdt_bind_static has always accepted: `most` is what they needed before the loss kernel's and the
     reduction's partial sums had memory of their own."""
     m = good_model()
@@ -102,7 +103,7 @@ def test_workspace_of_fp32_models_at_the_static_buffer(fields, dim, num_dense, h
     m.num_layers = len(sizes) - 1
     for i, w in enumerate(sizes):
         m.layer_sizes[i] = w
-    m.gemm_dtype, m.max_shards, m.max_batch, m.max_nnz = 0, shards, batch, lookups
+    m.gemm_dtype, m.max_shards, m.max_batch, m.max_nnz = gemm, shards, batch, lookups
     assert A.Context(m).workspace_bytes() <= most <= 32 << 20
 
 
