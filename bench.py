@@ -34,16 +34,16 @@ MEASURED_TRAFFIC = {
         "pool": (64.2e6, "embed.hip"),
         "sparse_adagrad": (192.2e6, "coalesce.hip"), "seg_reduce_long": (5.2e6, "coalesce.hip"),
     },
-    "cfg3": {"sparse_adagrad": (664.7e6, "coalesce.hip"), "gemm_wgrad": (529.6e6, "gemm.hip"),
+    "cfg3": {"sparse_adagrad": (664.7e6, "coalesce.hip"), "gemm_wgrad": (529.7e6, "gemm.hip"),
              "pool": (179.9e6, "embed.hip")},
-    "cfg4": {"sparse_adagrad": (5047.4e6, "coalesce.hip"), "wgrad_adagrad": (2046.7e6, "gemm.hip"),
+    "cfg4": {"sparse_adagrad": (5047.2e6, "coalesce.hip"), "wgrad_adagrad": (2048.9e6, "gemm.hip"),
              "pool": (1156.3e6, "embed.hip")},
     "cfg5": {"adam": (15032.4e6, "optim.hip")},
-    "sha1": {"gemm.hip": "6796c0f40b5864f32d3660f69ec733d2fbf3d85c",
+    "sha1": {"gemm.hip": "8a48fb9a08041f7115a56a350e392f73c305e062",
              "embed.hip": "87a1b7f61b5910b7a97e45e3c92ffc2864dd8c55",
              "coalesce.hip": "efd3807105898269ff08e64a2635a027ac729c34",
              "optim.hip": "10a9d8df954dfd1c5c03af1b0ba1d46512dc8303",
-             "ctx.hip": "00febdac1c47c54e59edd3b813aa527b6fdfaf30"},
+             "ctx.hip": "2a592045432b7f20803fbae63f0f5f294d100427"},
 }
 
 
