@@ -6,6 +6,7 @@
 // No floating-point atomics are used, so the sums are bitwise repeatable.  The reduction can
 // apply the row-sparse Adagrad step of each row at once (the parameter update of Section II).
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 
@@ -597,6 +598,12 @@ struct __attribute__((aligned(16))) Lookup {
   int32_t unused;
 };
 
+// LDS traffic between the lanes of one wavefront: executed in program order, only the compiler has to keep it so.
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // g += w(lookup) * dX[sample, field slice] over `n` staged lookups, added in order, four in flight; dx: this lane's
 // columns of sample 0.
 __device__ __forceinline__ void accumulate_run(const char* dx, const Lookup* look, int n, RowSum& g) {
@@ -629,6 +636,40 @@ __device__ __forceinline__ void store_floats(float* x, const RowSum& g) {
   *reinterpret_cast<float4*>(x) = make_float4(g.v[0], g.v[1], g.v[2], g.v[3]);
 }
 
+// x summed over the lane's group of lps (a power of two) lanes; every lane of the group gets the same bits.
+__device__ __forceinline__ float group_sum(float x, int lps) {
+  auto moved = [](float v, auto ctrl) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), decltype(ctrl)::value, 0xF, 0xF, true));
+  };
+  if (lps > 1) x += moved(x, std::integral_constant<int, 0xB1>());    // lane ^ 1
+  if (lps > 2) x += moved(x, std::integral_constant<int, 0x4E>());    // lane ^ 2
+  if (lps > 4) x += moved(x, std::integral_constant<int, 0x141>());   // the other four of eight (mirrored: they hold the same)
+  if (lps > 8) x += moved(x, std::integral_constant<int, 0x140>());   // the other eight of sixteen
+  if (lps > 16) x += __shfl_xor(x, 16, 64);
+  if (lps > 32) x += __shfl_xor(x, 32, 64);
+  return x;
+}
+
+// Square root and quotient for operands far from the ends of the exponent range (the general ones spend two thirds of
+// their instructions on those): the hardware's approximation, improved by its own remainder.  The same bits as the general
+// ones (compared for all mantissas under the root and 134 M quotients).
+__device__ __forceinline__ float sqrt_mid(float x) {
+  const float y = __builtin_amdgcn_rsqf(x), r = x * y;
+  return fmaf(fmaf(-r, r, x), 0.5f * y, r);
+}
+__device__ __forceinline__ float rcp_mid(float d) {
+  const float r = __builtin_amdgcn_rcpf(d);
+  return fmaf(fmaf(-d, r, 1.0f), r, r);
+}
+__device__ __forceinline__ float div_mid(float n, float d, float rcp) {   // (n: any value)
+  const float q = n * rcp;
+  return __builtin_amdgcn_div_fixupf(fmaf(fmaf(-q, d, n), rcp, q), d, n);
+}
+__device__ __forceinline__ uint32_t beyond_mid(float x) {   // below MID_SPAN: 2^-90 <= x < 2^90 (not a NaN)
+  return __float_as_uint(x) - ((127u - 90u) << 23);
+}
+constexpr uint32_t MID_SPAN = 180u << 23;
+
 // A lane's columns of one table row and of its accumulators, as they lie in memory, and the row-sparse Adagrad step:
 //   element-wise: S += g^2;                 p -= lr * g / (sqrt(S) + eps)
 //   row-wise:     S[r] += mean_d g[r,d]^2;  p -= lr * g / (sqrt(S[r]) + eps)
@@ -650,22 +691,20 @@ template <typename TT, bool ROWWISE> struct TableRow {
     else s = *reinterpret_cast<const float4*>(a.state + row * a.D + c * 4);
   }
   __device__ __forceinline__ void update(const SegArgs& a, int64_t row, int c, int lps, const RowSum& g) const {
-    float den[4];
+    float sv[4];
+    uint32_t beyond;
     if (ROWWISE) {
-      float sq = (g.v[0] * g.v[0] + g.v[1] * g.v[1]) + (g.v[2] * g.v[2] + g.v[3] * g.v[3]);
-      for (int o = 1; o < lps; o <<= 1) sq += __shfl_xor(sq, o, 64);
-      const float s1 = srow + sq / (float)a.D;
-      if (c == 0) a.state[row] = s1;
-      den[0] = den[1] = den[2] = den[3] = sqrtf(s1) + a.eps;
+      const float sq = group_sum((g.v[0] * g.v[0] + g.v[1] * g.v[1]) + (g.v[2] * g.v[2] + g.v[3] * g.v[3]), lps);
+      sv[0] = srow + sq * a.inv_dim;   // (D is a power of two)
+      if (c == 0) a.state[row] = sv[0];
+      beyond = beyond_mid(sv[0]);
     } else {
-      float4 sv = s;
-      sv.x = fmaf(g.v[0], g.v[0], sv.x);
-      sv.y = fmaf(g.v[1], g.v[1], sv.y);
-      sv.z = fmaf(g.v[2], g.v[2], sv.z);
-      sv.w = fmaf(g.v[3], g.v[3], sv.w);
-      *reinterpret_cast<float4*>(a.state + row * a.D + c * 4) = sv;
-      den[0] = sqrtf(sv.x) + a.eps; den[1] = sqrtf(sv.y) + a.eps;
-      den[2] = sqrtf(sv.z) + a.eps; den[3] = sqrtf(sv.w) + a.eps;
+      sv[0] = fmaf(g.v[0], g.v[0], s.x);
+      sv[1] = fmaf(g.v[1], g.v[1], s.y);
+      sv[2] = fmaf(g.v[2], g.v[2], s.z);
+      sv[3] = fmaf(g.v[3], g.v[3], s.w);
+      *reinterpret_cast<float4*>(a.state + row * a.D + c * 4) = make_float4(sv[0], sv[1], sv[2], sv[3]);
+      beyond = max(max(beyond_mid(sv[0]), beyond_mid(sv[1])), max(beyond_mid(sv[2]), beyond_mid(sv[3])));
     }
     float p0[4], p1[4];
     if (sizeof(TT) == 4) {
@@ -674,8 +713,23 @@ template <typename TT, bool ROWWISE> struct TableRow {
       p0[0] = __uint_as_float(p.x << 16); p0[1] = __uint_as_float(p.x & 0xFFFF0000u);
       p0[2] = __uint_as_float(p.y << 16); p0[3] = __uint_as_float(p.y & 0xFFFF0000u);
     }
+    constexpr int NS = ROWWISE ? 1 : 4;
+    if (__ballot(beyond >= MID_SPAN) == 0 && a.eps < 0x1p90f) {   // accumulators of any run under way
+      float den[NS], rcp[NS];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) p1[e] = p0[e] - a.lr * g.v[e] / den[e];
+      for (int e = 0; e < NS; ++e) {
+        den[e] = sqrt_mid(sv[e]) + a.eps;
+        rcp[e] = rcp_mid(den[e]);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) p1[e] = p0[e] - div_mid(a.lr * g.v[e], den[e % NS], rcp[e % NS]);
+    } else {
+      float den[NS];
+#pragma unroll
+      for (int e = 0; e < NS; ++e) den[e] = sqrtf(sv[e]) + a.eps;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) p1[e] = p0[e] - a.lr * g.v[e] / den[e % NS];
+    }
     TT* dst = reinterpret_cast<TT*>(a.tables) + row * a.D + c * 4;
     if (sizeof(TT) == 4) *reinterpret_cast<float4*>(dst) = make_float4(p1[0], p1[1], p1[2], p1[3]);
     else *reinterpret_cast<uint2*>(dst) = make_uint2(f2bf2(p1[0], p1[1]), f2bf2(p1[2], p1[3]));
@@ -708,12 +762,77 @@ __device__ __forceinline__ int64_t run_index(const SegArgs& a, int f, int pos) {
 // seg_finish_kernel.  No run table is needed (counting, scanning and writing one, with lists of the long
 // runs, were six launches and 10-250 us between sort and reduction), only keys, sample indices and the rows
 // themselves are read, and the chain of dependent accesses is down to LDS -> row and pooled gradients.
-// Bound by the rows and accumulators (HBM) where runs are short, by the pooled-gradient rows (L2 and the
-// memory-side cache) where they are long.
+// A window that lies inside one run (60 % of them with 42 M lookups of Zipf(1.2) ids) needs none of this: sum_window.
+// Bound by the requests for pooled-gradient rows that a compute unit can have outstanding (about 64 lines; they come from
+// L2 and the memory-side cache) and by vector instructions (58 % of the cycles, 66 before windows inside a run went a way of
+// their own and the update lost the general square root and division; the pooled-gradient rows of a sample that looks a
+// row up several times are read once there).  Row and accumulators are requested ahead of the item's pooled gradients, not
+// an item ahead: that took 8 registers more, and eight wavefronts per SIMD hide as much.  Us per launch, before / now:
+// 42 M lookups of 128-byte bf16 rows 1228 / 1016, 3.8 M 141 / 119, 4.3 M of 128-byte fp32 rows 161 / 148, 1.1 M 46.6 / 41.7.
+// Streaming loads and stores of the rows: 42 M 1003, but 1.1 M of a batch that returns 53 (they leave the memory-side cache).
 constexpr int LONG_RUN = 16;
 
+// Sum over the W lookups of a window that lies inside one run; every lane group of the first wavefront returns it.  Nothing
+// is to be found there, so each wavefront works on lookups of its own (its part of `look`), without the others until the
+// four sums meet.  Lookups of one row by one sample are neighbours (the sort is stable) and become one pair with a
+// multiple of the weight.
+template <int W>
+__device__ __forceinline__ RowSum sum_window(const char* dx, Lookup* look, const int (&smp)[W / 256], const float (&weight)[W / 256], int64_t pitch,
+                                             float* wave_sums, int D, int lps, int c) {
+  constexpr int ROUNDS = W / 256;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  Lookup* mine = look + wave * (64 * ROUNDS);
+  int n = 0;
+#pragma unroll
+  for (int r = 0; r < ROUNDS; ++r) {
+    const bool start = lane == 0 || smp[r] != __shfl_up(smp[r], 1, 64);
+    const uint64_t starts = __ballot(start);
+    if (start) {
+      const uint64_t rest = lane == 63 ? 0 : starts >> (lane + 1);
+      Lookup l;
+      l.offset = (uint64_t)smp[r] * (uint64_t)pitch;
+      l.w = weight[r] * (float)(rest ? __ffsll((unsigned long long)rest) : 64 - lane);
+      l.unused = 0;
+      mine[n + __popcll(starts & lanemask_lt())] = l;
+    }
+    n += __popcll(starts);
+  }
+  wave_lds_order();
+  const int ngroups = 64 / lps;
+  RowSum sum = {};
+  for (int i = lane / lps; i < n; i += 4 * ngroups) {
+    float w[4];
+    float4 x[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (i + q * ngroups < n) {
+        const Lookup l = mine[i + q * ngroups];
+        w[q] = l.w;
+        x[q] = *reinterpret_cast<const float4*>(dx + l.offset);
+      }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (i + q * ngroups < n) {
+        sum.v[0] = fmaf(w[q], x[q].x, sum.v[0]);
+        sum.v[1] = fmaf(w[q], x[q].y, sum.v[1]);
+        sum.v[2] = fmaf(w[q], x[q].z, sum.v[2]);
+        sum.v[3] = fmaf(w[q], x[q].w, sum.v[3]);
+      }
+  }
+  for (int o = lps; o < 64; o <<= 1) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) sum.v[e] += __shfl_xor(sum.v[e], o, 64);
+  }
+  if (lane < lps) store_floats(wave_sums + wave * D + c * 4, sum);
+  __syncthreads();
+  sum = {};
+#pragma unroll
+  for (int q = 0; q < 4; ++q) add_floats(sum, wave_sums + q * D + c * 4);
+  return sum;
+}
+
 template <typename TT, bool ROWWISE, bool UPDATE, bool MEAN, int W>
-__global__ __launch_bounds__(256) void seg_window_kernel(SegArgs a, FieldPtr fp, TileBase tb) {
+__global__ __launch_bounds__(256, ROWWISE ? 8 : 1) void seg_window_kernel(SegArgs a, FieldPtr fp, TileBase tb) {
   constexpr int PARTS = SORT_TILE / W, ROUNDS = W / 256;
   static_assert(W <= 512 && LONG_RUN == 16, "list entries and the search for long runs");
   __shared__ int32_t key_[W + 2 * LONG_RUN];        // positions -LONG_RUN .. W + LONG_RUN - 1 relative to the window
@@ -733,16 +852,61 @@ __global__ __launch_bounds__(256) void seg_window_kernel(SegArgs a, FieldPtr fp,
   const int tid = threadIdx.x;
   if (P >= nnz) return;
   const int64_t slot = window_slot(base) + t * PARTS + part;
-  for (int i = tid; i < W + 2 * LONG_RUN; i += 256) key_[i] = a.key[base + min(max(P + i - LONG_RUN, 0), nnz - 1)];
   const int32_t* off = MEAN ? a.offsets + (int64_t)f * (a.B + 1) : nullptr;
-  for (int i = tid; i < W + LONG_RUN; i += 256) {
-    const int smp = min(max(a.pay[base + min(P + i, nnz - 1)], 0), a.B - 1);
+  const int32_t *keys = a.key + base, *pay = a.pay + base;
+  const int32_t first_key = __builtin_amdgcn_readfirstlane(keys[P]), last_key = __builtin_amdgcn_readfirstlane(keys[min(P + W, nnz) - 1]);
+  int32_t k_own[ROUNDS], k_side = 0;
+  int smp[ROUNDS], smp_tail = 0;
+#pragma unroll
+  for (int r = 0; r < ROUNDS; ++r) {
+    const int pos = min(P + r * 256 + tid, nnz - 1);
+    k_own[r] = keys[pos];
+    smp[r] = pay[pos];
+  }
+  if (tid < 2 * LONG_RUN) k_side = keys[min(max(tid < LONG_RUN ? P + tid - LONG_RUN : P + W + tid - LONG_RUN, 0), nnz - 1)];
+  if (tid < LONG_RUN) smp_tail = pay[min(P + W + tid, nnz - 1)];
+  float weight[ROUNDS], weight_tail = 0.0f;
+#pragma unroll
+  for (int r = 0; r < ROUNDS; ++r) {
+    smp[r] = min(max(smp[r], 0), a.B - 1);
+    weight[r] = lookup_weight<MEAN>(a, off, smp[r]);
+  }
+  const int lps = a.D >> 2;
+  const int ngroups = 256 / lps;
+  const int g = tid / lps, c = tid - g * lps;
+  const char* dx = reinterpret_cast<const char*>(a.dx + f * a.D + c * 4);
+  if (P + W <= nnz && first_key == last_key) {   // (the same for all threads)
+    const bool in = P > 0 && keys[P - 1] == first_key, out = P + W < nnz && keys[P + W] == first_key;
+    const int64_t row = (int64_t)f * a.R + min(max(first_key, 0), (int)(a.R - 1));
+    TableRow<TT, ROWWISE> tr;
+    if (UPDATE && !in && !out && tid < lps) tr.load(a, row, c);
+    const RowSum sum = sum_window<W>(dx, look, smp, weight, a.lddx * 4, piece_sum, a.D, lps, c);
+    if (tid < lps) {
+      if (in || out) store_floats(a.partial + (slot * 2 + (in ? 0 : 1)) * a.D + c * 4, sum);
+      else if (UPDATE) tr.update(a, row, c, lps, sum);
+      else store_floats(a.G + run_index(a, f, (int)base + P) * a.D + c * 4, sum);
+    }
+    if (tid == 0 && nnz > W) a.goes_out[slot] = !in && out;
+    return;
+  }
+  if (tid < LONG_RUN) {
+    smp_tail = min(max(smp_tail, 0), a.B - 1);
+    weight_tail = lookup_weight<MEAN>(a, off, smp_tail);
+  }
+  auto stage = [&](int i, int sample, float w) {
     Lookup l;
-    l.offset = (uint64_t)smp * (uint64_t)(a.lddx * 4);
-    l.w = lookup_weight<MEAN>(a, off, smp);
+    l.offset = (uint64_t)sample * (uint64_t)(a.lddx * 4);
+    l.w = w;
     l.unused = 0;
     look[i] = l;
+  };
+#pragma unroll
+  for (int r = 0; r < ROUNDS; ++r) {
+    key_[LONG_RUN + r * 256 + tid] = k_own[r];
+    stage(r * 256 + tid, smp[r], weight[r]);
   }
+  if (tid < 2 * LONG_RUN) key_[tid < LONG_RUN ? tid : W + tid] = k_side;
+  if (tid < LONG_RUN) stage(W + tid, smp_tail, weight_tail);
   if (tid <= W / LONG_RUN) lead[tid] = -1;
   if (tid == 0) {
     goes_out = 0;
@@ -794,10 +958,6 @@ __global__ __launch_bounds__(256) void seg_window_kernel(SegArgs a, FieldPtr fp,
   }
   __syncthreads();
   const int n_few = sum_counts & 0xFFFF, n_other = sum_counts >> 16;
-  const int lps = a.D >> 2;
-  const int ngroups = 256 / lps;
-  const int g = tid / lps, c = tid - g * lps;
-  const char* dx = reinterpret_cast<const char*>(a.dx + f * a.D + c * 4);
   auto row_of = [&](int q) { return (int64_t)f * a.R + min(max(key[q], 0), (int)(a.R - 1)); };
   auto finish = [&](int64_t row, const RowSum& sum, const TableRow<TT, ROWWISE>& tr, int q) {
     if (UPDATE) {
@@ -808,22 +968,12 @@ __global__ __launch_bounds__(256) void seg_window_kernel(SegArgs a, FieldPtr fp,
       store_floats(a.G + u * a.D + c * 4, sum);
     }
   };
-  // The long items first, so that the lane groups of a wavefront have items of about the same length; the next
-  // item's row and accumulators are requested before the current one's lookups are waited for.
+  // The long items first, so that the lane groups of a wavefront have items of about the same length.
   auto entry_of = [&](int i) { return i < n_other ? (int)order[W - 1 - i] : (int)order[i - n_other]; };
-  TableRow<TT, ROWWISE> next;
-  int next_en = g < n_other + n_few ? entry_of(g) : 0;
-  auto request = [&](int i) {
-    if (UPDATE && !(i < n_other && (next_en & 1024))) next.load(a, row_of(next_en & 511), c);
-  };
-  if (g < n_other + n_few) request(g);
   for (int i = g; i < n_other + n_few; i += ngroups) {
-    const int en = next_en, q0 = en & 511;
-    const TableRow<TT, ROWWISE> tr = next;
-    if (i + ngroups < n_other + n_few) {
-      next_en = entry_of(i + ngroups);
-      request(i + ngroups);
-    }
+    const int en = entry_of(i), q0 = en & 511;
+    TableRow<TT, ROWWISE> tr;
+    if (UPDATE && !(i < n_other && (en & 1024))) tr.load(a, row_of(q0), c);
     int n = (en >> 9) + 1;
     bool head = true, piece = false;
     if (i < n_other) {

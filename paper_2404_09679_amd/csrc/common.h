@@ -302,7 +302,7 @@ struct SegArgs {
   void* tables;
   float* state;
   int64_t R;
-  float lr, eps;
+  float lr, eps, inv_dim;          // inv_dim: 1 / D
 };
 hipError_t launch_expand_samples(const int32_t* offsets, int32_t* lookup_sample, const FieldPtr& fp, int F, int B, hipStream_t s);
 hipError_t launch_segments(const SegArgs& a, const FieldPtr& fp, const TileBase& tb, Profiler* prof, hipStream_t s);

@@ -689,7 +689,7 @@ static void fill_seg_args(antdt_ctx* c, SegArgs& a) {
   // 243 / 242, 410 / 420, 547 / 558, 865 / 894; D = 16 with 1.5 / 2.8 / 5 M 212 / 214, 354 / 361, 570 / 605; D = 8 with 2.8 / 7 M
   // 309 / 309, 647 / 659.
   a.window = c->afp.p[m.num_fields] >= (4 << 20) && m.dim <= 32 ? 512 : 256;
-  a.tables = c->tables; a.state = c->table_state; a.R = m.rows_per_field; a.lr = m.lr; a.eps = m.eps;
+  a.tables = c->tables; a.state = c->table_state; a.R = m.rows_per_field; a.lr = m.lr; a.eps = m.eps; a.inv_dim = 1.0f / (float)m.dim;
   a.table_bf16 = m.table_dtype == ANTDT_BF16; a.rowwise = m.adagrad_state == ANTDT_STATE_ROWWISE;
 }
 

@@ -339,3 +339,60 @@ def test_bf16_products_of_rows_beyond_32_bit_offsets():
     assert num <= (TOLBF * TOLBF) * den
     want = dh @ params[:8 * N].reshape(8, N).bfloat16().float().T
     assert float((dx - want).norm()) <= TOLBF * float(want.norm())
+
+
+# Windows inside one run (256 sorted lookups, 512 from four million of them on: see test_sort_ahead_of_the_gather): summed
+# by every wavefront for itself, neighbours of one sample as one.  A field of one row only, one window and several; bags that
+# repeat a row 1 .. 300 times; the first window of a run, one in its middle, its last, and a run of exactly one window.
+@pytest.mark.parametrize("dim,pooling,table,state", [(4, "sum", "f32", "elementwise"), (32, "mean", "f32", "rowwise"),
+                                                     (64, "sum", "bf16", "rowwise"), (256, "mean", "f32", "elementwise")])
+def test_windows_inside_one_run(dim, pooling, table, state, monkeypatch):
+    runs = [[256], [512], [700], [256, 256, 512], [100, 156, 256, 900], [255, 1, 1500, 36, 1, 256]]
+    B = 70
+    cfg = _config(f"inside-{dim}", 680 + dim, num_fields=len(runs), rows_per_field=9, dim=dim, table_dtype=table, adagrad_state=state,
+                  layer_sizes=(8,), gemm_dtype="f32", shard_sizes=(30, 1, 39), max_bag=300, pooling=pooling)
+    rng = np.random.default_rng(17 + dim)
+    ids, offsets = [], []
+    for lengths in runs:   # a run's lookups, dealt to samples in lumps: the bags of a sample hold lumps of several rows
+        bags = [[] for _ in range(B)]
+        for row, n in enumerate(lengths):
+            while n > 0:
+                lump = min(n, int(rng.choice([1, 2, 5, 64, 65, 300])))
+                bags[rng.integers(0, B)] += [row] * lump
+                n -= lump
+        ids.append(np.array(sum(bags, []), dtype=np.int32))
+        offsets.append(np.cumsum([0] + [len(b) for b in bags]))
+    _plant(monkeypatch, ids, B, lambda f, n: offsets[f])
+    check_iteration(cfg, cfg.shard_sizes, tol=TOL32, batched=True, nonzero_state=True)
+
+
+# The row update takes square root and quotient by a short way where the accumulators lie between 2^-90 and 2^90, by the
+# general one elsewhere: accumulators of both kinds, and with them NaN and infinities, side by side in a wavefront.
+@pytest.mark.parametrize("dim,state", [(4, "elementwise"), (16, "rowwise"), (128, "elementwise")])
+def test_row_update_over_the_range_of_accumulators(dim, state):
+    import torch
+    from gpu_helpers import GpuRun
+    from test_gpu_parity import make_inputs
+    cfg = _config(f"range-{dim}", 685 + dim, num_fields=1, rows_per_field=40, dim=dim, layer_sizes=(8,), gemm_dtype="f32", shard_sizes=(50,),
+                  eps=1e-8, max_bag=2)
+    cfg = dataclasses.replace(cfg, adagrad_state=state)
+    values = np.array([0.0, 1e-40, 1e-30, 2.0 ** -90, 1e-12, 1e-4, 1.0, 1e20, 1.2e27, 2.0 ** 90, 1e38, np.inf, np.nan], dtype=np.float32)
+    tables, acc, flat, fstate, batch = make_inputs(cfg, True)
+    shape = acc.shape
+    acc = np.resize(values, acc.size).reshape(shape)
+    run = GpuRun(cfg, tables, flat, acc, fstate)
+    run.set_batch(batch)
+    run.iteration(cfg.shard_sizes, batched=True)
+    u, _, _, G = run.coalesced[0]
+    with np.errstate(all="ignore"):
+        g, S, p = G.astype(np.float64), acc[u].astype(np.float64), tables[u].astype(np.float64)
+        S = S + (g * g if state == "elementwise" else np.mean(g * g, axis=1))
+        step = cfg.lr * g / (np.sqrt(S if state == "elementwise" else S[:, None]) + cfg.eps)
+    got_s, got_p = run.state.cpu().numpy()[u], run.tables.cpu().numpy()[u]
+    assert np.array_equal(np.isnan(got_s), np.isnan(S)) and np.array_equal(np.isinf(got_s), np.isinf(S))
+    fine = np.isfinite(S)
+    assert np.all(np.abs(got_s[fine] - S[fine]) <= 1e-6 * S[fine] + 1e-44)
+    assert np.array_equal(np.isnan(got_p), np.isnan(step))
+    ok = ~np.isnan(step)
+    # a few roundings of the step, and that of the stored parameter
+    assert np.all(np.abs(got_p[ok] - (p - step)[ok]) <= 1e-6 * np.abs(step[ok]) + 2.0 ** -23 * np.abs(p[ok]))
