@@ -27,6 +27,23 @@ __device__ __forceinline__ uint64_t lanemask_lt() {
   return lane == 0 ? 0ull : (~0ull >> (64 - lane));
 }
 
+// LDS traffic between the lanes of one wavefront: executed in program order, only the compiler has to keep it so.
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// x summed over the lanes up to this one.
+__device__ __forceinline__ uint32_t wave_prefix(uint32_t x) {
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, false);   // rows of 16 lanes: one lane down, ...
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, false);
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, false);
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, false);   // ... eight
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false);   // last lane of a row to the next row (rows 1 and 3)
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false);   // lane 31 to rows 2 and 3
+  return x;
+}
+
 // Tile T of all fields' tiles -> (field, tile of the field): how many fields end at or before it, counted by the
 // lanes of the wavefront (one load of the table instead of a chain of them).
 __device__ __forceinline__ void field_of_tile(const TileBase& tb, int T, int& f, int& t) {
@@ -56,33 +73,38 @@ __device__ __forceinline__ bool tile_of_block(const TileBase& tb, int F, int par
 
 // ----------------------------------------------------------------- sort
 // Histogram layout: hist[(tile_base[f] + tile) << rb | digit] (digits of a tile contiguous);
-// digit_base[f << rb | digit] = number of the field's keys with a smaller digit.
+// digit_total[f << rb | digit] = number of the field's keys with the digit.
 
-// Digit histogram of one tile.
+// Digit histogram of one tile.  Hot rows make many lanes count one digit, and LDS adds to one address go one after
+// the other: every digit has copies of its counter, and the lanes take turns with them (42 M lookups of 21 bits: 60 / 102 / 121
+// us a pass with one counter, the keys more and more in order; 54 with eight, the blocks' loads and their latency).
 __global__ __launch_bounds__(SORT_THREADS) void sort_hist_kernel(const int32_t* keys, uint32_t* hist,
                                                                  FieldPtr fp, TileBase tb, int F, int shift, int rb) {
-  __shared__ uint32_t h[MAX_BINS];
+  constexpr int LOG_COUNTERS = 12, LOG_COPIES = 3;
+  __shared__ uint32_t h[1 << LOG_COUNTERS];
   int f, t, part;
   if (!tile_of_block(tb, F, 1, f, t, part)) return;
   const int nb = 1 << rb;
+  const int cb = min(LOG_COPIES, LOG_COUNTERS - rb);   // log2 of the copies
   const int64_t base = fp.p[f];
-  const int nnz = (int)(fp.p[f + 1] - base);
+  const int count = min((int)(fp.p[f + 1] - base) - t * SORT_TILE, SORT_TILE);
+  const int32_t* in = keys + base + (int64_t)t * SORT_TILE;
   int32_t k[SORT_ITEMS];
 #pragma unroll
-  for (int i = 0; i < SORT_ITEMS; ++i) {  // all loads first (clamped), so that they overlap
-    const int pos = min(t * SORT_TILE + i * SORT_THREADS + (int)threadIdx.x, nnz - 1);
-    k[i] = keys[base + pos];
-  }
-  for (int d = threadIdx.x; d < nb; d += SORT_THREADS) h[d] = 0;
+  for (int i = 0; i < SORT_ITEMS; ++i) k[i] = in[min(i * SORT_THREADS + (int)threadIdx.x, count - 1)];   // (all loads first)
+  for (int d = threadIdx.x; d < nb << cb; d += SORT_THREADS) h[d] = 0;
   __syncthreads();
+  const int copy = threadIdx.x & ((1 << cb) - 1);
 #pragma unroll
-  for (int i = 0; i < SORT_ITEMS; ++i) {
-    const int pos = t * SORT_TILE + i * SORT_THREADS + threadIdx.x;
-    if (pos < nnz) atomicAdd(&h[((uint32_t)k[i] >> shift) & (nb - 1)], 1u);
-  }
+  for (int i = 0; i < SORT_ITEMS; ++i)
+    if (i * SORT_THREADS + (int)threadIdx.x < count) atomicAdd(&h[((((uint32_t)k[i] >> shift) & (nb - 1)) << cb) + copy], 1u);
   __syncthreads();
   uint32_t* out = hist + ((int64_t)(tb.t[f] + t) << rb);
-  for (int d = threadIdx.x; d < nb; d += SORT_THREADS) out[d] = h[d];
+  for (int d = threadIdx.x; d < nb; d += SORT_THREADS) {
+    uint32_t sum = 0;
+    for (int c = 0; c < 1 << cb; ++c) sum += h[(d << cb) + ((c + d) & ((1 << cb) - 1))];   // (turned: neighbours read different banks)
+    out[d] = sum;
+  }
 }
 
 __device__ __forceinline__ void write_sample_weights(float* sample_w, const ShardTab& tab, int s) {
@@ -91,51 +113,51 @@ __device__ __forceinline__ void write_sample_weights(float* sample_w, const Shar
   if (s < tab.start[k] + tab.len[k]) sample_w[s] = tab.w[k];
 }
 
-// One block per field, one thread per digit: the counts of a digit are replaced by their
-// exclusive prefix over the tiles, and the digit totals by their exclusive prefix over digits.  Further blocks
-// (first pass) write the aggregation weight of every sample.
-__global__ __launch_bounds__(MAX_BINS) void sort_scan_kernel(uint32_t* hist, uint32_t* digit_base, TileBase tb, int F, int rb,
-                                                             float* sample_w, ShardTab tab) {
-  __shared__ uint32_t wsum[MAX_BINS / 64];
-  const int f = blockIdx.x;
+// The counts of a digit are replaced by their exclusive prefix over the tiles, and their total goes to digit_total.  A block has up to
+// SCAN_DIGITS digits of a field; a thread has a digit and one stretch of the tiles, which it walks twice (their sum; their
+// prefixes).  Bound by the chain of loads, and by what one compute unit can fetch (the counts were written by other XCDs): one
+// block per field, a chain of loads for each digit, took 18.8 us for 204 tiles of 128 digits, now 11.6, and 11 for 80 of
+// 1024, now 7.5.
+// Further blocks (first pass) write the aggregation weight of every sample.
+constexpr int SCAN_THREADS = 1024, SCAN_DIGITS = 128;
+__global__ __launch_bounds__(SCAN_THREADS) void sort_scan_kernel(uint32_t* hist, uint32_t* digit_total, TileBase tb, int F, int rb,
+                                                                 float* sample_w, ShardTab tab) {
+  __shared__ uint32_t sums[SCAN_THREADS];
+  const int nb = 1 << rb, digits = min(nb, SCAN_DIGITS), groups = nb / digits;
+  const int f = (int)blockIdx.x / groups;
   if (f >= F) {
-    write_sample_weights(sample_w, tab, (f - F) * MAX_BINS + (int)threadIdx.x);
+    write_sample_weights(sample_w, tab, ((int)blockIdx.x - F * groups) * SCAN_THREADS + (int)threadIdx.x);
     return;
   }
   const int tiles = tb.t[f + 1] - tb.t[f];
-  const int nb = 1 << rb;
-  const int d = threadIdx.x;
-  uint32_t run = 0;
-  if (d < nb) {
-    uint32_t* h = hist + ((int64_t)tb.t[f] << rb) + d;
-    int t = 0;
-    for (; t + 3 < tiles; t += 4) {  // four independent loads in flight
-      const uint32_t c0 = h[(int64_t)t << rb], c1 = h[(int64_t)(t + 1) << rb];
-      const uint32_t c2 = h[(int64_t)(t + 2) << rb], c3 = h[(int64_t)(t + 3) << rb];
-      h[(int64_t)t << rb] = run;
-      h[(int64_t)(t + 1) << rb] = run + c0;
-      h[(int64_t)(t + 2) << rb] = run + c0 + c1;
-      h[(int64_t)(t + 3) << rb] = run + c0 + c1 + c2;
-      run += c0 + c1 + c2 + c3;
-    }
-    for (; t < tiles; ++t) {
-      const uint32_t c = h[(int64_t)t << rb];
-      h[(int64_t)t << rb] = run;
-      run += c;
-    }
-  }
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  uint32_t incl = run;
+  const int parts = SCAN_THREADS / digits, dl = threadIdx.x & (digits - 1), part = threadIdx.x / digits;
+  const int d = ((int)blockIdx.x - f * groups) * digits + dl;
+  const int t0 = tiles * part / parts, t1 = tiles * (part + 1) / parts;
+  uint32_t* h = hist + ((int64_t)tb.t[f] << rb) + d;
+  auto walk = [&](uint32_t run, bool store) {
+    for (int t = t0; t < t1; t += 4) {
+      uint32_t c[4];
 #pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t v = __shfl_up(incl, o, 64);
-    if (lane >= o) incl += v;
-  }
-  if (lane == 63) wsum[w] = incl;
+      for (int q = 0; q < 4; ++q) c[q] = h[(int64_t)min(t + q, t1 - 1) << rb];
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (t + q < t1) {
+          if (store) h[(int64_t)(t + q) << rb] = run;
+          run += c[q];
+        }
+    }
+    return run;
+  };
+  sums[threadIdx.x] = walk(0, false);
   __syncthreads();
-  uint32_t wbase = 0;
-  for (int i = 0; i < w; ++i) wbase += wsum[i];
-  if (d < nb) digit_base[((int64_t)f << rb) + d] = wbase + incl - run;
+  uint32_t run = 0, total = 0;
+  for (int q = 0; q < parts; ++q) {
+    const uint32_t c = sums[q * digits + dl];
+    if (q < part) run += c;
+    total += c;
+  }
+  walk(run, true);
+  if (part == 0) digit_total[((int64_t)f << rb) + d] = total;
 }
 
 // Lanes (among the valid ones) that hold the same digit.  Per bit: the lane's bit spread over a word, one compare
@@ -156,138 +178,156 @@ __device__ __forceinline__ uint64_t same_digit(uint32_t d, int rb, bool valid) {
 // Stable scatter of one tile.  Wave w owns the contiguous slice w of the tile and walks it in
 // rounds of 64 keys; lanes holding equal digits find each other with one
 // ballot per digit bit, the per-wave running count of the digit lives in LDS.
-__global__ __launch_bounds__(SORT_THREADS) void sort_scatter_kernel(
-    const int32_t* keys_in, const int32_t* pay_in, int32_t* keys_out, int32_t* pay_out, const uint32_t* hist,
-    const uint32_t* digit_base, FieldPtr fp, TileBase tb, int F, int shift, int rb) {
-  __shared__ uint32_t cnt[SORT_WAVES][MAX_BINS];
-  __shared__ uint32_t gbase[MAX_BINS];
-  int f, t, part;
-  if (!tile_of_block(tb, F, 1, f, t, part)) return;
+// Bound by memory where fields are large (42 M keys in 7-bit digits: 678 MB of compulsory traffic in 134 us, a copy's rate), by
+// vector instructions else (75 an item, a third of them the ballots).  Us a pass, with counters in flat accesses, 32 bits wide,
+// and prefixes by LDS exchange / now: 42 M keys 172 / 134, 4.3 M in 10-bit digits 29.7 / 26, 1.1 M 13.1 / 11.3.
+// FULL: all the tile's keys exist.
+constexpr int DPT = MAX_BINS / SORT_THREADS;   // digits per thread: threadIdx.x + q SORT_THREADS
+struct ScatterLds {
+  union {
+    uint16_t cnt[SORT_WAVES][MAX_BINS];   // (a tile's counts fit 16 bits)
+    int32_t staged[2][SORT_TILE];         // then: the tile sorted by digit (keys, samples)
+  };
+  uint32_t gbase[MAX_BINS];
+  uint16_t dpre[MAX_BINS];
+  uint32_t wsum[2][DPT][SORT_WAVES];
+};
+template <bool FULL>
+__device__ __forceinline__ void scatter_tile(ScatterLds& lds, const int32_t* keys_in, const int32_t* pay_in, int32_t* keys_out, int32_t* pay_out,
+                                             const uint32_t* hb, const uint32_t* totals, int count, int nnz, int shift, int rb) {
+  constexpr int ITEMS = SORT_ITEMS;
   const int nb = 1 << rb;
-  const int64_t base = fp.p[f];
-  const int nnz = (int)(fp.p[f + 1] - base);
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  // first position of every digit's keys of this tile in the output (digits before it in the field +
-  // the digit's keys in earlier tiles): loaded up front with coalesced loads, looked up in LDS
-  const uint32_t* hb = hist + ((int64_t)(tb.t[f] + t) << rb);
-  const uint32_t* db = digit_base + ((int64_t)f << rb);
-  uint32_t gb[MAX_BINS / SORT_THREADS];
+  const int first = w * (64 * ITEMS) + lane;   // item i: position first + 64 i of the tile
+  // The first position of a digit's keys of this tile in the output: digits before it in the field, and the digit's keys in
+  // earlier tiles.  Loaded up front with coalesced loads, looked up in LDS.
+  uint32_t earlier[DPT], total[DPT];
 #pragma unroll
-  for (int q = 0; q < MAX_BINS / SORT_THREADS; ++q) {
-    const int d = min((int)threadIdx.x + q * SORT_THREADS, nb - 1);
-    gb[q] = db[d] + hb[d];
+  for (int q = 0; q < DPT; ++q) {
+    const int d = (int)threadIdx.x + q * SORT_THREADS;
+    earlier[q] = hb[min(d, nb - 1)];
+    total[q] = totals[min(d, nb - 1)];
   }
-  int32_t key[SORT_ITEMS], pay[SORT_ITEMS];
+  int32_t key[ITEMS], pay[ITEMS];
 #pragma unroll
-  for (int i = 0; i < SORT_ITEMS; ++i) {  // all loads first (clamped), so that they overlap
-    const int pos = min(t * SORT_TILE + w * (64 * SORT_ITEMS) + i * 64 + lane, nnz - 1);
-    key[i] = keys_in[base + pos];
-    pay[i] = pay_in[base + pos];
+  for (int i = 0; i < ITEMS; ++i) {  // all loads first (clamped), so that they overlap
+    const int pos = FULL ? first + i * 64 : min(first + i * 64, count - 1);
+    key[i] = keys_in[pos];
+    pay[i] = pay_in[pos];
   }
-  for (int d = threadIdx.x; d < SORT_WAVES * nb; d += SORT_THREADS) cnt[d >> rb][d & (nb - 1)] = 0;
-#pragma unroll
-  for (int q = 0; q < MAX_BINS / SORT_THREADS; ++q)
-    if ((int)threadIdx.x + q * SORT_THREADS < nb) gbase[threadIdx.x + q * SORT_THREADS] = gb[q];
-  __syncthreads();
+  for (int d = lane; d < nb; d += 64) lds.cnt[w][d] = 0;   // (each wavefront its own row)
+  wave_lds_order();
   const uint64_t lt = lanemask_lt();
-  volatile uint32_t* cw = cnt[w];
-  uint32_t rank[SORT_ITEMS];
+  uint32_t rank[ITEMS];
+  auto digit = [&](int32_t k) { return ((uint32_t)k >> shift) & (uint32_t)(nb - 1); };
 #pragma unroll
-  for (int i = 0; i < SORT_ITEMS; ++i) {
-    const int pos = t * SORT_TILE + w * (64 * SORT_ITEMS) + i * 64 + lane;
-    const bool valid = pos < nnz;
-    const uint32_t d = ((uint32_t)key[i] >> shift) & (nb - 1);
+  for (int i = 0; i < ITEMS; ++i) {
+    const bool valid = FULL || first + i * 64 < count;
+    const uint32_t d = digit(key[i]);
     const uint64_t m = same_digit(d, rb, valid);
-    rank[i] = 0;
-    if (valid) {
-      const uint32_t prior = cw[d];
-      rank[i] = prior + (uint32_t)__popcll(m & lt);
-      if ((m & lt) == 0) cw[d] = prior + (uint32_t)__popcll(m);  // lowest lane of the group
-    }
+    const uint32_t prior = lds.cnt[w][d];
+    wave_lds_order();
+    rank[i] = prior + (uint32_t)__popcll(m & lt);
+    if (valid && (m & lt) == 0) lds.cnt[w][d] = (uint16_t)(prior + (uint32_t)__popcll(m));  // lowest lane of the group
+    wave_lds_order();
   }
   __syncthreads();
   // Per digit: the counts of the wavefronts become exclusive prefixes (keys of the digit in
   // earlier wavefronts of the tile), their sum the tile's count of the digit; an exclusive scan of
-  // these counts in digit order gives every key its place in the tile sorted by digit.
-  constexpr int DPT = MAX_BINS / SORT_THREADS;  // digits per thread: d = threadIdx.x + q * SORT_THREADS
-  __shared__ uint32_t dpre[MAX_BINS];
-  __shared__ uint32_t wsum[DPT][SORT_WAVES];
-  uint32_t tot[DPT], incl[DPT];
+  // these counts in digit order gives every key its place in the tile sorted by digit, one of the totals of the
+  // field the place of the digit in the field.
+  uint32_t tot[DPT], incl[DPT], incl_total[DPT];
 #pragma unroll
   for (int q = 0; q < DPT; ++q) {
-    const int d = threadIdx.x + q * SORT_THREADS;
-    uint32_t run = 0;
-    if (d < nb) {
+    tot[q] = incl[q] = incl_total[q] = 0;
+    if (q * SORT_THREADS + (w << 6) < nb) {   // (uniform)
+      const int d = threadIdx.x + q * SORT_THREADS;
+      if (d < nb) {
 #pragma unroll
-      for (int ww = 0; ww < SORT_WAVES; ++ww) {
-        const uint32_t c = cnt[ww][d];
-        cnt[ww][d] = run;
-        run += c;
+        for (int ww = 0; ww < SORT_WAVES; ++ww) {
+          const uint32_t c = lds.cnt[ww][d];
+          lds.cnt[ww][d] = (uint16_t)tot[q];
+          tot[q] += c;
+        }
       }
+      incl[q] = wave_prefix(tot[q]);
+      incl_total[q] = wave_prefix(d < nb ? total[q] : 0);
     }
-    tot[q] = run;
-    incl[q] = run;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const uint32_t v = __shfl_up(incl[q], o, 64);
-      if (lane >= o) incl[q] += v;
+    if (lane == 63) {
+      lds.wsum[0][q][w] = incl[q];
+      lds.wsum[1][q][w] = incl_total[q];
     }
-    if (lane == 63) wsum[q][w] = incl[q];
   }
   __syncthreads();
   {
-    uint32_t before = 0;  // keys of the tile with a digit handled by an earlier (q, wavefront)
+    uint32_t before = 0, before_total = 0;  // keys with a digit handled by an earlier (q, wavefront): of the tile, of the field
 #pragma unroll
     for (int q = 0; q < DPT; ++q) {
-      uint32_t mine = before;
-      for (int ww = 0; ww < SORT_WAVES; ++ww) {
-        if (ww < w) mine += wsum[q][ww];
-        before += wsum[q][ww];
-      }
-      const int d = threadIdx.x + q * SORT_THREADS;
-      if (d < nb) {
-        const uint32_t first = mine + incl[q] - tot[q];  // place of the digit's first key in the sorted tile
-        dpre[d] = first;
-        gbase[d] -= first;   // output position = gbase[d] + place in the sorted tile
+      if (q * SORT_THREADS < nb) {   // (uniform)
+        uint32_t mine = before, mine_total = before_total;
+        for (int ww = 0; ww < SORT_WAVES; ++ww) {
+          const uint32_t c = lds.wsum[0][q][ww], ct = lds.wsum[1][q][ww];
+          if (ww < w) {
+            mine += c;
+            mine_total += ct;
+          }
+          before += c;
+          before_total += ct;
+        }
+        const int d = threadIdx.x + q * SORT_THREADS;
+        if (d < nb) {
+          const uint32_t place = mine + incl[q] - tot[q];  // of the digit's first key in the sorted tile
+          lds.dpre[d] = (uint16_t)place;
+          lds.gbase[d] = mine_total + incl_total[q] - total[q] + earlier[q] - place;   // output position = gbase[d] + place in the sorted tile
+        }
       }
     }
   }
   __syncthreads();
-  uint32_t lp[SORT_ITEMS];
+  uint32_t lp[ITEMS];
 #pragma unroll
-  for (int i = 0; i < SORT_ITEMS; ++i) {
-    const uint32_t d = ((uint32_t)key[i] >> shift) & (nb - 1);
-    lp[i] = dpre[d] + cnt[w][d] + rank[i];
+  for (int i = 0; i < ITEMS; ++i) {
+    const uint32_t d = digit(key[i]);
+    lp[i] = lds.dpre[d] + lds.cnt[w][d] + rank[i];
   }
   __syncthreads();  // the counters are dead: their memory stages the tile sorted by digit
-  int32_t* skey = reinterpret_cast<int32_t*>(&cnt[0][0]);
-  int32_t* spay = skey + SORT_TILE;
-  static_assert(2 * SORT_TILE <= SORT_WAVES * MAX_BINS, "the staged tile must fit the counters' memory");
-  const int tile_count = min(SORT_TILE, nnz - t * SORT_TILE);
 #pragma unroll
-  for (int i = 0; i < SORT_ITEMS; ++i) {
-    const int pos = t * SORT_TILE + w * (64 * SORT_ITEMS) + i * 64 + lane;
-    if (pos < nnz && lp[i] < (uint32_t)SORT_TILE) {
-      skey[lp[i]] = key[i];
-      spay[lp[i]] = pay[i];
+  for (int i = 0; i < ITEMS; ++i) {
+    if ((FULL || first + i * 64 < count) && lp[i] < (uint32_t)SORT_TILE) {
+      lds.staged[0][lp[i]] = key[i];
+      lds.staged[1][lp[i]] = pay[i];
     }
   }
   __syncthreads();
   // Consecutive threads hold consecutive keys of the sorted tile: keys of one digit go to consecutive
   // positions of the output, so that their 4-byte stores merge into one request per run.
 #pragma unroll
-  for (int q = 0; q < SORT_ITEMS; ++q) {
+  for (int q = 0; q < ITEMS; ++q) {
     const int j = q * SORT_THREADS + threadIdx.x;
-    if (j < tile_count) {
-      const int32_t k = skey[j];
-      const uint32_t d = ((uint32_t)k >> shift) & (nb - 1);
-      const uint32_t dst = gbase[d] + (uint32_t)j;
+    if (FULL || j < count) {
+      const int32_t k = lds.staged[0][j];
+      const uint32_t dst = lds.gbase[digit(k)] + (uint32_t)j;
       if (dst < (uint32_t)nnz) {
-        keys_out[base + dst] = k;
-        pay_out[base + dst] = spay[j];
+        keys_out[dst] = k;
+        pay_out[dst] = lds.staged[1][j];
       }
     }
   }
+}
+
+__global__ __launch_bounds__(SORT_THREADS, 8) void sort_scatter_kernel(
+    const int32_t* keys_in, const int32_t* pay_in, int32_t* keys_out, int32_t* pay_out, const uint32_t* hist,
+    const uint32_t* digit_total, FieldPtr fp, TileBase tb, int F, int shift, int rb) {
+  __shared__ ScatterLds lds;
+  static_assert(4 * sizeof(lds) <= 160 * 1024, "four blocks to fill a compute unit's places for wavefronts");
+  int f, t, part;
+  if (!tile_of_block(tb, F, 1, f, t, part)) return;
+  const int64_t base = fp.p[f], start = base + (int64_t)t * SORT_TILE;
+  const int nnz = (int)(fp.p[f + 1] - base), count = min(SORT_TILE, nnz - t * SORT_TILE);
+  const uint32_t* hb = hist + ((int64_t)(tb.t[f] + t) << rb);
+  const uint32_t* totals = digit_total + ((int64_t)f << rb);
+  if (count == SORT_TILE) scatter_tile<true>(lds, keys_in + start, pay_in + start, keys_out + base, pay_out + base, hb, totals, count, nnz, shift, rb);
+  else scatter_tile<false>(lds, keys_in + start, pay_in + start, keys_out + base, pay_out + base, hb, totals, count, nnz, shift, rb);
 }
 
 // All passes of a field's sort in one block, for fields of up to SMALL_THREADS * IT lookups: keys and sample
@@ -295,7 +335,7 @@ __global__ __launch_bounds__(SORT_THREADS) void sort_scatter_kernel(
 // holding the same number `per` of items a lane) and trade places through LDS.  Same ranking, hence the same stable
 // order, as the passes over many blocks, in one launch instead of three per pass; a block's time is a few microseconds per pass and 8 items of a
 // thread.  Blocks behind the fields write the samples' aggregation weights.
-// (26 fields of 1000 lookups, two passes: 29 us of kernels and their gaps -> one launch of 11 us.)
+// (26 fields of 1000 lookups, two passes: 29 us of kernels and their gaps -> one launch of 10 us.)
 constexpr int SMALL_THREADS = 1024, SMALL_WAVES = SMALL_THREADS / 64;
 template <int IT>
 __global__ __launch_bounds__(SMALL_THREADS) void sort_small_kernel(const int32_t* keys_in, const int32_t* pay_in, int32_t* keys_out,
@@ -328,10 +368,10 @@ __global__ __launch_bounds__(SMALL_THREADS) void sort_small_kernel(const int32_t
   }
   const int nb = 1 << rb;   // (at most one digit per thread)
   const uint64_t lt = lanemask_lt();
-  volatile uint16_t* cw = cnt[w];
   for (int p = 0; p < passes; ++p) {
     const int shift = p * rb;
-    for (int d = lane; d < nb; d += 64) cw[d] = 0;   // (each wavefront its own row)
+    for (int d = lane; d < nb; d += 64) cnt[w][d] = 0;   // (each wavefront its own row)
+    wave_lds_order();
     uint32_t rank[IT];
 #pragma unroll
     for (int i = 0; i < IT; ++i) {
@@ -340,11 +380,11 @@ __global__ __launch_bounds__(SMALL_THREADS) void sort_small_kernel(const int32_t
         const bool valid = first + i * 64 < nnz;
         const uint32_t d = ((uint32_t)key[i] >> shift) & (nb - 1);
         const uint64_t m = same_digit(d, rb, valid);
-        if (valid) {
-          const uint32_t prior = cw[d];
-          rank[i] = prior + (uint32_t)__popcll(m & lt);
-          if ((m & lt) == 0) cw[d] = (uint16_t)(prior + (uint32_t)__popcll(m));   // lowest lane of the group
-        }
+        const uint32_t prior = cnt[w][d];
+        wave_lds_order();
+        rank[i] = prior + (uint32_t)__popcll(m & lt);
+        if (valid && (m & lt) == 0) cnt[w][d] = (uint16_t)(prior + (uint32_t)__popcll(m));   // lowest lane of the group
+        wave_lds_order();
       }
     }
     __syncthreads();
@@ -360,12 +400,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void sort_small_kernel(const int32_t
         tot += c[q];
       }
     }
-    uint32_t incl = tot;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const uint32_t v = __shfl_up(incl, o, 64);
-      if (lane >= o) incl += v;
-    }
+    const uint32_t incl = wave_prefix(tot);
     if (lane == 63) wsum[w] = incl;
     __syncthreads();
     uint32_t before = 0;
@@ -597,12 +632,6 @@ struct __attribute__((aligned(16))) Lookup {
   float w;
   int32_t unused;
 };
-
-// LDS traffic between the lanes of one wavefront: executed in program order, only the compiler has to keep it so.
-__device__ __forceinline__ void wave_lds_order() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
 
 // g += w(lookup) * dX[sample, field slice] over `n` staged lookups, added in order, four in flight; dx: this lane's
 // columns of sample 0.
@@ -1116,14 +1145,15 @@ static hipError_t launch_sort_pass(const SortPlan& pl, const SortBuffers& sb, in
   }
   {
     ProfScope ps(prof, KID_SORT_SCAN, s);
-    const int wblocks = pass == 0 ? (pl.B + MAX_BINS - 1) / MAX_BINS : 0;
-    hipLaunchKernelGGL(sort_scan_kernel, dim3(pl.F + wblocks), dim3(MAX_BINS), 0, s, sb.hist, sb.digit_base, tb, pl.F, pl.radix_bits,
-                       sb.sample_w, tab);
+    const int groups = std::max(1, (1 << pl.radix_bits) / SCAN_DIGITS);
+    const int wblocks = pass == 0 ? (pl.B + SCAN_THREADS - 1) / SCAN_THREADS : 0;
+    hipLaunchKernelGGL(sort_scan_kernel, dim3(pl.F * groups + wblocks), dim3(SCAN_THREADS), 0, s, sb.hist, sb.digit_total, tb, pl.F,
+                       pl.radix_bits, sb.sample_w, tab);
   }
   {
     ProfScope ps(prof, KID_SORT_SCATTER, s);
     hipLaunchKernelGGL(sort_scatter_kernel, grid, dim3(SORT_THREADS), 0, s, kin, pin, sb.key[pass & 1],
-                       sb.pay[pass & 1], sb.hist, sb.digit_base, fp, tb, pl.F, shift, pl.radix_bits);
+                       sb.pay[pass & 1], sb.hist, sb.digit_total, fp, tb, pl.F, shift, pl.radix_bits);
   }
   return hipGetLastError();
 }
@@ -1132,7 +1162,7 @@ hipError_t launch_sort(const SortPlan& pl, const SortBuffers& sb, const FieldPtr
                        Profiler* prof, hipStream_t s, int* sorted_buf) {
   *sorted_buf = 0;
   if (pl.total_tiles == 0) return hipSuccess;
-  // One block per field as long as a field fits one: two passes over 1000 / 9000 lookups of a field take 10 / 26 us, the
+  // One block per field as long as a field fits one: two passes over 1000 / 9000 lookups of a field take 10 / 24 us, the
   // six launches 29 / 30 and the host four times as long.
   int64_t most = 0;
   for (int f = 0; f < pl.F; ++f) most = std::max(most, fp.p[f + 1] - fp.p[f]);

@@ -266,7 +266,7 @@ struct SortBuffers {
   int32_t* key[2];
   int32_t* pay[2];
   uint32_t* hist;                  // [total_tiles << radix_bits]
-  uint32_t* digit_base;            // [F << radix_bits]
+  uint32_t* digit_total;            // [F << radix_bits]
   float* sample_w;                 // [B] aggregation weight of every sample, written beside the first pass
 };
 // Sorts every field's lookups by row id (stable); the result is in key / pay [*sorted_buf].

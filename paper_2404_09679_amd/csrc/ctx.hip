@@ -121,7 +121,7 @@ struct antdt_ctx {
   int32_t *key[2] = {}, *pay[2] = {}, *tile_heads = nullptr, *ubase = nullptr, *uniq = nullptr;
   int32_t *segoff = nullptr, *pack_pay = nullptr, *segabs = nullptr, *goes_out = nullptr;
   float* partial = nullptr;
-  uint32_t *hist = nullptr, *digit_base = nullptr;
+  uint32_t *hist = nullptr, *digit_total = nullptr;
   // batch
   const int32_t* ids = nullptr;
   const int32_t* offsets = nullptr;
@@ -265,7 +265,7 @@ static size_t carve(antdt_ctx* c, char* base) {
     c->pay[i] = (int32_t*)take((size_t)N * 4);
   }
   c->hist = (uint32_t*)take((size_t)(c->max_tiles_total << c->radix_bits) * 4);
-  c->digit_base = (uint32_t*)take((size_t)(m.num_fields << c->radix_bits) * 4);
+  c->digit_total = (uint32_t*)take((size_t)(m.num_fields << c->radix_bits) * 4);
   const bool share = !c->act_bf16 && c->L == 1;   // (see below)
   const size_t jobs = (size_t)K * sizeof(LossJob), counts = (size_t)(ANTDT_MAX_FIELDS + 1) * 8;
   char* small = take(counts + 8 + (share ? 0 : jobs));
@@ -716,7 +716,7 @@ static int build_coalescing(antdt_ctx* c, const int32_t* ids, const int32_t* pay
   sb.ids = ids;
   sb.key[0] = c->key[0]; sb.key[1] = c->key[1]; sb.pay[0] = c->pay[0]; sb.pay[1] = c->pay[1];
   sb.hist = c->hist;
-  sb.digit_base = c->digit_base;
+  sb.digit_total = c->digit_total;
   sb.sample_w = c->sample_w;
   sb.pay0 = pay0;
   HIP_TRY(c, launch_sort(pl, sb, c->afp, c->atb, c->tab, pr, s, &c->sorted_buf));
