@@ -52,15 +52,21 @@ __device__ __forceinline__ void dense_columns(const PoolArgs& a, int sl0, int en
   }
 }
 
+constexpr int MOST_ITERATIONS = 15;   // (bags that take as many or more count as equally long)
+
 // Gather and sum-pool.  A block owns SPB consecutive samples of one field; a group of
 // LPR = D*sizeof(T)/16 lanes owns one bag, so a wavefront works on 64/LPR bags at once.
 // The group fetches LPR ids with one coalesced load, hands the rows' places round with lane
 // exchanges and issues the LPR row loads (16 bytes per lane, one whole row per group)
 // back to back before adding them, which keeps 64 rows in flight per wavefront; the next ids are
 // requested before the rows are waited for.  Every lookup's sample index is recorded for the sort.
-// Bound by vector instructions where bags are long (41.8 M lookups of 128-byte bf16 rows: they issue in 73 % of the
-// cycles; 40 per eight rows of a wavefront, 16 of them to unpack and add, 57 before bounds and addresses were worked out
-// once per lookup, by the lane that loads its id), else by round trips.  Like the sort's tiles, the blocks of a field go to one XCD: its rows are fetched into one L2.
+// Blocks of 64 samples hand them out in order of the iterations they take, so that the bags a wavefront works on at once are
+// about as long as each other: with 1 .. 50 lookups, the longest of eight in any order makes every second load of a wavefront
+// one of few lanes (41.8 M lookups: 10.7 M load and 209 M vector instructions, in order 7.1 M and 152 M).
+// Bound, where bags are long, by the rows' way from the L2s, 55 lines outstanding on a compute unit (41.8 M lookups of 128-byte
+// bf16 rows 507 -> 489 us, 4.3 M of fp32 rows 70.6 -> 68.1; buffer loads that need no bounds took the vector instructions
+// down to the additions and won nothing), else by round trips.  Like the sort's tiles, the blocks of a field go to one XCD: its
+// rows are fetched into one L2 (fields interleaved two to sixteen at a time: 492 .. 530 us).
 // WIDE: a table of 2^32 or more 16-byte pieces.
 template <typename TT, typename OT, int LPR, int SPB, bool WIDE>
 __global__ __launch_bounds__(256) void pool_tile_kernel(PoolArgs a, FieldPtr fp) {
@@ -82,20 +88,48 @@ __global__ __launch_bounds__(256) void pool_tile_kernel(PoolArgs a, FieldPtr fp)
   const uint4* tab = reinterpret_cast<const uint4*>(reinterpret_cast<const TT*>(a.tables) + (int64_t)f * a.R * a.D) + c;
   const int last = (int)(a.R - 1);
   auto fetch = [&](int j, int end) { return j < end ? ids[j] : 0; };
-  int begin[ROUNDS], end[ROUNDS];
+  // The bags of round r (sample of the block, lookups): as they come, or (64 of them) in order of the iterations they take, the
+  // longest first, every wavefront with long and short ones.
+  int sample[ROUNDS], begin[ROUNDS], end[ROUNDS];
+  const int32_t* off = a.offsets + (int64_t)f * (a.B + 1) + a.s0 + sl0;
+  if (SPB == 64) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    int b0 = 0, e0 = 0;
+    if (sl0 + lane < sl1) {
+      b0 = off[lane];
+      e0 = off[lane + 1];
+    }
+    const int iterations = min((max(e0 - b0, 0) + LPR - 1) / LPR, MOST_ITERATIONS);
+    int place = 0, longer = 0;
+    for (int i = MOST_ITERATIONS; i >= 0; --i) {
+      const uint64_t m = __ballot(iterations == i);
+      if (iterations == i) place = longer + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+      longer += __popcll(m);
+    }
+    const int sorted = __builtin_amdgcn_ds_permute(place * 4, lane), sb = __builtin_amdgcn_ds_permute(place * 4, b0),
+              se = __builtin_amdgcn_ds_permute(place * 4, e0);
+    constexpr int PER_WAVE = 64 / LPR;   // bags of a wavefront and round
 #pragma unroll
-  for (int r = 0; r < ROUNDS; ++r) {
-    const int ls = r * G + g;
-    begin[r] = end[r] = 0;
-    if (sl0 + ls < sl1) {
-      const int32_t* off = a.offsets + (int64_t)f * (a.B + 1) + a.s0 + sl0 + ls;
-      begin[r] = off[0];
-      end[r] = off[1];
+    for (int r = 0; r < ROUNDS; ++r) {
+      const int from = ((r * 4 + (r & 1 ? 3 - w : w)) * PER_WAVE + (threadIdx.x & 63) / LPR) * 4;
+      sample[r] = __builtin_amdgcn_ds_bpermute(from, sorted);
+      begin[r] = __builtin_amdgcn_ds_bpermute(from, sb);
+      end[r] = __builtin_amdgcn_ds_bpermute(from, se);
+    }
+  } else {
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+      sample[r] = r * G + g;
+      begin[r] = end[r] = 0;
+      if (sl0 + sample[r] < sl1) {
+        begin[r] = off[sample[r]];
+        end[r] = off[sample[r] + 1];
+      }
     }
   }
 #pragma unroll
   for (int r = 0; r < ROUNDS; ++r) {
-    const int ls = r * G + g;
+    const int ls = sample[r];
     const int64_t s = a.s0 + sl0 + ls;
     const int b0 = begin[r], e0 = end[r];
     float acc[EV];

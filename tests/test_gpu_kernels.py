@@ -396,3 +396,25 @@ def test_row_update_over_the_range_of_accumulators(dim, state):
     ok = ~np.isnan(step)
     # a few roundings of the step, and that of the stored parameter
     assert np.all(np.abs(got_p[ok] - (p - step)[ok]) <= 1e-6 * np.abs(step[ok]) + 2.0 ** -23 * np.abs(p[ok]))
+
+
+# The gather hands the 64 samples of a block out by the number of iterations their bags take (fifteen and more are one class):
+# equal bags, bags of every length up to 300, empty ones, blocks that end inside.  Rows of 4, 8 and 16 pieces of 16 bytes.
+@pytest.mark.parametrize("dim,table,pooling", [(16, "f32", "sum"), (32, "f32", "mean"), (128, "bf16", "sum"), (32, "bf16", "mean")])
+def test_gather_of_bags_of_many_lengths(dim, table, pooling, monkeypatch):
+    F, B = 40, 1700   # (enough blocks that they take 64 samples each)
+    assert F * (-(-B // 64)) >= 1024 and B % 64
+    cfg = _config(f"bags-{dim}", 690 + dim, num_fields=F, rows_per_field=300, dim=dim, table_dtype=table, adagrad_state="rowwise", layer_sizes=(8,),
+                  gemm_dtype="f32", shard_sizes=(700, 1, 999), max_bag=300, pooling=pooling)
+    rng = np.random.default_rng(dim)
+    lengths = [rng.integers(0, 3, B) for _ in range(F)]
+    lengths[0] = np.full(B, 7)
+    lengths[1] = rng.integers(0, 130, B)
+    lengths[2] = np.where(np.arange(B) % 64 == 17, 300, 0)
+    lengths[3] = np.arange(B) % 66
+    lengths[4] = (np.arange(B) == B - 1).astype(int)
+    ids = [rng.integers(0, 300, n.sum()) for n in lengths]
+    _plant(monkeypatch, ids, B, lambda f, n: np.concatenate([[0], np.cumsum(lengths[f])]))
+    # (accumulators from zero: with others, of about 1e-4, a step is about 1e-4 or less, and rounding the stored parameter of about
+    # 0.05 to fp32, 2^-25 * 0.05 = 1.5e-9, is 1.5e-5 of it: more than the 1e-5 that steps are compared to)
+    check_iteration(cfg, cfg.shard_sizes, tol=TOL32, batched=True)
