@@ -2,33 +2,67 @@
 // pass of the worker step, with the partial sums over samples that the last layer's
 // gradients and the shards' mean losses are made of.
 // Every reduction runs in a fixed order, so results are bitwise repeatable.
+#include <type_traits>
+
 #include "common.h"
 
 namespace antdt {
 namespace {
 
+// Sum over the wavefront, in every lane: halves, then quarters, ... (no trip through LDS, which a shuffle is).
 __device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+  auto both = [](u32x2 p) { return __uint_as_float(p.x) + __uint_as_float(p.y); };
+  auto moved = [](float x, auto ctrl) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), decltype(ctrl)::value, 0xF, 0xF, true));
+  };
+  v = both(__builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false));
+  v = both(__builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false));
+  v += moved(v, std::integral_constant<int, 0x128>());   // eight lanes round a row of sixteen
+  v += moved(v, std::integral_constant<int, 0x124>());   // four (the halves of the row are the same by now)
+  v += moved(v, std::integral_constant<int, 0x4E>());    // lane ^ 2
+  v += moved(v, std::integral_constant<int, 0xB1>());    // lane ^ 1
   return v;
 }
+__device__ __forceinline__ float lane_value(float v, int lane) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+}
+
+// Four neighbouring columns of a row (the first at `x`), and the store of four results.
+template <typename T> __device__ __forceinline__ void load4(const T* x, float (&v)[4]);
+template <> __device__ __forceinline__ void load4(const float* x, float (&v)[4]) {
+  const float4 q = *reinterpret_cast<const float4*>(x);
+  v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
+}
+template <> __device__ __forceinline__ void load4(const bf16_t* x, float (&v)[4]) {
+  const uint2 q = *reinterpret_cast<const uint2*>(x);
+  v[0] = __uint_as_float(q.x << 16); v[1] = __uint_as_float(q.x & 0xFFFF0000u);
+  v[2] = __uint_as_float(q.y << 16); v[3] = __uint_as_float(q.y & 0xFFFF0000u);
+}
+__device__ __forceinline__ void store4(float* x, const float (&v)[4]) { *reinterpret_cast<float4*>(x) = make_float4(v[0], v[1], v[2], v[3]); }
+__device__ __forceinline__ void store4(bf16_t* x, const float (&v)[4]) { *reinterpret_cast<uint2*>(x) = make_uint2(f2bf2(v[0], v[1]), f2bf2(v[2], v[3])); }
 
 // A block works on HEAD_TILE consecutive samples of one shard, four per wavefront; a lane holds the columns
-// lane, lane + 64, ... of all four, 512 columns at a time (its loads are then in flight together, and widths
+// 4 lane .. 4 lane + 3 of every 256 of all four, 512 columns at a time (its loads are then in flight together, and widths
 // up to 512 are read once).  Besides the loss, dz and dh it leaves the sums over its samples that the last
 // layer's weight gradient, bias gradient and the shard's loss are made of, so that nothing has to read the
 // activation again.
-// Bound by the chain of round trips (activation -> logit -> gradient), not by bytes.
-template <typename TH, typename TD>
+// Bound by the chain of round trips (activation -> logit -> gradient) and by its own instructions, each of which a launch
+// fetches anew and runs about once: a column at a time they were 9 KB.
+// VEC: widths and pitches are multiples of four (all bf16 models with a hidden layer), so columns are moved four at a time.
+template <typename TH, typename TD, bool VEC>
 __global__ __launch_bounds__(256) void head_tile_kernel(HeadArgs a, ShardTab tab, HeadTiles ht) {
   constexpr int SPW = HEAD_TILE / 4;   // samples per wavefront
-  constexpr int CPL = 8, CHUNK = 64 * CPL;
+  constexpr int PARTS = 2, CHUNK = 256 * PARTS;
   __shared__ float col[4][CHUNK];
   __shared__ float sums[4][2];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int tile = ht.base[a.k_begin] + blockIdx.x;
-  int k = a.k_begin;
-  while (k + 1 < a.k_end && tile >= ht.base[k + 1]) ++k;
+  // the shard: how many of the range's shards before the last end at or before the tile, counted by the lanes (one load of
+  // the table instead of a chain of them)
+  static_assert(ANTDT_MAX_SHARDS <= 64, "a table entry per lane");
+  const int shard_end = ht.base[min(lane, ANTDT_MAX_SHARDS - 1) + 1];
+  const int k = a.k_begin + __popcll(__ballot(lane >= a.k_begin && lane + 1 < a.k_end && shard_end <= tile));
   const int t0 = (tile - ht.base[k]) * HEAD_TILE;            // first sample inside the shard
   const int count = min(tab.len[k] - t0, HEAD_TILE);         // samples of the tile (at least one)
   const int rows = min(max(count - wave * SPW, 0), SPW);     // samples of this wavefront
@@ -44,34 +78,50 @@ __global__ __launch_bounds__(256) void head_tile_kernel(HeadArgs a, ShardTab tab
   const float label = a.labels[s0 + min(wave * SPW + min(lane, SPW - 1), count - 1)];   // lanes 0 .. SPW-1: one sample each
   const float bias = a.b[0];
 
-  float hv[SPW][CPL], w[CPL];
+  float hv[PARTS][SPW][4], w[PARTS][4];
   auto load = [&](int j0) {
 #pragma unroll
-    for (int i = 0; i < CPL; ++i) {
-      if (j0 + i * 64 >= a.width) {   // (the same for all lanes)
-        w[i] = 0.0f;
+    for (int i = 0; i < PARTS; ++i) {
+      const int j = j0 + i * 256 + lane * 4;
+      if (j0 + i * 256 >= a.width) {   // (the same for all lanes)
 #pragma unroll
-        for (int r = 0; r < SPW; ++r) hv[r][i] = 0.0f;
+        for (int e = 0; e < 4; ++e) {
+          w[i][e] = 0.0f;
+#pragma unroll
+          for (int r = 0; r < SPW; ++r) hv[i][r][e] = 0.0f;
+        }
+      } else if (VEC) {
+        const int jc = min(j, a.width - 4);
+        load4(a.w + jc, w[i]);
+#pragma unroll
+        for (int r = 0; r < SPW; ++r) load4(h[r] + jc, hv[i][r]);
       } else {
-        const int j = j0 + i * 64 + lane, jc = min(j, a.width - 1);
-        w[i] = a.w[jc];
 #pragma unroll
-        for (int r = 0; r < SPW; ++r) hv[r][i] = to_f32(h[r][jc]);
-        if (j >= a.width) {
-          w[i] = 0.0f;
+        for (int e = 0; e < 4; ++e) {
+          const int jc = min(j + e, a.width - 1);
+          w[i][e] = a.w[jc];
 #pragma unroll
-          for (int r = 0; r < SPW; ++r) hv[r][i] = 0.0f;
+          for (int r = 0; r < SPW; ++r) hv[i][r][e] = to_f32(h[r][jc]);
         }
       }
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (j + (VEC ? 0 : e) >= a.width) {   // (VEC: the four are inside or outside together)
+          w[i][e] = 0.0f;
+#pragma unroll
+          for (int r = 0; r < SPW; ++r) hv[i][r][e] = 0.0f;
+        }
     }
   };
   float part[SPW] = {};
   for (int j0 = 0; j0 < a.width; j0 += CHUNK) {
     load(j0);
 #pragma unroll
-    for (int i = 0; i < CPL; ++i)
+    for (int i = 0; i < PARTS; ++i)
 #pragma unroll
-      for (int r = 0; r < SPW; ++r) part[r] = fmaf(hv[r][i], w[i], part[r]);
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int r = 0; r < SPW; ++r) part[r] = fmaf(hv[i][r][e], w[i][e], part[r]);
   }
   float mine = 0.0f;   // lane r < SPW: logit of sample r
 #pragma unroll
@@ -81,47 +131,64 @@ __global__ __launch_bounds__(256) void head_tile_kernel(HeadArgs a, ShardTab tab
   }
   const float z = mine + bias;
   const float e = expf(-fabsf(z));
-  const float sig = z >= 0.0f ? 1.0f / (1.0f + e) : e / (1.0f + e);
+  const float sig = (z >= 0.0f ? 1.0f : e) / (1.0f + e);
   const bool on = lane < rows;
   const float dz_lane = on ? (sig - label) * (1.0f / (float)tab.len[k]) : 0.0f;
-  const float loss_lane = on ? fmaxf(z, 0.0f) - z * label + log1pf(e) : 0.0f;
-  float dz[SPW], sdz = 0.0f, sl = 0.0f;
+  float dz[SPW];
 #pragma unroll
-  for (int r = 0; r < SPW; ++r) {
-    dz[r] = __shfl(dz_lane, r, 64);
-    sdz += dz[r];
-    sl += __shfl(loss_lane, r, 64);
-  }
-  if (lane == 0) {
-    sums[wave][0] = sdz;
-    sums[wave][1] = sl;
-  }
+  for (int r = 0; r < SPW; ++r) dz[r] = lane_value(dz_lane, r);
   const bool per_sample = sizeof(TD) == 4 && a.dz;   // (bf16 gradients: there is a hidden layer)
-  if (per_sample && on) {   // (lane r < rows: the wavefront's sample r)
-    a.dz[s0 + wave * SPW + lane] = dz_lane;
-    a.loss_s[s0 + wave * SPW + lane] = loss_lane;
-  }
   float* part_out = a.part + (int64_t)tile * a.ldpart;
   for (int j0 = 0; j0 < a.width; j0 += CHUNK) {   // (dh_cols <= width)
     if (a.width > CHUNK) load(j0);
 #pragma unroll
-    for (int i = 0; i < CPL; ++i) {
-      const int j = j0 + i * 64 + lane;
-      float g = 0.0f;
+    for (int i = 0; i < PARTS; ++i) {
+      const int j = j0 + i * 256 + lane * 4;
+      if (j0 + i * 256 >= a.width) continue;   // (the same for all lanes)
+      float g[4] = {};
 #pragma unroll
       for (int r = 0; r < SPW; ++r)
         if (r < rows) {
-          g = fmaf(hv[r][i], dz[r], g);
-          const float d = (!a.relu || hv[r][i] > 0.0f) ? dz[r] * w[i] : 0.0f;
-          if (j < a.dh_cols) reinterpret_cast<TD*>(a.dh)[row[r] * a.lddh + j] = from_f32<TD>(d);
+          float d[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            g[e] = fmaf(hv[i][r][e], dz[r], g[e]);
+            d[e] = (!a.relu || hv[i][r][e] > 0.0f) ? dz[r] * w[i][e] : 0.0f;
+          }
+          TD* out = reinterpret_cast<TD*>(a.dh) + row[r] * a.lddh + j;
+          if (VEC) {
+            if (j < a.dh_cols) store4(out, d);   // (dh_cols: a multiple of four)
+          } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              if (j + e < a.dh_cols) out[e] = from_f32<TD>(d[e]);
+          }
         }
-      if (j0 + i * 64 < a.width) col[wave][i * 64 + lane] = g;
+      store4(&col[wave][i * 256 + lane * 4], g);
+    }
+    const bool last = j0 + CHUNK >= a.width;
+    if (last) {   // the losses, behind the stores of the gradient
+      const float loss_lane = on ? fmaxf(z, 0.0f) - z * label + log1pf(e) : 0.0f;
+      float sdz = 0.0f, sl = 0.0f;
+#pragma unroll
+      for (int r = 0; r < SPW; ++r) {
+        sdz += dz[r];
+        sl += lane_value(loss_lane, r);
+      }
+      if (lane == 0) {
+        sums[wave][0] = sdz;
+        sums[wave][1] = sl;
+      }
+      if (per_sample && on) {   // (lane r < rows: the wavefront's sample r)
+        a.dz[s0 + wave * SPW + lane] = dz_lane;
+        a.loss_s[s0 + wave * SPW + lane] = loss_lane;
+      }
     }
     if (per_sample) continue;
     __syncthreads();
     for (int q = threadIdx.x; q < CHUNK && j0 + q < a.width; q += 256)
       part_out[j0 + q] = (col[0][q] + col[1][q]) + (col[2][q] + col[3][q]);
-    __syncthreads();
+    if (!last) __syncthreads();
   }
   if (threadIdx.x == 0 && !per_sample) {
     part_out[a.width] = (sums[0][0] + sums[1][0]) + (sums[2][0] + sums[3][0]);
@@ -153,9 +220,14 @@ hipError_t launch_head_tiles(const HeadArgs& a, const ShardTab& tab, hipStream_t
   const HeadTiles ht = head_tiles(tab);
   const int tiles = ht.base[a.k_end] - ht.base[a.k_begin];
   if (tiles == 0) hipLaunchKernelGGL(head_no_samples_kernel, dim3(1), dim3(64), 0, s, a);
-  else if (a.bf16_dh) hipLaunchKernelGGL((head_tile_kernel<bf16_t, bf16_t>), dim3(tiles), dim3(256), 0, s, a, tab, ht);
-  else if (a.bf16_h) hipLaunchKernelGGL((head_tile_kernel<bf16_t, float>), dim3(tiles), dim3(256), 0, s, a, tab, ht);
-  else hipLaunchKernelGGL((head_tile_kernel<float, float>), dim3(tiles), dim3(256), 0, s, a, tab, ht);
+  else {
+    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(tiles), dim3(256), 0, s, a, tab, ht); };
+    // (16-byte aligned: the activations lie in the workspace, their rows one behind the other; the weights where the layers before end)
+    const bool vec = ((a.width | a.dh_cols | a.ldh | a.lddh) & 3) == 0 && (reinterpret_cast<uintptr_t>(a.w) & 15) == 0;
+    if (a.bf16_dh) vec ? launch(head_tile_kernel<bf16_t, bf16_t, true>) : launch(head_tile_kernel<bf16_t, bf16_t, false>);
+    else if (a.bf16_h) vec ? launch(head_tile_kernel<bf16_t, float, true>) : launch(head_tile_kernel<bf16_t, float, false>);
+    else vec ? launch(head_tile_kernel<float, float, true>) : launch(head_tile_kernel<float, float, false>);
+  }
   return hipGetLastError();
 }
 
