@@ -788,7 +788,7 @@ __device__ __forceinline__ int64_t run_index(const SegArgs& a, int f, int pos) {
 // end behind it), summed in sorted (= sample) order, or, of longer runs, a piece of at most LONG_RUN lookups
 // that ends at a multiple of LONG_RUN in the window.  The pieces' sums meet in LDS in order; what of a run leaves the window
 // goes to memory (two slots per window: the run that comes in, the run that goes out) and is added up by
-// seg_finish_kernel.  No run table is needed (counting, scanning and writing one, with lists of the long
+// seg_finish_kernel (nothing leaves it where a window holds its field: 1024 threads, see fill_seg_args in ctx.hip).  No run table is needed (counting, scanning and writing one, with lists of the long
 // runs, were six launches and 10-250 us between sort and reduction), only keys, sample indices and the rows
 // themselves are read, and the chain of dependent accesses is down to LDS -> row and pooled gradients.
 // A window that lies inside one run (60 % of them with 42 M lookups of Zipf(1.2) ids) needs none of this: sum_window.
@@ -803,12 +803,12 @@ constexpr int LONG_RUN = 16;
 
 // Sum over the W lookups of a window that lies inside one run; every lane group of the first wavefront returns it.  Nothing
 // is to be found there, so each wavefront works on lookups of its own (its part of `look`), without the others until the
-// four sums meet.  Lookups of one row by one sample are neighbours (the sort is stable) and become one pair with a
+// sums meet.  Lookups of one row by one sample are neighbours (the sort is stable) and become one pair with a
 // multiple of the weight.
-template <int W>
-__device__ __forceinline__ RowSum sum_window(const char* dx, Lookup* look, const int (&smp)[W / 256], const float (&weight)[W / 256], int64_t pitch,
-                                             float* wave_sums, int D, int lps, int c) {
-  constexpr int ROUNDS = W / 256;
+template <int W, int THREADS>
+__device__ __forceinline__ RowSum sum_window(const char* dx, Lookup* look, const int (&smp)[W / THREADS], const float (&weight)[W / THREADS],
+                                             int64_t pitch, float* wave_sums, int D, int lps, int c) {
+  constexpr int ROUNDS = W / THREADS;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   Lookup* mine = look + wave * (64 * ROUNDS);
   int n = 0;
@@ -856,19 +856,20 @@ __device__ __forceinline__ RowSum sum_window(const char* dx, Lookup* look, const
   __syncthreads();
   sum = {};
 #pragma unroll
-  for (int q = 0; q < 4; ++q) add_floats(sum, wave_sums + q * D + c * 4);
+  for (int q = 0; q < THREADS / 64; ++q) add_floats(sum, wave_sums + q * D + c * 4);
   return sum;
 }
 
-template <typename TT, bool ROWWISE, bool UPDATE, bool MEAN, int W>
-__global__ __launch_bounds__(256, ROWWISE ? 8 : 1) void seg_window_kernel(SegArgs a, FieldPtr fp, TileBase tb) {
-  constexpr int PARTS = SORT_TILE / W, ROUNDS = W / 256;
-  static_assert(W <= 512 && LONG_RUN == 16, "list entries and the search for long runs");
+template <typename TT, bool ROWWISE, bool UPDATE, bool MEAN, int W, int THREADS>
+__global__ __launch_bounds__(THREADS, ROWWISE ? 8 : 1) void seg_window_kernel(SegArgs a, FieldPtr fp, TileBase tb) {
+  constexpr int PARTS = SORT_TILE / W, ROUNDS = W / THREADS, WAVES = THREADS / 64;
+  constexpr int BITS = W <= 512 ? 9 : 11, POS = (1 << BITS) - 1, HEAD = 1 << BITS, PIECE = 2 << BITS;   // entries of `order`
+  static_assert(W <= 2048 && LONG_RUN == 16, "list entries and the search for long runs");
   __shared__ int32_t key_[W + 2 * LONG_RUN];        // positions -LONG_RUN .. W + LONG_RUN - 1 relative to the window
   __shared__ Lookup look[W + LONG_RUN];
   __shared__ uint16_t order[W];                     // work items: runs of up to four lookups from the front (position, length), others from the end
   __shared__ int16_t lead[W / LONG_RUN + 1];        // pieces' runs: [0] the one that comes in, [1 + j] starts in the j-th LONG_RUN positions
-  __shared__ int counts[ROUNDS][4];
+  __shared__ int counts[ROUNDS][WAVES];
   __shared__ int goes_out;
   __shared__ uint64_t heads[UPDATE ? 1 : W / 64];   // (sums written out: the place of a run is the window's first one's + heads before)
   __shared__ int64_t first_run;
@@ -888,7 +889,7 @@ __global__ __launch_bounds__(256, ROWWISE ? 8 : 1) void seg_window_kernel(SegArg
   int smp[ROUNDS], smp_tail = 0;
 #pragma unroll
   for (int r = 0; r < ROUNDS; ++r) {
-    const int pos = min(P + r * 256 + tid, nnz - 1);
+    const int pos = min(P + r * THREADS + tid, nnz - 1);
     k_own[r] = keys[pos];
     smp[r] = pay[pos];
   }
@@ -901,7 +902,7 @@ __global__ __launch_bounds__(256, ROWWISE ? 8 : 1) void seg_window_kernel(SegArg
     weight[r] = lookup_weight<MEAN>(a, off, smp[r]);
   }
   const int lps = a.D >> 2;
-  const int ngroups = 256 / lps;
+  const int ngroups = THREADS / lps;
   const int g = tid / lps, c = tid - g * lps;
   const char* dx = reinterpret_cast<const char*>(a.dx + f * a.D + c * 4);
   if (P + W <= nnz && first_key == last_key) {   // (the same for all threads)
@@ -909,7 +910,7 @@ __global__ __launch_bounds__(256, ROWWISE ? 8 : 1) void seg_window_kernel(SegArg
     const int64_t row = (int64_t)f * a.R + min(max(first_key, 0), (int)(a.R - 1));
     TableRow<TT, ROWWISE> tr;
     if (UPDATE && !in && !out && tid < lps) tr.load(a, row, c);
-    const RowSum sum = sum_window<W>(dx, look, smp, weight, a.lddx * 4, piece_sum, a.D, lps, c);
+    const RowSum sum = sum_window<W, THREADS>(dx, look, smp, weight, a.lddx * 4, piece_sum, a.D, lps, c);
     if (tid < lps) {
       if (in || out) store_floats(a.partial + (slot * 2 + (in ? 0 : 1)) * a.D + c * 4, sum);
       else if (UPDATE) tr.update(a, row, c, lps, sum);
@@ -931,8 +932,8 @@ __global__ __launch_bounds__(256, ROWWISE ? 8 : 1) void seg_window_kernel(SegArg
   };
 #pragma unroll
   for (int r = 0; r < ROUNDS; ++r) {
-    key_[LONG_RUN + r * 256 + tid] = k_own[r];
-    stage(r * 256 + tid, smp[r], weight[r]);
+    key_[LONG_RUN + r * THREADS + tid] = k_own[r];
+    stage(r * THREADS + tid, smp[r], weight[r]);
   }
   if (tid < 2 * LONG_RUN) key_[tid < LONG_RUN ? tid : W + tid] = k_side;
   if (tid < LONG_RUN) stage(W + tid, smp_tail, weight_tail);
@@ -950,7 +951,7 @@ __global__ __launch_bounds__(256, ROWWISE ? 8 : 1) void seg_window_kernel(SegArg
   bool few[ROUNDS], other[ROUNDS];
 #pragma unroll
   for (int r = 0; r < ROUNDS; ++r) {
-    const int q = r * 256 + tid;
+    const int q = r * THREADS + tid;
     const bool valid = P + q < nnz;
     const int32_t k = key[q];
     const bool head = valid && (P + q == 0 || key[q - 1] != k);
@@ -959,8 +960,8 @@ __global__ __launch_bounds__(256, ROWWISE ? 8 : 1) void seg_window_kernel(SegArg
     const bool long_inside = ahead || ((behind >> (tid & 48)) & 0xFFFFu) != 0;
     few[r] = head && !same(q + 4, k);
     other[r] = head ? !few[r] : valid && (q & (LONG_RUN - 1)) == 0 && long_inside;
-    entry[r] = few[r] ? q | (((int)same(q + 1, k) + (int)same(q + 2, k) + (int)same(q + 3, k)) << 9)
-                      : q | (head ? 512 : 0) | (!head || ahead ? 1024 : 0);
+    entry[r] = few[r] ? q | (((int)same(q + 1, k) + (int)same(q + 2, k) + (int)same(q + 3, k)) << BITS)
+                      : q | (head ? HEAD : 0) | (!head || ahead ? PIECE : 0);
     const uint64_t mf = __ballot(few[r]), mo = __ballot(other[r]);
     if ((tid & 63) == 0) counts[r][tid >> 6] = __popcll(mf) | (__popcll(mo) << 16);
     if (!UPDATE) {
@@ -977,7 +978,7 @@ __global__ __launch_bounds__(256, ROWWISE ? 8 : 1) void seg_window_kernel(SegArg
       const uint64_t mf = __ballot(few[r]), mo = __ballot(other[r]);
       int before = sum_counts;
 #pragma unroll
-      for (int w = 0; w < 4; ++w) {
+      for (int w = 0; w < WAVES; ++w) {
         if (w < (tid >> 6)) before += counts[r][w];
         sum_counts += counts[r][w];
       }
@@ -1000,14 +1001,14 @@ __global__ __launch_bounds__(256, ROWWISE ? 8 : 1) void seg_window_kernel(SegArg
   // The long items first, so that the lane groups of a wavefront have items of about the same length.
   auto entry_of = [&](int i) { return i < n_other ? (int)order[W - 1 - i] : (int)order[i - n_other]; };
   for (int i = g; i < n_other + n_few; i += ngroups) {
-    const int en = entry_of(i), q0 = en & 511;
+    const int en = entry_of(i), q0 = en & POS;
     TableRow<TT, ROWWISE> tr;
-    if (UPDATE && !(i < n_other && (en & 1024))) tr.load(a, row_of(q0), c);
-    int n = (en >> 9) + 1;
+    if (UPDATE && !(i < n_other && (en & PIECE))) tr.load(a, row_of(q0), c);
+    int n = (en >> BITS) + 1;
     bool head = true, piece = false;
     if (i < n_other) {
-      head = en & 512;
-      piece = en & 1024;
+      head = en & HEAD;
+      piece = en & PIECE;
       n = LONG_RUN - (q0 & (LONG_RUN - 1));   // of a long run that starts here: up to the next multiple
       if (!head || !piece) {                  // the run's keys from here on, LONG_RUN at most (sorted: bisection)
         const int32_t k = key[q0];
@@ -1105,15 +1106,18 @@ __global__ __launch_bounds__(256) void seg_finish_kernel(SegArgs a, FieldPtr fp,
   }
 }
 
-template <typename TT, bool ROWWISE, bool UPDATE, bool MEAN, int W>
+template <typename TT, bool ROWWISE, bool UPDATE, bool MEAN, int W, int THREADS = 256>
 void launch_reduce_window(const SegArgs& a, const FieldPtr& fp, const TileBase& tb, Profiler* prof, hipStream_t s) {
   const unsigned parts = SORT_TILE / W;
+  const int bytes = 2 * W / LONG_RUN * a.D * 4;
   {
+    static std::atomic<uint64_t> allowed{0};
+    constexpr int ONE_FIELD = W > 512 ? 48 * 1024 : 0;   // (static LDS of the wide windows)
+    if (allow_lds(seg_window_kernel<TT, ROWWISE, UPDATE, MEAN, W, THREADS>, ONE_FIELD ? 2 * W / LONG_RUN * 64 * 4 : bytes, ONE_FIELD, allowed) != hipSuccess) return;
     ProfScope ps(prof, UPDATE ? KID_SPARSE_ADAGRAD : KID_SEG_REDUCE, s);
-    hipLaunchKernelGGL((seg_window_kernel<TT, ROWWISE, UPDATE, MEAN, W>), dim3(tile_grid(a.total_tiles) * parts), dim3(256),
-                       2 * W / LONG_RUN * a.D * 4, s, a, fp, tb);
+    hipLaunchKernelGGL((seg_window_kernel<TT, ROWWISE, UPDATE, MEAN, W, THREADS>), dim3(tile_grid(a.total_tiles) * parts), dim3(THREADS), bytes, s, a, fp, tb);
   }
-  {
+  if (W < 1024) {   // (no run leaves a window that holds its field)
     ProfScope ps(prof, KID_SEG_REDUCE_LONG, s);
     hipLaunchKernelGGL((seg_finish_kernel<TT, ROWWISE, UPDATE>), dim3((a.total_tiles * parts + 3) / 4), dim3(256), 0, s, a, fp, tb, W);
   }
@@ -1121,7 +1125,9 @@ void launch_reduce_window(const SegArgs& a, const FieldPtr& fp, const TileBase& 
 
 template <typename TT, bool ROWWISE, bool UPDATE, bool MEAN>
 void launch_reduce_pooling(const SegArgs& a, const FieldPtr& fp, const TileBase& tb, Profiler* prof, hipStream_t s) {
-  if (a.window == 512) launch_reduce_window<TT, ROWWISE, UPDATE, MEAN, 512>(a, fp, tb, prof, s);
+  if (a.window == 2048) launch_reduce_window<TT, ROWWISE, UPDATE, MEAN, 2048, 1024>(a, fp, tb, prof, s);
+  else if (a.window == 1024) launch_reduce_window<TT, ROWWISE, UPDATE, MEAN, 1024, 1024>(a, fp, tb, prof, s);
+  else if (a.window == 512) launch_reduce_window<TT, ROWWISE, UPDATE, MEAN, 512>(a, fp, tb, prof, s);
   else launch_reduce_window<TT, ROWWISE, UPDATE, MEAN, 256>(a, fp, tb, prof, s);
 }
 

@@ -289,7 +289,7 @@ struct SegArgs {
   int32_t* segoff;                 // [U + F], per-field offsets; field f's slice starts at ubase[f] + f
   float* G;                        // [U, D] coalesced gradient (written when not updating)
   const float* sample_w;           // [B]
-  int32_t window;                  // sorted lookups per block of the reduction: 256 or 512
+  int32_t window;                  // sorted lookups per block of the reduction: 256 or 512, or (every field in one window) 1024 or 2048
   int32_t* goes_out;               // [slots] the last run of the window starts there, is long and goes on in the next one
   float* partial;                  // [slots, 2, D] sums over the window: of the run that comes in, of the run that goes out
   const float* dx;                 // [B, lddx]

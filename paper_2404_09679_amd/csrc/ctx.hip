@@ -689,6 +689,13 @@ static void fill_seg_args(antdt_ctx* c, SegArgs& a) {
   // 243 / 242, 410 / 420, 547 / 558, 865 / 894; D = 16 with 1.5 / 2.8 / 5 M 212 / 214, 354 / 361, 570 / 605; D = 8 with 2.8 / 7 M
   // 309 / 309, 647 / 659.
   a.window = c->afp.p[m.num_fields] >= (4 << 20) && m.dim <= 32 ? 512 : 256;
+  // Fields that fit one window (1024 or 2048 lookups, 1024 threads) take one each: no run goes on in another one, and the launch
+  // that adds those up is not needed.  A step, us, windows of 256 / of the whole field: 26 fields of 500 / 1000 / 1400 / 2000 lookups
+  // 74.1 / 68.8, 80.4 / 73.7, 85.6 / 82.9, 86.9 / 87.0; 8 fields of 640 (fp32) 53.8 / 50.1; 26 of 1900 with D = 64 86.3 / 86.3.  (Wider
+  // rows: the pieces' sums no longer fit LDS.)
+  int64_t most = 0;
+  for (int f = 0; f < m.num_fields; ++f) most = std::max(most, c->afp.p[f + 1] - c->afp.p[f]);
+  if (m.dim <= 64 && most <= 2048) a.window = most <= 1024 ? 1024 : 2048;
   a.tables = c->tables; a.state = c->table_state; a.R = m.rows_per_field; a.lr = m.lr; a.eps = m.eps; a.inv_dim = 1.0f / (float)m.dim;
   a.table_bf16 = m.table_dtype == ANTDT_BF16; a.rowwise = m.adagrad_state == ANTDT_STATE_ROWWISE;
 }

@@ -418,3 +418,25 @@ def test_gather_of_bags_of_many_lengths(dim, table, pooling, monkeypatch):
     # (accumulators from zero: with others, of about 1e-4, a step is about 1e-4 or less, and rounding the stored parameter of about
     # 0.05 to fp32, 2^-25 * 0.05 = 1.5e-9, is 1.5e-5 of it: more than the 1e-5 that steps are compared to)
     check_iteration(cfg, cfg.shard_sizes, tol=TOL32, batched=True)
+
+
+# Fields that fit one window of the reduction: the longest of 1024 or 2048 lookups, one fewer or more; one long run, runs
+# around the lengths that are cut into pieces, single lookups.  Rows of 128 columns keep the windows of 256.
+@pytest.mark.parametrize("most", [1, 1023, 1024, 1025, 2047, 2048, 2049])
+@pytest.mark.parametrize("dim,table,state,pooling", [(4, "f32", "rowwise", "sum"), (16, "f32", "elementwise", "mean"), (64, "f32", "elementwise", "sum"),
+                                                     (64, "bf16", "rowwise", "mean"), (128, "f32", "elementwise", "sum")])
+def test_windows_of_whole_fields(most, dim, table, state, pooling, monkeypatch):
+    sizes = [most, max(most - 1, 1), most // 2 + 1, 1, most]
+    B = 90
+    cfg = _config(f"whole-{dim}", 720 + dim, num_fields=len(sizes), rows_per_field=2300, dim=dim, table_dtype=table, adagrad_state=state, layer_sizes=(8,),
+                  gemm_dtype="f32", shard_sizes=(30, 0, 59, 1), max_bag=60, min_bag=0, pooling=pooling)
+    rng = np.random.default_rng(most + dim)
+    lengths = [700, 1, 2, 3, 4, 5, 15, 16, 17, 31, 33, 48, 250]
+    ids = []
+    for f, n in enumerate(sizes):
+        rows = np.repeat(np.arange(len(lengths)) * 170, lengths)[:n] if f < 4 else np.full(n, 2299)   # (the last field: one run)
+        rows = np.concatenate([rows, rng.permutation(2300)[:n - len(rows)]])
+        ids.append(rng.permutation(rows))
+    _plant(monkeypatch, ids, B, lambda f, n: np.concatenate([[0], np.sort(rng.integers(0, n + 1, B - 1)), [n]]))
+    # (accumulators from zero: see test_sort_over_many_blocks)
+    check_iteration(cfg, cfg.shard_sizes, tol=TOL32, batched=True)
