@@ -107,28 +107,16 @@ __global__ __launch_bounds__(SORT_THREADS) void sort_hist_kernel(const int32_t* 
   }
 }
 
-__device__ __forceinline__ void write_sample_weights(float* sample_w, const ShardTab& tab, int s) {
-  int k = 0;
-  while (k + 1 < tab.K && s >= tab.start[k + 1]) ++k;   // (an empty shard starts where the next one does)
-  if (s < tab.start[k] + tab.len[k]) sample_w[s] = tab.w[k];
-}
-
 // The counts of a digit are replaced by their exclusive prefix over the tiles, and their total goes to digit_total.  A block has up to
 // SCAN_DIGITS digits of a field; a thread has a digit and one stretch of the tiles, which it walks twice (their sum; their
 // prefixes).  Bound by the chain of loads, and by what one compute unit can fetch (the counts were written by other XCDs): one
 // block per field, a chain of loads for each digit, took 18.8 us for 204 tiles of 128 digits, now 11.6, and 11 for 80 of
 // 1024, now 7.5.
-// Further blocks (first pass) write the aggregation weight of every sample.
 constexpr int SCAN_THREADS = 1024, SCAN_DIGITS = 128;
-__global__ __launch_bounds__(SCAN_THREADS) void sort_scan_kernel(uint32_t* hist, uint32_t* digit_total, TileBase tb, int F, int rb,
-                                                                 float* sample_w, ShardTab tab) {
+__global__ __launch_bounds__(SCAN_THREADS) void sort_scan_kernel(uint32_t* hist, uint32_t* digit_total, TileBase tb, int rb) {
   __shared__ uint32_t sums[SCAN_THREADS];
   const int nb = 1 << rb, digits = min(nb, SCAN_DIGITS), groups = nb / digits;
   const int f = (int)blockIdx.x / groups;
-  if (f >= F) {
-    write_sample_weights(sample_w, tab, ((int)blockIdx.x - F * groups) * SCAN_THREADS + (int)threadIdx.x);
-    return;
-  }
   const int tiles = tb.t[f + 1] - tb.t[f];
   const int parts = SCAN_THREADS / digits, dl = threadIdx.x & (digits - 1), part = threadIdx.x / digits;
   const int d = ((int)blockIdx.x - f * groups) * digits + dl;
@@ -334,22 +322,17 @@ __global__ __launch_bounds__(SORT_THREADS, 8) void sort_scatter_kernel(
 // indices stay in registers between the passes (item i of wavefront w: position 64 (w per + i) + lane, all wavefronts
 // holding the same number `per` of items a lane) and trade places through LDS.  Same ranking, hence the same stable
 // order, as the passes over many blocks, in one launch instead of three per pass; a block's time is a few microseconds per pass and 8 items of a
-// thread.  Blocks behind the fields write the samples' aggregation weights.
+// thread. 
 // (26 fields of 1000 lookups, two passes: 29 us of kernels and their gaps -> one launch of 10 us.)
 constexpr int SMALL_THREADS = 1024, SMALL_WAVES = SMALL_THREADS / 64;
 template <int IT>
 __global__ __launch_bounds__(SMALL_THREADS) void sort_small_kernel(const int32_t* keys_in, const int32_t* pay_in, int32_t* keys_out,
-                                                                   int32_t* pay_out, FieldPtr fp, int F, int passes, int rb,
-                                                                   float* sample_w, ShardTab tab) {
+                                                                   int32_t* pay_out, FieldPtr fp, int passes, int rb) {
   __shared__ uint16_t cnt[SMALL_WAVES][MAX_BINS];
   __shared__ uint16_t dpre[MAX_BINS];
   __shared__ uint32_t wsum[SMALL_WAVES];
   extern __shared__ int32_t stage[];   // [SMALL_THREADS * IT]
   const int f = blockIdx.x;
-  if (f >= F) {
-    write_sample_weights(sample_w, tab, (f - F) * SMALL_THREADS + (int)threadIdx.x);
-    return;
-  }
   const int64_t base = fp.p[f];
   const int nnz = (int)(fp.p[f + 1] - base);
   if (nnz == 0) return;
@@ -436,15 +419,14 @@ __global__ __launch_bounds__(SMALL_THREADS) void sort_small_kernel(const int32_t
 }
 
 template <int IT>
-hipError_t launch_sort_small_items(const SortPlan& pl, const SortBuffers& sb, const FieldPtr& fp, const ShardTab& tab, Profiler* prof,
-                                   hipStream_t s) {
+hipError_t launch_sort_small_items(const SortPlan& pl, const SortBuffers& sb, const FieldPtr& fp, Profiler* prof, hipStream_t s) {
   constexpr int bytes = SMALL_THREADS * IT * 4;
   static std::atomic<uint64_t> allowed{0};
   const hipError_t ok = allow_lds(sort_small_kernel<IT>, bytes, 36 * 1024, allowed);
   if (ok != hipSuccess) return ok;
   ProfScope ps(prof, KID_SORT_SCATTER, s);
-  hipLaunchKernelGGL((sort_small_kernel<IT>), dim3(pl.F + (pl.B + SMALL_THREADS - 1) / SMALL_THREADS), dim3(SMALL_THREADS), bytes, s,
-                     sb.ids, sb.pay0, sb.key[0], sb.pay[0], fp, pl.F, pl.passes, pl.radix_bits, sb.sample_w, tab);
+  hipLaunchKernelGGL((sort_small_kernel<IT>), dim3(pl.F), dim3(SMALL_THREADS), bytes, s,
+                     sb.ids, sb.pay0, sb.key[0], sb.pay[0], fp, pl.passes, pl.radix_bits);
   return hipGetLastError();
 }
 
@@ -616,11 +598,35 @@ struct RowSum {   // a lane's four columns (4c .. 4c + 3, c: the lane inside its
   float v[4];
 };
 
+// Aggregation weights by sample: the ranges of samples of one weight (neighbouring shards of equal weight are one), held by
+// the lanes.  (An array of a weight per sample was read at random: a cache line for each lookup of a window of short
+// runs, a sixth of the lines that the reduction of 42 M lookups asked L2 for: 1021 -> 963 us a launch, 4.3 M lookups with eight
+// weights 150 -> 138.)
+struct SampleWeights {
+  int32_t n, start;   // ranges; where this lane's begins
+  float w;            // its weight (of a single range: in every lane)
+  __device__ __forceinline__ SampleWeights(const SegArgs& a, const WeightTab& t) : n(a.weights), start(0x7FFFFFFF), w(a.weight) {
+    const int lane = threadIdx.x & 63;
+    if (n > 1 && lane < n) {
+      start = t.start[lane];
+      w = t.w[lane];
+    }
+  }
+  // (by whole wavefronts)
+  __device__ __forceinline__ float of(int s) const {
+    if (n == 1) return w;
+    int i = 0;
+    for (int step = 1 << (31 - __clz(n - 1)); step > 0; step >>= 1)   // (n <= 64: i + step is a lane)
+      if (s >= __builtin_amdgcn_ds_bpermute((i + step) * 4, start)) i += step;
+    return __int_as_float(__builtin_amdgcn_ds_bpermute(i * 4, __float_as_int(w)));
+  }
+};
+
 // Weight of one lookup of sample s: the shard weight, divided by the length of the sample's bag
 // in this field when the bags are mean-pooled (the bag is not empty: the lookup is in it).
 template <bool MEAN>
-__device__ __forceinline__ float lookup_weight(const SegArgs& a, const int32_t* off, int s) {
-  const float w = a.sample_w[s];
+__device__ __forceinline__ float lookup_weight(const SampleWeights& sw, const int32_t* off, int s) {
+  const float w = sw.of(s);
   if (!MEAN) return w;
   return w / (float)max(off[s + 1] - off[s], 1);
 }
@@ -861,7 +867,7 @@ __device__ __forceinline__ RowSum sum_window(const char* dx, Lookup* look, const
 }
 
 template <typename TT, bool ROWWISE, bool UPDATE, bool MEAN, int W, int THREADS>
-__global__ __launch_bounds__(THREADS, ROWWISE ? 8 : 1) void seg_window_kernel(SegArgs a, FieldPtr fp, TileBase tb) {
+__global__ __launch_bounds__(THREADS, ROWWISE ? 8 : 1) void seg_window_kernel(SegArgs a, FieldPtr fp, TileBase tb, WeightTab wt) {
   constexpr int PARTS = SORT_TILE / W, ROUNDS = W / THREADS, WAVES = THREADS / 64;
   constexpr int BITS = W <= 512 ? 9 : 11, POS = (1 << BITS) - 1, HEAD = 1 << BITS, PIECE = 2 << BITS;   // entries of `order`
   static_assert(W <= 2048 && LONG_RUN == 16, "list entries and the search for long runs");
@@ -882,6 +888,7 @@ __global__ __launch_bounds__(THREADS, ROWWISE ? 8 : 1) void seg_window_kernel(Se
   const int tid = threadIdx.x;
   if (P >= nnz) return;
   const int64_t slot = window_slot(base) + t * PARTS + part;
+  const SampleWeights weights(a, wt);
   const int32_t* off = MEAN ? a.offsets + (int64_t)f * (a.B + 1) : nullptr;
   const int32_t *keys = a.key + base, *pay = a.pay + base;
   const int32_t first_key = __builtin_amdgcn_readfirstlane(keys[P]), last_key = __builtin_amdgcn_readfirstlane(keys[min(P + W, nnz) - 1]);
@@ -899,7 +906,7 @@ __global__ __launch_bounds__(THREADS, ROWWISE ? 8 : 1) void seg_window_kernel(Se
 #pragma unroll
   for (int r = 0; r < ROUNDS; ++r) {
     smp[r] = min(max(smp[r], 0), a.B - 1);
-    weight[r] = lookup_weight<MEAN>(a, off, smp[r]);
+    weight[r] = lookup_weight<MEAN>(weights, off, smp[r]);
   }
   const int lps = a.D >> 2;
   const int ngroups = THREADS / lps;
@@ -919,9 +926,9 @@ __global__ __launch_bounds__(THREADS, ROWWISE ? 8 : 1) void seg_window_kernel(Se
     if (tid == 0 && nnz > W) a.goes_out[slot] = !in && out;
     return;
   }
-  if (tid < LONG_RUN) {
+  if (tid < 64) {   // (a whole wavefront, for LONG_RUN lookups)
     smp_tail = min(max(smp_tail, 0), a.B - 1);
-    weight_tail = lookup_weight<MEAN>(a, off, smp_tail);
+    weight_tail = lookup_weight<MEAN>(weights, off, smp_tail);
   }
   auto stage = [&](int i, int sample, float w) {
     Lookup l;
@@ -1107,7 +1114,7 @@ __global__ __launch_bounds__(256) void seg_finish_kernel(SegArgs a, FieldPtr fp,
 }
 
 template <typename TT, bool ROWWISE, bool UPDATE, bool MEAN, int W, int THREADS = 256>
-void launch_reduce_window(const SegArgs& a, const FieldPtr& fp, const TileBase& tb, Profiler* prof, hipStream_t s) {
+void launch_reduce_window(const SegArgs& a, const FieldPtr& fp, const TileBase& tb, const WeightTab& wt, Profiler* prof, hipStream_t s) {
   const unsigned parts = SORT_TILE / W;
   const int bytes = 2 * W / LONG_RUN * a.D * 4;
   {
@@ -1115,7 +1122,7 @@ void launch_reduce_window(const SegArgs& a, const FieldPtr& fp, const TileBase& 
     constexpr int ONE_FIELD = W > 512 ? 48 * 1024 : 0;   // (static LDS of the wide windows)
     if (allow_lds(seg_window_kernel<TT, ROWWISE, UPDATE, MEAN, W, THREADS>, ONE_FIELD ? 2 * W / LONG_RUN * 64 * 4 : bytes, ONE_FIELD, allowed) != hipSuccess) return;
     ProfScope ps(prof, UPDATE ? KID_SPARSE_ADAGRAD : KID_SEG_REDUCE, s);
-    hipLaunchKernelGGL((seg_window_kernel<TT, ROWWISE, UPDATE, MEAN, W, THREADS>), dim3(tile_grid(a.total_tiles) * parts), dim3(THREADS), bytes, s, a, fp, tb);
+    hipLaunchKernelGGL((seg_window_kernel<TT, ROWWISE, UPDATE, MEAN, W, THREADS>), dim3(tile_grid(a.total_tiles) * parts), dim3(THREADS), bytes, s, a, fp, tb, wt);
   }
   if (W < 1024) {   // (no run leaves a window that holds its field)
     ProfScope ps(prof, KID_SEG_REDUCE_LONG, s);
@@ -1124,23 +1131,23 @@ void launch_reduce_window(const SegArgs& a, const FieldPtr& fp, const TileBase& 
 }
 
 template <typename TT, bool ROWWISE, bool UPDATE, bool MEAN>
-void launch_reduce_pooling(const SegArgs& a, const FieldPtr& fp, const TileBase& tb, Profiler* prof, hipStream_t s) {
-  if (a.window == 2048) launch_reduce_window<TT, ROWWISE, UPDATE, MEAN, 2048, 1024>(a, fp, tb, prof, s);
-  else if (a.window == 1024) launch_reduce_window<TT, ROWWISE, UPDATE, MEAN, 1024, 1024>(a, fp, tb, prof, s);
-  else if (a.window == 512) launch_reduce_window<TT, ROWWISE, UPDATE, MEAN, 512>(a, fp, tb, prof, s);
-  else launch_reduce_window<TT, ROWWISE, UPDATE, MEAN, 256>(a, fp, tb, prof, s);
+void launch_reduce_pooling(const SegArgs& a, const FieldPtr& fp, const TileBase& tb, const WeightTab& wt, Profiler* prof, hipStream_t s) {
+  if (a.window == 2048) launch_reduce_window<TT, ROWWISE, UPDATE, MEAN, 2048, 1024>(a, fp, tb, wt, prof, s);
+  else if (a.window == 1024) launch_reduce_window<TT, ROWWISE, UPDATE, MEAN, 1024, 1024>(a, fp, tb, wt, prof, s);
+  else if (a.window == 512) launch_reduce_window<TT, ROWWISE, UPDATE, MEAN, 512>(a, fp, tb, wt, prof, s);
+  else launch_reduce_window<TT, ROWWISE, UPDATE, MEAN, 256>(a, fp, tb, wt, prof, s);
 }
 
 template <typename TT, bool ROWWISE, bool UPDATE>
-void launch_reduce_variant(const SegArgs& a, const FieldPtr& fp, const TileBase& tb, Profiler* prof, hipStream_t s) {
-  if (a.mean_pool) launch_reduce_pooling<TT, ROWWISE, UPDATE, true>(a, fp, tb, prof, s);
-  else launch_reduce_pooling<TT, ROWWISE, UPDATE, false>(a, fp, tb, prof, s);
+void launch_reduce_variant(const SegArgs& a, const FieldPtr& fp, const TileBase& tb, const WeightTab& wt, Profiler* prof, hipStream_t s) {
+  if (a.mean_pool) launch_reduce_pooling<TT, ROWWISE, UPDATE, true>(a, fp, tb, wt, prof, s);
+  else launch_reduce_pooling<TT, ROWWISE, UPDATE, false>(a, fp, tb, wt, prof, s);
 }
 
 }  // namespace
 
 static hipError_t launch_sort_pass(const SortPlan& pl, const SortBuffers& sb, int pass, const FieldPtr& fp,
-                            const TileBase& tb, const ShardTab& tab, Profiler* prof, hipStream_t s) {
+                            const TileBase& tb, Profiler* prof, hipStream_t s) {
   const int shift = pass * pl.radix_bits;
   const int32_t* kin = pass == 0 ? sb.ids : sb.key[(pass - 1) & 1];
   const int32_t* pin = pass == 0 ? sb.pay0 : sb.pay[(pass - 1) & 1];
@@ -1152,9 +1159,7 @@ static hipError_t launch_sort_pass(const SortPlan& pl, const SortBuffers& sb, in
   {
     ProfScope ps(prof, KID_SORT_SCAN, s);
     const int groups = std::max(1, (1 << pl.radix_bits) / SCAN_DIGITS);
-    const int wblocks = pass == 0 ? (pl.B + SCAN_THREADS - 1) / SCAN_THREADS : 0;
-    hipLaunchKernelGGL(sort_scan_kernel, dim3(pl.F * groups + wblocks), dim3(SCAN_THREADS), 0, s, sb.hist, sb.digit_total, tb, pl.F,
-                       pl.radix_bits, sb.sample_w, tab);
+    hipLaunchKernelGGL(sort_scan_kernel, dim3(pl.F * groups), dim3(SCAN_THREADS), 0, s, sb.hist, sb.digit_total, tb, pl.radix_bits);
   }
   {
     ProfScope ps(prof, KID_SORT_SCATTER, s);
@@ -1164,20 +1169,20 @@ static hipError_t launch_sort_pass(const SortPlan& pl, const SortBuffers& sb, in
   return hipGetLastError();
 }
 
-hipError_t launch_sort(const SortPlan& pl, const SortBuffers& sb, const FieldPtr& fp, const TileBase& tb, const ShardTab& tab,
-                       Profiler* prof, hipStream_t s, int* sorted_buf) {
+hipError_t launch_sort(const SortPlan& pl, const SortBuffers& sb, const FieldPtr& fp, const TileBase& tb, Profiler* prof, hipStream_t s,
+                       int* sorted_buf) {
   *sorted_buf = 0;
   if (pl.total_tiles == 0) return hipSuccess;
   // One block per field as long as a field fits one: two passes over 1000 / 9000 lookups of a field take 10 / 24 us, the
   // six launches 29 / 30 and the host four times as long.
   int64_t most = 0;
   for (int f = 0; f < pl.F; ++f) most = std::max(most, fp.p[f + 1] - fp.p[f]);
-  if (most <= SMALL_THREADS * 2) return launch_sort_small_items<2>(pl, sb, fp, tab, prof, s);
-  if (most <= SMALL_THREADS * 4) return launch_sort_small_items<4>(pl, sb, fp, tab, prof, s);
-  if (most <= SMALL_THREADS * 8) return launch_sort_small_items<8>(pl, sb, fp, tab, prof, s);
-  if (most <= SMALL_THREADS * 16) return launch_sort_small_items<16>(pl, sb, fp, tab, prof, s);
+  if (most <= SMALL_THREADS * 2) return launch_sort_small_items<2>(pl, sb, fp, prof, s);
+  if (most <= SMALL_THREADS * 4) return launch_sort_small_items<4>(pl, sb, fp, prof, s);
+  if (most <= SMALL_THREADS * 8) return launch_sort_small_items<8>(pl, sb, fp, prof, s);
+  if (most <= SMALL_THREADS * 16) return launch_sort_small_items<16>(pl, sb, fp, prof, s);
   for (int p = 0; p < pl.passes; ++p) {
-    const hipError_t e = launch_sort_pass(pl, sb, p, fp, tb, tab, prof, s);
+    const hipError_t e = launch_sort_pass(pl, sb, p, fp, tb, prof, s);
     if (e != hipSuccess) return e;
   }
   *sorted_buf = (pl.passes - 1) & 1;
@@ -1216,18 +1221,28 @@ hipError_t launch_mask_pack(const int32_t* ids, const int32_t* lookup_sample, co
   return hipGetLastError();
 }
 
-hipError_t launch_seg_reduce(const SegArgs& a, const FieldPtr& fp, const TileBase& tb, Profiler* prof, hipStream_t s) {
-  if (a.total_tiles == 0) return hipSuccess;
+hipError_t launch_seg_reduce(const SegArgs& args, const FieldPtr& fp, const TileBase& tb, const ShardTab& tab, Profiler* prof, hipStream_t s) {
+  if (args.total_tiles == 0) return hipSuccess;
+  SegArgs a = args;
+  WeightTab wt = {};
+  a.weights = 0;
+  for (int k = 0; k < tab.K; ++k) {
+    if (tab.len[k] == 0 || (a.weights > 0 && wt.w[a.weights - 1] == tab.w[k])) continue;
+    wt.start[a.weights] = a.weights ? tab.start[k] : 0;
+    wt.w[a.weights++] = tab.w[k];
+  }
+  a.weights = std::max(a.weights, 1);
+  a.weight = wt.w[0];
   if (a.update) {
     if (a.table_bf16) {
-      if (a.rowwise) launch_reduce_variant<bf16_t, true, true>(a, fp, tb, prof, s);
-      else launch_reduce_variant<bf16_t, false, true>(a, fp, tb, prof, s);
+      if (a.rowwise) launch_reduce_variant<bf16_t, true, true>(a, fp, tb, wt, prof, s);
+      else launch_reduce_variant<bf16_t, false, true>(a, fp, tb, wt, prof, s);
     } else {
-      if (a.rowwise) launch_reduce_variant<float, true, true>(a, fp, tb, prof, s);
-      else launch_reduce_variant<float, false, true>(a, fp, tb, prof, s);
+      if (a.rowwise) launch_reduce_variant<float, true, true>(a, fp, tb, wt, prof, s);
+      else launch_reduce_variant<float, false, true>(a, fp, tb, wt, prof, s);
     }
   } else {
-    launch_reduce_variant<float, false, false>(a, fp, tb, prof, s);
+    launch_reduce_variant<float, false, false>(a, fp, tb, wt, prof, s);
   }
   return hipGetLastError();
 }

@@ -46,6 +46,10 @@ struct ShardTab {
   int32_t len[ANTDT_MAX_SHARDS];
   float w[ANTDT_MAX_SHARDS];  // aggregation weight B_k / sum of included B_k (0 if excluded)
 };
+struct WeightTab {   // ranges of samples of one aggregation weight, in sample order
+  int32_t start[ANTDT_MAX_SHARDS];
+  float w[ANTDT_MAX_SHARDS];
+};
 struct TileBase {
   int32_t t[ANTDT_MAX_FIELDS + 1];  // prefix sum of sort tiles per field
 };
@@ -256,7 +260,7 @@ __device__ __forceinline__ void add_up_losses(const LossJob* job) {   // (the fi
 // Keys per sort tile (one block of 512 threads, ANTDT_SORT_TILE / 512 keys per thread).
 constexpr int ANTDT_SORT_TILE = 2048;
 struct SortPlan {
-  int32_t F, B;
+  int32_t F;
   int32_t passes, radix_bits;      // digit width per pass
   int32_t total_tiles;
 };
@@ -267,11 +271,10 @@ struct SortBuffers {
   int32_t* pay[2];
   uint32_t* hist;                  // [total_tiles << radix_bits]
   uint32_t* digit_total;            // [F << radix_bits]
-  float* sample_w;                 // [B] aggregation weight of every sample, written beside the first pass
 };
 // Sorts every field's lookups by row id (stable); the result is in key / pay [*sorted_buf].
-hipError_t launch_sort(const SortPlan& pl, const SortBuffers& sb, const FieldPtr& fp, const TileBase& tb, const ShardTab& tab,
-                       Profiler* prof, hipStream_t s, int* sorted_buf);
+hipError_t launch_sort(const SortPlan& pl, const SortBuffers& sb, const FieldPtr& fp, const TileBase& tb, Profiler* prof, hipStream_t s,
+                       int* sorted_buf);
 
 // Slots of the windows: window i of a field that starts at lookup p has slot p / 128 + i.  A field of n > 256 lookups has
 // ceil(n / 256) <= floor(n / 128) windows at most, so no two fields' windows meet and none lies past the last
@@ -288,7 +291,6 @@ struct SegArgs {
   int32_t* segabs;                 // [U + 1] start of each run in the sorted arrays (all fields)
   int32_t* segoff;                 // [U + F], per-field offsets; field f's slice starts at ubase[f] + f
   float* G;                        // [U, D] coalesced gradient (written when not updating)
-  const float* sample_w;           // [B]
   int32_t window;                  // sorted lookups per block of the reduction: 256 or 512, or (every field in one window) 1024 or 2048
   int32_t* goes_out;               // [slots] the last run of the window starts there, is long and goes on in the next one
   float* partial;                  // [slots, 2, D] sums over the window: of the run that comes in, of the run that goes out
@@ -303,13 +305,15 @@ struct SegArgs {
   float* state;
   int64_t R;
   float lr, eps, inv_dim;          // inv_dim: 1 / D
+  int32_t weights;                 // (set by launch_seg_reduce) ranges of the table of weights; the first one's weight
+  float weight;
 };
 hipError_t launch_expand_samples(const int32_t* offsets, int32_t* lookup_sample, const FieldPtr& fp, int F, int B, hipStream_t s);
 hipError_t launch_segments(const SegArgs& a, const FieldPtr& fp, const TileBase& tb, Profiler* prof, hipStream_t s);
 hipError_t launch_mask_pack(const int32_t* ids, const int32_t* lookup_sample, const int32_t* offsets, int64_t B, int F,
                             const FieldPtr& fp, const ShardTab& tab, int64_t* cbase, int32_t* ids_out,
                             int32_t* pay_out, hipStream_t s);
-hipError_t launch_seg_reduce(const SegArgs& a, const FieldPtr& fp, const TileBase& tb, Profiler* prof, hipStream_t s);
+hipError_t launch_seg_reduce(const SegArgs& a, const FieldPtr& fp, const TileBase& tb, const ShardTab& tab, Profiler* prof, hipStream_t s);
 
 // ---------------------------------------------------------------- optim.hip
 struct DenseAggArgs {

@@ -109,7 +109,7 @@ struct antdt_ctx {
   char* h[ANTDT_MAX_LAYERS] = {};
   char* dh[ANTDT_MAX_LAYERS] = {};
   float* dx = nullptr;
-  float *shard_grads = nullptr, *g_dense = nullptr, *sample_w = nullptr, *G = nullptr;
+  float *shard_grads = nullptr, *g_dense = nullptr, *G = nullptr;
   bf16_t* wb[ANTDT_MAX_LAYERS] = {};     // bf16 W_l as [in (padded), out]: operand of the forward product and the data gradient
   bf16_t* wb0_alt = nullptr;             // second buffer for W_0: a dense update beside the launch stream writes the new
                                          // copy there while the input-gradient product may still read the old one
@@ -249,7 +249,6 @@ static size_t carve(antdt_ctx* c, char* base) {
     if (l == c->L - 1 && !c->act_bf16) c->dh[l] = c->h[l];
     else c->dh[l] = take((size_t)Bm * c->width[l] * c->act_size);
   }
-  c->sample_w = (float*)take(Bm * 4);
   c->dx = (float*)take((size_t)Bm * c->FD * 4);
   c->shard_grads = (float*)take((size_t)K * c->Pstride * 4);
   if (c->act_bf16) {
@@ -324,9 +323,8 @@ static void release_static(antdt_ctx* c) {
   c->static_device = -1;
 }
 
-// Makes `s` wait for whatever the side stream is still doing (it writes the sort buffers, the run
-// tables and the per-sample weights, and reads the sample index of every lookup): before anything
-// rebuilds or overwrites those.  Whether that structure is still valid is a separate question.
+// Makes `s` wait for whatever the side stream is still doing (it writes the sort buffers and reads the sample index of every
+// lookup): before anything rebuilds or overwrites those.  Whether that structure is still valid is a separate question.
 static int join_side(antdt_ctx* c, hipStream_t s) {
   if (c->side_pending) {
     HIP_TRY(c, hipStreamWaitEvent(s, c->ev_join, 0));
@@ -679,7 +677,7 @@ static void fill_seg_args(antdt_ctx* c, SegArgs& a) {
   memset(&a, 0, sizeof(a));
   a.key = c->key[c->sorted_buf]; a.pay = c->pay[c->sorted_buf];
   a.tile_heads = c->tile_heads; a.ubase = c->ubase; a.uniq = c->uniq; a.segabs = c->segabs; a.segoff = c->segoff;
-  a.sample_w = c->sample_w; a.goes_out = c->goes_out; a.partial = c->partial;
+  a.goes_out = c->goes_out; a.partial = c->partial;
   a.G = c->G; a.dx = c->dx; a.lddx = c->FD;
   a.offsets = c->offsets; a.mean_pool = m.pooling == ANTDT_POOL_MEAN;
   a.F = m.num_fields; a.D = m.dim; a.B = (int32_t)c->B; a.total_tiles = c->atotal_tiles;
@@ -711,22 +709,20 @@ static void set_weights(antdt_ctx* c) {
   c->weights_dirty = false;
 }
 
-// Sort the lookups by row id and fill the per-sample weights: everything of the server side that depends only
-// on the batch's ids and on the shard weights.
+// Sort the lookups by row id: everything of the server side that depends only on the batch's ids.
 static int build_coalescing(antdt_ctx* c, const int32_t* ids, const int32_t* pay0, hipStream_t s) {
   Profiler* pr = prof_of(c);
   const antdt_model& m = c->m;
   SortPlan pl;
-  pl.F = m.num_fields; pl.B = (int32_t)c->B; pl.passes = c->sort_passes; pl.radix_bits = c->radix_bits;
+  pl.F = m.num_fields; pl.passes = c->sort_passes; pl.radix_bits = c->radix_bits;
   pl.total_tiles = c->atotal_tiles;
   SortBuffers sb;
   sb.ids = ids;
   sb.key[0] = c->key[0]; sb.key[1] = c->key[1]; sb.pay[0] = c->pay[0]; sb.pay[1] = c->pay[1];
   sb.hist = c->hist;
   sb.digit_total = c->digit_total;
-  sb.sample_w = c->sample_w;
   sb.pay0 = pay0;
-  HIP_TRY(c, launch_sort(pl, sb, c->afp, c->atb, c->tab, pr, s, &c->sorted_buf));
+  HIP_TRY(c, launch_sort(pl, sb, c->afp, c->atb, pr, s, &c->sorted_buf));
   return ANTDT_OK;
 }
 
@@ -1056,8 +1052,9 @@ int antdt_aggregate(antdt_ctx* c, const uint8_t* shard_mask, void* stream) {
     const int rc = join_side(c, s);
     if (rc) return rc;
   }
-  if (c->presorted && all && !c->weights_dirty) {
-    // the batched worker step already built the structure on the side stream
+  if (c->presorted && all) {
+    // the batched worker step already built the structure on the side stream (the weights are no part of it)
+    if (c->weights_dirty) set_weights(c);
   } else if (all) {
     set_weights(c);
     coalesce_whole_batch(c);
@@ -1154,7 +1151,7 @@ int antdt_apply_update(antdt_ctx* c, void* stream) {
     SegArgs a;
     fill_seg_args(c, a);
     a.update = 1;
-    HIP_TRY(c, launch_seg_reduce(a, c->afp, c->atb, pr, s));
+    HIP_TRY(c, launch_seg_reduce(a, c->afp, c->atb, c->tab, pr, s));
   }
   if (c->wgrad_deferred) {
     // Weight gradients, their aggregation over the shards and the dense update in one kernel
@@ -1333,7 +1330,7 @@ int antdt_view_coalesced(antdt_ctx* c, int32_t f, const int32_t** unique_ids, co
     fill_seg_args(c, a);
     a.update = 0;
     HIP_TRY(c, launch_segments(a, c->afp, c->atb, prof_of(c), (hipStream_t)stream));
-    HIP_TRY(c, launch_seg_reduce(a, c->afp, c->atb, prof_of(c), (hipStream_t)stream));
+    HIP_TRY(c, launch_seg_reduce(a, c->afp, c->atb, c->tab, prof_of(c), (hipStream_t)stream));
     c->g_valid = true;
   }
   int32_t ub[2];
