@@ -8,7 +8,7 @@
 #include <algorithm>
 #include <type_traits>
 
-#include "common.h"
+#include "sort.h"
 
 namespace antdt {
 namespace {
@@ -17,32 +17,9 @@ constexpr int SORT_THREADS = 512;
 constexpr int SORT_WAVES = SORT_THREADS / 64;
 constexpr int SORT_TILE = ANTDT_SORT_TILE;            // keys per block
 constexpr int SORT_ITEMS = SORT_TILE / SORT_THREADS;
-constexpr int MAX_BINS = 1024;
 
 // Blocks of a launch of one block per tile (see tile_of_block).
 unsigned tile_grid(int total_tiles) { return 8u * ((total_tiles + 7) / 8); }
-
-__device__ __forceinline__ uint64_t lanemask_lt() {
-  const unsigned lane = threadIdx.x & 63;
-  return lane == 0 ? 0ull : (~0ull >> (64 - lane));
-}
-
-// LDS traffic between the lanes of one wavefront: executed in program order, only the compiler has to keep it so.
-__device__ __forceinline__ void wave_lds_order() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
-
-// x summed over the lanes up to this one.
-__device__ __forceinline__ uint32_t wave_prefix(uint32_t x) {
-  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, false);   // rows of 16 lanes: one lane down, ...
-  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, false);
-  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, false);
-  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, false);   // ... eight
-  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false);   // last lane of a row to the next row (rows 1 and 3)
-  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false);   // lane 31 to rows 2 and 3
-  return x;
-}
 
 // Tile T of all fields' tiles -> (field, tile of the field): how many fields end at or before it, counted by the
 // lanes of the wavefront (one load of the table instead of a chain of them).
@@ -146,21 +123,6 @@ __global__ __launch_bounds__(SCAN_THREADS) void sort_scan_kernel(uint32_t* hist,
   }
   walk(run, true);
   if (part == 0) digit_total[((int64_t)f << rb) + d] = total;
-}
-
-// Lanes (among the valid ones) that hold the same digit.  Per bit: the lane's bit spread over a word, one compare
-// for the ballot, and one three-operand logic operation per half of the mask (these instructions are what
-// bounds the sort's scatter).
-__device__ __forceinline__ uint64_t same_digit(uint32_t d, int rb, bool valid) {
-  const uint64_t all = __ballot(valid);
-  uint32_t lo = (uint32_t)all, hi = (uint32_t)(all >> 32);
-  for (int b = 0; b < rb; ++b) {
-    const uint32_t mine = (uint32_t)__builtin_amdgcn_sbfe((int)d, b, 1);   // 0 or ~0
-    const uint64_t bal = __ballot(mine != 0);
-    lo &= ~(mine ^ (uint32_t)bal);
-    hi &= ~(mine ^ (uint32_t)(bal >> 32));
-  }
-  return (uint64_t)lo | ((uint64_t)hi << 32);
 }
 
 // Stable scatter of one tile.  Wave w owns the contiguous slice w of the tile and walks it in
@@ -318,104 +280,14 @@ __global__ __launch_bounds__(SORT_THREADS, 8) void sort_scatter_kernel(
   else scatter_tile<false>(lds, keys_in + start, pay_in + start, keys_out + base, pay_out + base, hb, totals, count, nnz, shift, rb);
 }
 
-// All passes of a field's sort in one block, for fields of up to SMALL_THREADS * IT lookups: keys and sample
-// indices stay in registers between the passes (item i of wavefront w: position 64 (w per + i) + lane, all wavefronts
-// holding the same number `per` of items a lane) and trade places through LDS.  Same ranking, hence the same stable
-// order, as the passes over many blocks, in one launch instead of three per pass; a block's time is a few microseconds per pass and 8 items of a
-// thread. 
-// (26 fields of 1000 lookups, two passes: 29 us of kernels and their gaps -> one launch of 10 us.)
-constexpr int SMALL_THREADS = 1024, SMALL_WAVES = SMALL_THREADS / 64;
+// Block = field.
 template <int IT>
 __global__ __launch_bounds__(SMALL_THREADS) void sort_small_kernel(const int32_t* keys_in, const int32_t* pay_in, int32_t* keys_out,
                                                                    int32_t* pay_out, FieldPtr fp, int passes, int rb) {
-  __shared__ uint16_t cnt[SMALL_WAVES][MAX_BINS];
-  __shared__ uint16_t dpre[MAX_BINS];
-  __shared__ uint32_t wsum[SMALL_WAVES];
+  __shared__ SmallSortLds lds;
   extern __shared__ int32_t stage[];   // [SMALL_THREADS * IT]
-  const int f = blockIdx.x;
-  const int64_t base = fp.p[f];
-  const int nnz = (int)(fp.p[f + 1] - base);
-  if (nnz == 0) return;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int per = (nnz + SMALL_THREADS - 1) / SMALL_THREADS;   // <= IT
-  const int first = w * (64 * per) + lane;
-  auto mine = [&](int i) { return i < per && first + i * 64 < nnz; };
-  int32_t key[IT], pay[IT];
-#pragma unroll
-  for (int i = 0; i < IT; ++i) {
-    const int pos = min(first + i * 64, nnz - 1);
-    if (i < per) {
-      key[i] = keys_in[base + pos];
-      pay[i] = pay_in[base + pos];
-    }
-  }
-  const int nb = 1 << rb;   // (at most one digit per thread)
-  const uint64_t lt = lanemask_lt();
-  for (int p = 0; p < passes; ++p) {
-    const int shift = p * rb;
-    for (int d = lane; d < nb; d += 64) cnt[w][d] = 0;   // (each wavefront its own row)
-    wave_lds_order();
-    uint32_t rank[IT];
-#pragma unroll
-    for (int i = 0; i < IT; ++i) {
-      rank[i] = 0;
-      if (i < per && w * (64 * per) + i * 64 < nnz) {   // (uniform)
-        const bool valid = first + i * 64 < nnz;
-        const uint32_t d = ((uint32_t)key[i] >> shift) & (nb - 1);
-        const uint64_t m = same_digit(d, rb, valid);
-        const uint32_t prior = cnt[w][d];
-        wave_lds_order();
-        rank[i] = prior + (uint32_t)__popcll(m & lt);
-        if (valid && (m & lt) == 0) cnt[w][d] = (uint16_t)(prior + (uint32_t)__popcll(m));   // lowest lane of the group
-        wave_lds_order();
-      }
-    }
-    __syncthreads();
-    // per digit: exclusive prefix over the wavefronts, then over the digits
-    uint32_t tot = 0;
-    if ((int)threadIdx.x < nb) {
-      uint32_t c[SMALL_WAVES];
-#pragma unroll
-      for (int q = 0; q < SMALL_WAVES; ++q) c[q] = cnt[q][threadIdx.x];
-#pragma unroll
-      for (int q = 0; q < SMALL_WAVES; ++q) {
-        cnt[q][threadIdx.x] = (uint16_t)tot;
-        tot += c[q];
-      }
-    }
-    const uint32_t incl = wave_prefix(tot);
-    if (lane == 63) wsum[w] = incl;
-    __syncthreads();
-    uint32_t before = 0;
-    for (int q = 0; q < w; ++q) before += wsum[q];
-    if ((int)threadIdx.x < nb) dpre[threadIdx.x] = (uint16_t)(before + incl - tot);
-    __syncthreads();
-    uint32_t place[IT];
-#pragma unroll
-    for (int i = 0; i < IT; ++i) {
-      if (i >= per) break;
-      const uint32_t d = ((uint32_t)key[i] >> shift) & (nb - 1);
-      place[i] = dpre[d] + cnt[w][d] + rank[i];
-    }
-    auto trade = [&](int32_t (&x)[IT]) {
-#pragma unroll
-      for (int i = 0; i < IT; ++i)
-        if (mine(i)) stage[place[i]] = x[i];
-      __syncthreads();
-#pragma unroll
-      for (int i = 0; i < IT; ++i)
-        if (mine(i)) x[i] = stage[first + i * 64];
-      __syncthreads();
-    };
-    trade(key);
-    trade(pay);
-  }
-#pragma unroll
-  for (int i = 0; i < IT; ++i)
-    if (mine(i)) {
-      keys_out[base + first + i * 64] = key[i];
-      pay_out[base + first + i * 64] = pay[i];
-    }
+  const int64_t base = fp.p[blockIdx.x];
+  sort_small_field<IT>(lds, stage, keys_in + base, pay_in + base, keys_out + base, pay_out + base, (int)(fp.p[blockIdx.x + 1] - base), passes, rb);
 }
 
 template <int IT>
@@ -1188,12 +1060,12 @@ hipError_t launch_sort(const SortPlan& pl, const SortBuffers& sb, const FieldPtr
   if (pl.total_tiles == 0) return hipSuccess;
   // One block per field as long as a field fits one: two passes over 1000 / 9000 lookups of a field take 10 / 24 us, the
   // six launches 29 / 30 and the host four times as long.
-  int64_t most = 0;
-  for (int f = 0; f < pl.F; ++f) most = std::max(most, fp.p[f + 1] - fp.p[f]);
-  if (most <= SMALL_THREADS * 2) return launch_sort_small_items<2>(pl, sb, fp, prof, s);
-  if (most <= SMALL_THREADS * 4) return launch_sort_small_items<4>(pl, sb, fp, prof, s);
-  if (most <= SMALL_THREADS * 8) return launch_sort_small_items<8>(pl, sb, fp, prof, s);
-  if (most <= SMALL_THREADS * 16) return launch_sort_small_items<16>(pl, sb, fp, prof, s);
+  switch (small_sort_items(pl.F, fp)) {
+    case 2: return launch_sort_small_items<2>(pl, sb, fp, prof, s);
+    case 4: return launch_sort_small_items<4>(pl, sb, fp, prof, s);
+    case 8: return launch_sort_small_items<8>(pl, sb, fp, prof, s);
+    case 16: return launch_sort_small_items<16>(pl, sb, fp, prof, s);
+  }
   for (int p = 0; p < pl.passes; ++p) {
     const hipError_t e = launch_sort_pass(pl, sb, p, fp, tb, prof, s);
     if (e != hipSuccess) return e;
@@ -1201,6 +1073,8 @@ hipError_t launch_sort(const SortPlan& pl, const SortBuffers& sb, const FieldPtr
   *sorted_buf = (pl.passes - 1) & 1;
   return hipSuccess;
 }
+
+bool sort_fits_blocks(int F, const FieldPtr& fp) { return small_sort_items(F, fp) > 0; }
 
 hipError_t launch_expand_samples(const int32_t* offsets, int32_t* lookup_sample, const FieldPtr& fp, int F, int B, hipStream_t s) {
   if (B <= 0) return hipSuccess;

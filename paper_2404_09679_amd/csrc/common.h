@@ -172,6 +172,21 @@ struct KSegments {
   int32_t ts[ANTDT_MAX_SHARDS], te[ANTDT_MAX_SHARDS];   // tiles of the loss kernel [ts, te)
   float w[ANTDT_MAX_SHARDS];
 };
+// Keys per sort tile (one block of 512 threads, ANTDT_SORT_TILE / 512 keys per thread).
+constexpr int ANTDT_SORT_TILE = 2048;
+struct SortPlan {
+  int32_t F;
+  int32_t passes, radix_bits;      // digit width per pass
+  int32_t total_tiles;
+};
+struct SortBuffers {
+  const int32_t* ids;
+  const int32_t* pay0;             // sample index of every lookup (payload of the first pass)
+  int32_t* key[2];
+  int32_t* pay[2];
+  uint32_t* hist;                  // [total_tiles << radix_bits]
+  uint32_t* digit_total;            // [F << radix_bits]
+};
 // Weight gradients of all layers in one launch (see wgrad_kernel, wgrad_f32_kernel): per range written to
 // the shards' flat gradients, or aggregated and applied (Adagrad) on the spot, in which case neither
 // the per-shard nor the aggregated gradient goes to memory.
@@ -198,6 +213,10 @@ struct WgradArgs {
   int32_t k0;
 };
 hipError_t launch_wgrad(const WgradArgs& a, const KSegments& seg, bool store, hipStream_t s);
+// Per-shard gradients of an fp32 model and, in the same launch, the sort (launch_sort with every field in one block, result in
+// key / pay [0]).
+hipError_t launch_wgrad_and_sort(const WgradArgs& a, const KSegments& seg, const SortPlan& pl, const SortBuffers& sb, const FieldPtr& fp, hipStream_t s);
+bool sort_fits_blocks(int F, const FieldPtr& fp);   // every field in one block
 
 struct CastArgs {  // fp32 [rows, cols] -> bf16 [rows_pad, cols], extra rows zero
   const float* src;
@@ -257,21 +276,6 @@ __device__ __forceinline__ void add_up_losses(const LossJob* job) {   // (the fi
 }
 
 // ------------------------------------------------------------- coalesce.hip
-// Keys per sort tile (one block of 512 threads, ANTDT_SORT_TILE / 512 keys per thread).
-constexpr int ANTDT_SORT_TILE = 2048;
-struct SortPlan {
-  int32_t F;
-  int32_t passes, radix_bits;      // digit width per pass
-  int32_t total_tiles;
-};
-struct SortBuffers {
-  const int32_t* ids;
-  const int32_t* pay0;             // sample index of every lookup (payload of the first pass)
-  int32_t* key[2];
-  int32_t* pay[2];
-  uint32_t* hist;                  // [total_tiles << radix_bits]
-  uint32_t* digit_total;            // [F << radix_bits]
-};
 // Sorts every field's lookups by row id (stable); the result is in key / pay [*sorted_buf].
 hipError_t launch_sort(const SortPlan& pl, const SortBuffers& sb, const FieldPtr& fp, const TileBase& tb, Profiler* prof, hipStream_t s,
                        int* sorted_buf);

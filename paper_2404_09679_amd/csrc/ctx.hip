@@ -710,19 +710,22 @@ static void set_weights(antdt_ctx* c) {
 }
 
 // Sort the lookups by row id: everything of the server side that depends only on the batch's ids.
-static int build_coalescing(antdt_ctx* c, const int32_t* ids, const int32_t* pay0, hipStream_t s) {
-  Profiler* pr = prof_of(c);
+static void fill_sort(antdt_ctx* c, const int32_t* ids, const int32_t* pay0, SortPlan& pl, SortBuffers& sb) {
   const antdt_model& m = c->m;
-  SortPlan pl;
   pl.F = m.num_fields; pl.passes = c->sort_passes; pl.radix_bits = c->radix_bits;
   pl.total_tiles = c->atotal_tiles;
-  SortBuffers sb;
   sb.ids = ids;
   sb.key[0] = c->key[0]; sb.key[1] = c->key[1]; sb.pay[0] = c->pay[0]; sb.pay[1] = c->pay[1];
   sb.hist = c->hist;
   sb.digit_total = c->digit_total;
   sb.pay0 = pay0;
-  HIP_TRY(c, launch_sort(pl, sb, c->afp, c->atb, pr, s, &c->sorted_buf));
+}
+
+static int build_coalescing(antdt_ctx* c, const int32_t* ids, const int32_t* pay0, hipStream_t s) {
+  SortPlan pl;
+  SortBuffers sb;
+  fill_sort(c, ids, pay0, pl, sb);
+  HIP_TRY(c, launch_sort(pl, sb, c->afp, c->atb, prof_of(c), s, &c->sorted_buf));
   return ANTDT_OK;
 }
 
@@ -745,8 +748,9 @@ static void fill_wgrad_args(antdt_ctx* c, WgradArgs& u) {
   u.grads = c->shard_grads; u.stride = c->Pstride;
 }
 
-// Per-shard gradients of all dense layers for shards [k0, k1), one launch on `ws`.
-static int shard_weight_gradients(antdt_ctx* c, int k0, int k1, hipStream_t ws) {
+// Per-shard gradients of all dense layers for shards [k0, k1), one launch on `ws`; with `sort` the launch of an fp32 model
+// also sorts the batch's lookups.
+static int shard_weight_gradients(antdt_ctx* c, int k0, int k1, hipStream_t ws, bool sort = false) {
   WgradArgs u;
   fill_wgrad_args(c, u);
   u.k0 = k0;
@@ -759,7 +763,15 @@ static int shard_weight_gradients(antdt_ctx* c, int k0, int k1, hipStream_t ws) 
     seg.ts[q] = ht.base[k0 + q]; seg.te[q] = ht.base[k0 + q + 1];
   }
   ProfScope ps(prof_of(c), KID_GEMM_WGRAD, ws);
-  HIP_TRY(c, launch_wgrad(u, seg, true, ws));
+  if (sort) {
+    SortPlan pl;
+    SortBuffers sb;
+    fill_sort(c, c->ids, c->lookup_sample, pl, sb);
+    HIP_TRY(c, launch_wgrad_and_sort(u, seg, pl, sb, c->afp, ws));
+    c->sorted_buf = 0;
+  } else {
+    HIP_TRY(c, launch_wgrad(u, seg, true, ws));
+  }
   return ANTDT_OK;
 }
 
@@ -1010,8 +1022,16 @@ static int worker_range(antdt_ctx* c, int k0, int k1, float* loss_out, hipStream
   }
   bwd_scope.close();
   if (!deferred) {
-    const int rc = shard_weight_gradients(c, k0, k1, s);
+    // All shards of an fp32 model whose sort goes to no other stream: it runs beside the weight gradients
+    const bool sort = c->batched && !beside && !c->act_bf16 && c->total_tiles > 0 && sort_fits_blocks(m.num_fields, c->fp);
+    if (sort) {
+      for (int k = 0; k < tab.K; ++k) c->included[k] = true;
+      set_weights(c);
+      coalesce_whole_batch(c);
+    }
+    const int rc = shard_weight_gradients(c, k0, k1, s, sort);
     if (rc) return rc;
+    c->presorted = c->presorted || sort;
   }
   for (int k = k0; k < k1; ++k) {
     c->stepped[k] = true;

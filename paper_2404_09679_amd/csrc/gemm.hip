@@ -5,6 +5,7 @@
 #include <algorithm>
 
 #include "mfma.h"
+#include "sort.h"
 
 namespace antdt {
 namespace {
@@ -170,11 +171,11 @@ __device__ __forceinline__ float adagrad1(float p, float& s, float g, float lr, 
 // samples, or, of a model without a hidden layer, may have left dz per sample (the sums are then formed from the samples,
 // T: type of the input); 64 columns per block, four lanes of tiles or samples per column.
 template <WgradMode MODE, typename T>
-__device__ __forceinline__ void last_layer(const WgradArgs& u, const KSegments& seg, int block, float (*red)[64]) {
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
+__device__ __forceinline__ void last_layer(const WgradArgs& u, const KSegments& seg, int block, int shard, int tid, float (*red)[64]) {
+  const int tx = tid & 63, ty = tid >> 6;
   const int j = block * 64 + tx;
   const bool on = j <= u.width;
-  const int q0 = MODE == WGRAD_STORE ? (int)blockIdx.y : 0, q1 = MODE == WGRAD_STORE ? q0 + 1 : seg.n;
+  const int q0 = MODE == WGRAD_STORE ? shard : 0, q1 = MODE == WGRAD_STORE ? q0 + 1 : seg.n;
   float g = 0.0f;
   for (int q = q0; q < q1; ++q) {
     float sum = 0.0f;
@@ -203,7 +204,7 @@ __device__ __forceinline__ void last_layer(const WgradArgs& u, const KSegments& 
   if (!on || ty != 0) return;
   const int64_t idx = u.last_off + j;
   if (MODE == WGRAD_STORE) {
-    u.grads[(int64_t)(u.k0 + blockIdx.y) * u.stride + idx] = g;
+    u.grads[(int64_t)(u.k0 + shard) * u.stride + idx] = g;
   } else {
     float s1 = u.state[idx];
     u.p[idx] = adagrad1(u.p[idx], s1, g, u.lr, u.eps);
@@ -216,7 +217,7 @@ __global__ __launch_bounds__(64 * WR * WC) void wgrad_kernel(WgradArgs u, KSegme
   typedef BlockProduct<TM, TN, WR, WC, BK, STAGES, true, true, FAR> P;
   extern __shared__ __attribute__((aligned(16))) char lds[];
   if ((int)blockIdx.x >= u.tile_base[u.n_layers]) {
-    last_layer<MODE, bf16_t>(u, seg, blockIdx.x - u.tile_base[u.n_layers], reinterpret_cast<float(*)[64]>(lds));
+    last_layer<MODE, bf16_t>(u, seg, blockIdx.x - u.tile_base[u.n_layers], blockIdx.y, threadIdx.x, reinterpret_cast<float(*)[64]>(lds));
     return;
   }
   int li = 0;
@@ -479,20 +480,26 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs p, int tiles_n, 
 // four wavefronts of a block share one tile and take every fourth step of the contraction (over samples:
 // there are few tiles and the contraction is long); their sums are added in LDS.  397-256-128 model, 1500 samples
 // of five shards: 16 us, against 177 us for the four products and bias sums of one layer each before.
+// (By 256 threads; `tid`: this one's number among them.  Two barriers either way.)
+template <int TM, int TN> struct WgradF32Lds {
+  static constexpr int BM = 16 * TM, BN = 16 * TN, PITCH = BN + 4;
+  float red[4][(BM + 1) * PITCH];   // row BM: the bias gradient
+};
 template <int TM, int TN, int D>
-__global__ __launch_bounds__(256) void wgrad_f32_kernel(WgradArgs u, KSegments seg) {
-  constexpr int BM = 16 * TM, BN = 16 * TN, PITCH = BN + 4;
-  __shared__ __attribute__((aligned(16))) float red[4][(BM + 1) * PITCH];   // row BM: the bias gradient
-  if ((int)blockIdx.x >= u.tile_base[u.n_layers]) {
-    last_layer<WGRAD_STORE, float>(u, seg, blockIdx.x - u.tile_base[u.n_layers], reinterpret_cast<float(*)[64]>(&red[0][0]));
+__device__ __forceinline__ void wgrad_f32_tile(const WgradArgs& u, const KSegments& seg, int tile, int q, int tid, WgradF32Lds<TM, TN>& lds) {
+  typedef WgradF32Lds<TM, TN> Lds;
+  constexpr int BM = Lds::BM, BN = Lds::BN, PITCH = Lds::PITCH;
+  auto& red = lds.red;
+  if (tile >= u.tile_base[u.n_layers]) {
+    last_layer<WGRAD_STORE, float>(u, seg, tile - u.tile_base[u.n_layers], q, tid, reinterpret_cast<float(*)[64]>(&red[0][0]));
     return;
   }
   int li = 0;
-  while (li + 1 < u.n_layers && (int)blockIdx.x >= u.tile_base[li + 1]) ++li;
-  const int pid = blockIdx.x - u.tile_base[li], q = blockIdx.y;
+  while (li + 1 < u.n_layers && tile >= u.tile_base[li + 1]) ++li;
+  const int pid = tile - u.tile_base[li];
   const int M = u.M[li], N = u.N[li];
   const int m0 = (pid / u.tiles_n[li]) * BM, n0 = (pid % u.tiles_n[li]) * BN;
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const bool ones = m0 == 0;
   f32x4 acc[TM][TN] = {}, accb[TN] = {};
   const float* A = reinterpret_cast<const float*>(u.A[li]) + (int64_t)seg.ks[q] * u.lda[li];
@@ -510,12 +517,41 @@ __global__ __launch_bounds__(256) void wgrad_f32_kernel(WgradArgs u, KSegments s
   }
   __syncthreads();
   float* out = u.grads + (int64_t)(u.k0 + q) * u.stride + u.w_off[li];
-  for (int e = threadIdx.x; e < (BM + (ones ? 1 : 0)) * BN; e += 256) {
+  for (int e = tid; e < (BM + (ones ? 1 : 0)) * BN; e += 256) {
     const int r = e / BN, c = e % BN, n = n0 + c;
     const int m = r == BM ? M : m0 + r;   // the bias lies behind the weights
     if (n >= N || (r < BM && m >= M)) continue;
     const int o = r * PITCH + c;
     out[(int64_t)m * N + n] = (red[0][o] + red[1][o]) + (red[2][o] + red[3][o]);
+  }
+  __syncthreads();
+}
+
+template <int TM, int TN, int D>
+__global__ __launch_bounds__(256) void wgrad_f32_kernel(WgradArgs u, KSegments seg) {
+  __shared__ __attribute__((aligned(16))) WgradF32Lds<TM, TN> lds;
+  wgrad_f32_tile<TM, TN, D>(u, seg, blockIdx.x, blockIdx.y, threadIdx.x, lds);
+}
+
+// The same with the sort of the coming aggregation beside it, a field to a block ahead of the others, which do four tiles each:
+// neither waits for the other, both leave most compute units idle, and one stream runs its launches one after the other
+// (1500 samples, 397-256-128, 12 fields of 9000 lookups: 15 + 23 us apart, 256 samples, 141-64-32, 8 fields of 640: 5 + 6).
+template <int TM, int TN, int D, int IT>
+__global__ __launch_bounds__(SMALL_THREADS) void wgrad_f32_sort_kernel(WgradArgs u, KSegments seg, int tiles, SortBuffers sb, FieldPtr fp, int F,
+                                                                       int passes, int rb) {
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  if ((int)blockIdx.x < F) {
+    const int64_t base = fp.p[blockIdx.x];
+    sort_small_field<IT>(*reinterpret_cast<SmallSortLds*>(lds), reinterpret_cast<int32_t*>(lds + sizeof(SmallSortLds)), sb.ids + base, sb.pay0 + base,
+                         sb.key[0] + base, sb.pay[0] + base, (int)(fp.p[blockIdx.x + 1] - base), passes, rb);
+    return;
+  }
+  const int sub = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8), i = ((int)blockIdx.x - F) * 4 + sub;
+  if (i < tiles * seg.n) {
+    wgrad_f32_tile<TM, TN, D>(u, seg, i % tiles, i / tiles, threadIdx.x & 255, reinterpret_cast<WgradF32Lds<TM, TN>*>(lds)[sub]);
+  } else {   // (the others' barriers)
+    __syncthreads();
+    __syncthreads();
   }
 }
 
@@ -577,23 +613,46 @@ hipError_t launch_f32(const GemmArgs& a, hipStream_t s) {
   return launch_f32_tile<1, 1, 4>(a, s);
 }
 
+template <int TM, int TN, int D, int IT>
+hipError_t launch_wgrad_f32_sort(const WgradArgs& u, const KSegments& seg, int tiles, const SortPlan& pl, const SortBuffers& sb, const FieldPtr& fp,
+                                 hipStream_t s) {
+  constexpr int sort_bytes = (int)sizeof(SmallSortLds) + SMALL_THREADS * IT * 4, tile_bytes = 4 * (int)sizeof(WgradF32Lds<TM, TN>);
+  constexpr int bytes = sort_bytes > tile_bytes ? sort_bytes : tile_bytes;
+  static std::atomic<uint64_t> allowed{0};
+  const hipError_t ok = allow_lds(wgrad_f32_sort_kernel<TM, TN, D, IT>, bytes, 0, allowed);
+  if (ok != hipSuccess) return ok;
+  hipLaunchKernelGGL((wgrad_f32_sort_kernel<TM, TN, D, IT>), dim3(pl.F + (tiles * seg.n + 3) / 4), dim3(SMALL_THREADS), bytes, s, u, seg, tiles, sb, fp,
+                     pl.F, pl.passes, pl.radix_bits);
+  return hipGetLastError();
+}
+
 template <int TM, int TN, int D>
-hipError_t launch_wgrad_f32_tile(const WgradArgs& a, const KSegments& seg, hipStream_t s) {
+hipError_t launch_wgrad_f32_tile(const WgradArgs& a, const KSegments& seg, const SortPlan* pl, const SortBuffers* sb, const FieldPtr* fp, hipStream_t s) {
   WgradArgs u = a;
   u.tile_base[0] = 0;
   for (int l = 0; l < u.n_layers; ++l) {
     u.tiles_n[l] = (u.N[l] + 16 * TN - 1) / (16 * TN);
     u.tile_base[l + 1] = u.tile_base[l] + (u.M[l] + 16 * TM - 1) / (16 * TM) * u.tiles_n[l];
   }
-  hipLaunchKernelGGL((wgrad_f32_kernel<TM, TN, D>), dim3(u.tile_base[u.n_layers] + (u.width + 64) / 64, seg.n), dim3(256), 0, s, u, seg);
+  const int tiles = u.tile_base[u.n_layers] + (u.width + 64) / 64;
+  if (pl) {
+    switch (small_sort_items(pl->F, *fp)) {
+      case 2: return launch_wgrad_f32_sort<TM, TN, D, 2>(u, seg, tiles, *pl, *sb, *fp, s);
+      case 4: return launch_wgrad_f32_sort<TM, TN, D, 4>(u, seg, tiles, *pl, *sb, *fp, s);
+      case 8: return launch_wgrad_f32_sort<TM, TN, D, 8>(u, seg, tiles, *pl, *sb, *fp, s);
+      case 16: return launch_wgrad_f32_sort<TM, TN, D, 16>(u, seg, tiles, *pl, *sb, *fp, s);
+      default: return hipErrorInvalidValue;
+    }
+  }
+  hipLaunchKernelGGL((wgrad_f32_kernel<TM, TN, D>), dim3(tiles, seg.n), dim3(256), 0, s, u, seg);
   return hipGetLastError();
 }
 
-hipError_t launch_wgrad_f32(const WgradArgs& a, const KSegments& seg, hipStream_t s) {
+hipError_t launch_wgrad_f32(const WgradArgs& a, const KSegments& seg, const SortPlan* pl, const SortBuffers* sb, const FieldPtr* fp, hipStream_t s) {
   int64_t blocks = 0;
   for (int l = 0; l < a.n_layers; ++l) blocks += (int64_t)((a.M[l] + 31) / 32) * ((a.N[l] + 31) / 32);
-  if (blocks * seg.n >= 512) return launch_wgrad_f32_tile<2, 2, 2>(a, seg, s);
-  return launch_wgrad_f32_tile<1, 1, 4>(a, seg, s);
+  if (blocks * seg.n >= 512) return launch_wgrad_f32_tile<2, 2, 2>(a, seg, pl, sb, fp, s);
+  return launch_wgrad_f32_tile<1, 1, 4>(a, seg, pl, sb, fp, s);
 }
 
 template <int TM, int TN, int WR, int WC, int BK, int STAGES, WgradMode MODE, bool FAR = false>
@@ -642,9 +701,16 @@ hipError_t launch_wgrad(const WgradArgs& a, const KSegments& seg, bool store, hi
   if (store && seg.n <= 0) return hipSuccess;
   for (int l = 0; l < a.n_layers; ++l)
     if (a.M[l] <= 0 || a.N[l] <= 0 || (a.bf16 && (a.N[l] & 7))) return hipErrorInvalidValue;
-  if (!a.bf16) return store ? launch_wgrad_f32(a, seg, s) : hipErrorInvalidValue;
+  if (!a.bf16) return store ? launch_wgrad_f32(a, seg, nullptr, nullptr, nullptr, s) : hipErrorInvalidValue;
   if (store) return launch_wgrad_sized<WGRAD_STORE>(a, seg, seg.n, s);
   return seg.n == 1 ? launch_wgrad_sized<WGRAD_ONE>(a, seg, 1, s) : launch_wgrad_sized<WGRAD_MANY>(a, seg, 1, s);
+}
+
+hipError_t launch_wgrad_and_sort(const WgradArgs& a, const KSegments& seg, const SortPlan& pl, const SortBuffers& sb, const FieldPtr& fp, hipStream_t s) {
+  for (int l = 0; l < a.n_layers; ++l)
+    if (a.M[l] <= 0 || a.N[l] <= 0) return hipErrorInvalidValue;
+  if (a.bf16 || seg.n <= 0) return hipErrorInvalidValue;
+  return launch_wgrad_f32(a, seg, &pl, &sb, &fp, s);
 }
 
 hipError_t launch_cast_bf16(const CastArgs& a, hipStream_t s) {
