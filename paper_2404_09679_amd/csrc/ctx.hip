@@ -179,22 +179,23 @@ struct antdt_ctx {
 
 // The library's own streams, or none when the context works on the caller's stream only.  Going to another stream
 // and back costs the host about 25 us (the waits on events), so it has to hide that much GPU work.
-//   Sort: all but the smallest batches (5 000 / 26 000 / 140 000 lookups, sort on the side or not: 71 / 62, 92 / 95 and
-//   106 / 115 us per step).
-//   Dense update beside the sparse one: where there are many lookups or many weights (26 fields, 1024-512-256:
-//   26 000 / 70 000 / 140 000 / 560 000 lookups, beside or after: 98 / 92, 107 / 101, 106 / 108, 137 / 145 us per
-//   step; 3840-1024-512 at 50 000: 102 / 122).  After one worker step per shard not: six workers, 1024-512-256, with
+//   Sort: from 100 000 lookups (26 fields, 1024-512-256, dense update on the launch stream, sort on the side or not, us per step:
+//   22 000 / 36 000 / 52 000 / 82 000 / 115 000 / 164 000 / 273 000 lookups 80 / 73, 83 / 79, 85 / 82, 89 / 85, 90 / 91, 93 / 99, 101 / 115;
+//   3200-1024-512 with D = 64 at 70 000, dense update on the side: 100 / 90).
+//   Dense update beside the sparse one: where there are many lookups or many weights (the same model, beside or after:
+//   164 000 / 273 000 / 355 000 / 546 000 / 682 000 / 874 000 lookups 111 / 93, 112 / 101, 115 / 109, 134 / 126, 140 / 144, 158 / 168;
+//   3840-1024-512 at 50 000: 102 / 122).  After one worker step per shard not: six workers, 1024-512-256, with
 //   300 000 / 500 000 / 700 000 / 1.6 M / 4.1 M lookups 367 / 322, 398 / 345, 424 / 376, 539 / 500, 838 / 816 us; eight, 3840-1024-512
 //   with 0.9 / 3.8 / 12 M 550 / 505, 846 / 845, 1504 / 1497 us.  Unless shards were left out: the host has then waited for the
 //   stream and is no longer ahead of it (one of six workers left out, 700 000 / 1.6 M / 4.1 M lookups 374 / 380, 473 / 482,
 //   804 / 829 us, fewer lookups alike; one of eight with 0.9 / 3.8 M 486 / 508, 778 / 822).  fp32 models never (176 / 171 us
 //   at 430 000 lookups).
 static inline hipStream_t side_stream(const antdt_ctx* c) {
-  return (c->static_bound || c->no_streams || c->fp.p[c->m.num_fields] < 16384) ? nullptr : c->side;
+  return (c->static_bound || c->no_streams || c->fp.p[c->m.num_fields] < 100000) ? nullptr : c->side;
 }
 static inline hipStream_t wgrad_stream(const antdt_ctx* c) {
   const bool enough = c->act_bf16 && (c->batched || c->left_out) &&
-                      (c->fp.p[c->m.num_fields] >= (c->batched ? 100000 : 600000) || c->P >= 2000000);
+                      (c->fp.p[c->m.num_fields] >= 600000 || c->P >= 2000000);
   return (c->static_bound || c->no_streams || !enough) ? nullptr : c->wside;
 }
 

@@ -535,7 +535,7 @@ __global__ __launch_bounds__(256) void wgrad_f32_kernel(WgradArgs u, KSegments s
 
 // The same with the sort of the coming aggregation beside it, a field to a block ahead of the others, which do four tiles each:
 // neither waits for the other, both leave most compute units idle, and one stream runs its launches one after the other
-// (1500 samples, 397-256-128, 12 fields of 9000 lookups: 15 + 23 us apart, 256 samples, 141-64-32, 8 fields of 640: 5 + 6).
+// (1500 samples, 397-256-128, 12 fields of 9000 lookups: 15 + 23 us apart, 256 samples, 141-64-32, 8 fields of 640: 5 + 6; together 31 and 8).
 template <int TM, int TN, int D, int IT>
 __global__ __launch_bounds__(SMALL_THREADS) void wgrad_f32_sort_kernel(WgradArgs u, KSegments seg, int tiles, SortBuffers sb, FieldPtr fp, int F,
                                                                        int passes, int rb) {
