@@ -440,3 +440,19 @@ def test_windows_of_whole_fields(most, dim, table, state, pooling, monkeypatch):
     _plant(monkeypatch, ids, B, lambda f, n: np.concatenate([[0], np.sort(rng.integers(0, n + 1, B - 1)), [n]]))
     # (accumulators from zero: see test_sort_over_many_blocks)
     check_iteration(cfg, cfg.shard_sizes, tol=TOL32, batched=True)
+
+
+# fp32 models of a batched step: the sort of fields that fit a block in the weight-gradient launch, tiles of 32 rows and columns
+# (many shards) and of 16, each size of the sort; an empty field, an empty shard, blocks of four tiles that are not all there
+@pytest.mark.parametrize("most", [2048, 4096, 8192, 16384])
+@pytest.mark.parametrize("hidden,shards", [((264, 136), (90, 1, 0, 200, 9, 50)), ((40, 24), (341, 9))], ids=["tiles-32", "tiles-16"])
+def test_sort_beside_the_weight_gradients(most, hidden, shards, monkeypatch):
+    sizes = [most, most // 2 + 1, 0, 1]
+    B = sum(shards)
+    cfg = _config(f"beside-{most}", 760, num_fields=len(sizes), rows_per_field=3000, dim=8, layer_sizes=hidden, gemm_dtype="f32", shard_sizes=shards,
+                  max_bag=most // 300 + 2, min_bag=0)
+    rng = np.random.default_rng(most)
+    ids = [rng.integers(0, 3000, n) // rng.integers(1, 40, n) for n in sizes]
+    _plant(monkeypatch, ids, B, lambda f, n: np.concatenate([[0], np.sort(rng.integers(0, n + 1, B - 1)), [n]]))
+    # (accumulators from zero: see test_sort_over_many_blocks)
+    check_iteration(cfg, cfg.shard_sizes, tol=TOL32, batched=True)

@@ -180,3 +180,30 @@ def test_dense_update_beside_the_launch_stream(cfg, batched):
                 run.ctx.aggregate([0] + [1] * (K - 1))
             run.ctx.apply_update()
     assert_same(weights(runs[0]), weights(runs[1]), "three iterations")
+
+
+# The same with the sort on a stream of its own (105 000 lookups) and, of fp32 models, in the weight-gradient launch
+LONG_BF = wl.scaled(WIDE_BF, name="order-long", shard_sizes=(600, 74, 0, 1326))
+
+
+@pytest.mark.parametrize("cfg,streams", [(LONG_BF, True), (wl.scaled(LONG_BF, name="order-long-f32", gemm_dtype="f32", layer_sizes=(173, 256, 64, 1)), True),
+                                         (wl.scaled(SMALL_BF, name="order-f32", gemm_dtype="f32"), True),
+                                         (wl.scaled(SMALL_BF, name="order-f32", gemm_dtype="f32"), False)],
+                         ids=["sort-beside", "sort-beside-f32", "sort-in-launch", "sort-in-launch-one-stream"])
+def test_replays_with_the_sort_elsewhere(cfg, streams):
+    assert (len(wl.make_batch(cfg).ids) >= 100_000) == cfg.name.startswith("order-long")
+    test_replays_of_a_captured_iteration(cfg, streams)
+
+
+@pytest.mark.parametrize("cfg", [wl.scaled(SMALL_BF, name="order-f32", gemm_dtype="f32"), LONG_BF], ids=lambda c: c.name)
+def test_factors_set_behind_a_batched_step(cfg):
+    """The sort of the batched step stays; the weights are the new ones."""
+    scale = (0.5, 2.0, 1.0, 1.5)
+    early, late = start(cfg), start(cfg)
+    early.ctx.set_shard_scale(scale)
+    step(early)
+    late.ctx.worker_step_all(late.loss)
+    late.ctx.set_shard_scale(scale)
+    late.ctx.aggregate()
+    late.ctx.apply_update()
+    assert_same(weights(late), weights(early), cfg.name)
