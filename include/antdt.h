@@ -277,9 +277,8 @@ int antdt_set_lr(antdt_ctx* ctx, float lr);
  * on that worker's gradient.  The factors are not renormalised.  scale: host array of K values,
  * finite and >= 0; NULL resets all factors to 1 (the state after antdt_create).  They stay in
  * force until changed, also across antdt_set_batch and antdt_assign_shard (a worker index
- * beyond the K given here has factor 1).  May be called at any point before antdt_aggregate; when
- * it comes after antdt_worker_step_all, that aggregate rebuilds the lookup weights on its stream
- * instead of using the ones prepared beside the worker step.  Host only.
+ * beyond the K given here has factor 1).  May be called at any point before antdt_aggregate, which
+ * forms the weights anew (what the worker step has sorted stays).  Host only.
  */
 int antdt_set_shard_scale(antdt_ctx* ctx, const double* scale, int32_t K);
 

@@ -688,7 +688,8 @@ __device__ __forceinline__ int64_t run_index(const SegArgs& a, int f, int pos) {
 // their own and the update lost the general square root and division; the pooled-gradient rows of a sample that looks a
 // row up several times are read once there).  Row and accumulators are requested ahead of the item's pooled gradients, not
 // an item ahead: that took 8 registers more, and eight wavefronts per SIMD hide as much.  Us per launch, before / now:
-// 42 M lookups of 128-byte bf16 rows 1228 / 1016, 3.8 M 141 / 119, 4.3 M of 128-byte fp32 rows 161 / 148, 1.1 M 46.6 / 41.7.
+// 42 M lookups of 128-byte bf16 rows 1228 / 1016 (963 with the weights in registers, see SampleWeights; of that 880 in the
+// windows of short runs), 3.8 M 141 / 119, 4.3 M of 128-byte fp32 rows 161 / 148 (138), 1.1 M 46.6 / 41.7 (40).
 // Streaming loads and stores of the rows: 42 M 1003, but 1.1 M of a batch that returns 53 (they leave the memory-side cache).
 constexpr int LONG_RUN = 16;
 
