@@ -606,10 +606,12 @@ hipError_t launch_f32_tile(const GemmArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// 32 x 32 per wavefront (half the operand bytes of 16 x 16) where that leaves every SIMD of the 256 compute units
-// two wavefronts, else 16 x 16.  Every tile shape adds up the products in the same order.
+// 32 x 32 per wavefront (half the operand bytes of 16 x 16) where that still leaves enough wavefronts; with 16 x 16 the operands'
+// requests are the bound (six steps in flight instead of four: 12.3 -> 13.3 us).  A step, us, 16 x 16 / 32 x 32: input gradients
+// in 512 / 528 / 564 / 756 / 1536 tiles of 32 193 / 195, 99.8 / 96.2, 107 / 103, 107 / 103, 147 / 136; forward products in 752 / 768 / 1024
+// (256 columns) / 1024 (1001) tiles 122.7 / 124.2, 234.8 / 233.3, 136.0 / 134.3, 226 / 212.  Every tile shape adds up the products in the same order.
 hipError_t launch_f32(const GemmArgs& a, hipStream_t s) {
-  if ((int64_t)((a.M + 31) / 32) * ((a.N + 31) / 32) >= 2048) return launch_f32_tile<2, 2, 2>(a, s);
+  if ((int64_t)((a.M + 31) / 32) * ((a.N + 31) / 32) > (a.b_kc ? 512 : 767)) return launch_f32_tile<2, 2, 2>(a, s);
   return launch_f32_tile<1, 1, 4>(a, s);
 }
 
