@@ -39,7 +39,7 @@ MEASURED_TRAFFIC = {
     "cfg4": {"sparse_adagrad": (4823.7e6, "coalesce.hip"), "wgrad_adagrad": (2045.2e6, "gemm.hip"),
              "pool": (1214.9e6, "embed.hip")},
     "cfg5": {"adam": (15032.4e6, "optim.hip")},
-    "sha1": {"gemm.hip": "e14a1aa07c124097840cde4fb95c698fa69ef85d",
+    "sha1": {"gemm.hip": "f0fd9d7ae7a7ccd697149cb7ac2511a5fe5b5ca2",
              "embed.hip": "cb4a24cd47d081bb82b88f0f7f5976f1498133f5",
              "coalesce.hip": "72db62eb582d258a31d4d291c505aee10f2edf80",
              "optim.hip": "10a9d8df954dfd1c5c03af1b0ba1d46512dc8303",
