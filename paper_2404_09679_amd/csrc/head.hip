@@ -9,13 +9,15 @@
 namespace antdt {
 namespace {
 
-// Sum over the wavefront, in every lane: halves, then quarters, ... (no trip through LDS, which a shuffle is).
+// Another lane's value (no trip through LDS, which a shuffle is).
+template <int CTRL> __device__ __forceinline__ float moved(float x, std::integral_constant<int, CTRL>) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xF, 0xF, true));
+}
+
+// Sum over the wavefront, in every lane: halves, then quarters, ...
 __device__ __forceinline__ float wave_sum(float v) {
   typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
   auto both = [](u32x2 p) { return __uint_as_float(p.x) + __uint_as_float(p.y); };
-  auto moved = [](float x, auto ctrl) {
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), decltype(ctrl)::value, 0xF, 0xF, true));
-  };
   v = both(__builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false));
   v = both(__builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false));
   v += moved(v, std::integral_constant<int, 0x128>());   // eight lanes round a row of sixteen
@@ -42,17 +44,24 @@ template <> __device__ __forceinline__ void load4(const bf16_t* x, float (&v)[4]
 __device__ __forceinline__ void store4(float* x, const float (&v)[4]) { *reinterpret_cast<float4*>(x) = make_float4(v[0], v[1], v[2], v[3]); }
 __device__ __forceinline__ void store4(bf16_t* x, const float (&v)[4]) { *reinterpret_cast<uint2*>(x) = make_uint2(f2bf2(v[0], v[1]), f2bf2(v[2], v[3])); }
 
-// A block works on HEAD_TILE consecutive samples of one shard, four per wavefront; a lane holds the columns
-// 4 lane .. 4 lane + 3 of every 256 of all four, 512 columns at a time (its loads are then in flight together, and widths
-// up to 512 are read once).  Besides the loss, dz and dh it leaves the sums over its samples that the last
-// layer's weight gradient, bias gradient and the shard's loss are made of, so that nothing has to read the
-// activation again.
+// A block works on HEAD_TILE consecutive samples of one shard, four per wavefront, 512 columns at a time.  Besides the loss, dz
+// and dh it leaves the sums over its samples that the last layer's weight gradient, bias gradient and the shard's
+// loss are made of, so that nothing has to read the activation again.
 // Bound by the chain of round trips (activation -> logit -> gradient) and by its own instructions, each of which a launch
 // fetches anew and runs about once: a column at a time they were 9 KB.
 // VEC: widths and pitches are multiples of four (all bf16 models with a hidden layer), so columns are moved four at a time.
+//
+// The logit's products are added in one order whatever the path: 64 chains, chain c of the columns c, c + 64, c + 128, ..., and
+// then the chains in halves (c and c ^ 32, c ^ 16, ... c ^ 1).  Any other order moves logits by their last bit, and bf16 models
+// amplify that: single entries of dh then round to another bf16 neighbour (up to 3e-4 of a step).
+//   Without VEC a lane is a chain, of each of the four samples.
+//   VEC: sixteen lanes have a sample, four chains each (columns 4 (lane & 15) .. + 3 of every 64).  The sums over the samples and
+//   dh need a column of all four samples in one lane, the columns 4 lane .. 4 lane + 3 of every 256; these are loaded too (up to
+//   512 columns ahead of the logit: the same lines, in flight together).
 template <typename TH, typename TD, bool VEC>
 __global__ __launch_bounds__(256) void head_tile_kernel(HeadArgs a, ShardTab tab, HeadTiles ht) {
   constexpr int SPW = HEAD_TILE / 4;   // samples per wavefront
+  static_assert(SPW == 4, "sixteen lanes per sample");
   constexpr int PARTS = 2, CHUNK = 256 * PARTS;
   __shared__ float col[4][CHUNK];
   __shared__ float sums[4][2];
@@ -67,22 +76,28 @@ __global__ __launch_bounds__(256) void head_tile_kernel(HeadArgs a, ShardTab tab
   const int count = min(tab.len[k] - t0, HEAD_TILE);         // samples of the tile (at least one)
   const int rows = min(max(count - wave * SPW, 0), SPW);     // samples of this wavefront
   const int64_t s0 = (int64_t)tab.start[k] + t0;
+  const int own = lane >> 4;                                 // the lane's sample (of the wavefront's)
   // (fp32: dh may lie in h's place, so a wavefront reads its own samples only, or the weights if it has none)
+  auto sample_row = [&](int r) { return s0 + min(wave * SPW + min(r, max(rows - 1, 0)), count - 1); };
+  auto activation = [&](int64_t at) {
+    return sizeof(TH) == 4 && rows == 0 ? reinterpret_cast<const TH*>(a.w) : reinterpret_cast<const TH*>(a.h) + at * a.ldh;
+  };
   int64_t row[SPW];
   const TH* h[SPW];
 #pragma unroll
   for (int r = 0; r < SPW; ++r) {
-    row[r] = s0 + min(wave * SPW + min(r, max(rows - 1, 0)), count - 1);
-    h[r] = sizeof(TH) == 4 && rows == 0 ? reinterpret_cast<const TH*>(a.w) : reinterpret_cast<const TH*>(a.h) + row[r] * a.ldh;
+    row[r] = sample_row(r);
+    h[r] = activation(row[r]);
   }
-  const float label = a.labels[s0 + min(wave * SPW + min(lane, SPW - 1), count - 1)];   // lanes 0 .. SPW-1: one sample each
+  const float label = a.labels[s0 + min(wave * SPW + own, count - 1)];
   const float bias = a.b[0];
 
+  // Columns of all four samples: column(i, e) of the 512 from j0 on.
   float hv[PARTS][SPW][4], w[PARTS][4];
+  auto column = [&](int i, int e) { return i * 256 + (VEC ? lane * 4 + e : e * 64 + lane); };
   auto load = [&](int j0) {
 #pragma unroll
     for (int i = 0; i < PARTS; ++i) {
-      const int j = j0 + i * 256 + lane * 4;
       if (j0 + i * 256 >= a.width) {   // (the same for all lanes)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -91,14 +106,14 @@ __global__ __launch_bounds__(256) void head_tile_kernel(HeadArgs a, ShardTab tab
           for (int r = 0; r < SPW; ++r) hv[i][r][e] = 0.0f;
         }
       } else if (VEC) {
-        const int jc = min(j, a.width - 4);
+        const int jc = min(j0 + column(i, 0), a.width - 4);
         load4(a.w + jc, w[i]);
 #pragma unroll
         for (int r = 0; r < SPW; ++r) load4(h[r] + jc, hv[i][r]);
       } else {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const int jc = min(j + e, a.width - 1);
+          const int jc = min(j0 + column(i, e), a.width - 1);
           w[i][e] = a.w[jc];
 #pragma unroll
           for (int r = 0; r < SPW; ++r) hv[i][r][e] = to_f32(h[r][jc]);
@@ -106,44 +121,77 @@ __global__ __launch_bounds__(256) void head_tile_kernel(HeadArgs a, ShardTab tab
       }
 #pragma unroll
       for (int e = 0; e < 4; ++e)
-        if (j + (VEC ? 0 : e) >= a.width) {   // (VEC: the four are inside or outside together)
+        if (j0 + column(i, VEC ? 0 : e) >= a.width) {   // (VEC: the four are inside or outside together)
           w[i][e] = 0.0f;
 #pragma unroll
           for (int r = 0; r < SPW; ++r) hv[i][r][e] = 0.0f;
         }
     }
   };
-  float part[SPW] = {};
-  for (int j0 = 0; j0 < a.width; j0 += CHUNK) {
-    load(j0);
+  const bool loaded = a.width <= CHUNK;
+  float z;   // logit of the lane's sample, without the bias
+  if (VEC) {
+    const TH* h_own = activation(sample_row(own));
+    float chain[4] = {};
+    for (int j0 = 0; j0 < a.width; j0 += CHUNK) {
+      constexpr int STEPS = CHUNK / 64;
+      float x[STEPS][4], y[STEPS][4];
 #pragma unroll
-    for (int i = 0; i < PARTS; ++i)
+      for (int i = 0; i < STEPS; ++i)
+        if (j0 + i * 64 < a.width) {   // (the same for all lanes)
+          const int jc = min(j0 + i * 64 + (lane & 15) * 4, a.width - 4);
+          load4(h_own + jc, x[i]);
+          load4(a.w + jc, y[i]);
+        }
+      if (loaded) load(0);
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
+      for (int i = 0; i < STEPS; ++i)
+        if (j0 + i * 64 < a.width) {
+          const bool in = j0 + i * 64 + (lane & 15) * 4 < a.width;
 #pragma unroll
-        for (int r = 0; r < SPW; ++r) part[r] = fmaf(hv[i][r][e], w[i][e], part[r]);
+          for (int e = 0; e < 4; ++e) chain[e] = fmaf(in ? x[i][e] : 0.0f, in ? y[i][e] : 0.0f, chain[e]);
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {   // chains 4 q + e of the sixteen lanes q
+      chain[e] += moved(chain[e], std::integral_constant<int, 0x128>());   // eight lanes round the row of sixteen: chains c and c ^ 32
+      chain[e] += moved(chain[e], std::integral_constant<int, 0x124>());   // four (the halves of the row are the same by now): c ^ 16
+      chain[e] += moved(chain[e], std::integral_constant<int, 0x4E>());    // lane ^ 2: c ^ 8
+      chain[e] += moved(chain[e], std::integral_constant<int, 0xB1>());    // lane ^ 1: c ^ 4
+    }
+    z = (chain[0] + chain[2]) + (chain[1] + chain[3]);
+  } else {
+    float part[SPW] = {};
+    for (int j0 = 0; j0 < a.width; j0 += CHUNK) {
+      load(j0);
+#pragma unroll
+      for (int i = 0; i < PARTS; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int r = 0; r < SPW; ++r) part[r] = fmaf(hv[i][r][e], w[i][e], part[r]);
+    }
+    z = 0.0f;
+#pragma unroll
+    for (int r = 0; r < SPW; ++r) {
+      const float sum = wave_sum(part[r]);
+      if (own == r) z = sum;
+    }
   }
-  float mine = 0.0f;   // lane r < SPW: logit of sample r
-#pragma unroll
-  for (int r = 0; r < SPW; ++r) {
-    const float z = wave_sum(part[r]);
-    if (lane == r) mine = z;
-  }
-  const float z = mine + bias;
+  z += bias;
   const float e = expf(-fabsf(z));
   const float sig = (z >= 0.0f ? 1.0f : e) / (1.0f + e);
-  const bool on = lane < rows;
+  const bool on = own < rows;
   const float dz_lane = on ? (sig - label) * (1.0f / (float)tab.len[k]) : 0.0f;
   float dz[SPW];
 #pragma unroll
-  for (int r = 0; r < SPW; ++r) dz[r] = lane_value(dz_lane, r);
+  for (int r = 0; r < SPW; ++r) dz[r] = lane_value(dz_lane, r * 16);
   const bool per_sample = sizeof(TD) == 4 && a.dz;   // (bf16 gradients: there is a hidden layer)
   float* part_out = a.part + (int64_t)tile * a.ldpart;
   for (int j0 = 0; j0 < a.width; j0 += CHUNK) {   // (dh_cols <= width)
-    if (a.width > CHUNK) load(j0);
+    if (!loaded) load(j0);
 #pragma unroll
     for (int i = 0; i < PARTS; ++i) {
-      const int j = j0 + i * 256 + lane * 4;
       if (j0 + i * 256 >= a.width) continue;   // (the same for all lanes)
       float g[4] = {};
 #pragma unroll
@@ -155,16 +203,21 @@ __global__ __launch_bounds__(256) void head_tile_kernel(HeadArgs a, ShardTab tab
             g[e] = fmaf(hv[i][r][e], dz[r], g[e]);
             d[e] = (!a.relu || hv[i][r][e] > 0.0f) ? dz[r] * w[i][e] : 0.0f;
           }
-          TD* out = reinterpret_cast<TD*>(a.dh) + row[r] * a.lddh + j;
+          TD* out = reinterpret_cast<TD*>(a.dh) + row[r] * a.lddh + j0;
           if (VEC) {
-            if (j < a.dh_cols) store4(out, d);   // (dh_cols: a multiple of four)
+            if (j0 + column(i, 0) < a.dh_cols) store4(out + column(i, 0), d);   // (dh_cols: a multiple of four)
           } else {
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-              if (j + e < a.dh_cols) out[e] = from_f32<TD>(d[e]);
+              if (j0 + column(i, e) < a.dh_cols) out[column(i, e)] = from_f32<TD>(d[e]);
           }
         }
-      store4(&col[wave][i * 256 + lane * 4], g);
+      if (VEC) {
+        store4(&col[wave][column(i, 0)], g);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) col[wave][column(i, e)] = g[e];
+      }
     }
     const bool last = j0 + CHUNK >= a.width;
     if (last) {   // the losses, behind the stores of the gradient
@@ -173,15 +226,15 @@ __global__ __launch_bounds__(256) void head_tile_kernel(HeadArgs a, ShardTab tab
 #pragma unroll
       for (int r = 0; r < SPW; ++r) {
         sdz += dz[r];
-        sl += lane_value(loss_lane, r);
+        sl += lane_value(loss_lane, r * 16);
       }
       if (lane == 0) {
         sums[wave][0] = sdz;
         sums[wave][1] = sl;
       }
-      if (per_sample && on) {   // (lane r < rows: the wavefront's sample r)
-        a.dz[s0 + wave * SPW + lane] = dz_lane;
-        a.loss_s[s0 + wave * SPW + lane] = loss_lane;
+      if (per_sample && on && (lane & 15) == 0) {
+        a.dz[s0 + wave * SPW + own] = dz_lane;
+        a.loss_s[s0 + wave * SPW + own] = loss_lane;
       }
     }
     if (per_sample) continue;

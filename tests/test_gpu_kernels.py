@@ -456,3 +456,55 @@ def test_sort_beside_the_weight_gradients(most, hidden, shards, monkeypatch):
     _plant(monkeypatch, ids, B, lambda f, n: np.concatenate([[0], np.sort(rng.integers(0, n + 1, B - 1)), [n]]))
     # (accumulators from zero: see test_sort_over_many_blocks)
     check_iteration(cfg, cfg.shard_sizes, tol=TOL32, batched=True)
+
+
+# The loss kernel adds a logit's products in one order, whatever the type, the width and the way the columns are loaded: 64 chains
+# of every 64th column, then the chains in halves.  (Another order moves logits by their last bit, and with them the entries of
+# bf16 gradients that lie between two neighbours.)  A shard's loss shows the logit of one of its samples bit for bit: at a label of 0 and
+# z >= 32 the loss is z (what is added to it is below 2e-14), at z = -1000 it is 0, and lengths are powers of two.
+@pytest.mark.parametrize("gemm,width,hidden", [("f32", 13, False), ("f32", 256, False), ("f32", 704, False), ("f32", 131, True), ("f32", 128, True),
+                                               ("bf16", 264, False), ("bf16", 66, False), ("bf16", 8, True), ("bf16", 72, True),
+                                               ("bf16", 256, True), ("bf16", 512, True), ("bf16", 1096, True)])
+def test_order_of_a_logit(gemm, width, hidden):
+    import torch
+    from gpu_helpers import GpuRun
+    from test_gpu_parity import make_inputs
+    sizes = (16,) * 16 + (1, 2, 8)
+    shown = [i for i in range(16)] + [0, 1, 5]   # whose logit is the shard's loss
+    num_dense = width if hidden else width - 4   # (a pooled field of four columns ahead, all bags empty)
+    cfg = _config(f"logit-{gemm}-{width}", 770, num_fields=1, rows_per_field=8, dim=4, num_dense=num_dense, layer_sizes=(width,) if hidden else (),
+                  gemm_dtype=gemm, shard_sizes=sizes, min_bag=0, max_bag=1)
+    B, K = sum(sizes), len(sizes)
+    rng = np.random.default_rng(width)
+    kill, first = num_dense // 2, np.cumsum((0,) + sizes)
+    dense = np.zeros((B, num_dense), dtype=np.float32)
+    dense[:, kill] = 1.0
+    for k in range(K):   # (bf16 values: a hidden layer that passes them on does so exactly)
+        dense[first[k] + shown[k]] = rng.integers(64, 128, num_dense) / 64.0
+        dense[first[k] + shown[k], kill] = 0.0
+    w = rng.uniform(1.0, 16.0, width).astype(np.float32)
+    w[(0 if hidden else 4) + kill] = -1000.0
+    bias = np.float32(0.37)
+    parts = [np.concatenate([np.zeros((4, width)), np.eye(width)]).reshape(-1), np.zeros(width)] if hidden else []
+    flat = np.concatenate(parts + [w, [bias]]).astype(np.float32)
+    tables, state, _, _, batch = make_inputs(cfg)
+    batch = dataclasses.replace(batch, ids=np.zeros(0, np.int32), offsets=np.zeros((1, B + 1), np.int32), field_ptr=np.zeros(2, np.int64),
+                                dense=dense, labels=np.zeros(B, np.float32))
+    run = GpuRun(cfg, tables, flat, state, max_batch=B, max_nnz=1)
+    run.set_batch(batch)
+    run.ctx.assign_shard(B, K, sizes=sizes)
+    loss = torch.zeros(K, device="cuda:0")
+    run.ctx.worker_step_all(loss)
+    torch.cuda.synchronize()
+    h = dense[[first[k] + shown[k] for k in range(K)]]
+    if not hidden:
+        h = np.concatenate([np.zeros((K, 4), np.float32), h], axis=1)
+    chains = np.zeros((K, 64), np.float32)
+    for j0 in range(0, width, 64):   # (products of 8 and 24 bits, added to 24: exact in 64-bit floats, rounded once)
+        n = min(64, width - j0)
+        chains[:, :n] = (h[:, j0:j0 + n].astype(np.float64) * w[j0:j0 + n] + chains[:, :n]).astype(np.float32)
+    for o in (32, 16, 8, 4, 2, 1):
+        chains = chains[:, :o] + chains[:, o:2 * o]
+    z = chains[:, 0] + bias
+    assert np.all(z >= 32)
+    assert np.array_equal(loss.cpu().numpy() * np.array(sizes, np.float32), z)
