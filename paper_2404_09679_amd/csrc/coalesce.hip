@@ -8,6 +8,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "pack.h"
 #include "sort.h"
 
 namespace antdt {
@@ -346,10 +347,9 @@ __global__ __launch_bounds__(256) void mask_count_kernel(const int32_t* offsets,
 
 // Blocks (k, f, *) copy the ids and sample indices of shard k's lookups in field f, PACK_LOOKUPS each in turn: bound by the chain
 // of loads (one block for all of them: 5 shards x 26 fields of 5300 lookups 16 us).
-constexpr int PACK_BLOCKS = 8, PACK_ITEMS = 4, PACK_LOOKUPS = 256 * PACK_ITEMS;
-__global__ __launch_bounds__(256) void mask_pack_kernel(const int32_t* ids, const int32_t* lookup_sample,
-                                                        const int32_t* offsets, int64_t B, FieldPtr fp, ShardTab tab,
-                                                        const int64_t* cbase, int32_t* ids_out, int32_t* pay_out) {
+__global__ __launch_bounds__(PACK_THREADS) void mask_pack_kernel(const int32_t* ids, const int32_t* lookup_sample,
+                                                                 const int32_t* offsets, int64_t B, FieldPtr fp, ShardTab tab,
+                                                                 const int64_t* cbase, int32_t* ids_out, int32_t* pay_out) {
   const int k = blockIdx.x, f = blockIdx.y;
   if (tab.w[k] == 0.0f) return;
   const int32_t* off = offsets + (int64_t)f * (B + 1);
@@ -357,22 +357,22 @@ __global__ __launch_bounds__(256) void mask_pack_kernel(const int32_t* ids, cons
   for (int q = 0; q < k; ++q)
     if (tab.w[q] != 0.0f) dst += off[tab.start[q] + tab.len[q]] - off[tab.start[q]];
   const int64_t src = fp.p[f] + off[tab.start[k]];
-  const int n = off[tab.start[k] + tab.len[k]] - off[tab.start[k]];
-  for (int i0 = blockIdx.z * PACK_LOOKUPS + threadIdx.x; i0 < n; i0 += PACK_BLOCKS * PACK_LOOKUPS) {
+  const int64_t n = off[tab.start[k] + tab.len[k]] - off[tab.start[k]];
+  pack_rounds(blockIdx.z, threadIdx.x, n, [&](int64_t i0) {
     int32_t id[PACK_ITEMS], smp[PACK_ITEMS];
 #pragma unroll
     for (int q = 0; q < PACK_ITEMS; ++q) {
-      const int i = min(i0 + q * 256, n - 1);
+      const int64_t i = min(i0 + q * PACK_THREADS, n - 1);
       id[q] = ids[src + i];
       smp[q] = lookup_sample[src + i];
     }
 #pragma unroll
     for (int q = 0; q < PACK_ITEMS; ++q)
-      if (i0 + q * 256 < n) {
-        ids_out[dst + i0 + q * 256] = id[q];
-        pay_out[dst + i0 + q * 256] = smp[q];
+      if (i0 + q * PACK_THREADS < n) {
+        ids_out[dst + i0 + q * PACK_THREADS] = id[q];
+        pay_out[dst + i0 + q * PACK_THREADS] = smp[q];
       }
-  }
+  });
 }
 
 // ------------------------------------------------------------- segments
@@ -1104,7 +1104,7 @@ hipError_t launch_mask_pack(const int32_t* ids, const int32_t* lookup_sample, co
                             const FieldPtr& fp, const ShardTab& tab, int64_t* cbase, int32_t* ids_out,
                             int32_t* pay_out, hipStream_t s) {
   hipLaunchKernelGGL(mask_count_kernel, dim3(1), dim3(256), 0, s, offsets, B, F, tab, cbase);
-  hipLaunchKernelGGL(mask_pack_kernel, dim3(tab.K, F, PACK_BLOCKS), dim3(256), 0, s, ids, lookup_sample, offsets, B, fp, tab, cbase,
+  hipLaunchKernelGGL(mask_pack_kernel, dim3(tab.K, F, PACK_BLOCKS), dim3(PACK_THREADS), 0, s, ids, lookup_sample, offsets, B, fp, tab, cbase,
                      ids_out, pay_out);
   return hipGetLastError();
 }

@@ -4,6 +4,7 @@ Section VI-A (Eq. 3) require.  No kernel is launched here."""
 import ctypes as C
 import os
 import re
+import subprocess
 from fractions import Fraction
 
 import numpy as np
@@ -349,3 +350,44 @@ def test_training_model_rejects_bad_arguments():
             kw["t0"], kw["v"] = [], []
         with pytest.raises(A.AntdtError):
             A.simulate_bsp(**kw)
+
+
+PACK_WALK = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "pack.h"
+using namespace antdt;
+int main(int argc, char** argv) {
+  const long long n = atoll(argv[1]);
+  long long dealt = 0;
+  for (int block = 0; block < PACK_BLOCKS; ++block)
+    for (int thread = 0; thread < PACK_THREADS; ++thread) {
+      long long before = (long long)block * PACK_LOOKUPS + thread - PACK_BLOCKS * PACK_LOOKUPS;
+      pack_rounds(block, thread, n, [&](auto i) {
+        if ((long long)i != before + PACK_BLOCKS * PACK_LOOKUPS || i < 0 || i >= n) {
+          std::printf("round at %lld behind one at %lld of %lld\n", (long long)i, before, n);
+          std::exit(1);
+        }
+        before = i;
+        for (int q = 0; q < PACK_ITEMS; ++q) dealt += (long long)i + q * PACK_THREADS < n;
+      });
+    }
+  if (dealt != n) std::printf("%lld of %lld dealt\n", dealt, n);
+  return dealt != n;
+}
+"""
+
+
+def test_packing_deals_every_lookup_once(tmp_path):
+    """The lookups of a shard that stays are packed in rounds of 8192: every index is inside the shard's, also of a field with as many
+    lookups as antdt_create accepts, where the index behind the last round no longer fits 32 bits."""
+    source, program = tmp_path / "walk.cpp", tmp_path / "walk"
+    source.write_text(PACK_WALK)
+    subprocess.run(["g++", "-std=c++17", "-O2", "-fwrapv", "-I", os.path.join(ROOT, "paper_2404_09679_amd", "csrc"), str(source), "-o", str(program)], check=True)
+    most = 2 ** 31 - 4097
+    m = good_model()
+    m.max_nnz = most
+    A.Context(m)
+    for n in (0, 1, 255, 1024, 1025, 8191, 8192, 8193, 100_000, 2 ** 31 - 8191, most):
+        r = subprocess.run([str(program), str(n)], capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0, r.stdout
