@@ -584,10 +584,11 @@ hipError_t launch_bf16_sized(const GemmArgs& a, hipStream_t s) {
   // 15625 x 512 x 1024: 38 / 24 / 31 / 61;  4096 x 1024 x 848: 32 / 16 / 18 / 35;  4096 x 512 x 1024: 31 / 15 / 10 / 20;
   // 1531 x 1024 x 848: - / 16 / 10 / 16;  96 x 1024 x 848: - / 15 / 7.7 / 6.4.   The largest tile that gives most of
   // the 256 compute units a block wins (it reads the fewest operand bytes), and below that more blocks do.
-  // 256 x 256 only from 200 blocks on: at 150 it gains nothing alone (30 / 32 us above), and with weight gradients on a second
-  // stream its 128 KB of LDS wait for compute units that those have left (2501 samples of a 3840-1024-512 model: 111 us
-  // instead of 61, the step 397 -> 380).
-  if (blocks(256, 256) >= 200) return launch_bf16<4, 2, 2, 4, 64, 2, BS>(a, s);
+  // 256 x 256 from 200 blocks on instead of 150 was measured over 75 models and calls of 150 .. 199 such blocks (a step, or a
+  // worker's: 3000 samples of 3840-1024-512 222 -> 240 us, 166 -> 173; 9800 of 845-1024-512-256 287 -> 295, 210 -> 218): 1 .. 8 %
+  // slower but for five, of 3.8 M lookups in tables of half a million rows and more, where the tiles wait for compute
+  // units that the weight gradients hold (2501 samples of 3840-1024-512 392 -> 380).
+  if (blocks(256, 256) >= 150) return launch_bf16<4, 2, 2, 4, 64, 2, BS>(a, s);
   if (blocks(128, 128) >= 200) return launch_bf16<2, 1, 2, 4, 64, 2, BS>(a, s);
   if (blocks(64, 64) >= 100) return launch_bf16<1, 1, 2, 2, 64, 3, BS>(a, s);
   return launch_bf16<1, 1, 1, 1, 128, 3, BS>(a, s);
