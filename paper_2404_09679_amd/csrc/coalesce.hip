@@ -1075,8 +1075,6 @@ hipError_t launch_sort(const SortPlan& pl, const SortBuffers& sb, const FieldPtr
   return hipSuccess;
 }
 
-bool sort_fits_blocks(int F, const FieldPtr& fp) { return small_sort_items(F, fp) > 0; }
-
 hipError_t launch_expand_samples(const int32_t* offsets, int32_t* lookup_sample, const FieldPtr& fp, int F, int B, hipStream_t s) {
   if (B <= 0) return hipSuccess;
   hipLaunchKernelGGL(expand_samples_kernel, dim3((B + 31) / 32, F), dim3(256), 0, s, offsets, lookup_sample, fp, B);

@@ -216,7 +216,7 @@ hipError_t launch_wgrad(const WgradArgs& a, const KSegments& seg, bool store, hi
 // Per-shard gradients of an fp32 model and, in the same launch, the sort (launch_sort with every field in one block, result in
 // key / pay [0]).
 hipError_t launch_wgrad_and_sort(const WgradArgs& a, const KSegments& seg, const SortPlan& pl, const SortBuffers& sb, const FieldPtr& fp, hipStream_t s);
-bool sort_fits_blocks(int F, const FieldPtr& fp);   // every field in one block
+bool wgrad_takes_sort(const WgradArgs& a, int ranges, int64_t samples, int F, const FieldPtr& fp);   // it pays
 
 struct CastArgs {  // fp32 [rows, cols] -> bf16 [rows_pad, cols], extra rows zero
   const float* src;

@@ -749,6 +749,13 @@ static void fill_wgrad_args(antdt_ctx* c, WgradArgs& u) {
   u.grads = c->shard_grads; u.stride = c->Pstride;
 }
 
+// Whether the sort of a batched step runs in the launch of the weight gradients (where it goes to no stream of its own).
+static bool sort_joins(antdt_ctx* c) {
+  WgradArgs u;
+  fill_wgrad_args(c, u);
+  return wgrad_takes_sort(u, c->tab.K, c->B, c->m.num_fields, c->fp);
+}
+
 // Per-shard gradients of all dense layers for shards [k0, k1), one launch on `ws`; with `sort` the launch of an fp32 model
 // also sorts the batch's lookups.
 static int shard_weight_gradients(antdt_ctx* c, int k0, int k1, hipStream_t ws, bool sort = false) {
@@ -1024,7 +1031,7 @@ static int worker_range(antdt_ctx* c, int k0, int k1, float* loss_out, hipStream
   bwd_scope.close();
   if (!deferred) {
     // All shards of an fp32 model whose sort goes to no other stream: it runs beside the weight gradients
-    const bool sort = c->batched && !beside && !c->act_bf16 && c->total_tiles > 0 && sort_fits_blocks(m.num_fields, c->fp);
+    const bool sort = c->batched && !beside && c->total_tiles > 0 && sort_joins(c);
     if (sort) {
       for (int k = 0; k < tab.K; ++k) c->included[k] = true;
       set_weights(c);

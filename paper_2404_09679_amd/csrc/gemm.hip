@@ -651,10 +651,15 @@ hipError_t launch_wgrad_f32_tile(const WgradArgs& a, const KSegments& seg, const
   return hipGetLastError();
 }
 
+int64_t wgrad_f32_tiles(const WgradArgs& a, int size) {   // of `size` rows and columns, of the hidden layers
+  int64_t n = 0;
+  for (int l = 0; l < a.n_layers; ++l) n += (int64_t)((a.M[l] + size - 1) / size) * ((a.N[l] + size - 1) / size);
+  return n;
+}
+bool wgrad_f32_wide(const WgradArgs& a, int ranges) { return wgrad_f32_tiles(a, 32) * ranges >= 512; }
+
 hipError_t launch_wgrad_f32(const WgradArgs& a, const KSegments& seg, const SortPlan* pl, const SortBuffers* sb, const FieldPtr* fp, hipStream_t s) {
-  int64_t blocks = 0;
-  for (int l = 0; l < a.n_layers; ++l) blocks += (int64_t)((a.M[l] + 31) / 32) * ((a.N[l] + 31) / 32);
-  if (blocks * seg.n >= 512) return launch_wgrad_f32_tile<2, 2, 2>(a, seg, pl, sb, fp, s);
+  if (wgrad_f32_wide(a, seg.n)) return launch_wgrad_f32_tile<2, 2, 2>(a, seg, pl, sb, fp, s);
   return launch_wgrad_f32_tile<1, 1, 4>(a, seg, pl, sb, fp, s);
 }
 
@@ -707,6 +712,18 @@ hipError_t launch_wgrad(const WgradArgs& a, const KSegments& seg, bool store, hi
   if (!a.bf16) return store ? launch_wgrad_f32(a, seg, nullptr, nullptr, nullptr, s) : hipErrorInvalidValue;
   if (store) return launch_wgrad_sized<WGRAD_STORE>(a, seg, seg.n, s);
   return seg.n == 1 ? launch_wgrad_sized<WGRAD_ONE>(a, seg, 1, s) : launch_wgrad_sized<WGRAD_MANY>(a, seg, 1, s);
+}
+
+// Beside the sort the tiles lie four to a block that has the sort's LDS too, so fewer of them share a compute unit: that costs them
+// about 6 us per 1000 blocks, and 15 - 20 us per million tiles (of 32) x samples where there are few.  What it saves is the
+// sort's time, 4.5 / 8 / 16 / 25 us with 2 / 4 / 8 / 16 lookups a thread.  A step, us, one after the other / together (fp32, one stream;
+// 512 samples in 1 / 4 / 12 shards, 26 fields of 1000 lookups): 256-128 81 / 77, 81 / 79, 89 / 90; 512-256 101 / 104, 100 / 101, 118 / 123;
+// 1024-512-256 172 / 180, 176 / 181, 226 / 250; of 15 000 lookups: 121 / 111, 121 / 112, 130 / 113; 141 / 125, 142 / 126, 161 / 146; 215 / 198,
+// 219 / 203, 269 / 271.  100 fields of 1300, 1024-512-256 in four shards 317 / 340; eight of 10 000, 2048-1024 in eight 356 / 373.
+bool wgrad_takes_sort(const WgradArgs& a, int ranges, int64_t samples, int F, const FieldPtr& fp) {
+  const int64_t saved = std::min(small_sort_items(F, fp), 12);   // (0: a field does not fit a block)
+  return !a.bf16 && wgrad_f32_tiles(a, 32) * samples <= 100000 * saved &&
+         wgrad_f32_tiles(a, wgrad_f32_wide(a, ranges) ? 32 : 16) * ranges <= 1280 * saved && saved > 0;
 }
 
 hipError_t launch_wgrad_and_sort(const WgradArgs& a, const KSegments& seg, const SortPlan& pl, const SortBuffers& sb, const FieldPtr& fp, hipStream_t s) {

@@ -458,6 +458,34 @@ def test_sort_beside_the_weight_gradients(most, hidden, shards, monkeypatch):
     check_iteration(cfg, cfg.shard_sizes, tol=TOL32, batched=True)
 
 
+# Many gradient tiles and short fields keep the sort to a launch of its own, ahead of the reduction; few tiles or longer fields do not.
+# Class counts say which way a step went.
+@pytest.mark.parametrize("hidden,shards,most,launches", [((1024, 512), (8,) * 12, 300, 1), ((1024, 512), (24,) * 4, 300, 0), ((1024, 512), (8,) * 12, 16_384, 0),
+                                                         ((64, 32), (24,) * 4, 300, 0), ((64, 32), (24,) * 4, 16_385, 6)])
+def test_where_an_fp32_step_sorts(hidden, shards, most, launches, monkeypatch):
+    import torch
+    import paper_2404_09679_amd as A
+    from gpu_helpers import GpuRun
+    from test_gpu_parity import make_inputs
+    B = sum(shards)
+    cfg = _config(f"where-{most}", 780, layer_sizes=hidden, gemm_dtype="f32", shard_sizes=shards, max_bag=most // 90 + 2, rows_per_field=200_000)
+    rng = np.random.default_rng(most)
+    _plant(monkeypatch, [rng.integers(0, 200_000, n) for n in (most, 5, most // 2)], B,
+           lambda f, n: np.concatenate([[0], np.sort(rng.integers(0, n + 1, B - 1)), [n]]))
+    tables, state, flat, fstate, batch = make_inputs(cfg)
+    run = GpuRun(cfg, tables, flat, state, fstate, streams=False)
+    run.ctx.profile(1)
+    run.set_batch(batch)
+    run.ctx.assign_shard(B, len(shards), sizes=shards)
+    run.ctx.worker_step_all(torch.zeros(len(shards), device="cuda:0"))
+    run.ctx.aggregate()
+    run.ctx.apply_update()
+    torch.cuda.synchronize()
+    n = {name: run.ctx.profile_read(i)[0] for i, name in enumerate(A.kernel_names())}
+    assert n["gemm_wgrad"] == 1 and n["sort_hist"] + n["sort_scan"] + n["sort_scatter"] == launches
+    check_iteration(cfg, cfg.shard_sizes, tol=TOL32, batched=True)
+
+
 # The loss kernel adds a logit's products in one order, whatever the type, the width and the way the columns are loaded: 64 chains
 # of every 64th column, then the chains in halves.  (Another order moves logits by their last bit, and with them the entries of
 # bf16 gradients that lie between two neighbours.)  A shard's loss shows the logit of one of its samples bit for bit: at a label of 0 and
