@@ -168,6 +168,9 @@ struct antdt_ctx {
   hipEvent_t ev_dh[ANTDT_MAX_LAYERS + 1] = {};  // [0]: the operands of the weight gradients are complete; [L]: all before the dense update
   hipEvent_t ev_wgrad = nullptr;                // all weight gradients of the last worker step are written
   bool wgrad_pending = false;
+  // The last batched step that sorted in its weight-gradient launch did not do so for nothing: an aggregation of all shards
+  // followed.  Where none did (shards left out, only the gradients wanted) the next step leaves the sort to the aggregation.
+  bool joined_sort_used = true;
   bool presorted = false;     // the coalescing structure of the current batch and split is built (or being built)
   bool side_pending = false;  // work is in flight on the side stream that no other stream has waited for yet
   // bound by antdt_bind_static: the workspace is the library's static device buffer and every
@@ -1031,8 +1034,9 @@ static int worker_range(antdt_ctx* c, int k0, int k1, float* loss_out, hipStream
   bwd_scope.close();
   if (!deferred) {
     // All shards of an fp32 model whose sort goes to no other stream: it runs beside the weight gradients
-    const bool sort = c->batched && !beside && c->total_tiles > 0 && sort_joins(c);
+    const bool sort = c->batched && !beside && c->total_tiles > 0 && c->joined_sort_used && sort_joins(c);
     if (sort) {
+      c->joined_sort_used = false;
       for (int k = 0; k < tab.K; ++k) c->included[k] = true;
       set_weights(c);
       coalesce_whole_batch(c);
@@ -1113,6 +1117,7 @@ int antdt_aggregate(antdt_ctx* c, const uint8_t* shard_mask, void* stream) {
     if (rc) return rc;
   }
   c->left_out = !all;
+  if (all) c->joined_sort_used = true;
   c->presorted = false;
   c->g_valid = false;
   c->gdense_valid = false;  // the dense sum is formed inside the optimizer kernel (or on request)

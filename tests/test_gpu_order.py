@@ -207,3 +207,33 @@ def test_factors_set_behind_a_batched_step(cfg):
     late.ctx.aggregate()
     late.ctx.apply_update()
     assert_same(weights(late), weights(early), cfg.name)
+
+
+def sorts(run):
+    """Launches of the sort (of fields that fit a block) since the last call, apart from those in a weight-gradient launch."""
+    import paper_2404_09679_amd as A
+    torch.cuda.synchronize()
+    return run.ctx.profile_read(A.kernel_names().index("sort_scatter"))[0]
+
+
+def test_steps_whose_sort_nobody_uses():
+    """fp32 models sort in the weight-gradient launch of a batched step, but not behind a step whose sort was not used (shards left out,
+    gradients only); an aggregation of all shards brings it back.  Results are those of steps that never left it out."""
+    cfg = wl.scaled(SMALL_BF, name="order-f32", gemm_dtype="f32")
+    run, ref = start(cfg, streams=False), start(cfg, streams=False)
+    run.ctx.profile(1)
+    mask = [0, 1, 1, 1]
+    for i, (use, launches) in enumerate([(None, 0), (mask, 1), (mask, 1), (None, 1), (None, 0), ("step", 0), ("step", 0), (None, 1), (None, 0)]):
+        run.ctx.worker_step_all(run.loss)
+        if use == "step":
+            assert sorts(run) == 0
+            continue
+        for k in range(4):
+            if not use or use[k]:
+                ref.ctx.worker_step(k, ref.loss[k:k + 1])
+        for r in (run, ref):
+            r.ctx.aggregate(use)
+            r.ctx.apply_update()
+        assert sorts(run) == launches, i
+        if not use:   # (of a shard that was left out the steps by worker form no loss)
+            assert_same(weights(run), weights(ref), f"iteration {i}")
