@@ -181,25 +181,53 @@ struct antdt_ctx {
 };
 
 // The library's own streams, or none when the context works on the caller's stream only.  Going to another stream
-// and back costs the host about 25 us (the waits on events), so it has to hide that much GPU work.
+// and back costs the host about 25 us (the waits on events), so it has to hide that much GPU work, and the step has to be one whose
+// kernels take longer than the host's calls.
 //   Sort: from 100 000 lookups (26 fields, 1024-512-256, dense update on the launch stream, sort on the side or not, us per step:
 //   22 000 / 36 000 / 52 000 / 82 000 / 115 000 / 164 000 / 273 000 lookups 80 / 73, 83 / 79, 85 / 82, 89 / 85, 90 / 91, 93 / 99, 101 / 115;
-//   3200-1024-512 with D = 64 at 70 000, dense update on the side: 100 / 90).
-//   Dense update beside the sparse one: where there are many lookups or many weights (the same model, beside or after:
+//   3200-1024-512 with D = 64 at 70 000, dense update on the side: 100 / 90), and below where a long field makes it long (more than 4096
+//   lookups: 14 us and more in one block) and the MLP hides it: bf16 models from 2e8 samples x parameters (four fields; 1000 samples,
+//   1024-512-256, 42 000 lookups 88 / 102; 4096, 256-128, 49 000 89 / 98; 12 000, 512-256, 48 000 150 / 164; less: 2000, 256-128, 84 000 99 / 90),
+//   fp32 models from 8192 samples (256-128, 48 000 lookups 173 / 190) or, where the sort has no place in the weight-gradient launch, from 1e8
+//   (2000, 512-256, 84 000 115 / 130, 256-128 101 / 102; with a place: 4096, 256-128, 49 000 109 / 102).
+//   Dense update beside the sparse one: where there are many lookups or many weights (26 fields, 1024-512-256, beside or after:
 //   164 000 / 273 000 / 355 000 / 546 000 / 682 000 / 874 000 lookups 111 / 93, 112 / 101, 115 / 109, 134 / 126, 140 / 144, 158 / 168;
-//   3840-1024-512 at 50 000: 102 / 122).  After one worker step per shard not: six workers, 1024-512-256, with
+//   3840-1024-512 at 50 000: 102 / 122).  With 100 000 lookups and more also where the kernels take long and those beside each other get on:
+//   the weight gradients formed in pieces (see cut_ranges; 8192 samples, 1024-512-256, 213 000 lookups 187 / 199; 12 000, 512-256 with D = 64,
+//   312 000 254 / 280), or by few blocks over at least 8192 samples (four fields, 12 000, 512-256, 504 000 163 / 180; 26 of D = 16, 256-128,
+//   8192 105 / 114, 512-256, 9000 134 / 149), or by those of a large model over no more than 5000 (26 fields, 4096, 1024-512-256, 106 000
+//   140 / 146; 39 of D = 16, 5000 158 / 164).  Otherwise the blocks hold the compute units that the input gradient waits for (26 fields,
+//   512-256, 9000, 351 000 199 / 160; D = 64, 8192, 213 000 229 / 190).
+//   After one worker step per shard not: six workers, 1024-512-256, with
 //   300 000 / 500 000 / 700 000 / 1.6 M / 4.1 M lookups 367 / 322, 398 / 345, 424 / 376, 539 / 500, 838 / 816 us; eight, 3840-1024-512
 //   with 0.9 / 3.8 / 12 M 550 / 505, 846 / 845, 1504 / 1497 us.  Unless shards were left out: the host has then waited for the
 //   stream and is no longer ahead of it (one of six workers left out, 700 000 / 1.6 M / 4.1 M lookups 374 / 380, 473 / 482,
 //   804 / 829 us, fewer lookups alike; one of eight with 0.9 / 3.8 M 486 / 508, 778 / 822).  fp32 models never (176 / 171 us
 //   at 430 000 lookups).
-static inline hipStream_t side_stream(const antdt_ctx* c) {
-  return (c->static_bound || c->no_streams || c->fp.p[c->m.num_fields] < 100000) ? nullptr : c->side;
+static bool sort_joins(antdt_ctx* c);
+static bool wgrad_in_pieces(const antdt_ctx* c);
+static hipStream_t side_stream(antdt_ctx* c) {
+  if (c->static_bound || c->no_streams) return nullptr;
+  const int64_t lookups = c->fp.p[c->m.num_fields];
+  bool enough = lookups >= 100000;
+  if (!enough && lookups >= 16384) {
+    int64_t most = 0;
+    for (int f = 0; f < c->m.num_fields; ++f) most = std::max(most, c->fp.p[f + 1] - c->fp.p[f]);
+    const double work = (double)c->B * (double)c->P;
+    enough = most > 4096 && (c->act_bf16 ? work >= 2e8 : c->B >= 8192 || (work >= 1e8 && !sort_joins(c)));
+  }
+  return enough ? c->side : nullptr;
 }
-static inline hipStream_t wgrad_stream(const antdt_ctx* c) {
-  const bool enough = c->act_bf16 && (c->batched || c->left_out) &&
-                      (c->fp.p[c->m.num_fields] >= 600000 || c->P >= 2000000);
-  return (c->static_bound || c->no_streams || !enough) ? nullptr : c->wside;
+static hipStream_t wgrad_stream(const antdt_ctx* c) {
+  if (c->static_bound || c->no_streams || !c->act_bf16 || !(c->batched || c->left_out)) return nullptr;
+  const int64_t lookups = c->fp.p[c->m.num_fields];
+  bool enough = lookups >= 600000 || c->P >= 2000000;
+  if (!enough && c->batched && lookups >= 100000 && c->B >= 3000) {
+    int64_t blocks = 0;
+    for (int l = 0; l + 1 < c->L; ++l) blocks += (int64_t)((c->width[l] + 63) / 64) * ((c->width[l + 1] + 63) / 64);
+    enough = (c->B <= 5000 && c->P >= 1250000) || (c->B >= 8192 && blocks <= 100) || wgrad_in_pieces(c);
+  }
+  return enough ? c->wside : nullptr;
 }
 
 // A captured call is replayed behind the library's back, with the addresses it was captured with: from the first one on
@@ -872,6 +900,21 @@ static int cut_ranges(const antdt_ctx* c, const KSegments& seg, KSegments& piece
     pieces.ts[i] = all.ts[j]; pieces.te[i] = all.te[j];
   }
   return pieces.n;
+}
+
+// Whether the split's ranges would be cut (shards of equal length weigh the same unless they have factors).
+static bool wgrad_in_pieces(const antdt_ctx* c) {
+  KSegments seg, pieces;
+  memset(&seg, 0, sizeof(seg));
+  for (int k = 0; k < c->tab.K; ++k) {
+    const int ks = c->tab.start[k], ke = ks + c->tab.len[k];
+    if (seg.n > 0 && c->tab.len[k] == c->tab.len[k - 1]) {
+      seg.ke[seg.n - 1] = ke;
+    } else {
+      seg.ks[seg.n] = ks; seg.ke[seg.n++] = ke;
+    }
+  }
+  return cut_ranges(c, seg, pieces) > 0;
 }
 
 // Lookups from which the sort does not wait for the gather: the sample index of every lookup then comes from a launch of

@@ -715,15 +715,18 @@ hipError_t launch_wgrad(const WgradArgs& a, const KSegments& seg, bool store, hi
 }
 
 // Beside the sort the tiles lie four to a block that has the sort's LDS too, so fewer of them share a compute unit: that costs them
-// about 6 us per 1000 blocks, and 15 - 20 us per million tiles (of 32) x samples where there are few.  What it saves is the
+// about 6 us per 1000 blocks, and 15 - 20 us per million tiles (of 32) x samples where there are few (less where they fill several rounds
+// of blocks: 4096 samples in eight shards, 12 fields of 12 000, 512-256 217 / 204).  What it saves is the
 // sort's time, 4.5 / 8 / 16 / 25 us with 2 / 4 / 8 / 16 lookups a thread.  A step, us, one after the other / together (fp32, one stream;
 // 512 samples in 1 / 4 / 12 shards, 26 fields of 1000 lookups): 256-128 81 / 77, 81 / 79, 89 / 90; 512-256 101 / 104, 100 / 101, 118 / 123;
 // 1024-512-256 172 / 180, 176 / 181, 226 / 250; of 15 000 lookups: 121 / 111, 121 / 112, 130 / 113; 141 / 125, 142 / 126, 161 / 146; 215 / 198,
 // 219 / 203, 269 / 271.  100 fields of 1300, 1024-512-256 in four shards 317 / 340; eight of 10 000, 2048-1024 in eight 356 / 373.
 bool wgrad_takes_sort(const WgradArgs& a, int ranges, int64_t samples, int F, const FieldPtr& fp) {
   const int64_t saved = std::min(small_sort_items(F, fp), 12);   // (0: a field does not fit a block)
-  return !a.bf16 && wgrad_f32_tiles(a, 32) * samples <= 100000 * saved &&
-         wgrad_f32_tiles(a, wgrad_f32_wide(a, ranges) ? 32 : 16) * ranges <= 1280 * saved && saved > 0;
+  if (a.bf16 || saved == 0) return false;
+  const int64_t tiles = wgrad_f32_tiles(a, wgrad_f32_wide(a, ranges) ? 32 : 16) * ranges;
+  const int64_t work = wgrad_f32_tiles(a, 32) * samples;
+  return tiles <= 1280 * saved && work <= 100000 * saved * (tiles >= 2048 ? 4 : 3) / 3;
 }
 
 hipError_t launch_wgrad_and_sort(const WgradArgs& a, const KSegments& seg, const SortPlan& pl, const SortBuffers& sb, const FieldPtr& fp, hipStream_t s) {

@@ -160,8 +160,13 @@ def test_weight_gradient_option_changed_between_worker_steps(first, then):
         assert torch.equal(a, b), f"shard {k}"
 
 
+# (the last three: 100 000 lookups and more, and few blocks over many samples, a large model on few samples, and pieces)
 @pytest.mark.parametrize("cfg", [WIDE_BF, wl.scaled(WIDE_BF, name="order-equal", shard_sizes=(250,) * 4),
-                                 wl.scaled(PIECES, name="order-pieces-wide", layer_sizes=(53, 1288, 1544, 1))], ids=lambda c: c.name)
+                                 wl.scaled(PIECES, name="order-pieces-wide", layer_sizes=(53, 1288, 1544, 1)),
+                                 wl.scaled(SMALL_BF, name="order-many-samples", shard_sizes=(3000, 37, 0, 5163), max_bag=5),
+                                 wl.scaled(SMALL_BF, name="order-large-model", layer_sizes=(173, 1032, 1048, 1), shard_sizes=(700, 37, 0, 2263), max_bag=14),
+                                 wl.scaled(SMALL_BF, name="order-pieces-long", layer_sizes=(173, 1288, 1032, 1), shard_sizes=(1750,) * 4, max_bag=6)],
+                         ids=lambda c: c.name)
 @pytest.mark.parametrize("batched", [True, False], ids=["batched", "by-worker"])
 def test_dense_update_beside_the_launch_stream(cfg, batched):
     """Models whose dense update runs beside the input gradient and the sparse update (batched steps; after steps by worker
@@ -214,6 +219,33 @@ def sorts(run):
     import paper_2404_09679_amd as A
     torch.cuda.synchronize()
     return run.ctx.profile_read(A.kernel_names().index("sort_scatter"))[0]
+
+
+FEW = wl.scaled(SMALL_BF, name="order-few", num_fields=4, layer_sizes=(141, 1024, 256, 1), shard_sizes=(300, 37, 0, 663))
+
+
+@pytest.mark.parametrize("cfg,ahead", [(FEW, True), (wl.scaled(FEW, layer_sizes=(141, 256, 64, 1)), False),                     # (a short MLP)
+                                       (wl.scaled(FEW, max_bag=6), False),                                                      # (short fields)
+                                       (wl.scaled(FEW, layer_sizes=(141, 64, 1), shard_sizes=(1500, 1100), max_bag=20), True),  # (100 000 lookups)
+                                       (wl.scaled(FEW, gemm_dtype="f32"), False),                                               # (in the weight-gradient launch)
+                                       (wl.scaled(FEW, gemm_dtype="f32", layer_sizes=(141, 64, 1), shard_sizes=(8192,), max_bag=3), True),
+                                       (wl.scaled(FEW, gemm_dtype="f32", shard_sizes=(850,), max_bag=45), True)],               # (fields too long for that launch)
+                         ids=["work", "short-mlp", "short-fields", "many-lookups", "f32-joined", "f32-samples", "f32-long-fields"])
+def test_steps_that_sort_ahead(cfg, ahead):
+    """Where the sort of a batched step goes to a stream of its own it is enqueued by the step and not by the aggregation; the results are those
+    of one stream either way."""
+    lookups = np.diff(wl.make_batch(cfg).field_ptr)
+    assert lookups.sum() < 100_000 or cfg.layer_sizes == (141, 64, 1)
+    run, ref = start(cfg), start(cfg, streams=False)
+    run.ctx.profile(1)
+    for _ in range(2):
+        run.ctx.worker_step_all(run.loss)
+        assert (sorts(run) > 0) == ahead
+        run.ctx.aggregate()
+        run.ctx.apply_update()
+        sorts(run)
+        step(ref)
+    assert_same(weights(run), weights(ref), cfg.name)
 
 
 def test_steps_whose_sort_nobody_uses():
