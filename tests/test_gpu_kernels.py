@@ -100,12 +100,19 @@ def test_sort_variants(most, rows, monkeypatch):
 
 
 # The sort over many blocks (one field of more than 16384 lookups, ten tiles and a bit) with the other fields at the tile
-# boundaries, before and after shards are left out; built beside the MLP, behind it, anew after a new split; mean-pooled
-@pytest.mark.parametrize("how", ["batched", "by-worker", "masked", "masked-batched", "mean", "mean-masked", "new-split", "late-factors"])
+# boundaries, before and after shards are left out, and anew after a new split; mean-pooled.  All of these sort in the
+# aggregation; the long ones (of 100 000 lookups) of a batched step beside the MLP.
+@pytest.mark.parametrize("how", ["batched", "by-worker", "masked", "masked-batched", "mean", "mean-masked", "new-split", "late-factors",
+                                 "batched-long", "masked-batched-long", "mean-long", "new-split-long", "late-factors-long"])
 def test_sort_over_many_blocks(how, monkeypatch):
     import torch
     sizes = [2048, 4096, 2049, 2047, 4095, 4097, 1, 0, 6144, 20_483, 2048]
     left = [2048, 2048, 1, 2047, 2048, 4097, 1, 0, 4096, 18_432, 0]      # ... of these in the first shard and the last
+    long = how.endswith("-long")
+    how = how[:-5] if long else how
+    if long:
+        sizes, left = sizes + [30_000, 30_721], left + [20_000, 28_673]
+    assert (sum(sizes) >= 100_000) == long
     B, shards = 900, (300, 200, 400)
     cfg = _config(f"blocks-{how}", 620, num_fields=len(sizes), rows_per_field=5000, dim=8, layer_sizes=(8,), gemm_dtype="f32",
                   shard_sizes=shards, max_bag=24, pooling="mean" if how.startswith("mean") else "sum")

@@ -18,6 +18,8 @@ TOLBF = 2e-2
 MID = wl.RankingConfig("mid-f32", 5, 100_000, 32, "f32", "elementwise", 13, (173, 256, 128, 64, 1), "f32",
                        20, 1.1, (300, 37, 0, 663), wl.SEED0 + 201)
 MID_BF = wl.scaled(MID, name="mid-bf16gemm", gemm_dtype="bf16")
+MID_LONG = wl.scaled(MID, name="mid-long-f32", shard_sizes=(600, 74, 0, 1326))
+MID_LONG_BF = wl.scaled(MID_LONG, name="mid-long-bf16gemm", gemm_dtype="bf16")
 ROW_BF = wl.RankingConfig("rowwise-bf16-tables", 4, 50_000, 64, "bf16", "rowwise", 0, (256, 128, 64, 1), "bf16",
                           50, 1.2, (128, 200, 184), wl.SEED0 + 202)
 # row sizes at the other end of the supported range: 256-byte rows (16 lanes per row in the tile
@@ -203,8 +205,8 @@ def test_masked_aggregation_leaves_shards_out():
 
 def test_per_worker_factors_on_the_aggregation_weights():
     """Table II, ADJUST_LR (Section III: a learning rate per worker that penalises the lagging
-    ones): w_k = c_k B_k / B, set before the worker steps, after a batched step (the prepared
-    lookup weights are rebuilt), together with a mask, and reset."""
+    ones): w_k = c_k B_k / B, set before the worker steps, after a batched step (what it sorted
+    stays, the weights are formed anew), together with a mask, and reset."""
     cfg = wl.CONFIGS[1]
     check_iteration(cfg, cfg.shard_sizes, scale=(1.0, 0.25, 2.0, 0.5))
     check_iteration(cfg, cfg.shard_sizes, scale=(1.0, 0.25, 2.0, 0.5), batched=True)
@@ -272,6 +274,11 @@ def test_new_split_after_a_batched_step():
     check_iteration(MID, (500, 0, 250, 250), prelude=batched_step_with_another_split)
     check_iteration(MID, (100, 900), batched=True, mask=(0, 1), prelude=batched_step_with_another_split)
     check_iteration(MID_BF, (640, 360), tol=TOLBF, bf16_gemm_oracle=True, prelude=batched_step_with_another_split)
+    # (enough lookups for the library's side stream; the others sort in the weight-gradient launch or in the aggregation)
+    assert len(wl.make_batch(MID_LONG).ids) >= 100_000
+    check_iteration(MID_LONG, (1000, 0, 400, 600), prelude=batched_step_with_another_split)
+    check_iteration(MID_LONG, (300, 1700), batched=True, mask=(0, 1), prelude=batched_step_with_another_split)
+    check_iteration(MID_LONG_BF, (1640, 360), tol=TOLBF, bf16_gemm_oracle=True, prelude=batched_step_with_another_split)
 
 
 def _time_worker_steps(ctx, K, reps=5):
