@@ -1000,34 +1000,38 @@ __global__ __launch_bounds__(256) void seg_finish_kernel(SegArgs a, FieldPtr fp,
 }
 
 template <typename TT, bool ROWWISE, bool UPDATE, bool MEAN, int W, int THREADS = 256>
-void launch_reduce_window(const SegArgs& a, const FieldPtr& fp, const TileBase& tb, const WeightTab& wt, Profiler* prof, hipStream_t s) {
+hipError_t launch_reduce_window(const SegArgs& a, const FieldPtr& fp, const TileBase& tb, const WeightTab& wt, Profiler* prof, hipStream_t s) {
   const unsigned parts = SORT_TILE / W;
   const int bytes = 2 * W / LONG_RUN * a.D * 4;
   {
     static std::atomic<uint64_t> allowed{0};
     constexpr int ONE_FIELD = W > 512 ? 48 * 1024 : 0;   // (static LDS of the wide windows)
-    if (allow_lds(seg_window_kernel<TT, ROWWISE, UPDATE, MEAN, W, THREADS>, ONE_FIELD ? 2 * W / LONG_RUN * 64 * 4 : bytes, ONE_FIELD, allowed) != hipSuccess) return;
+    const hipError_t ok = allow_lds(seg_window_kernel<TT, ROWWISE, UPDATE, MEAN, W, THREADS>, ONE_FIELD ? 2 * W / LONG_RUN * 64 * 4 : bytes,
+                                    ONE_FIELD, allowed);
+    if (ok != hipSuccess) return ok;
     ProfScope ps(prof, UPDATE ? KID_SPARSE_ADAGRAD : KID_SEG_REDUCE, s);
-    hipLaunchKernelGGL((seg_window_kernel<TT, ROWWISE, UPDATE, MEAN, W, THREADS>), dim3(tile_grid(a.total_tiles) * parts), dim3(THREADS), bytes, s, a, fp, tb, wt);
+    hipLaunchKernelGGL((seg_window_kernel<TT, ROWWISE, UPDATE, MEAN, W, THREADS>), dim3(tile_grid(a.total_tiles) * parts), dim3(THREADS),
+                       bytes, s, a, fp, tb, wt);
   }
   if (W < 1024) {   // (no run leaves a window that holds its field)
     ProfScope ps(prof, KID_SEG_REDUCE_LONG, s);
     hipLaunchKernelGGL((seg_finish_kernel<TT, ROWWISE, UPDATE>), dim3((a.total_tiles * parts + 3) / 4), dim3(256), 0, s, a, fp, tb, W);
   }
+  return hipGetLastError();
 }
 
 template <typename TT, bool ROWWISE, bool UPDATE, bool MEAN>
-void launch_reduce_pooling(const SegArgs& a, const FieldPtr& fp, const TileBase& tb, const WeightTab& wt, Profiler* prof, hipStream_t s) {
-  if (a.window == 2048) launch_reduce_window<TT, ROWWISE, UPDATE, MEAN, 2048, 1024>(a, fp, tb, wt, prof, s);
-  else if (a.window == 1024) launch_reduce_window<TT, ROWWISE, UPDATE, MEAN, 1024, 1024>(a, fp, tb, wt, prof, s);
-  else if (a.window == 512) launch_reduce_window<TT, ROWWISE, UPDATE, MEAN, 512>(a, fp, tb, wt, prof, s);
-  else launch_reduce_window<TT, ROWWISE, UPDATE, MEAN, 256>(a, fp, tb, wt, prof, s);
+hipError_t launch_reduce_pooling(const SegArgs& a, const FieldPtr& fp, const TileBase& tb, const WeightTab& wt, Profiler* prof, hipStream_t s) {
+  if (a.window == 2048) return launch_reduce_window<TT, ROWWISE, UPDATE, MEAN, 2048, 1024>(a, fp, tb, wt, prof, s);
+  if (a.window == 1024) return launch_reduce_window<TT, ROWWISE, UPDATE, MEAN, 1024, 1024>(a, fp, tb, wt, prof, s);
+  if (a.window == 512) return launch_reduce_window<TT, ROWWISE, UPDATE, MEAN, 512>(a, fp, tb, wt, prof, s);
+  return launch_reduce_window<TT, ROWWISE, UPDATE, MEAN, 256>(a, fp, tb, wt, prof, s);
 }
 
 template <typename TT, bool ROWWISE, bool UPDATE>
-void launch_reduce_variant(const SegArgs& a, const FieldPtr& fp, const TileBase& tb, const WeightTab& wt, Profiler* prof, hipStream_t s) {
-  if (a.mean_pool) launch_reduce_pooling<TT, ROWWISE, UPDATE, true>(a, fp, tb, wt, prof, s);
-  else launch_reduce_pooling<TT, ROWWISE, UPDATE, false>(a, fp, tb, wt, prof, s);
+hipError_t launch_reduce_variant(const SegArgs& a, const FieldPtr& fp, const TileBase& tb, const WeightTab& wt, Profiler* prof, hipStream_t s) {
+  if (a.mean_pool) return launch_reduce_pooling<TT, ROWWISE, UPDATE, true>(a, fp, tb, wt, prof, s);
+  return launch_reduce_pooling<TT, ROWWISE, UPDATE, false>(a, fp, tb, wt, prof, s);
 }
 
 }  // namespace
@@ -1119,18 +1123,13 @@ hipError_t launch_seg_reduce(const SegArgs& args, const FieldPtr& fp, const Tile
   }
   a.weights = std::max(a.weights, 1);
   a.weight = wt.w[0];
-  if (a.update) {
-    if (a.table_bf16) {
-      if (a.rowwise) launch_reduce_variant<bf16_t, true, true>(a, fp, tb, wt, prof, s);
-      else launch_reduce_variant<bf16_t, false, true>(a, fp, tb, wt, prof, s);
-    } else {
-      if (a.rowwise) launch_reduce_variant<float, true, true>(a, fp, tb, wt, prof, s);
-      else launch_reduce_variant<float, false, true>(a, fp, tb, wt, prof, s);
-    }
-  } else {
-    launch_reduce_variant<float, false, false>(a, fp, tb, wt, prof, s);
+  if (!a.update) return launch_reduce_variant<float, false, false>(a, fp, tb, wt, prof, s);
+  if (a.table_bf16) {
+    if (a.rowwise) return launch_reduce_variant<bf16_t, true, true>(a, fp, tb, wt, prof, s);
+    return launch_reduce_variant<bf16_t, false, true>(a, fp, tb, wt, prof, s);
   }
-  return hipGetLastError();
+  if (a.rowwise) return launch_reduce_variant<float, true, true>(a, fp, tb, wt, prof, s);
+  return launch_reduce_variant<float, false, true>(a, fp, tb, wt, prof, s);
 }
 
 }  // namespace antdt
