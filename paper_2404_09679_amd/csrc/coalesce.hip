@@ -571,8 +571,11 @@ __device__ __forceinline__ float group_sum(float x, int lps) {
 }
 
 // Square root and quotient for operands far from the ends of the exponent range (the general ones spend two thirds of
-// their instructions on those): the hardware's approximation, improved by its own remainder.  The same bits as the general
-// ones (compared for all mantissas under the root and 134 M quotients).
+// their instructions on those): the hardware's estimates, a Newton step, and for the quotient Markstein's correction by the
+// remainder ("Computation of elementary functions on the IBM RISC System/6000 processor", 1990), which rounds right if the
+// reciprocal does and neither quotient nor remainder leaves the range.  Rounded right on this hardware are the roots of all floats from
+// 2^-90 to 2^90 and the reciprocals of all from 2^-46 to 2^47 (each compared), so with roots and numerators bounded as in
+// TableRow::update, quotients within 2^-125 .. 2^124, these are the bits of the general ones (1.7e10 pairs compared: the same).
 __device__ __forceinline__ float sqrt_mid(float x) {
   const float y = __builtin_amdgcn_rsqf(x), r = x * y;
   return fmaf(fmaf(-r, r, x), 0.5f * y, r);
@@ -581,7 +584,7 @@ __device__ __forceinline__ float rcp_mid(float d) {
   const float r = __builtin_amdgcn_rcpf(d);
   return fmaf(fmaf(-d, r, 1.0f), r, r);
 }
-__device__ __forceinline__ float div_mid(float n, float d, float rcp) {   // (n: any value)
+__device__ __forceinline__ float div_mid(float n, float d, float rcp) {   // (fixed up: NaN stays NaN, infinity infinite, 0 / d is 0)
   const float q = n * rcp;
   return __builtin_amdgcn_div_fixupf(fmaf(fmaf(-q, d, n), rcp, q), d, n);
 }
@@ -589,6 +592,10 @@ __device__ __forceinline__ uint32_t beyond_mid(float x) {   // below MID_SPAN: 2
   return __float_as_uint(x) - ((127u - 90u) << 23);
 }
 constexpr uint32_t MID_SPAN = 180u << 23;
+__device__ __forceinline__ uint32_t magnitude_or_zero(float x) {   // from MID_LEAST on: 2^-75 <= |x|, or 0
+  return (__float_as_uint(x) << 1) - 1;
+}
+constexpr uint32_t MID_LEAST = ((127u - 75u) << 24) - 1;
 
 // A lane's columns of one table row and of its accumulators, as they lie in memory, and the row-sparse Adagrad step:
 //   element-wise: S += g^2;                 p -= lr * g / (sqrt(S) + eps)
@@ -634,7 +641,12 @@ template <typename TT, bool ROWWISE> struct TableRow {
       p0[2] = __uint_as_float(p.y << 16); p0[3] = __uint_as_float(p.y & 0xFFFF0000u);
     }
     constexpr int NS = ROWWISE ? 1 : 4;
-    if (__ballot(beyond >= MID_SPAN) == 0 && a.eps < 0x1p90f) {   // accumulators of any run under way
+    float n[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) n[e] = a.lr * g.v[e];
+    const uint32_t least = min(min(magnitude_or_zero(n[0]), magnitude_or_zero(n[1])), min(magnitude_or_zero(n[2]), magnitude_or_zero(n[3])));
+    // Accumulators and gradients of any run under way.  (A root is below 2^45, a gradient of 256 columns below 2^49 then.)
+    if (__ballot(beyond >= MID_SPAN || least < MID_LEAST) == 0 && a.eps < 0x1p45f && a.lr < 0x1p30f) {
       float den[NS], rcp[NS];
 #pragma unroll
       for (int e = 0; e < NS; ++e) {
@@ -642,13 +654,13 @@ template <typename TT, bool ROWWISE> struct TableRow {
         rcp[e] = rcp_mid(den[e]);
       }
 #pragma unroll
-      for (int e = 0; e < 4; ++e) p1[e] = p0[e] - div_mid(a.lr * g.v[e], den[e % NS], rcp[e % NS]);
+      for (int e = 0; e < 4; ++e) p1[e] = p0[e] - div_mid(n[e], den[e % NS], rcp[e % NS]);
     } else {
       float den[NS];
 #pragma unroll
       for (int e = 0; e < NS; ++e) den[e] = sqrtf(sv[e]) + a.eps;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) p1[e] = p0[e] - a.lr * g.v[e] / den[e % NS];
+      for (int e = 0; e < 4; ++e) p1[e] = p0[e] - n[e] / den[e % NS];
     }
     TT* dst = reinterpret_cast<TT*>(a.tables) + row * a.D + c * 4;
     if (sizeof(TT) == 4) *reinterpret_cast<float4*>(dst) = make_float4(p1[0], p1[1], p1[2], p1[3]);

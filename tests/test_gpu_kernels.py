@@ -405,6 +405,42 @@ def test_row_update_over_the_range_of_accumulators(dim, state):
     assert np.all(np.abs(got_p[ok] - (p - step)[ok]) <= 1e-6 * np.abs(step[ok]) + 2.0 ** -23 * np.abs(p[ok]))
 
 
+# The same to the bit: gradients and accumulators over the whole range, each row one lookup's (a table of zeros shows the quotient itself).
+@pytest.mark.parametrize("dim,state,lr", [(128, "elementwise", 0.01), (4, "elementwise", 2.0 ** 31), (64, "rowwise", 1.0), (256, "rowwise", 2.0 ** -20)])
+def test_row_update_rounds_as_a_division_does(dim, state, lr):
+    from gpu_helpers import GpuRun
+    from test_gpu_parity import make_inputs
+    F, B = 4, 500
+    cfg = _config(f"rounds-{dim}", 690 + dim, num_fields=F, rows_per_field=B, dim=dim, layer_sizes=(), gemm_dtype="f32", shard_sizes=(200, 300),
+                  adagrad_state=state, max_bag=1, lr=lr)
+    rng = np.random.default_rng(dim)
+    _, acc, flat, fstate, batch = make_inputs(cfg)
+    span = 2.0 ** rng.uniform(-135, 40, flat.shape)   # (dX = dz w, dz about 1e-3)
+    flat = (span * rng.choice([-1.0, 1.0], flat.shape) * (rng.random(flat.shape) > 0.05)).astype(np.float32)
+    flat[1::5] *= np.float32(2.0 ** -115) / np.abs(flat[1::5]).clip(2.0 ** -135)   # (some of them tiny whatever the width)
+    flat[-1] = 0.0
+    acc = (2.0 ** rng.uniform(-85, 85, acc.shape)).astype(np.float32)
+    acc[::7] = (2.0 ** rng.uniform(-140, 120, acc[::7].shape)).astype(np.float32)
+    ids = np.concatenate([rng.permutation(B) for _ in range(F)]).astype(np.int32)
+    batch = dataclasses.replace(batch, ids=ids, offsets=np.tile(np.arange(B + 1, dtype=np.int32), (F, 1)), field_ptr=np.arange(F + 1, dtype=np.int64) * B,
+                                dense=np.zeros_like(batch.dense))
+    run = GpuRun(cfg, np.zeros((F * B, dim), np.float32), flat, acc, fstate, max_batch=B, max_nnz=F * B)
+    run.set_batch(batch)
+    run.iteration(cfg.shard_sizes, batched=True)
+    got, S = run.tables.cpu().numpy(), run.state.cpu().numpy()
+    tiny = 0
+    with np.errstate(all="ignore"):
+        for f in range(F):
+            u, _, _, G = run.coalesced[f]
+            rows = f * B + u
+            tiny += np.sum((np.abs(G) > 0) & (np.abs(G) < 2.0 ** -110))
+            den = np.sqrt(S[rows] if state == "elementwise" else S[rows][:, None]) + np.float32(cfg.eps)
+            want = np.float32(0) - np.float32(lr) * G / den
+            assert den.dtype == want.dtype == np.float32
+            assert np.array_equal(got[rows], want)
+    assert tiny > 100
+
+
 # The gather hands the 64 samples of a block out by the number of iterations their bags take (fifteen and more are one class):
 # equal bags, bags of every length up to 300, empty ones, blocks that end inside.  Rows of 4, 8 and 16 pieces of 16 bytes.
 @pytest.mark.parametrize("dim,table,pooling", [(16, "f32", "sum"), (32, "f32", "mean"), (128, "bf16", "sum"), (32, "bf16", "mean")])
