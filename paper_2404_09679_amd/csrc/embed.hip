@@ -60,7 +60,7 @@ constexpr int MOST_ITERATIONS = 15;   // (bags that take as many or more count a
 // exchanges and issues the LPR row loads (16 bytes per lane, one whole row per group)
 // back to back before adding them, which keeps 64 rows in flight per wavefront; the next ids are
 // requested before the rows are waited for.  Every lookup's sample index is recorded for the sort.
-// Blocks of 64 samples hand them out in order of the iterations they take, so that the bags a wavefront works on at once are
+// ORDERED: a block hands its 64 samples out in order of the iterations they take, so that the bags a wavefront works on at once are
 // about as long as each other: with 1 .. 50 lookups, the longest of eight in any order makes every second load of a wavefront
 // one of few lanes (41.8 M lookups: 10.7 M load and 209 M vector instructions, in order 7.1 M and 152 M).
 // Bound, where bags are long, by the rows' way from the L2s, 55 lines outstanding on a compute unit (41.8 M lookups of 128-byte
@@ -68,7 +68,7 @@ constexpr int MOST_ITERATIONS = 15;   // (bags that take as many or more count a
 // down to the additions and won nothing), else by round trips.  Like the sort's tiles, the blocks of a field go to one XCD: its
 // rows are fetched into one L2 (fields interleaved two to sixteen at a time: 492 .. 530 us).
 // WIDE: a table of 2^32 or more 16-byte pieces.
-template <typename TT, typename OT, int LPR, int SPB, bool WIDE>
+template <typename TT, typename OT, int LPR, int SPB, bool ORDERED, bool WIDE>
 __global__ __launch_bounds__(256) void pool_tile_kernel(PoolArgs a, FieldPtr fp) {
   constexpr int EV = Vec16<TT>::N;
   constexpr int G = 256 / LPR;       // bags per round
@@ -92,7 +92,8 @@ __global__ __launch_bounds__(256) void pool_tile_kernel(PoolArgs a, FieldPtr fp)
   // longest first, every wavefront with long and short ones.
   int sample[ROUNDS], begin[ROUNDS], end[ROUNDS];
   const int32_t* off = a.offsets + (int64_t)f * (a.B + 1) + a.s0 + sl0;
-  if (SPB == 64) {
+  static_assert(!ORDERED || SPB == 64, "a lane per sample");
+  if (ORDERED) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     int b0 = 0, e0 = 0;
     if (sl0 + lane < sl1) {
@@ -212,20 +213,26 @@ __global__ __launch_bounds__(256) void pool_dense_kernel(PoolArgs a) {
   dense_columns<OT>(a, blockIdx.x * 64, a.ns);
 }
 
-template <typename TT, typename OT, int LPR, int SPB>
+template <typename TT, typename OT, int LPR, int SPB, bool ORDERED>
 static void launch_pool_tiles(const PoolArgs& a, const FieldPtr& fp, hipStream_t s) {
   const dim3 grid(8 * (((a.ns + SPB - 1) / SPB * (a.F + 1) + 7) / 8)), block(256);
-  if ((uint64_t)a.R * LPR >> 32) hipLaunchKernelGGL((pool_tile_kernel<TT, OT, LPR, SPB, true>), grid, block, 0, s, a, fp);
-  else hipLaunchKernelGGL((pool_tile_kernel<TT, OT, LPR, SPB, false>), grid, block, 0, s, a, fp);
+  if ((uint64_t)a.R * LPR >> 32) hipLaunchKernelGGL((pool_tile_kernel<TT, OT, LPR, SPB, ORDERED, true>), grid, block, 0, s, a, fp);
+  else hipLaunchKernelGGL((pool_tile_kernel<TT, OT, LPR, SPB, ORDERED, false>), grid, block, 0, s, a, fp);
 }
 
 // 64 samples per block, or as many as the block takes at once (at most 32) where that leaves most of the places on the
-// compute units empty and the round trips of one bag after the other are the kernel's time: 26 fields x 64 samples
-// 9.4 us -> 6.0, x 1531 samples (624 blocks of 64) 12.5 -> 11.4, x 4096 samples 17.2 -> 18.2.
+// compute units empty and the round trips of one bag after the other are the kernel's time (a worker's step of 26 fields and small layers, us,
+// 32 / 64 samples: 260 blocks of 64 47.4 / 48.6, 494 53.1 / 54.6, 832 57.3 / 58.1, 1040 67.0 / 67.1, 1664 82.9 / 83.1).
+// The samples of a block in order (see pool_tile_kernel) from eight lookups a bag on, and where eight or more lanes take a row: shorter bags
+// are of one length in iterations and pay for the order (the same, as they come / in order: 12 000 samples of 26 fields, bags of up to
+// 8 / 20 / 50, rows of 8 lanes 59.8 / 60.3, 84.0 / 82.6, 145.5 / 143.9, of 16 lanes 101.4 / 102.5, 139 / 133, 230 / 214; bags of one, 100 fields,
+// 4096 samples 174.8 / 177.4), and rows of 4 lanes, sixteen bags to a wavefront, lose by it at any length (100 fields, 12 000 samples, bags
+// of up to 20 210 / 223).
 template <typename TT, typename OT, int LPR>
 static void launch_pool_row(const PoolArgs& a, const FieldPtr& fp, hipStream_t s) {
-  if ((int64_t)((a.ns + 63) / 64) * a.F < 1024) launch_pool_tiles<TT, OT, LPR, (LPR > 8 ? 256 / LPR : 32)>(a, fp, s);
-  else launch_pool_tiles<TT, OT, LPR, 64>(a, fp, s);
+  if ((int64_t)((a.ns + 63) / 64) * a.F < 1024) launch_pool_tiles<TT, OT, LPR, (LPR > 8 ? 256 / LPR : 32), false>(a, fp, s);
+  else if (LPR >= 8 && fp.p[a.F] >= (int64_t)8 * a.F * a.B) launch_pool_tiles<TT, OT, LPR, 64, (LPR >= 8)>(a, fp, s);
+  else launch_pool_tiles<TT, OT, LPR, 64, false>(a, fp, s);
 }
 
 template <typename TT, typename OT>

@@ -442,20 +442,23 @@ def test_row_update_rounds_as_a_division_does(dim, state, lr):
 
 
 # The gather hands the 64 samples of a block out by the number of iterations their bags take (fifteen and more are one class):
-# equal bags, bags of every length up to 300, empty ones, blocks that end inside.  Rows of 4, 8 and 16 pieces of 16 bytes.
+# equal bags, bags of every length up to 300, empty ones, blocks that end inside.  Rows of 4, 8 and 16 pieces of 16 bytes.  (Rows of 4
+# pieces, and batches of short bags, as they come.)
+@pytest.mark.parametrize("bags", ["short", "long"])
 @pytest.mark.parametrize("dim,table,pooling", [(16, "f32", "sum"), (32, "f32", "mean"), (128, "bf16", "sum"), (32, "bf16", "mean")])
-def test_gather_of_bags_of_many_lengths(dim, table, pooling, monkeypatch):
+def test_gather_of_bags_of_many_lengths(dim, table, pooling, bags, monkeypatch):
     F, B = 40, 1700   # (enough blocks that they take 64 samples each)
     assert F * (-(-B // 64)) >= 1024 and B % 64
     cfg = _config(f"bags-{dim}", 690 + dim, num_fields=F, rows_per_field=300, dim=dim, table_dtype=table, adagrad_state="rowwise", layer_sizes=(8,),
                   gemm_dtype="f32", shard_sizes=(700, 1, 999), max_bag=300, pooling=pooling)
     rng = np.random.default_rng(dim)
-    lengths = [rng.integers(0, 3, B) for _ in range(F)]
+    lengths = [rng.integers(0, 3 if bags == "short" else 20, B) for _ in range(F)]
     lengths[0] = np.full(B, 7)
     lengths[1] = rng.integers(0, 130, B)
     lengths[2] = np.where(np.arange(B) % 64 == 17, 300, 0)
     lengths[3] = np.arange(B) % 66
     lengths[4] = (np.arange(B) == B - 1).astype(int)
+    assert (sum(n.sum() for n in lengths) >= 8 * F * B) == (bags == "long")
     ids = [rng.integers(0, 300, n.sum()) for n in lengths]
     _plant(monkeypatch, ids, B, lambda f, n: np.concatenate([[0], np.cumsum(lengths[f])]))
     # (accumulators from zero: with others, of about 1e-4, a step is about 1e-4 or less, and rounding the stored parameter of about
