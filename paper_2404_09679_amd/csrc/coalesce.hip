@@ -690,10 +690,10 @@ __device__ __forceinline__ int64_t run_index(const SegArgs& a, int f, int pos) {
 // D/4 lanes take one item of work each: a whole run of up to LONG_RUN lookups that starts in the window (it may
 // end behind it), summed in sorted (= sample) order, or, of longer runs, a piece of at most LONG_RUN lookups
 // that ends at a multiple of LONG_RUN in the window.  The pieces' sums meet in LDS in order; what of a run leaves the window
-// goes to memory (two slots per window: the run that comes in, the run that goes out) and is added up by
-// seg_finish_kernel (nothing leaves it where a window holds its field: 1024 threads, see fill_seg_args in ctx.hip).  No run table is needed (counting, scanning and writing one, with lists of the long
-// runs, were six launches and 10-250 us between sort and reduction), only keys, sample indices and the rows
-// themselves are read, and the chain of dependent accesses is down to LDS -> row and pooled gradients.
+// goes to memory (two slots per window: the run that comes in, the run that goes out) and is added up by seg_finish_kernel (nothing leaves it
+// where a window holds its field: 1024 threads, see fill_seg_args in ctx.hip).  No run table is needed (counting, scanning and
+// writing one, with lists of the long runs, were six launches and 10-250 us between sort and reduction), only keys, sample indices and
+// the rows themselves are read, and the chain of dependent accesses is down to LDS -> row and pooled gradients.
 // A window that lies inside one run (60 % of them with 42 M lookups of Zipf(1.2) ids) needs none of this: sum_window.
 // Bound by the requests for pooled-gradient rows that a compute unit can have outstanding (about 64 lines; they come from
 // L2 and the memory-side cache) and by vector instructions (58 % of the cycles, 66 before windows inside a run went a way of
@@ -777,7 +777,8 @@ __global__ __launch_bounds__(THREADS, ROWWISE ? 8 : 1) void seg_window_kernel(Se
   __shared__ int goes_out;
   __shared__ uint64_t heads[UPDATE ? 1 : W / 64];   // (sums written out: the place of a run is the window's first one's + heads before)
   __shared__ int64_t first_run;
-  extern __shared__ __attribute__((aligned(16))) float piece_sum[];   // [2 W / LONG_RUN][D]: 2 j: starts at LONG_RUN j inside its run, 2 j + 1: at the run's head
+  // [2 W / LONG_RUN][D], piece 2 j: starts at LONG_RUN j inside its run, 2 j + 1: at the run's head
+  extern __shared__ __attribute__((aligned(16))) float piece_sum[];
   int f, t, part;
   if (!tile_of_block(tb, a.F, PARTS, f, t, part)) return;
   const int64_t base = fp.p[f];

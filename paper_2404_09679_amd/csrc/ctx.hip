@@ -741,7 +741,6 @@ static void set_weights(antdt_ctx* c) {
   c->weights_dirty = false;
 }
 
-// Sort the lookups by row id: everything of the server side that depends only on the batch's ids.
 static void fill_sort(antdt_ctx* c, const int32_t* ids, const int32_t* pay0, SortPlan& pl, SortBuffers& sb) {
   const antdt_model& m = c->m;
   pl.F = m.num_fields; pl.passes = c->sort_passes; pl.radix_bits = c->radix_bits;
@@ -753,6 +752,7 @@ static void fill_sort(antdt_ctx* c, const int32_t* ids, const int32_t* pay0, Sor
   sb.pay0 = pay0;
 }
 
+// Sort the lookups by row id: everything of the server side that depends only on the batch's ids.
 static int build_coalescing(antdt_ctx* c, const int32_t* ids, const int32_t* pay0, hipStream_t s) {
   SortPlan pl;
   SortBuffers sb;
@@ -866,9 +866,9 @@ static int dense_update(antdt_ctx* c, const ShardTab& tab, bf16_t* wb0, hipStrea
 // are better formed piece by piece, on large tiles, and added up by the update than by blocks that each walk all
 // samples.  With few tiles and many samples the latter have to be small tiles to be enough for the compute
 // units, and read each operand twice as often (845-1024-512-256, 15625 samples of eight unequal shards: 168 us against
-// 85 + 19 for the update; the whole step at 9000 / 15625 samples 389 / 577 -> 376 / 542 us).  Every piece costs a write
-// and a read of all gradients, which takes about a thousand samples to pay (6500 samples in 7 pieces 284 / 294 us,
-// 2573-1024-512 with 6500 in 12 pieces 471 / 507, 11000 in 12 779 / 777).
+// 85 + 19 for the update; the whole step with 1.1 M (4.3 M) lookups 483 -> 381 (624 -> 517) us, of 9000 samples 314 -> 273 (391 -> 369), 6500
+// in one range 218 -> 202).  Every piece costs a write and a read of all gradients, which takes about a thousand samples to pay (6500
+// samples in 7 pieces 284 / 294 us, 2573-1024-512 with 6500 in 12 pieces 471 / 507, 11000 in 12 779 / 777: measured on earlier kernels).
 static int cut_ranges(const antdt_ctx* c, const KSegments& seg, KSegments& pieces) {
   int64_t samples = 0, tiles = 0;
   for (int q = 0; q < seg.n; ++q) samples += seg.ke[q] - seg.ks[q];
@@ -918,8 +918,8 @@ static bool wgrad_in_pieces(const antdt_ctx* c) {
 }
 
 // Lookups from which the sort does not wait for the gather: the sample index of every lookup then comes from a launch of
-// its own on the sort's stream, one more for the host (behind / beside the gather, us per step: 1.1 M lookups 183 / 192,
-// 1.8 M 220 / 220, 3.8 M 421 / 411, 4.3 M 550 / 543, 42 M 3350 / 3313).
+// its own on the sort's stream, one more for the host (behind / beside the gather, us per step: 26 fields, 1.1 M lookups 193 / 200,
+// 1.8 M 267 / 282, 2.5 M 361 / 357, 3.3 M 435 / 438, 4.3 M 521 / 515; 60 fields, 2.0 M 238 / 238, 3.8 M 397 / 385; 100, 42 M 2879 / 2820).
 static constexpr int64_t EARLY_MIN = 3000000;
 
 // Forward and backward of shards [k0, k1) as one batched sequence of launches.
@@ -1123,12 +1123,12 @@ int antdt_aggregate(antdt_ctx* c, const uint8_t* shard_mask, void* stream) {
   }
   bool all = true;  // leaving out an empty shard changes nothing
   for (int k = 0; k < K; ++k) all = all && (c->included[k] || c->tab.len[k] == 0);
-  {  // also when the structure built there is stale (a new split): its buffers are rebuilt below
+  {  // also when what is sorted there is stale (a new split): its buffers are rebuilt below
     const int rc = join_side(c, s);
     if (rc) return rc;
   }
   if (c->presorted && all) {
-    // the batched worker step already built the structure on the side stream (the weights are no part of it)
+    // the batched worker step has sorted, on the side stream or in its weight-gradient launch (the weights are no part of it)
     if (c->weights_dirty) set_weights(c);
   } else if (all) {
     set_weights(c);
@@ -1176,7 +1176,7 @@ int antdt_set_shard_scale(antdt_ctx* c, const double* scale, int32_t K) {
       if (!(scale[k] >= 0.0) || !isfinite(scale[k]))
         return fail(c, ANTDT_INVALID_ARG, "antdt_set_shard_scale: factors must be finite and >= 0");
   for (int k = 0; k < ANTDT_MAX_SHARDS; ++k) c->shard_scale[k] = (scale && k < K) ? scale[k] : 1.0;
-  c->weights_dirty = true;  // an aggregation structure built ahead of time carries the old weights
+  c->weights_dirty = true;  // those in `tab` are stale: antdt_aggregate forms them anew, also where the sort was made ahead of time
   return ANTDT_OK;
 }
 
