@@ -30,16 +30,37 @@ __device__ __forceinline__ float lane_value(float v, int lane) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
 }
 
-// Four neighbouring columns of a row (the first at `x`), and the store of four results.
-template <typename T> __device__ __forceinline__ void load4(const T* x, float (&v)[4]);
-template <> __device__ __forceinline__ void load4(const float* x, float (&v)[4]) {
-  const float4 q = *reinterpret_cast<const float4*>(x);
-  v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
-}
-template <> __device__ __forceinline__ void load4(const bf16_t* x, float (&v)[4]) {
-  const uint2 q = *reinterpret_cast<const uint2*>(x);
-  v[0] = __uint_as_float(q.x << 16); v[1] = __uint_as_float(q.x & 0xFFFF0000u);
-  v[2] = __uint_as_float(q.y << 16); v[3] = __uint_as_float(q.y & 0xFFFF0000u);
+// Four neighbouring columns of a row as they lie in memory, and the store of four results.
+template <typename T> struct Quad;
+template <> struct Quad<float> {
+  static constexpr int WORDS = 4;
+  uint32_t d[4];
+  __device__ __forceinline__ void load(const float* x) {
+    const uint4 q = *reinterpret_cast<const uint4*>(x);
+    d[0] = q.x; d[1] = q.y; d[2] = q.z; d[3] = q.w;
+  }
+  __device__ __forceinline__ float operator[](int e) const { return __uint_as_float(d[e]); }
+};
+template <> struct Quad<bf16_t> {
+  static constexpr int WORDS = 2;
+  uint32_t d[2];
+  __device__ __forceinline__ void load(const bf16_t* x) {
+    const uint2 q = *reinterpret_cast<const uint2*>(x);
+    d[0] = q.x; d[1] = q.y;
+  }
+  __device__ __forceinline__ float operator[](int e) const { return __uint_as_float(e & 1 ? d[e >> 1] & 0xFFFF0000u : d[e >> 1] << 16); }
+};
+// The 4 x 4 of registers and rows of sixteen lanes turned: register r of row q takes register q of row r.
+__device__ __forceinline__ void turn(uint32_t& a, uint32_t& b, uint32_t& c, uint32_t& d) {
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+  auto swap = [](u32x2 p, uint32_t& x, uint32_t& y) {
+    x = p.x;
+    y = p.y;
+  };
+  swap(__builtin_amdgcn_permlane32_swap(a, c, false, false), a, c);
+  swap(__builtin_amdgcn_permlane32_swap(b, d, false, false), b, d);
+  swap(__builtin_amdgcn_permlane16_swap(a, b, false, false), a, b);
+  swap(__builtin_amdgcn_permlane16_swap(c, d, false, false), c, d);
 }
 __device__ __forceinline__ void store4(float* x, const float (&v)[4]) { *reinterpret_cast<float4*>(x) = make_float4(v[0], v[1], v[2], v[3]); }
 __device__ __forceinline__ void store4(bf16_t* x, const float (&v)[4]) { *reinterpret_cast<uint2*>(x) = make_uint2(f2bf2(v[0], v[1]), f2bf2(v[2], v[3])); }
@@ -56,10 +77,11 @@ __device__ __forceinline__ void store4(bf16_t* x, const float (&v)[4]) { *reinte
 // amplify that: single entries of dh then round to another bf16 neighbour (up to 3e-4 of a step).
 //   Without VEC a lane is a chain, of each of the four samples.
 //   VEC: sixteen lanes have a sample, four chains each (columns 4 (lane & 15) .. + 3 of every 64).  The sums over the samples and
-//   dh need a column of all four samples in one lane, the columns 4 lane .. 4 lane + 3 of every 256; these are loaded too (up to
-//   512 columns ahead of the logit: the same lines, in flight together).
+//   dh need a column of all four samples in one lane; the registers are turned for them (loaded a second time in that order they
+//   left a SIMD three wavefronts).  A launch, us, with columns loaded one at a time / twice / turned: 64 x 256 7.0 / 5.9 / 5.8,
+//   4096 x 256 6.6 / 6.2 / 5.9, 15 625 x 256 10.8 / 12.9 / 10.0, 16 384 x 512 13.7 / 17.7 / 12.6.
 template <typename TH, typename TD, bool VEC>
-__global__ __launch_bounds__(256) void head_tile_kernel(HeadArgs a, ShardTab tab, HeadTiles ht) {
+__global__ __launch_bounds__(256, sizeof(TH) == 2 ? 5 : 4) void head_tile_kernel(HeadArgs a, ShardTab tab, HeadTiles ht) {
   constexpr int SPW = HEAD_TILE / 4;   // samples per wavefront
   static_assert(SPW == 4, "sixteen lanes per sample");
   constexpr int PARTS = 2, CHUNK = 256 * PARTS;
@@ -93,64 +115,78 @@ __global__ __launch_bounds__(256) void head_tile_kernel(HeadArgs a, ShardTab tab
   const float bias = a.b[0];
 
   // Columns of all four samples: column(i, e) of the 512 from j0 on.
-  float hv[PARTS][SPW][4], w[PARTS][4];
+  typedef Quad<typename std::conditional<VEC, TH, float>::type> Columns;
+  Columns hv[PARTS][SPW];
+  Quad<float> w[PARTS];
   auto column = [&](int i, int e) { return i * 256 + (VEC ? lane * 4 + e : e * 64 + lane); };
-  auto load = [&](int j0) {
+  auto load_w = [&](int j0) {
 #pragma unroll
     for (int i = 0; i < PARTS; ++i) {
-      if (j0 + i * 256 >= a.width) {   // (the same for all lanes)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          w[i][e] = 0.0f;
-#pragma unroll
-          for (int r = 0; r < SPW; ++r) hv[i][r][e] = 0.0f;
-        }
-      } else if (VEC) {
-        const int jc = min(j0 + column(i, 0), a.width - 4);
-        load4(a.w + jc, w[i]);
-#pragma unroll
-        for (int r = 0; r < SPW; ++r) load4(h[r] + jc, hv[i][r]);
+      if (j0 + i * 256 >= a.width) continue;   // (the same for all lanes)
+      if (VEC) {
+        w[i].load(a.w + min(j0 + column(i, 0), a.width - 4));
       } else {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int jc = min(j0 + column(i, e), a.width - 1);
-          w[i][e] = a.w[jc];
+        for (int e = 0; e < 4; ++e) w[i].d[e] = j0 + column(i, e) < a.width ? __float_as_uint(a.w[j0 + column(i, e)]) : 0;
+      }
+    }
+  };
+  auto load_h = [&](int j0) {
 #pragma unroll
-          for (int r = 0; r < SPW; ++r) hv[i][r][e] = to_f32(h[r][jc]);
+    for (int i = 0; i < PARTS; ++i) {
+      if (j0 + i * 256 >= a.width) continue;
+#pragma unroll
+      for (int r = 0; r < SPW; ++r) {
+        if constexpr (VEC) {
+          hv[i][r].load(h[r] + min(j0 + column(i, 0), a.width - 4));
+          if (j0 + column(i, 0) >= a.width) hv[i][r] = {};   // (the four are inside or outside together)
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            hv[i][r].d[e] = j0 + column(i, e) < a.width ? __float_as_uint(to_f32(h[r][j0 + column(i, e)])) : 0;
         }
       }
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (j0 + column(i, VEC ? 0 : e) >= a.width) {   // (VEC: the four are inside or outside together)
-          w[i][e] = 0.0f;
-#pragma unroll
-          for (int r = 0; r < SPW; ++r) hv[i][r][e] = 0.0f;
-        }
     }
   };
   const bool loaded = a.width <= CHUNK;
   float z;   // logit of the lane's sample, without the bias
-  if (VEC) {
+  if constexpr (VEC) {
     const TH* h_own = activation(sample_row(own));
+    constexpr int STEPS = CHUNK / 64;
     float chain[4] = {};
     for (int j0 = 0; j0 < a.width; j0 += CHUNK) {
-      constexpr int STEPS = CHUNK / 64;
-      float x[STEPS][4], y[STEPS][4];
+      Columns x[STEPS];
+      Quad<float> y[STEPS];
 #pragma unroll
-      for (int i = 0; i < STEPS; ++i)
+      for (int i = 0; i < STEPS; ++i) {
+        x[i] = {};
+        y[i] = {};
         if (j0 + i * 64 < a.width) {   // (the same for all lanes)
           const int jc = min(j0 + i * 64 + (lane & 15) * 4, a.width - 4);
-          load4(h_own + jc, x[i]);
-          load4(a.w + jc, y[i]);
+          x[i].load(h_own + jc);
+          y[i].load(a.w + jc);
         }
-      if (loaded) load(0);
+      }
+      if (loaded) load_w(0);
 #pragma unroll
-      for (int i = 0; i < STEPS; ++i)
-        if (j0 + i * 64 < a.width) {
-          const bool in = j0 + i * 64 + (lane & 15) * 4 < a.width;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) chain[e] = fmaf(in ? x[i][e] : 0.0f, in ? y[i][e] : 0.0f, chain[e]);
+      for (int i = 0; i < STEPS; ++i) {
+        if (j0 + i * 64 >= a.width) continue;
+        if (j0 + i * 64 + (lane & 15) * 4 >= a.width) {
+          x[i] = {};
+          y[i] = {};
         }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) chain[e] = fmaf(x[i][e], y[i][e], chain[e]);
+      }
+      if (loaded) {
+#pragma unroll
+        for (int i = 0; i < PARTS; ++i) {
+#pragma unroll
+          for (int r = 0; r < SPW; ++r) hv[i][r] = x[i * 4 + r];
+#pragma unroll
+          for (int k = 0; k < Columns::WORDS; ++k) turn(hv[i][0].d[k], hv[i][1].d[k], hv[i][2].d[k], hv[i][3].d[k]);
+        }
+      }
     }
 #pragma unroll
     for (int e = 0; e < 4; ++e) {   // chains 4 q + e of the sixteen lanes q
@@ -163,13 +199,16 @@ __global__ __launch_bounds__(256) void head_tile_kernel(HeadArgs a, ShardTab tab
   } else {
     float part[SPW] = {};
     for (int j0 = 0; j0 < a.width; j0 += CHUNK) {
-      load(j0);
+      load_w(j0);
+      load_h(j0);
 #pragma unroll
-      for (int i = 0; i < PARTS; ++i)
+      for (int i = 0; i < PARTS; ++i) {
+        if (j0 + i * 256 >= a.width) continue;
 #pragma unroll
         for (int e = 0; e < 4; ++e)
 #pragma unroll
           for (int r = 0; r < SPW; ++r) part[r] = fmaf(hv[i][r][e], w[i][e], part[r]);
+      }
     }
     z = 0.0f;
 #pragma unroll
@@ -189,7 +228,10 @@ __global__ __launch_bounds__(256) void head_tile_kernel(HeadArgs a, ShardTab tab
   const bool per_sample = sizeof(TD) == 4 && a.dz;   // (bf16 gradients: there is a hidden layer)
   float* part_out = a.part + (int64_t)tile * a.ldpart;
   for (int j0 = 0; j0 < a.width; j0 += CHUNK) {   // (dh_cols <= width)
-    if (!loaded) load(j0);
+    if (!loaded) {
+      load_w(j0);
+      load_h(j0);
+    }
 #pragma unroll
     for (int i = 0; i < PARTS; ++i) {
       if (j0 + i * 256 >= a.width) continue;   // (the same for all lanes)
