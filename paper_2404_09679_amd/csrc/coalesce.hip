@@ -646,7 +646,7 @@ template <typename TT, bool ROWWISE> struct TableRow {
     for (int e = 0; e < 4; ++e) n[e] = a.lr * g.v[e];
     const uint32_t least = min(min(magnitude_or_zero(n[0]), magnitude_or_zero(n[1])), min(magnitude_or_zero(n[2]), magnitude_or_zero(n[3])));
     // Accumulators and gradients of any run under way.  (A root is below 2^45, a gradient of 256 columns below 2^49 then.)
-    if (__ballot(beyond >= MID_SPAN || least < MID_LEAST) == 0 && a.eps < 0x1p45f && a.lr < 0x1p30f) {
+    if ((__ballot(beyond >= MID_SPAN) | __ballot(least < MID_LEAST)) == 0 && a.eps < 0x1p45f && a.lr < 0x1p30f) {
       float den[NS], rcp[NS];
 #pragma unroll
       for (int e = 0; e < NS; ++e) {
@@ -696,12 +696,13 @@ __device__ __forceinline__ int64_t run_index(const SegArgs& a, int f, int pos) {
 // the rows themselves are read, and the chain of dependent accesses is down to LDS -> row and pooled gradients.
 // A window that lies inside one run (60 % of them with 42 M lookups of Zipf(1.2) ids) needs none of this: sum_window.
 // Bound by the requests for pooled-gradient rows that a compute unit can have outstanding (about 64 lines; they come from
-// L2 and the memory-side cache) and by vector instructions (58 % of the cycles, 66 before windows inside a run went a way of
-// their own and the update lost the general square root and division; the pooled-gradient rows of a sample that looks a
+// L2 and the memory-side cache) and by vector instructions (67 % of the cycles; windows inside a run have a way of their own and the
+// update goes without the general square root and division; the pooled-gradient rows of a sample that looks a
 // row up several times are read once there).  Row and accumulators are requested ahead of the item's pooled gradients, not
 // an item ahead: that took 8 registers more, and eight wavefronts per SIMD hide as much.  Us per launch, before / now:
 // 42 M lookups of 128-byte bf16 rows 1228 / 1016 (963 with the weights in registers, see SampleWeights; of that 880 in the
-// windows of short runs), 3.8 M 141 / 119, 4.3 M of 128-byte fp32 rows 161 / 148 (138), 1.1 M 46.6 / 41.7 (40).
+// windows of short runs; 978 with the update's numerators bounded), 3.8 M 141 / 119 (122), 4.3 M of 128-byte fp32 rows 161 / 148 (138),
+// 1.1 M 46.6 / 41.7 (42).
 // Streaming loads and stores of the rows: 42 M 1003, but 1.1 M of a batch that returns 53 (they leave the memory-side cache).
 constexpr int LONG_RUN = 16;
 

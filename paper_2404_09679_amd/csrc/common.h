@@ -75,7 +75,7 @@ enum KernelId {
   KID_POOL = 0,
   KID_GEMM_FWD,
   KID_GEMM_DGRAD,      // gone: counted under KID_GEMM_BWD
-  KID_GEMM_WGRAD,
+  KID_GEMM_WGRAD,      // (of an fp32 model with the sort, where it joins)
   KID_HEAD,
   KID_HEAD_REDUCE,     // gone: blocks of the input-gradient and the weight-gradient launch
   KID_BIAS_GRAD,       // gone: part of the weight gradients
