@@ -35,13 +35,15 @@ __device__ __forceinline__ void zero_acc(f32x16 (&acc)[TM][TN]) {
 }
 
 // C[m, n] = sum_k A(m, k) * B(n, k) with the epilogue of GemmArgs; A contiguous along k, B either way.
-// Blocks are numbered so that the blocks sharing an A row-panel run on the same XCD (L2).
+// Blocks are numbered so that an XCD (block i runs on XCD i mod 8) has a share of consecutive tiles, and tiles along the shorter side of C
+// are neighbours: of the longer operand an XCD's L2 then fetches its own share only, of the shorter one all.  (Rows of C
+// neighbours always, weights of 2 to 8 MB fetched by all eight: 512 x 3840 x 1024 12.2 us, so 9.3; 256 x 832 x 1024 5.7 / 4.8.)
 // The results leave through LDS, 32 rows of a wavefront's tile at a time: a lane of the MFMA result holds
 // groups of four neighbouring columns of one row, which would be 8-byte stores (16 with fp32 results) all
 // over 32 rows; staged, they are 16-byte stores of whole row segments.
-template <int TM, int TN, int WR, int WC, int BK, int STAGES, bool B_STRIDED, bool FAR>
-__global__ __launch_bounds__(64 * WR * WC) void gemm_bf16_kernel(GemmArgs p, int tiles_n) {
-  typedef BlockProduct<TM, TN, WR, WC, BK, STAGES, false, B_STRIDED, FAR> P;
+template <int TM, int TN, int WR, int WC, int BK, int STAGES, bool B_STRIDED, bool FAR, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void gemm_bf16_kernel(GemmArgs p, int tiles_minor, bool m_minor) {
+  typedef BlockProduct<TM, TN, WR, WC, BK, STAGES, false, B_STRIDED, FAR, WAVES> P;
   extern __shared__ __attribute__((aligned(16))) char lds[];
   int pid = blockIdx.x;
   const int nblk = gridDim.x - p.loss_blocks;
@@ -49,8 +51,9 @@ __global__ __launch_bounds__(64 * WR * WC) void gemm_bf16_kernel(GemmArgs p, int
     add_up_losses(p.loss + (pid - nblk));
     return;
   }
-  if ((nblk & 7) == 0) pid = (pid & 7) * (nblk >> 3) + (pid >> 3);
-  const int m0 = (pid / tiles_n) * P::BM, n0 = (pid % tiles_n) * P::BN;
+  pid = (pid & 7) * (nblk >> 3) + min(pid & 7, nblk & 7) + (pid >> 3);
+  const int major = pid / tiles_minor, minor = pid - major * tiles_minor;
+  const int m0 = (m_minor ? minor : major) * P::BM, n0 = (m_minor ? major : minor) * P::BN;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int fr = lane & 31, fg = lane >> 5;
@@ -65,6 +68,7 @@ __global__ __launch_bounds__(64 * WR * WC) void gemm_bf16_kernel(GemmArgs p, int
   zero_acc(acc);
   P::run(reinterpret_cast<const bf16_t*>(p.A), reinterpret_cast<const bf16_t*>(p.B), p.lda, p.ldb, p.M, p.N, m0, n0, 0,
          p.K, lds, acc);
+  if (WAVES > WR * WC && wave >= WR * WC) return;
   __builtin_assume(wave < WR * WC);   // (which the compiler cannot see)
   const int wr = wave / WC, wc = wave % WC;
   const int mw = m0 + wr * (32 * TM), nw = n0 + wc * WN;
@@ -561,15 +565,16 @@ __global__ __launch_bounds__(256) void cast_bf16_kernel(CastArgs a) {
     a.dst[i] = i < a.n_src ? f2bf(a.src[i]) : (bf16_t)0;
 }
 
-template <int TM, int TN, int WR, int WC, int BK, int STAGES, bool BS, bool FAR = false>
+template <int TM, int TN, int WR, int WC, int BK, int STAGES, bool BS, bool FAR = false, int WAVES = WR * WC>
 hipError_t launch_bf16(const GemmArgs& a, hipStream_t s) {
-  typedef BlockProduct<TM, TN, WR, WC, BK, STAGES, false, BS, FAR> P;
+  typedef BlockProduct<TM, TN, WR, WC, BK, STAGES, false, BS, FAR, WAVES> P;
   static std::atomic<uint64_t> allowed{0};
-  const hipError_t ok = allow_lds(gemm_bf16_kernel<TM, TN, WR, WC, BK, STAGES, BS, FAR>, P::LDS_BYTES, 0, allowed);
+  const hipError_t ok = allow_lds(gemm_bf16_kernel<TM, TN, WR, WC, BK, STAGES, BS, FAR, WAVES>, P::LDS_BYTES, 0, allowed);
   if (ok != hipSuccess) return ok;
   const int tiles_m = (a.M + P::BM - 1) / P::BM, tiles_n = (a.N + P::BN - 1) / P::BN;
-  hipLaunchKernelGGL((gemm_bf16_kernel<TM, TN, WR, WC, BK, STAGES, BS, FAR>), dim3(tiles_m * tiles_n + a.loss_blocks), dim3(P::THREADS),
-                     P::LDS_BYTES, s, a, tiles_n);
+  const bool m_minor = a.M < a.N;
+  hipLaunchKernelGGL((gemm_bf16_kernel<TM, TN, WR, WC, BK, STAGES, BS, FAR, WAVES>), dim3(tiles_m * tiles_n + a.loss_blocks), dim3(P::THREADS),
+                     P::LDS_BYTES, s, a, m_minor ? tiles_m : tiles_n, m_minor);
   return hipGetLastError();
 }
 
@@ -579,19 +584,30 @@ hipError_t launch_bf16_sized(const GemmArgs& a, hipStream_t s) {
   // offsets where those reach.
   if (std::max(a.lda, a.ldb) * (256 * 2) >> 32) return launch_bf16<1, 1, 1, 1, 128, 3, BS, true>(a, s);
   auto blocks = [&](int bm, int bn) { return (int64_t)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
-  // Measured (us; M x N x K; tiles of 256, 128, 64 and 32 rows and columns, eight wavefronts on the first two,
-  // four, one):  16384 x 1024 x 6400: 189 / 224 / 483 / -;   2501 x 3840 x 1024: 30 / 32 / 47 / 89;
-  // 15625 x 512 x 1024: 38 / 24 / 31 / 61;  4096 x 1024 x 848: 32 / 16 / 18 / 35;  4096 x 512 x 1024: 31 / 15 / 10 / 20;
-  // 1531 x 1024 x 848: - / 16 / 10 / 16;  96 x 1024 x 848: - / 15 / 7.7 / 6.4.   The largest tile that gives most of
-  // the 256 compute units a block wins (it reads the fewest operand bytes), and below that more blocks do.
+  // The largest tile that gives most of the 256 compute units a block wins (it reads the fewest operand bytes); below that
+  // blocks that all find a place at once do, with few of them those that get their loads away fastest.  Measured (us; M x N x K):
+  //   256 x 256 / 128 x 128:                            16384 x 1024 x 6400 187 / 226; 16384 x 3840 x 1024 151 / 183; 15625 x 1024 x 848 33 / 35;
+  //   128 x 128 with two (two blocks to a compute unit) / three stages / 64 x 64:  8192 x 1024 x 848 19.2 / 20.4 / 27; 4096 x 1024 x 848
+  //     15.0 / 11.7 / 16.6; 4096 x 832 x 1024 15.9 / 13.1 / 17; 2560 x 1024 x 848 14.5 / 10.9 / 12.9; 2048 x 1024 x 848 14.4 / 10.7 / 10.0; input-like
+  //     operands (BS false) 3072 x 1024 x 512 10.3 / 9.0 / 8.6, 3072 x 832 x 1024 15.2 / 12.2 / 12.1, 768 x 3840 x 1024 15.8 / 12.6 / 12.8;
+  //   64 x 64 / 32 x 64, loads by eight wavefronts / 32 x 32, by four / by its own:  1024 x 1024 x 848 7.1 / 8.4 / 10.7 / 11.7;
+  //     512 x 1024 x 848 7.1 / 5.8 / 7.5 / 7.4; 1024 x 512 x 1024 6.8 / 5.9 / 6.3 / 6.2; 256 x 1024 x 848 6.3 / 5.6 / 5.7 / 5.8; 96 x 1024 x 848 6.3 / 5.4 /
+  //     5.0 / 5.4; 64 x 256 x 512 4.5 / 4.2 / 3.9 / 4.1; BS false: 896 x 832 x 1024 7.5 / 8.4 / 7.5 / 6.8; 512 x 1024 x 512 5.2 / 4.8 / 4.8 / 4.8;
+  //     64 x 832 x 1024 6.4 / 5.6 / 5.0 / 5.1.  (256 instead of 128 slots a stage, by four: 5.0, 3.7 and 4.5 us at 96, 64 and 64 samples, launched over and over,
+  //     but a worker step on 64 samples 44.8 us, with 128 44.5: every launch fetches its instructions anew.)
   // 256 x 256 from 200 blocks on instead of 150 was measured over 75 models and calls of 150 .. 199 such blocks (a step, or a
   // worker's: 3000 samples of 3840-1024-512 222 -> 240 us, 166 -> 173; 9800 of 845-1024-512-256 287 -> 295, 210 -> 218): 1 .. 8 %
   // slower but for five, of 3.8 M lookups in tables of half a million rows and more, where the tiles wait for compute
   // units that the weight gradients hold (2501 samples of 3840-1024-512 392 -> 380).
   if (blocks(256, 256) >= 150) return launch_bf16<4, 2, 2, 4, 64, 2, BS>(a, s);
-  if (blocks(128, 128) >= 200) return launch_bf16<2, 1, 2, 4, 64, 2, BS>(a, s);
-  if (blocks(64, 64) >= 100) return launch_bf16<1, 1, 2, 2, 64, 3, BS>(a, s);
-  return launch_bf16<1, 1, 1, 1, 128, 3, BS>(a, s);
+  if (blocks(128, 128) > 256) return launch_bf16<2, 1, 2, 4, 64, 2, BS>(a, s);
+  if (blocks(128, 128) >= (BS ? 150 : 200)) return launch_bf16<2, 1, 2, 4, 64, 3, BS>(a, s);
+  if (blocks(32, 32) <= 256) return launch_bf16<1, 1, 1, 1, 128, 3, BS, false, 4>(a, s);
+  if constexpr (BS) {
+    if (blocks(32, 64) <= 256) return launch_bf16<1, 1, 1, 2, 128, 3, BS, false, 8>(a, s);
+  }
+  if (!BS && blocks(32, 32) <= 768) return launch_bf16<1, 1, 1, 1, 128, 3, BS>(a, s);
+  return launch_bf16<1, 1, 2, 2, 64, 3, BS>(a, s);
 }
 
 template <int TM, int TN, int D>

@@ -97,10 +97,12 @@ struct OperandTile {
 // The tiles of one block: WR x WC wavefronts of TM x TN MFMA tiles each.  Every shape adds up the products in the
 // same order, so that a sample's results do not depend on how many samples are computed with it.
 // FAR: pieces of a tile may lie 4 GiB or more from its origin (operands wider than 2^31 / rows of the tile).
-template <int TM, int TN, int WR, int WC, int BK, int STAGES, bool A_STRIDED, bool B_STRIDED, bool FAR = false>
+// WAVES: wavefronts of the block; those behind the first WR x WC only request pieces (one wavefront gets a load away every 64 cycles or
+// so, so a tile of one wavefront alone waits for its own requests).
+template <int TM, int TN, int WR, int WC, int BK, int STAGES, bool A_STRIDED, bool B_STRIDED, bool FAR = false, int WAVES = WR * WC>
 struct BlockProduct {
   typedef typename std::conditional<FAR, uint64_t, uint32_t>::type Offset;
-  static constexpr int THREADS = 64 * WR * WC;
+  static constexpr int THREADS = 64 * WAVES;
   static constexpr int BM = 32 * TM * WR, BN = 32 * TN * WC;
   typedef OperandTile<BM, BK, A_STRIDED> TA;
   typedef OperandTile<BN, BK, B_STRIDED> TB;
@@ -172,6 +174,10 @@ struct BlockProduct {
       if (t + STAGES - 2 < nk) wait_loads<(STAGES - 2) * PER_STAGE>();
       else wait_loads<0>();
       block_barrier();          // ... and so have everyone's; stage t-1 has been read by everyone
+      if (WAVES > WR * WC && wave >= WR * WC) {
+        if (left > 0) issue();
+        continue;
+      }
       // The fragments of the next contraction step are requested before the current one is multiplied, and
       // the next stage behind the first multiplications: with one or two wavefronts per SIMD nothing else
       // would hide those instructions.

@@ -22,10 +22,10 @@ def _config(name, seed, **kw):
     return wl.RankingConfig(**base)
 
 
-# (samples per shard, hidden widths): tiles of 32 (few blocks), 64, 128 and 256 rows and columns in the forward
-# and data-gradient products, tiles of 64 and 128 in the weight gradients; no dimension a multiple of its tile
-PRODUCT_SHAPES = [((1,), (8,)), ((20, 13), (40, 8)), ((513, 0, 199), (264, 72)), ((2000, 1301), (1032, 136)),
-                  ((5003, 3200), (2056, 1544))]
+# (samples per shard, hidden widths): tiles of 32 (few blocks), 32 x 64, 64, 128 (two and three stages) and 256 rows and columns in
+# the forward and data-gradient products, tiles of 64 and 128 in the weight gradients; no dimension a multiple of its tile
+PRODUCT_SHAPES = [((1,), (8,)), ((20, 13), (40, 8)), ((151, 150), (1032, 264)), ((513, 0, 199), (264, 72)), ((1300, 801), (1544, 1160)),
+                  ((2000, 1301), (1032, 136)), ((5003, 3200), (2056, 1544))]
 
 
 @pytest.mark.parametrize("sizes,hidden", PRODUCT_SHAPES, ids=[str(sum(s)) for s, _ in PRODUCT_SHAPES])
