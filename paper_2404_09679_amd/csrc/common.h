@@ -213,9 +213,14 @@ struct WgradArgs {
   int32_t k0;
 };
 hipError_t launch_wgrad(const WgradArgs& a, const KSegments& seg, bool store, hipStream_t s);
+// Per-shard gradients and, in the same launch, the gradient of the pooled input: where wgrad_takes_dgrad says so (`sorted`: the launch sorts
+// those F fields too, else NULL).
+bool wgrad_takes_dgrad(const WgradArgs& a, int ranges, const GemmArgs& g, int F, const FieldPtr* sorted);
+hipError_t launch_wgrad_and_dgrad(const WgradArgs& a, const KSegments& seg, const GemmArgs& g, hipStream_t s);
 // Per-shard gradients of an fp32 model and, in the same launch, the sort (launch_sort with every field in one block, result in
-// key / pay [0]).
-hipError_t launch_wgrad_and_sort(const WgradArgs& a, const KSegments& seg, const SortPlan& pl, const SortBuffers& sb, const FieldPtr& fp, hipStream_t s);
+// key / pay [0]) and, unless NULL, the gradient of the pooled input (as above).
+hipError_t launch_wgrad_and_sort(const WgradArgs& a, const KSegments& seg, const SortPlan& pl, const SortBuffers& sb, const FieldPtr& fp,
+                                 const GemmArgs* dgrad, hipStream_t s);
 bool wgrad_takes_sort(const WgradArgs& a, int ranges, int64_t samples, int F, const FieldPtr& fp);   // it pays
 
 struct CastArgs {  // fp32 [rows, cols] -> bf16 [rows_pad, cols], extra rows zero
@@ -268,11 +273,14 @@ struct LossJob {
 };
 __device__ __forceinline__ void add_up_losses(const LossJob* job) {   // (the first wavefront of a block)
   if (threadIdx.x >= 64) return;
+  // (pointers from memory are not known to be global ones, and a flat access makes the compiler wait for all loads in the rest of the kernel)
+  typedef __attribute__((address_space(1))) float global_float;
+  const global_float* sums = (const global_float*)job->sums;
   float l = 0.0f;
-  for (int t = (int)threadIdx.x; t < job->tiles; t += 64) l += job->sums[(int64_t)t * job->ldpart];
+  for (int t = (int)threadIdx.x; t < job->tiles; t += 64) l += sums[(int64_t)t * job->ldpart];
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) l += __shfl_xor(l, o, 64);
-  if (threadIdx.x == 0 && job->loss_out) *job->loss_out = job->len > 0 ? l / (float)job->len : 0.0f;
+  if (threadIdx.x == 0 && job->loss_out) *(global_float*)job->loss_out = job->len > 0 ? l / (float)job->len : 0.0f;
 }
 
 // ------------------------------------------------------------- coalesce.hip

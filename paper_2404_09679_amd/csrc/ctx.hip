@@ -28,8 +28,11 @@ struct Profiler {
   int64_t launches[KID_COUNT] = {};
 };
 
+static bool prof_times(const Profiler* p, int kid) {
+  return p->mode != 0 && !(p->mode == 2 && kid != p->sel) && !(p->mode == 3 && !((p->sel >> kid) & 1));
+}
 int prof_begin(Profiler* p, int kid, hipStream_t s) {
-  if (p->mode == 0 || (p->mode == 2 && kid != p->sel) || (p->mode == 3 && !((p->sel >> kid) & 1))) return -1;
+  if (!prof_times(p, kid)) return -1;
   ProfRec r;
   r.kid = kid;
   if (!p->pool.empty()) {
@@ -259,6 +262,8 @@ static int fail(antdt_ctx* c, int code, const std::string& msg) {
 static constexpr unsigned SYNC_EVENT_FLAGS = hipEventDisableTiming | hipEventDisableSystemFence;
 
 static inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
+// Whether one of two classes is being timed: launches that would do the work of both are then made apart.
+static inline bool prof_apart(const Profiler* p, int a, int b) { return p && (prof_times(p, a) || prof_times(p, b)); }
 static inline Profiler* prof_of(antdt_ctx* c) { return c->prof.mode ? &c->prof : nullptr; }
 
 static bool is_pow2(int64_t v) { return v > 0 && (v & (v - 1)) == 0; }
@@ -787,9 +792,9 @@ static bool sort_joins(antdt_ctx* c) {
   return wgrad_takes_sort(u, c->tab.K, c->B, c->m.num_fields, c->fp);
 }
 
-// Per-shard gradients of all dense layers for shards [k0, k1), one launch on `ws`; with `sort` the launch of an fp32 model
-// also sorts the batch's lookups.
-static int shard_weight_gradients(antdt_ctx* c, int k0, int k1, hipStream_t ws, bool sort = false) {
+// Per-shard gradients of all dense layers for shards [k0, k1), one launch on `ws`; with `dgrad` it forms the gradient of the pooled
+// input too, with `sort` that of an fp32 model also sorts the batch's lookups.
+static int shard_weight_gradients(antdt_ctx* c, int k0, int k1, hipStream_t ws, bool sort = false, const GemmArgs* dgrad = nullptr) {
   WgradArgs u;
   fill_wgrad_args(c, u);
   u.k0 = k0;
@@ -806,8 +811,10 @@ static int shard_weight_gradients(antdt_ctx* c, int k0, int k1, hipStream_t ws, 
     SortPlan pl;
     SortBuffers sb;
     fill_sort(c, c->ids, c->lookup_sample, pl, sb);
-    HIP_TRY(c, launch_wgrad_and_sort(u, seg, pl, sb, c->afp, ws));
+    HIP_TRY(c, launch_wgrad_and_sort(u, seg, pl, sb, c->afp, dgrad, ws));
     c->sorted_buf = 0;
+  } else if (dgrad) {
+    HIP_TRY(c, launch_wgrad_and_dgrad(u, seg, *dgrad, ws));
   } else {
     HIP_TRY(c, launch_wgrad(u, seg, true, ws));
   }
@@ -1050,6 +1057,13 @@ static int worker_range(antdt_ctx* c, int k0, int k1, float* loss_out, hipStream
   }
   c->operands_captured = capturing;
   if (deferred && L <= 2) HIP_TRY(c, hipEventRecord(c->ev_dh[0], s));
+  // All shards of an fp32 model whose sort goes to no other stream: it runs beside the weight gradients
+  const bool sort = !deferred && c->batched && !beside && c->total_tiles > 0 && c->joined_sort_used && sort_joins(c);
+  // The gradient of the pooled input, which only the aggregation reads, shares the launch of weight gradients that are formed here, where
+  // that takes it (and nobody times the two classes apart).
+  GemmArgs joined;
+  bool joins = false;
+  const bool apart = deferred || prof_apart(pr, KID_GEMM_BWD, KID_GEMM_WGRAD);
   ProfScope bwd_scope(L > 1 ? pr : nullptr, KID_GEMM_BWD, s);
   bwd_scope.launches(L - 1);
   for (int l = L - 2; l >= 0; --l) {   // gradient w.r.t. act_l: through W_l, then the ReLU of layer l-1 (none for the input)
@@ -1071,20 +1085,24 @@ static int worker_range(antdt_ctx* c, int k0, int k1, float* loss_out, hipStream
         g.loss_blocks = k1 - k0;
       }
     }
-    HIP_TRY(c, launch_gemm(g, s));
+    if (l == 0 && !apart) {
+      WgradArgs u;
+      fill_wgrad_args(c, u);
+      joined = g;
+      joins = wgrad_takes_dgrad(u, k1 - k0, g, m.num_fields, sort ? &c->fp : nullptr);
+    }
+    if (!joins) HIP_TRY(c, launch_gemm(g, s));
     if (l == 1 && deferred) HIP_TRY(c, hipEventRecord(c->ev_dh[0], s));
   }
   bwd_scope.close();
   if (!deferred) {
-    // All shards of an fp32 model whose sort goes to no other stream: it runs beside the weight gradients
-    const bool sort = c->batched && !beside && c->total_tiles > 0 && c->joined_sort_used && sort_joins(c);
     if (sort) {
       c->joined_sort_used = false;
       for (int k = 0; k < tab.K; ++k) c->included[k] = true;
       set_weights(c);
       coalesce_whole_batch(c);
     }
-    const int rc = shard_weight_gradients(c, k0, k1, s, sort);
+    const int rc = shard_weight_gradients(c, k0, k1, s, sort, joins ? &joined : nullptr);
     if (rc) return rc;
     c->presorted = c->presorted || sort;
   }

@@ -42,15 +42,8 @@ __device__ __forceinline__ void zero_acc(f32x16 (&acc)[TM][TN]) {
 // groups of four neighbouring columns of one row, which would be 8-byte stores (16 with fp32 results) all
 // over 32 rows; staged, they are 16-byte stores of whole row segments.
 template <int TM, int TN, int WR, int WC, int BK, int STAGES, bool B_STRIDED, bool FAR, int WAVES>
-__global__ __launch_bounds__(64 * WAVES) void gemm_bf16_kernel(GemmArgs p, int tiles_minor, bool m_minor) {
+__device__ __forceinline__ void gemm_bf16_tile(GemmArgs p, int pid, int nblk, int tiles_minor, bool m_minor, char* lds) {
   typedef BlockProduct<TM, TN, WR, WC, BK, STAGES, false, B_STRIDED, FAR, WAVES> P;
-  extern __shared__ __attribute__((aligned(16))) char lds[];
-  int pid = blockIdx.x;
-  const int nblk = gridDim.x - p.loss_blocks;
-  if (pid >= nblk) {
-    add_up_losses(p.loss + (pid - nblk));
-    return;
-  }
   pid = (pid & 7) * (nblk >> 3) + min(pid & 7, nblk & 7) + (pid >> 3);
   const int major = pid / tiles_minor, minor = pid - major * tiles_minor;
   const int m0 = (m_minor ? minor : major) * P::BM, n0 = (m_minor ? major : minor) * P::BN;
@@ -153,10 +146,21 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_bf16_kernel(GemmArgs p, int t
   }
 }
 
+template <int TM, int TN, int WR, int WC, int BK, int STAGES, bool B_STRIDED, bool FAR, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void gemm_bf16_kernel(GemmArgs p, int tiles_minor, bool m_minor) {
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  const int nblk = gridDim.x - p.loss_blocks;
+  if ((int)blockIdx.x >= nblk) {
+    add_up_losses(p.loss + (blockIdx.x - nblk));
+    return;
+  }
+  gemm_bf16_tile<TM, TN, WR, WC, BK, STAGES, B_STRIDED, FAR, WAVES>(p, blockIdx.x, nblk, tiles_minor, m_minor, lds);
+}
+
 // Weight gradients of all hidden layers in one launch (see WgradArgs): block = one tile of one layer's
 //   [dW_l ; db_l] = [act_l ; 1]^T dH_{l+1}
 // over sample ranges; both operands are read as they lie in memory, [sample, width].
-//   WGRAD_STORE   the ranges of shard blockIdx.y: written to that shard's flat gradient;
+//   WGRAD_STORE   the range of `shard`: written to that shard's flat gradient;
 //   otherwise     every range's sum from zero, added up with the ranges' weights in range order
 //                 (g = fma(w_k, sum_k, g), the order in which the stand-alone dense update adds the shards'
 //                 gradients), then Adagrad on the tile and the bf16 copy of the new weights.
@@ -217,16 +221,15 @@ __device__ __forceinline__ void last_layer(const WgradArgs& u, const KSegments& 
 }
 
 template <int TM, int TN, int WR, int WC, int BK, int STAGES, WgradMode MODE, bool FAR>
-__global__ __launch_bounds__(64 * WR * WC) void wgrad_kernel(WgradArgs u, KSegments seg) {
+__device__ __forceinline__ void wgrad_tile(const WgradArgs& u, const KSegments& seg, int tile, int shard, char* lds) {
   typedef BlockProduct<TM, TN, WR, WC, BK, STAGES, true, true, FAR> P;
-  extern __shared__ __attribute__((aligned(16))) char lds[];
-  if ((int)blockIdx.x >= u.tile_base[u.n_layers]) {
-    last_layer<MODE, bf16_t>(u, seg, blockIdx.x - u.tile_base[u.n_layers], blockIdx.y, threadIdx.x, reinterpret_cast<float(*)[64]>(lds));
+  if (tile >= u.tile_base[u.n_layers]) {
+    last_layer<MODE, bf16_t>(u, seg, tile - u.tile_base[u.n_layers], shard, threadIdx.x, reinterpret_cast<float(*)[64]>(lds));
     return;
   }
   int li = 0;
-  while (li + 1 < u.n_layers && (int)blockIdx.x >= u.tile_base[li + 1]) ++li;
-  const int pid = blockIdx.x - u.tile_base[li];
+  while (li + 1 < u.n_layers && tile >= u.tile_base[li + 1]) ++li;
+  const int pid = tile - u.tile_base[li];
   const int M = u.M[li], N = u.N[li];
   const int m0 = (pid / u.tiles_n[li]) * P::BM, n0 = (pid % u.tiles_n[li]) * P::BN;
   const int lane = threadIdx.x & 63;
@@ -239,7 +242,7 @@ __global__ __launch_bounds__(64 * WR * WC) void wgrad_kernel(WgradArgs u, KSegme
   zero_acc(tot);
   zero_acc(totb);
   if (MODE != WGRAD_MANY) {
-    const int q = MODE == WGRAD_STORE ? blockIdx.y : 0;
+    const int q = MODE == WGRAD_STORE ? shard : 0;
     P::template run<true>(reinterpret_cast<const bf16_t*>(u.A[li]), reinterpret_cast<const bf16_t*>(u.B[li]), u.lda[li], u.ldb[li], M, N, m0, n0, seg.ks[q], seg.ke[q], lds, tot, totb[0], ones);
     if (MODE == WGRAD_ONE) {
       const float w = seg.w[0];
@@ -279,7 +282,7 @@ __global__ __launch_bounds__(64 * WR * WC) void wgrad_kernel(WgradArgs u, KSegme
   constexpr int CPR = WN / 4, RPI = 64 / CPR;
   const int rr = lane / CPR, cc = (lane % CPR) * 4;
   const int64_t base = u.w_off[li];
-  float* out = MODE == WGRAD_STORE ? u.grads + (int64_t)(u.k0 + blockIdx.y) * u.stride + base : nullptr;
+  float* out = MODE == WGRAD_STORE ? u.grads + (int64_t)(u.k0 + shard) * u.stride + base : nullptr;
   float* Pm = u.p + base;
   float* S = u.state + base;
   bf16_t* Wb = u.wb[li];
@@ -326,6 +329,28 @@ __global__ __launch_bounds__(64 * WR * WC) void wgrad_kernel(WgradArgs u, KSegme
           finish4((int64_t)M * N + n, make_float4(totb[0][j][4 * v], totb[0][j][4 * v + 1], totb[0][j][4 * v + 2], totb[0][j][4 * v + 3]), false);
       }
   }
+}
+
+template <int TM, int TN, int WR, int WC, int BK, int STAGES, WgradMode MODE, bool FAR>
+__global__ __launch_bounds__(64 * WR * WC) void wgrad_kernel(WgradArgs u, KSegments seg) {
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  wgrad_tile<TM, TN, WR, WC, BK, STAGES, MODE, FAR>(u, seg, blockIdx.x, blockIdx.y, lds);
+}
+
+// The per-shard weight gradients and, in further blocks, the gradient of the pooled input (GEMM: its tile) and the losses: neither
+// waits for the other, and on one stream the second launch would wait for the first one's last block.
+template <int TM, int TN, int WR, int WC, int BK, int STAGES>
+__global__ __launch_bounds__(256) void wgrad_dgrad_kernel(WgradArgs u, KSegments seg, int tiles, GemmArgs p, int tiles_minor, bool m_minor) {
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  int i = blockIdx.x;
+  if (i < tiles * seg.n) {
+    wgrad_tile<1, 1, 2, 2, 64, 3, WGRAD_STORE, false>(u, seg, i % tiles, i / tiles, lds);
+    return;
+  }
+  i -= tiles * seg.n;
+  const int nblk = gridDim.x - tiles * seg.n - p.loss_blocks;
+  if (i >= nblk) add_up_losses(p.loss + (i - nblk));
+  else gemm_bf16_tile<TM, TN, WR, WC, BK, STAGES, false, false, 4>(p, i, nblk, tiles_minor, m_minor, lds);
 }
 
 // ---------------------------------------------------------------- fp32 products
@@ -445,18 +470,10 @@ __device__ __forceinline__ void f32_product(const OA& oa, const OB& ob, int K, i
   }
 }
 
-// C[m, n] = sum_k A[m * lda + k] B(n, k) with the epilogue of GemmArgs; four wavefronts per block, each a tile of
-// its own (neighbours along n first: they share the rows of A).
+// C[m, n] = sum_k A[m * lda + k] B(n, k) with the epilogue of GemmArgs: the tile of one wavefront.
 template <int TM, int TN, int D, bool BKC, F32Load L>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs p, int tiles_n, int tiles) {
-  const int nblk = gridDim.x - p.loss_blocks;
-  if ((int)blockIdx.x >= nblk) {
-    add_up_losses(p.loss + (blockIdx.x - nblk));
-    return;
-  }
+__device__ __forceinline__ void gemm_f32_tile(GemmArgs p, int tiles_n, int id) {
   const int lane = threadIdx.x & 63;
-  const int id = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (id >= tiles) return;
   const int m0 = id / tiles_n * (16 * TM), n0 = id % tiles_n * (16 * TN);
   const F32Operand<TM, true, L> oa(reinterpret_cast<const float*>(p.A), p.lda, m0, p.M, lane);
   const F32Operand<TN, BKC, L> ob(reinterpret_cast<const float*>(p.B), p.ldb, n0, p.N, lane);
@@ -478,6 +495,18 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs p, int tiles_n, 
         C[(int64_t)m * p.ldc + n] = v;
       }
     }
+}
+
+// Four wavefronts per block, each a tile of its own (neighbours along n first: they share the rows of A).
+template <int TM, int TN, int D, bool BKC, F32Load L>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs p, int tiles_n, int tiles) {
+  const int nblk = gridDim.x - p.loss_blocks;
+  if ((int)blockIdx.x >= nblk) {
+    add_up_losses(p.loss + (blockIdx.x - nblk));
+    return;
+  }
+  const int id = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (id < tiles) gemm_f32_tile<TM, TN, D, BKC, L>(p, tiles_n, id);
 }
 
 // Per-shard weight gradients of an fp32 model: tile blockIdx.x, shard blockIdx.y (wgrad_kernel's WGRAD_STORE).  The
@@ -537,12 +566,39 @@ __global__ __launch_bounds__(256) void wgrad_f32_kernel(WgradArgs u, KSegments s
   wgrad_f32_tile<TM, TN, D>(u, seg, blockIdx.x, blockIdx.y, threadIdx.x, lds);
 }
 
+// The gradient of the pooled input (and the losses) in further blocks of the launch of the weight gradients: neither waits for the other.
+struct DgradF32 {
+  GemmArgs p;
+  int32_t tiles_n, tiles;   // of gemm_f32_tile, one per wavefront; 0: none
+  int32_t aligned;          // F32_ALIGNED, else F32_ANY
+};
+template <int GT, int GD>   // GT: 16 x 16 pieces of a wavefront's tile, each way; 0: no such blocks (their registers cost the others 8 - 15 us of 150 - 200)
+__device__ __forceinline__ void dgrad_f32_block(DgradF32 d, int block, int waves) {
+  const int id = block * waves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nblk = (d.tiles + waves - 1) / waves;
+  if (block >= nblk) {
+    if (block - nblk < d.p.loss_blocks) add_up_losses(d.p.loss + (block - nblk));
+    return;
+  }
+  if (id >= d.tiles) return;
+  if (d.aligned) gemm_f32_tile<GT, GT, GD, true, F32_ALIGNED>(d.p, d.tiles_n, id);
+  else gemm_f32_tile<GT, GT, GD, true, F32_ANY>(d.p, d.tiles_n, id);
+}
+
+template <int TM, int TN, int D, int GT, int GD>
+__global__ __launch_bounds__(256) void wgrad_dgrad_f32_kernel(WgradArgs u, KSegments seg, int tiles, DgradF32 d) {
+  __shared__ __attribute__((aligned(16))) WgradF32Lds<TM, TN> lds;
+  const int i = blockIdx.x;
+  if (i < tiles * seg.n) wgrad_f32_tile<TM, TN, D>(u, seg, i % tiles, i / tiles, threadIdx.x, lds);
+  else dgrad_f32_block<GT, GD>(d, i - tiles * seg.n, 4);
+}
+
 // The same with the sort of the coming aggregation beside it, a field to a block ahead of the others, which do four tiles each:
 // neither waits for the other, both leave most compute units idle, and one stream runs its launches one after the other
 // (1500 samples, 397-256-128, 12 fields of 9000 lookups: 15 + 23 us apart, 256 samples, 141-64-32, 8 fields of 640: 5 + 6; together 31 and 8).
-template <int TM, int TN, int D, int IT>
+template <int TM, int TN, int D, int IT, int GT, int GD>
 __global__ __launch_bounds__(SMALL_THREADS) void wgrad_f32_sort_kernel(WgradArgs u, KSegments seg, int tiles, SortBuffers sb, FieldPtr fp, int F,
-                                                                       int passes, int rb) {
+                                                                       int passes, int rb, DgradF32 d) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
   if ((int)blockIdx.x < F) {
     const int64_t base = fp.p[blockIdx.x];
@@ -550,7 +606,14 @@ __global__ __launch_bounds__(SMALL_THREADS) void wgrad_f32_sort_kernel(WgradArgs
                          sb.key[0] + base, sb.pay[0] + base, (int)(fp.p[blockIdx.x + 1] - base), passes, rb);
     return;
   }
-  const int sub = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8), i = ((int)blockIdx.x - F) * 4 + sub;
+  const int block = (int)blockIdx.x - F, wblocks = (tiles * seg.n + 3) / 4;
+  if constexpr (GT > 0) {
+    if (block >= wblocks) {
+      dgrad_f32_block<GT, GD>(d, block - wblocks, SMALL_THREADS / 64);
+      return;
+    }
+  }
+  const int sub = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8), i = block * 4 + sub;
   if (i < tiles * seg.n) {
     wgrad_f32_tile<TM, TN, D>(u, seg, i % tiles, i / tiles, threadIdx.x & 255, reinterpret_cast<WgradF32Lds<TM, TN>*>(lds)[sub]);
   } else {   // (the others' barriers)
@@ -610,12 +673,13 @@ hipError_t launch_bf16_sized(const GemmArgs& a, hipStream_t s) {
   return launch_bf16<1, 1, 2, 2, 64, 3, BS>(a, s);
 }
 
+bool f32_aligned(const void* x, int64_t ld) { return (ld & 3) == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0; }
+
 template <int TM, int TN, int D>
 hipError_t launch_f32_tile(const GemmArgs& a, hipStream_t s) {
   const int tiles_n = (a.N + 16 * TN - 1) / (16 * TN), tiles = (a.M + 16 * TM - 1) / (16 * TM) * tiles_n;
   const dim3 grid((tiles + 3) / 4 + a.loss_blocks), block(256);
-  auto aligned = [](const void* x, int64_t ld) { return (ld & 3) == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0; };
-  const F32Load load = aligned(a.A, a.lda) && (!a.b_kc || aligned(a.B, a.ldb)) ? F32_ALIGNED : a.K >= 4 ? F32_ANY : F32_SLOTS;
+  const F32Load load = f32_aligned(a.A, a.lda) && (!a.b_kc || f32_aligned(a.B, a.ldb)) ? F32_ALIGNED : a.K >= 4 ? F32_ANY : F32_SLOTS;
   auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, s, a, tiles_n, tiles); };
   if (load == F32_ALIGNED) a.b_kc ? launch(gemm_f32_kernel<TM, TN, D, true, F32_ALIGNED>) : launch(gemm_f32_kernel<TM, TN, D, false, F32_ALIGNED>);
   else if (load == F32_ANY) a.b_kc ? launch(gemm_f32_kernel<TM, TN, D, true, F32_ANY>) : launch(gemm_f32_kernel<TM, TN, D, false, F32_ANY>);
@@ -627,26 +691,29 @@ hipError_t launch_f32_tile(const GemmArgs& a, hipStream_t s) {
 // requests are the bound (six steps in flight instead of four: 12.3 -> 13.3 us).  A step, us, 16 x 16 / 32 x 32: input gradients
 // in 512 / 528 / 564 / 756 / 1536 tiles of 32 193 / 195, 99.8 / 96.2, 107 / 103, 107 / 103, 147 / 136; forward products in 752 / 768 / 1024
 // (256 columns) / 1024 (1001) tiles 122.7 / 124.2, 234.8 / 233.3, 136.0 / 134.3, 226 / 212.  Every tile shape adds up the products in the same order.
+bool f32_wide(const GemmArgs& a) { return (int64_t)((a.M + 31) / 32) * ((a.N + 31) / 32) > (a.b_kc ? 512 : 767); }
 hipError_t launch_f32(const GemmArgs& a, hipStream_t s) {
-  if ((int64_t)((a.M + 31) / 32) * ((a.N + 31) / 32) > (a.b_kc ? 512 : 767)) return launch_f32_tile<2, 2, 2>(a, s);
+  if (f32_wide(a)) return launch_f32_tile<2, 2, 2>(a, s);
   return launch_f32_tile<1, 1, 4>(a, s);
 }
 
-template <int TM, int TN, int D, int IT>
+template <int TM, int TN, int D, int IT, int GT, int GD>
 hipError_t launch_wgrad_f32_sort(const WgradArgs& u, const KSegments& seg, int tiles, const SortPlan& pl, const SortBuffers& sb, const FieldPtr& fp,
-                                 hipStream_t s) {
+                                 const DgradF32& d, hipStream_t s) {
   constexpr int sort_bytes = (int)sizeof(SmallSortLds) + SMALL_THREADS * IT * 4, tile_bytes = 4 * (int)sizeof(WgradF32Lds<TM, TN>);
-  constexpr int bytes = sort_bytes > tile_bytes ? sort_bytes : tile_bytes;
+  constexpr int bytes = sort_bytes > tile_bytes ? sort_bytes : tile_bytes, waves = SMALL_THREADS / 64;
   static std::atomic<uint64_t> allowed{0};
-  const hipError_t ok = allow_lds(wgrad_f32_sort_kernel<TM, TN, D, IT>, bytes, 0, allowed);
+  const hipError_t ok = allow_lds(wgrad_f32_sort_kernel<TM, TN, D, IT, GT, GD>, bytes, 0, allowed);
   if (ok != hipSuccess) return ok;
-  hipLaunchKernelGGL((wgrad_f32_sort_kernel<TM, TN, D, IT>), dim3(pl.F + (tiles * seg.n + 3) / 4), dim3(SMALL_THREADS), bytes, s, u, seg, tiles, sb, fp,
-                     pl.F, pl.passes, pl.radix_bits);
+  const int blocks = pl.F + (tiles * seg.n + 3) / 4 + (d.tiles + waves - 1) / waves + d.p.loss_blocks;
+  hipLaunchKernelGGL((wgrad_f32_sort_kernel<TM, TN, D, IT, GT, GD>), dim3(blocks), dim3(SMALL_THREADS), bytes, s, u, seg, tiles, sb, fp,
+                     pl.F, pl.passes, pl.radix_bits, d);
   return hipGetLastError();
 }
 
-template <int TM, int TN, int D>
-hipError_t launch_wgrad_f32_tile(const WgradArgs& a, const KSegments& seg, const SortPlan* pl, const SortBuffers* sb, const FieldPtr* fp, hipStream_t s) {
+template <int TM, int TN, int D, int GT, int GD>
+hipError_t launch_wgrad_f32_tile(const WgradArgs& a, const KSegments& seg, const SortPlan* pl, const SortBuffers* sb, const FieldPtr* fp,
+                                 const GemmArgs* dgrad, hipStream_t s) {
   WgradArgs u = a;
   u.tile_base[0] = 0;
   for (int l = 0; l < u.n_layers; ++l) {
@@ -654,16 +721,26 @@ hipError_t launch_wgrad_f32_tile(const WgradArgs& a, const KSegments& seg, const
     u.tile_base[l + 1] = u.tile_base[l] + (u.M[l] + 16 * TM - 1) / (16 * TM) * u.tiles_n[l];
   }
   const int tiles = u.tile_base[u.n_layers] + (u.width + 64) / 64;
+  DgradF32 d = {};
+  if constexpr (GT > 0) {
+    d.p = *dgrad;
+    d.tiles_n = (d.p.N + 16 * GT - 1) / (16 * GT);
+    d.tiles = (d.p.M + 16 * GT - 1) / (16 * GT) * d.tiles_n;
+    d.aligned = f32_aligned(d.p.A, d.p.lda) && f32_aligned(d.p.B, d.p.ldb);
+  }
   if (pl) {
     switch (small_sort_items(pl->F, *fp)) {
-      case 2: return launch_wgrad_f32_sort<TM, TN, D, 2>(u, seg, tiles, *pl, *sb, *fp, s);
-      case 4: return launch_wgrad_f32_sort<TM, TN, D, 4>(u, seg, tiles, *pl, *sb, *fp, s);
-      case 8: return launch_wgrad_f32_sort<TM, TN, D, 8>(u, seg, tiles, *pl, *sb, *fp, s);
-      case 16: return launch_wgrad_f32_sort<TM, TN, D, 16>(u, seg, tiles, *pl, *sb, *fp, s);
+      case 2: return launch_wgrad_f32_sort<TM, TN, D, 2, GT, GD>(u, seg, tiles, *pl, *sb, *fp, d, s);
+      case 4: return launch_wgrad_f32_sort<TM, TN, D, 4, GT, GD>(u, seg, tiles, *pl, *sb, *fp, d, s);
+      case 8: return launch_wgrad_f32_sort<TM, TN, D, 8, GT, GD>(u, seg, tiles, *pl, *sb, *fp, d, s);
+      case 16: return launch_wgrad_f32_sort<TM, TN, D, 16, GT, GD>(u, seg, tiles, *pl, *sb, *fp, d, s);
       default: return hipErrorInvalidValue;
     }
   }
-  hipLaunchKernelGGL((wgrad_f32_kernel<TM, TN, D>), dim3(tiles, seg.n), dim3(256), 0, s, u, seg);
+  if constexpr (GT > 0)
+    hipLaunchKernelGGL((wgrad_dgrad_f32_kernel<TM, TN, D, GT, GD>), dim3(tiles * seg.n + (d.tiles + 3) / 4 + d.p.loss_blocks), dim3(256), 0, s, u, seg, tiles, d);
+  else
+    hipLaunchKernelGGL((wgrad_f32_kernel<TM, TN, D>), dim3(tiles, seg.n), dim3(256), 0, s, u, seg);
   return hipGetLastError();
 }
 
@@ -674,9 +751,17 @@ int64_t wgrad_f32_tiles(const WgradArgs& a, int size) {   // of `size` rows and 
 }
 bool wgrad_f32_wide(const WgradArgs& a, int ranges) { return wgrad_f32_tiles(a, 32) * ranges >= 512; }
 
-hipError_t launch_wgrad_f32(const WgradArgs& a, const KSegments& seg, const SortPlan* pl, const SortBuffers* sb, const FieldPtr* fp, hipStream_t s) {
-  if (wgrad_f32_wide(a, seg.n)) return launch_wgrad_f32_tile<2, 2, 2>(a, seg, pl, sb, fp, s);
-  return launch_wgrad_f32_tile<1, 1, 4>(a, seg, pl, sb, fp, s);
+hipError_t launch_wgrad_f32(const WgradArgs& a, const KSegments& seg, const SortPlan* pl, const SortBuffers* sb, const FieldPtr* fp, const GemmArgs* dgrad,
+                            hipStream_t s) {
+  auto tiles = [&](auto gt, auto gd) {
+    constexpr int GT = decltype(gt)::value, GD = decltype(gd)::value;
+    if (wgrad_f32_wide(a, seg.n)) return launch_wgrad_f32_tile<2, 2, 2, GT, GD>(a, seg, pl, sb, fp, dgrad, s);
+    return launch_wgrad_f32_tile<1, 1, 4, GT, GD>(a, seg, pl, sb, fp, dgrad, s);
+  };
+  typedef std::integral_constant<int, 0> None;
+  if (!dgrad) return tiles(None(), None());
+  if (f32_wide(*dgrad)) return tiles(std::integral_constant<int, 2>(), std::integral_constant<int, 2>());
+  return tiles(std::integral_constant<int, 1>(), std::integral_constant<int, 4>());
 }
 
 template <int TM, int TN, int WR, int WC, int BK, int STAGES, WgradMode MODE, bool FAR = false>
@@ -696,21 +781,49 @@ hipError_t launch_wgrad_tile(const WgradArgs& a, const KSegments& seg, int group
   return hipGetLastError();
 }
 
+bool wgrad_far(const WgradArgs& a) {   // 64 samples of a tile beyond 32-bit offsets
+  for (int l = 0; l < a.n_layers; ++l)
+    if ((int64_t)std::max(a.lda[l], a.ldb[l]) * (64 * 2) >> 32) return true;
+  return false;
+}
+// Every block walks all samples, so a large tile means few operand bytes per output but also few blocks.
+// Measured alone (us; tiles of 128 x 128 with eight wavefronts / 64 x 64): 6400-1024-512 model, 16384 samples,
+// one range (432 large tiles) 320 / 509; 3840-1024-512, 2501 samples, 16 ranges (272) 128 / 83;
+// 845-1024-512-256, 4096 samples, one range (96) 61 / 39; 15625 samples, 8 ranges 269 / 167.
+bool wgrad_large_tiles(const WgradArgs& a, int groups) {
+  int n = 0;
+  for (int l = 0; l < a.n_layers; ++l) n += ((a.M[l] + 127) / 128) * ((a.N[l] + 127) / 128);
+  return n * groups >= 400;
+}
+
 template <WgradMode MODE>
 hipError_t launch_wgrad_sized(const WgradArgs& a, const KSegments& seg, int groups, hipStream_t s) {
-  auto blocks_of = [&](int bm, int bn) {
-    int n = 0;
-    for (int l = 0; l < a.n_layers; ++l) n += ((a.M[l] + bm - 1) / bm) * ((a.N[l] + bn - 1) / bn);
-    return n * groups;
-  };
-  for (int l = 0; l < a.n_layers; ++l)   // 64 samples of a tile beyond 32-bit offsets
-    if ((int64_t)std::max(a.lda[l], a.ldb[l]) * (64 * 2) >> 32) return launch_wgrad_tile<1, 1, 2, 2, 64, 3, MODE, true>(a, seg, groups, s);
-  // Every block walks all samples, so a large tile means few operand bytes per output but also few blocks.
-  // Measured alone (us; tiles of 128 x 128 with eight wavefronts / 64 x 64): 6400-1024-512 model, 16384 samples,
-  // one range (432 large tiles) 320 / 509; 3840-1024-512, 2501 samples, 16 ranges (272) 128 / 83;
-  // 845-1024-512-256, 4096 samples, one range (96) 61 / 39; 15625 samples, 8 ranges 269 / 167.
-  if (blocks_of(128, 128) >= 400) return launch_wgrad_tile<2, 1, 2, 4, 64, 2, MODE>(a, seg, groups, s);
+  if (wgrad_far(a)) return launch_wgrad_tile<1, 1, 2, 2, 64, 3, MODE, true>(a, seg, groups, s);
+  if (wgrad_large_tiles(a, groups)) return launch_wgrad_tile<2, 1, 2, 4, 64, 2, MODE>(a, seg, groups, s);
   return launch_wgrad_tile<1, 1, 2, 2, 64, 3, MODE>(a, seg, groups, s);
+}
+
+template <int TM, int TN, int WR, int WC, int BK, int STAGES>
+hipError_t launch_wgrad_dgrad_tile(const WgradArgs& a, const KSegments& seg, const GemmArgs& g, hipStream_t s) {
+  typedef BlockProduct<1, 1, 2, 2, 64, 3, true, true> PW;
+  typedef BlockProduct<TM, TN, WR, WC, BK, STAGES, false, false, false, 4> PG;
+  static_assert(PW::THREADS == 256 && PG::THREADS == 256, "blocks of one launch");
+  constexpr int bytes = std::max(PW::LDS_BYTES, PG::LDS_BYTES);
+  static std::atomic<uint64_t> allowed{0};
+  const hipError_t ok = allow_lds(wgrad_dgrad_kernel<TM, TN, WR, WC, BK, STAGES>, bytes, 0, allowed);
+  if (ok != hipSuccess) return ok;
+  WgradArgs u = a;
+  u.tile_base[0] = 0;
+  for (int l = 0; l < u.n_layers; ++l) {
+    u.tiles_n[l] = (u.N[l] + PW::BN - 1) / PW::BN;
+    u.tile_base[l + 1] = u.tile_base[l] + ((u.M[l] + PW::BM - 1) / PW::BM) * u.tiles_n[l];
+  }
+  const int tiles = u.tile_base[u.n_layers] + (u.width + 64) / 64;
+  const int tiles_m = (g.M + PG::BM - 1) / PG::BM, tiles_n = (g.N + PG::BN - 1) / PG::BN;
+  const bool m_minor = g.M < g.N;
+  hipLaunchKernelGGL((wgrad_dgrad_kernel<TM, TN, WR, WC, BK, STAGES>), dim3(tiles * seg.n + tiles_m * tiles_n + g.loss_blocks), dim3(256), bytes, s,
+                     u, seg, tiles, g, m_minor ? tiles_m : tiles_n, m_minor);
+  return hipGetLastError();
 }
 
 }  // namespace
@@ -725,7 +838,7 @@ hipError_t launch_wgrad(const WgradArgs& a, const KSegments& seg, bool store, hi
   if (store && seg.n <= 0) return hipSuccess;
   for (int l = 0; l < a.n_layers; ++l)
     if (a.M[l] <= 0 || a.N[l] <= 0 || (a.bf16 && (a.N[l] & 7))) return hipErrorInvalidValue;
-  if (!a.bf16) return store ? launch_wgrad_f32(a, seg, nullptr, nullptr, nullptr, s) : hipErrorInvalidValue;
+  if (!a.bf16) return store ? launch_wgrad_f32(a, seg, nullptr, nullptr, nullptr, nullptr, s) : hipErrorInvalidValue;
   if (store) return launch_wgrad_sized<WGRAD_STORE>(a, seg, seg.n, s);
   return seg.n == 1 ? launch_wgrad_sized<WGRAD_ONE>(a, seg, 1, s) : launch_wgrad_sized<WGRAD_MANY>(a, seg, 1, s);
 }
@@ -745,11 +858,43 @@ bool wgrad_takes_sort(const WgradArgs& a, int ranges, int64_t samples, int F, co
   return tiles <= 1280 * saved && work <= 100000 * saved * (tiles >= 2048 ? 4 : 3) / 3;
 }
 
-hipError_t launch_wgrad_and_sort(const WgradArgs& a, const KSegments& seg, const SortPlan& pl, const SortBuffers& sb, const FieldPtr& fp, hipStream_t s) {
+hipError_t launch_wgrad_and_sort(const WgradArgs& a, const KSegments& seg, const SortPlan& pl, const SortBuffers& sb, const FieldPtr& fp,
+                                 const GemmArgs* dgrad, hipStream_t s) {
   for (int l = 0; l < a.n_layers; ++l)
     if (a.M[l] <= 0 || a.N[l] <= 0) return hipErrorInvalidValue;
   if (a.bf16 || seg.n <= 0) return hipErrorInvalidValue;
-  return launch_wgrad_f32(a, seg, &pl, &sb, &fp, s);
+  return launch_wgrad_f32(a, seg, &pl, &sb, &fp, dgrad, s);
+}
+
+// One launch for both (us, apart / together; a worker step whose weight gradients belong to it): bf16, 1024-512-256, on 8 / 64 / 500 / 1531 / 3072 samples
+// 43.2 / 39.4, 44.4 / 39.4, 51.4 / 43.9, 69.6 / 64.2, 126 / 121.  fp32, a whole step: 4096 / 16384 samples of 845-1024-512-256 692 / 675, 2228 / 2142;
+// 4096 of 653-256-128 192 / 182; not where small tiles of the one, which want many wavefronts, would wait behind thousands of wide blocks of the other
+// (512 of 845-1024-512-256 198 / 212).  In the launch that has the sort, blocks of 1024 threads with the sort's LDS and registers, only where all find a
+// place at once, one or (small tiles, up to eight lookups a thread) two to a compute unit: 256 samples of 141-64-32 47.8 / 45.7, 1500 of 397-256-128
+// 101.4 / 97.9, 1024 of 525-64-32 67.7 / 65.2; beyond it 4096 of 653-256-128 in eight shards 153 / 161.
+bool wgrad_takes_dgrad(const WgradArgs& a, int ranges, const GemmArgs& g, int F, const FieldPtr* sorted) {
+  if (ranges <= 0 || g.M <= 0 || g.N <= 0 || !g.b_kc) return false;
+  if (a.bf16) {
+    if (!g.bf16_in || sorted || wgrad_far(a) || wgrad_large_tiles(a, ranges) || std::max(g.lda, g.ldb) * (256 * 2) >> 32) return false;
+    return (int64_t)((g.M + 127) / 128) * ((g.N + 127) / 128) < 200;   // (see launch_bf16_sized: else tiles of other blocks)
+  }
+  if (g.bf16_in || g.K < 4) return false;
+  const bool wide = f32_wide(g), wgrad_wide = wgrad_f32_wide(a, ranges);
+  const int size = wide ? 32 : 16;
+  const int64_t tiles = (wgrad_f32_tiles(a, wgrad_wide ? 32 : 16) + (a.width + 64) / 64) * ranges;
+  const int64_t dtiles = (int64_t)((g.M + size - 1) / size) * ((g.N + size - 1) / size);
+  if (!sorted) return wide || !wgrad_wide || tiles + dtiles / 4 <= 1024;
+  const int64_t blocks = F + (tiles + 3) / 4 + (dtiles + 15) / 16 + g.loss_blocks;
+  return blocks <= (wide || wgrad_wide || small_sort_items(F, *sorted) > 8 ? 256 : 512);
+}
+
+hipError_t launch_wgrad_and_dgrad(const WgradArgs& a, const KSegments& seg, const GemmArgs& g, hipStream_t s) {
+  for (int l = 0; l < a.n_layers; ++l)
+    if (a.M[l] <= 0 || a.N[l] <= 0 || (a.bf16 && (a.N[l] & 7))) return hipErrorInvalidValue;
+  if (!wgrad_takes_dgrad(a, seg.n, g, 0, nullptr)) return hipErrorInvalidValue;
+  if (!a.bf16) return launch_wgrad_f32(a, seg, nullptr, nullptr, nullptr, &g, s);
+  if ((int64_t)((g.M + 31) / 32) * ((g.N + 31) / 32) <= 256) return launch_wgrad_dgrad_tile<1, 1, 1, 1, 128, 3>(a, seg, g, s);
+  return launch_wgrad_dgrad_tile<1, 1, 2, 2, 64, 3>(a, seg, g, s);
 }
 
 hipError_t launch_cast_bf16(const CastArgs& a, hipStream_t s) {

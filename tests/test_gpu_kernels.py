@@ -582,3 +582,34 @@ def test_order_of_a_logit(gemm, width, hidden):
     z = chains[:, 0] + bias
     assert np.all(z >= 32)
     assert np.array_equal(loss.cpu().numpy() * np.array(sizes, np.float32), z)
+
+
+# The gradient of the pooled input beside the weight gradients: the bits of a launch of its own (made while a class is timed), for fp32
+# tiles of 16 and of 32 rows and columns of both products, rows at any place and too short for that (a launch of its own either way), and bf16
+# tiles of 32 and of 64, and from 200 tiles of 128 on (its own); an empty shard, remainders of tiles and of blocks.
+@pytest.mark.parametrize("gemm,sizes,hidden,num_dense", [("f32", (90, 1, 0, 200, 9, 50), (264, 136), 3), ("f32", (17,), (40, 24), 0),
+                                                         ("f32", (1500, 40), (101,), 5), ("f32", (33, 31), (3,), 1), ("f32", (4100,), (72, 40), 2), ("f32", (900,) * 4, (256, 128), 7),
+                                                         ("bf16", (5, 0, 60), (264, 72), 13), ("bf16", (700, 9), (264, 72), 0),
+                                                         ("bf16", (3300, 0, 4100), (136,), 13)])
+def test_input_gradient_beside_the_weight_gradients(gemm, sizes, hidden, num_dense):
+    import torch
+    from gpu_helpers import GpuRun
+    from test_gpu_parity import make_inputs
+    cfg = _config(f"joined-{gemm}-{sum(sizes)}", 790, num_fields=12, dim=32, layer_sizes=hidden, num_dense=num_dense, gemm_dtype=gemm, shard_sizes=sizes,
+                  table_dtype="f32")
+    tables, state, flat, fstate, batch = make_inputs(cfg)
+    out = []
+    for mode in (0, 1):
+        run = GpuRun(cfg, tables, flat, state, fstate, streams=False, eager=True)
+        run.ctx.profile(mode)
+        run.set_batch(batch)
+        run.ctx.assign_shard(sum(sizes), len(sizes), sizes=sizes)
+        loss = torch.full((len(sizes),), -1.0, device="cuda:0")
+        run.ctx.worker_step_all(loss)
+        torch.cuda.synchronize()
+        views = [t.cpu().numpy().copy() for k in range(len(sizes)) for t in run.ctx.view_shard_grads(k)]
+        out.append([loss.cpu().numpy()] + views)
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
+    if gemm == "f32":
+        check_iteration(cfg, cfg.shard_sizes, tol=TOL32, batched=True)
