@@ -325,7 +325,18 @@ hipError_t launch_segments(const SegArgs& a, const FieldPtr& fp, const TileBase&
 hipError_t launch_mask_pack(const int32_t* ids, const int32_t* lookup_sample, const int32_t* offsets, int64_t B, int F,
                             const FieldPtr& fp, const ShardTab& tab, int64_t* cbase, int32_t* ids_out,
                             int32_t* pay_out, hipStream_t s);
-hipError_t launch_seg_reduce(const SegArgs& a, const FieldPtr& fp, const TileBase& tb, const ShardTab& tab, Profiler* prof, hipStream_t s);
+// The dense update of an fp32 model in further blocks of that launch (of the one over the windows): n parameters, K rows of gradients.
+struct DenseJob {
+  float* p;
+  float* state;
+  const float* grads;              // [K, stride]
+  int64_t stride, n;               // n = 0: none
+  float lr, eps;
+  int32_t K;
+  float w[ANTDT_MAX_SHARDS];
+};
+hipError_t launch_seg_reduce(const SegArgs& a, const FieldPtr& fp, const TileBase& tb, const ShardTab& tab, const DenseJob& dense, Profiler* prof,
+                             hipStream_t s);
 
 // ---------------------------------------------------------------- optim.hip
 struct DenseAggArgs {

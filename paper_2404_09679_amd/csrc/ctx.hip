@@ -1241,11 +1241,19 @@ int antdt_apply_update(antdt_ctx* c, void* stream) {
     HIP_TRY(c, hipEventRecord(c->ev_dh[c->L], s));  // everything enqueued on `s` so far (loss, last layer's gradient)
     HIP_TRY(c, hipStreamWaitEvent(ds, c->ev_dh[c->L], 0));
   }
+  // Of an fp32 model the dense update (see dense_update) is a few blocks more of the sparse one's launch, unless nothing was looked up
+  // or the two are timed apart.
+  DenseJob dense = {};
+  if (!c->act_bf16 && c->atotal_tiles > 0 && !prof_apart(pr, KID_SPARSE_ADAGRAD, KID_DENSE_ADAGRAD)) {
+    dense.p = c->params; dense.state = c->pstate; dense.grads = c->shard_grads; dense.stride = c->Pstride; dense.n = c->P;
+    dense.lr = c->m.lr; dense.eps = c->m.eps; dense.K = c->tab.K;
+    memcpy(dense.w, c->tab.w, sizeof(dense.w));
+  }
   {  // weighted run sums with the Adagrad step of every touched row applied on the spot
     SegArgs a;
     fill_seg_args(c, a);
     a.update = 1;
-    HIP_TRY(c, launch_seg_reduce(a, c->afp, c->atb, c->tab, pr, s));
+    HIP_TRY(c, launch_seg_reduce(a, c->afp, c->atb, c->tab, dense, pr, s));
   }
   if (c->wgrad_deferred) {
     // Weight gradients, their aggregation over the shards and the dense update in one kernel
@@ -1307,7 +1315,7 @@ int antdt_apply_update(antdt_ctx* c, void* stream) {
       HIP_TRY(c, hipStreamWaitEvent(s, c->ev_wgrad, 0));
     }
     c->wgrad_pending = false;  // `s` now waits for everything on that stream
-  } else {
+  } else if (dense.n == 0) {
     const int rc = dense_update(c, c->tab, c->wb[0], ds);
     if (rc) return rc;
     if (ds != s) {
@@ -1424,7 +1432,7 @@ int antdt_view_coalesced(antdt_ctx* c, int32_t f, const int32_t** unique_ids, co
     fill_seg_args(c, a);
     a.update = 0;
     HIP_TRY(c, launch_segments(a, c->afp, c->atb, prof_of(c), (hipStream_t)stream));
-    HIP_TRY(c, launch_seg_reduce(a, c->afp, c->atb, c->tab, prof_of(c), (hipStream_t)stream));
+    HIP_TRY(c, launch_seg_reduce(a, c->afp, c->atb, c->tab, DenseJob{}, prof_of(c), (hipStream_t)stream));
     c->g_valid = true;
   }
   int32_t ub[2];

@@ -1,46 +1,18 @@
 // Server-side dense aggregation and the parameter updates (Section II: the servers
 // combine the workers' gradients, then update the parameters).
 // All of these stream through memory once: they are bound by HBM bandwidth.
-#include "common.h"
+#include "dense.h"
 
 namespace antdt {
 namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ float weighted_sum(const float* grads, int64_t stride, int64_t i, const ShardTab& tab) {
-  // Every load is issued (a branch per load would serialise them); the value of a shard
-  // with weight 0, which may never have been written, is replaced by 0 afterwards.
-  float acc = 0.0f;
-  int k = 0;
-  for (; k + 3 < tab.K; k += 4) {  // four loads in flight, added in shard order
-    float x[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) x[q] = grads[(int64_t)(k + q) * stride + i];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) acc = fmaf(tab.w[k + q], tab.w[k + q] != 0.0f ? x[q] : 0.0f, acc);
-  }
-  for (; k < tab.K; ++k) {
-    const float x = grads[(int64_t)k * stride + i];
-    acc = fmaf(tab.w[k], tab.w[k] != 0.0f ? x : 0.0f, acc);
-  }
-  return acc;
-}
-
 // g[i] = sum_k w_k * grads[k][i], shards added in index order.
 __global__ __launch_bounds__(256) void dense_agg_kernel(DenseAggArgs a, ShardTab tab) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < a.P; i += stride)
     a.g[i] = weighted_sum(a.grads, a.stride, i, tab);
-}
-
-__device__ __forceinline__ float adagrad_elem(const DenseAdagradArgs& a, const ShardTab& tab, int64_t i) {
-  const float g = weighted_sum(a.grads, a.stride, i, tab);
-  const float s1 = fmaf(g, g, a.state[i]);
-  const float p1 = a.p[i] - a.lr * g / (sqrtf(s1) + a.eps);
-  a.state[i] = s1;
-  a.p[i] = p1;
-  return p1;
 }
 
 __global__ __launch_bounds__(256) void dense_adagrad_kernel(DenseAdagradArgs a, ShardTab tab) {

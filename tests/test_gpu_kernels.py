@@ -613,3 +613,38 @@ def test_input_gradient_beside_the_weight_gradients(gemm, sizes, hidden, num_den
         assert np.array_equal(a, b)
     if gemm == "f32":
         check_iteration(cfg, cfg.shard_sizes, tol=TOL32, batched=True)
+
+
+# The dense update of an fp32 model in blocks of the sparse update's launch: the bits of a launch of its own (made while a class is timed), for
+# windows of 256 lookups and of whole fields, fewer parameters than a block and more than many, a shard left out that never stepped, and no
+# lookups at all (a launch of its own either way).
+@pytest.mark.parametrize("hidden,fields,max_bag,mask", [((), 1, 1, None), ((40, 24), 3, 3, (1, 0, 1)), ((40, 24), 2, 90, None), ((264, 136), 12, 30, (1, 0, 1)),
+                                                        ((72,), 3, 0, None)])
+def test_dense_update_beside_the_sparse_one(hidden, fields, max_bag, mask):
+    import torch
+    from gpu_helpers import GpuRun
+    from test_gpu_parity import make_inputs
+    sizes = (70, 33, 6)
+    cfg = _config(f"dense-{max_bag}", 800, num_fields=fields, layer_sizes=hidden, gemm_dtype="f32", shard_sizes=sizes, max_bag=max(max_bag, 1),
+                  min_bag=0 if max_bag == 0 else 1)
+    tables, state, flat, fstate, batch = make_inputs(cfg, True)
+    if max_bag == 0:
+        batch = dataclasses.replace(batch, ids=np.zeros(0, np.int32), offsets=np.zeros((fields, sum(sizes) + 1), np.int32),
+                                    field_ptr=np.zeros(fields + 1, np.int64))
+    out = []
+    for mode in (0, 1):
+        run = GpuRun(cfg, tables, flat, state, fstate)
+        run.ctx.profile(mode)
+        run.set_batch(batch)
+        run.ctx.assign_shard(sum(sizes), len(sizes), sizes=sizes)
+        loss = torch.zeros(len(sizes), device="cuda:0")
+        for k in range(len(sizes)):
+            if mask is None or mask[k]:
+                run.ctx.worker_step(k, loss[k:k + 1])
+        run.ctx.aggregate(mask)
+        run.ctx.apply_update()
+        torch.cuda.synchronize()
+        out.append([t.cpu().numpy() for t in (run.params, run.pstate, run.tables, run.state, loss)])
+    assert not np.array_equal(out[0][0], flat)
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
