@@ -51,16 +51,166 @@ __device__ __forceinline__ bool tile_of_block(const TileBase& tb, int F, int par
 }
 
 // ----------------------------------------------------------------- sort
+// The sort by buckets (see sort_buckets_kernel): a field's rows are cut into ranges of about as many lookups each, one pass over many
+// blocks puts the lookups into them, and a block each sorts them in LDS.
+constexpr int BUCKET_THREADS = 512, BUCKET_WAVES = BUCKET_THREADS / 64, BUCKET_ITEMS = 16, BUCKET_KEYS = BUCKET_THREADS * BUCKET_ITEMS;
+constexpr int BUCKET_BITS = 8;                     // of a pass inside a bucket, at most; a bucket has up to 2^16 rows
+constexpr int MAX_BUCKETS = 256, BUCKET_CELLS = 256;
+struct FieldBuckets {
+  int32_t first[MAX_BUCKETS + 4];                  // first row of each bucket (one without rows: the number of rows)
+  uint16_t cell[BUCKET_CELLS];                     // buckets of the first and the last row (high half) of an equal part of the rows
+};
+struct BucketPlan {
+  int32_t rb;           // log2 of the number of buckets of a field
+  int32_t range_bits;   // log2 of the most rows of a bucket; range_bits + sample_bits <= 32
+  int32_t sample_bits;
+  int32_t cell_bits;    // log2 of the rows of a cell
+  int32_t last_row;
+  FieldBuckets* fields;
+  int32_t* large;       // [0]: number of buckets of more than BUCKET_KEYS lookups and one row, then those (field, bucket)
+  // (ids that are no rows go where the update takes them to be: the first row, the last one)
+  __device__ __forceinline__ int32_t in_range(int32_t key) const { return min(max(key, 0), last_row); }
+  __device__ __forceinline__ uint32_t bucket(const FieldBuckets& fb, int32_t key) const {
+    const uint32_t c = fb.cell[key >> cell_bits];
+    uint32_t lo = c & 0xFF, hi = c >> 8;
+    while (lo < hi) {
+      const uint32_t mid = (lo + hi + 1) >> 1;
+      if (fb.first[mid] <= key) lo = mid;
+      else hi = mid - 1;
+    }
+    return lo;
+  }
+};
+template <int THREADS>
+__device__ __forceinline__ void load_buckets(FieldBuckets& to, const FieldBuckets& from) {
+  constexpr int WORDS = sizeof(FieldBuckets) / 4;
+  for (int i = threadIdx.x; i < WORDS; i += THREADS) reinterpret_cast<uint32_t*>(&to)[i] = reinterpret_cast<const uint32_t*>(&from)[i];
+}
+
+// The threads' values (x: a word each) in ascending order, by the first N threads; steps within a wavefront need no memory.
+template <int N>
+__device__ __forceinline__ int32_t bitonic_sort(int32_t v, int32_t* x) {
+  const int i = threadIdx.x;
+#pragma unroll
+  for (int k = 2; k <= N; k <<= 1)
+#pragma unroll
+    for (int j = k >> 1; j > 0; j >>= 1) {
+      int32_t o;
+      if (j >= 64) {
+        if (i < N) x[i] = v;
+        __syncthreads();
+        o = i < N ? x[i ^ j] : v;
+        __syncthreads();
+      } else {
+        o = __shfl_xor(v, j, 64);
+      }
+      v = ((i & j) == 0) == ((i & k) == 0) ? min(v, o) : max(v, o);
+    }
+  if (i < N) x[i] = v;
+  __syncthreads();
+  return v;
+}
+// Sum of the values of the threads before this one (wsum: a word per wavefront), and of all.
+__device__ __forceinline__ uint32_t block_prefix(uint32_t x, uint32_t* wsum, int waves, uint32_t& all, bool again = true) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const uint32_t incl = wave_prefix(x);
+  if (lane == 63) wsum[w] = incl;
+  __syncthreads();
+  uint32_t before = 0;
+  all = 0;
+  for (int q = 0; q < waves; ++q) {
+    const uint32_t c = wsum[q];
+    before += q < w ? c : 0;
+    all += c;
+  }
+  if (again) __syncthreads();   // (another one may follow)
+  return before + incl - x;
+}
+
+// Cuts a field's rows into buckets, by SAMPLE_KEYS of its lookups: a row that seems to have half of BUCKET_KEYS lookups or more is a bucket by
+// itself (they are in order once they are together), the others are cut where equal shares of their lookups end, and every 2^range_bits rows.
+// (Which cuts are made changes no result.)
+constexpr int SAMPLE_KEYS = 1024, HOT_KEYS = 4;
+__global__ __launch_bounds__(SAMPLE_KEYS) void sort_cuts_kernel(const int32_t* keys, FieldPtr fp, BucketPlan bp) {
+  __shared__ int32_t key[SAMPLE_KEYS], cut[SAMPLE_KEYS];
+  __shared__ uint8_t hot[SAMPLE_KEYS];
+  __shared__ uint32_t wsum[SAMPLE_KEYS / 64];
+  __shared__ FieldBuckets fb;
+  const int f = blockIdx.x, i = threadIdx.x;
+  if (f == 0 && i == 0) bp.large[0] = 0;
+  const int64_t n = fp.p[f + 1] - fp.p[f];
+  if (n == 0) return;
+  const int32_t k = bitonic_sort<SAMPLE_KEYS>(bp.in_range(keys[fp.p[f] + n * i / SAMPLE_KEYS]), key);
+  auto bound = [&](int32_t v) {   // sampled keys below v
+    int lo = 0, hi = SAMPLE_KEYS;
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (key[mid] < v) lo = mid + 1;
+      else hi = mid;
+    }
+    return lo;
+  };
+  const int head = bound(k), many = 1 << bp.rb, fixed = (bp.last_row >> bp.range_bits) + 1;
+  uint32_t all, hots;
+  const int hot_keys = min((int)((int64_t)SAMPLE_KEYS * (BUCKET_KEYS / 2) / n) + HOT_KEYS, SAMPLE_KEYS);
+  const bool is_hot = head == i && i + hot_keys <= SAMPLE_KEYS && key[i + hot_keys - 1] == k;
+  const uint32_t hot_place = block_prefix(is_hot, wsum, SAMPLE_KEYS / 64, hots);
+  const uint32_t most_hot = (uint32_t)(many - fixed) / 4;
+  hot[i] = is_hot && hot_place < most_hot;
+  hots = min(hots, most_hot);
+  __syncthreads();
+  const bool cold = !hot[head];
+  const uint32_t cold_place = block_prefix(cold, wsum, SAMPLE_KEYS / 64, all);
+  const int cuts = many - fixed - 2 * (int)hots;                 // (at least half of those that are not fixed)
+  const int step = max(((int)all + cuts - 1) / cuts, 1);
+  cut[i] = 0x7FFFFFFF;
+  __syncthreads();
+  const bool quantile = cold && cold_place % (uint32_t)step == 0;
+  if (i < fixed) cut[i] = i << bp.range_bits;
+  if (hot[i]) {
+    cut[fixed + 2 * (int)hot_place] = k;
+    cut[fixed + 2 * (int)hot_place + 1] = k + 1;
+  }
+  if (quantile) cut[fixed + 2 * (int)hots + (int)(cold_place / (uint32_t)step)] = k;
+  __syncthreads();
+  bitonic_sort<MAX_BUCKETS>(i < MAX_BUCKETS ? cut[i] : 0, cut);   // (no more than `many` of them)
+  const int rows = bp.last_row + 1;
+  const bool first = i < many && cut[i] < rows && (i == 0 || cut[i] != cut[i - 1]);
+  const uint32_t place = block_prefix(first, wsum, SAMPLE_KEYS / 64, all);
+  if (i < MAX_BUCKETS + 4) fb.first[i] = rows;
+  __syncthreads();
+  if (first) fb.first[place] = cut[i];
+  __syncthreads();
+  auto last_at = [&](int32_t row) {   // the bucket of a row
+    int lo = 0, hi = (int)all - 1;
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (fb.first[mid] <= row) lo = mid;
+      else hi = mid - 1;
+    }
+    return lo;
+  };
+  if (i < BUCKET_CELLS) {
+    const int64_t r0 = (int64_t)i << bp.cell_bits, r1 = r0 + (1 << bp.cell_bits) - 1;
+    fb.cell[i] = (uint16_t)(last_at((int32_t)min(r0, (int64_t)bp.last_row)) | last_at((int32_t)min(r1, (int64_t)bp.last_row)) << 8);
+  }
+  __syncthreads();
+  load_buckets<SAMPLE_KEYS>(bp.fields[f], fb);
+}
+
 // Histogram layout: hist[(tile_base[f] + tile) << rb | digit] (digits of a tile contiguous);
 // digit_total[f << rb | digit] = number of the field's keys with the digit.
 
 // Digit histogram of one tile.  Hot rows make many lanes count one digit, and LDS adds to one address go one after
 // the other: every digit has copies of its counter, and the lanes take turns with them (42 M lookups of 21 bits: 60 / 102 / 121
 // us a pass with one counter, the keys more and more in order; 54 with eight, the blocks' loads and their latency).
+// BUCKETS: their numbers are the digits.
+template <bool BUCKETS>
 __global__ __launch_bounds__(SORT_THREADS) void sort_hist_kernel(const int32_t* keys, uint32_t* hist,
-                                                                 FieldPtr fp, TileBase tb, int F, int shift, int rb) {
+                                                                 FieldPtr fp, TileBase tb, int F, int shift, int rb, BucketPlan bp) {
   constexpr int LOG_COUNTERS = 12, LOG_COPIES = 3;
   __shared__ uint32_t h[1 << LOG_COUNTERS];
+  __shared__ typename std::conditional<BUCKETS, FieldBuckets, int>::type fb;
   int f, t, part;
   if (!tile_of_block(tb, F, 1, f, t, part)) return;
   const int nb = 1 << rb;
@@ -72,11 +222,20 @@ __global__ __launch_bounds__(SORT_THREADS) void sort_hist_kernel(const int32_t* 
 #pragma unroll
   for (int i = 0; i < SORT_ITEMS; ++i) k[i] = in[min(i * SORT_THREADS + (int)threadIdx.x, count - 1)];   // (all loads first)
   for (int d = threadIdx.x; d < nb << cb; d += SORT_THREADS) h[d] = 0;
+  if constexpr (BUCKETS) load_buckets<SORT_THREADS>(fb, bp.fields[f]);
   __syncthreads();
   const int copy = threadIdx.x & ((1 << cb) - 1);
 #pragma unroll
   for (int i = 0; i < SORT_ITEMS; ++i)
-    if (i * SORT_THREADS + (int)threadIdx.x < count) atomicAdd(&h[((((uint32_t)k[i] >> shift) & (nb - 1)) << cb) + copy], 1u);
+    if (i * SORT_THREADS + (int)threadIdx.x < count) {
+      uint32_t d;
+      if constexpr (BUCKETS) {
+        d = bp.bucket(fb, bp.in_range(k[i]));
+      } else {
+        d = ((uint32_t)k[i] >> shift) & (nb - 1);
+      }
+      atomicAdd(&h[(d << cb) + copy], 1u);
+    }
   __syncthreads();
   uint32_t* out = hist + ((int64_t)(tb.t[f] + t) << rb);
   for (int d = threadIdx.x; d < nb; d += SORT_THREADS) {
@@ -92,7 +251,8 @@ __global__ __launch_bounds__(SORT_THREADS) void sort_hist_kernel(const int32_t* 
 // block per field, a chain of loads for each digit, took 18.8 us for 204 tiles of 128 digits, now 11.6, and 11 for 80 of
 // 1024, now 7.5.
 constexpr int SCAN_THREADS = 1024, SCAN_DIGITS = 128;
-__global__ __launch_bounds__(SCAN_THREADS) void sort_scan_kernel(uint32_t* hist, uint32_t* digit_total, TileBase tb, int rb) {
+template <bool BUCKETS>
+__global__ __launch_bounds__(SCAN_THREADS) void sort_scan_kernel(uint32_t* hist, uint32_t* digit_total, TileBase tb, int rb, BucketPlan bp) {
   __shared__ uint32_t sums[SCAN_THREADS];
   const int nb = 1 << rb, digits = min(nb, SCAN_DIGITS), groups = nb / digits;
   const int f = (int)blockIdx.x / groups;
@@ -124,7 +284,11 @@ __global__ __launch_bounds__(SCAN_THREADS) void sort_scan_kernel(uint32_t* hist,
     total += c;
   }
   walk(run, true);
-  if (part == 0) digit_total[((int64_t)f << rb) + d] = total;
+  if (part == 0) {
+    digit_total[((int64_t)f << rb) + d] = total;
+    if (BUCKETS && total > (uint32_t)BUCKET_KEYS && bp.fields[f].first[d + 1] - bp.fields[f].first[d] > 1)
+      bp.large[1 + atomicAdd(bp.large, 1)] = f << 16 | d;   // (in any order: each is a block's work)
+  }
 }
 
 // Stable scatter of one tile.  Wave w owns the contiguous slice w of the tile and walks it in
@@ -133,7 +297,8 @@ __global__ __launch_bounds__(SCAN_THREADS) void sort_scan_kernel(uint32_t* hist,
 // Bound by memory where fields are large (42 M keys in 7-bit digits: 678 MB of compulsory traffic in 134 us, a copy's rate), by
 // vector instructions else (75 an item, a third of them the ballots).  Us a pass, with counters in flat accesses, 32 bits wide,
 // and prefixes by LDS exchange / now: 42 M keys 172 / 134, 4.3 M in 10-bit digits 29.7 / 26, 1.1 M 13.1 / 11.3.
-// FULL: all the tile's keys exist.
+// FULL: all the tile's keys exist.  BUCKETS: place inside the bucket's rows and sample leave as one word (packed), or, of a bucket of one row,
+// key and sample.
 constexpr int DPT = MAX_BINS / SORT_THREADS;   // digits per thread: threadIdx.x + q SORT_THREADS
 struct ScatterLds {
   union {
@@ -144,9 +309,10 @@ struct ScatterLds {
   uint16_t dpre[MAX_BINS];
   uint32_t wsum[2][DPT][SORT_WAVES];
 };
-template <bool FULL>
+template <bool FULL, bool BUCKETS, typename Buckets>
 __device__ __forceinline__ void scatter_tile(ScatterLds& lds, const int32_t* keys_in, const int32_t* pay_in, int32_t* keys_out, int32_t* pay_out,
-                                             const uint32_t* hb, const uint32_t* totals, int count, int nnz, int shift, int rb) {
+                                             int32_t* packed, const uint32_t* hb, const uint32_t* totals, int count, int nnz, int shift, int rb,
+                                             const BucketPlan& bp, Buckets& fb, const FieldBuckets* table) {
   constexpr int ITEMS = SORT_ITEMS;
   const int nb = 1 << rb;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -167,15 +333,24 @@ __device__ __forceinline__ void scatter_tile(ScatterLds& lds, const int32_t* key
     key[i] = keys_in[pos];
     pay[i] = pay_in[pos];
   }
+  if constexpr (BUCKETS) load_buckets<SORT_THREADS>(fb, *table);
   for (int d = lane; d < nb; d += 64) lds.cnt[w][d] = 0;   // (each wavefront its own row)
   wave_lds_order();
+  if (BUCKETS) __syncthreads();
   const uint64_t lt = lanemask_lt();
   uint32_t rank[ITEMS];
+  uint32_t digits[ITEMS];
   auto digit = [&](int32_t k) { return ((uint32_t)k >> shift) & (uint32_t)(nb - 1); };
 #pragma unroll
   for (int i = 0; i < ITEMS; ++i) {
+    if (BUCKETS) key[i] = bp.in_range(key[i]);
+    if constexpr (BUCKETS) digits[i] = bp.bucket(fb, key[i]);
+    else digits[i] = digit(key[i]);
+  }
+#pragma unroll
+  for (int i = 0; i < ITEMS; ++i) {
     const bool valid = FULL || first + i * 64 < count;
-    const uint32_t d = digit(key[i]);
+    const uint32_t d = digits[i];
     const uint64_t m = same_digit(d, rb, valid);
     const uint32_t prior = lds.cnt[w][d];
     wave_lds_order();
@@ -231,6 +406,8 @@ __device__ __forceinline__ void scatter_tile(ScatterLds& lds, const int32_t* key
           const uint32_t place = mine + incl[q] - tot[q];  // of the digit's first key in the sorted tile
           lds.dpre[d] = (uint16_t)place;
           lds.gbase[d] = mine_total + incl_total[q] - total[q] + earlier[q] - place;   // output position = gbase[d] + place in the sorted tile
+          // (positions are 31 bits wide: the highest one says that the bucket has one row)
+          if constexpr (BUCKETS) lds.gbase[d] = (lds.gbase[d] & 0x7FFFFFFFu) | (fb.first[d + 1] - fb.first[d] == 1 ? 0x80000000u : 0);
         }
       }
     }
@@ -239,15 +416,20 @@ __device__ __forceinline__ void scatter_tile(ScatterLds& lds, const int32_t* key
   uint32_t lp[ITEMS];
 #pragma unroll
   for (int i = 0; i < ITEMS; ++i) {
-    const uint32_t d = digit(key[i]);
+    const uint32_t d = digits[i];
     lp[i] = lds.dpre[d] + lds.cnt[w][d] + rank[i];
   }
   __syncthreads();  // the counters are dead: their memory stages the tile sorted by digit
 #pragma unroll
   for (int i = 0; i < ITEMS; ++i) {
     if ((FULL || first + i * 64 < count) && lp[i] < (uint32_t)SORT_TILE) {
-      lds.staged[0][lp[i]] = key[i];
-      lds.staged[1][lp[i]] = pay[i];
+      if constexpr (BUCKETS) {
+        lds.staged[0][lp[i]] = (int32_t)((uint32_t)(key[i] - fb.first[digits[i]]) << bp.sample_bits | ((uint32_t)pay[i] & ((1u << bp.sample_bits) - 1)));
+        lds.staged[1][lp[i]] = (int32_t)digits[i];
+      } else {
+        lds.staged[0][lp[i]] = key[i];
+        lds.staged[1][lp[i]] = pay[i];
+      }
     }
   }
   __syncthreads();
@@ -258,28 +440,236 @@ __device__ __forceinline__ void scatter_tile(ScatterLds& lds, const int32_t* key
     const int j = q * SORT_THREADS + threadIdx.x;
     if (FULL || j < count) {
       const int32_t k = lds.staged[0][j];
-      const uint32_t dst = lds.gbase[digit(k)] + (uint32_t)j;
-      if (dst < (uint32_t)nnz) {
-        keys_out[dst] = k;
-        pay_out[dst] = lds.staged[1][j];
+      if constexpr (BUCKETS) {
+        const int d = lds.staged[1][j];
+        const uint32_t base = lds.gbase[d], dst = (base + (uint32_t)j) & 0x7FFFFFFFu;
+        if (dst >= (uint32_t)nnz) continue;
+        if ((int32_t)base >= 0) {
+          packed[dst] = k;
+        } else {
+          keys_out[dst] = fb.first[d];
+          pay_out[dst] = k;
+        }
+      } else {
+        const uint32_t dst = lds.gbase[digit(k)] + (uint32_t)j;
+        if (dst < (uint32_t)nnz) {
+          keys_out[dst] = k;
+          pay_out[dst] = lds.staged[1][j];
+        }
       }
     }
   }
 }
 
+template <bool BUCKETS>
 __global__ __launch_bounds__(SORT_THREADS, 8) void sort_scatter_kernel(
-    const int32_t* keys_in, const int32_t* pay_in, int32_t* keys_out, int32_t* pay_out, const uint32_t* hist,
-    const uint32_t* digit_total, FieldPtr fp, TileBase tb, int F, int shift, int rb) {
+    const int32_t* keys_in, const int32_t* pay_in, int32_t* keys_out, int32_t* pay_out, int32_t* packed, const uint32_t* hist,
+    const uint32_t* digit_total, FieldPtr fp, TileBase tb, int F, int shift, int rb, BucketPlan bp) {
   __shared__ ScatterLds lds;
-  static_assert(4 * sizeof(lds) <= 160 * 1024, "four blocks to fill a compute unit's places for wavefronts");
+  __shared__ typename std::conditional<BUCKETS, FieldBuckets, int>::type fb;
+  static_assert(4 * (sizeof(lds) + sizeof(fb)) <= 160 * 1024, "four blocks to fill a compute unit's places for wavefronts");
   int f, t, part;
   if (!tile_of_block(tb, F, 1, f, t, part)) return;
   const int64_t base = fp.p[f], start = base + (int64_t)t * SORT_TILE;
   const int nnz = (int)(fp.p[f + 1] - base), count = min(SORT_TILE, nnz - t * SORT_TILE);
   const uint32_t* hb = hist + ((int64_t)(tb.t[f] + t) << rb);
   const uint32_t* totals = digit_total + ((int64_t)f << rb);
-  if (count == SORT_TILE) scatter_tile<true>(lds, keys_in + start, pay_in + start, keys_out + base, pay_out + base, hb, totals, count, nnz, shift, rb);
-  else scatter_tile<false>(lds, keys_in + start, pay_in + start, keys_out + base, pay_out + base, hb, totals, count, nnz, shift, rb);
+  if (count == SORT_TILE) scatter_tile<true, BUCKETS>(lds, keys_in + start, pay_in + start, keys_out + base, pay_out + base, packed + base, hb, totals, count, nnz, shift, rb, bp, fb, bp.fields + f);
+  else scatter_tile<false, BUCKETS>(lds, keys_in + start, pay_in + start, keys_out + base, pay_out + base, packed + base, hb, totals, count, nnz, shift, rb, bp, fb, bp.fields + f);
+}
+
+// A block sorts a bucket's lookups (place of the row in the bucket, sample; in sample order) by the rows and takes the words apart.  Up to
+// BUCKET_KEYS of them stay in LDS, in passes of up to BUCKET_BITS bits; what more there are (cuts are made by a sample) go
+// through memory, BUCKET_KEYS at a time, by the first blocks of the launch.
+// A lookup is read and written twice on the way from the batch to its place, as one word in between, where a pass over all of them reads it
+// twice and writes it once (42 M lookups: 1.0 GB instead of 2.5).  Bound by the ballots (a bit of a lookup costs four instructions a
+// wavefront either way).  42 M lookups of Zipf(1.2) ids, us: cuts 17, histogram 79, scan 12, scatter 153, buckets 184.  By the ids' highest bits instead, the
+// buckets of hot rows kept single blocks busy: 522; 1024 threads with 8 lookups each: 337 where ids are even (512 with 16: 214).  Four
+// tiles a block in the histogram, or the buckets' numbers kept as bytes for the scatter: 77 and 98 there, 154 and 141 in the scatter.
+struct BucketLds {
+  uint16_t cnt[BUCKET_WAVES][1 << BUCKET_BITS];
+  uint32_t base[1 << BUCKET_BITS];           // place of a digit's first key of those in hand
+  uint32_t count[2][1 << BUCKET_BITS];       // large buckets: where the digit's next key goes, of each pass
+  uint32_t wsum[BUCKET_WAVES];
+  int32_t stage[BUCKET_KEYS];
+};
+// Ranks of the n keys in hand (item i of wavefront w: position 64 (w per + i) + lane) among those of their digit in their wavefront;
+// lds.cnt: keys of the digit in the wavefronts before.  Returns the block's keys of digit threadIdx.x.
+__device__ __forceinline__ uint32_t rank_keys(BucketLds& lds, const uint32_t (&x)[BUCKET_ITEMS], int n, int per, int shift, int bits,
+                                              uint32_t (&rank)[BUCKET_ITEMS]) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nb = 1 << bits;
+  const int first = w * (64 * per) + lane;
+  const uint64_t lt = lanemask_lt();
+  for (int d = lane; d < nb; d += 64) lds.cnt[w][d] = 0;   // (each wavefront its own row)
+  wave_lds_order();
+#pragma unroll
+  for (int i = 0; i < BUCKET_ITEMS; ++i) {
+    rank[i] = 0;
+    if (i < per && w * (64 * per) + i * 64 < n) {   // (uniform)
+      const bool valid = first + i * 64 < n;
+      const uint32_t d = (x[i] >> shift) & (uint32_t)(nb - 1);
+      const uint64_t m = same_digit(d, bits, valid);
+      const uint32_t prior = lds.cnt[w][d];
+      wave_lds_order();
+      rank[i] = prior + (uint32_t)__popcll(m & lt);
+      if (valid && (m & lt) == 0) lds.cnt[w][d] = (uint16_t)(prior + (uint32_t)__popcll(m));   // lowest lane of the group
+      wave_lds_order();
+    }
+  }
+  __syncthreads();
+  uint32_t tot = 0;
+  if ((int)threadIdx.x < nb) {
+    uint32_t c[BUCKET_WAVES];
+#pragma unroll
+    for (int q = 0; q < BUCKET_WAVES; ++q) c[q] = lds.cnt[q][threadIdx.x];
+#pragma unroll
+    for (int q = 0; q < BUCKET_WAVES; ++q) {
+      lds.cnt[q][threadIdx.x] = (uint16_t)tot;
+      tot += c[q];
+    }
+  }
+  return tot;
+}
+__device__ __forceinline__ void sort_bucket(BucketLds& lds, const BucketPlan& bp, const uint32_t* in, int32_t* keys_out, int32_t* pay_out, int n,
+                                            int row0, int rows) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int per = (n + BUCKET_THREADS - 1) / BUCKET_THREADS;   // <= BUCKET_ITEMS
+  const int first = w * (64 * per) + lane;
+  auto mine = [&](int i) { return i < per && first + i * 64 < n; };
+  uint32_t x[BUCKET_ITEMS] = {};
+#pragma unroll
+  for (int i = 0; i < BUCKET_ITEMS; ++i)
+    if (i < per) x[i] = in[min(first + i * 64, n - 1)];
+  const int low = 32 - __clz(rows - 1), passes = (low + BUCKET_BITS - 1) / BUCKET_BITS, most = (low + passes - 1) / passes;
+  for (int from = 0; from < low; from += most) {
+    const int bits = min(low - from, most), shift = bp.sample_bits + from, nb = 1 << bits;
+    uint32_t rank[BUCKET_ITEMS], all;
+    const uint32_t tot = rank_keys(lds, x, n, per, shift, bits, rank);
+    const uint32_t before = block_prefix(tot, lds.wsum, BUCKET_WAVES, all, false);   // (the sums are read by all before the next barrier)
+    if ((int)threadIdx.x < nb) lds.base[threadIdx.x] = before;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < BUCKET_ITEMS; ++i)
+      if (mine(i)) {
+        const uint32_t d = (x[i] >> shift) & (uint32_t)(nb - 1);
+        lds.stage[lds.base[d] + lds.cnt[w][d] + rank[i]] = (int32_t)x[i];
+      }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < BUCKET_ITEMS; ++i)
+      if (mine(i)) x[i] = (uint32_t)lds.stage[first + i * 64];   // (three barriers before the next pass writes there)
+  }
+#pragma unroll
+  for (int i = 0; i < BUCKET_ITEMS; ++i)
+    if (mine(i)) {
+      keys_out[first + i * 64] = row0 + (int32_t)(x[i] >> bp.sample_bits);
+      pay_out[first + i * 64] = (int32_t)(x[i] & ((1u << bp.sample_bits) - 1));
+    }
+}
+// More than BUCKET_KEYS lookups: two passes from `in` to `between` to the results.
+__device__ __forceinline__ void sort_large_bucket(BucketLds& lds, const BucketPlan& bp, const uint32_t* in, uint32_t* between, int32_t* keys_out,
+                                                  int32_t* pay_out, int n, int row0, int rows) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int low = 32 - __clz(rows - 1);
+  const int bits[2] = {(low + 1) / 2, low / 2}, shift[2] = {bp.sample_bits, bp.sample_bits + bits[0]};
+  for (int d = threadIdx.x; d < 2 << BUCKET_BITS; d += BUCKET_THREADS) (&lds.count[0][0])[d] = 0;
+  __syncthreads();
+  for (int c0 = 0; c0 < n; c0 += BUCKET_KEYS) {   // keys of every digit
+    uint32_t x[BUCKET_ITEMS];
+#pragma unroll
+    for (int i = 0; i < BUCKET_ITEMS; ++i) x[i] = in[min(c0 + i * BUCKET_THREADS + (int)threadIdx.x, n - 1)];
+#pragma unroll
+    for (int i = 0; i < BUCKET_ITEMS; ++i) {
+      const bool valid = c0 + i * BUCKET_THREADS + (int)threadIdx.x < n;
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {   // one addition for the lanes of a digit: hot rows make them many
+        const uint32_t d = (x[i] >> shift[p]) & ((1u << bits[p]) - 1);
+        const uint64_t m = same_digit(d, bits[p], valid);
+        if (valid && (m & lanemask_lt()) == 0) atomicAdd(&lds.count[p][d], (uint32_t)__popcll(m));
+      }
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    const uint32_t tot = (int)threadIdx.x < 1 << BUCKET_BITS ? lds.count[p][threadIdx.x & ((1 << BUCKET_BITS) - 1)] : 0;
+    uint32_t all;
+    const uint32_t before = block_prefix(tot, lds.wsum, BUCKET_WAVES, all);
+    if ((int)threadIdx.x < 1 << BUCKET_BITS) lds.count[p][threadIdx.x] = before;
+  }
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    const uint32_t* from = p == 0 ? in : between;
+    for (int c0 = 0; c0 < n; c0 += BUCKET_KEYS) {
+      const int nc = min(n - c0, BUCKET_KEYS), per = (nc + BUCKET_THREADS - 1) / BUCKET_THREADS, first = w * (64 * per) + lane;
+      uint32_t x[BUCKET_ITEMS] = {}, rank[BUCKET_ITEMS];
+#pragma unroll
+      for (int i = 0; i < BUCKET_ITEMS; ++i)
+        if (i < per) x[i] = from[c0 + min(first + i * 64, nc - 1)];
+      const uint32_t tot = rank_keys(lds, x, nc, per, shift[p], bits[p], rank);
+      if ((int)threadIdx.x < 1 << bits[p]) {
+        const uint32_t at = lds.count[p][threadIdx.x];
+        lds.base[threadIdx.x] = at;
+        lds.count[p][threadIdx.x] = at + tot;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < BUCKET_ITEMS; ++i)
+        if (i < per && first + i * 64 < nc) {
+          const uint32_t d = (x[i] >> shift[p]) & ((1u << bits[p]) - 1);
+          const uint32_t dst = lds.base[d] + lds.cnt[w][d] + rank[i];
+          if (dst >= (uint32_t)n) continue;   // (never)
+          if (p == 0) {
+            between[dst] = x[i];
+          } else {
+            keys_out[dst] = row0 + (int32_t)(x[i] >> bp.sample_bits);
+            pay_out[dst] = (int32_t)(x[i] & ((1u << bp.sample_bits) - 1));
+          }
+        }
+      __syncthreads();   // (counters and bases are the next ones')
+    }
+    // (what other wavefronts wrote is read next: they are of this block, and its compute unit, whose barrier waits for their stores)
+  }
+}
+__global__ __launch_bounds__(BUCKET_THREADS) void sort_buckets_kernel(const int32_t* in, int32_t* between, int32_t* keys_out, int32_t* pay_out,
+                                                                      const uint32_t* digit_total, FieldPtr fp, int F, int large_blocks,
+                                                                      BucketPlan bp) {
+  __shared__ BucketLds lds;
+  auto place = [&](int f, int b, int64_t& at, int& n) {   // the bucket's lookups: those of the field's buckets before it come first
+    const uint32_t* totals = digit_total + ((int64_t)f << bp.rb);
+    const int lane = threadIdx.x & 63;
+    uint32_t t[MAX_BUCKETS / 64], before = 0;
+#pragma unroll
+    for (int q = 0; q < MAX_BUCKETS / 64; ++q) t[q] = totals[min(q * 64 + lane, b)];
+#pragma unroll
+    for (int q = 0; q < MAX_BUCKETS / 64; ++q) before += q * 64 + lane < b ? t[q] : 0;
+    before = (uint32_t)__builtin_amdgcn_readlane((int)wave_prefix(before), 63);
+    at = fp.p[f] + before;
+    n = max(min((int64_t)totals[b], fp.p[f + 1] - at), (int64_t)0);
+  };
+  int64_t at;
+  int n;
+  if ((int)blockIdx.x < large_blocks) {
+    const int count = bp.large[0];
+    for (int i = blockIdx.x; i < count; i += large_blocks) {
+      const int f = bp.large[1 + i] >> 16, b = bp.large[1 + i] & 0xFFFF;
+      place(f, b, at, n);
+      const int row0 = bp.fields[f].first[b], rows = bp.fields[f].first[b + 1] - row0;
+      sort_large_bucket(lds, bp, reinterpret_cast<const uint32_t*>(in) + at, reinterpret_cast<uint32_t*>(between) + at, keys_out + at, pay_out + at, n, row0,
+                        rows);
+    }
+    return;
+  }
+  // (the buckets of a field on the XCD that its tiles were scattered on, see tile_of_block)
+  const int block = (int)blockIdx.x - large_blocks, total = F << bp.rb, share = (total + 7) >> 3, i = (block & 7) * share + (block >> 3);
+  if ((block >> 3) >= share || i >= total) return;
+  const int f = i >> bp.rb, b = i - (f << bp.rb);
+  if (fp.p[f + 1] == fp.p[f]) return;
+  const int row0 = bp.fields[f].first[b], rows = bp.fields[f].first[b + 1] - row0;
+  if (rows <= 1) return;   // (the partition has put these where they belong)
+  place(f, b, at, n);
+  if (n == 0 || n > BUCKET_KEYS) return;
+  sort_bucket(lds, bp, reinterpret_cast<const uint32_t*>(in) + at, keys_out + at, pay_out + at, n, row0, rows);
 }
 
 // Block = field.
@@ -1073,18 +1463,70 @@ static hipError_t launch_sort_pass(const SortPlan& pl, const SortBuffers& sb, in
   dim3 grid(tile_grid(pl.total_tiles));
   {
     ProfScope ps(prof, KID_SORT_HIST, s);
-    hipLaunchKernelGGL(sort_hist_kernel, grid, dim3(SORT_THREADS), 0, s, kin, sb.hist, fp, tb, pl.F, shift, pl.radix_bits);
+    hipLaunchKernelGGL(sort_hist_kernel<false>, grid, dim3(SORT_THREADS), 0, s, kin, sb.hist, fp, tb, pl.F, shift, pl.radix_bits, BucketPlan());
   }
   {
     ProfScope ps(prof, KID_SORT_SCAN, s);
     const int groups = std::max(1, (1 << pl.radix_bits) / SCAN_DIGITS);
-    hipLaunchKernelGGL(sort_scan_kernel, dim3(pl.F * groups), dim3(SCAN_THREADS), 0, s, sb.hist, sb.digit_total, tb, pl.radix_bits);
+    hipLaunchKernelGGL(sort_scan_kernel<false>, dim3(pl.F * groups), dim3(SCAN_THREADS), 0, s, sb.hist, sb.digit_total, tb, pl.radix_bits, BucketPlan());
   }
   {
     ProfScope ps(prof, KID_SORT_SCATTER, s);
-    hipLaunchKernelGGL(sort_scatter_kernel, grid, dim3(SORT_THREADS), 0, s, kin, pin, sb.key[pass & 1],
-                       sb.pay[pass & 1], sb.hist, sb.digit_total, fp, tb, pl.F, shift, pl.radix_bits);
+    hipLaunchKernelGGL(sort_scatter_kernel<false>, grid, dim3(SORT_THREADS), 0, s, kin, pin, sb.key[pass & 1],
+                       sb.pay[pass & 1], sb.key[0], sb.hist, sb.digit_total, fp, tb, pl.F, shift, pl.radix_bits, BucketPlan());
   }
+  return hipGetLastError();
+}
+
+static int bits_of(int64_t n) {   // of the numbers below n
+  int b = 0;
+  while (b < 62 && (1ll << b) < n) ++b;
+  return b;
+}
+// Whether the sort goes by buckets, and how: from as many lookups on as pay for its launches' chain.  Alone, by passes / by buckets, us: 42 M lookups
+// (1.2 M rows, 3 passes) 614 / 449, 4.1 M (1 M rows, 2 passes) 93 / 91, 3.8 M (0.5 M rows) 79 / 82; a step of 4.1 M on one stream 551 / 552, of 3.8 M
+// 420 / 424, of 2.2 M 383 / 387.  Beside the gather and the MLP it takes less memory traffic from them, us a step: 2.2 M 341 / 336, 3.8 M 372 / 361, 4.1 M
+// 507 / 496, 42 M 2738 / 2536; 1.5 M 251 / 253.  The buckets follow the lookups, so how the hot rows lie does not matter (ids in order of their
+// frequency: 3.8 M 362 / 340, 20 M 1490 / 1387).
+static constexpr int64_t BUCKETS_MIN = 6000000, BUCKETS_MIN_BESIDE = 2000000;
+static bool plan_buckets(const SortPlan& pl, const SortBuffers& sb, const FieldPtr& fp, BucketPlan& bp) {
+  if (pl.passes < 2 || fp.p[pl.F] < (pl.beside ? BUCKETS_MIN_BESIDE : BUCKETS_MIN)) return false;
+  int64_t most = 0;
+  for (int f = 0; f < pl.F; ++f) most = std::max(most, fp.p[f + 1] - fp.p[f]);
+  bp.sample_bits = bits_of(pl.samples);
+  bp.range_bits = std::min(2 * BUCKET_BITS, 32 - bp.sample_bits);
+  bp.last_row = (int32_t)(pl.rows - 1);
+  bp.cell_bits = std::max(bits_of(pl.rows) - bits_of(BUCKET_CELLS), 0);
+  bp.rb = std::min({bits_of(std::max<int64_t>(most / 3000, 32)), pl.radix_bits, bits_of(MAX_BUCKETS)});   // (the histograms' space)
+  const int64_t fixed = ((int64_t)bp.last_row >> std::max(bp.range_bits, 0)) + 1;
+  if (bp.range_bits < BUCKET_BITS || 2 * fixed > (1 << bp.rb)) return false;
+  // the buckets' tables and the list of the large ones
+  constexpr int64_t WORDS = sizeof(FieldBuckets) / 4;
+  bp.fields = reinterpret_cast<FieldBuckets*>(sb.slots);
+  bp.large = sb.slots + WORDS * pl.F;
+  return WORDS * pl.F + 1 + fp.p[pl.F] / (BUCKET_KEYS + 1) <= window_slots(fp.p[pl.F]);
+}
+static hipError_t launch_sort_buckets(const SortPlan& pl, const SortBuffers& sb, const FieldPtr& fp, const TileBase& tb, const BucketPlan& bp,
+                                      Profiler* prof, hipStream_t s) {
+  const dim3 grid(tile_grid(pl.total_tiles));
+  {
+    ProfScope ps(prof, KID_SORT_HIST, s);
+    hipLaunchKernelGGL(sort_cuts_kernel, dim3(pl.F), dim3(SAMPLE_KEYS), 0, s, sb.ids, fp, bp);
+    hipLaunchKernelGGL(sort_hist_kernel<true>, grid, dim3(SORT_THREADS), 0, s, sb.ids, sb.hist, fp, tb, pl.F, 0, bp.rb, bp);
+    ps.launches(2);
+  }
+  {
+    ProfScope ps(prof, KID_SORT_SCAN, s);
+    const int groups = std::max(1, (1 << bp.rb) / SCAN_DIGITS);
+    hipLaunchKernelGGL(sort_scan_kernel<true>, dim3(pl.F * groups), dim3(SCAN_THREADS), 0, s, sb.hist, sb.digit_total, tb, bp.rb, bp);
+  }
+  ProfScope ps(prof, KID_SORT_SCATTER, s);
+  hipLaunchKernelGGL(sort_scatter_kernel<true>, grid, dim3(SORT_THREADS), 0, s, sb.ids, sb.pay0, sb.key[0], sb.pay[0], sb.key[1], sb.hist,
+                     sb.digit_total, fp, tb, pl.F, 0, bp.rb, bp);
+  const int large_blocks = (int)std::min<int64_t>((fp.p[pl.F] / (BUCKET_KEYS + 1) + 7) / 8 * 8, 1024);   // (the others keep their XCDs)
+  hipLaunchKernelGGL(sort_buckets_kernel, dim3(large_blocks + 8 * (((pl.F << bp.rb) + 7) / 8)), dim3(BUCKET_THREADS), 0, s, sb.key[1], sb.pay[1],
+                     sb.key[0], sb.pay[0], sb.digit_total, fp, pl.F, large_blocks, bp);
+  ps.launches(2);
   return hipGetLastError();
 }
 
@@ -1100,6 +1542,8 @@ hipError_t launch_sort(const SortPlan& pl, const SortBuffers& sb, const FieldPtr
     case 8: return launch_sort_small_items<8>(pl, sb, fp, prof, s);
     case 16: return launch_sort_small_items<16>(pl, sb, fp, prof, s);
   }
+  BucketPlan bp = {};
+  if (plan_buckets(pl, sb, fp, bp)) return launch_sort_buckets(pl, sb, fp, tb, bp, prof, s);
   for (int p = 0; p < pl.passes; ++p) {
     const hipError_t e = launch_sort_pass(pl, sb, p, fp, tb, prof, s);
     if (e != hipSuccess) return e;

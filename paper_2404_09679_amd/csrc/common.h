@@ -178,6 +178,8 @@ struct SortPlan {
   int32_t F;
   int32_t passes, radix_bits;      // digit width per pass
   int32_t total_tiles;
+  int64_t rows, samples;           // row ids and sample indices lie below
+  bool beside;                     // runs beside other work
 };
 struct SortBuffers {
   const int32_t* ids;
@@ -186,6 +188,7 @@ struct SortBuffers {
   int32_t* pay[2];
   uint32_t* hist;                  // [total_tiles << radix_bits]
   uint32_t* digit_total;            // [F << radix_bits]
+  int32_t* slots;                  // scratch, a word per slot of the windows (window_slots)
 };
 // Weight gradients of all layers in one launch (see wgrad_kernel, wgrad_f32_kernel): per range written to
 // the shards' flat gradients, or aggregated and applied (Adagrad) on the spot, in which case neither

@@ -750,10 +750,12 @@ static void fill_sort(antdt_ctx* c, const int32_t* ids, const int32_t* pay0, Sor
   const antdt_model& m = c->m;
   pl.F = m.num_fields; pl.passes = c->sort_passes; pl.radix_bits = c->radix_bits;
   pl.total_tiles = c->atotal_tiles;
+  pl.rows = m.rows_per_field; pl.samples = c->B; pl.beside = false;
   sb.ids = ids;
   sb.key[0] = c->key[0]; sb.key[1] = c->key[1]; sb.pay[0] = c->pay[0]; sb.pay[1] = c->pay[1];
   sb.hist = c->hist;
   sb.digit_total = c->digit_total;
+  sb.slots = c->goes_out;   // (the reduction's, which follows)
   sb.pay0 = pay0;
 }
 
@@ -762,6 +764,7 @@ static int build_coalescing(antdt_ctx* c, const int32_t* ids, const int32_t* pay
   SortPlan pl;
   SortBuffers sb;
   fill_sort(c, ids, pay0, pl, sb);
+  pl.beside = s == c->side;
   HIP_TRY(c, launch_sort(pl, sb, c->afp, c->atb, prof_of(c), s, &c->sorted_buf));
   return ANTDT_OK;
 }

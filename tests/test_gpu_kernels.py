@@ -154,6 +154,63 @@ def test_sort_ahead_of_the_gather(how, bag):
     check_iteration(cfg, cfg.shard_sizes, tol=TOL32, batched=True, **kw)   # (from zero accumulators: smaller steps than above)
 
 
+# From two million lookups of a batched step the sort goes by buckets: rows cut where a sample of the lookups says.  Fields of many
+# lookups, none, one and a few; ids spread evenly, by frequency, in the first rows, in one, in some that are neighbours, at both ends, past a
+# multiple of 2^16 rows; buckets larger than a block holds (64 of them for 900 000 lookups of 1500 rows).  The sorted lookups are those
+# of a stable sort, one for one.
+@pytest.mark.parametrize("kind", ["even", "zipf", "first-rows", "one-row", "neighbours", "ends", "past-65536"])
+@pytest.mark.parametrize("rows", [1500, 70_001, 1_100_000])
+def test_sort_by_buckets(kind, rows):
+    import torch
+    import paper_2404_09679_amd as A
+    dev, B = "cuda:0", 3001
+    sizes = [900_000, 0, 700_001, 1, 8193, 500_000]
+    cfg = _config(f"buckets-{kind}", 640, num_fields=len(sizes), rows_per_field=rows, dim=4, layer_sizes=(8,), gemm_dtype="f32", num_dense=0,
+                  shard_sizes=(2000, B - 2000), max_bag=400)
+    g = torch.Generator(device=dev).manual_seed(rows)
+    draw = lambda lo, hi, n: torch.randint(lo, hi, (n,), generator=g, device=dev)
+
+    def ids_of(n):
+        if kind == "zipf":
+            u = torch.rand(n, generator=g, device=dev, dtype=torch.float64)
+            return ((u.clamp(min=1e-6) ** -1.5).long() * 7919) % rows
+        if kind == "first-rows":
+            return torch.minimum(draw(0, rows, n), draw(0, 40, n) ** 2 % rows)
+        if kind == "one-row":
+            return torch.full((n,), rows // 3, device=dev)
+        if kind == "neighbours":
+            return rows - 1 - draw(0, 12, n)
+        if kind == "ends":
+            return draw(0, 2, n) * (rows - 1)
+        if kind == "past-65536":
+            return (65_530 + draw(0, 13, n)) % rows
+        return draw(0, rows, n)
+
+    ids = [ids_of(n).int() for n in sizes]
+    offsets = torch.zeros((len(sizes), B + 1), dtype=torch.int32, device=dev)
+    for f, n in enumerate(sizes):
+        offsets[f, 1:B] = torch.sort(draw(0, n + 1, B - 1))[0].int()
+        offsets[f, B] = n
+    tables = torch.randn((len(sizes) * rows, 4), generator=g, device=dev) * 0.05
+    state = torch.ones_like(tables)
+    params = torch.randn(sum(i * o + o for i, o in zip((24, 8), (8, 1))), generator=g, device=dev) * 0.3
+    ctx = A.Context(A.model_from_config(cfg, max_batch=B, max_nnz=sum(sizes), max_shards=2))
+    ctx.bind(tables, state, params, torch.ones_like(params))
+    ptr = np.concatenate([[0], np.cumsum(sizes)]).tolist()
+    ctx.set_batch(torch.cat(ids), ptr, offsets, None, (torch.rand(B, generator=g, device=dev) < 0.25).float())
+    ctx.assign_shard(B, 2, sizes=[2000, B - 2000])
+    ctx.worker_step_all(torch.zeros(2, device=dev))
+    ctx.aggregate()
+    for f, n in enumerate(sizes):
+        u, so, ss, _ = ctx.view_coalesced(f)
+        key, order = torch.sort(ids[f], stable=True)
+        rows_f, counts = torch.unique_consecutive(key, return_counts=True)
+        sample = torch.repeat_interleave(torch.arange(B, device=dev), (offsets[f, 1:] - offsets[f, :-1]).long())
+        assert torch.equal(u.long(), rows_f.long()), (f, "rows")
+        assert torch.equal(so.long()[1:], torch.cumsum(counts, 0)) and int(so[0]) == 0, (f, "runs")
+        assert torch.equal(ss.long(), sample[order]), (f, "samples")
+
+
 def test_gather_from_a_table_of_2_32_pieces():
     """2^30 rows of 64 bytes: places of rows no longer fit 32 bits.  Pooled inputs and updated rows against torch, the rows
     2^28, 2^29, ... away from the looked-up ones against their initial values."""
