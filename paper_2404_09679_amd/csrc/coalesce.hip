@@ -66,6 +66,8 @@ struct BucketPlan {
   int32_t sample_bits;
   int32_t cell_bits;    // log2 of the rows of a cell
   int32_t last_row;
+  const int32_t* offsets;   // [F][B + 1] where the samples of the lookups are to be worked out from these, or NULL
+  int32_t B;
   FieldBuckets* fields;
   int32_t* large;       // [0]: number of buckets of more than BUCKET_KEYS lookups and one row, then those (field, bucket)
   // (ids that are no rows go where the update takes them to be: the first row, the last one)
@@ -81,6 +83,36 @@ struct BucketPlan {
     return lo;
   }
 };
+// Samples of 256 neighbouring lookups of a field, from position p0 (one of the field's) on, by a wavefront: lane l receives those of
+// p0 + 64 i + l (past the field's end: any).  off: the field's bag boundaries, off[0] = 0, off[B] its lookups; mark: 256 words of LDS.
+__device__ __forceinline__ void samples_of(const int32_t* off, int B, int p0, uint32_t* mark, int32_t (&sample)[4]) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) mark[i * 64 + lane] = 0;
+  int lo = 0, hi = B;   // the bag of p0: off[lo] <= p0 < off[hi]
+  while (hi - lo > 1) {
+    const int step = (hi - lo + 64) / 65, at = lo + (lane + 1) * step;
+    const int below = __popcll(__ballot(at < hi && off[min(at, hi)] <= p0));
+    hi = min(hi, lo + (below + 1) * step);
+    lo += below * step;
+  }
+  wave_lds_order();
+  for (int s = lo + 1; s < B; s += 64) {   // bags that begin among the lookups behind p0, empty ones too
+    const int begin = off[min(s + lane, B)] - p0;
+    if (s + lane < B && begin > 0 && begin < 256) atomicAdd(&mark[begin], 1u);
+    if (__ballot(begin >= 256)) break;
+  }
+  wave_lds_order();
+  uint32_t bags = (uint32_t)lo;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const uint32_t upto = bags + wave_prefix(mark[i * 64 + lane]);
+    sample[i] = (int32_t)upto;
+    bags = (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
+  }
+  wave_lds_order();
+}
+
 template <int THREADS>
 __device__ __forceinline__ void load_buckets(FieldBuckets& to, const FieldBuckets& from) {
   constexpr int WORDS = sizeof(FieldBuckets) / 4;
@@ -312,7 +344,8 @@ struct ScatterLds {
 template <bool FULL, bool BUCKETS, typename Buckets>
 __device__ __forceinline__ void scatter_tile(ScatterLds& lds, const int32_t* keys_in, const int32_t* pay_in, int32_t* keys_out, int32_t* pay_out,
                                              int32_t* packed, const uint32_t* hb, const uint32_t* totals, int count, int nnz, int shift, int rb,
-                                             const BucketPlan& bp, Buckets& fb, const FieldBuckets* table) {
+                                             const BucketPlan& bp, Buckets& fb, const FieldBuckets* table,
+                                             int f, int tile0) {
   constexpr int ITEMS = SORT_ITEMS;
   const int nb = 1 << rb;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -331,9 +364,14 @@ __device__ __forceinline__ void scatter_tile(ScatterLds& lds, const int32_t* key
   for (int i = 0; i < ITEMS; ++i) {  // all loads first (clamped), so that they overlap
     const int pos = FULL ? first + i * 64 : min(first + i * 64, count - 1);
     key[i] = keys_in[pos];
-    pay[i] = pay_in[pos];
+    if (!BUCKETS || !bp.offsets) pay[i] = pay_in[pos];
   }
   if constexpr (BUCKETS) load_buckets<SORT_THREADS>(fb, *table);
+  if constexpr (BUCKETS) {
+    static_assert(ITEMS == 4 && sizeof(lds.cnt[0]) >= 256 * 4, "lookups of a wavefront");
+    if (bp.offsets && w * (64 * ITEMS) < count)
+      samples_of(bp.offsets + (int64_t)f * (bp.B + 1), bp.B, tile0 + w * (64 * ITEMS), reinterpret_cast<uint32_t*>(lds.cnt[w]), pay);
+  }
   for (int d = lane; d < nb; d += 64) lds.cnt[w][d] = 0;   // (each wavefront its own row)
   wave_lds_order();
   if (BUCKETS) __syncthreads();
@@ -474,8 +512,10 @@ __global__ __launch_bounds__(SORT_THREADS, 8) void sort_scatter_kernel(
   const int nnz = (int)(fp.p[f + 1] - base), count = min(SORT_TILE, nnz - t * SORT_TILE);
   const uint32_t* hb = hist + ((int64_t)(tb.t[f] + t) << rb);
   const uint32_t* totals = digit_total + ((int64_t)f << rb);
-  if (count == SORT_TILE) scatter_tile<true, BUCKETS>(lds, keys_in + start, pay_in + start, keys_out + base, pay_out + base, packed + base, hb, totals, count, nnz, shift, rb, bp, fb, bp.fields + f);
-  else scatter_tile<false, BUCKETS>(lds, keys_in + start, pay_in + start, keys_out + base, pay_out + base, packed + base, hb, totals, count, nnz, shift, rb, bp, fb, bp.fields + f);
+  if (count == SORT_TILE) scatter_tile<true, BUCKETS>(lds, keys_in + start, pay_in + start, keys_out + base, pay_out + base, packed + base, hb, totals, count, nnz, shift, rb, bp, fb, bp.fields + f, f,
+                                                    t * SORT_TILE);
+  else scatter_tile<false, BUCKETS>(lds, keys_in + start, pay_in + start, keys_out + base, pay_out + base, packed + base, hb, totals, count, nnz, shift, rb, bp, fb, bp.fields + f, f,
+                                                    t * SORT_TILE);
 }
 
 // A block sorts a bucket's lookups (place of the row in the bucket, sample; in sample order) by the rows and takes the words apart.  Up to
@@ -1496,6 +1536,8 @@ static bool plan_buckets(const SortPlan& pl, const SortBuffers& sb, const FieldP
   bp.sample_bits = bits_of(pl.samples);
   bp.range_bits = std::min(2 * BUCKET_BITS, 32 - bp.sample_bits);
   bp.last_row = (int32_t)(pl.rows - 1);
+  bp.offsets = sb.offsets;
+  bp.B = (int32_t)pl.samples;
   bp.cell_bits = std::max(bits_of(pl.rows) - bits_of(BUCKET_CELLS), 0);
   bp.rb = std::min({bits_of(std::max<int64_t>(most / 3000, 32)), pl.radix_bits, bits_of(MAX_BUCKETS)});   // (the histograms' space)
   const int64_t fixed = ((int64_t)bp.last_row >> std::max(bp.range_bits, 0)) + 1;
@@ -1528,6 +1570,11 @@ static hipError_t launch_sort_buckets(const SortPlan& pl, const SortBuffers& sb,
                      sb.key[0], sb.pay[0], sb.digit_total, fp, pl.F, large_blocks, bp);
   ps.launches(2);
   return hipGetLastError();
+}
+
+bool sort_finds_samples(const SortPlan& pl, const SortBuffers& sb, const FieldPtr& fp) {
+  BucketPlan bp = {};
+  return small_sort_items(pl.F, fp) == 0 && plan_buckets(pl, sb, fp, bp);
 }
 
 hipError_t launch_sort(const SortPlan& pl, const SortBuffers& sb, const FieldPtr& fp, const TileBase& tb, Profiler* prof, hipStream_t s,

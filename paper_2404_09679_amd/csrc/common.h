@@ -184,6 +184,7 @@ struct SortPlan {
 struct SortBuffers {
   const int32_t* ids;
   const int32_t* pay0;             // sample index of every lookup (payload of the first pass)
+  const int32_t* offsets;          // [F][samples + 1] bag boundaries, of a sort that finds the samples by itself (see sort_finds_samples), or NULL
   int32_t* key[2];
   int32_t* pay[2];
   uint32_t* hist;                  // [total_tiles << radix_bits]
@@ -287,6 +288,8 @@ __device__ __forceinline__ void add_up_losses(const LossJob* job) {   // (the fi
 }
 
 // ------------------------------------------------------------- coalesce.hip
+// Whether launch_sort can do without sample indices, and work them out of the bags' boundaries (of a whole batch).
+bool sort_finds_samples(const SortPlan& pl, const SortBuffers& sb, const FieldPtr& fp);
 // Sorts every field's lookups by row id (stable); the result is in key / pay [*sorted_buf].
 hipError_t launch_sort(const SortPlan& pl, const SortBuffers& sb, const FieldPtr& fp, const TileBase& tb, Profiler* prof, hipStream_t s,
                        int* sorted_buf);

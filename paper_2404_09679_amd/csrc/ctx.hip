@@ -174,6 +174,7 @@ struct antdt_ctx {
   // The last batched step that sorted in its weight-gradient launch did not do so for nothing: an aggregation of all shards
   // followed.  Where none did (shards left out, only the gradients wanted) the next step leaves the sort to the aggregation.
   bool joined_sort_used = true;
+  bool samples_missing = false;   // a batched step left the lookups' sample indices to its sort, which needs none (see sample_indices)
   bool presorted = false;     // the coalescing structure of the current batch and split is built (or being built)
   bool side_pending = false;  // work is in flight on the side stream that no other stream has waited for yet
   // bound by antdt_bind_static: the workspace is the library's static device buffer and every
@@ -625,6 +626,7 @@ int antdt_set_batch(antdt_ctx* c, const int32_t* ids, const int64_t* field_ptr, 
     if (rc) return rc;
   }
   c->presorted = false;
+  c->samples_missing = false;
   memset(c->stepped, 0, sizeof(c->stepped));
   return ANTDT_OK;
 }
@@ -757,6 +759,7 @@ static void fill_sort(antdt_ctx* c, const int32_t* ids, const int32_t* pay0, Sor
   sb.digit_total = c->digit_total;
   sb.slots = c->goes_out;   // (the reduction's, which follows)
   sb.pay0 = pay0;
+  sb.offsets = nullptr;
 }
 
 // Sort the lookups by row id: everything of the server side that depends only on the batch's ids.
@@ -765,7 +768,31 @@ static int build_coalescing(antdt_ctx* c, const int32_t* ids, const int32_t* pay
   SortBuffers sb;
   fill_sort(c, ids, pay0, pl, sb);
   pl.beside = s == c->side;
+  if (!pay0) sb.offsets = c->offsets;
   HIP_TRY(c, launch_sort(pl, sb, c->afp, c->atb, prof_of(c), s, &c->sorted_buf));
+  return ANTDT_OK;
+}
+
+// Whether the sort beside a batched step finds the samples of the lookups by itself: by buckets it reads the lookups in the batch's order
+// once, and works them out of the bags' boundaries on the way.  Saves writing and reading them, but moves the sort further into the gather,
+// which wants the memory too (with a launch for the samples ahead / so, a step, us: 42 M lookups 2537 / 2499, 9 M 685 / 674; 6 M
+// 518 / 532, 4.1 M 501 / 503, 3.8 M 361 / 356, 3.2 M 413 / 427; behind the gather 42 M 2547 / 2517, 3.8 M 359 / 375).
+static constexpr int64_t FINDS_MIN = 8000000;
+static bool sort_beside_finds_samples(antdt_ctx* c) {
+  if (c->fp.p[c->m.num_fields] < FINDS_MIN) return false;
+  SortPlan pl;
+  SortBuffers sb;
+  coalesce_whole_batch(c);
+  fill_sort(c, c->ids, nullptr, pl, sb);
+  pl.beside = true;
+  return sort_finds_samples(pl, sb, c->afp);
+}
+
+// The sample index of every lookup, where the last batched step left none.
+static int sample_indices(antdt_ctx* c, hipStream_t s) {
+  if (!c->samples_missing) return ANTDT_OK;
+  HIP_TRY(c, launch_expand_samples(c->offsets, c->lookup_sample, c->fp, c->m.num_fields, (int)c->B, s));
+  c->samples_missing = false;
   return ANTDT_OK;
 }
 
@@ -928,7 +955,7 @@ static bool wgrad_in_pieces(const antdt_ctx* c) {
 }
 
 // Lookups from which the sort does not wait for the gather: the sample index of every lookup then comes from a launch of
-// its own on the sort's stream, one more for the host (behind / beside the gather, us per step: 26 fields, 1.1 M lookups 193 / 200,
+// its own on the sort's stream, one more for the host (or is not needed, see FINDS_MIN; behind / beside the gather, us per step: 26 fields, 1.1 M lookups 193 / 200,
 // 1.8 M 267 / 282, 2.5 M 361 / 357, 3.3 M 435 / 438, 4.3 M 521 / 515; 60 fields, 2.0 M 238 / 238, 3.8 M 397 / 385; 100, 42 M 2879 / 2820).
 static constexpr int64_t EARLY_MIN = 3000000;
 
@@ -957,7 +984,7 @@ static int worker_range(antdt_ctx* c, int k0, int k1, float* loss_out, hipStream
   c->batched = k0 == 0 && k1 == tab.K;
   c->left_out = false;
   const bool beside = c->batched && side_stream(c);
-  const bool early = beside && c->fp.p[m.num_fields] >= EARLY_MIN;
+  const bool finds = beside && sort_beside_finds_samples(c), early = beside && c->fp.p[m.num_fields] >= EARLY_MIN;
   if (early) HIP_TRY(c, hipEventRecord(c->ev_fork, s));
   {
     PoolArgs a;
@@ -970,6 +997,7 @@ static int worker_range(antdt_ctx* c, int k0, int k1, float* loss_out, hipStream
     ProfScope ps(pr, KID_POOL, s);
     HIP_TRY(c, launch_pool(a, c->fp, s));
   }
+  if (c->batched) c->samples_missing = finds;
   if (beside) {
     // All shards in one pass: the sort of the coming aggregate depends on the batch alone, so it runs beside the MLP
     // and, of large batches, beside the gather too (see EARLY_MIN).
@@ -978,8 +1006,8 @@ static int worker_range(antdt_ctx* c, int k0, int k1, float* loss_out, hipStream
     if (!early) HIP_TRY(c, hipEventRecord(c->ev_fork, s));
     HIP_TRY(c, hipStreamWaitEvent(c->side, c->ev_fork, 0));
     coalesce_whole_batch(c);
-    if (early) HIP_TRY(c, launch_expand_samples(c->offsets, c->lookup_sample, c->fp, m.num_fields, (int)c->B, c->side));
-    const int rc = build_coalescing(c, c->ids, c->lookup_sample, c->side);
+    if (early && !finds) HIP_TRY(c, launch_expand_samples(c->offsets, c->lookup_sample, c->fp, m.num_fields, (int)c->B, c->side));
+    const int rc = build_coalescing(c, c->ids, finds ? nullptr : c->lookup_sample, c->side);
     if (rc) return rc;
     HIP_TRY(c, hipEventRecord(c->ev_join, c->side));
     c->presorted = true;
@@ -1154,7 +1182,9 @@ int antdt_aggregate(antdt_ctx* c, const uint8_t* shard_mask, void* stream) {
   } else if (all) {
     set_weights(c);
     coalesce_whole_batch(c);
-    const int rc = build_coalescing(c, c->ids, c->lookup_sample, s);
+    int rc = sample_indices(c, s);
+    if (rc) return rc;
+    rc = build_coalescing(c, c->ids, c->lookup_sample, s);
     if (rc) return rc;
   } else {
     // Some shards are left out: pack the lookups of the others (the unique-id buffer serves as
@@ -1164,6 +1194,8 @@ int antdt_aggregate(antdt_ctx* c, const uint8_t* shard_mask, void* stream) {
     const int F = c->m.num_fields;
     int32_t* ids_in = c->uniq;
     int32_t* pay_in = c->pack_pay;
+    const int rcs = sample_indices(c, s);
+    if (rcs) return rcs;
     HIP_TRY(c, launch_mask_pack(c->ids, c->lookup_sample, c->offsets, c->B, F, c->fp, c->tab, c->cbase, ids_in,
                                 pay_in, s));
     int64_t cb[ANTDT_MAX_FIELDS + 1];

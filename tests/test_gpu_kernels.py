@@ -158,13 +158,15 @@ def test_sort_ahead_of_the_gather(how, bag):
 # lookups, none, one and a few; ids spread evenly, by frequency, in the first rows, in one, in some that are neighbours, at both ends, past a
 # multiple of 2^16 rows; buckets larger than a block holds (64 of them for 900 000 lookups of 1500 rows).  The sorted lookups are those
 # of a stable sort, one for one.
-@pytest.mark.parametrize("kind", ["even", "zipf", "first-rows", "one-row", "neighbours", "ends", "past-65536"])
+# From eight million on the sort also works the samples out of the bags' boundaries: bags of one, empty ones, one of all.
 @pytest.mark.parametrize("rows", [1500, 70_001, 1_100_000])
+@pytest.mark.parametrize("kind", ["even", "zipf", "first-rows", "one-row", "neighbours", "ends", "past-65536", "even-8M", "zipf-8M"])
 def test_sort_by_buckets(kind, rows):
     import torch
     import paper_2404_09679_amd as A
     dev, B = "cuda:0", 3001
-    sizes = [900_000, 0, 700_001, 1, 8193, 500_000]
+    kind, longest = (kind[:-3], 7_000_000) if kind.endswith("-8M") else (kind, 900_000)
+    sizes = [longest, 0, 700_001, 1, 8193, 500_000]
     cfg = _config(f"buckets-{kind}", 640, num_fields=len(sizes), rows_per_field=rows, dim=4, layer_sizes=(8,), gemm_dtype="f32", num_dense=0,
                   shard_sizes=(2000, B - 2000), max_bag=400)
     g = torch.Generator(device=dev).manual_seed(rows)
@@ -189,7 +191,13 @@ def test_sort_by_buckets(kind, rows):
     ids = [ids_of(n).int() for n in sizes]
     offsets = torch.zeros((len(sizes), B + 1), dtype=torch.int32, device=dev)
     for f, n in enumerate(sizes):
-        offsets[f, 1:B] = torch.sort(draw(0, n + 1, B - 1))[0].int()
+        cuts = draw(0, n + 1, B - 1)
+        if f == 0:     # bags of one lookup, and empty ones
+            cuts[:1000] = torch.arange(1000, device=dev) + 5000
+            cuts[1000:1300] = 70_000
+        if f == 5:     # one bag of nearly all
+            cuts %= 100
+        offsets[f, 1:B] = torch.sort(cuts)[0].int()
         offsets[f, B] = n
     tables = torch.randn((len(sizes) * rows, 4), generator=g, device=dev) * 0.05
     state = torch.ones_like(tables)
@@ -199,16 +207,30 @@ def test_sort_by_buckets(kind, rows):
     ptr = np.concatenate([[0], np.cumsum(sizes)]).tolist()
     ctx.set_batch(torch.cat(ids), ptr, offsets, None, (torch.rand(B, generator=g, device=dev) < 0.25).float())
     ctx.assign_shard(B, 2, sizes=[2000, B - 2000])
-    ctx.worker_step_all(torch.zeros(2, device=dev))
+    loss = torch.zeros(2, device=dev)
+    sample = [torch.repeat_interleave(torch.arange(B, device=dev), (offsets[f, 1:] - offsets[f, :-1]).long()) for f in range(len(sizes))]
+
+    def check(below):
+        for f in range(len(sizes)):
+            u, so, ss, _ = ctx.view_coalesced(f)
+            on = sample[f] < below
+            key, order = torch.sort(ids[f][on], stable=True)
+            rows_f, counts = torch.unique_consecutive(key, return_counts=True)
+            assert torch.equal(u.long(), rows_f.long()), (f, "rows")
+            assert torch.equal(so.long()[1:], torch.cumsum(counts, 0)) and int(so[0]) == 0, (f, "runs")
+            assert torch.equal(ss.long(), sample[f][on][order]), (f, "samples")
+
+    ctx.worker_step_all(loss)
     ctx.aggregate()
-    for f, n in enumerate(sizes):
-        u, so, ss, _ = ctx.view_coalesced(f)
-        key, order = torch.sort(ids[f], stable=True)
-        rows_f, counts = torch.unique_consecutive(key, return_counts=True)
-        sample = torch.repeat_interleave(torch.arange(B, device=dev), (offsets[f, 1:] - offsets[f, :-1]).long())
-        assert torch.equal(u.long(), rows_f.long()), (f, "rows")
-        assert torch.equal(so.long()[1:], torch.cumsum(counts, 0)) and int(so[0]) == 0, (f, "runs")
-        assert torch.equal(ss.long(), sample[order]), (f, "samples")
+    check(B)
+    # what follows a batched step finds the samples it left out: a shard stepped anew, a shard left out
+    ctx.worker_step_all(loss)
+    ctx.worker_step(1, loss[1:])
+    ctx.aggregate()
+    check(B)
+    ctx.worker_step_all(loss)
+    ctx.aggregate([1, 0])
+    check(2000)
 
 
 def test_gather_from_a_table_of_2_32_pieces():
