@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "common.h"
+#include "sort.h"
 
 namespace antdt {
 
@@ -1018,6 +1019,29 @@ static int worker_range(antdt_ctx* c, int k0, int k1, float* loss_out, hipStream
   auto weight = [&](int l) -> const void* {
     return c->act_bf16 ? (const void*)c->wb[l] : (const void*)(c->params + c->w_off[l]);
   };
+  // All shards of a bf16 model whose sort goes to no other stream, no field longer than a block takes in a pass: the passes run beside the products,
+  // one in a launch (behind / beside them, a step, us: 1024-512-256, 26 fields of 670 / 1000 / 2000 / 3200 / 3800 lookups 75.4 / 69.7, 72.8 / 67.6,
+  // 84.6 / 81.0, 90.1 / 87.5, 91.3 / 90.8, three passes of 1000 79.1 / 73.7; ten fields of 4100 91.1 / 90.8; 256-128, 26 of 1600 70.5 / 68.0;
+  // 1024-512, 30 of 3000 90.0 / 87.8).
+  const bool passes_join = c->act_bf16 && c->batched && !beside && c->total_tiles > 0 && c->joined_sort_used &&
+                           L > 1 && ns > 0 && passes_fit(m.num_fields, c->fp) && !prof_apart(pr, KID_GEMM_FWD, KID_SORT_SCATTER) &&
+                           !prof_apart(pr, KID_GEMM_BWD, KID_SORT_SCATTER);
+  SortPlan sort_plan;
+  SortBuffers sort_buffers;
+  SortPass sort_pass;
+  int sort_next = 0;   // pass
+  if (passes_join) {
+    coalesce_whole_batch(c);
+    fill_sort(c, c->ids, c->lookup_sample, sort_plan, sort_buffers);
+    plan_sort_pass(sort_plan, sort_buffers, c->fp, 0, sort_pass);
+  }
+  auto product = [&](const GemmArgs& g) {
+    const bool sorts = passes_join && sort_next < c->sort_passes;
+    bool took = false;
+    const hipError_t e = launch_gemm_and_sort(g, sorts ? &sort_pass : nullptr, &took, s);
+    if (took && ++sort_next < c->sort_passes) plan_sort_pass(sort_plan, sort_buffers, c->fp, sort_next, sort_pass);
+    return e;
+  };
   // the matrix products of each pass are timed as one bracket when they run back to back
   ProfScope fwd_scope(L > 1 ? pr : nullptr, KID_GEMM_FWD, s);
   fwd_scope.launches(L - 1);
@@ -1036,7 +1060,7 @@ static int worker_range(antdt_ctx* c, int k0, int k1, float* loss_out, hipStream
       g.B = c->params + c->w_off[l]; g.ldb = c->width[l + 1]; g.b_kc = 0;
     }
     g.epi = EPI_BIAS_RELU; g.bf16_in = c->act_bf16; g.bf16_out = c->act_bf16;
-    HIP_TRY(c, launch_gemm(g, s));
+    HIP_TRY(c, product(g));
   }
   fwd_scope.close();
   {
@@ -1122,10 +1146,21 @@ static int worker_range(antdt_ctx* c, int k0, int k1, float* loss_out, hipStream
       joined = g;
       joins = wgrad_takes_dgrad(u, k1 - k0, g, m.num_fields, sort ? &c->fp : nullptr);
     }
-    if (!joins) HIP_TRY(c, launch_gemm(g, s));
+    if (!joins) HIP_TRY(c, product(g));
     if (l == 1 && deferred) HIP_TRY(c, hipEventRecord(c->ev_dh[0], s));
   }
   bwd_scope.close();
+  if (passes_join) {
+    for (; sort_next < c->sort_passes; ++sort_next) {   // (no launch took it)
+      plan_sort_pass(sort_plan, sort_buffers, c->fp, sort_next, sort_pass);
+      HIP_TRY(c, launch_sort_pass_alone(sort_pass, pr, s));
+    }
+    c->sorted_buf = (c->sort_passes - 1) & 1;
+    c->joined_sort_used = false;
+    for (int k = 0; k < tab.K; ++k) c->included[k] = true;
+    set_weights(c);
+    c->presorted = true;
+  }
   if (!deferred) {
     if (sort) {
       c->joined_sort_used = false;

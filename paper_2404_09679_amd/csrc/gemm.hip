@@ -157,6 +157,18 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_bf16_kernel(GemmArgs p, int t
   gemm_bf16_tile<TM, TN, WR, WC, BK, STAGES, B_STRIDED, FAR, WAVES>(p, blockIdx.x, nblk, tiles_minor, m_minor, lds);
 }
 
+// The same with a pass of the sort of the coming aggregation in the first blocks, a field each: neither waits for the other, and a small
+// step's products leave most compute units idle (96 samples of 845-1024-512-256, 26 fields of 1000 lookups: the sort in a launch of its
+// own behind the products 8.7 us).
+template <int TM, int TN, int WR, int WC, int BK, int STAGES, bool B_STRIDED, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void gemm_bf16_sort_kernel(GemmArgs p, int tiles_minor, bool m_minor, SortPass sp) {
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  const int block = (int)blockIdx.x - sp.F, nblk = (int)gridDim.x - sp.F - p.loss_blocks;
+  if (block < 0) sort_pass_field<64 * WAVES>(sp, blockIdx.x, *reinterpret_cast<SortPassLds<64 * WAVES>*>(lds));
+  else if (block >= nblk) add_up_losses(p.loss + (block - nblk));
+  else gemm_bf16_tile<TM, TN, WR, WC, BK, STAGES, B_STRIDED, false, WAVES>(p, block, nblk, tiles_minor, m_minor, lds);
+}
+
 // Weight gradients of all hidden layers in one launch (see WgradArgs): block = one tile of one layer's
 //   [dW_l ; db_l] = [act_l ; 1]^T dH_{l+1}
 // over sample ranges; both operands are read as they lie in memory, [sample, width].
@@ -641,8 +653,24 @@ hipError_t launch_bf16(const GemmArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <int TM, int TN, int WR, int WC, int BK, int STAGES, bool BS, int WAVES>
+hipError_t launch_bf16_or_sort(const GemmArgs& a, const SortPass* sp, hipStream_t s) {
+  if (!sp) return launch_bf16<TM, TN, WR, WC, BK, STAGES, BS, false, WAVES>(a, s);
+  typedef BlockProduct<TM, TN, WR, WC, BK, STAGES, false, BS, false, WAVES> P;
+  constexpr int bytes = std::max(P::LDS_BYTES, (int)sizeof(SortPassLds<P::THREADS>));
+  static std::atomic<uint64_t> allowed{0};
+  const hipError_t ok = allow_lds(gemm_bf16_sort_kernel<TM, TN, WR, WC, BK, STAGES, BS, WAVES>, bytes, 0, allowed);
+  if (ok != hipSuccess) return ok;
+  const int tiles_m = (a.M + P::BM - 1) / P::BM, tiles_n = (a.N + P::BN - 1) / P::BN;
+  const bool m_minor = a.M < a.N;
+  hipLaunchKernelGGL((gemm_bf16_sort_kernel<TM, TN, WR, WC, BK, STAGES, BS, WAVES>), dim3(sp->F + tiles_m * tiles_n + a.loss_blocks), dim3(P::THREADS),
+                     bytes, s, a, m_minor ? tiles_m : tiles_n, m_minor, *sp);
+  return hipGetLastError();
+}
+
+// sp: a pass of the sort for the same launch (or NULL); *took: the launch has it (large tiles, and small ones of one wavefront, don't take it).
 template <bool BS>
-hipError_t launch_bf16_sized(const GemmArgs& a, hipStream_t s) {
+hipError_t launch_bf16_sized(const GemmArgs& a, const SortPass* sp, bool* took, hipStream_t s) {
   // A tile holds up to 256 rows of an operand (128 contraction slots of a strided one); its pieces are addressed by 32-bit
   // offsets where those reach.
   if (std::max(a.lda, a.ldb) * (256 * 2) >> 32) return launch_bf16<1, 1, 1, 1, 128, 3, BS, true>(a, s);
@@ -665,12 +693,16 @@ hipError_t launch_bf16_sized(const GemmArgs& a, hipStream_t s) {
   if (blocks(256, 256) >= 150) return launch_bf16<4, 2, 2, 4, 64, 2, BS>(a, s);
   if (blocks(128, 128) > 256) return launch_bf16<2, 1, 2, 4, 64, 2, BS>(a, s);
   if (blocks(128, 128) >= (BS ? 150 : 200)) return launch_bf16<2, 1, 2, 4, 64, 3, BS>(a, s);
-  if (blocks(32, 32) <= 256) return launch_bf16<1, 1, 1, 1, 128, 3, BS, false, 4>(a, s);
+  *took = sp != nullptr;
+  if (blocks(32, 32) <= 256) return launch_bf16_or_sort<1, 1, 1, 1, 128, 3, BS, 4>(a, sp, s);
   if constexpr (BS) {
-    if (blocks(32, 64) <= 256) return launch_bf16<1, 1, 1, 2, 128, 3, BS, false, 8>(a, s);
+    if (blocks(32, 64) <= 256) return launch_bf16_or_sort<1, 1, 1, 2, 128, 3, BS, 8>(a, sp, s);
   }
-  if (!BS && blocks(32, 32) <= 768) return launch_bf16<1, 1, 1, 1, 128, 3, BS>(a, s);
-  return launch_bf16<1, 1, 2, 2, 64, 3, BS>(a, s);
+  if (!BS && blocks(32, 32) <= 768) {
+    *took = false;
+    return launch_bf16<1, 1, 1, 1, 128, 3, BS>(a, s);
+  }
+  return launch_bf16_or_sort<1, 1, 2, 2, 64, 3, BS, 4>(a, sp, s);
 }
 
 bool f32_aligned(const void* x, int64_t ld) { return (ld & 3) == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0; }
@@ -829,9 +861,14 @@ hipError_t launch_wgrad_dgrad_tile(const WgradArgs& a, const KSegments& seg, con
 }  // namespace
 
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
+  bool took;
+  return launch_gemm_and_sort(a, nullptr, &took, s);
+}
+hipError_t launch_gemm_and_sort(const GemmArgs& a, const SortPass* sp, bool* took, hipStream_t s) {
+  *took = false;
   if (a.M <= 0 || a.N <= 0) return hipSuccess;
   if (!a.bf16_in) return launch_f32(a, s);
-  return a.b_kc ? launch_bf16_sized<false>(a, s) : launch_bf16_sized<true>(a, s);
+  return a.b_kc ? launch_bf16_sized<false>(a, sp, took, s) : launch_bf16_sized<true>(a, sp, took, s);
 }
 
 hipError_t launch_wgrad(const WgradArgs& a, const KSegments& seg, bool store, hipStream_t s) {

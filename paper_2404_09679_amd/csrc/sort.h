@@ -143,6 +143,104 @@ __device__ __forceinline__ void sort_small_field(SmallSortLds& lds, int32_t* sta
     }
 }
 
+// One pass of a field's sort by a block of a launch that does something else beside it (gemm.hip): up to PASS_KEYS lookups from memory to memory,
+// in the same stable order.
+constexpr int PASS_KEYS = 4096;
+struct SortPass {
+  const int32_t *keys_in, *pay_in;
+  int32_t *keys_out, *pay_out;
+  int32_t F, shift, rb;
+  FieldPtr fp;
+};
+template <int THREADS>
+struct SortPassLds {
+  uint16_t cnt[THREADS / 64][MAX_BINS];
+  uint16_t dpre[MAX_BINS];
+  uint32_t wsum[THREADS / 64];
+};
+template <int THREADS>
+__device__ __forceinline__ void sort_pass_field(const SortPass& sp, int f, SortPassLds<THREADS>& lds) {
+  constexpr int IT = PASS_KEYS / THREADS, WAVES = THREADS / 64, DIGITS = MAX_BINS / THREADS;   // digits of a thread: DIGITS threadIdx.x + q
+  const int64_t base = sp.fp.p[f];
+  const int n = (int)min(sp.fp.p[f + 1] - base, (int64_t)PASS_KEYS);
+  if (n == 0) return;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nb = 1 << sp.rb;
+  const int per = (n + THREADS - 1) / THREADS;   // <= IT; item i of wavefront w: position 64 (w per + i) + lane
+  const int first = w * (64 * per) + lane;
+  int32_t key[IT], pay[IT];
+#pragma unroll
+  for (int i = 0; i < IT; ++i)
+    if (i < per) {
+      const int pos = min(first + i * 64, n - 1);
+      key[i] = sp.keys_in[base + pos];
+      pay[i] = sp.pay_in[base + pos];
+    }
+  for (int d = lane; d < nb; d += 64) lds.cnt[w][d] = 0;   // (each wavefront its own row)
+  wave_lds_order();
+  const uint64_t lt = lanemask_lt();
+  uint32_t rank[IT];
+#pragma unroll
+  for (int i = 0; i < IT; ++i) {
+    rank[i] = 0;
+    if (i < per && w * (64 * per) + i * 64 < n) {   // (uniform)
+      const bool valid = first + i * 64 < n;
+      const uint32_t d = ((uint32_t)key[i] >> sp.shift) & (uint32_t)(nb - 1);
+      const uint64_t m = same_digit(d, sp.rb, valid);
+      const uint32_t prior = lds.cnt[w][d];
+      wave_lds_order();
+      rank[i] = prior + (uint32_t)__popcll(m & lt);
+      if (valid && (m & lt) == 0) lds.cnt[w][d] = (uint16_t)(prior + (uint32_t)__popcll(m));   // lowest lane of the group
+      wave_lds_order();
+    }
+  }
+  __syncthreads();
+  // per digit: exclusive prefix over the wavefronts, then over the digits
+  uint32_t tot[DIGITS], sum = 0;
+#pragma unroll
+  for (int q = 0; q < DIGITS; ++q) {
+    const int d = (int)threadIdx.x * DIGITS + q;
+    tot[q] = 0;
+    if (d < nb) {
+      uint32_t c[WAVES];
+#pragma unroll
+      for (int v = 0; v < WAVES; ++v) c[v] = lds.cnt[v][d];
+#pragma unroll
+      for (int v = 0; v < WAVES; ++v) {
+        lds.cnt[v][d] = (uint16_t)tot[q];
+        tot[q] += c[v];
+      }
+    }
+    sum += tot[q];
+  }
+  const uint32_t incl = wave_prefix(sum);
+  if (lane == 63) lds.wsum[w] = incl;
+  __syncthreads();
+  uint32_t before = incl - sum;
+  for (int q = 0; q < w; ++q) before += lds.wsum[q];
+#pragma unroll
+  for (int q = 0; q < DIGITS; ++q) {
+    const int d = (int)threadIdx.x * DIGITS + q;
+    if (d < nb) lds.dpre[d] = (uint16_t)before;
+    before += tot[q];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < IT; ++i)
+    if (i < per && first + i * 64 < n) {
+      const uint32_t d = ((uint32_t)key[i] >> sp.shift) & (uint32_t)(nb - 1);
+      const uint32_t place = lds.dpre[d] + lds.cnt[w][d] + rank[i];
+      if (place < (uint32_t)n) {
+        sp.keys_out[base + place] = key[i];
+        sp.pay_out[base + place] = pay[i];
+      }
+    }
+}
+inline bool passes_fit(int F, const FieldPtr& fp) {
+  for (int f = 0; f < F; ++f)
+    if (fp.p[f + 1] - fp.p[f] > PASS_KEYS) return false;
+  return true;
+}
+
 // Lookups per thread (2, 4, 8 or 16) that the longest field takes, 0 if it does not fit one block.
 inline int small_sort_items(int F, const FieldPtr& fp) {
   int64_t most = 0;

@@ -99,6 +99,21 @@ def test_sort_variants(most, rows, monkeypatch):
     check_iteration(cfg, cfg.shard_sizes, tol=TOL32, batched=True, nonzero_state=True)
 
 
+# bf16 models of a batched step: a pass of the sort in each of the first products' launches (tiles of 32 by four wavefronts, of 32 x 64 by eight and
+# of 64), up to 4096 lookups of a field; one pass, two, and three where two launches are all there are.
+@pytest.mark.parametrize("most", [1, 64, 257, 1025, 2048, 4096, 4097])
+@pytest.mark.parametrize("rows,hidden", [(900, (40,)), (70_000, (520, 264)), (70_000, (1032, 8)), (1_100_000, (264,))])
+def test_sort_beside_bf16_products(most, rows, hidden, monkeypatch):
+    sizes = [most, most - 1, 0, 1, 255, 1023]
+    F, B = (6, 500) if rows < 1_000_000 else (2, 500)
+    cfg = _config(f"sort-bf16-{most}", 650, num_fields=F, rows_per_field=rows, dim=4, layer_sizes=hidden, shard_sizes=(100, 0, 399, 1),
+                  max_bag=most // 400 + 1)
+    rng = np.random.default_rng(most + rows)
+    ids = [rng.integers(0, rows, n) // rng.integers(1, 9, n) for n in sizes[:F]]
+    _plant(monkeypatch, ids, B, lambda f, n: np.concatenate([[0], np.sort(rng.integers(0, n + 1, B - 1)), [n]]))
+    check_iteration(cfg, cfg.shard_sizes, tol=TOLBF, bf16_gemm_oracle=True, batched=True, nonzero_state=True)
+
+
 # The sort over many blocks (one field of more than 16384 lookups, ten tiles and a bit) with the other fields at the tile
 # boundaries, before and after shards are left out, and anew after a new split; mean-pooled.  All of these sort in the
 # aggregation; the long ones (of 100 000 lookups) of a batched step beside the MLP.
