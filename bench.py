@@ -85,6 +85,8 @@ def _bytes_and_flops(cfg, stats, model):
     fwd = sum(2 * B * s[l] * s[l + 1] for l in range(L - 1))
     dgrad = sum(2 * B * s[l + 1] * (s[l] if l > 0 else F * D) for l in range(L - 1))
     passes = model["sort_passes"]
+    # (large batches: one pass by ranges of rows, low bits and sample in a word, the rest of the sort in LDS)
+    by_ranges = passes > 1 and nnz >= 2_000_000
     gemm = "mfma" if cfg.gemm_dtype == "bf16" else "alu"
     out = {
         # ids, offsets, every distinct row once, pooled inputs and the sample index of every lookup for the sort
@@ -93,8 +95,8 @@ def _bytes_and_flops(cfg, stats, model):
         "gemm_bwd": (gemm, dgrad),           # the data-gradient chain on the launch stream
         "gemm_wgrad": (gemm, fwd),
         "wgrad_adagrad": (gemm, fwd),    # weight gradients with the aggregation and dense Adagrad in the epilogue
-        "sort_hist": ("hbm", passes * 4 * nnz),
-        "sort_scatter": ("hbm", 4 * nnz + 8 * nnz + (passes - 1) * 16 * nnz),
+        "sort_hist": ("hbm", (1 if by_ranges else passes) * 4 * nnz),
+        "sort_scatter": ("hbm", (8 + 4 + 4 + 8) * nnz if by_ranges else 4 * nnz + 8 * nnz + (passes - 1) * 16 * nnz),
         "seg_heads": ("hbm", 4 * nnz),
         "seg_emit": ("hbm", 4 * nnz + 8 * U),
         # one fused kernel: segmented sum of the per-lookup gradient rows + row-sparse Adagrad

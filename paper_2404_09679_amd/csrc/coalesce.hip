@@ -1,6 +1,6 @@
 // Server-side coalescing of the pushed sparse gradients (Section II: the servers combine
-// the gradients of all workers): per field, a stable LSD radix
-// sort of (row id, sample index) pairs, detection of the runs of equal ids
+// the gradients of all workers): per field, a stable sort of (row id, sample index) pairs
+// (LSD radix, of large batches by ranges of rows), detection of the runs of equal ids
 // (unique ids + segment offsets), and the weighted segmented reduction
 //   G[u, :] = sum over the run of w(sample) * dX[sample, field slice].
 // No floating-point atomics are used, so the sums are bitwise repeatable.  The reduction can
