@@ -70,6 +70,7 @@ struct BucketPlan {
   int32_t B;
   FieldBuckets* fields;
   int32_t* large;       // [0]: number of buckets of more than BUCKET_KEYS lookups and one row, then those (field, bucket)
+  int32_t most_large;   // no more of them
   // (ids that are no rows go where the update takes them to be: the first row, the last one)
   __device__ __forceinline__ int32_t in_range(int32_t key) const { return min(max(key, 0), last_row); }
   __device__ __forceinline__ uint32_t bucket(const FieldBuckets& fb, int32_t key) const {
@@ -318,8 +319,10 @@ __global__ __launch_bounds__(SCAN_THREADS) void sort_scan_kernel(uint32_t* hist,
   walk(run, true);
   if (part == 0) {
     digit_total[((int64_t)f << rb) + d] = total;
-    if (BUCKETS && total > (uint32_t)BUCKET_KEYS && bp.fields[f].first[d + 1] - bp.fields[f].first[d] > 1)
-      bp.large[1 + atomicAdd(bp.large, 1)] = f << 16 | d;   // (in any order: each is a block's work)
+    if (BUCKETS && total > (uint32_t)BUCKET_KEYS && bp.fields[f].first[d + 1] - bp.fields[f].first[d] > 1) {
+      const int at = atomicAdd(bp.large, 1);
+      if (at < bp.most_large) bp.large[1 + at] = f << 16 | d;   // (in any order: each is a block's work)
+    }
   }
 }
 
@@ -690,7 +693,7 @@ __global__ __launch_bounds__(BUCKET_THREADS) void sort_buckets_kernel(const int3
   int64_t at;
   int n;
   if ((int)blockIdx.x < large_blocks) {
-    const int count = bp.large[0];
+    const int count = min(bp.large[0], bp.most_large);
     for (int i = blockIdx.x; i < count; i += large_blocks) {
       const int f = bp.large[1 + i] >> 16, b = bp.large[1 + i] & 0xFFFF;
       place(f, b, at, n);
@@ -1535,7 +1538,7 @@ static int bits_of(int64_t n) {   // of the numbers below n
 // frequency: 3.8 M 362 / 340, 20 M 1490 / 1387).
 static constexpr int64_t BUCKETS_MIN = 6000000, BUCKETS_MIN_BESIDE = 2000000;
 static bool plan_buckets(const SortPlan& pl, const SortBuffers& sb, const FieldPtr& fp, BucketPlan& bp) {
-  if (pl.passes < 2 || fp.p[pl.F] < (pl.beside ? BUCKETS_MIN_BESIDE : BUCKETS_MIN)) return false;
+  if (!sb.slots || pl.passes < 2 || fp.p[pl.F] < (pl.beside ? BUCKETS_MIN_BESIDE : BUCKETS_MIN)) return false;
   int64_t most = 0;
   for (int f = 0; f < pl.F; ++f) most = std::max(most, fp.p[f + 1] - fp.p[f]);
   bp.sample_bits = bits_of(pl.samples);
@@ -1551,7 +1554,8 @@ static bool plan_buckets(const SortPlan& pl, const SortBuffers& sb, const FieldP
   constexpr int64_t WORDS = sizeof(FieldBuckets) / 4;
   bp.fields = reinterpret_cast<FieldBuckets*>(sb.slots);
   bp.large = sb.slots + WORDS * pl.F;
-  return WORDS * pl.F + 1 + fp.p[pl.F] / (BUCKET_KEYS + 1) <= window_slots(fp.p[pl.F]);
+  bp.most_large = (int32_t)(fp.p[pl.F] / (BUCKET_KEYS + 1));
+  return WORDS * pl.F + 1 + bp.most_large <= window_slots(fp.p[pl.F]);
 }
 static hipError_t launch_sort_buckets(const SortPlan& pl, const SortBuffers& sb, const FieldPtr& fp, const TileBase& tb, const BucketPlan& bp,
                                       Profiler* prof, hipStream_t s) {
@@ -1570,7 +1574,7 @@ static hipError_t launch_sort_buckets(const SortPlan& pl, const SortBuffers& sb,
   ProfScope ps(prof, KID_SORT_SCATTER, s);
   hipLaunchKernelGGL(sort_scatter_kernel<true>, grid, dim3(SORT_THREADS), 0, s, sb.ids, sb.pay0, sb.key[0], sb.pay[0], sb.key[1], sb.hist,
                      sb.digit_total, fp, tb, pl.F, 0, bp.rb, bp);
-  const int large_blocks = (int)std::min<int64_t>((fp.p[pl.F] / (BUCKET_KEYS + 1) + 7) / 8 * 8, 1024);   // (the others keep their XCDs)
+  const int large_blocks = std::min((bp.most_large + 7) / 8 * 8, 1024);   // (the others keep their XCDs)
   hipLaunchKernelGGL(sort_buckets_kernel, dim3(large_blocks + 8 * (((pl.F << bp.rb) + 7) / 8)), dim3(BUCKET_THREADS), 0, s, sb.key[1], sb.pay[1],
                      sb.key[0], sb.pay[0], sb.digit_total, fp, pl.F, large_blocks, bp);
   ps.launches(2);

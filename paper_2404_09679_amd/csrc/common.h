@@ -191,7 +191,7 @@ struct SortBuffers {
   int32_t* pay[2];
   uint32_t* hist;                  // [total_tiles << radix_bits]
   uint32_t* digit_total;            // [F << radix_bits]
-  int32_t* slots;                  // scratch, a word per slot of the windows (window_slots)
+  int32_t* slots;                  // scratch, a word per slot of the windows (window_slots), or NULL: none that is free
 };
 // Weight gradients of all layers in one launch (see wgrad_kernel, wgrad_f32_kernel): per range written to
 // the shards' flat gradients, or aggregated and applied (Adagrad) on the spot, in which case neither

@@ -175,6 +175,7 @@ struct antdt_ctx {
   // The last batched step that sorted in its weight-gradient launch did not do so for nothing: an aggregation of all shards
   // followed.  Where none did (shards left out, only the gradients wanted) the next step leaves the sort to the aggregation.
   bool joined_sort_used = true;
+  bool slots_apart = false;       // the loss kernel's sums and jobs end before the windows' slots (see carve)
   bool samples_missing = false;   // a batched step left the lookups' sample indices to its sort, which needs none (see sample_indices)
   bool presorted = false;     // the coalescing structure of the current batch and split is built (or being built)
   bool side_pending = false;  // work is in flight on the side stream that no other stream has waited for yet
@@ -311,7 +312,8 @@ static size_t carve(antdt_ctx* c, char* base) {
   c->vflags = (int32_t*)(small ? small + counts : nullptr);
   c->loss_job = (LossJob*)(small ? small + counts + 8 : nullptr);
   // The loss kernel's sums and jobs.  Of an fp32 model without a hidden layer they share memory with what only an
-  // aggregation and what follows it use: the worker step itself reads them last (in bf16 models apply_update does).
+  // aggregation and what follows it use: the worker step itself reads them last (in bf16 models apply_update does).  What else runs
+  // beside a worker step keeps away from there (see slots_apart).
   // Where that is too small for sums over tiles (few lookups, many dense features), or where those of a bf16 model
   // without a hidden layer would take more than its inputs (most shards hold one sample), they are kept per sample instead,
   // and the last layer's gradient is added up from the samples.
@@ -330,13 +332,16 @@ static size_t carve(antdt_ctx* c, char* base) {
   c->segoff = (int32_t*)take((size_t)(N + m.num_fields + 1) * 4);
   c->pack_pay = (int32_t*)take((size_t)N * 4);
   c->segabs = (int32_t*)take((size_t)(N + 1) * 4);
-  c->goes_out = (int32_t*)take((size_t)window_slots(N) * 4);
   c->partial = (float*)take((size_t)window_slots(N) * 2 * m.dim * 4);
   c->G = (float*)take((size_t)N * m.dim * 4);
+  // (last: a batched step's sort has its tables there, beside the worker step, which the sums above seldom reach)
+  const size_t slots = off;
+  c->goes_out = (int32_t*)take((size_t)window_slots(N) * 4);
   if (share && behind > off) {
     c->sums_per_sample = true;
     behind = align_up(sums + (size_t)Bm * 8, 256);
   }
+  c->slots_apart = !share || behind <= slots;
   return std::max(off, behind);
 }
 
@@ -749,16 +754,17 @@ static void set_weights(antdt_ctx* c) {
   c->weights_dirty = false;
 }
 
-static void fill_sort(antdt_ctx* c, const int32_t* ids, const int32_t* pay0, SortPlan& pl, SortBuffers& sb) {
+// beside: the sort runs beside the worker step (on the side stream).
+static void fill_sort(antdt_ctx* c, const int32_t* ids, const int32_t* pay0, SortPlan& pl, SortBuffers& sb, bool beside = false) {
   const antdt_model& m = c->m;
   pl.F = m.num_fields; pl.passes = c->sort_passes; pl.radix_bits = c->radix_bits;
   pl.total_tiles = c->atotal_tiles;
-  pl.rows = m.rows_per_field; pl.samples = c->B; pl.beside = false;
+  pl.rows = m.rows_per_field; pl.samples = c->B; pl.beside = beside;
   sb.ids = ids;
   sb.key[0] = c->key[0]; sb.key[1] = c->key[1]; sb.pay[0] = c->pay[0]; sb.pay[1] = c->pay[1];
   sb.hist = c->hist;
   sb.digit_total = c->digit_total;
-  sb.slots = c->goes_out;   // (the reduction's, which follows)
+  sb.slots = beside && !c->slots_apart ? nullptr : c->goes_out;   // (the reduction's, which follows)
   sb.pay0 = pay0;
   sb.offsets = nullptr;
 }
@@ -767,8 +773,7 @@ static void fill_sort(antdt_ctx* c, const int32_t* ids, const int32_t* pay0, Sor
 static int build_coalescing(antdt_ctx* c, const int32_t* ids, const int32_t* pay0, hipStream_t s) {
   SortPlan pl;
   SortBuffers sb;
-  fill_sort(c, ids, pay0, pl, sb);
-  pl.beside = s == c->side;
+  fill_sort(c, ids, pay0, pl, sb, c->side && s == c->side);
   if (!pay0) sb.offsets = c->offsets;
   HIP_TRY(c, launch_sort(pl, sb, c->afp, c->atb, prof_of(c), s, &c->sorted_buf));
   return ANTDT_OK;
@@ -784,8 +789,7 @@ static bool sort_beside_finds_samples(antdt_ctx* c) {
   SortPlan pl;
   SortBuffers sb;
   coalesce_whole_batch(c);
-  fill_sort(c, c->ids, nullptr, pl, sb);
-  pl.beside = true;
+  fill_sort(c, c->ids, nullptr, pl, sb, true);
   return sort_finds_samples(pl, sb, c->afp);
 }
 

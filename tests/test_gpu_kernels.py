@@ -248,6 +248,76 @@ def test_sort_by_buckets(kind, rows):
     check(2000)
 
 
+# An fp32 model without a hidden layer, whose loss kernel's sums share memory with what follows the worker step, and enough lookups that the sort
+# beside it goes by buckets: sums that end where the reduction's memory has not ended, and (69 088 samples) where its last part, which the sort
+# takes too, has begun.  Against float64.
+@pytest.mark.parametrize("dim,B", [(16, 40_000), (4, 69_088)])
+def test_sort_beside_a_model_without_hidden_layer(dim, B):
+    import torch
+    import paper_2404_09679_amd as A
+    dev, F, rows, num_dense, sizes = "cuda:0", 2, 60_000, 4096, [900_001, 1_299_999]
+    shards = [B // 2, 0, 7, B // 3, B - B // 2 - 7 - B // 3]
+    cfg = _config(f"head-{B}", 641, num_fields=F, rows_per_field=rows, dim=dim, layer_sizes=(), gemm_dtype="f32", num_dense=num_dense,
+                  shard_sizes=shards, max_bag=400)
+    g = torch.Generator(device=dev).manual_seed(B)
+    ids = [(torch.rand(n, generator=g, device=dev) ** 3 * rows).int() for n in sizes]
+    offsets = torch.zeros((F, B + 1), dtype=torch.int32, device=dev)
+    for f, n in enumerate(sizes):
+        offsets[f, 1:B] = torch.sort(torch.randint(0, n + 1, (B - 1,), generator=g, device=dev))[0].int()
+        offsets[f, B] = n
+    width = F * dim + num_dense
+    tables = torch.randn((F * rows, dim), generator=g, device=dev) * 0.05
+    state = torch.full_like(tables, 1e-12)   # (accumulators as large as the squared gradients)
+    params = torch.randn(width + 1, generator=g, device=dev) * width ** -0.5
+    pstate = torch.full_like(params, 1e-5)
+    dense = torch.randn((B, num_dense), generator=g, device=dev)
+    labels = (torch.rand(B, generator=g, device=dev) < 0.25).float()
+    ctx = A.Context(A.model_from_config(cfg, max_batch=B, max_nnz=sum(sizes), max_shards=len(shards)))
+    ctx.bind(tables, state, params, pstate)
+    ctx.set_batch(torch.cat(ids), [0, sizes[0], sum(sizes)], offsets, dense, labels)
+    ctx.assign_shard(B, len(shards), sizes=shards)
+    # the step in float64
+    sample = [torch.repeat_interleave(torch.arange(B, device=dev), (offsets[f, 1:] - offsets[f, :-1]).long()) for f in range(F)]
+    x = torch.zeros((B, width), dtype=torch.float64, device=dev)
+    for f in range(F):
+        x[:, f * dim:(f + 1) * dim].index_add_(0, sample[f], tables[f * rows + ids[f].long()].double())
+    x[:, F * dim:] = dense
+    w = params.double()
+    z = x @ w[:width] + w[width]
+    losses = torch.nn.functional.binary_cross_entropy_with_logits(z, labels.double(), reduction="none")
+    starts = np.concatenate([[0], np.cumsum(shards)])
+    dz = torch.sigmoid(z) - labels.double()
+    want_loss, want_grad, total = [], torch.zeros(width + 1, dtype=torch.float64, device=dev), torch.zeros(B, dtype=torch.float64, device=dev)
+    for k, n in enumerate(shards):
+        at = slice(int(starts[k]), int(starts[k + 1]))
+        want_loss.append(float(losses[at].mean()) if n else 0.0)
+        want_grad += torch.cat([x[at].T @ dz[at], dz[at].sum()[None]]) / B   # (weight n / B, mean over n)
+        total[at] = dz[at] / B
+    rel = lambda a, b: float((a.double() - b).norm() / b.norm())
+    old = tables.double()
+    want = old.clone()
+    for f in range(F):
+        gr = torch.zeros((rows, dim), dtype=torch.float64, device=dev)
+        gr.index_add_(0, ids[f].long(), total[sample[f]][:, None] * w[None, f * dim:(f + 1) * dim])
+        want[f * rows:(f + 1) * rows] -= cfg.lr * gr / ((1e-12 + gr * gr).sqrt() + cfg.eps)
+    loss = torch.zeros(len(shards), device=dev)
+    for _ in range(3):
+        ctx.worker_step_all(loss)
+        ctx.aggregate()
+        assert np.allclose(loss.cpu().numpy(), want_loss, rtol=1e-5)
+        assert rel(ctx.view_dense_grad(), want_grad) < 1e-5
+        for f in range(F):
+            u, so, ss, _ = ctx.view_coalesced(f)
+            key, order = torch.sort(ids[f], stable=True)
+            rows_f, counts = torch.unique_consecutive(key, return_counts=True)
+            assert torch.equal(u, rows_f) and torch.equal(so.long()[1:], torch.cumsum(counts, 0)) and torch.equal(ss.long(), sample[f][order])
+    ctx.apply_update()
+    torch.cuda.synchronize()
+    # (a step grows no faster than its gradient; rows of 0.05 are rounded to 2e-9 behind steps of 1e-3 and more)
+    assert rel(tables.double() - old, want - old) < 1e-5
+    assert rel(w - params.double(), cfg.lr * want_grad / ((1e-5 + want_grad ** 2).sqrt() + cfg.eps)) < 1e-5
+
+
 def test_gather_from_a_table_of_2_32_pieces():
     """2^30 rows of 64 bytes: places of rows no longer fit 32 bits.  Pooled inputs and updated rows against torch, the rows
     2^28, 2^29, ... away from the looked-up ones against their initial values."""

@@ -391,3 +391,94 @@ def test_packing_deals_every_lookup_once(tmp_path):
     for n in (0, 1, 255, 1024, 1025, 8191, 8192, 8193, 100_000, 2 ** 31 - 8191, most):
         r = subprocess.run([str(program), str(n)], capture_output=True, text=True, timeout=120)
         assert r.returncode == 0, r.stdout
+
+
+STEP_MEMORY = r"""
+#include "ctx.hip"
+#include <cstdio>
+using namespace antdt;
+struct Part { const char* name; const char* at; size_t bytes; };
+int main() {
+  int plans = 0, by_buckets = 0, refused = 0, bad = 0;
+  for (int gemm : {ANTDT_F32, ANTDT_BF16})
+  for (int hidden : {0, 64})
+  for (int fields : {1, 2, 26, 100})
+  for (int dim : {4, 16, 128, 256})
+  for (int num_dense : {0, 13, 600, 4096})
+  for (int64_t lookups : {100000, 2100000, 3400000, 9000000, 42000000}) {
+    int64_t to_slots = 0;   // batch whose sums would end among the slots
+    for (int64_t batch : {5000, 40000, 100000, 400000, 0}) {
+    if (batch == 0) batch = std::min<int64_t>(std::max<int64_t>(to_slots, 1000), 100000000);
+    antdt_model m = {};
+    m.num_fields = fields; m.dim = dim; m.rows_per_field = 60000; m.num_dense = num_dense; m.gemm_dtype = gemm;
+    m.max_batch = batch; m.max_nnz = lookups; m.max_shards = 8; m.lr = 0.1f; m.eps = 1e-8f;
+    m.layer_sizes[m.num_layers++] = fields * dim + num_dense;
+    if (hidden) m.layer_sizes[m.num_layers++] = hidden;
+    m.layer_sizes[m.num_layers] = 1;
+    antdt_ctx* c;
+    if (antdt_create(&m, &c)) return std::puts(antdt_last_error(nullptr)), 2;
+    char* const base = (char*)(1ull << 40);
+    const size_t bytes = carve(c, base);
+    to_slots = (((char*)c->goes_out - (char*)c->head_part + window_slots(lookups) * 2) / (c->ldpart * 4) - m.max_shards) * HEAD_TILE;
+    c->B = batch;
+    for (int f = 0; f < fields; ++f) c->fp.p[f + 1] = lookups * (f + 1) / fields;
+    for (int f = fields; f < ANTDT_MAX_FIELDS; ++f) c->fp.p[f + 1] = c->fp.p[f];
+    plan_tiles(fields, c->fp, c->tb, c->total_tiles);
+    coalesce_whole_batch(c);
+    SortPlan pl;
+    SortBuffers sb;
+    fill_sort(c, nullptr, c->lookup_sample, pl, sb, true);
+    const bool buckets = sort_finds_samples(pl, sb, c->afp);
+    SortPlan pl_any;
+    SortBuffers sb_any;
+    fill_sort(c, nullptr, c->lookup_sample, pl_any, sb_any, false);
+    pl_any.beside = true;
+    ++plans;
+    by_buckets += buckets;
+    refused += !buckets && sort_finds_samples(pl_any, sb_any, c->afp);
+    const size_t N = lookups, tiles = std::min(batch, batch / HEAD_TILE + m.max_shards);
+    std::vector<Part> sort = {{"lookup_sample", (char*)c->lookup_sample, N * 4}, {"key 0", (char*)sb.key[0], N * 4}, {"key 1", (char*)sb.key[1], N * 4},
+                              {"pay 0", (char*)sb.pay[0], N * 4}, {"pay 1", (char*)sb.pay[1], N * 4},
+                              {"hist", (char*)sb.hist, ((size_t)c->total_tiles << c->radix_bits) * 4},
+                              {"digit_total", (char*)sb.digit_total, ((size_t)fields << c->radix_bits) * 4}};
+    if (buckets) sort.push_back({"slots", (char*)sb.slots, (size_t)window_slots(lookups) * 4});
+    std::vector<Part> step = {{"x", c->x, (size_t)batch * c->ldx * c->act_size}, {"dx", (char*)c->dx, (size_t)batch * c->FD * 4},
+                              {"shard_grads", (char*)c->shard_grads, (size_t)m.max_shards * c->Pstride * 4},
+                              {"loss_job", (char*)c->loss_job, m.max_shards * sizeof(LossJob)},
+                              {"head_part", (char*)c->head_part, c->sums_per_sample ? (size_t)batch * 8 : tiles * c->ldpart * 4}};
+    for (int l = 1; l < c->L; ++l) {
+      step.push_back({"h", c->h[l], (size_t)batch * c->width[l] * c->act_size});
+      step.push_back({"dh", c->dh[l], (size_t)batch * c->width[l] * c->act_size});
+    }
+    for (const Part& a : sort)
+      for (const Part& b : step)
+        if ((a.at < b.at + b.bytes && b.at < a.at + a.bytes) || a.at + a.bytes > base + bytes || b.at + b.bytes > base + bytes) {
+          if (++bad < 20)
+            std::printf("%s [%zu, %zu) of the sort and %s [%zu, %zu) of the step, of %zu: products %d, hidden %d, %d fields of %d, %d dense features, %lld samples, %zu lookups\n",
+                        a.name, (size_t)(a.at - base), (size_t)(a.at + a.bytes - base), b.name, (size_t)(b.at - base), (size_t)(b.at + b.bytes - base), bytes, gemm, hidden,
+                        fields, dim, num_dense, (long long)batch, N);
+        }
+    antdt_destroy(c);
+    }
+  }
+  std::printf("%d plans, %d by buckets, %d for want of memory not, %d overlaps\n", plans, by_buckets, refused, bad);
+  return bad != 0 || by_buckets == 0 || refused == 0;
+}
+"""
+
+
+def test_sort_of_a_batched_step_keeps_off_the_memory_of_the_step(tmp_path):
+    """The sort runs on a stream of its own beside the MLP, so nothing that it writes may be what the worker step reads or writes; models without a
+    hidden layer too, whose loss kernel shares memory with the aggregation."""
+    import importlib.util
+    spec = importlib.util.spec_from_file_location("antdt_build", os.path.join(ROOT, "paper_2404_09679_amd", "build.py"))
+    build = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(build)
+    source, program = tmp_path / "memory.hip", tmp_path / "memory"
+    source.write_text(STEP_MEMORY)
+    flags = [f for f in build.FLAGS if f not in ("-O3", "-Wall")] + ["-O1", "-w"]
+    subprocess.run([build.HIPCC] + flags + ["-c", str(source), "-o", str(program) + ".o"], check=True, capture_output=True)
+    subprocess.run([build.HIPCC, "--offload-arch=gfx950", str(program) + ".o", "-o", str(program), "-L", build.HERE, "-l:libantdt_hip.so",
+                    "-Wl,-rpath," + build.HERE], check=True, capture_output=True)
+    r = subprocess.run([str(program)], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout + r.stderr
