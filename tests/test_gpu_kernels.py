@@ -248,6 +248,48 @@ def test_sort_by_buckets(kind, rows):
     check(2000)
 
 
+# Bags of one length in a batch of a multiple of 1024 samples: evenly spaced lookups are then all at one place of their bags, and where the ids have
+# an order in the bag, rows cut by those alone make ranges of most of the lookups, a block's work each.  The sort takes about as long
+# as that of the same ids in random order (several times as long, were most in one range), and gives the same.
+@pytest.mark.parametrize("B,bag,rows", [(16_384, 50, 50_000), (8192, 100, 1_100_000)])
+@pytest.mark.parametrize("order", ["ascending", "first", "padded"])
+def test_sort_by_buckets_of_bags_of_one_length(order, B, bag, rows):
+    import torch
+    import paper_2404_09679_amd as A
+    dev, F = "cuda:0", 3
+    cfg = _config(f"bags-{bag}", 642, num_fields=F, rows_per_field=rows, dim=4, layer_sizes=(8,), gemm_dtype="f32", num_dense=0, shard_sizes=(B,), max_bag=bag)
+    g = torch.Generator(device=dev).manual_seed(bag)
+    even = torch.randint(0, rows, (F, B, bag), generator=g, device=dev).int()
+    ids = {"ascending": torch.sort(even, dim=2)[0], "first": torch.cat([torch.full_like(even[:, :, :1], rows // 2), even[:, :, 1:]], 2),
+           "padded": torch.where(torch.arange(bag, device=dev) < torch.randint(1, bag, (F, B, 1), generator=g, device=dev), even, 0)}[order]
+    mixed = torch.stack([t.flatten()[torch.randperm(B * bag, generator=g, device=dev)] for t in ids]).flatten().contiguous()
+    offsets = (torch.arange(B + 1, dtype=torch.int32, device=dev) * bag).repeat(F, 1).contiguous()
+    tables = torch.randn((F * rows, 4), generator=g, device=dev) * 0.05
+    params = torch.randn(sum(i * o + o for i, o in zip((12, 8), (8, 1))), generator=g, device=dev) * 0.3
+    ctx = A.Context(A.model_from_config(cfg, max_batch=B, max_nnz=F * B * bag, max_shards=1))
+    ctx.bind(tables, torch.ones_like(tables), params, torch.ones_like(params))
+    labels, loss = (torch.rand(B, generator=g, device=dev) < 0.25).float(), torch.zeros(1, device=dev)
+    kid = A.kernel_names().index("sort_scatter")
+    took = []
+    for x in (mixed, ids.flatten().contiguous()):
+        ctx.set_batch(x, [f * B * bag for f in range(F + 1)], offsets, None, labels)
+        ctx.assign_shard(B, 1)
+        times = []
+        for _ in range(5):
+            ctx.profile(2, kid)
+            ctx.worker_step_all(loss)
+            ctx.aggregate()
+            times.append(ctx.profile_read(kid)[1])
+            ctx.profile(0)
+        took.append(min(times))
+    for f in range(F):
+        key, at = torch.sort(ids[f].flatten(), stable=True)
+        u, so, ss, _ = ctx.view_coalesced(f)
+        rows_f, counts = torch.unique_consecutive(key, return_counts=True)
+        assert torch.equal(u, rows_f) and torch.equal(so.long()[1:], torch.cumsum(counts, 0)) and torch.equal(ss.long(), at // bag)
+    assert took[1] < 2 * took[0], took
+
+
 # An fp32 model without a hidden layer, whose loss kernel's sums share memory with what follows the worker step, and enough lookups that the sort
 # beside it goes by buckets: sums that end where the reduction's memory has not ended, and (69 088 samples) where its last part, which the sort
 # takes too, has begun.  Against float64.
