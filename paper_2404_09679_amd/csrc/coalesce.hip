@@ -1549,9 +1549,23 @@ static int bits_of(int64_t n) {   // of the numbers below n
 // 507 / 496, 42 M 2738 / 2536; 1.5 M 251 / 253.  The buckets follow a sample of the lookups, so neither how the hot rows lie matters (ids in
 // order of their frequency: 3.8 M 362 / 340, 20 M 1490 / 1387) nor an order of the ids in their bags (60 fields of 4096 bags of 50 lookups, at random / ascending /
 // padded with row 0: 561 / 500, 560 / 499, 551 / 485).
-static constexpr int64_t BUCKETS_MIN = 6000000, BUCKETS_MIN_BESIDE = 2000000;
+// Two passes cost little, most of all of short digits, and the sort by buckets is then the longer chain: it pays where it is long all the same, or
+// where it saves memory traffic from a gather that takes long.  A step with the sort beside it, by passes / by buckets:
+//   Digits of up to 9 bits (2^18 rows): 20 fields of 4096 samples, 256-128, 2.5 / 4.5 / 6.5 / 10 / 16 M lookups 136 / 149, 163 / 176, 198 / 212, 288 / 287,
+//   451 / 408, 1024-512-256 179 / 187, 210 / 212, 247 / 249, 335 / 309, 494 / 450; three of 8192 3.2 / 6.5 M 202 / 238, 295 / 319; everything on one stream, eight
+//   fields, 6.2 / 9.5 M 280 / 298, 384 / 376.  Many pooled inputs: 39 fields of 16 columns, 16384 samples, 64 in fp32, 4.5 M 247 / 258; 26 of 32, 16384, 256-128,
+//   3.2 / 6.5 M 249 / 204, 300 / 249; 60 of 64, 4096, 64 in fp32, 4.5 M 395 / 308.
+//   Of 10 bits: three fields of 8192 samples, 256-128, 2.1 / 3.2 / 4.5 M 183 / 196, 222 / 236, 249 / 253; six of 4096 3.2 M 181 / 192; eight of 8192 2.1 / 3.2 / 4.5 M
+//   147 / 145, 175 / 160, 198 / 174.
+static constexpr int64_t BUCKETS_MIN = 6000000, BUCKETS_MIN_BESIDE = 2000000, BUCKETS_MIN_SHORT = 8000000, BUCKETS_MIN_TWO = 3500000,
+                         MANY_POOLED = 12000000;
+static int64_t buckets_min(const SortPlan& pl) {
+  const int64_t least = pl.beside ? BUCKETS_MIN_BESIDE : BUCKETS_MIN;
+  if (pl.passes > 2 || (pl.beside && pl.samples * pl.width >= MANY_POOLED)) return least;
+  return std::max(least, pl.radix_bits <= 9 ? BUCKETS_MIN_SHORT : BUCKETS_MIN_TWO);
+}
 static bool plan_buckets(const SortPlan& pl, const SortBuffers& sb, const FieldPtr& fp, BucketPlan& bp) {
-  if (!sb.slots || pl.passes < 2 || fp.p[pl.F] < (pl.beside ? BUCKETS_MIN_BESIDE : BUCKETS_MIN)) return false;
+  if (!sb.slots || pl.passes < 2 || fp.p[pl.F] < buckets_min(pl)) return false;
   int64_t most = 0;
   for (int f = 0; f < pl.F; ++f) most = std::max(most, fp.p[f + 1] - fp.p[f]);
   bp.sample_bits = bits_of(pl.samples);

@@ -181,6 +181,7 @@ struct SortPlan {
   int32_t passes, radix_bits;      // digit width per pass
   int32_t total_tiles;
   int64_t rows, samples;           // row ids and sample indices lie below
+  int64_t width;                   // pooled inputs of a sample
   bool beside;                     // runs beside other work
 };
 struct SortBuffers {

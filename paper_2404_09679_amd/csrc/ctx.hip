@@ -759,7 +759,7 @@ static void fill_sort(antdt_ctx* c, const int32_t* ids, const int32_t* pay0, Sor
   const antdt_model& m = c->m;
   pl.F = m.num_fields; pl.passes = c->sort_passes; pl.radix_bits = c->radix_bits;
   pl.total_tiles = c->atotal_tiles;
-  pl.rows = m.rows_per_field; pl.samples = c->B; pl.beside = beside;
+  pl.rows = m.rows_per_field; pl.samples = c->B; pl.width = c->FD; pl.beside = beside;
   sb.ids = ids;
   sb.key[0] = c->key[0]; sb.key[1] = c->key[1]; sb.pay[0] = c->pay[0]; sb.pay[1] = c->pay[1];
   sb.hist = c->hist;

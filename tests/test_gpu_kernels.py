@@ -169,18 +169,28 @@ def test_sort_ahead_of_the_gather(how, bag):
     check_iteration(cfg, cfg.shard_sizes, tol=TOL32, batched=True, **kw)   # (from zero accumulators: smaller steps than above)
 
 
-# From two million lookups of a batched step the sort goes by buckets: rows cut where a sample of the lookups says.  Fields of many
+# Large batches are sorted by buckets: rows cut where a sample of the lookups says.  From two million lookups of a batched step on if the passes
+# are three (1.1 M rows) or the pooled inputs many (500 100 samples), else from 3.5 million, and of up to 2^18 rows from eight million; not
+# where ranges that leave room for the sample in a word are too many (1.1 M rows, 500 100 samples).  Fields of many
 # lookups, none, one and a few; ids spread evenly, by frequency, in the first rows, in one, in some that are neighbours, at both ends, past a
 # multiple of 2^16 rows; buckets larger than a block holds (64 of them for 900 000 lookups of 1500 rows).  The sorted lookups are those
 # of a stable sort, one for one.
 # From eight million on the sort also works the samples out of the bags' boundaries: bags of one, empty ones, one of all.
+KINDS = ["even", "zipf", "first-rows", "one-row", "neighbours", "ends", "past-65536"]
+
+
 @pytest.mark.parametrize("rows", [1500, 70_001, 1_100_000])
-@pytest.mark.parametrize("kind", ["even", "zipf", "first-rows", "one-row", "neighbours", "ends", "past-65536", "even-8M", "zipf-8M"])
-def test_sort_by_buckets(kind, rows):
+@pytest.mark.parametrize("kind,B", [(k, 3001) for k in KINDS + ["even-8M", "zipf-8M"]] + [(k, 500_100) for k in KINDS + ["even-8M"]] +
+                         [("even-8M", 65_536), ("even-8M", 65_537), ("ends-8M", 65_537), ("one-row-8M", 3001), ("first-rows-8M", 3001), ("past-65536-8M", 3001)])
+def test_sort_by_buckets(kind, B, rows):
     import torch
     import paper_2404_09679_amd as A
-    dev, B = "cuda:0", 3001
-    kind, longest = (kind[:-3], 7_000_000) if kind.endswith("-8M") else (kind, 900_000)
+    dev = "cuda:0"
+    many = kind.endswith("-8M")
+    kind, longest = (kind[:-3], 7_000_000) if many else (kind, 900_000)
+    buckets = many or (B == 3001 and rows == 1_100_000) or B == 500_100
+    if B == 500_100 and rows == 1_100_000:
+        buckets = False
     sizes = [longest, 0, 700_001, 1, 8193, 500_000]
     cfg = _config(f"buckets-{kind}", 640, num_fields=len(sizes), rows_per_field=rows, dim=4, layer_sizes=(8,), gemm_dtype="f32", num_dense=0,
                   shard_sizes=(2000, B - 2000), max_bag=400)
@@ -235,8 +245,12 @@ def test_sort_by_buckets(kind, rows):
             assert torch.equal(so.long()[1:], torch.cumsum(counts, 0)) and int(so[0]) == 0, (f, "runs")
             assert torch.equal(ss.long(), sample[f][on][order]), (f, "samples")
 
+    scan = A.kernel_names().index("sort_scan")
+    ctx.profile(2, scan)
     ctx.worker_step_all(loss)
     ctx.aggregate()
+    assert ctx.profile_read(scan)[0] == (1 if buckets else 3 if rows == 1_100_000 else 2)
+    ctx.profile(0)
     check(B)
     # what follows a batched step finds the samples it left out: a shard stepped anew, a shard left out
     ctx.worker_step_all(loss)
@@ -251,12 +265,12 @@ def test_sort_by_buckets(kind, rows):
 # Bags of one length in a batch of a multiple of 1024 samples: evenly spaced lookups are then all at one place of their bags, and where the ids have
 # an order in the bag, rows cut by those alone make ranges of most of the lookups, a block's work each.  The sort takes about as long
 # as that of the same ids in random order (several times as long, were most in one range), and gives the same.
-@pytest.mark.parametrize("B,bag,rows", [(16_384, 50, 50_000), (8192, 100, 1_100_000)])
+@pytest.mark.parametrize("B,bag,rows", [(16_384, 50, 50_000), (8192, 100, 1_100_000)])   # (more fields where fewer rows ask for more lookups)
 @pytest.mark.parametrize("order", ["ascending", "first", "padded"])
 def test_sort_by_buckets_of_bags_of_one_length(order, B, bag, rows):
     import torch
     import paper_2404_09679_amd as A
-    dev, F = "cuda:0", 3
+    dev, F = "cuda:0", 3 if rows > 1 << 20 else 10
     cfg = _config(f"bags-{bag}", 642, num_fields=F, rows_per_field=rows, dim=4, layer_sizes=(8,), gemm_dtype="f32", num_dense=0, shard_sizes=(B,), max_bag=bag)
     g = torch.Generator(device=dev).manual_seed(bag)
     even = torch.randint(0, rows, (F, B, bag), generator=g, device=dev).int()
@@ -265,7 +279,7 @@ def test_sort_by_buckets_of_bags_of_one_length(order, B, bag, rows):
     mixed = torch.stack([t.flatten()[torch.randperm(B * bag, generator=g, device=dev)] for t in ids]).flatten().contiguous()
     offsets = (torch.arange(B + 1, dtype=torch.int32, device=dev) * bag).repeat(F, 1).contiguous()
     tables = torch.randn((F * rows, 4), generator=g, device=dev) * 0.05
-    params = torch.randn(sum(i * o + o for i, o in zip((12, 8), (8, 1))), generator=g, device=dev) * 0.3
+    params = torch.randn(sum(i * o + o for i, o in zip((4 * F, 8), (8, 1))), generator=g, device=dev) * 0.3
     ctx = A.Context(A.model_from_config(cfg, max_batch=B, max_nnz=F * B * bag, max_shards=1))
     ctx.bind(tables, torch.ones_like(tables), params, torch.ones_like(params))
     labels, loss = (torch.rand(B, generator=g, device=dev) < 0.25).float(), torch.zeros(1, device=dev)
