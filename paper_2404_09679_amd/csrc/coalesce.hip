@@ -727,11 +727,6 @@ __global__ __launch_bounds__(BUCKET_THREADS) void sort_buckets_kernel(const int3
   sort_bucket(lds, bp, reinterpret_cast<const uint32_t*>(in) + at, keys_out + at, pay_out + at, n, row0, rows);
 }
 
-__global__ __launch_bounds__(256) void sort_pass_kernel(SortPass sp) {
-  __shared__ SortPassLds<256> lds;
-  sort_pass_field<256>(sp, blockIdx.x, lds);
-}
-
 // Block = field.
 template <int IT>
 __global__ __launch_bounds__(SMALL_THREADS) void sort_small_kernel(const int32_t* keys_in, const int32_t* pay_in, int32_t* keys_out,
@@ -1615,11 +1610,6 @@ void plan_sort_pass(const SortPlan& pl, const SortBuffers& sb, const FieldPtr& f
   sp.pay_out = sb.pay[pass & 1];
   sp.F = pl.F; sp.shift = pass * pl.radix_bits; sp.rb = pl.radix_bits;
   sp.fp = fp;
-}
-hipError_t launch_sort_pass_alone(const SortPass& sp, Profiler* prof, hipStream_t s) {
-  ProfScope ps(prof, KID_SORT_SCATTER, s);
-  hipLaunchKernelGGL(sort_pass_kernel, dim3(sp.F), dim3(256), 0, s, sp);
-  return hipGetLastError();
 }
 bool sort_finds_samples(const SortPlan& pl, const SortBuffers& sb, const FieldPtr& fp) {
   BucketPlan bp = {};

@@ -162,9 +162,9 @@ struct GemmArgs {
   int32_t loss_blocks;
   const struct LossJob* loss;   // [loss_blocks]
 };
-hipError_t launch_gemm(const GemmArgs& a, hipStream_t s);
 struct SortPass;   // sort.h
-hipError_t launch_gemm_and_sort(const GemmArgs& a, const SortPass* sp, bool* took, hipStream_t s);   // with a pass of the sort, if it takes one
+bool gemm_takes_sort(const GemmArgs& a);   // the launch has room for a pass of the sort
+hipError_t launch_gemm(const GemmArgs& a, const SortPass* sp, hipStream_t s);   // sp: a pass of the sort for such a launch, or NULL
 
 // Sample ranges (shards; neighbours of equal weight merged) in sample order, with their aggregation
 // weights, and the partial sums that the loss kernel left for them.
@@ -291,9 +291,8 @@ __device__ __forceinline__ void add_up_losses(const LossJob* job) {   // (the fi
 }
 
 // ------------------------------------------------------------- coalesce.hip
-// Pass `pass` of a sort whose fields fit sort_pass_field, for a launch of something else to take; by itself.
+// Pass `pass` of a sort whose fields fit sort_pass_field, for a launch of something else to take.
 void plan_sort_pass(const SortPlan& pl, const SortBuffers& sb, const FieldPtr& fp, int pass, SortPass& sp);
-hipError_t launch_sort_pass_alone(const SortPass& sp, Profiler* prof, hipStream_t s);
 // Whether launch_sort can do without sample indices, and work them out of the bags' boundaries (of a whole batch).
 bool sort_finds_samples(const SortPlan& pl, const SortBuffers& sb, const FieldPtr& fp);
 // Sorts every field's lookups by row id (stable); the result is in key / pay [*sorted_buf].

@@ -1023,33 +1023,7 @@ static int worker_range(antdt_ctx* c, int k0, int k1, float* loss_out, hipStream
   auto weight = [&](int l) -> const void* {
     return c->act_bf16 ? (const void*)c->wb[l] : (const void*)(c->params + c->w_off[l]);
   };
-  // All shards of a bf16 model whose sort goes to no other stream, no field longer than a block takes in a pass: the passes run beside the products,
-  // one in a launch (behind / beside them, a step, us: 1024-512-256, 26 fields of 670 / 1000 / 2000 / 3200 / 3800 lookups 75.4 / 69.7, 72.8 / 67.6,
-  // 84.6 / 81.0, 90.1 / 87.5, 91.3 / 90.8, three passes of 1000 79.1 / 73.7; ten fields of 4100 91.1 / 90.8; 256-128, 26 of 1600 70.5 / 68.0;
-  // 1024-512, 30 of 3000 90.0 / 87.8).
-  const bool passes_join = c->act_bf16 && c->batched && !beside && c->total_tiles > 0 && c->joined_sort_used &&
-                           L > 1 && ns > 0 && passes_fit(m.num_fields, c->fp) && !prof_apart(pr, KID_GEMM_FWD, KID_SORT_SCATTER) &&
-                           !prof_apart(pr, KID_GEMM_BWD, KID_SORT_SCATTER);
-  SortPlan sort_plan;
-  SortBuffers sort_buffers;
-  SortPass sort_pass;
-  int sort_next = 0;   // pass
-  if (passes_join) {
-    coalesce_whole_batch(c);
-    fill_sort(c, c->ids, c->lookup_sample, sort_plan, sort_buffers);
-    plan_sort_pass(sort_plan, sort_buffers, c->fp, 0, sort_pass);
-  }
-  auto product = [&](const GemmArgs& g) {
-    const bool sorts = passes_join && sort_next < c->sort_passes;
-    bool took = false;
-    const hipError_t e = launch_gemm_and_sort(g, sorts ? &sort_pass : nullptr, &took, s);
-    if (took && ++sort_next < c->sort_passes) plan_sort_pass(sort_plan, sort_buffers, c->fp, sort_next, sort_pass);
-    return e;
-  };
-  // the matrix products of each pass are timed as one bracket when they run back to back
-  ProfScope fwd_scope(L > 1 ? pr : nullptr, KID_GEMM_FWD, s);
-  fwd_scope.launches(L - 1);
-  for (int l = 0; l + 1 < L; ++l) {  // hidden layers
+  auto forward = [&](int l) {   // hidden layer l + 1
     GemmArgs g;
     memset(&g, 0, sizeof(g));
     g.A = act(l) + s0 * ld(l) * es; g.lda = ld(l);
@@ -1064,8 +1038,83 @@ static int worker_range(antdt_ctx* c, int k0, int k1, float* loss_out, hipStream
       g.B = c->params + c->w_off[l]; g.ldb = c->width[l + 1]; g.b_kc = 0;
     }
     g.epi = EPI_BIAS_RELU; g.bf16_in = c->act_bf16; g.bf16_out = c->act_bf16;
-    HIP_TRY(c, product(g));
+    return g;
+  };
+  auto backward = [&](int l) {   // gradient w.r.t. act_l: through W_l, then the ReLU of layer l-1 (none for the input)
+    GemmArgs g;
+    memset(&g, 0, sizeof(g));
+    g.A = c->dh[l + 1] + s0 * c->width[l + 1] * es; g.lda = c->width[l + 1];
+    g.B = weight(l); g.ldb = c->width[l + 1]; g.b_kc = 1;
+    g.M = (int32_t)ns; g.K = c->width[l + 1];
+    g.bf16_in = c->act_bf16;
+    if (l > 0) {
+      g.C = c->dh[l] + s0 * c->width[l] * es; g.ldc = c->width[l]; g.N = c->width[l];
+      g.mask = c->h[l] + s0 * c->width[l] * es; g.ldmask = c->width[l];
+      g.epi = EPI_RELU_MASK; g.bf16_out = c->act_bf16;
+    } else {
+      g.C = c->dx + s0 * c->FD; g.ldc = c->FD; g.N = c->FD;
+      g.epi = EPI_PLAIN; g.bf16_out = 0;
+      if (loss_out) {
+        g.loss = c->loss_job + k0;
+        g.loss_blocks = k1 - k0;
+      }
+    }
+    return g;
+  };
+  // Backward.  The data-gradient chain dH_{l+1} -> dH_l first; nothing needs the weight gradients before the dense
+  // update.  With bf16 products they are not computed here at all, unless the caller asked for them or the
+  // library may have no streams of its own: apply_update forms them inside the dense update (aggregated over
+  // the shards in registers, never written per shard), and this step only records when their operands are
+  // complete; the per-shard gradients of the contract are computed when a view asks for them.  Otherwise
+  // (fp32 models: they are small) one launch behind the chain: beside the input gradient on another stream it would
+  // hide less than the hop costs (one worker's step on 64 / 1531 samples: 87 / 109 us that way, 54 / 78 here).
+  bool defer = !c->eager_wgrad;
+  for (int k = 0; k < tab.K; ++k)   // (also when another shard's step of this iteration did: apply_update goes one way for all)
+    defer = defer || ((k < k0 || k >= k1) && c->stepped[k] && c->wgrad_deferred);
+  const bool deferred = defer && c->act_bf16 && c->wside && !c->static_bound;
+  // All shards of an fp32 model whose sort goes to no other stream: it runs beside the weight gradients
+  const bool sort = !deferred && c->batched && !beside && c->total_tiles > 0 && c->joined_sort_used && sort_joins(c);
+  // The gradient of the pooled input, which only the aggregation reads, shares the launch of weight gradients that are formed here, where
+  // that takes it (and nobody times the two classes apart).
+  bool joins = false;
+  if (L > 1 && !deferred && !prof_apart(pr, KID_GEMM_BWD, KID_GEMM_WGRAD)) {
+    WgradArgs u;
+    fill_wgrad_args(c, u);
+    joins = wgrad_takes_dgrad(u, k1 - k0, backward(0), m.num_fields, sort ? &c->fp : nullptr);
   }
+  // All shards of a bf16 model whose sort goes to no other stream, no field longer than a block takes in a pass: the passes run beside the products,
+  // one in a launch (behind / beside them, a step, us: 1024-512-256, 26 fields of 670 / 1000 / 2000 / 3200 / 3800 lookups 75.4 / 69.7, 72.8 / 67.6,
+  // 84.6 / 81.0, 90.1 / 87.5, 91.3 / 90.8, three passes of 1000 79.1 / 73.7; ten fields of 4100 91.1 / 90.8; 256-128, 26 of 1600 70.5 / 68.0;
+  // 1024-512, 30 of 3000 90.0 / 87.8).  Where as many products have room for one: large tiles have none, and a pass in a launch of its own takes
+  // longer than all of them in one block a field (in one block / by pass: 1024, 24 fields of 64 columns, 4095 samples 134 / 149, three passes 138 / 161; 256, 20
+  // of 2000 samples, three passes and two products 80 / 87).
+  bool passes_join = c->act_bf16 && c->batched && !beside && c->total_tiles > 0 && c->joined_sort_used &&
+                     L > 1 && ns > 0 && passes_fit(m.num_fields, c->fp) && !prof_apart(pr, KID_GEMM_FWD, KID_SORT_SCATTER) &&
+                     !prof_apart(pr, KID_GEMM_BWD, KID_SORT_SCATTER);
+  if (passes_join) {
+    int room = 0;
+    for (int l = 0; l + 1 < L; ++l) room += gemm_takes_sort(forward(l)) + ((l > 0 || !joins) && gemm_takes_sort(backward(l)));
+    passes_join = room >= c->sort_passes;
+  }
+  SortPlan sort_plan;
+  SortBuffers sort_buffers;
+  SortPass sort_pass;
+  int sort_next = 0;   // pass
+  if (passes_join) {
+    coalesce_whole_batch(c);
+    fill_sort(c, c->ids, c->lookup_sample, sort_plan, sort_buffers);
+    plan_sort_pass(sort_plan, sort_buffers, c->fp, 0, sort_pass);
+  }
+  auto product = [&](const GemmArgs& g) {
+    const bool sorts = passes_join && sort_next < c->sort_passes && gemm_takes_sort(g);
+    const hipError_t e = launch_gemm(g, sorts ? &sort_pass : nullptr, s);
+    if (sorts && ++sort_next < c->sort_passes) plan_sort_pass(sort_plan, sort_buffers, c->fp, sort_next, sort_pass);
+    return e;
+  };
+  // the matrix products of each pass are timed as one bracket when they run back to back
+  ProfScope fwd_scope(L > 1 ? pr : nullptr, KID_GEMM_FWD, s);
+  fwd_scope.launches(L - 1);
+  for (int l = 0; l + 1 < L; ++l) HIP_TRY(c, product(forward(l)));
   fwd_scope.close();
   {
     HeadArgs a;
@@ -1089,17 +1138,6 @@ static int worker_range(antdt_ctx* c, int k0, int k1, float* loss_out, hipStream
     HIP_TRY(c, launch_head_tiles(a, tab, s));
     if (L == 1 && loss_out && ns > 0) HIP_TRY(c, launch_losses(c->loss_job + k0, k1 - k0, s));   // (else beside the input gradient)
   }
-  // Backward.  The data-gradient chain dH_{l+1} -> dH_l first; nothing needs the weight gradients before the dense
-  // update.  With bf16 products they are not computed here at all, unless the caller asked for them or the
-  // library may have no streams of its own: apply_update forms them inside the dense update (aggregated over
-  // the shards in registers, never written per shard), and this step only records when their operands are
-  // complete; the per-shard gradients of the contract are computed when a view asks for them.  Otherwise
-  // (fp32 models: they are small) one launch behind the chain: beside the input gradient on another stream it would
-  // hide less than the hop costs (one worker's step on 64 / 1531 samples: 87 / 109 us that way, 54 / 78 here).
-  bool defer = !c->eager_wgrad;
-  for (int k = 0; k < tab.K; ++k)   // (also when another shard's step of this iteration did: apply_update goes one way for all)
-    defer = defer || ((k < k0 || k >= k1) && c->stepped[k] && c->wgrad_deferred);
-  const bool deferred = defer && c->act_bf16 && c->wside && !c->static_bound;
   c->wgrad_deferred = deferred;
   c->shard_grads_done = false;
   // The event behind the last operand of the weight gradients (with up to one hidden layer the loss kernel
@@ -1116,49 +1154,14 @@ static int worker_range(antdt_ctx* c, int k0, int k1, float* loss_out, hipStream
   }
   c->operands_captured = capturing;
   if (deferred && L <= 2) HIP_TRY(c, hipEventRecord(c->ev_dh[0], s));
-  // All shards of an fp32 model whose sort goes to no other stream: it runs beside the weight gradients
-  const bool sort = !deferred && c->batched && !beside && c->total_tiles > 0 && c->joined_sort_used && sort_joins(c);
-  // The gradient of the pooled input, which only the aggregation reads, shares the launch of weight gradients that are formed here, where
-  // that takes it (and nobody times the two classes apart).
-  GemmArgs joined;
-  bool joins = false;
-  const bool apart = deferred || prof_apart(pr, KID_GEMM_BWD, KID_GEMM_WGRAD);
   ProfScope bwd_scope(L > 1 ? pr : nullptr, KID_GEMM_BWD, s);
   bwd_scope.launches(L - 1);
-  for (int l = L - 2; l >= 0; --l) {   // gradient w.r.t. act_l: through W_l, then the ReLU of layer l-1 (none for the input)
-    GemmArgs g;
-    memset(&g, 0, sizeof(g));
-    g.A = c->dh[l + 1] + s0 * c->width[l + 1] * es; g.lda = c->width[l + 1];
-    g.B = weight(l); g.ldb = c->width[l + 1]; g.b_kc = 1;
-    g.M = (int32_t)ns; g.K = c->width[l + 1];
-    g.bf16_in = c->act_bf16;
-    if (l > 0) {
-      g.C = c->dh[l] + s0 * c->width[l] * es; g.ldc = c->width[l]; g.N = c->width[l];
-      g.mask = c->h[l] + s0 * c->width[l] * es; g.ldmask = c->width[l];
-      g.epi = EPI_RELU_MASK; g.bf16_out = c->act_bf16;
-    } else {
-      g.C = c->dx + s0 * c->FD; g.ldc = c->FD; g.N = c->FD;
-      g.epi = EPI_PLAIN; g.bf16_out = 0;
-      if (loss_out) {
-        g.loss = c->loss_job + k0;
-        g.loss_blocks = k1 - k0;
-      }
-    }
-    if (l == 0 && !apart) {
-      WgradArgs u;
-      fill_wgrad_args(c, u);
-      joined = g;
-      joins = wgrad_takes_dgrad(u, k1 - k0, g, m.num_fields, sort ? &c->fp : nullptr);
-    }
-    if (!joins) HIP_TRY(c, product(g));
+  for (int l = L - 2; l >= 0; --l) {
+    if (l > 0 || !joins) HIP_TRY(c, product(backward(l)));
     if (l == 1 && deferred) HIP_TRY(c, hipEventRecord(c->ev_dh[0], s));
   }
   bwd_scope.close();
   if (passes_join) {
-    for (; sort_next < c->sort_passes; ++sort_next) {   // (no launch took it)
-      plan_sort_pass(sort_plan, sort_buffers, c->fp, sort_next, sort_pass);
-      HIP_TRY(c, launch_sort_pass_alone(sort_pass, pr, s));
-    }
     c->sorted_buf = (c->sort_passes - 1) & 1;
     c->joined_sort_used = false;
     for (int k = 0; k < tab.K; ++k) c->included[k] = true;
@@ -1172,7 +1175,8 @@ static int worker_range(antdt_ctx* c, int k0, int k1, float* loss_out, hipStream
       set_weights(c);
       coalesce_whole_batch(c);
     }
-    const int rc = shard_weight_gradients(c, k0, k1, s, sort, joins ? &joined : nullptr);
+    const GemmArgs dgrad = joins ? backward(0) : GemmArgs{};
+    const int rc = shard_weight_gradients(c, k0, k1, s, sort, joins ? &dgrad : nullptr);
     if (rc) return rc;
     c->presorted = c->presorted || sort;
   }

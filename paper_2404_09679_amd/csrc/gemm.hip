@@ -668,12 +668,13 @@ hipError_t launch_bf16_or_sort(const GemmArgs& a, const SortPass* sp, hipStream_
   return hipGetLastError();
 }
 
-// sp: a pass of the sort for the same launch (or NULL); *took: the launch has it (large tiles, and small ones of one wavefront, don't take it).
-template <bool BS>
-hipError_t launch_bf16_sized(const GemmArgs& a, const SortPass* sp, bool* took, hipStream_t s) {
+// Tiles of a product of bf16 operands.
+enum Bf16Tiles { TILES_FAR, TILES_256, TILES_128, TILES_128_DEEP, TILES_64, TILES_32_X_64, TILES_32, TILES_32_LOADERS };
+Bf16Tiles bf16_tiles(const GemmArgs& a) {
   // A tile holds up to 256 rows of an operand (128 contraction slots of a strided one); its pieces are addressed by 32-bit
   // offsets where those reach.
-  if (std::max(a.lda, a.ldb) * (256 * 2) >> 32) return launch_bf16<1, 1, 1, 1, 128, 3, BS, true>(a, s);
+  if (std::max(a.lda, a.ldb) * (256 * 2) >> 32) return TILES_FAR;
+  const bool strided = !a.b_kc;   // (BS)
   auto blocks = [&](int bm, int bn) { return (int64_t)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
   // The largest tile that gives most of the 256 compute units a block wins (it reads the fewest operand bytes); below that
   // blocks that all find a place at once do, with few of them those that get their loads away fastest.  Measured (us; M x N x K):
@@ -690,19 +691,33 @@ hipError_t launch_bf16_sized(const GemmArgs& a, const SortPass* sp, bool* took, 
   // worker's: 3000 samples of 3840-1024-512 222 -> 240 us, 166 -> 173; 9800 of 845-1024-512-256 287 -> 295, 210 -> 218): 1 .. 8 %
   // slower but for five, of 3.8 M lookups in tables of half a million rows and more, where the tiles wait for compute
   // units that the weight gradients hold (2501 samples of 3840-1024-512 392 -> 380).
-  if (blocks(256, 256) >= 150) return launch_bf16<4, 2, 2, 4, 64, 2, BS>(a, s);
-  if (blocks(128, 128) > 256) return launch_bf16<2, 1, 2, 4, 64, 2, BS>(a, s);
-  if (blocks(128, 128) >= (BS ? 150 : 200)) return launch_bf16<2, 1, 2, 4, 64, 3, BS>(a, s);
-  *took = sp != nullptr;
-  if (blocks(32, 32) <= 256) return launch_bf16_or_sort<1, 1, 1, 1, 128, 3, BS, 4>(a, sp, s);
-  if constexpr (BS) {
-    if (blocks(32, 64) <= 256) return launch_bf16_or_sort<1, 1, 1, 2, 128, 3, BS, 8>(a, sp, s);
+  if (blocks(256, 256) >= 150) return TILES_256;
+  if (blocks(128, 128) > 256) return TILES_128;
+  if (blocks(128, 128) >= (strided ? 150 : 200)) return TILES_128_DEEP;
+  if (blocks(32, 32) <= 256) return TILES_32_LOADERS;
+  if (strided && blocks(32, 64) <= 256) return TILES_32_X_64;
+  if (!strided && blocks(32, 32) <= 768) return TILES_32;
+  return TILES_64;
+}
+
+// sp: a pass of the sort for the same launch, or NULL (see gemm_takes_sort).
+template <bool BS>
+hipError_t launch_bf16_sized(const GemmArgs& a, const SortPass* sp, hipStream_t s) {
+  switch (bf16_tiles(a)) {
+    case TILES_FAR: return launch_bf16<1, 1, 1, 1, 128, 3, BS, true>(a, s);
+    case TILES_256: return launch_bf16<4, 2, 2, 4, 64, 2, BS>(a, s);
+    case TILES_128: return launch_bf16<2, 1, 2, 4, 64, 2, BS>(a, s);
+    case TILES_128_DEEP: return launch_bf16<2, 1, 2, 4, 64, 3, BS>(a, s);
+    case TILES_64: return launch_bf16_or_sort<1, 1, 2, 2, 64, 3, BS, 4>(a, sp, s);
+    case TILES_32_LOADERS: return launch_bf16_or_sort<1, 1, 1, 1, 128, 3, BS, 4>(a, sp, s);
+    case TILES_32_X_64:
+      if constexpr (BS) return launch_bf16_or_sort<1, 1, 1, 2, 128, 3, BS, 8>(a, sp, s);
+      break;
+    case TILES_32:
+      if constexpr (!BS) return launch_bf16<1, 1, 1, 1, 128, 3, BS>(a, s);
+      break;
   }
-  if (!BS && blocks(32, 32) <= 768) {
-    *took = false;
-    return launch_bf16<1, 1, 1, 1, 128, 3, BS>(a, s);
-  }
-  return launch_bf16_or_sort<1, 1, 2, 2, 64, 3, BS, 4>(a, sp, s);
+  return hipErrorInvalidValue;
 }
 
 bool f32_aligned(const void* x, int64_t ld) { return (ld & 3) == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0; }
@@ -860,15 +875,16 @@ hipError_t launch_wgrad_dgrad_tile(const WgradArgs& a, const KSegments& seg, con
 
 }  // namespace
 
-hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
-  bool took;
-  return launch_gemm_and_sort(a, nullptr, &took, s);
+bool gemm_takes_sort(const GemmArgs& a) {   // (large tiles, and small ones of one wavefront, don't)
+  if (a.M <= 0 || a.N <= 0 || !a.bf16_in) return false;
+  const Bf16Tiles tiles = bf16_tiles(a);
+  return tiles == TILES_64 || tiles == TILES_32_X_64 || tiles == TILES_32_LOADERS;
 }
-hipError_t launch_gemm_and_sort(const GemmArgs& a, const SortPass* sp, bool* took, hipStream_t s) {
-  *took = false;
+hipError_t launch_gemm(const GemmArgs& a, const SortPass* sp, hipStream_t s) {
+  if (sp && !gemm_takes_sort(a)) return hipErrorInvalidValue;
   if (a.M <= 0 || a.N <= 0) return hipSuccess;
   if (!a.bf16_in) return launch_f32(a, s);
-  return a.b_kc ? launch_bf16_sized<false>(a, sp, took, s) : launch_bf16_sized<true>(a, sp, took, s);
+  return a.b_kc ? launch_bf16_sized<false>(a, sp, s) : launch_bf16_sized<true>(a, sp, s);
 }
 
 hipError_t launch_wgrad(const WgradArgs& a, const KSegments& seg, bool store, hipStream_t s) {
@@ -913,7 +929,7 @@ bool wgrad_takes_dgrad(const WgradArgs& a, int ranges, const GemmArgs& g, int F,
   if (ranges <= 0 || g.M <= 0 || g.N <= 0 || !g.b_kc) return false;
   if (a.bf16) {
     if (!g.bf16_in || sorted || wgrad_far(a) || wgrad_large_tiles(a, ranges) || std::max(g.lda, g.ldb) * (256 * 2) >> 32) return false;
-    return (int64_t)((g.M + 127) / 128) * ((g.N + 127) / 128) < 200;   // (see launch_bf16_sized: else tiles of other blocks)
+    return (int64_t)((g.M + 127) / 128) * ((g.N + 127) / 128) < 200;   // (see bf16_tiles: else tiles of other blocks)
   }
   if (g.bf16_in || g.K < 4) return false;
   const bool wide = f32_wide(g), wgrad_wide = wgrad_f32_wide(a, ranges);

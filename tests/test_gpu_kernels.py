@@ -100,7 +100,7 @@ def test_sort_variants(most, rows, monkeypatch):
 
 
 # bf16 models of a batched step: a pass of the sort in each of the first products' launches (tiles of 32 by four wavefronts, of 32 x 64 by eight and
-# of 64), up to 4096 lookups of a field; one pass, two, and three where two launches are all there are.
+# of 64), up to 4096 lookups of a field; one pass, two, and three where two launches are all there are (the aggregation then sorts).
 @pytest.mark.parametrize("most", [1, 64, 257, 1025, 2048, 4096, 4097])
 @pytest.mark.parametrize("rows,hidden", [(900, (40,)), (70_000, (520, 264)), (70_000, (1032, 8)), (1_100_000, (264,))])
 def test_sort_beside_bf16_products(most, rows, hidden, monkeypatch):
@@ -112,6 +112,41 @@ def test_sort_beside_bf16_products(most, rows, hidden, monkeypatch):
     ids = [rng.integers(0, rows, n) // rng.integers(1, 9, n) for n in sizes[:F]]
     _plant(monkeypatch, ids, B, lambda f, n: np.concatenate([[0], np.sort(rng.integers(0, n + 1, B - 1)), [n]]))
     check_iteration(cfg, cfg.shard_sizes, tol=TOLBF, bf16_gemm_oracle=True, batched=True, nonzero_state=True)
+
+
+# Where a batched step of a bf16 model has its sort's passes beside the products: if as many of them have room for one.  Tiles of 128 have none, two
+# products too few for three passes, and an input gradient in the launch of the weight gradients is no launch of its own; the aggregation then
+# sorts, in one launch.
+@pytest.mark.parametrize("fields,dim,samples,hidden,rows,eager,joins", [(26, 32, 96, (1024, 512, 256), 1_200_000, False, True), (24, 64, 4095, (1024,), 50_000, False, False),
+                                                                       (24, 64, 4095, (1024, 64), 50_000, False, False), (24, 64, 4095, (1024, 64, 64), 50_000, False, True), (20, 64, 2000, (256,), 50_000, False, True),
+                                                                       (20, 64, 2000, (256,), 1_200_000, False, False), (26, 32, 300, (256,), 50_000, True, False),
+                                                                       (26, 32, 300, (256,), 900, True, True)])
+def test_where_a_bf16_step_sorts(fields, dim, samples, hidden, rows, eager, joins):
+    import torch
+    import paper_2404_09679_amd as A
+    dev = "cuda:0"
+    cfg = _config(f"where-{samples}", 643, num_fields=fields, rows_per_field=rows, dim=dim, layer_sizes=hidden, num_dense=0, shard_sizes=(samples,), max_bag=1)
+    g = torch.Generator(device=dev).manual_seed(samples)
+    ids = torch.randint(0, rows, (fields, samples), generator=g, device=dev).int()
+    tables = torch.zeros((fields * rows, dim), device=dev)
+    params = torch.zeros(sum(i * o + o for i, o in zip(cfg.layer_sizes, cfg.layer_sizes[1:])), device=dev)
+    ctx = A.Context(A.model_from_config(cfg, max_batch=samples, max_nnz=fields * samples, max_shards=1))
+    ctx.set_eager_weight_gradients(eager)
+    ctx.bind(tables, torch.ones_like(tables), params, torch.ones_like(params))
+    ctx.set_batch(ids.flatten(), [f * samples for f in range(fields + 1)], torch.arange(samples + 1, dtype=torch.int32, device=dev).repeat(fields, 1), None,
+                  torch.zeros(samples, device=dev))
+    ctx.assign_shard(samples, 1)
+    scatter = A.kernel_names().index("sort_scatter")
+    ctx.worker_step_all(torch.zeros(1, device=dev))
+    ctx.profile(2, scatter)
+    ctx.aggregate()
+    assert ctx.profile_read(scatter)[0] == (0 if joins else 1)
+    ctx.profile(0)
+    for f in range(fields):
+        u, so, ss, _ = ctx.view_coalesced(f)
+        key, order = torch.sort(ids[f], stable=True)
+        rows_f, counts = torch.unique_consecutive(key, return_counts=True)
+        assert torch.equal(u, rows_f) and torch.equal(so.long()[1:], torch.cumsum(counts, 0)) and torch.equal(ss.long(), order)
 
 
 # The sort over many blocks (one field of more than 16384 lookups, ten tiles and a bit) with the other fields at the tile
