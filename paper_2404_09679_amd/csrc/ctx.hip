@@ -177,6 +177,7 @@ struct antdt_ctx {
   bool joined_sort_used = true;
   bool slots_apart = false;       // the loss kernel's sums and jobs end before the windows' slots (see carve)
   bool samples_missing = false;   // a batched step left the lookups' sample indices to its sort, which needs none (see sample_indices)
+  bool replays_leave_samples = false;   // a capture has recorded such a step
   bool presorted = false;     // the coalescing structure of the current batch and split is built (or being built)
   bool side_pending = false;  // work is in flight on the side stream that no other stream has waited for yet
   // bound by antdt_bind_static: the workspace is the library's static device buffer and every
@@ -515,6 +516,7 @@ int antdt_bind(antdt_ctx* c, void* tables, float* table_state, float* mlp_params
   c->pstate = mlp_state;
   carve(c, (char*)workspace);
   c->captured = false;
+  c->replays_leave_samples = false;
   memset(c->grads_viewed, 0, sizeof(c->grads_viewed));
   if (!c->side) {
     HIP_TRY(c, hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking));
@@ -582,6 +584,7 @@ int antdt_bind_static(antdt_ctx* c, void* tables, float* table_state, float* mlp
   c->pstate = mlp_state;
   carve(c, (char*)base);
   c->captured = false;
+  c->replays_leave_samples = false;
   memset(c->grads_viewed, 0, sizeof(c->grads_viewed));
   c->stage = ST_BOUND;
   c->have_shards = false;
@@ -793,11 +796,13 @@ static bool sort_beside_finds_samples(antdt_ctx* c) {
   return sort_finds_samples(pl, sb, c->afp);
 }
 
-// The sample index of every lookup, where the last batched step left none.
+// The sample index of every lookup, where the last batched step may have left none: also if that was a replay (of other bags perhaps), or will be,
+// when this capture is replayed.  What is captured here has not run.
 static int sample_indices(antdt_ctx* c, hipStream_t s) {
-  if (!c->samples_missing) return ANTDT_OK;
+  const bool capturing = note_capture(c, s), leaves = capturing && c->fp.p[c->m.num_fields] >= FINDS_MIN;
+  if (!c->samples_missing && !c->replays_leave_samples && !leaves) return ANTDT_OK;
   HIP_TRY(c, launch_expand_samples(c->offsets, c->lookup_sample, c->fp, c->m.num_fields, (int)c->B, s));
-  c->samples_missing = false;
+  c->samples_missing = c->samples_missing && capturing;
   return ANTDT_OK;
 }
 
@@ -988,6 +993,7 @@ static int worker_range(antdt_ctx* c, int k0, int k1, float* loss_out, hipStream
   c->presorted = false;
   c->batched = k0 == 0 && k1 == tab.K;
   c->left_out = false;
+  const bool capturing = note_capture(c, s);
   const bool beside = c->batched && side_stream(c);
   const bool finds = beside && sort_beside_finds_samples(c), early = beside && c->fp.p[m.num_fields] >= EARLY_MIN;
   if (early) HIP_TRY(c, hipEventRecord(c->ev_fork, s));
@@ -1003,6 +1009,7 @@ static int worker_range(antdt_ctx* c, int k0, int k1, float* loss_out, hipStream
     HIP_TRY(c, launch_pool(a, c->fp, s));
   }
   if (c->batched) c->samples_missing = finds;
+  c->replays_leave_samples = c->replays_leave_samples || (finds && capturing);
   if (beside) {
     // All shards in one pass: the sort of the coming aggregate depends on the batch alone, so it runs beside the MLP
     // and, of large batches, beside the gather too (see EARLY_MIN).
@@ -1142,7 +1149,6 @@ static int worker_range(antdt_ctx* c, int k0, int k1, float* loss_out, hipStream
   c->shard_grads_done = false;
   // The event behind the last operand of the weight gradients (with up to one hidden layer the loss kernel
   // writes it, else the data gradient of layer 1).
-  const bool capturing = note_capture(c, s);
   if (deferred) {
     // Steps of other shards since the last update on another stream: the library's stream waits for their operands before
     // the event stands for this step's (in a capture on one stream the caller's own order is all there is).

@@ -269,3 +269,60 @@ def test_steps_whose_sort_nobody_uses():
         assert sorts(run) == launches, i
         if not use:   # (of a shard that was left out the steps by worker form no loss)
             assert_same(weights(run), weights(ref), f"iteration {i}")
+
+
+@pytest.mark.parametrize("graph_of", ["step", "aggregation", "aggregation behind another"])
+def test_samples_of_a_large_batch_behind_a_graph(graph_of):
+    """A step of more than eight million lookups leaves their sample indices to its sort; an aggregation that sorts anew finds them all the same, also if the
+    step is a replay on other bags of the same number of lookups, or if what wrote them is a graph that has not run."""
+    import paper_2404_09679_amd as A
+    dev, F, rows, B, n = "cuda:0", 3, 5000, 4000, 2_800_000
+    cfg = wl.scaled(SMALL_BF, name="order-samples", num_fields=F, rows_per_field=rows, dim=8, num_dense=0, layer_sizes=(24, 16, 1), shard_sizes=(2500, B - 2500))
+    g = torch.Generator(device=dev).manual_seed(3)
+    ids = torch.empty(F * n, dtype=torch.int32, device=dev)
+    offsets = torch.zeros((F, B + 1), dtype=torch.int32, device=dev)
+
+    def draw():
+        ids.copy_(torch.randint(0, rows, (F * n,), generator=g, device=dev))
+        offsets[:, 1:B] = torch.sort(torch.randint(0, n + 1, (F, B - 1), generator=g, device=dev))[0].int()
+        offsets[:, B] = n
+
+    draw()
+    tables = torch.randn((F * rows, 8), generator=g, device=dev) * 0.05
+    params = torch.randn(24 * 16 + 16 + 17, generator=g, device=dev) * 0.3
+    ctx = A.Context(A.model_from_config(cfg, max_batch=B, max_nnz=F * n, max_shards=2))
+    ctx.bind(tables, torch.ones_like(tables), params, torch.ones_like(params))
+    ctx.set_batch(ids, [f * n for f in range(F + 1)], offsets, None, torch.zeros(B, device=dev))
+    ctx.assign_shard(B, 2, sizes=cfg.shard_sizes)
+    loss = torch.zeros(2, device=dev)
+
+    def check(mask, below):
+        if mask != "replayed":
+            ctx.aggregate(mask)
+        for f in range(F):
+            sample = torch.repeat_interleave(torch.arange(B, device=dev), (offsets[f, 1:] - offsets[f, :-1]).long())
+            key, order = torch.sort(ids[f * n:(f + 1) * n][sample < below], stable=True)
+            u, so, ss, _ = ctx.view_coalesced(f)
+            assert torch.equal(u, torch.unique_consecutive(key)) and torch.equal(ss.long(), sample[sample < below][order]), f
+
+    ctx.worker_step_all(loss)
+    check(None, B)
+    if graph_of == "aggregation behind another":   # (the indices are there when the graph is made, and not when it is replayed)
+        check([1, 0], 2500)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        if graph_of == "step":
+            ctx.worker_step_all(loss)
+        ctx.aggregate()
+    if graph_of != "step":
+        check([1, 0], 2500)
+    for _ in range(3):
+        draw()
+        if graph_of != "step":
+            ctx.worker_step_all(loss)
+            ctx.aggregate()
+        graph.replay()
+        check("replayed", B)
+        check([1, 0], 2500)
+        check(None, B)
