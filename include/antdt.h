@@ -452,7 +452,12 @@ int antdt_view_coalesced(antdt_ctx* ctx, int32_t f, const int32_t** unique_ids,
  * Optional per-kernel timing with HIP events on the launch stream.  mode 0: off;
  * mode 1: every kernel class; mode 2: only the class `kernel_id`; mode 3: the classes whose bit
  * is set in `kernel_id` read as a mask (bit i = class i).  The matrix products of a pass that
- * are launched back to back share one pair of events.  Timings accumulate until
+ * are launched back to back share one pair of events.  Some launches do the work of two classes
+ * (the gradient of the pooled input and the weight gradients, passes of a small sort and the
+ * products, an fp32 model's two updates); while one of the two is timed they are made apart, so
+ * that its time is that of its own work in a step of a few launches more, not a share of the
+ * launch that an untimed step has.  (An fp32 model's sort in the launch of its weight gradients
+ * is timed with those.)  Timings accumulate until
  * antdt_profile_read, which synchronises the recorded events and reports, per class, the
  * number of launches and their total duration in milliseconds, then resets.
  * antdt_kernel_name returns the class name (NULL past the last class).
