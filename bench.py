@@ -84,19 +84,22 @@ def _bytes_and_flops(cfg, stats, model):
     L = len(s) - 1
     fwd = sum(2 * B * s[l] * s[l + 1] for l in range(L - 1))
     dgrad = sum(2 * B * s[l + 1] * (s[l] if l > 0 else F * D) for l in range(L - 1))
-    passes = model["sort_passes"]
-    # (large batches: one pass by ranges of rows, low bits and sample in a word, the rest of the sort in LDS)
-    by_ranges = passes > 1 and nnz >= 2_000_000 and cfg.rows_per_field <= 128 << 16
+    # The way of the sort, as its launches say: a scan of counts per pass over the whole batch, none where a field is one block's work.  By ranges
+    # of rows there is one pass for several digits: ids in, low bits and sample out as a word, and once more in and out as a pair.
+    scans, passes = model["sort_scans"], model["sort_passes"]
+    by_ranges = scans == 1 and passes > 1
+    sort_scatter = 20 if by_ranges else 12 + 16 * max(scans - 1, 0)
     gemm = "mfma" if cfg.gemm_dtype == "bf16" else "alu"
     out = {
-        # ids, offsets, every distinct row once, pooled inputs and the sample index of every lookup for the sort
-        "pool": ("hbm", 4 * nnz + 4 * F * (B + 1) + U * D * e + B * ldx * es + 4 * nnz),
+        # ids, offsets, every distinct row once, pooled inputs (the samples of the lookups follow from the offsets: not counted here where they
+        # are written down for the sort, nor there where they are read)
+        "pool": ("hbm", 4 * nnz + 4 * F * (B + 1) + U * D * e + B * ldx * es),
         "gemm_fwd": (gemm, fwd),
         "gemm_bwd": (gemm, dgrad),           # the data-gradient chain on the launch stream
         "gemm_wgrad": (gemm, fwd),
         "wgrad_adagrad": (gemm, fwd),    # weight gradients with the aggregation and dense Adagrad in the epilogue
-        "sort_hist": ("hbm", (1 if by_ranges else passes) * 4 * nnz),
-        "sort_scatter": ("hbm", (8 + 4 + 4 + 8) * nnz if by_ranges else 4 * nnz + 8 * nnz + (passes - 1) * 16 * nnz),
+        "sort_hist": ("hbm", scans * 4 * nnz),
+        "sort_scatter": ("hbm", sort_scatter * nnz),
         "seg_heads": ("hbm", 4 * nnz),
         "seg_emit": ("hbm", 4 * nnz + 8 * U),
         # one fused kernel: segmented sum of the per-lookup gradient rows + row-sparse Adagrad
@@ -193,7 +196,7 @@ def run_ranking(args, cfg_id):
     bits = max(1, int(np.ceil(np.log2(R))))
     stats = dict(B=B, K=K, nnz=float(np.mean([b.field_ptr[-1] for b in batches])),
                  U=float(np.mean([sum(len(np.unique(b.field_ids(f))) for f in range(F)) for b in batches])))
-    table = _bytes_and_flops(cfg, stats, dict(sort_passes=(bits + 9) // 10))
+    table = _bytes_and_flops(cfg, stats, dict(sort_passes=(bits + 9) // 10, sort_scans=int(per_class.get("sort_scan", (0, 0.0))[0])))
     # candidates for the reported roofline: classes on the launch stream that have a byte (or flop) count
     critical = {k: v for k, v in per_class.items() if k not in side and table.get(k, ("", 0.0))[1] > 0}
     if not critical:
