@@ -34,16 +34,16 @@ MEASURED_TRAFFIC = {
         "pool": (68.6e6, "embed.hip"),
         "sparse_adagrad": (191.0e6, "coalesce.hip"), "seg_reduce_long": (5.2e6, "coalesce.hip"),
     },
-    "cfg3": {"sparse_adagrad": (644.4e6, "coalesce.hip"), "gemm_wgrad": (529.6e6, "gemm.hip"),
+    "cfg3": {"sparse_adagrad": (644.7e6, "coalesce.hip"), "gemm_wgrad": (530.5e6, "gemm.hip"),
              "pool": (183.1e6, "embed.hip")},
     "cfg4": {"sparse_adagrad": (4819.5e6, "coalesce.hip"), "wgrad_adagrad": (2046.9e6, "gemm.hip"),
-             "pool": (1215.0e6, "embed.hip")},
+             "pool": (1214.8e6, "embed.hip")},
     "cfg5": {"adam": (15032.4e6, "optim.hip")},
-    "sha1": {"gemm.hip": "55f47a5c440398e5ff9fd703a451f9d48d942fe1",
+    "sha1": {"gemm.hip": "ecb4a30a0a309c404ddccbca0d20e40db6b6751d",
              "embed.hip": "6ff0ac548f03601688028bebb6dbfca2517950ef",
-             "coalesce.hip": "238271cd62f4400997f7b652a14e75878e5df24d",
+             "coalesce.hip": "d0a5ef9c7adb28081b4bffb93f47a19838c52308",
              "optim.hip": "e5d81db53e4298eb8c02b8d53232d5a3b543017c",
-             "ctx.hip": "3071525697a3cfe265e12933310324cc71c08a74"},
+             "ctx.hip": "32ce49b24cdc4e656b37ebf77d69132b3dae0d83"},
 }
 
 
